@@ -262,3 +262,77 @@ def run(s):
         if op == "gin":
             out["eps"] = grads["eps"]
     return out
+
+
+def exact(case, seed):
+    """The outputs, the loss and the pushed tables in 64 bits, with plain torch: Algorithm 1's forward pass over the batch
+    from the same inputs.  Gradients and updated weights have no such value that two correct passes are near to: a hidden
+    unit within rounding of its threshold takes its whole gradient with it (see `tolerance`)."""
+    c, s = case, prepare(case, seed)
+    bg, op, L, nb = s["bg"], c["op"], c["layers"], s["bg"].nb
+    deg_rows = (bg.rowptr[1:] - bg.rowptr[:-1]).long()
+    row = torch.repeat_interleave(torch.arange(nb, device=s["x"].device), deg_rows)
+    col, n_id = bg.col.long(), bg.n_id.long()
+    tables = s["tables"].double()
+
+    def adjacency(val):
+        return torch.sparse_csr_tensor(bg.rowptr.long(), col, val, size=(nb, bg.nv))
+
+    def norm():
+        # 1 / sqrt((deg v + 1) (deg w + 1)), degrees of the whole graph; prepare's pattern carries the self-loops
+        deg = _graph(c, seed, s["x"].device).deg.double().to(s["x"].device) + 1.0
+        q = deg[n_id].rsqrt()
+        return q[row] * q[col]
+
+    x = s["x"][n_id].double()
+    if op in ("gcn", "gcnii"):
+        a = adjacency(norm())
+    elif op == "gin":
+        a = adjacency(torch.ones_like(col, dtype=torch.float64))
+    if op == "gcnii":
+        h0 = x = torch.relu(x @ s["model"].w_in.double())
+    for l in range(1, L + 1):
+        w = s["weights"][l - 1]
+        w = [m.double() for m in w] if isinstance(w, tuple) else w.double()
+        if op == "gcn":
+            y = (a @ x) @ w
+        elif op == "gin":
+            y = torch.relu((a @ x + x[:nb]) @ w[0]) @ w[1]
+        elif op == "gcnii":
+            beta = math.log(0.5 / l + 1.0)
+            z = (1.0 - ALPHA) * (a @ x) + ALPHA * h0[:nb]
+            y = (1.0 - beta) * z + beta * (z @ w)
+        elif op == "pna":
+            f, f1 = x.shape[1], w[0].shape[1]
+            p = x @ w[0][f:]
+            own = deg_rows.clamp(min=1)[:, None]
+            index = row[:, None].expand(-1, f1)
+            zero = torch.zeros(nb, f1, dtype=torch.float64, device=x.device)
+            agg = [torch.zeros_like(zero).index_add_(0, row, p[col]) / own,
+                   torch.zeros_like(zero).scatter_reduce_(0, index, p[col], "amin", include_self=False),
+                   torch.zeros_like(zero).scatter_reduce_(0, index, p[col], "amax", include_self=False)]
+            some = (deg_rows > 0)[:, None]
+            agg = [torch.where(some, t + x[:nb] @ w[0][:f], zero) for t in agg]
+            scale = torch.log(deg_rows.double() + 1.0)[:, None] / s["delta"]
+            blocks = agg + [scale * t for t in agg] + [torch.where(some, t / scale, zero) for t in agg]
+            y = torch.cat([x[:nb]] + blocks, 1) @ w[1]
+        else:
+            p, fh = x @ w[0], w[0].shape[1] // c["heads"]
+            y = torch.zeros(nb, w[0].shape[1], dtype=torch.float64, device=x.device)
+            for h in range(c["heads"]):
+                k = slice(h * fh, (h + 1) * fh)
+                score = torch.nn.functional.leaky_relu((p[:nb, k] @ w[1][k])[row] + (p[:, k] @ w[2][k])[col], 0.2)
+                top = torch.full((nb,), -math.inf, dtype=torch.float64, device=x.device)
+                e = torch.exp(score - top.scatter_reduce_(0, row, score, "amax")[row])
+                total = torch.zeros(nb, dtype=torch.float64, device=x.device).index_add_(0, row, e)
+                y[:, k] = adjacency(e / total[row]) @ p[:, k].contiguous()
+        if l < L:
+            y = torch.relu(y)
+            tables[l - 1, n_id[:nb]] = y
+            x = torch.cat([y, tables[l - 1, n_id[nb:]]])
+    out = {"y": y, "tables": tables}
+    if c["mode"] == TRAIN:
+        known = s["labels"] >= 0
+        loss = torch.logsumexp(y, 1) - y.gather(1, s["labels"].clamp(min=0).long()[:, None])[:, 0]
+        out.update(loss=loss[known].sum()[None], grads=None, weights=None)
+    return out
