@@ -4,7 +4,7 @@
 //
 // This is the only dense contraction of the step (the W of the paper's GCN,
 // GCNII and GIN operator equations), so it is the only place MFMA is used.
-// fp32 data uses v_mfma_f32_32x32x2_f32, bf16 data v_mfma_f32_32x32x16_bf16
+// fp32 data uses the bf16 instruction on operands split in three (split.h), bf16 data v_mfma_f32_32x32x16_bf16
 // with fp32 accumulation.
 //
 // Tiling: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN tile of Y, each
@@ -23,13 +23,11 @@
 #include <type_traits>
 
 #include "common.h"
+#include "split.h"
 #include <mutex>
 
 namespace gas {
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 
 struct LinArgs {
     const char* Z;   int64_t ldz;      // elements
@@ -185,80 +183,83 @@ __device__ __forceinline__ void mfma_tile_f32(const float* A, int lda, int arow0
     }
 }
 
-template <int BM, int BN, bool VEC, bool TRANS>
-__global__ __launch_bounds__(256) void linear_f32_kernel(LinArgs a) {
-    constexpr int TM = BM / 64, TN = BN / 64;
-    __shared__ __attribute__((aligned(16))) float As[BM][kLdA];
-    __shared__ __attribute__((aligned(16))) float Bs[kBK][BN + 4];
-    const float* Z = reinterpret_cast<const float*>(a.Z);
-    const float* W = reinterpret_cast<const float*>(a.W);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN;
-    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
-    f32x16 acc[TM][TN];
-    zero_acc(acc);
-    ATileF32<BM, VEC> ta;
-    BTileF32<BN, VEC> tb;
-    constexpr bool tr = TRANS;           // compile-time: the plain path keeps its straight-line staging
-    ta.fetch(Z, a.ldz, a.M, a.K, m0, 0, tid);
-    tb.fetch(W, a.K, a.N, 0, n0, tid, tr);
-    for (int k0 = 0; k0 < a.K; k0 += kBK) {
-        __syncthreads();                 // everyone is done reading the previous tile
-        ta.stage(As, tid);
-        tb.stage(Bs, tid, tr);
-        __syncthreads();
-        if (k0 + kBK < a.K) {
-            ta.fetch(Z, a.ldz, a.M, a.K, m0, k0 + kBK, tid);
-            tb.fetch(W, a.K, a.N, k0 + kBK, n0, tid, tr);
-        }
-        mfma_tile_f32<TM, TN, BN>(&As[0][0], kLdA, wm0, 0, Bs, wn0, li, lh, acc);
-    }
-    // Epilogue: one output row at a time (register r of tile i), its address formed once; the optional terms
-    // (identity, mask, push) are decided once per kernel, not once per element.
-    float* Y = reinterpret_cast<float*>(a.Y);
+// The wavefront's 32 x 32 blocks of the output, at row m0 and column n0.  WHOLE: they lie inside the output and the
+// strides are below 2^26, so a row's address is a scalar base and one 32-bit lane offset; else every element is checked.
+// (With the checks and 64-bit addresses everywhere this took 4 us per 128 x 128 tile, a sixth of the tile's time.)
+template <int TM, int TN, bool WHOLE, bool EXTRA, bool PUSH>
+__device__ __forceinline__ void store_rows(const LinArgs& a, int64_t m0, int n0, int li, int lh, const f32x16 (&acc)[TM][TN]) {
     const float* bias = reinterpret_cast<const float*>(a.bias);
-    const float* mask = reinterpret_cast<const float*>(a.mask);
-    float* PH = reinterpret_cast<float*>(a.push_hist);
-    const int nl = n0 + wn0 + li;                      // column of tile j = nl + 32 j
     float bv[TN];
 #pragma unroll
-    for (int j = 0; j < TN; ++j) bv[j] = (bias && nl + 32 * j < a.N) ? bias[nl + 32 * j] : 0.f;
-    auto rows = [&](auto cid_tag, auto mask_tag, auto push_tag) {
-        constexpr bool CID = decltype(cid_tag)::value, MASK = decltype(mask_tag)::value, PUSH = decltype(push_tag)::value;
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t m = m0 + wm0 + 32 * i + 8 * (r / 4) + 4 * lh + (r % 4);
-                if (m >= a.M) continue;
-                float* yrow = Y + m * a.ldy + nl;
-                const float* zrow = CID ? Z + m * a.ldz + nl : nullptr;
-                const float* krow = MASK ? mask + m * a.ldmask + nl : nullptr;
-                float* hrow = PUSH ? PH + (int64_t)a.push_idx[m] * a.ld_push + nl : nullptr;
-#pragma unroll
-                for (int j = 0; j < TN; ++j) {
-                    if (nl + 32 * j >= a.N) continue;
-                    float y = a.c_w * acc[i][j][r] + bv[j];
-                    if constexpr (CID) y += a.c_id * zrow[32 * j];
-                    if (a.relu) y = fmaxf(y, 0.f);
-                    if constexpr (MASK) { if (!(krow[32 * j] > 0.f)) y = 0.f; }
-                    yrow[32 * j] = y;
-                    if constexpr (PUSH) hrow[32 * j] = y;      // Push in the epilogue
-                }
-            }
+    for (int j = 0; j < TN; ++j) bv[j] = bias && (WHOLE || n0 + 32 * j + li < a.N) ? bias[n0 + 32 * j + li] : 0.f;
+    auto at = [&](const char* X, int64_t ld, int64_t row) {       // element (row + 4 lh, n0 + li)
+        if constexpr (WHOLE)
+            return reinterpret_cast<float*>(const_cast<char*>(X) + (row * ld + n0) * 4 + (uint32_t)((4 * lh * (int)ld + li) * 4));
+        else
+            return reinterpret_cast<float*>(const_cast<char*>(X) + ((row + 4 * lh) * ld + n0 + li) * 4);
     };
-    using T = std::true_type;
-    using F = std::false_type;
-    const bool cid = a.c_id != 0.f;
-    if (!cid && !mask && !a.push_idx) rows(F{}, F{}, F{});
-    else if (!cid && !mask) rows(F{}, F{}, T{});
-    else if (cid && !mask && !a.push_idx) rows(T{}, F{}, F{});
-    else if (cid && !mask) rows(T{}, F{}, T{});
-    else if (!cid && !a.push_idx) rows(F{}, T{}, F{});
-    else if (!a.push_idx) rows(T{}, T{}, F{});
-    else if (!cid) rows(F{}, T{}, T{});
-    else rows(T{}, T{}, T{});
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            const int64_t row = m0 + 32 * i + 8 * (r / 4) + r % 4;
+            if (!WHOLE && row + 4 * lh >= a.M) continue;
+            float* yrow = at(a.Y, a.ldy, row);
+            const float* zrow = EXTRA && a.c_id != 0.f ? at(a.Z, a.ldz, row) : nullptr;
+            const float* krow = EXTRA && a.mask ? at(a.mask, a.ldmask, row) : nullptr;
+            float* hrow = nullptr;
+            if constexpr (PUSH)
+                hrow = reinterpret_cast<float*>(a.push_hist) + n0 + li +
+                       (WHOLE ? (uint64_t)(uint32_t)a.push_idx[row + 4 * lh] * (uint32_t)a.ld_push
+                              : (uint64_t)((int64_t)a.push_idx[row + 4 * lh] * a.ld_push));
+#pragma unroll
+            for (int j = 0; j < TN; ++j) {
+                if (!WHOLE && n0 + 32 * j + li >= a.N) continue;
+                float y = a.c_w * acc[i][j][r] + bv[j];
+                if (EXTRA && a.c_id != 0.f) y += a.c_id * zrow[32 * j];
+                if (a.relu) y = fmaxf(y, 0.f);
+                if (EXTRA && a.mask && !(krow[32 * j] > 0.f)) y = 0.f;
+                yrow[32 * j] = y;
+                if constexpr (PUSH) hrow[32 * j] = y;             // Push in the epilogue
+            }
+        }
+}
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile(const LinArgs& a, int64_t m0, int n0, int li, int lh, const f32x16 (&acc)[TM][TN]) {
+    constexpr int64_t kNear = 1 << 26;
+    const bool whole = m0 + 32 * TM <= a.M && n0 + 32 * TN <= a.N && a.ldy < kNear && a.ldz < kNear && a.ldmask < kNear &&
+                       a.ld_push < kNear;
+    const bool extra = a.c_id != 0.f || a.mask;
+    if (whole && !extra && !a.push_idx) store_rows<TM, TN, true, false, false>(a, m0, n0, li, lh, acc);
+    else if (whole && !extra) store_rows<TM, TN, true, false, true>(a, m0, n0, li, lh, acc);
+    else if (whole && !a.push_idx) store_rows<TM, TN, true, true, false>(a, m0, n0, li, lh, acc);
+    else if (!a.push_idx) store_rows<TM, TN, false, true, false>(a, m0, n0, li, lh, acc);
+    else store_rows<TM, TN, false, true, true>(a, m0, n0, li, lh, acc);
+}
+
+// Y tile of BM x BN by 2 x 2 wavefronts, operands split into bf16 parts on their way into LDS (split.h).  The column
+// tiles of one row tile follow each other on one XCD (workgroups are dealt to the eight XCDs in turn): the second
+// reads the rows of Z from that L2.
+template <int BM, int BN, int KS, bool TRANS, int WPS>
+__global__ __launch_bounds__(256, WPS) void linear_split_kernel(LinArgs a) {
+    using G = SplitGemm<BM, BN, 2, 2, KS, true, TRANS>;
+    constexpr int TM = G::TM, TN = G::TN;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const float* Z = reinterpret_cast<const float*>(a.Z);
+    const float* W = reinterpret_cast<const float*>(a.W);
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned gn = (a.N + BN - 1) / BN, of_xcd = blockIdx.x / 8;
+    const int64_t m0 = ((int64_t)(of_xcd / gn) * 8 + blockIdx.x % 8) * BM;
+    if (m0 >= a.M) return;                             // the grid is padded to a multiple of eight row tiles
+    const int n0 = (int)(of_xcd % gn) * BN;
+    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    const int64_t ldw = TRANS ? a.K : a.N;
+    G g;
+    f32x16 acc[TM][TN];
+    if (!g.run(Z, a.ldz, m0, a.M, W, ldw, n0, a.N, 0, a.K, reinterpret_cast<uint16_t*>(smem), wm0, wn0, acc))
+        plain_tile<TM, TN, true, TRANS>(Z, a.ldz, m0 + wm0, a.M, W, ldw, n0 + wn0, a.N, 0, a.K, acc);
+    store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
 // fp32 fused MLP: 32 rows per workgroup; wavefront w owns hidden / output
@@ -1161,75 +1162,33 @@ struct DwArgs {
     int slab;                       // rows per slab
 };
 
-// fp32: both operands are read as single dwords from row-major LDS tiles (lanes run along the feature index).
-template <bool VEC>
-__global__ __launch_bounds__(256) void dw_f32_kernel(DwArgs a) {
-    constexpr int BM = 32;                                  // rows per step
-    __shared__ __attribute__((aligned(16))) float Zs[BM][kDwTile + 4];
-    __shared__ __attribute__((aligned(16))) float Gs[BM][kDwTile + 4];
-    const float* Z = reinterpret_cast<const float*>(a.Z);
-    const float* G = reinterpret_cast<const float*>(a.G);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-    const int slab = blockIdx.x, k0 = blockIdx.y * kDwTile, n0 = blockIdx.z * kDwTile;
+// fp32: both operands split into bf16 parts (split.h), eight consecutive rows of one feature per LDS piece.  The tiles
+// of one slab follow each other on one XCD: they read the same rows.
+constexpr int kDwSplitKS = 2;
+__global__ __launch_bounds__(256, 2) void dw_split_kernel(DwArgs a) {
+    using S = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const unsigned tn = (a.N + kDwTile - 1) / kDwTile, tiles = (a.K + kDwTile - 1) / kDwTile * tn;
+    const unsigned of_xcd = blockIdx.x / 8, tile = of_xcd % tiles;
+    const int slab = (int)(of_xcd / tiles * 8 + blockIdx.x % 8);
+    if (slab >= a.n_slabs) return;                     // the grid is padded to a multiple of eight slabs
+    const int k0 = (int)(tile / tn) * kDwTile, n0 = (int)(tile % tn) * kDwTile;
     const int64_t m_begin = (int64_t)slab * a.slab;
     const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
     const int wk0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
-    f32x16 acc[2][2];
-    zero_acc(acc);
-    f32x4 rz[4], rg[4];
-    auto fetch = [&](int64_t m0) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {                       // 32 x 128 floats = 1024 float4 per operand
-            const int idx = tid + 256 * i;
-            const int64_t m = m0 + idx / 32;
-            const int c = 4 * (idx % 32);
-            f32x4 vz = {0.f, 0.f, 0.f, 0.f}, vg = {0.f, 0.f, 0.f, 0.f};
-            if (m < m_end) {
-                if constexpr (VEC) {
-                    if (k0 + c < a.K) vz = *reinterpret_cast<const f32x4*>(Z + m * a.ldz + k0 + c);
-                    if (n0 + c < a.N) vg = *reinterpret_cast<const f32x4*>(G + m * a.ldg + n0 + c);
-                } else {
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        if (k0 + c + e < a.K) vz[e] = Z[m * a.ldz + k0 + c + e];
-                        if (n0 + c + e < a.N) vg[e] = G[m * a.ldg + n0 + c + e];
-                    }
-                }
-            }
-            rz[i] = vz;
-            rg[i] = vg;
-        }
-    };
-    fetch(m_begin);
-    for (int64_t m0 = m_begin; m0 < m_end; m0 += BM) {
-        __syncthreads();
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int idx = tid + 256 * i;
-            *reinterpret_cast<f32x4*>(&Zs[idx / 32][4 * (idx % 32)]) = rz[i];
-            *reinterpret_cast<f32x4*>(&Gs[idx / 32][4 * (idx % 32)]) = rg[i];
-        }
-        __syncthreads();
-        if (m0 + BM < m_end) fetch(m0 + BM);
-#pragma unroll
-        for (int mm = 0; mm < BM; mm += 2) {                // one MFMA step covers rows mm (lanes 0-31) and mm+1
-            float fa[2], fb[2];
-#pragma unroll
-            for (int i = 0; i < 2; ++i) fa[i] = Zs[mm + lh][wk0 + 32 * i + li];
-#pragma unroll
-            for (int j = 0; j < 2; ++j) fb[j] = Gs[mm + lh][wn0 + 32 * j + li];
-#pragma unroll
-            for (int i = 0; i < 2; ++i)
-#pragma unroll
-                for (int j = 0; j < 2; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
-        }
-    }
+    const float* Z = reinterpret_cast<const float*>(a.Z);
+    const float* G = reinterpret_cast<const float*>(a.G);
+    S g;
+    f32x16 acc[S::TM][S::TN];
+    if (!g.run(Z, a.ldz, k0, a.K, G, a.ldg, n0, a.N, m_begin, m_end, reinterpret_cast<uint16_t*>(smem), wk0, wn0, acc))
+        plain_tile<S::TM, S::TN, false, false>(Z, a.ldz, k0 + wk0, a.K, G, a.ldg, n0 + wn0, a.N, m_begin, m_end, acc);
     float* out = a.partial + (int64_t)slab * a.K * a.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < S::TM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < S::TN; ++j) {
             const int n = n0 + wn0 + 32 * j + li;
             if (n >= a.N) continue;
 #pragma unroll
@@ -1445,19 +1404,15 @@ __global__ __launch_bounds__(256) void relu_bwd_kernel(const char* GY, int64_t l
 }
 
 // ====================================================================== launchers
-template <int BM, int BN>
-gas_status launch_f32(const LinArgs& a, bool vec, hipStream_t s) {
-    const int64_t gm = (a.M + BM - 1) / BM;
-    const int gn = (a.N + BN - 1) / BN;
-    if (gm > 0x7FFFFFFF || gn > 65535) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
-    dim3 grid((unsigned)gm, (unsigned)gn), block(256);
-    if (a.trans_w) {
-        if (vec) hipLaunchKernelGGL((linear_f32_kernel<BM, BN, true, true>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((linear_f32_kernel<BM, BN, false, true>), grid, block, 0, s, a);
-    } else {
-        if (vec) hipLaunchKernelGGL((linear_f32_kernel<BM, BN, true, false>), grid, block, 0, s, a);
-        else hipLaunchKernelGGL((linear_f32_kernel<BM, BN, false, false>), grid, block, 0, s, a);
-    }
+template <int BM, int BN, int KS, int WPS>
+gas_status launch_split(const LinArgs& a, hipStream_t s) {
+    constexpr int smem = SplitGemm<BM, BN, 2, 2, KS, true, true>::kLdsBytes;
+    static_assert(smem <= 65536, "no attribute needed");
+    const int64_t gm = ((a.M + BM - 1) / BM + 7) / 8 * 8, gn = (a.N + BN - 1) / BN;
+    if (gm * gn > 0x7FFFFFFF) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
+    const dim3 grid((unsigned)(gm * gn)), block(256);
+    if (a.trans_w) hipLaunchKernelGGL((linear_split_kernel<BM, BN, KS, true, WPS>), grid, block, smem, s, a);
+    else hipLaunchKernelGGL((linear_split_kernel<BM, BN, KS, false, WPS>), grid, block, smem, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
@@ -1518,13 +1473,13 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     a.c_id = c_identity; a.c_w = c_weight; a.relu = relu;
     a.trans_w = trans_w; a.mask = static_cast<const char*>(mask); a.ldmask = ldmask;
     if (dt == GAS_F32) {
-        const bool vec = aligned16(Z) && aligned16(W) && ldz % 4 == 0 && F_in % 4 == 0 && F_out % 4 == 0;
         a.push_idx = push.idx; a.push_hist = static_cast<char*>(push.hist); a.ld_push = push.ld_hist;
-        // a small batch in 128-row tiles would leave most compute units without a workgroup: 64 x 64 tiles then
-        // (the same products in the same order, so the same bits)
-        const int64_t tiles128 = ((n_rows + 127) / 128) * ((F_out + (F_out <= 64 ? 63 : 127)) / (F_out <= 64 ? 64 : 128));
-        if (tiles128 < 512) return launch_f32<64, 64>(a, vec, s);
-        return F_out <= 64 ? launch_f32<128, 64>(a, vec, s) : launch_f32<128, 128>(a, vec, s);
+        // The largest tile that still gives most compute units a workgroup: a larger one splits each value for more
+        // products.  50,000 x 256 x 256: 54 us in 128 x 128 tiles; 4,000 x 256 x 256: 11 us in 64 x 64 tiles.
+        const int64_t tiles = (n_rows + 127) / 128;
+        if (F_out > 64 && tiles * ((F_out + 127) / 128) >= 192) return launch_split<128, 128, 2, 2>(a, s);
+        if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);
+        return launch_split<64, 64, 2, 4>(a, s);
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
     if (!vec) {
@@ -1631,9 +1586,11 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
     GAS_REQUIRE(tk <= 65535 && tn <= 65535, "gas_linear_bwd_weight: widths too large");
     dim3 grid((unsigned)n_slabs, tk, tn);
     if (dt == GAS_F32) {
-        const bool vec = aligned16(Z) && aligned16(GP) && ldz % 4 == 0 && ldgp % 4 == 0;
-        if (vec) hipLaunchKernelGGL(dw_f32_kernel<true>, grid, dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(dw_f32_kernel<false>, grid, dim3(256), 0, s, a);
+        constexpr int smem = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
+        static_assert(smem <= 65536, "no attribute needed");
+        const int64_t blocks = (n_slabs + 7) / 8 * 8 * tk * tn;
+        GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for one launch");
+        hipLaunchKernelGGL(dw_split_kernel, dim3((unsigned)blocks), dim3(256), smem, s, a);
     } else {
         const bool vec = aligned16(Z) && aligned16(GP) && ldz % 8 == 0 && ldgp % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
         if (vec && F_in <= 256 && F_out <= 256 && F_in > 128 && F_out > 128) {

@@ -1,0 +1,285 @@
+// Products of fp32 operands on the bf16 matrix instructions.
+//
+// A float is the sum of three bf16 numbers: x = h + m + l with h the nearest bf16 to x, m the nearest to x - h and l
+// to x - h - m (8 + 8 + 8 significant bits; both differences are exact).  A product is then taken as
+//     a b = ah bh + (ah bm + am bh) + (am bm + ah bl + al bh),
+// six v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the three dropped terms are below 2^-26 of |a b|, a quarter
+// of the fp32 rounding of one product.  Six instructions of 32 cycles do what eight v_mfma_f32_32x32x2_f32 of 64
+// cycles do: 16 k of a 32 x 32 block.
+//
+// ah bh has an accumulator of its own and the five small terms share another, so the large one is rounded once per 16
+// k: the relative error against 64 bits (2-norm, N(0,1) operands) is 9.0e-8 at K = 256 and 1.7e-7 at K = 832, with the
+// fp32 instruction 2.9e-7 and 5.2e-7.  With one accumulator for all six it is 2.5e-7 and 4.5e-7, but the instruction's
+// rounding has a bias that adds up: 2.1e-6 against 8.8e-7 for a weight gradient over 600,000 rows.
+//
+// What bounds it: matrix pipe 52 %, vector instructions of the split 31 % of the cycles by the counters, the clock
+// falls to 1.8 GHz under this load; 50,000 x 256 x 256 take 54 us (91 us with the fp32 instruction), 600,000 rows
+// 534 us (748).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
+// compute unit: 55-63 us; products and split interleaved by hand in one wavefront, two LDS buffers: 49-56 us.
+//
+// What the split cannot represent is found in its result: an infinity, a NaN or a value that rounds to an infinite
+// bf16 makes the accumulator non-finite (0 * inf in the terms beside it, if not itself), and a wavefront that finds
+// one takes its block again with the fp32 instruction (plain_tile), so such inputs give what fp32 arithmetic gives.
+#pragma once
+#include "common.h"
+
+namespace gas {
+namespace {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef f32x4 f32x4_any __attribute__((aligned(4)));      // a 16-byte load at a float's alignment
+
+// x0, x1 -> their three bf16 parts, packed in pairs
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
+    h = pack_bf16(x0, x1);
+    const float r0 = x0 - bf16_lo(h), r1 = x1 - bf16_hi(h);
+    m = pack_bf16(r0, r1);
+    l = pack_bf16(r0 - bf16_lo(m), r1 - bf16_hi(m));
+}
+
+// One operand's tile of a workgroup of T threads: ROWS rows (output rows or columns) x 16 KS values of the reduced
+// index q.  KC: element (r, q) lies at X[r ld + q] (q contiguous), else at X[q ld + r].  A thread holds pieces of
+// eight consecutive q of one row and writes them to LDS as one 16-byte piece per part: [part][row][q], the pieces of a
+// row exchanged so that the 16-byte reads of consecutive rows fall on different banks.
+template <int ROWS, int KS, bool KC, int T>
+struct SplitTile {
+    static constexpr int kQ = 16 * KS, kCh = 2 * KS, kPieces = ROWS * kCh;
+    static constexpr int kPlane = ROWS * kQ;                              // bf16 elements
+    static constexpr int NV = (kPieces + T - 1) / T;
+    static_assert(KS == 1 || KS == 2, "two or four pieces a row");
+    static_assert(KC || (T % ROWS == 0 && ROWS % 64 == 0), "a thread stays with one row, a wavefront with one piece index");
+    const float* p[NV];        // KC: the thread's pieces; else the workgroup's first row, one scalar address for all ...
+    uint32_t off;              // ... and the thread's row from there, in bytes: a load is scalar base + 32-bit offset
+    float v[NV][8];
+    int64_t ld;
+
+    static __device__ __forceinline__ int row_of(int i) {
+        const int idx = threadIdx.x + T * i;
+        return KC ? idx / kCh : idx % ROWS;
+    }
+    static __device__ __forceinline__ int piece_of(int i) {
+        // q contiguous: neighbouring threads take one row's pieces; else a wavefront has one piece index
+        if constexpr (KC) return (threadIdx.x + T * i) % kCh;
+        else return (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 + T * i) / ROWS;
+    }
+    static __device__ __forceinline__ bool holds(int i) { return kPieces % T == 0 || (int)threadIdx.x + T * i < kPieces; }
+    // where piece `piece` of row `row` lies in a plane
+    static __device__ __forceinline__ int at(int row, int piece) {
+        return row * kQ + 8 * (KS == 2 ? (piece ^ ((row >> 1) & 3)) : (piece ^ ((row >> 2) & 1)));
+    }
+
+    // rows r0 .. r_end - 1; rows beyond take the last one's values, which nothing stores
+    __device__ __forceinline__ void init(const float* X, int64_t ld_, int64_t r0, int64_t r_end) {
+        ld = ld_;
+        const int64_t last = r_end - 1 - r0;
+        off = (uint32_t)(row_of(0) < last ? row_of(0) : last) * 4;             // not KC: T is a multiple of ROWS
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+            p[i] = KC ? X + (r0 + (row_of(i) < last ? row_of(i) : last)) * ld + 8 * piece_of(i) : X + r0;
+    }
+    __device__ __forceinline__ void fetch(int64_t q0) {                       // q0 .. q0 + kQ - 1
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (!holds(i)) continue;
+            if constexpr (KC) {
+                const f32x4 a = *reinterpret_cast<const f32x4_any*>(p[i] + q0);
+                const f32x4 b = *reinterpret_cast<const f32x4_any*>(p[i] + q0 + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { v[i][e] = a[e]; v[i][4 + e] = b[e]; }
+            } else {
+                const char* u = reinterpret_cast<const char*>(p[i] + (q0 + 8 * piece_of(i)) * ld);
+#pragma unroll
+                for (int e = 0; e < 8; ++e, u += ld * 4) v[i][e] = *reinterpret_cast<const float*>(u + off);
+            }
+        }
+    }
+    // the same where the step reaches beyond q_end: values from there on repeat the last one until mask() clears them
+    // (after the wait for the loads: a select beside each load would wait for each)
+    __device__ __forceinline__ void fetch_last(int64_t q0, int64_t q_end) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (!holds(i)) continue;
+            const int64_t q = q0 + 8 * piece_of(i);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int64_t k = q + e < q_end ? q + e : q_end - 1;
+                v[i][e] = KC ? p[i][k - 8 * piece_of(i)]
+                             : *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p[i] + k * ld) + off);
+            }
+        }
+    }
+    __device__ __forceinline__ void mask(int left) {             // left: values of the step inside
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[i][e] = 8 * piece_of(i) + e < left ? v[i][e] : 0.f;
+    }
+    __device__ __forceinline__ void stage(uint16_t* planes) const {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            if (!holds(i)) continue;
+            u32x4 h, m, l;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                uint32_t a, b, c;
+                split_pair(v[i][2 * e], v[i][2 * e + 1], a, b, c);
+                h[e] = a; m[e] = b; l[e] = c;
+            }
+            uint16_t* to = planes + at(row_of(i), piece_of(i));
+            *reinterpret_cast<u32x4*>(to) = h;
+            *reinterpret_cast<u32x4*>(to + kPlane) = m;
+            *reinterpret_cast<u32x4*>(to + 2 * kPlane) = l;
+        }
+    }
+};
+
+// A BM x BN tile of sum_q A(r, q) B(c, q), q_begin <= q < q_end (not empty), by WM x WN wavefronts; `lds` holds
+// 3 (BM + BN) 16 KS bf16 elements.  acc: the wavefront's TM x TN blocks of 32 x 32, at rows wm0.. and columns wn0..
+// of the tile.
+template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC>
+struct SplitGemm {
+    static constexpr int T = 64 * WM * WN, TM = BM / 32 / WM, TN = BN / 32 / WN;     // threads, 32 x 32 blocks of a wavefront
+    using TA = SplitTile<BM, KS, AKC, T>;
+    using TB = SplitTile<BN, KS, BKC, T>;
+    static constexpr int kLdsBytes = 3 * (TA::kPlane + TB::kPlane) * 2;
+    TA ta;
+    TB tb;
+
+    static __device__ __forceinline__ void products(const uint16_t* lds, int wm0, int wn0, f32x16 (&acc)[TM][TN],
+                                                    f32x16 (&small)[TM][TN]) {
+        const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+        const uint16_t* B = lds + 3 * TA::kPlane;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) {
+            bf16x8 fa[3][TM], fb[3][TN];
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    fa[part][i] = *reinterpret_cast<const bf16x8*>(lds + part * TA::kPlane + TA::at(wm0 + 32 * i + li, 2 * ks + lh));
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    fb[part][j] = *reinterpret_cast<const bf16x8*>(B + part * TB::kPlane + TB::at(wn0 + 32 * j + li, 2 * ks + lh));
+            }
+            constexpr int PA[6] = {0, 1, 0, 1, 2, 0}, PB[6] = {0, 0, 1, 1, 0, 2};
+#pragma unroll
+            for (int t = 0; t < 6; ++t)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) {
+                        f32x16& c = t == 0 ? acc[i][j] : small[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[PA[t]][i], fb[PB[t]][j], c, 0, 0, 0);
+                    }
+        }
+    }
+
+    // acc = the products; whether all values of the wavefront's blocks are finite (else: plain_tile)
+    __device__ __forceinline__ bool run(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
+                                        int64_t b0, int64_t b_end, int64_t q_begin, int64_t q_end, uint16_t* lds, int wm0,
+                                        int wn0, f32x16 (&acc)[TM][TN]) {
+        ta.init(A, lda, a0, a_end);
+        tb.init(B, ldb, b0, b_end);
+        if (q_begin + TA::kQ <= q_end) {
+            ta.fetch(q_begin);
+            tb.fetch(q_begin);
+        } else {
+            ta.fetch_last(q_begin, q_end);
+            tb.fetch_last(q_begin, q_end);
+        }
+        f32x16 small[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
+        auto stage = [&]() {
+            __syncthreads();                 // everyone is done reading the previous step
+            ta.stage(lds);
+            tb.stage(lds + 3 * TA::kPlane);
+            __syncthreads();
+        };
+        auto multiply = [&]() {
+            __builtin_amdgcn_s_setprio(1);   // the matrix pipe first: the other workgroup splits meanwhile
+            products(lds, wm0, wn0, acc, small);
+            __builtin_amdgcn_s_setprio(0);
+        };
+        int64_t q = q_begin;
+        for (; q + 2 * TA::kQ <= q_end; q += TA::kQ) {
+            stage();
+            ta.fetch(q + TA::kQ);
+            tb.fetch(q + TA::kQ);
+            multiply();
+        }
+        if (q + TA::kQ <= q_end) {           // the last whole step
+            stage();
+            if (q + TA::kQ < q_end) {
+                ta.fetch_last(q + TA::kQ, q_end);
+                tb.fetch_last(q + TA::kQ, q_end);
+            }
+            multiply();
+            q += TA::kQ;
+        }
+        if (q < q_end) {                     // a step that is not whole
+            ta.mask((int)(q_end - q));
+            tb.mask((int)(q_end - q));
+            stage();
+            multiply();
+        }
+        float bad = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    acc[i][j][r] += small[i][j][r];
+                    bad = fmaf(acc[i][j][r], 0.f, bad);      // stays 0 for finite values, else NaN
+                }
+        return !__any(bad != 0.f);
+    }
+};
+
+// The wavefront's block by the fp32 instruction, straight from memory: rows a_r0.. of A and b_r0.. of B (clamped to
+// the last), q0 <= q < q_end.
+template <int TM, int TN, bool AKC, bool BKC>
+__device__ __forceinline__ void plain_tile(const float* A, int64_t lda, int64_t a_r0, int64_t a_end, const float* B,
+                                        int64_t ldb, int64_t b_r0, int64_t b_end, int64_t q0, int64_t q_end,
+                                        f32x16 (&acc)[TM][TN]) {
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll 1
+    for (int64_t q = q0; q < q_end; q += 2) {                // lanes 0-31 take q, lanes 32-63 q + 1
+        const bool in = q + lh < q_end;
+        const int64_t qq = in ? q + lh : q;
+        float fa[TM], fb[TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i) {
+            int64_t r = a_r0 + 32 * i + li;
+            r = r < a_end ? r : a_end - 1;
+            fa[i] = AKC ? A[r * lda + qq] : A[qq * lda + r];
+            fa[i] = in ? fa[i] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            int64_t r = b_r0 + 32 * j + li;
+            r = r < b_end ? r : b_end - 1;
+            fb[j] = BKC ? B[r * ldb + qq] : B[qq * ldb + r];
+            fb[j] = in ? fb[j] : 0.f;
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[i], fb[j], acc[i][j], 0, 0, 0);
+    }
+}
+
+}  // namespace
+}  // namespace gas
