@@ -829,104 +829,147 @@ __global__ __launch_bounds__(256) void gat_bwd_rank_one_kernel(GatBwdArgs a) {
     *reinterpret_cast<u32x4*>(gp) = pack<BF>(g);
 }
 
-// out[f] = sum_i w[i] M[i, f] in a fixed order: slabs of 1024 rows, one partial row per slab, then groups of 256
-// partial rows at a time until one is left.
-constexpr int kSlab = 1024;
-constexpr int kGroup = 256;
+// Two weighted column sums of one matrix in a pass over it (the gradients of the two attention vectors):
+//     out_a[f] = sum_{i < n_a} wa[i] M[i, f]        out_b[f] = sum_{i < n_b} wb[i] M[i, f]        n_a <= n_b
+// Slabs of rows, a partial row of each sum per slab, and the partial rows added in slab order in double: no atomics.
+// HBM-bound once every compute unit has rows to read.  About 1,024 slabs (four workgroups per compute unit), of 64 to
+// 1,024 rows.  95,000 rows of 64 floats, both sums: 8.6 us (two passes with slabs of 1,024 rows, a row per wavefront
+// and one thread per column in the reduction: 112 us).
+struct ColSums {
+    const char* M; int64_t ldm;
+    const float *wa, *wb;
+    int64_t n_a, n_b;
+    int F;
+    int slab;
+    int64_t n_slabs;
+    float* partial;                  // [n_slabs][2][F]
+    float *out_a, *out_b;
+};
+int colsum_slab(int64_t n) {
+    const int64_t rows = ((n + 1023) / 1024 + 63) / 64 * 64;
+    return (int)(rows < 64 ? 64 : (rows > 1024 ? 1024 : rows));
+}
+int64_t colsum_scratch_floats(int64_t n, int F) {
+    const int64_t slab = colsum_slab(n);
+    return (n + slab - 1) / slab * 2 * (int64_t)F;
+}
+// any width and alignment: a thread per column
 template <bool BF>
-__global__ __launch_bounds__(256) void wcolsum_partial_kernel(const char* M, int64_t ldm, const float* w, int64_t n, int F,
-                                                              float* partial) {
-    const int64_t r0 = (int64_t)blockIdx.x * kSlab, r1 = min(n, r0 + kSlab);
-    for (int f = threadIdx.x; f < F; f += 256) {
-        float acc = 0.f;
-        for (int64_t i = r0; i < r1; ++i) acc = fmaf(w[i], ld<BF>(M, i * ldm + f), acc);
-        partial[(int64_t)blockIdx.x * F + f] = acc;
+__global__ __launch_bounds__(256) void colsum_partial_kernel(ColSums a) {
+    const int64_t r0 = (int64_t)blockIdx.x * a.slab, r1 = min(a.n_b, r0 + a.slab);
+    for (int f = threadIdx.x; f < a.F; f += 256) {
+        float sa = 0.f, sb = 0.f;
+        for (int64_t i = r0; i < r1; ++i) {
+            const float x = ld<BF>(a.M, i * a.ldm + f);
+            if (i < a.n_a) sa = fmaf(a.wa[i], x, sa);
+            sb = fmaf(a.wb[i], x, sb);
+        }
+        a.partial[(2 * (int64_t)blockIdx.x) * a.F + f] = sa;
+        a.partial[(2 * (int64_t)blockIdx.x + 1) * a.F + f] = sb;
     }
 }
-// The same for rows of at most 64 pieces of 16 bytes: each of the four wavefronts takes a quarter of the slab, a
-// whole row per load, eight rows in flight; the four partial rows are added in wavefront order.
-template <bool BF>
-__global__ __launch_bounds__(256) void wcolsum_partial_vec_kernel(const char* M, int64_t ldm, const float* w, int64_t n, int F,
-                                                                  float* partial) {
-    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8;
-    __shared__ float part[4][64 * E];
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int64_t r0 = (int64_t)blockIdx.x * kSlab + wave * (kSlab / 4), r1 = min(n, r0 + kSlab / 4);
-    const bool on = lane * E < F;
-    float acc[E];
+// rows of at most LP pieces of 16 bytes (LP a power of two): teams of LP lanes take a row each, four rows in flight
+// per team; the teams' sums are added in team order
+template <bool BF, int LP>
+__global__ __launch_bounds__(256) void colsum_partial_vec_kernel(ColSums a) {
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, T = 256 / LP, U = 4;
+    __shared__ float part[T][2][LP * E];
+    const int team = threadIdx.x / LP, piece = threadIdx.x % LP;
+    const int64_t r0 = (int64_t)blockIdx.x * a.slab, r1 = min(a.n_b, r0 + a.slab);
+    float sa[E], sb[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) acc[i] = 0.f;
-    for (int64_t i0 = r0; i0 < r1; i0 += 64) {
-        const int cnt = (int)min<int64_t>(64, r1 - i0);
-        const float mine = lane < cnt ? w[i0 + lane] : 0.f;
-        for (int j0 = 0; j0 < cnt; j0 += U) {
+    for (int i = 0; i < E; ++i) sa[i] = sb[i] = 0.f;
+    if (piece * E < a.F) {
+        const char* base = a.M + (int64_t)piece * E * EB;
+        for (int64_t i0 = r0 + team; i0 < r1; i0 += U * T) {
             u32x4 r[U];
+            float wa[U], wb[U];
 #pragma unroll
             for (int j = 0; j < U; ++j) {
+                const int64_t i = i0 + j * T;
+                const bool in = i < r1;
                 r[j] = u32x4{0u, 0u, 0u, 0u};
-                if (on && j0 + j < cnt)
-                    r[j] = *reinterpret_cast<const u32x4*>(M + ((i0 + j0 + j) * ldm + (int64_t)lane * E) * EB);
+                if (in) r[j] = *reinterpret_cast<const u32x4*>(base + i * a.ldm * EB);
+                wa[j] = in && i < a.n_a ? a.wa[i] : 0.f;
+                wb[j] = in ? a.wb[i] : 0.f;
             }
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const float wj = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, mine), (j0 + j) & 63));
                 float x[E];
                 unpack<BF>(r[j], x);
+                const bool first = i0 + j * T < a.n_a;      // a row outside sum a stays out of it, whatever it holds
 #pragma unroll
-                for (int i = 0; i < E; ++i) acc[i] = fmaf(wj, x[i], acc[i]);     // rows beyond cnt: weight 0, row 0
+                for (int i = 0; i < E; ++i) {
+                    if (first) sa[i] = fmaf(wa[j], x[i], sa[i]);
+                    sb[i] = fmaf(wb[j], x[i], sb[i]);
+                }
             }
         }
     }
 #pragma unroll
-    for (int i = 0; i < E; ++i) part[wave][lane * E + i] = acc[i];
+    for (int i = 0; i < E; ++i) {
+        part[team][0][piece * E + i] = sa[i];
+        part[team][1][piece * E + i] = sb[i];
+    }
     __syncthreads();
-    for (int f = threadIdx.x; f < F; f += 256)
-        partial[(int64_t)blockIdx.x * F + f] = ((part[0][f] + part[1][f]) + part[2][f]) + part[3][f];
+    for (int o = threadIdx.x; o < 2 * a.F; o += 256) {
+        const int k = o >= a.F, f = o - k * a.F;
+        float t = part[0][k][f];
+#pragma unroll
+        for (int w = 1; w < T; ++w) t += part[w][k][f];
+        a.partial[2 * (int64_t)blockIdx.x * a.F + o] = t;
+    }
 }
-// out[g, f] = sum of the partial rows of group g (kGroup of them), added in order
-__global__ __launch_bounds__(256) void wcolsum_reduce_kernel(const float* partial, int64_t n, int F, float* out) {
-    const int f = blockIdx.y * 256 + threadIdx.x;
-    if (f >= F) return;
-    const int64_t i0 = (int64_t)blockIdx.x * kGroup, i1 = min(n, i0 + kGroup);
-    double acc = 0.0;
-    for (int64_t i = i0; i < i1; ++i) acc += (double)partial[i * F + f];
-    out[(int64_t)blockIdx.x * F + f] = (float)acc;
+// 32 of the 2 F outputs per workgroup; 32 threads per output add every 32nd slab, their sums are added in order.
+// No slabs: zeros.
+__global__ __launch_bounds__(1024) void colsum_reduce_kernel(ColSums a) {
+    __shared__ double part[32][33];
+    const int o = threadIdx.x % 32, way = threadIdx.x / 32;
+    const int idx = blockIdx.x * 32 + o;
+    const int64_t per = 2 * (int64_t)a.F;
+    double s = 0.0;
+    if (idx < per) {
+        const float* p = a.partial + idx;
+        int64_t k = way;
+        for (; k + 96 < a.n_slabs; k += 128) {
+            const float v0 = p[k * per], v1 = p[(k + 32) * per], v2 = p[(k + 64) * per], v3 = p[(k + 96) * per];
+            s = (((s + v0) + v1) + v2) + v3;
+        }
+        for (; k < a.n_slabs; k += 32) s += p[k * per];
+    }
+    part[way][o] = s;
+    __syncthreads();
+    if (way == 0 && idx < per) {
+        double t = part[0][o];
+#pragma unroll
+        for (int w = 1; w < 32; ++w) t += part[w][o];
+        if (idx < a.F) a.out_a[idx] = (float)t;
+        else a.out_b[idx - a.F] = (float)t;
+    }
 }
 
-int64_t align_up(int64_t x);
-int64_t wcolsum_scratch_floats(int64_t n, int F) {
-    const int64_t slabs = (n + kSlab - 1) / kSlab;
-    return (slabs + (slabs + kGroup - 1) / kGroup + 2) * (int64_t)F;
-}
-// scratch: wcolsum_scratch_floats(n, F) floats.  n == 0 gives zeros.
-void weighted_column_sum(const char* M, int64_t ldm, const float* w, int64_t n, int F, bool bf, bool vec, float* scratch,
-                         float* out, hipStream_t s) {
-    const int64_t slabs = (n + kSlab - 1) / kSlab;
-    const unsigned fblocks = (unsigned)((F + 255) / 256);
-    if (slabs > 0) {
-        if (vec) {
-            if (bf) hipLaunchKernelGGL(wcolsum_partial_vec_kernel<true>, dim3((unsigned)slabs), dim3(256), 0, s, M, ldm, w, n, F, scratch);
-            else hipLaunchKernelGGL(wcolsum_partial_vec_kernel<false>, dim3((unsigned)slabs), dim3(256), 0, s, M, ldm, w, n, F, scratch);
+// scratch: colsum_scratch_floats(n_b, F) floats
+void column_sums(ColSums a, bool bf, bool vec, float* scratch, hipStream_t s) {
+    a.slab = colsum_slab(a.n_b);
+    a.n_slabs = (a.n_b + a.slab - 1) / a.slab;
+    a.partial = scratch;
+    if (a.n_slabs > 0) {
+        const dim3 grid((unsigned)a.n_slabs), block(256);
+        const int pieces = a.F / (bf ? 8 : 4);
+        if (!vec) {
+            if (bf) hipLaunchKernelGGL(colsum_partial_kernel<true>, grid, block, 0, s, a);
+            else hipLaunchKernelGGL(colsum_partial_kernel<false>, grid, block, 0, s, a);
+        } else if (bf) {
+            if (pieces <= 8) hipLaunchKernelGGL((colsum_partial_vec_kernel<true, 8>), grid, block, 0, s, a);
+            else if (pieces <= 32) hipLaunchKernelGGL((colsum_partial_vec_kernel<true, 32>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((colsum_partial_vec_kernel<true, 64>), grid, block, 0, s, a);
         } else {
-            if (bf) hipLaunchKernelGGL(wcolsum_partial_kernel<true>, dim3((unsigned)slabs), dim3(256), 0, s, M, ldm, w, n, F, scratch);
-            else hipLaunchKernelGGL(wcolsum_partial_kernel<false>, dim3((unsigned)slabs), dim3(256), 0, s, M, ldm, w, n, F, scratch);
+            if (pieces <= 16) hipLaunchKernelGGL((colsum_partial_vec_kernel<false, 16>), grid, block, 0, s, a);
+            else if (pieces <= 32) hipLaunchKernelGGL((colsum_partial_vec_kernel<false, 32>), grid, block, 0, s, a);
+            else hipLaunchKernelGGL((colsum_partial_vec_kernel<false, 64>), grid, block, 0, s, a);
         }
     }
-    float* cur = scratch;
-    float* other = scratch + slabs * (int64_t)F;
-    int64_t count = slabs;
-    for (;;) {
-        const int64_t groups = (count + kGroup - 1) / kGroup;
-        if (groups <= 1) {                      // also count == 0: one block whose empty sum writes zeros
-            hipLaunchKernelGGL(wcolsum_reduce_kernel, dim3(1, fblocks), dim3(256), 0, s, cur, count, F, out);
-            return;
-        }
-        hipLaunchKernelGGL(wcolsum_reduce_kernel, dim3((unsigned)groups, fblocks), dim3(256), 0, s, cur, count, F, other);
-        float* t = cur;
-        cur = other;
-        other = t;                              // the groups of one level always fit in front of the level before
-        count = groups;
-    }
+    hipLaunchKernelGGL(colsum_reduce_kernel, dim3((unsigned)((2 * a.F + 31) / 32)), dim3(1024), 0, s, a);
 }
 
 int64_t align_up(int64_t x) { return (x + 255) / 256 * 256; }
@@ -1041,7 +1084,7 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
 int64_t gas_gat_aggregate_bwd_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F) {
     if (n_rows < 0 || n_cols <= 0 || nnz < 0 || F <= 0) return 0;
     return 4 * align_up(nnz * 4) + align_up(n_rows * 4) + align_up(n_cols * 4) +
-           2 * align_up(wcolsum_scratch_floats(n_cols, F) * 4);
+           align_up(colsum_scratch_floats(n_cols, F) * 4);
 }
 
 gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
@@ -1078,8 +1121,7 @@ gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
     float* dt_t = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
     a.csum = reinterpret_cast<float*>(w); w += align_up(n_rows * 4);
     a.tsum = reinterpret_cast<float*>(w); w += align_up(n_cols * 4);
-    float* part_dst = reinterpret_cast<float*>(w); w += align_up(wcolsum_scratch_floats(n_cols, F) * 4);
-    float* part_src = reinterpret_cast<float*>(w);
+    float* colsum_scratch = reinterpret_cast<float*>(w);
     a.F = F; a.slope = negative_slope;
     hipStream_t s = (hipStream_t)stream;
     const bool bf = dt == GAS_BF16;
@@ -1124,8 +1166,11 @@ gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
         else hipLaunchKernelGGL(gat_bwd_cols_kernel<false>, dim3((unsigned)n_cols), dim3(64), 0, s, a);
     }
     // Ga_dst = sum over the in-batch nodes of (row total of dt) P[v];  Ga_src = sum over all nodes of (column total) P[u]
-    weighted_column_sum(a.P, ldp, a.csum, n_rows, F, bf, vec, part_dst, Ga_dst, s);
-    weighted_column_sum(a.P, ldp, a.tsum, n_cols, F, bf, vec, part_src, Ga_src, s);
+    ColSums c{};
+    c.M = a.P; c.ldm = ldp;
+    c.wa = a.csum; c.n_a = n_rows; c.wb = a.tsum; c.n_b = n_cols;
+    c.F = F; c.out_a = Ga_dst; c.out_b = Ga_src;
+    column_sums(c, bf, vec, colsum_scratch, s);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
