@@ -5,8 +5,10 @@
 // rows, with the edge weights of the GCN / GCNII / GIN operators folded into
 // `val`, `diag`, `s_agg` and the residual term.
 //
-// Mapping to the machine.  A feature row is cut into 16-byte units; a "team" of
-// G = 2^k lanes (G >= units per row, at most 64) owns one row, so one wavefront
+// Mapping to the machine.  A feature row is cut into 16-byte units (a width that
+// is no whole number of them: the last unit starts E elements before the row's
+// end and shares elements with the one before it, both compute the same sums;
+// rows need no alignment beyond their element's); a "team" of G = 2^k lanes (G >= units per row, at most 64) owns one row, so one wavefront
 // works on 64/G neighbours at a time and a wavefront-wide load instruction
 // always fetches whole contiguous rows.  The wavefront stages 64 column
 // indices and weights at a time in registers (one coalesced load) and
@@ -44,8 +46,8 @@ struct SpmmArgs {
     int64_t z_stride;
     float diag, s_agg, s_res;
     int64_t n_rows, n_diag;
-    int units;            // 16-byte units per row of X
-    int F;
+    int units;            // 16-byte units per row of X, the last one may overlap its neighbour
+    int F;                // at least one unit's elements
     int threshold;
     const int32_t* chunk;       // plan lists
     int64_t n_chunks;
@@ -75,6 +77,21 @@ struct Unit {
     }
 };
 
+// 16-byte accesses of rows that are aligned to their elements only (global memory takes them at any byte address)
+typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
+typedef u32x4 u32x4_at4 __attribute__((aligned(4)));
+typedef f32x4 f32x4_at4 __attribute__((aligned(4)));
+template <bool BF>
+__device__ __forceinline__ u32x4 load_unit(const char* p) {
+    if constexpr (BF) return *reinterpret_cast<const u32x4_at2*>(p);
+    else return *reinterpret_cast<const u32x4_at4*>(p);
+}
+// first element of a unit
+template <bool XBF>
+__device__ __forceinline__ int unit_start(const SpmmArgs& a, int unit) {
+    return min(unit * Unit<XBF>::E, a.F - Unit<XBF>::E);
+}
+
 template <int G>
 __device__ __forceinline__ int bcast_i(int v, int k) {
     if constexpr (G == 64) return __builtin_amdgcn_readlane(v, k);
@@ -99,9 +116,10 @@ __device__ __forceinline__ void accumulate(const SpmmArgs& a, int begin, int end
     for (int p = 0; p < UPT; ++p)
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[p][e] = 0.f;
-    const char* xb = a.X + (int64_t)tl * 16;
-    const char* hb = a.H + (int64_t)tl * 16;
     const int nunits = a.units;
+    int start[UPT];                            // byte offset of the lane's units in a row
+#pragma unroll
+    for (int p = 0; p < UPT; ++p) start[p] = unit_start<XBF>(a, tl + p * G) * (XBF ? 2 : 4);
     for (int t = begin; t < end; t += kWave) {
         const int cnt = min(kWave, end - t);
         int my_c = 0;
@@ -125,10 +143,9 @@ __device__ __forceinline__ void accumulate(const SpmmArgs& a, int begin, int end
                     v[u][p] = u32x4{0u, 0u, 0u, 0u};
                     // index >= 0: row of the mini-batch tensor; index < 0: row -1-index of the history table
                     const bool in_batch = c >= 0;
-                    const char* src = (in_batch ? xb : hb) +
+                    const char* src = (in_batch ? a.X : a.H) +
                                       (int64_t)(in_batch ? c : -1 - c) * (in_batch ? a.x_stride : a.h_stride);
-                    if (ok && tl + p * G < nunits)
-                        v[u][p] = *reinterpret_cast<const u32x4*>(src + (int64_t)p * G * 16);
+                    if (ok && tl + p * G < nunits) v[u][p] = load_unit<XBF>(src + start[p]);
                 }
             }
 #pragma unroll
@@ -150,7 +167,8 @@ __device__ __forceinline__ void accumulate(const SpmmArgs& a, int begin, int end
 // Z[row, unit] = s_agg * acc + diag * X[row, unit] + s_res * R[row, unit]
 template <bool XBF, bool ZBF>
 __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int unit, float (&acc)[Unit<XBF>::E]) {
-    constexpr int E = Unit<XBF>::E;
+    constexpr int E = Unit<XBF>::E, EB = XBF ? 2 : 4;
+    const int start = unit_start<XBF>(a, unit);
     float z[E];
 #pragma unroll
     for (int e = 0; e < E; ++e) z[e] = a.s_agg * acc[e];
@@ -158,7 +176,7 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
         float t[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) t[e] = 0.f;
-        Unit<XBF>::fma(t, a.diag, *reinterpret_cast<const u32x4*>(a.X + row * a.x_stride + (int64_t)unit * 16));
+        Unit<XBF>::fma(t, a.diag, load_unit<XBF>(a.X + row * a.x_stride + start * EB));
 #pragma unroll
         for (int e = 0; e < E; ++e) z[e] += t[e];
     }
@@ -166,7 +184,7 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
         float t[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) t[e] = 0.f;
-        Unit<XBF>::fma(t, a.s_res, *reinterpret_cast<const u32x4*>(a.R + row * a.r_stride + (int64_t)unit * 16));
+        Unit<XBF>::fma(t, a.s_res, load_unit<XBF>(a.R + row * a.r_stride + start * EB));
 #pragma unroll
         for (int e = 0; e < E; ++e) z[e] += t[e];
     }
@@ -176,12 +194,12 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
         u32x4 o;
 #pragma unroll
         for (int i = 0; i < 4; ++i) o[i] = pack_bf16(z[2 * i], z[2 * i + 1]);
-        __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(zp + (int64_t)unit * 16));
+        __builtin_nontemporal_store(o, reinterpret_cast<u32x4_at2*>(zp + start * 2));
     } else {
 #pragma unroll
         for (int q = 0; q < E / 4; ++q) {
             f32x4 o = {z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]};
-            __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(zp + ((int64_t)unit * E + 4 * q) * 4));
+            __builtin_nontemporal_store(o, reinterpret_cast<f32x4_at4*>(zp + (start + 4 * q) * 4));
         }
     }
 }
@@ -419,10 +437,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
         for (int p = 0; p < UPT; ++p) {
             const int unit = lane + p * G;
             if (unit < a.units) {
-                float* dst = a.partial + (int64_t)a.chunk[3 * c] * a.F + (int64_t)unit * E;
+                float* dst = a.partial + (int64_t)a.chunk[3 * c] * a.F + unit_start<XBF>(a, unit);
 #pragma unroll
                 for (int q = 0; q < E / 4; ++q)
-                    *reinterpret_cast<f32x4*>(dst + 4 * q) =
+                    *reinterpret_cast<f32x4_at4*>(dst + 4 * q) =
                         f32x4{acc[p][4 * q], acc[p][4 * q + 1], acc[p][4 * q + 2], acc[p][4 * q + 3]};
             }
         }
@@ -475,10 +493,10 @@ __global__ __launch_bounds__(256) void spmm_heavy_reduce_kernel(SpmmArgs a) {
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[e] = 0.f;
         for (int c = first; c < last; ++c) {
-            const float* src = a.partial + (int64_t)c * a.F + (int64_t)unit * E;
+            const float* src = a.partial + (int64_t)c * a.F + unit_start<XBF>(a, unit);
 #pragma unroll
             for (int q = 0; q < E / 4; ++q) {
-                const f32x4 v = *reinterpret_cast<const f32x4*>(src + 4 * q);
+                const f32x4 v = *reinterpret_cast<const f32x4_at4*>(src + 4 * q);
 #pragma unroll
                 for (int i = 0; i < 4; ++i) acc[4 * q + i] += v[i];
             }
@@ -487,8 +505,7 @@ __global__ __launch_bounds__(256) void spmm_heavy_reduce_kernel(SpmmArgs a) {
     }
 }
 
-// Element-wise path for rows that are not 16-byte aligned or not a whole
-// number of 16-byte units: one wavefront per row, one lane per feature.
+// Element-wise path for rows shorter than one 16-byte unit: one wavefront per row, one lane per feature.
 template <bool XBF, bool ZBF>
 __global__ __launch_bounds__(256) void spmm_generic_kernel(SpmmArgs a) {
     const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -521,12 +538,13 @@ gas_status launch_chunks(const SpmmArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
+// `whole`: rows are whole numbers of 16-byte aligned units, as the wave-per-row kernels need
 template <bool XBF>
-gas_status dispatch_chunks(const SpmmArgs& a, hipStream_t s) {
+gas_status dispatch_chunks(const SpmmArgs& a, bool whole, hipStream_t s) {
     const int u = a.units;
-    if (u == 64) return launch_chunks<64, 1, 8, XBF, 16>(a, s);
-    if (u == 32) return launch_chunks<32, 1, 8, XBF, 8>(a, s);
-    if (u == 16) return launch_chunks<16, 1, 8, XBF, 4>(a, s);
+    if (whole && u == 64) return launch_chunks<64, 1, 8, XBF, 16>(a, s);
+    if (whole && u == 32) return launch_chunks<32, 1, 8, XBF, 8>(a, s);
+    if (whole && u == 16) return launch_chunks<16, 1, 8, XBF, 4>(a, s);
     if (u <= 8) return launch_chunks<8, 1, 8, XBF>(a, s);
     if (u <= 16) return launch_chunks<16, 1, 8, XBF>(a, s);
     if (u <= 32) return launch_chunks<32, 1, 8, XBF>(a, s);
@@ -551,21 +569,21 @@ gas_status launch_rows(const SpmmArgs& a, hipStream_t s) {
 }
 
 template <bool XBF, bool ZBF>
-gas_status dispatch_units(const SpmmArgs& a, hipStream_t s) {
+gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
     const int u = a.units;
     if (u > 256) return fail(GAS_ERR_ARG, "feature rows longer than 4096 bytes are not supported (F*size = %d)", u * 16);
     // heavy rows first: chunk partials, then their reduction; the light rows follow on the same stream
     if (a.n_chunks > 0) {
-        const gas_status st = dispatch_chunks<XBF>(a, s);
+        const gas_status st = dispatch_chunks<XBF>(a, whole, s);
         if (st != GAS_OK) return st;
         hipLaunchKernelGGL((spmm_heavy_reduce_kernel<XBF, ZBF>), dim3((unsigned)((a.n_heavy + 3) / 4)), dim3(256),
                            0, s, a);
     }
     gas_status st;
     // rows of exactly 1 KiB, 512 B or 256 B: grouped wave-per-row path
-    if (a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
-    else if (a.group && u == 32) st = launch_rows<32, 1, 4, XBF, ZBF, 8>(a, s);
-    else if (a.group && u == 16) st = launch_rows<16, 1, 4, XBF, ZBF, 4>(a, s);
+    if (whole && a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
+    else if (whole && a.group && u == 32) st = launch_rows<32, 1, 4, XBF, ZBF, 8>(a, s);
+    else if (whole && a.group && u == 16) st = launch_rows<16, 1, 4, XBF, ZBF, 4>(a, s);
     else if (u <= 8) st = launch_rows<8, 1, 2, XBF, ZBF>(a, s);
     else if (u <= 16) st = launch_rows<16, 1, 4, XBF, ZBF>(a, s);
     else if (u <= 32) st = launch_rows<32, 1, 4, XBF, ZBF>(a, s);
@@ -614,7 +632,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.Z = static_cast<char*>(Z); a.z_stride = ldz * zb;
     a.diag = diag; a.s_agg = s_agg; a.s_res = s_res;
     a.n_rows = plan->n_rows; a.n_diag = n_diag;
-    a.units = (F * xb) / 16; a.F = F;
+    a.units = (F * xb + 15) / 16; a.F = F;
     a.threshold = plan->threshold;
     a.chunk = plan->d_chunk; a.n_chunks = plan->n_chunks;
     a.heavy = plan->d_heavy; a.n_heavy = plan->n_heavy;
@@ -622,13 +640,15 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.group = plan->d_group; a.n_groups = plan->n_groups;
     a.xcd_ranges = plan->xcd_ranges;
     for (int x = 0; x < 9; ++x) a.xcd_start[x] = plan->xcd_start[x];
-    const bool vec = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
-                     a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
-                     (!H || (aligned16(H) && a.h_stride % 16 == 0));
+    const bool whole = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
+                       a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
+                       (!H || (aligned16(H) && a.h_stride % 16 == 0));
     const bool xbf = dt_x == GAS_BF16, zbf = dt_z == GAS_BF16;
-    if (vec) {
-        if (!xbf) return dispatch_units<false, false>(a, s);
-        return zbf ? dispatch_units<true, true>(a, s) : dispatch_units<true, false>(a, s);
+    // From one 16-byte unit on, rows go by units whatever their width and alignment: a row of 1,433 floats 5,000 times,
+    // 11 entries each, 49 us (element-wise 254 us).
+    if (F * xb >= 16) {
+        if (!xbf) return dispatch_units<false, false>(a, whole, s);
+        return zbf ? dispatch_units<true, true>(a, whole, s) : dispatch_units<true, false>(a, whole, s);
     }
     const unsigned blocks = (unsigned)((a.n_rows + 3) / 4);
     if (!xbf) hipLaunchKernelGGL((spmm_generic_kernel<false, false>), dim3(blocks), dim3(256), 0, s, a);

@@ -1,0 +1,53 @@
+"""Aggregation of feature rows that are no whole number of 16-byte units or not 16-byte aligned: the widths around a unit,
+a team and a panel, tables whose rows start at odd addresses, light rows and rows that are cut into chunks."""
+import numpy as np
+import pytest
+import torch
+
+from gas_inputs import rng
+from oracle import ops as oops
+from tests.util import node_rel_err, to_np
+
+pytestmark = pytest.mark.gpu
+
+TOL = {torch.float32: 1e-5, torch.bfloat16: 2e-2}         # of the aggregation's other parity tests
+
+
+def _pattern(n_rows, n_cols, long_row):
+    """Rows of 0 to 70 entries and one of long_row, columns in order."""
+    lens = np.array([(7 * i) % 71 for i in range(n_rows)])
+    lens[n_rows // 2] = long_row
+    ptr = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    col = np.concatenate([np.sort((np.arange(k) * 7919 + 13 * i) % n_cols) for i, k in enumerate(lens)]).astype(np.int32)
+    return ptr, col
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("F", [1, 3, 4, 5, 7, 8, 9, 33, 63, 65, 129, 250, 257, 511, 1023, 1027, 1433, 2051])
+def test_aggregation_of_odd_rows(F, dtype):
+    import paper_2106_05609_amd as gas
+    nb, nh, n_table = 60, 40, 300
+    ptr, col = _pattern(nb, nb + nh, 1500)
+    n_id = to_np(rng.permutation(3, 800, n_table)[:nb + nh].to(torch.int32))
+    val = to_np(rng.normal(3, 801, 0, col.size))
+    # rows of X start at one element past a 16-byte boundary, the table's rows have an odd stride
+    x = torch.empty(nb, F + 3, dtype=dtype, device="cuda")[:, 1:F + 1]
+    x.copy_(rng.normal_matrix(3, 802, nb, F, dtype=dtype))
+    hist = rng.normal_matrix(3, 803, n_table, F, dtype=dtype).cuda()
+    d_ptr, d_col, d_val = (torch.from_numpy(a).cuda() for a in (ptr, col, val))
+    src = torch.from_numpy(np.where(col < nb, col, -1 - n_id[col]).astype(np.int32)).cuda()
+    plan = gas.gas_plan_create(d_ptr, col.size, F, ind=d_col)
+    pad = torch.full((nb + 1, F + 2), 7.0, dtype=dtype, device="cuda")
+    z = pad[:nb, 1:F + 1]
+    gas.gas_spmm_hist(plan, d_ptr, src, d_val, x, hist, z, diag=0.5, r=x, s_res=0.25)
+    torch.cuda.synchronize()
+    xo = np.concatenate([to_np(x), oops.pull(to_np(hist), n_id[nb:])])
+    want = oops.spmm(ptr, col, val, xo, diag=0.5, r=to_np(x), s_res=0.25)
+    assert node_rel_err(to_np(z), want) <= TOL[dtype]
+    assert bool((pad[:, 0] == 7.0).all()) and bool((pad[:, F + 1] == 7.0).all()) and bool((pad[nb] == 7.0).all())
+    # the same pattern as a backward aggregation (one source, no residual)
+    z2 = torch.full((nb, F), float("nan"), dtype=dtype, device="cuda")
+    xfull = torch.from_numpy(xo.view(np.int16) if dtype == torch.bfloat16 else xo)
+    xfull = (xfull.view(torch.bfloat16) if dtype == torch.bfloat16 else xfull).cuda()
+    gas.gas_spmm_t(plan, d_ptr, d_col, d_val, xfull, z2)
+    assert node_rel_err(to_np(z2), oops.spmm(ptr, col, val, xo)) <= TOL[dtype]
