@@ -220,6 +220,15 @@ GAS_API gas_status gas_spmm_t(const gas_plan* plan, const int32_t* colptr, const
                       void* GX, int64_t ldgx, gas_dtype dt_gx, void* stream);
 
 /*
+ * gas_spmm_t followed by gas_relu_bwd with the activations Y [n_rows of the plan, F] (of G's type) in one pass:
+ * GX is zero where Y is not positive.  Same bits as the two calls.
+ */
+GAS_API gas_status gas_spmm_t_relu(const gas_plan* plan, const int32_t* colptr, const int32_t* row,
+                           const float* val, float diag, float s_agg, int64_t n_diag,
+                           const void* G, int64_t ldg, gas_dtype dt, int32_t F,
+                           const void* Y, int64_t ldy, void* GX, int64_t ldgx, void* stream);
+
+/*
  * Dense transform of the GCN / GCNII operators:
  *     Y = act( c_identity * Z + c_weight * (Z W) + bias )
  * Z [n_rows, F_in], W [F_in, F_out] row-major contiguous, bias [F_out] or NULL,
@@ -333,6 +342,15 @@ GAS_API gas_status gas_relu_bwd(const void* GY, int64_t ldgy, const void* Y, int
 GAS_API gas_status gas_linear_bwd_input(const void* GP, int64_t ldgp, int64_t n_rows, int32_t F_out,
                                 const void* W, int32_t F_in, gas_dtype dt, float c_identity, float c_weight,
                                 const void* mask, int64_t ldmask, void* GZ, int64_t ldgz, void* stream);
+/*
+ * gas_linear_bwd_input with what usually follows it in the same pass:
+ *   GZ = mask > 0 ? c_identity GP + c_weight GP W^T + add : 0,      total += c_total GZ
+ * add, mask, total [n_rows, F_in] of type dt, each may be NULL; fp32 takes GZ == add.
+ */
+GAS_API gas_status gas_linear_bwd_input_add(const void* GP, int64_t ldgp, int64_t n_rows, int32_t F_out, const void* W,
+                                    int32_t F_in, gas_dtype dt, float c_identity, float c_weight, const void* add,
+                                    int64_t ldadd, const void* mask, int64_t ldmask, float c_total, void* total,
+                                    int64_t ldtotal, void* GZ, int64_t ldgz, void* stream);
 GAS_API int64_t gas_linear_bwd_weight_workspace(int64_t n_rows, int32_t F_in, int32_t F_out);
 GAS_API gas_status gas_linear_bwd_weight(const void* Z, int64_t ldz, const void* GP, int64_t ldgp,
                                  int64_t n_rows, int32_t F_in, int32_t F_out, gas_dtype dt, float c_weight,
@@ -380,6 +398,9 @@ GAS_API gas_status gas_softmax_xent(const void* A, int64_t lda, int64_t n_rows, 
                             void* G, int64_t ldg, void* stream);
 GAS_API gas_status gas_sgd_step(void* W, int64_t n, gas_dtype dt, const float* dW, float lr, float weight_decay,
                         void* stream);
+/* gas_sgd_step of `count` matrices, in order (W, n, dW: host arrays of `count`); the matrices share launches. */
+GAS_API gas_status gas_sgd_steps(int32_t count, void* const* W, const int64_t* n, gas_dtype dt, const float* const* dW,
+                         float lr, float weight_decay, void* stream);
 
 /*
  * Gradient clipping by the global norm (Section 3 of the paper: clipping keeps

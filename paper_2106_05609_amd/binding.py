@@ -15,10 +15,10 @@ OK = 0
 EXPORTS = [
     "gas_last_error", "gas_version", "gas_validate_indices",
     "gas_pull", "gas_push", "gas_host_table_pointer", "gas_pull_host", "gas_push_host",
-    "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_fuse_sources", "gas_spmm_t",
+    "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
     "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear",
-    "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace", "gas_linear_bwd_weight_static",
-    "gas_softmax_xent", "gas_sgd_step", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
+    "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace", "gas_linear_bwd_weight_static",
+    "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
     "gas_pna_aggregate", "gas_gat_aggregate", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
     "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
     "gas_disk_open", "gas_disk_close", "gas_disk_pull", "gas_disk_push", "gas_disk_wait", "gas_disk_read_rows",
@@ -61,6 +61,7 @@ _SIGNATURES = dict(
     gas_pull_host="pqqpqqiipqp", gas_push_host="pqpqqiipqqp", gas_gcn_norm="ppqpppp", gas_plan_create_opt="ppqqippp",
     gas_plan_describe="pp", gas_plan_copy_lists="ppppp", gas_spmm="ppppfpqiifpqfpqip",
     gas_spmm_hist="ppppfpqpqqiifpqfpqip", gas_fuse_sources="pqqppp", gas_spmm_t="ppppffqpqiipqip",
+    gas_spmm_t_relu="ppppffqpqiipqpqp", gas_linear_bwd_input_add="pqqipiiffpqpqfpqpqp", gas_sgd_steps="ippipffp",
     gas_linear="pqqipipiffipqp", gas_mlp2="pqqipippipiipqp", gas_linear_push="pqqipipiffipqppqqp",
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
     gas_spmm_linear="pppqpqpqqiiffpqfpipffipqpqppqqp", gas_relu_bwd="pqpqqiipqp", gas_linear_bwd_input="pqqipiiffpqpqp",
@@ -275,6 +276,18 @@ def gas_spmm_t(plan, colptr, row, val, g, gx, diag=0.0, s_agg=1.0):
                             op, ldo, _dt(gx), _stream()))
 
 
+def gas_spmm_t_relu(plan, colptr, row, val, g, y, gx, diag=0.0, s_agg=1.0):
+    """gas_spmm_t, then zero where the activations y [n_rows, F] are not positive."""
+    gp, ldg = _mat(g)
+    yp, ldy = _mat(y)
+    op, ldo = _mat(gx)
+    if gx.shape[1] != g.shape[1] or gx.shape[0] < plan.n_rows or y.shape[1] != g.shape[1] or y.shape[0] < plan.n_rows or \
+            not (g.dtype == y.dtype == gx.dtype):
+        raise ValueError("gas_spmm_t_relu: shapes or dtypes do not match")
+    _check(_calls().gas_spmm_t_relu(plan.handle, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32),
+                                    diag, s_agg, g.shape[0], gp, ldg, _dt(g), g.shape[1], yp, ldy, op, ldo, _stream()))
+
+
 def gas_linear(z, w, y, bias=None, c_identity=0.0, c_weight=1.0, relu=False):
     zp, ldz = _mat(z)
     yp, ldy = _mat(y)
@@ -326,6 +339,20 @@ def gas_linear_bwd_input(gp, w, gz, c_identity=0.0, c_weight=1.0, mask=None):
     _check(_calls().gas_linear_bwd_input(a, lda, gp.shape[0], gp.shape[1], _ptr(w),
                                       w.shape[0], _dt(gp), c_identity,
                                       c_weight, mp, ldm, c, ldc, _stream()))
+
+
+def gas_linear_bwd_input_add(gp, w, gz, c_identity=0.0, c_weight=1.0, add=None, mask=None, total=None, c_total=0.0):
+    """gas_linear_bwd_input with `add` added before the mask; total += c_total * gz where given."""
+    a, lda = _mat(gp)
+    c, ldc = _mat(gz)
+    ap, ldadd = (0, 0) if add is None else _mat(add)
+    mp, ldm = (0, 0) if mask is None else _mat(mask)
+    tp, ldt = (0, 0) if total is None else _mat(total)
+    if w.dtype != gp.dtype or gz.dtype != gp.dtype or w.shape[1] != gp.shape[1] or gz.shape != (gp.shape[0], w.shape[0]) \
+            or any(t is not None and (t.shape != gz.shape or t.dtype != gp.dtype) for t in (add, mask, total)):
+        raise ValueError("gas_linear_bwd_input_add: shapes or dtypes do not match")
+    _check(_calls().gas_linear_bwd_input_add(a, lda, gp.shape[0], gp.shape[1], _ptr(w), w.shape[0], _dt(gp), c_identity,
+                                             c_weight, ap, ldadd, mp, ldm, c_total, tp, ldt, c, ldc, _stream()))
 
 
 def gas_linear_bwd_weight_workspace(n_rows, f_in, f_out) -> int:
@@ -455,6 +482,21 @@ def gas_sgd_step(w, dw, lr, weight_decay=0.0):
         raise ValueError("gas_sgd_step: w and dw must be contiguous and of equal size, dw float32")
     _check(_calls().gas_sgd_step(_ptr(w), w.numel(), _dt(w), _ptr(dw, torch.float32),
                               lr, weight_decay, _stream()))
+
+
+def gas_sgd_steps(pairs, lr, weight_decay=0.0):
+    """gas_sgd_step on every (w, dw) of a list of matrices of one dtype, in order; they share launches."""
+    n = len(pairs)
+    if n == 0:
+        return
+    dt = pairs[0][0].dtype
+    for w, dw in pairs:
+        if not w.is_contiguous() or not dw.is_contiguous() or dw.dtype != torch.float32 or dw.numel() != w.numel() or \
+                w.dtype != dt:
+            raise ValueError("gas_sgd_steps: w and dw must be contiguous and of equal size, dw float32, w of one dtype")
+    _check(_calls().gas_sgd_steps(n, (C.c_void_p * n)(*[w.data_ptr() for w, _ in pairs]),
+                                  (C.c_int64 * n)(*[w.numel() for w, _ in pairs]), _dt(pairs[0][0]),
+                                  (C.c_void_p * n)(*[dw.data_ptr() for _, dw in pairs]), lr, weight_decay, _stream()))
 
 
 def gas_sq_norm(x, out):

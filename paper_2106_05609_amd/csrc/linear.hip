@@ -42,6 +42,9 @@ struct LinArgs {
     const char* mask; int64_t ldmask;  // optional [M, N]: outputs where mask <= 0 are set to zero
     const int32_t* push_idx = nullptr; // optional (fp32 tile kernel): row m also goes to push_hist[push_idx[m], :]
     char* push_hist = nullptr; int64_t ld_push = 0;
+    const char* add = nullptr; int64_t ldadd = 0;     // optional (fp32): [M, N] added before the mask (may be Y itself)
+    char* total = nullptr; int64_t ldtotal = 0;       // optional (fp32): [M, N], total += c_total * output
+    float c_total = 0.f;
 };
 
 struct MlpArgs {
@@ -207,6 +210,8 @@ __device__ __forceinline__ void store_rows(const LinArgs& a, int64_t m0, int n0,
             float* yrow = at(a.Y, a.ldy, row);
             const float* zrow = EXTRA && a.c_id != 0.f ? at(a.Z, a.ldz, row) : nullptr;
             const float* krow = EXTRA && a.mask ? at(a.mask, a.ldmask, row) : nullptr;
+            const float* arow = EXTRA && a.add ? at(a.add, a.ldadd, row) : nullptr;
+            float* trow = EXTRA && a.total ? at(a.total, a.ldtotal, row) : nullptr;
             float* hrow = nullptr;
             if constexpr (PUSH)
                 hrow = reinterpret_cast<float*>(a.push_hist) + n0 + li +
@@ -217,9 +222,11 @@ __device__ __forceinline__ void store_rows(const LinArgs& a, int64_t m0, int n0,
                 if (!WHOLE && n0 + 32 * j + li >= a.N) continue;
                 float y = a.c_w * acc[i][j][r] + bv[j];
                 if (EXTRA && a.c_id != 0.f) y += a.c_id * zrow[32 * j];
+                if (EXTRA && a.add) y += arow[32 * j];
                 if (a.relu) y = fmaxf(y, 0.f);
                 if (EXTRA && a.mask && !(krow[32 * j] > 0.f)) y = 0.f;
                 yrow[32 * j] = y;
+                if (EXTRA && a.total) trow[32 * j] += a.c_total * y;
                 if constexpr (PUSH) hrow[32 * j] = y;             // Push in the epilogue
             }
         }
@@ -228,8 +235,8 @@ template <int TM, int TN>
 __device__ __forceinline__ void store_tile(const LinArgs& a, int64_t m0, int n0, int li, int lh, const f32x16 (&acc)[TM][TN]) {
     constexpr int64_t kNear = 1 << 26;
     const bool whole = m0 + 32 * TM <= a.M && n0 + 32 * TN <= a.N && a.ldy < kNear && a.ldz < kNear && a.ldmask < kNear &&
-                       a.ld_push < kNear;
-    const bool extra = a.c_id != 0.f || a.mask;
+                       a.ld_push < kNear && a.ldadd < kNear && a.ldtotal < kNear;
+    const bool extra = a.c_id != 0.f || a.mask || a.add || a.total;
     if (whole && !extra && !a.push_idx) store_rows<TM, TN, true, false, false>(a, m0, n0, li, lh, acc);
     else if (whole && !extra) store_rows<TM, TN, true, false, true>(a, m0, n0, li, lh, acc);
     else if (whole && !a.push_idx) store_rows<TM, TN, true, true, false>(a, m0, n0, li, lh, acc);
@@ -1452,7 +1459,8 @@ static gas_status push_after(const PushTarget& p, const void* Y, int64_t ldy, in
 static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_t n_rows, int32_t F_in, const void* W,
                              int trans_w, int32_t F_out, const void* bias, gas_dtype dt, float c_identity,
                              float c_weight, int relu, const void* mask, int64_t ldmask, void* Y, int64_t ldy,
-                             hipStream_t s, const PushTarget& push = PushTarget()) {
+                             hipStream_t s, const PushTarget& push = PushTarget(), const void* add = nullptr,
+                             int64_t ldadd = 0, float c_total = 0.f, void* total = nullptr, int64_t ldtotal = 0) {
     if (push.idx) {
         GAS_REQUIRE(push.hist && push.ld_hist >= F_out && push.n_hist_rows > 0, "%s: bad history table for the fused push", who);
         GAS_REQUIRE(push.hist != Y, "%s: the history table aliases the output", who);
@@ -1473,6 +1481,8 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     a.c_id = c_identity; a.c_w = c_weight; a.relu = relu;
     a.trans_w = trans_w; a.mask = static_cast<const char*>(mask); a.ldmask = ldmask;
     if (dt == GAS_F32) {
+        a.add = static_cast<const char*>(add); a.ldadd = ldadd;
+        a.total = static_cast<char*>(total); a.ldtotal = ldtotal; a.c_total = c_total;
         a.push_idx = push.idx; a.push_hist = static_cast<char*>(push.hist); a.ld_push = push.ld_hist;
         // The largest tile that still gives most compute units a workgroup: a larger one splits each value for more
         // products.  50,000 x 256 x 256: 54 us in 128 x 128 tiles; 4,000 x 256 x 256: 11 us in 64 x 64 tiles.
@@ -1533,6 +1543,28 @@ gas_status gas_linear_bwd_input(const void* GP, int64_t ldgp, int64_t n_rows, in
     // GZ = c_identity * GP + c_weight * (GP W^T): a product with the [F_in, F_out] matrix taken transposed
     return run_linear("gas_linear_bwd_input", GP, ldgp, n_rows, F_out, W, 1, F_in, nullptr, dt, c_identity, c_weight,
                       0, mask, ldmask, GZ, ldgz, (hipStream_t)stream);
+}
+
+gas_status gas_linear_bwd_input_add(const void* GP, int64_t ldgp, int64_t n_rows, int32_t F_out, const void* W,
+                                    int32_t F_in, gas_dtype dt, float c_identity, float c_weight, const void* add,
+                                    int64_t ldadd, const void* mask, int64_t ldmask, float c_total, void* total,
+                                    int64_t ldtotal, void* GZ, int64_t ldgz, void* stream) {
+    const char* who = "gas_linear_bwd_input_add";
+    GAS_REQUIRE((!add || ldadd >= F_in) && (!total || ldtotal >= F_in), "%s: row stride smaller than the row", who);
+    GAS_REQUIRE(!total || (total != GZ && total != GP && total != add && total != mask), "%s: the total aliases another matrix", who);
+    GAS_REQUIRE(!add || add != GZ || ldadd == ldgz, "%s: an output in place of the addend needs its row stride", who);
+    hipStream_t s = (hipStream_t)stream;
+    if (dt == GAS_F32)
+        return run_linear(who, GP, ldgp, n_rows, F_out, W, 1, F_in, nullptr, dt, c_identity, c_weight, 0, mask, ldmask, GZ,
+                          ldgz, s, PushTarget(), add, ldadd, c_total, total, ldtotal);
+    // bf16: every step rounds to storage, as the calls one after the other do
+    GAS_REQUIRE(!add || add != GZ, "%s: bf16 needs an output beside the addend", who);
+    gas_status st = run_linear(who, GP, ldgp, n_rows, F_out, W, 1, F_in, nullptr, dt, c_identity, c_weight, 0,
+                               add ? nullptr : mask, ldmask, GZ, ldgz, s);
+    if (st == GAS_OK && add) st = gas_axpy(add, ldadd, GZ, ldgz, n_rows, F_in, dt, 1.f, GZ, ldgz, stream);
+    if (st == GAS_OK && add && mask) st = gas_relu_bwd(GZ, ldgz, mask, ldmask, n_rows, F_in, dt, GZ, ldgz, stream);
+    if (st == GAS_OK && total) st = gas_axpy(total, ldtotal, GZ, ldgz, n_rows, F_in, dt, c_total, total, ldtotal, stream);
+    return st;
 }
 
 int64_t gas_linear_bwd_weight_workspace(int64_t n_rows, int32_t F_in, int32_t F_out) {

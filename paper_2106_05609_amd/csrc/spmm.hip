@@ -42,6 +42,8 @@ struct SpmmArgs {
     int64_t h_stride;
     const char* R;
     int64_t r_stride;
+    const char* Y;        // optional (MASK kernels): activations of X's type; outputs where Y <= 0 are zero
+    int64_t y_stride;
     char* Z;
     int64_t z_stride;
     float diag, s_agg, s_res;
@@ -164,7 +166,7 @@ __device__ __forceinline__ void accumulate(const SpmmArgs& a, int begin, int end
     }
 }
 
-// Z[row, unit] = s_agg * acc + diag * X[row, unit] + s_res * R[row, unit]
+// Z[row, unit] = s_agg * acc + diag * X[row, unit] + s_res * R[row, unit], zero where the activation Y is not positive
 template <bool XBF, bool ZBF>
 __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int unit, float (&acc)[Unit<XBF>::E]) {
     constexpr int E = Unit<XBF>::E, EB = XBF ? 2 : 4;
@@ -187,6 +189,14 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
         Unit<XBF>::fma(t, a.s_res, load_unit<XBF>(a.R + row * a.r_stride + start * EB));
 #pragma unroll
         for (int e = 0; e < E; ++e) z[e] += t[e];
+    }
+    if (a.Y) {
+        const u32x4 y = load_unit<XBF>(a.Y + row * a.y_stride + start * EB);
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const float v = XBF ? (e & 1 ? bf16_hi(y[e / 2]) : bf16_lo(y[e / 2])) : __uint_as_float(y[e % 4]);
+            z[e] = v > 0.f ? z[e] : 0.f;
+        }
     }
     char* zp = a.Z + row * a.z_stride;
     if constexpr (ZBF) {
@@ -244,10 +254,11 @@ struct LaneAcc {
     }
 };
 
-template <int VB, bool XBF, bool ZBF>
+template <int VB, bool XBF, bool ZBF, bool MASK>
 __device__ __forceinline__ void flush_row(const SpmmArgs& a, int64_t row, int lane, LaneAcc<VB, XBF>& acc,
-                                          const typename VecOf<VB>::type& own) {
-    // `own` = this lane's piece of X[row, :], loaded ahead of time by the caller (only read when diag != 0)
+                                          const typename VecOf<VB>::type& own, const typename VecOf<VB>::type& act) {
+    // `own` = this lane's piece of X[row, :], `act` of Y[row, :], loaded ahead of time by the caller (only read when
+    // diag != 0; MASK)
     typedef typename VecOf<VB>::type V;
     constexpr int E = LaneAcc<VB, XBF>::E, NW = VB / 4;
     float z[E];
@@ -266,6 +277,13 @@ __device__ __forceinline__ void flush_row(const SpmmArgs& a, int64_t row, int la
         t.fma(a.s_res, *reinterpret_cast<const V*>(a.R + row * a.r_stride + (int64_t)lane * VB));
 #pragma unroll
         for (int e = 0; e < E; ++e) z[e] += t.v[e];
+    }
+    if constexpr (MASK) {
+#pragma unroll
+        for (int e = 0; e < E; ++e) {
+            const float v = XBF ? (e & 1 ? bf16_hi(act[e / 2]) : bf16_lo(act[e / 2])) : __uint_as_float(act[e % NW]);
+            z[e] = v > 0.f ? z[e] : 0.f;
+        }
     }
     char* zp = a.Z + row * a.z_stride;
     if constexpr (ZBF) {
@@ -290,7 +308,7 @@ __device__ __forceinline__ void flush_row(const SpmmArgs& a, int64_t row, int la
     acc.clear();
 }
 
-template <int VB, bool XBF, bool ZBF>
+template <int VB, bool XBF, bool ZBF, bool MASK>
 __device__ __forceinline__ void light_group(const SpmmArgs& a, int64_t g) {
     typedef typename VecOf<VB>::type V;
     constexpr int U = 8;
@@ -319,11 +337,27 @@ __device__ __forceinline__ void light_group(const SpmmArgs& a, int64_t g) {
     };
 #pragma unroll
     for (int d = 0; d < D; ++d) own[d] = load_own(d);
+    // the same for the rows of the mask
+    V act[MASK ? D : 1];
+    auto load_act = [&](int rr) -> V {
+        V v{};
+        if (rr < nrows) v = __builtin_nontemporal_load(reinterpret_cast<const V*>(a.Y + ((int64_t)r0 + rr) * a.y_stride + (int64_t)lane * VB));
+        return v;
+    };
+    if constexpr (MASK) {
+#pragma unroll
+        for (int d = 0; d < D; ++d) act[d] = load_act(d);
+    }
     auto flush = [&]() {
-        flush_row<VB, XBF, ZBF>(a, r0 + r, lane, acc, own[0]);
+        flush_row<VB, XBF, ZBF, MASK>(a, r0 + r, lane, acc, own[0], act[0]);
 #pragma unroll
         for (int d = 0; d + 1 < D; ++d) own[d] = own[d + 1];
         own[D - 1] = load_own(r + D);
+        if constexpr (MASK) {
+#pragma unroll
+            for (int d = 0; d + 1 < D; ++d) act[d] = act[d + 1];
+            act[D - 1] = load_act(r + D);
+        }
         ++r;
     };
     // a single row longer than 64 entries makes its own group: walk it 64 entries at a time
@@ -450,7 +484,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // Light rows, finished in one go (epilogue and store).  VB > 0: bundled into
 // groups, one wavefront per row (rows of exactly 64 vectors of VB bytes);
 // VB == 0: one wavefront per row, teams of G lanes per neighbour.
-template <int G, int UPT, int U, bool XBF, bool ZBF, int VB>
+template <int G, int UPT, int U, bool XBF, bool ZBF, int VB, bool MASK>
 __global__ __launch_bounds__(256) void spmm_rows_kernel(SpmmArgs a) {
     if constexpr (VB > 0) {
         // Workgroups go to the eight XCDs in turn and each XCD has its own L2: with xcd_ranges every XCD takes one
@@ -462,7 +496,7 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(SpmmArgs a) {
             g = a.xcd_start[x] + (int64_t)(blockIdx.x >> 3) * 4 + (threadIdx.x >> 6);
             g_end = a.xcd_start[x + 1];
         }
-        if (g < g_end) light_group<VB, XBF, ZBF>(a, g);
+        if (g < g_end) light_group<VB, XBF, ZBF, MASK>(a, g);
     } else {
         constexpr int E = Unit<XBF>::E;
         const int lane = threadIdx.x & 63;
@@ -525,6 +559,7 @@ __global__ __launch_bounds__(256) void spmm_generic_kernel(SpmmArgs a) {
         float z = a.s_agg * acc;
         if (a.diag != 0.f && row < a.n_diag) z += a.diag * ld(a.X, a.x_stride, row, f);
         if (a.R) z += a.s_res * ld(a.R, a.r_stride, row, f);
+        if (a.Y && !(ld(a.Y, a.y_stride, row, f) > 0.f)) z = 0.f;
         if constexpr (ZBF) *reinterpret_cast<uint16_t*>(a.Z + row * a.z_stride + 2 * f) = (uint16_t)f32_to_bf16(z);
         else *reinterpret_cast<float*>(a.Z + row * a.z_stride + 4 * (int64_t)f) = z;
     }
@@ -563,8 +598,11 @@ gas_status launch_rows(const SpmmArgs& a, hipStream_t s) {
         blocks = 8 * ((longest + 3) / 4);
     }
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
-    if (blocks > 0)
-        hipLaunchKernelGGL((spmm_rows_kernel<G, UPT, U, XBF, ZBF, VB>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    if (blocks > 0) {
+        // (the kernels by units look at a.Y themselves)
+        if (VB > 0 && a.Y) hipLaunchKernelGGL((spmm_rows_kernel<G, UPT, U, XBF, ZBF, VB, (VB > 0)>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((spmm_rows_kernel<G, UPT, U, XBF, ZBF, VB, false>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    }
     return GAS_OK;
 }
 
@@ -598,7 +636,8 @@ gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
 gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, const int32_t* ind, const float* val,
                     float diag, int64_t n_diag, const void* X, int64_t ldx, const void* H, int64_t ldh,
                     gas_dtype dt_x, int32_t F, float s_agg,
-                    const void* R, int64_t ldr, float s_res, void* Z, int64_t ldz, gas_dtype dt_z, hipStream_t s) {
+                    const void* R, int64_t ldr, float s_res, void* Z, int64_t ldz, gas_dtype dt_z, hipStream_t s,
+                    const void* Y = nullptr, int64_t ldy = 0) {
     if (!valid_dtype(dt_x) || !valid_dtype(dt_z)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype", who);
     if (dt_x == GAS_F32 && dt_z == GAS_BF16)
         return fail(GAS_ERR_DTYPE, "%s: fp32 input with bf16 output is not supported", who);
@@ -608,7 +647,8 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     GAS_REQUIRE(plan->nnz == 0 || ind, "%s: null index array", who);
     GAS_REQUIRE(F > 0 && F <= plan->max_F, "%s: F=%d outside (0, plan max_F=%d]", who, F, plan->max_F);
     GAS_REQUIRE(ldx >= F && ldz >= F && (!R || ldr >= F) && (!H || ldh >= F), "%s: row stride smaller than F", who);
-    GAS_REQUIRE(Z != X && Z != R, "%s: output aliases an input", who);
+    GAS_REQUIRE(!Y || ldy >= F, "%s: row stride of the mask smaller than F", who);
+    GAS_REQUIRE(Z != X && Z != R && Z != Y, "%s: output aliases an input", who);
     const int xb = elem_bytes(dt_x), zb = elem_bytes(dt_z);
     // Rows longer than 4096 bytes (a wide input layer) are aggregated panel by panel: the sum is separate for
     // every feature column, so a panel of columns is an aggregation of its own over the same pattern.
@@ -619,7 +659,8 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
             const gas_status st = run_spmm(who, plan, ptr, ind, val, diag, n_diag, static_cast<const char*>(X) + f0 * xb,
                                            ldx, H ? static_cast<const char*>(H) + f0 * xb : nullptr, ldh, dt_x, fw, s_agg,
                                            R ? static_cast<const char*>(R) + f0 * xb : nullptr, ldr, s_res,
-                                           static_cast<char*>(Z) + f0 * zb, ldz, dt_z, s);
+                                           static_cast<char*>(Z) + f0 * zb, ldz, dt_z, s,
+                                           Y ? static_cast<const char*>(Y) + f0 * xb : nullptr, ldy);
             if (st != GAS_OK) return st;
         }
         return GAS_OK;
@@ -629,6 +670,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.X = static_cast<const char*>(X); a.x_stride = ldx * xb;
     a.H = static_cast<const char*>(H); a.h_stride = ldh * xb;
     a.R = static_cast<const char*>(R); a.r_stride = ldr * xb;
+    a.Y = static_cast<const char*>(Y); a.y_stride = ldy * xb;
     a.Z = static_cast<char*>(Z); a.z_stride = ldz * zb;
     a.diag = diag; a.s_agg = s_agg; a.s_res = s_res;
     a.n_rows = plan->n_rows; a.n_diag = n_diag;
@@ -642,7 +684,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     for (int x = 0; x < 9; ++x) a.xcd_start[x] = plan->xcd_start[x];
     const bool whole = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
                        a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
-                       (!H || (aligned16(H) && a.h_stride % 16 == 0));
+                       (!H || (aligned16(H) && a.h_stride % 16 == 0)) && (!Y || (aligned16(Y) && a.y_stride % 16 == 0));
     const bool xbf = dt_x == GAS_BF16, zbf = dt_z == GAS_BF16;
     // From one 16-byte unit on, rows go by units whatever their width and alignment: a row of 1,433 floats 5,000 times,
     // 11 entries each, 49 us (element-wise 254 us).
@@ -687,6 +729,15 @@ gas_status gas_spmm_t(const gas_plan* plan, const int32_t* colptr, const int32_t
     GAS_REQUIRE(n_diag >= 0, "gas_spmm_t: n_diag=%lld", (long long)n_diag);
     return run_spmm("gas_spmm_t", plan, colptr, row, val, diag, n_diag, G, ldg, nullptr, 0, dt_g, F, s_agg, nullptr,
                     0, 0.f, GX, ldgx, dt_gx, (hipStream_t)stream);
+}
+
+gas_status gas_spmm_t_relu(const gas_plan* plan, const int32_t* colptr, const int32_t* row, const float* val, float diag,
+                           float s_agg, int64_t n_diag, const void* G, int64_t ldg, gas_dtype dt, int32_t F,
+                           const void* Y, int64_t ldy, void* GX, int64_t ldgx, void* stream) {
+    GAS_REQUIRE(n_diag >= 0, "gas_spmm_t_relu: n_diag=%lld", (long long)n_diag);
+    GAS_REQUIRE(Y || !plan || plan->n_rows == 0, "gas_spmm_t_relu: null activations");
+    return run_spmm("gas_spmm_t_relu", plan, colptr, row, val, diag, n_diag, G, ldg, nullptr, 0, dt, F, s_agg, nullptr,
+                    0, 0.f, GX, ldgx, dt, (hipStream_t)stream, Y, ldy);
 }
 
 gas_status gas_spmm_hist(const gas_plan* plan, const int32_t* rowptr, const int32_t* src, const float* val,

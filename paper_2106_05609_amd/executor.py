@@ -515,15 +515,12 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
     for l in range(L, 0, -1):
-        z, h, yl = saved[l - 1]
-        if l != L:
-            gp = torch.empty_like(g)
-            B.gas_relu_bwd(g, yl, gp)
-            g = gp
-        gz = torch.empty_like(z)
+        z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
+        gz = torch.empty_like(z) if l > 1 or model.op != "gcn" else None
         if model.op == "gcn":
             grads[l - 1] = weight_grad(z, g)
-            B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
+            if l > 1:                         # below the first layer there is nothing to train
+                B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
         elif model.op == "gin":
             w1, w2 = model.weights[l - 1]
             dw2 = weight_grad(h, g)
@@ -539,23 +536,26 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         else:
             beta = gcnii_beta(l)
             grads[l - 1] = weight_grad(z, g, beta)
-            B.gas_linear_bwd_input(g, model.weights[l - 1], gz, c_identity=1.0 - beta, c_weight=beta)
             if g_h0 is None:
                 g_h0 = torch.zeros((nv, gz.shape[1]), dtype=dt, device=dev)
-            B.gas_axpy(g_h0[:nb], gz, g_h0[:nb], model.alpha)      # the initial residual's share: g_h0 += alpha * gz
+            # the initial residual's share on the way: g_h0 += alpha * gz
+            B.gas_linear_bwd_input_add(g, model.weights[l - 1], gz, c_identity=1.0 - beta, c_weight=beta,
+                                       total=g_h0[:nb], c_total=model.alpha)
         if l == 1:
             if model.op == "gcnii":
                 gx = torch.empty((nv, gz.shape[1]), dtype=dt, device=dev)
                 B.gas_spmm_t(bg.plan_t_all, bg.colptr, bg.row, bg.val_t, gz, gx, s_agg=1.0 - model.alpha)
                 B.gas_axpy(g_h0, gx, g_h0, 1.0)
             break
+        # the adjoint of the aggregation and of the layer below's ReLU in one pass
         gx = torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
+        y_below = saved[l - 2][2]
         if model.op == "gin":
-            B.gas_spmm_t(bg.plan_t, bg.colptr, bg.row, None, gz, gx, diag=1.0 + model.gin_eps)
+            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, None, gz, y_below, gx, diag=1.0 + model.gin_eps)
         elif model.op == "gcn":
-            B.gas_spmm_t(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, gx)
+            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, y_below, gx)
         else:
-            B.gas_spmm_t(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, gx, s_agg=1.0 - model.alpha)
+            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, y_below, gx, s_agg=1.0 - model.alpha)
         g = gx
     if model.op == "gcnii":
         gp = torch.empty_like(g_h0)
@@ -564,8 +564,17 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     return y, grads, {"x0": x0, "h0": h0, "layers": saved}
 
 
+def _sgd(pairs, lr, weight_decay):
+    """The plain update of every (w, dw), matrices of one dtype sharing launches."""
+    if all(w.dtype == pairs[0][0].dtype for w, _ in pairs):
+        B.gas_sgd_steps(pairs, lr, weight_decay)
+        return
+    for w, dw in pairs:
+        B.gas_sgd_step(w, dw, lr, weight_decay)
+
+
 def apply_sgd(model: Model, grads, lr, weight_decay=0.0, max_norm=None):
-    """One gradient-descent update of every weight matrix, in place (gas_sgd_step per matrix).  max_norm: the
+    """One gradient-descent update of every weight matrix, in place (gas_sgd_steps).  max_norm: the
     gradients are first clipped by their global L2 norm (paper, Section 3): one gas_sq_norm per gradient, then
     gas_sgd_step_clipped, which forms the common factor on the device."""
     pairs = []
@@ -577,8 +586,7 @@ def apply_sgd(model: Model, grads, lr, weight_decay=0.0, max_norm=None):
     if model.op == "gcnii":
         pairs.append((model.w_in, grads["w_in"]))
     if max_norm is None:
-        for w, dw in pairs:
-            B.gas_sgd_step(w, dw, lr, weight_decay)
+        _sgd(pairs, lr, weight_decay)
         return
     sq = torch.empty(len(pairs), dtype=torch.float32, device=pairs[0][0].device)
     for k, (_, dw) in enumerate(pairs):
@@ -801,12 +809,8 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
     g = grad_out(y) if callable(grad_out) else grad_out
     for l in range(L, 0, -1):
         w1, w2 = weights[l - 1]
-        x, p, cat, yl = kept[l - 1]
+        x, p, cat, _ = kept[l - 1]            # g: the gradient before this layer's activation
         f, f1 = x.shape[1], w1.shape[1]
-        if l != L:
-            gm = torch.empty_like(g)
-            B.gas_relu_bwd(g, yl, gm)
-            g = gm
         dw2 = _weight_grad(cat, g)
         gcat = torch.empty_like(cat)
         B.gas_linear_bwd_input(g, w2, gcat)
@@ -820,14 +824,12 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         grads[l - 1] = (dw1, dw2)
         if l == 1:
             break
-        # dL/dX[:nb] = the copy of h_v in the concatenation + the neighbour part + the receiving-node part
-        gx = torch.empty((nb, f), dtype=dt, device=dev)
-        B.gas_linear_bwd_input(gp[:nb], w1[f:], gx)
-        B.gas_axpy(gcat[:, :f], gx, gx, 1.0)
-        t = torch.empty((nb, f), dtype=dt, device=dev)
-        B.gas_linear_bwd_input(gq, w1[:f], t)
-        B.gas_axpy(gx, t, gx, 1.0)
-        g = gx
+        # dL/dX[:nb] = the copy of h_v in the concatenation + the neighbour part + the receiving-node part, then the
+        # layer below's ReLU
+        part = torch.empty((nb, f), dtype=dt, device=dev)
+        B.gas_linear_bwd_input_add(gp[:nb], w1[f:], part, add=gcat[:, :f])
+        g = torch.empty((nb, f), dtype=dt, device=dev)
+        B.gas_linear_bwd_input_add(gq, w1[:f], g, add=part, mask=kept[l - 2][3])
     return y, grads, kept
 
 
@@ -868,11 +870,7 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
     g = grad_out(y) if callable(grad_out) else grad_out
     for l in range(L, 0, -1):
         w, a_dst, a_src = weights[l - 1]
-        x, p, yl = kept[l - 1]
-        if l != L:
-            gm = torch.empty_like(g)
-            B.gas_relu_bwd(g, yl, gm)
-            g = gm
+        x, p, _ = kept[l - 1]                 # g: the gradient before this layer's activation
         gp = torch.empty_like(p)
         gd = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         gs = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
@@ -882,17 +880,14 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         grads[l - 1] = (_weight_grad(x, gp), gd, gs)
         if l == 1:
             break
-        gx = torch.empty((nb, w.shape[0]), dtype=dt, device=dev)
-        B.gas_linear_bwd_input(gp[:nb], w, gx)
-        g = gx
+        g = torch.empty((nb, w.shape[0]), dtype=dt, device=dev)
+        B.gas_linear_bwd_input(gp[:nb], w, g, mask=kept[l - 2][2])
     return y, grads, kept
 
 
 def sgd_update(weights, grads, lr, weight_decay=0.0):
     """gas_sgd_step on every tensor of a list of per-layer weight tuples (PNA, GAT) with the matching gradients."""
-    for l, ws in enumerate(weights):
-        for w, dw in zip(ws, grads[l]):
-            B.gas_sgd_step(w, dw, lr, weight_decay)
+    _sgd([pair for l, ws in enumerate(weights) for pair in zip(ws, grads[l])], lr, weight_decay)
 
 
 def layer_forward(model: Model, l, bg: BatchGraph, x, h0=None, y=None):
