@@ -201,33 +201,52 @@ __device__ __forceinline__ void store_rows(const LinArgs& a, int64_t m0, int n0,
         else
             return reinterpret_cast<float*>(const_cast<char*>(X) + ((row + 4 * lh) * ld + n0 + li) * 4);
     };
+    // the optional operands of eight rows are loaded together, before any of them is needed
+    constexpr int R = EXTRA ? 8 : 1;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-            const int64_t row = m0 + 32 * i + 8 * (r / 4) + r % 4;
-            if (!WHOLE && row + 4 * lh >= a.M) continue;
-            float* yrow = at(a.Y, a.ldy, row);
-            const float* zrow = EXTRA && a.c_id != 0.f ? at(a.Z, a.ldz, row) : nullptr;
-            const float* krow = EXTRA && a.mask ? at(a.mask, a.ldmask, row) : nullptr;
-            const float* arow = EXTRA && a.add ? at(a.add, a.ldadd, row) : nullptr;
-            float* trow = EXTRA && a.total ? at(a.total, a.ldtotal, row) : nullptr;
-            float* hrow = nullptr;
-            if constexpr (PUSH)
-                hrow = reinterpret_cast<float*>(a.push_hist) + n0 + li +
-                       (WHOLE ? (uint64_t)(uint32_t)a.push_idx[row + 4 * lh] * (uint32_t)a.ld_push
-                              : (uint64_t)((int64_t)a.push_idx[row + 4 * lh] * a.ld_push));
+        for (int r0 = 0; r0 < 16; r0 += R) {
+            auto row_of = [&](int r) { return m0 + 32 * i + 8 * (r / 4) + r % 4; };
+            auto in = [&](int r, int j) { return WHOLE || (row_of(r) + 4 * lh < a.M && n0 + 32 * j + li < a.N); };
+            float zv[R][TN], kv[R][TN], av[R][TN], tv[R][TN];
+            auto load = [&](float (&v)[R][TN], const char* X, int64_t ld) {
 #pragma unroll
-            for (int j = 0; j < TN; ++j) {
-                if (!WHOLE && n0 + 32 * j + li >= a.N) continue;
-                float y = a.c_w * acc[i][j][r] + bv[j];
-                if (EXTRA && a.c_id != 0.f) y += a.c_id * zrow[32 * j];
-                if (EXTRA && a.add) y += arow[32 * j];
-                if (a.relu) y = fmaxf(y, 0.f);
-                if (EXTRA && a.mask && !(krow[32 * j] > 0.f)) y = 0.f;
-                yrow[32 * j] = y;
-                if (EXTRA && a.total) trow[32 * j] += a.c_total * y;
-                if constexpr (PUSH) hrow[32 * j] = y;             // Push in the epilogue
+                for (int r = 0; r < R; ++r) {
+                    const float* x = at(X, ld, row_of(r0 + r));
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) v[r][j] = in(r0 + r, j) ? x[32 * j] : 0.f;
+                }
+            };
+            if constexpr (EXTRA) {
+                if (a.c_id != 0.f) load(zv, a.Z, a.ldz);
+                if (a.add) load(av, a.add, a.ldadd);
+                if (a.mask) load(kv, a.mask, a.ldmask);
+                if (a.total) load(tv, a.total, a.ldtotal);
+            }
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                const int64_t row = row_of(r0 + r);
+                if (!WHOLE && row + 4 * lh >= a.M) continue;
+                float* yrow = at(a.Y, a.ldy, row);
+                float* trow = EXTRA && a.total ? at(a.total, a.ldtotal, row) : nullptr;
+                float* hrow = nullptr;
+                if constexpr (PUSH)
+                    hrow = reinterpret_cast<float*>(a.push_hist) + n0 + li +
+                           (WHOLE ? (uint64_t)(uint32_t)a.push_idx[row + 4 * lh] * (uint32_t)a.ld_push
+                                  : (uint64_t)((int64_t)a.push_idx[row + 4 * lh] * a.ld_push));
+#pragma unroll
+                for (int j = 0; j < TN; ++j) {
+                    if (!WHOLE && n0 + 32 * j + li >= a.N) continue;
+                    float y = a.c_w * acc[i][j][r0 + r] + bv[j];
+                    if (EXTRA && a.c_id != 0.f) y += a.c_id * zv[r][j];
+                    if (EXTRA && a.add) y += av[r][j];
+                    if (a.relu) y = fmaxf(y, 0.f);
+                    if (EXTRA && a.mask && !(kv[r][j] > 0.f)) y = 0.f;
+                    yrow[32 * j] = y;
+                    if (EXTRA && a.total) trow[32 * j] = tv[r][j] + a.c_total * y;
+                    if constexpr (PUSH) hrow[32 * j] = y;         // Push in the epilogue
+                }
             }
         }
 }
