@@ -1191,19 +1191,20 @@ struct DwArgs {
 // fp32: both operands split into bf16 parts (split.h), eight consecutive rows of one feature per LDS piece.  The tiles
 // of one slab follow each other on one XCD: they read the same rows.
 constexpr int kDwSplitKS = 2;
-__global__ __launch_bounds__(256, 2) void dw_split_kernel(DwArgs a) {
-    using S = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>;
+template <int BT, int WPS>
+__global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
+    using S = SplitGemm<BT, BT, 2, 2, kDwSplitKS, false, false>;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned tn = (a.N + kDwTile - 1) / kDwTile, tiles = (a.K + kDwTile - 1) / kDwTile * tn;
+    const unsigned tn = (a.N + BT - 1) / BT, tiles = (a.K + BT - 1) / BT * tn;
     const unsigned of_xcd = blockIdx.x / 8, tile = of_xcd % tiles;
     const int slab = (int)(of_xcd / tiles * 8 + blockIdx.x % 8);
     if (slab >= a.n_slabs) return;                     // the grid is padded to a multiple of eight slabs
-    const int k0 = (int)(tile / tn) * kDwTile, n0 = (int)(tile % tn) * kDwTile;
+    const int k0 = (int)(tile / tn) * BT, n0 = (int)(tile % tn) * BT;
     const int64_t m_begin = (int64_t)slab * a.slab;
     const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
-    const int wk0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
+    const int wk0 = (wave >> 1) * (BT / 2), wn0 = (wave & 1) * (BT / 2);
     const float* Z = reinterpret_cast<const float*>(a.Z);
     const float* G = reinterpret_cast<const float*>(a.G);
     S g;
@@ -1637,11 +1638,16 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
     GAS_REQUIRE(tk <= 65535 && tn <= 65535, "gas_linear_bwd_weight: widths too large");
     dim3 grid((unsigned)n_slabs, tk, tn);
     if (dt == GAS_F32) {
-        constexpr int smem = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
-        static_assert(smem <= 65536, "no attribute needed");
         const int64_t blocks = (n_slabs + 7) / 8 * 8 * tk * tn;
         GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for one launch");
-        hipLaunchKernelGGL(dw_split_kernel, dim3((unsigned)blocks), dim3(256), smem, s, a);
+        if (F_in <= 64 && F_out <= 64) {             // 21,000 x 64 x 64: 8 us, in a tile of 128 x 128 15 us
+            constexpr int smem = SplitGemm<64, 64, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
+            hipLaunchKernelGGL((dw_split_kernel<64, 4>), dim3((unsigned)blocks), dim3(256), smem, s, a);
+        } else {
+            constexpr int smem = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
+            static_assert(smem <= 65536, "no attribute needed");
+            hipLaunchKernelGGL((dw_split_kernel<kDwTile, 2>), dim3((unsigned)blocks), dim3(256), smem, s, a);
+        }
     } else {
         const bool vec = aligned16(Z) && aligned16(GP) && ldz % 8 == 0 && ldgp % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
         if (vec && F_in <= 256 && F_out <= 256 && F_in > 128 && F_out > 128) {
