@@ -28,13 +28,17 @@ namespace {
 constexpr int kCopyThreads = 256;
 constexpr int kCopyUnroll = 4;
 
-// One "team" of 2^g_log2 lanes moves one row of `units` vectors of type V.
+// One "team" of 2^g_log2 lanes moves one row of `units` vectors of type V; where
+// a row is no whole number of them the last one ends with the row and shares
+// bytes with the one before it, which store the same values.  ANY: rows are aligned
+// to their elements only (global memory takes 16 bytes at any byte address).
 // Source row i is src_idx[i] (or src_base + i), destination row likewise.
-template <typename V>
+template <typename V, bool ANY = false>
 __global__ __launch_bounds__(kCopyThreads) void copy_rows_kernel(
     const char* __restrict__ src, int64_t src_stride, const int32_t* __restrict__ src_idx, int64_t src_base,
     char* __restrict__ dst, int64_t dst_stride, const int32_t* __restrict__ dst_idx, int64_t dst_base,
-    int64_t n, int units, int g_log2, int64_t n_blocks) {
+    int64_t n, int units, int last, int g_log2, int64_t n_blocks) {
+    typedef V VA __attribute__((aligned(ANY ? 2 : alignof(V))));
     const int team = threadIdx.x >> g_log2;
     const int lane = threadIdx.x & ((1 << g_log2) - 1);
     const int teams = kCopyThreads >> g_log2;
@@ -50,16 +54,17 @@ __global__ __launch_bounds__(kCopyThreads) void copy_rows_kernel(
             drow[j] = ok ? (dst_idx ? (int64_t)dst_idx[r] : dst_base + r) : -1;
         }
         for (int u = lane; u < units; u += (1 << g_log2)) {
+            const int at = min(u * (int)sizeof(V), last);          // last: where a row's last vector starts
             V tmp[kCopyUnroll];
 #pragma unroll
             for (int j = 0; j < kCopyUnroll; ++j)
                 if (srow[j] >= 0)
                     tmp[j] = __builtin_nontemporal_load(
-                        reinterpret_cast<const V*>(src + srow[j] * src_stride) + u);
+                        reinterpret_cast<const VA*>(src + srow[j] * src_stride + at));
 #pragma unroll
             for (int j = 0; j < kCopyUnroll; ++j)
                 if (srow[j] >= 0)
-                    __builtin_nontemporal_store(tmp[j], reinterpret_cast<V*>(dst + drow[j] * dst_stride) + u);
+                    __builtin_nontemporal_store(tmp[j], reinterpret_cast<VA*>(dst + drow[j] * dst_stride + at));
         }
     }
 }
@@ -70,11 +75,16 @@ gas_status launch_copy(const void* src, int64_t ld_src, const int32_t* src_idx, 
     if (n == 0) return GAS_OK;
     const int eb = elem_bytes(dt);
     const int64_t row_bytes = (int64_t)F * eb, ss = ld_src * eb, ds = ld_dst * eb;
-    int vec = eb;   // widest access that divides everything
-    if (aligned16(src) && aligned16(dst) && row_bytes % 16 == 0 && ss % 16 == 0 && ds % 16 == 0) vec = 16;
+    // 16-byte accesses from 16 bytes a row on.  5,000 rows of 1,433 floats: 23 us (by single floats 34 us).
+    // Rows in host memory keep to accesses that divide everything: what crosses the link stays aligned.
+    const bool whole = aligned16(src) && aligned16(dst) && row_bytes % 16 == 0 && ss % 16 == 0 && ds % 16 == 0;
+    const bool device = max_blocks == 0;
+    int vec = eb;
+    if (whole || (device && row_bytes >= 16)) vec = 16;
     else if (eb == 2 && ((uintptr_t)src % 4 == 0) && ((uintptr_t)dst % 4 == 0) && row_bytes % 4 == 0 &&
              ss % 4 == 0 && ds % 4 == 0) vec = 4;
-    const int units = (int)(row_bytes / vec);
+    GAS_REQUIRE(row_bytes <= 0x7FFFFFFF, "rows of %lld bytes are too long", (long long)row_bytes);
+    const int units = (int)((row_bytes + vec - 1) / vec), last = (int)row_bytes - vec;
     int g_log2 = 0;
     while ((1 << g_log2) < units && g_log2 < 6) ++g_log2;
     const int teams = kCopyThreads >> g_log2;
@@ -84,15 +94,18 @@ gas_status launch_copy(const void* src, int64_t ld_src, const int32_t* src_idx, 
     dim3 grid((unsigned)((max_blocks > 0 && max_blocks < blocks) ? max_blocks : blocks)), block(kCopyThreads);
     const char* s = static_cast<const char*>(src);
     char* d = static_cast<char*>(dst);
-    if (vec == 16)
+    if (vec == 16 && !whole)
+        hipLaunchKernelGGL((copy_rows_kernel<u32x4, true>), grid, block, 0, stream, s, ss, src_idx, src_base, d, ds,
+                           dst_idx, dst_base, n, units, last, g_log2, blocks);
+    else if (vec == 16)
         hipLaunchKernelGGL(copy_rows_kernel<u32x4>, grid, block, 0, stream, s, ss, src_idx, src_base, d, ds,
-                           dst_idx, dst_base, n, units, g_log2, blocks);
+                           dst_idx, dst_base, n, units, last, g_log2, blocks);
     else if (vec == 4)
         hipLaunchKernelGGL(copy_rows_kernel<uint32_t>, grid, block, 0, stream, s, ss, src_idx, src_base, d, ds,
-                           dst_idx, dst_base, n, units, g_log2, blocks);
+                           dst_idx, dst_base, n, units, last, g_log2, blocks);
     else
         hipLaunchKernelGGL(copy_rows_kernel<uint16_t>, grid, block, 0, stream, s, ss, src_idx, src_base, d, ds,
-                           dst_idx, dst_base, n, units, g_log2, blocks);
+                           dst_idx, dst_base, n, units, last, g_log2, blocks);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
