@@ -456,6 +456,11 @@ GAS_API gas_status gas_gat_aggregate(const int32_t* rowptr, const int32_t* col, 
                              const void* P, int64_t ldp, gas_dtype dt, int32_t F,
                              const void* a_dst, const void* a_src, float negative_slope, int relu,
                              void* Z, int64_t ldz, void* stream);
+/* `heads` attention heads in one call: head h has columns h F .. (h + 1) F - 1 of P and Z and elements h F .. of a_dst
+ * and a_src; F is the width of one head. */
+GAS_API gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* P,
+                                   int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
+                                   const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz, void* stream);
 
 /*
  * Backward passes of the two aggregations above (chain rule on the equations of the operator appendix), without
@@ -498,6 +503,14 @@ GAS_API gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* 
                                  const void* a_dst, const void* a_src, float negative_slope,
                                  const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
                                  void* workspace, int64_t workspace_bytes, void* stream);
+/* The same for `heads` heads side by side (as gas_gat_aggregate_heads; Ga_dst, Ga_src [heads * F]). */
+GAS_API int64_t gas_gat_aggregate_bwd_heads_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F, int32_t heads);
+GAS_API gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                       const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
+                                       int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
+                                       int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
+                                       const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
+                                       void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
  * Pieces of the auxiliary loss of Eq. (3), || f(h) - f(h + eps) ||, which is

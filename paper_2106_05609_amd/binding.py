@@ -19,8 +19,9 @@ EXPORTS = [
     "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear",
     "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace", "gas_linear_bwd_weight_static",
     "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
-    "gas_pna_aggregate", "gas_gat_aggregate", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
-    "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
+    "gas_pna_aggregate", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
+    "gas_gat_aggregate_bwd_heads", "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
+    "gas_gat_aggregate_bwd_heads_workspace",
     "gas_disk_open", "gas_disk_close", "gas_disk_pull", "gas_disk_push", "gas_disk_wait", "gas_disk_read_rows",
     "gas_disk_write_rows", "gas_disk_sync",
 ]
@@ -48,6 +49,7 @@ def lib():
         L.gas_linear_bwd_weight_workspace.restype = C.c_int64
         L.gas_pna_aggregate_bwd_workspace.restype = C.c_int64
         L.gas_gat_aggregate_bwd_workspace.restype = C.c_int64
+        L.gas_gat_aggregate_bwd_heads_workspace.restype = C.c_int64
         for name in EXPORTS:
             if name not in ("gas_last_error", "gas_version", "gas_plan_destroy") and not name.endswith("_workspace"):
                 getattr(L, name).restype = C.c_int
@@ -68,9 +70,9 @@ _SIGNATURES = dict(
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
     gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp",
-    gas_gat_aggregate="ppqpqiippfipqp", gas_pna_aggregate_bwd_workspace="qqi",
-    gas_pna_aggregate_bwd="pppqqpppqpqiifpqpqpqpqp", gas_gat_aggregate_bwd_workspace="qqqi",
-    gas_gat_aggregate_bwd="pppqpppqqqpqiippfpqpqpppqp", gas_axpy="pqpqqiifpqp", gas_row_distance="pqpqqiippp",
+    gas_gat_aggregate_heads="ppqpqiiippfipqp", gas_pna_aggregate_bwd_workspace="qqi",
+    gas_pna_aggregate_bwd="pppqqpppqpqiifpqpqpqpqp", gas_gat_aggregate_bwd_heads_workspace="qqqii",
+    gas_gat_aggregate_bwd_heads="pppqpppqqqpqiiippfpqpqpppqp", gas_axpy="pqpqqiifpqp", gas_row_distance="pqpqqiippp",
     gas_row_dot="pqpqqiippp", gas_row_distance_bwd="pqpqqiifpqp", gas_disk_open="pqiiiiqp", gas_disk_close="p",
     gas_disk_pull="ppqqpqpp", gas_disk_push="ppqqpqpp", gas_disk_wait="pq", gas_disk_read_rows="ppqqpq",
     gas_disk_write_rows="ppqqpq", gas_disk_sync="p",
@@ -531,17 +533,18 @@ def gas_pna_aggregate(rowptr, col, x, out, delta, add=None):
                                    _stream()))
 
 
-def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False):
-    """z[v] = sum_k softmax_k(LeakyReLU(a_dst.p[v] + a_src.p[col k])) p[col k] over the entries of row v."""
+def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False, heads=1):
+    """z[v] = sum_k softmax_k(LeakyReLU(a_dst.p[v] + a_src.p[col k])) p[col k] over the entries of row v.  heads > 1: the
+    columns of p and z and the elements of a_dst and a_src are that many equal blocks, a head each."""
     pp, ldp = _mat(p)
     zp, ldz = _mat(z)
-    n_rows = rowptr.numel() - 1
-    if z.dtype != p.dtype or a_dst.dtype != p.dtype or a_src.dtype != p.dtype or z.shape[1] != p.shape[1] or \
-            z.shape[0] < n_rows or a_dst.numel() != p.shape[1] or a_src.numel() != p.shape[1]:
+    n_rows, width = rowptr.numel() - 1, p.shape[1]
+    if z.dtype != p.dtype or a_dst.dtype != p.dtype or a_src.dtype != p.dtype or z.shape[1] != width or \
+            z.shape[0] < n_rows or a_dst.numel() != width or a_src.numel() != width or heads < 1 or width % heads:
         raise ValueError("gas_gat_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_gat_aggregate(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, pp, ldp,
-                                   _dt(p), p.shape[1], _ptr(a_dst), _ptr(a_src),
-                                   negative_slope, int(relu), zp, ldz, _stream()))
+    _check(_calls().gas_gat_aggregate_heads(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, pp, ldp, _dt(p),
+                                            width // heads, heads, _ptr(a_dst), _ptr(a_src), negative_slope, int(relu), zp,
+                                            ldz, _stream()))
 
 
 def gas_axpy(x, e, y, alpha=1.0):
@@ -714,21 +717,21 @@ def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, ga
 
 
 def gas_gat_aggregate_bwd(rowptr, col, colptr, row, csc_pos, p, a_dst, a_src, gz, gp_out, ga_dst, ga_src,
-                          negative_slope=0.2, plan_t=None):
+                          negative_slope=0.2, plan_t=None, heads=1):
     """Backward of gas_gat_aggregate (gz: gradient before any activation): gp_out [n_out, F] rows of P's gradient,
-    ga_dst / ga_src float32 [F].  plan_t: a Plan of the CSC copy for those n_out columns (fast path), or None."""
+    ga_dst / ga_src float32 [F].  plan_t: a Plan of the CSC copy for those n_out columns, or None (checked only)."""
     pp, ldp = _mat(p)
     zp, ldz = _mat(gz)
     op, ldo = _mat(gp_out)
     n_rows, n_cols, F, nnz = rowptr.numel() - 1, p.shape[0], p.shape[1], col.numel()
     if gz.shape != (n_rows, F) or gp_out.shape[1] != F or colptr.numel() != n_cols + 1 or gz.dtype != p.dtype or \
-            gp_out.dtype != p.dtype or ga_dst.dtype != torch.float32 or ga_src.dtype != torch.float32:
+            gp_out.dtype != p.dtype or ga_dst.dtype != torch.float32 or ga_src.dtype != torch.float32 or heads < 1 or F % heads:
         raise ValueError("gas_gat_aggregate_bwd: shapes or dtypes do not match")
-    nbytes = int(_calls().gas_gat_aggregate_bwd_workspace(n_rows, n_cols, nnz, F))
+    nbytes = int(_calls().gas_gat_aggregate_bwd_heads_workspace(n_rows, n_cols, nnz, F // heads, heads))
     ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=p.device)
-    _check(_calls().gas_gat_aggregate_bwd(plan_t.handle if plan_t is not None else 0,
-                                       _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
-                                       _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
-                                       n_cols, gp_out.shape[0], nnz, pp, ldp,
-                                       _dt(p), F, _ptr(a_dst), _ptr(a_src), negative_slope,
-                                       zp, ldz, op, ldo, _ptr(ga_dst), _ptr(ga_src), _ptr(ws), nbytes, _stream()))
+    _check(_calls().gas_gat_aggregate_bwd_heads(plan_t.handle if plan_t is not None else 0,
+                                                _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
+                                                _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
+                                                n_cols, gp_out.shape[0], nnz, pp, ldp, _dt(p), F // heads, heads, _ptr(a_dst),
+                                                _ptr(a_src), negative_slope, zp, ldz, op, ldo, _ptr(ga_dst), _ptr(ga_src),
+                                                _ptr(ws), nbytes, _stream()))

@@ -498,11 +498,12 @@ struct GatBwdArgs {
     const char* a_dst; const char* a_src;
     const char* GZ; int64_t ldgz;
     char* GP; int64_t ldgp;
-    float* alpha;      // [nnz]: scores, then attention weights
-    float* dt;         // [nnz]: dalpha, then the gradient at the raw scores
-    float* csum;       // [n_rows]: sum of dt over the row
-    float* tsum;       // [n_cols]: sum of dt over the column
-    int F;
+    float* alpha;      // plain path, [nnz]: scores, then attention weights
+    float* dt;         // plain path, [nnz]: dalpha, then the gradient at the raw scores
+    f32x2_t* pair;     // fast path, [nnz][heads]: both of them side by side
+    float* csum;       // [n_rows][heads]: sum of dt over the row
+    float* tsum;       // [n_cols][heads]: sum of dt over the column
+    int F;             // width of a head; head h has columns h F .. of P, GZ and GP
     float slope;
 };
 
@@ -611,24 +612,25 @@ __global__ __launch_bounds__(64) void gat_bwd_cols_kernel(GatBwdArgs a) {
     }
 }
 
-// ---- fast path: rows of at most 64 pieces of 16 bytes
+// ---- fast path: rows of at most 64 pieces of 16 bytes, H heads side by side (HeadTeams in wave.h)
 // Row v = [b, e), b < e, as gat_bwd_rows_kernel, with the gathers of the forward kernel: eight neighbour rows in
 // flight per lane, both dot products of an entry (with a_src for the score, with GZ[v] for the gradient of its
-// attention weight) reduced over the lanes eight entries at a time.  A row of at most G < 64 pieces is held by each
-// of the wavefront's S = 64 / G teams of G lanes, which take the entries in turn (team t the entries t, t + S, ...).
-// W = 1: one wavefront has the whole row.  W = kLongWaves: the wavefronts of a workgroup take the row's blocks of 64
-// entries in turn (wavefront w the blocks w, w + W, ...) and meet for the row's maximum and its three sums, which
-// are added in wavefront order; `red` is their W floats of LDS.  Either way entry k is stored and read again by
-// one and the same lane, so no lane ever reads another lane's store.
-template <bool BF, int G, int W>
-__device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int b, int e, float* red) {
-    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = 64 / G;
-    const int lane = threadIdx.x & 63, team = lane / G, tl = lane % G;
+// attention weight) reduced over the team's lanes eight entries at a time.  W = 1: one wavefront has the whole row.
+// W = kLongWaves: the wavefronts of a workgroup take the row's blocks of 64 entries in turn (wavefront w the blocks
+// w, w + W, ...) and meet for the row's maximum and its three sums, which are added in wavefront order; `red` is
+// their LDS.  Either way an entry's pair is stored and read again by one and the same lane (lane tl < 8 of a team has
+// the slot's tl-th entry of a block), so no lane ever reads another lane's store.
+template <bool BF, int G, int H, int W>
+__device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int b, int e, float (*red)[4]) {
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = HeadTeams<G, H>::kSlots;
+    const HeadTeams<G, H> ht;
+    const int lane = threadIdx.x & 63;
     const int first = W == 1 ? 0 : (int)(threadIdx.x >> 6);
-    const bool on = tl * E < a.F;
+    const bool on = ht.tl * E < a.F, writer = ht.tl == 0 && ht.slot == 0;
+    const int64_t own = (int64_t)ht.head * a.F + ht.tl * E;            // the lane's first column
     auto piece = [&](const char* base, int64_t row_elems) {
         u32x4 t = {0u, 0u, 0u, 0u};
-        if (on) t = *reinterpret_cast<const u32x4*>(base + (row_elems + (int64_t)tl * E) * EB);
+        if (on) t = *reinterpret_cast<const u32x4*>(base + (row_elems + own) * EB);
         return t;
     };
     float ar[E], gz[E], x[E], ad[E];
@@ -636,10 +638,14 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
     unpack<BF>(piece(a.a_dst, 0), ad);
     unpack<BF>(piece(a.GZ, v * a.ldgz), gz);
     unpack<BF>(piece(a.P, v * a.ldp), x);
-    float sv = 0.f;
+    float sv = 0.f, size = 0.f;
 #pragma unroll
-    for (int i = 0; i < E; ++i) sv += ad[i] * x[i];
+    for (int i = 0; i < E; ++i) {
+        sv += ad[i] * x[i];
+        size += fabsf(ad[i] * x[i]);
+    }
     sv = team_sum<G>(sv);
+    size = team_sum<G>(size);
     float mx = -INFINITY;
     for (int k0 = b + 64 * first; k0 < e; k0 += 64 * W) {
         const int cnt = min(64, e - k0);
@@ -648,13 +654,12 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
             u32x4 r[U];
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                const int kk = j0 + j * S + team;
+                const int kk = j0 + j * S + ht.slot;
                 int c;
                 if constexpr (S == 1) c = __builtin_amdgcn_readlane(mine, kk & 63);
                 else c = __shfl(mine, kk & 63);
                 r[j] = u32x4{0u, 0u, 0u, 0u};
-                if (on && kk < cnt)
-                    r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + (int64_t)tl * E) * EB);
+                if (on && kk < cnt) r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + own) * EB);
             }
             float sw[U], da[U];
 #pragma unroll
@@ -670,167 +675,237 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
             }
             team_sum8<G>(sw);
             team_sum8<G>(da);
-            // entry j0 + i of the block is stored by lane j0 + i; its two sums are with team i % S, in slot i / S
-            const int mine_i = lane - j0;
-            float my_t = 0.f, my_da = 0.f;
+            f32x2_t kept = {0.f, 0.f};
 #pragma unroll
             for (int j = 0; j < U; ++j) {
-                float tj = sv + sw[j], dj = da[j];
-                if (j * S + team < cnt - j0) mx = fmaxf(mx, tj > 0.f ? tj : a.slope * tj);
-                if constexpr (S > 1) {
-                    const int src = (mine_i & (S - 1)) * G;
-                    tj = __shfl(tj, src);
-                    dj = __shfl(dj, src);
-                }
-                if (mine_i >= j * S && mine_i < (j + 1) * S) { my_t = tj; my_da = dj; }
+                const float t = sv + sw[j];
+                if (j0 + j * S + ht.slot < cnt) mx = fmaxf(mx, t > 0.f ? t : a.slope * t);
+                if (ht.tl == j) kept = f32x2_t{t, da[j]};
             }
-            if (mine_i >= 0 && mine_i < U * S && lane < cnt) { a.alpha[k0 + lane] = my_t; a.dt[k0 + lane] = my_da; }
+            const int kk = j0 + ht.tl * S + ht.slot;
+            const bool mine_too = ht.tl < U && kk < cnt;
+            // The gradient is not continuous where a score is zero (LeakyReLU): a score that fp32 rounding leaves near
+            // there, about one in 10^5, is formed again in 64 bits from rows read again.
+            const bool near = mine_too && fabsf(kept[0]) <= 0x1p-20f * (size + fabsf(kept[0] - sv));
+            if (__any(near)) {
+#pragma unroll 1
+                for (int j = 0; j < U; ++j) {
+                    const int kj = j0 + j * S + ht.slot;
+                    float xd[E], xv[E], xs[E], xw[E];
+                    unpack<BF>(piece(a.a_dst, 0), xd);
+                    unpack<BF>(piece(a.P, v * a.ldp), xv);
+                    unpack<BF>(piece(a.a_src, 0), xs);
+                    unpack<BF>(piece(a.P, (int64_t)a.col[k0 + min(kj, cnt - 1)] * a.ldp), xw);
+                    double s = 0.0;
+#pragma unroll
+                    for (int i = 0; i < E; ++i) s += (double)xd[i] * xv[i] + (double)xs[i] * xw[i];
+#pragma unroll
+                    for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
+                    if (near && ht.tl == j) kept[0] = (float)s;
+                }
+            }
+            if (mine_too) a.pair[(int64_t)(k0 + kk) * H + ht.head] = kept;
         }
     }
-#pragma unroll
-    for (int o = G; o < 64; o <<= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
-    mx = across_waves<W, true>(mx, red);
+    // the lane's own entries once more
+    auto each = [&](auto&& fn) {
+        for (int k0 = b + 64 * first; k0 < e; k0 += 64 * W)
+            for (int kk = ht.tl * S + ht.slot; kk < min(64, e - k0); kk += U * S)
+                if (ht.tl < U) fn(a.pair[(int64_t)(k0 + kk) * H + ht.head]);
+    };
+    auto total = [&](float x) {
+        return across_waves_by_head<W, false>(HeadTeams<G, H>::over_slots(team_sum<G>(x)), ht.head, writer, red);
+    };
+    mx = across_waves_by_head<W, true>(HeadTeams<G, H>::max_over_slots(mx), ht.head, writer, red);
     float den = 0.f;
-    for (int k = b + 64 * first + lane; k < e; k += 64 * W) {
-        const float t = a.alpha[k];
-        den += expf((t > 0.f ? t : a.slope * t) - mx);
-    }
-    den = across_waves<W, false>(wave_sum(den), red);
+    each([&](f32x2_t& p) { den += expf((p[0] > 0.f ? p[0] : a.slope * p[0]) - mx); });
+    den = total(den);
     float mean_da = 0.f;
-    for (int k = b + 64 * first + lane; k < e; k += 64 * W) {
-        const float t = a.alpha[k];
-        mean_da += expf((t > 0.f ? t : a.slope * t) - mx) / den * a.dt[k];
-    }
-    mean_da = across_waves<W, false>(wave_sum(mean_da), red);
+    each([&](f32x2_t& p) { mean_da += expf((p[0] > 0.f ? p[0] : a.slope * p[0]) - mx) / den * p[1]; });
+    mean_da = total(mean_da);
     float sum_dt = 0.f;
-    for (int k = b + 64 * first + lane; k < e; k += 64 * W) {
-        const float t = a.alpha[k];
-        const float al = expf((t > 0.f ? t : a.slope * t) - mx) / den;
-        const float dtk = al * (a.dt[k] - mean_da) * (t > 0.f ? 1.f : a.slope);
-        a.alpha[k] = al;
-        a.dt[k] = dtk;
+    each([&](f32x2_t& p) {
+        const f32x2_t q = p;
+        const float al = expf((q[0] > 0.f ? q[0] : a.slope * q[0]) - mx) / den;
+        const float dtk = al * (q[1] - mean_da) * (q[0] > 0.f ? 1.f : a.slope);
+        p = f32x2_t{al, dtk};
         sum_dt += dtk;
-    }
-    sum_dt = across_waves<W, false>(wave_sum(sum_dt), red);
-    if (threadIdx.x == 0) a.csum[v] = sum_dt;
+    });
+    sum_dt = total(sum_dt);
+    if (writer && first == 0) a.csum[v * H + ht.head] = sum_dt;
 }
 
 // one wavefront per row; long rows are left to gat_bwd_long_rows_kernel
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __global__ __launch_bounds__(64) void gat_bwd_rows_vec_kernel(GatBwdArgs a) {
     const int64_t v = blockIdx.x;
     const int b = a.rowptr[v], e = a.rowptr[v + 1];
     if (e == b) {
-        if (threadIdx.x == 0) a.csum[v] = 0.f;
+        if (threadIdx.x < H) a.csum[v * H + threadIdx.x] = 0.f;
         return;
     }
     if (e - b > kLongRow) return;
-    gat_bwd_row<BF, G, 1>(a, v, b, e, nullptr);
+    gat_bwd_row<BF, G, H, 1>(a, v, b, e, nullptr);
 }
 
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_rows_kernel(GatBwdArgs a) {
     constexpr int T = 64 * kLongWaves;
     __shared__ int queue[T];
     __shared__ int n_queued;
-    __shared__ float red[kLongWaves];
+    __shared__ float red[kLongWaves][4];
     for (int64_t r0 = blockIdx.x; r0 < a.n_rows; r0 += (int64_t)T * gridDim.x) {
         const int nq = queue_long_rows(a.rowptr, a.n_rows, r0, queue, &n_queued);
         for (int q = 0; q < nq; ++q) {
             const int64_t v = queue[q];
-            gat_bwd_row<BF, G, kLongWaves>(a, v, a.rowptr[v], a.rowptr[v + 1], red);   // ends with a barrier
+            gat_bwd_row<BF, G, H, kLongWaves>(a, v, a.rowptr[v], a.rowptr[v + 1], red);   // ends with a barrier
         }
     }
 }
 
-template <bool BF, int G>
-void launch_gat_bwd_rows(const GatBwdArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((gat_bwd_rows_vec_kernel<BF, G>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
-    const unsigned blocks = long_row_blocks(a.n_rows);
-    hipLaunchKernelGGL((gat_bwd_long_rows_kernel<BF, G>), dim3(blocks), dim3(64 * kLongWaves), 0, s, a);
-}
-
-// The attention weights and the score gradients in the order of the CSC copy: the coefficients of the backward
-// aggregation, and the terms of the column totals.
-__global__ __launch_bounds__(256) void permute_entries_kernel(const float* __restrict__ alpha, const float* __restrict__ dt,
-                                                              const int32_t* __restrict__ pos, int64_t n,
-                                                              float* __restrict__ val_t, float* __restrict__ dt_t) {
-    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (q >= n) return;
-    const int k = pos[q];
-    val_t[q] = alpha[k];
-    dt_t[q] = dt[k];
-}
-
-// tsum[u] = the column's total of dt.  A wavefront takes 64 consecutive columns, whose terms are contiguous: a lane
-// adds the terms of its own column in stored order when there are at most 64 of them.  Longer columns are left to
-// column_totals_long_kernel: hub columns sit next to each other, and sixty-four of them in one wavefront's share,
-// summed one after the other, were most of this step's time.
-constexpr int kLongColumn = 64;
-
-__global__ __launch_bounds__(256) void column_totals_kernel(const int32_t* __restrict__ colptr, const float* __restrict__ dt_t,
-                                                            int64_t n_cols, float* __restrict__ tsum) {
-    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (u >= n_cols) return;
-    const int b = colptr[u], e = colptr[u + 1];
-    if (e - b > kLongColumn) return;
-    float ts = 0.f;
-    for (int q = b; q < e; q += 8) {                  // eight loads in flight, added in stored order
-        float x[8];
+// Column u = [b, e) of the pattern = row u of P: the blocks first, first + stride, ... of its entries (v, u), eight
+// rows of GZ in flight per lane with the entries' pairs beside them; afterwards every slot holds the sums
+// acc = sum alpha GZ[v] (for u < n_out) and ts = sum dt.  One gather does what a permutation of the pairs into column
+// order, column totals, an aggregation per head and a rank-one update did in six launches a head.
+template <bool BF, int G, int H>
+__device__ __forceinline__ void gat_bwd_col(const GatBwdArgs& a, int64_t u, int b, int e, int first, int stride, float& ts,
+                                            float (&acc)[Elems<BF>::E]) {
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = HeadTeams<G, H>::kSlots;
+    const HeadTeams<G, H> ht;
+    const int lane = threadIdx.x & 63;
+    const bool on = ht.tl * E < a.F && u < a.n_out;
+    const char* gz = a.GZ + ((int64_t)ht.head * a.F + ht.tl * E) * EB;
+    ts = 0.f;
 #pragma unroll
-        for (int j = 0; j < 8; ++j) x[j] = q + j < e ? dt_t[q + j] : 0.f;
+    for (int i = 0; i < E; ++i) acc[i] = 0.f;
+    for (int k0 = b + 64 * first; k0 < e; k0 += 64 * stride) {
+        const int cnt = min(64, e - k0);
+        const int my_row = lane < cnt ? a.row[k0 + lane] : 0, my_pos = lane < cnt ? a.csc_pos[k0 + lane] : 0;
+        for (int j0 = 0; j0 < cnt; j0 += U * S) {
+            u32x4 r[U];
+            f32x2_t w[U];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) ts += x[j];
+            for (int j = 0; j < U; ++j) {
+                const int kk = j0 + j * S + ht.slot;
+                int v, k;
+                if constexpr (S == 1) {
+                    v = __builtin_amdgcn_readlane(my_row, kk & 63);
+                    k = __builtin_amdgcn_readlane(my_pos, kk & 63);
+                } else {
+                    v = __shfl(my_row, kk & 63);
+                    k = __shfl(my_pos, kk & 63);
+                }
+                r[j] = u32x4{0u, 0u, 0u, 0u};
+                w[j] = f32x2_t{0.f, 0.f};
+                if (kk < cnt) {
+                    w[j] = a.pair[(int64_t)k * H + ht.head];
+                    if (on) r[j] = *reinterpret_cast<const u32x4*>(gz + (int64_t)v * a.ldgz * EB);
+                }
+            }
+            float tb = 0.f, part[E];                       // eight entries by themselves first, as in the forward pass
+#pragma unroll
+            for (int i = 0; i < E; ++i) part[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                float x[E];
+                unpack<BF>(r[j], x);
+                tb += w[j][1];
+#pragma unroll
+                for (int i = 0; i < E; ++i) part[i] = fmaf(w[j][0], x[i], part[i]);
+            }
+            ts += tb;
+#pragma unroll
+            for (int i = 0; i < E; ++i) acc[i] += part[i];
+        }
     }
-    tsum[u] = ts;
+    ts = HeadTeams<G, H>::over_slots(ts);
+#pragma unroll
+    for (int i = 0; i < E; ++i) acc[i] = HeadTeams<G, H>::over_slots(acc[i]);
 }
 
-// The columns of more than kLongColumn terms, found as the long rows are: one wavefront per column, lanes stride over
-// its terms, then a fixed reduction over the lanes.
-__global__ __launch_bounds__(64 * kLongWaves) void column_totals_long_kernel(const int32_t* __restrict__ colptr,
-                                                                             const float* __restrict__ dt_t, int64_t n_cols,
-                                                                             float* __restrict__ tsum) {
-    constexpr int T = 64 * kLongWaves;
+// GP[u] = acc + ts a_src + csum[u] a_dst
+template <bool BF, int G, int H>
+__device__ __forceinline__ void gat_bwd_col_finish(const GatBwdArgs& a, int64_t u, float ts, float (&acc)[Elems<BF>::E]) {
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4;
+    const HeadTeams<G, H> ht;
+    if (ht.slot > 0) return;
+    if (ht.tl == 0) a.tsum[u * H + ht.head] = ts;
+    if (u >= a.n_out || ht.tl * E >= a.F) return;
+    const int64_t own = (int64_t)ht.head * a.F + ht.tl * E;
+    const float cs = u < a.n_rows ? a.csum[u * H + ht.head] : 0.f;
+    float ar[E], ad[E];
+    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_src + own * EB), ar);
+    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_dst + own * EB), ad);
+#pragma unroll
+    for (int i = 0; i < E; ++i) acc[i] = acc[i] + ts * ar[i] + cs * ad[i];
+    *reinterpret_cast<u32x4*>(a.GP + (u * a.ldgp + own) * EB) = pack<BF>(acc);
+}
+
+// one wavefront per column; long columns are left to gat_bwd_long_cols_kernel
+template <bool BF, int G, int H>
+__global__ __launch_bounds__(64) void gat_bwd_cols_vec_kernel(GatBwdArgs a) {
+    const int64_t u = blockIdx.x;
+    const int b = a.colptr[u], e = a.colptr[u + 1];
+    if (e - b > kLongRow) return;
+    float ts, acc[Elems<BF>::E];
+    gat_bwd_col<BF, G, H>(a, u, b, e, 0, 1, ts, acc);
+    gat_bwd_col_finish<BF, G, H>(a, u, ts, acc);
+}
+
+template <bool BF, int G, int H>
+__global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_cols_kernel(GatBwdArgs a) {
+    constexpr int E = Elems<BF>::E, T = 64 * kLongWaves;
     __shared__ int queue[T];
     __shared__ int n_queued;
+    __shared__ float red[kLongWaves][E + 1][64];
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for (int64_t r0 = blockIdx.x; r0 < n_cols; r0 += (int64_t)T * gridDim.x) {
-        const int nq = queue_long_rows(colptr, n_cols, r0, queue, &n_queued, kLongColumn);
-        for (int q = w; q < nq; q += kLongWaves) {
+    for (int64_t r0 = blockIdx.x; r0 < a.n_cols; r0 += (int64_t)T * gridDim.x) {
+        const int nq = queue_long_rows(a.colptr, a.n_cols, r0, queue, &n_queued);
+        for (int q = 0; q < nq; ++q) {
             const int64_t u = queue[q];
-            const int b = colptr[u], e = colptr[u + 1];
-            float p = 0.f;
-            for (int t = b + lane; t < e; t += 64) p += dt_t[t];
-            p = wave_sum(p);
-            if (lane == 0) tsum[u] = p;
+            float ts, acc[E];
+            gat_bwd_col<BF, G, H>(a, u, a.colptr[u], a.colptr[u + 1], w, kLongWaves, ts, acc);
+            if (w > 0) {
+                red[w][E][lane] = ts;
+#pragma unroll
+                for (int i = 0; i < E; ++i) red[w][i][lane] = acc[i];
+            }
+            __syncthreads();
+            if (w == 0) {
+                for (int o = 1; o < kLongWaves; ++o) {
+                    ts += red[o][E][lane];
+#pragma unroll
+                    for (int i = 0; i < E; ++i) acc[i] += red[o][i][lane];
+                }
+                gat_bwd_col_finish<BF, G, H>(a, u, ts, acc);
+            }
+            __syncthreads();
         }
-        __syncthreads();
     }
 }
 
-// GP[u] += tsum[u] a_src + csum[u] a_dst after the backward aggregation has left sum_k alpha_k GZ[row k] in GP[u]:
-// one thread per 16-byte piece.
+template <bool BF, int G, int H>
+void launch_gat_bwd(const GatBwdArgs& a, hipStream_t s) {
+    if (a.n_rows > 0) {
+        hipLaunchKernelGGL((gat_bwd_rows_vec_kernel<BF, G, H>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
+        hipLaunchKernelGGL((gat_bwd_long_rows_kernel<BF, G, H>), dim3(long_row_blocks(a.n_rows)), dim3(64 * kLongWaves), 0, s, a);
+    }
+    hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H>), dim3((unsigned)a.n_cols), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((gat_bwd_long_cols_kernel<BF, G, H>), dim3(long_row_blocks(a.n_cols)), dim3(64 * kLongWaves), 0, s, a);
+}
+
 template <bool BF>
-__global__ __launch_bounds__(256) void gat_bwd_rank_one_kernel(GatBwdArgs a) {
-    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4;
-    const int pieces = a.F / E;
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= a.n_out * pieces) return;
-    const int64_t u = idx / pieces;
-    const int p = (int)(idx - u * pieces);
-    const float ts = a.tsum[u], cs = u < a.n_rows ? a.csum[u] : 0.f;
-    float g[E], ar[E], ad[E];
-    char* gp = a.GP + (u * a.ldgp + (int64_t)p * E) * EB;
-    unpack<BF>(*reinterpret_cast<const u32x4*>(gp), g);
-    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_src + (int64_t)p * E * EB), ar);
-    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_dst + (int64_t)p * E * EB), ad);
-#pragma unroll
-    for (int i = 0; i < E; ++i) g[i] = g[i] + ts * ar[i] + cs * ad[i];
-    *reinterpret_cast<u32x4*>(gp) = pack<BF>(g);
+void launch_gat_bwd_heads(const GatBwdArgs& a, int H, hipStream_t s) {
+    const int G = gat_team<BF>(a.F);
+    if (G == 64) launch_gat_bwd<BF, 64, 1>(a, s);
+    else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, s) : launch_gat_bwd<BF, 32, 1>(a, s);
+    else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, s) : launch_gat_bwd<BF, 16, 1>(a, s);
+    else if constexpr (BF) H == 4 ? launch_gat_bwd<BF, 8, 4>(a, s) : H == 2 ? launch_gat_bwd<BF, 8, 2>(a, s) : launch_gat_bwd<BF, 8, 1>(a, s);
 }
 
 // Two weighted column sums of one matrix in a pass over it (the gradients of the two attention vectors):
 //     out_a[f] = sum_{i < n_a} wa[i] M[i, f]        out_b[f] = sum_{i < n_b} wb[i] M[i, f]        n_a <= n_b
+// with weights of its own for every head (block of columns).
 // Slabs of rows, a partial row of each sum per slab, and the partial rows added in slab order in double: no atomics.
 // HBM-bound once every compute unit has rows to read.  About 1,024 slabs (four workgroups per compute unit), of 64 to
 // 1,024 rows.  95,000 rows of 64 floats, both sums: 8.6 us (two passes with slabs of 1,024 rows, a row per wavefront
@@ -839,7 +914,8 @@ struct ColSums {
     const char* M; int64_t ldm;
     const float *wa, *wb;
     int64_t n_a, n_b;
-    int F;
+    int F;                           // columns of M: heads of `per` columns, head h weighted by w[i heads + h]
+    int per, heads;
     int slab;
     int64_t n_slabs;
     float* partial;                  // [n_slabs][2][F]
@@ -861,8 +937,8 @@ __global__ __launch_bounds__(256) void colsum_partial_kernel(ColSums a) {
         float sa = 0.f, sb = 0.f;
         for (int64_t i = r0; i < r1; ++i) {
             const float x = ld<BF>(a.M, i * a.ldm + f);
-            if (i < a.n_a) sa = fmaf(a.wa[i], x, sa);
-            sb = fmaf(a.wb[i], x, sb);
+            if (i < a.n_a) sa = fmaf(a.wa[i * a.heads + f / a.per], x, sa);
+            sb = fmaf(a.wb[i * a.heads + f / a.per], x, sb);
         }
         a.partial[(2 * (int64_t)blockIdx.x) * a.F + f] = sa;
         a.partial[(2 * (int64_t)blockIdx.x + 1) * a.F + f] = sb;
@@ -881,6 +957,7 @@ __global__ __launch_bounds__(256) void colsum_partial_vec_kernel(ColSums a) {
     for (int i = 0; i < E; ++i) sa[i] = sb[i] = 0.f;
     if (piece * E < a.F) {
         const char* base = a.M + (int64_t)piece * E * EB;
+        const int head = piece * E / a.per;
         for (int64_t i0 = r0 + team; i0 < r1; i0 += U * T) {
             u32x4 r[U];
             float wa[U], wb[U];
@@ -890,8 +967,8 @@ __global__ __launch_bounds__(256) void colsum_partial_vec_kernel(ColSums a) {
                 const bool in = i < r1;
                 r[j] = u32x4{0u, 0u, 0u, 0u};
                 if (in) r[j] = *reinterpret_cast<const u32x4*>(base + i * a.ldm * EB);
-                wa[j] = in && i < a.n_a ? a.wa[i] : 0.f;
-                wb[j] = in ? a.wb[i] : 0.f;
+                wa[j] = in && i < a.n_a ? a.wa[i * a.heads + head] : 0.f;
+                wb[j] = in ? a.wb[i * a.heads + head] : 0.f;
             }
 #pragma unroll
             for (int j = 0; j < U; ++j) {
@@ -1081,10 +1158,84 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
     return GAS_OK;
 }
 
+int64_t gas_gat_aggregate_bwd_heads_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F, int32_t heads) {
+    if (n_rows < 0 || n_cols <= 0 || nnz < 0 || F <= 0 || heads <= 0) return 0;
+    const int64_t H = heads < 4 ? heads : 4;               // heads taken together
+    return align_up(nnz * H * 8) + align_up(n_rows * H * 4) + align_up(n_cols * H * 4) +
+           align_up(colsum_scratch_floats(n_cols, (int)(H * F)) * 4);
+}
+
 int64_t gas_gat_aggregate_bwd_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F) {
-    if (n_rows < 0 || n_cols <= 0 || nnz < 0 || F <= 0) return 0;
-    return 4 * align_up(nnz * 4) + align_up(n_rows * 4) + align_up(n_cols * 4) +
-           align_up(colsum_scratch_floats(n_cols, F) * 4);
+    return gas_gat_aggregate_bwd_heads_workspace(n_rows, n_cols, nnz, F, 1);
+}
+
+gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                       const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
+                                       int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
+                                       int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
+                                       const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
+                                       void* workspace, int64_t workspace_bytes, void* stream) {
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_gat_aggregate_bwd: unknown dtype %d", (int)dt);
+    GAS_REQUIRE(n_rows >= 0 && n_cols >= n_rows && n_out >= 0 && n_out <= n_cols && nnz >= 0 && F > 0 && heads > 0 &&
+                F <= 64 * kMaxPerLane, "gas_gat_aggregate_bwd: n_rows=%lld n_cols=%lld n_out=%lld nnz=%lld F=%d (F <= %d) heads=%d",
+                (long long)n_rows, (long long)n_cols, (long long)n_out, (long long)nnz, F, 64 * kMaxPerLane, heads);
+    GAS_REQUIRE(n_cols <= 0x7FFFFFFFLL, "gas_gat_aggregate_bwd: too many rows for one launch");
+    if (n_cols == 0) return GAS_OK;
+    GAS_REQUIRE(rowptr && colptr && P && a_dst && a_src && GZ && Ga_dst && Ga_src && (nnz == 0 || (col && row && csc_pos)),
+                "gas_gat_aggregate_bwd: null pointer");
+    const int64_t width = (int64_t)heads * F;
+    GAS_REQUIRE(ldp >= width && ldgz >= width && (n_out == 0 || (GP && ldgp >= width)),
+                "gas_gat_aggregate_bwd: null output or row stride smaller than the row");
+    const int64_t need = gas_gat_aggregate_bwd_heads_workspace(n_rows, n_cols, nnz, F, heads);
+    GAS_REQUIRE(workspace && workspace_bytes >= need, "gas_gat_aggregate_bwd: workspace of %lld bytes needed, %lld given",
+                (long long)need, (long long)workspace_bytes);
+    GAS_REQUIRE(!plan_t || plan_t->n_rows == n_out, "gas_gat_aggregate_bwd: the plan is for %lld columns, n_out is %lld",
+                plan_t ? (long long)plan_t->n_rows : 0ll, (long long)n_out);
+    GAS_REQUIRE(!plan_t || plan_t->nnz <= nnz, "gas_gat_aggregate_bwd: the plan has %lld entries, the pattern %lld",
+                plan_t ? (long long)plan_t->nnz : 0ll, (long long)nnz);
+    hipStream_t s = (hipStream_t)stream;
+    const bool bf = dt == GAS_BF16;
+    const int eb = elem_bytes(dt);
+    const bool vec = vec_rows(dt, F, {P, GZ, GP, a_dst, a_src}, {ldp, ldgz, ldgp});
+    const int H = vec ? gat_heads_together(bf ? gat_team<true>(F) : gat_team<false>(F), heads) : 1;
+    GatBwdArgs a;
+    a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;
+    a.colptr = colptr; a.row = row; a.csc_pos = csc_pos; a.n_cols = n_cols; a.n_out = n_out;
+    a.P = static_cast<const char*>(P); a.ldp = ldp;
+    a.a_dst = static_cast<const char*>(a_dst); a.a_src = static_cast<const char*>(a_src);
+    a.GZ = static_cast<const char*>(GZ); a.ldgz = ldgz;
+    a.GP = static_cast<char*>(GP); a.ldgp = ldgp;
+    a.F = F; a.slope = negative_slope;
+    char* w = static_cast<char*>(workspace);
+    a.pair = reinterpret_cast<f32x2_t*>(w);
+    a.alpha = reinterpret_cast<float*>(w); a.dt = a.alpha + nnz; w += align_up(nnz * H * 8);
+    a.csum = reinterpret_cast<float*>(w); w += align_up(n_rows * H * 4);
+    a.tsum = reinterpret_cast<float*>(w); w += align_up(n_cols * H * 4);
+    float* colsum_scratch = reinterpret_cast<float*>(w);
+    for (int32_t h = 0; h < heads; h += H) {
+        if (vec) {
+            if (bf) launch_gat_bwd_heads<true>(a, H, s);
+            else launch_gat_bwd_heads<false>(a, H, s);
+        } else {
+            if (n_rows > 0) {
+                if (bf) hipLaunchKernelGGL(gat_bwd_rows_kernel<true>, dim3((unsigned)n_rows), dim3(64), 0, s, a);
+                else hipLaunchKernelGGL(gat_bwd_rows_kernel<false>, dim3((unsigned)n_rows), dim3(64), 0, s, a);
+            }
+            if (bf) hipLaunchKernelGGL(gat_bwd_cols_kernel<true>, dim3((unsigned)n_cols), dim3(64), 0, s, a);
+            else hipLaunchKernelGGL(gat_bwd_cols_kernel<false>, dim3((unsigned)n_cols), dim3(64), 0, s, a);
+        }
+        // Ga_dst = sum over the in-batch nodes of (row total of dt) P[v];  Ga_src = sum over all nodes of (column total) P[u]
+        ColSums c{};
+        c.M = a.P; c.ldm = ldp;
+        c.wa = a.csum; c.n_a = n_rows; c.wb = a.tsum; c.n_b = n_cols;
+        c.F = H * F; c.per = F; c.heads = H; c.out_a = Ga_dst + (int64_t)h * F; c.out_b = Ga_src + (int64_t)h * F;
+        column_sums(c, bf, vec, colsum_scratch, s);
+        GAS_CHECK_HIP(hipGetLastError());
+        const int64_t step = (int64_t)H * F * eb;
+        a.P += step; a.a_dst += step; a.a_src += step; a.GZ += step;
+        if (a.GP) a.GP += step;
+    }
+    return GAS_OK;
 }
 
 gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
@@ -1093,86 +1244,9 @@ gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
                                  const void* a_dst, const void* a_src, float negative_slope, const void* GZ,
                                  int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src, void* workspace,
                                  int64_t workspace_bytes, void* stream) {
-    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_gat_aggregate_bwd: unknown dtype %d", (int)dt);
-    GAS_REQUIRE(n_rows >= 0 && n_cols >= n_rows && n_out >= 0 && n_out <= n_cols && nnz >= 0 && F > 0 &&
-                F <= 64 * kMaxPerLane, "gas_gat_aggregate_bwd: n_rows=%lld n_cols=%lld n_out=%lld nnz=%lld F=%d (F <= %d)",
-                (long long)n_rows, (long long)n_cols, (long long)n_out, (long long)nnz, F, 64 * kMaxPerLane);
-    GAS_REQUIRE(n_cols <= 0x7FFFFFFFLL, "gas_gat_aggregate_bwd: too many rows for one launch");
-    if (n_cols == 0) return GAS_OK;
-    GAS_REQUIRE(rowptr && colptr && P && a_dst && a_src && GZ && Ga_dst && Ga_src && (nnz == 0 || (col && row && csc_pos)),
-                "gas_gat_aggregate_bwd: null pointer");
-    GAS_REQUIRE(ldp >= F && ldgz >= F && (n_out == 0 || (GP && ldgp >= F)), "gas_gat_aggregate_bwd: null output or row stride smaller than F");
-    GAS_REQUIRE(workspace && workspace_bytes >= gas_gat_aggregate_bwd_workspace(n_rows, n_cols, nnz, F),
-                "gas_gat_aggregate_bwd: workspace of %lld bytes needed, %lld given",
-                (long long)gas_gat_aggregate_bwd_workspace(n_rows, n_cols, nnz, F), (long long)workspace_bytes);
-    GAS_REQUIRE(!plan_t || plan_t->n_rows == n_out, "gas_gat_aggregate_bwd: the plan is for %lld columns, n_out is %lld",
-                plan_t ? (long long)plan_t->n_rows : 0ll, (long long)n_out);
-    char* w = static_cast<char*>(workspace);
-    GatBwdArgs a;
-    a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;
-    a.colptr = colptr; a.row = row; a.csc_pos = csc_pos; a.n_cols = n_cols; a.n_out = n_out;
-    a.P = static_cast<const char*>(P); a.ldp = ldp;
-    a.a_dst = static_cast<const char*>(a_dst); a.a_src = static_cast<const char*>(a_src);
-    a.GZ = static_cast<const char*>(GZ); a.ldgz = ldgz;
-    a.GP = static_cast<char*>(GP); a.ldgp = ldgp;
-    a.alpha = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
-    a.dt = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
-    float* val_t = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
-    float* dt_t = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
-    a.csum = reinterpret_cast<float*>(w); w += align_up(n_rows * 4);
-    a.tsum = reinterpret_cast<float*>(w); w += align_up(n_cols * 4);
-    float* colsum_scratch = reinterpret_cast<float*>(w);
-    a.F = F; a.slope = negative_slope;
-    hipStream_t s = (hipStream_t)stream;
-    const bool bf = dt == GAS_BF16;
-    const bool vec = vec_rows(dt, F, {P, GZ, GP, a_dst, a_src}, {ldp, ldgz, ldgp});
-    if (plan_t && n_out > 0 && vec) {
-        if (n_rows > 0) {
-            const int pieces = F / (bf ? 8 : 4);
-            if (bf) {
-                if (pieces <= 16) launch_gat_bwd_rows<true, 16>(a, s);
-                else if (pieces <= 32) launch_gat_bwd_rows<true, 32>(a, s);
-                else launch_gat_bwd_rows<true, 64>(a, s);
-            } else {
-                if (pieces <= 16) launch_gat_bwd_rows<false, 16>(a, s);
-                else if (pieces <= 32) launch_gat_bwd_rows<false, 32>(a, s);
-                else launch_gat_bwd_rows<false, 64>(a, s);
-            }
-        }
-        GAS_REQUIRE(plan_t->nnz <= nnz, "gas_gat_aggregate_bwd: the plan has %lld entries, the pattern %lld",
-                    (long long)plan_t->nnz, (long long)nnz);
-        if (nnz > 0)
-            hipLaunchKernelGGL(permute_entries_kernel, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, s, a.alpha, a.dt,
-                               csc_pos, nnz, val_t, dt_t);
-        hipLaunchKernelGGL(column_totals_kernel, dim3((unsigned)((n_cols + 255) / 256)), dim3(256), 0, s, colptr, dt_t, n_cols,
-                           a.tsum);
-        hipLaunchKernelGGL(column_totals_long_kernel, dim3(long_row_blocks(n_cols)), dim3(64 * kLongWaves), 0, s, colptr, dt_t,
-                           n_cols, a.tsum);
-        GAS_CHECK_HIP(hipGetLastError());
-        // GP[u] = sum over the entries (v, u) of alpha GZ[v]: the backward aggregation with the attention weights
-        // as coefficients, in the order of the CSC copy; then the two rank-one terms
-        const gas_status st = gas_spmm_t(plan_t, colptr, row, val_t, 0.f, 1.f, 0, GZ, ldgz, dt, F, GP, ldgp, dt, stream);
-        if (st != GAS_OK) return st;
-        const int64_t pieces = n_out * (F / (bf ? 8 : 4));
-        GAS_REQUIRE((pieces + 255) / 256 <= 0x7FFFFFFFLL, "gas_gat_aggregate_bwd: output too large for one launch");
-        if (bf) hipLaunchKernelGGL(gat_bwd_rank_one_kernel<true>, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
-        else hipLaunchKernelGGL(gat_bwd_rank_one_kernel<false>, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
-    } else {
-        if (n_rows > 0) {
-            if (bf) hipLaunchKernelGGL(gat_bwd_rows_kernel<true>, dim3((unsigned)n_rows), dim3(64), 0, s, a);
-            else hipLaunchKernelGGL(gat_bwd_rows_kernel<false>, dim3((unsigned)n_rows), dim3(64), 0, s, a);
-        }
-        if (bf) hipLaunchKernelGGL(gat_bwd_cols_kernel<true>, dim3((unsigned)n_cols), dim3(64), 0, s, a);
-        else hipLaunchKernelGGL(gat_bwd_cols_kernel<false>, dim3((unsigned)n_cols), dim3(64), 0, s, a);
-    }
-    // Ga_dst = sum over the in-batch nodes of (row total of dt) P[v];  Ga_src = sum over all nodes of (column total) P[u]
-    ColSums c{};
-    c.M = a.P; c.ldm = ldp;
-    c.wa = a.csum; c.n_a = n_rows; c.wb = a.tsum; c.n_b = n_cols;
-    c.F = F; c.out_a = Ga_dst; c.out_b = Ga_src;
-    column_sums(c, bf, vec, colsum_scratch, s);
-    GAS_CHECK_HIP(hipGetLastError());
-    return GAS_OK;
+    return gas_gat_aggregate_bwd_heads(plan_t, rowptr, col, n_rows, colptr, row, csc_pos, n_cols, n_out, nnz, P, ldp, dt, F, 1,
+                                       a_dst, a_src, negative_slope, GZ, ldgz, GP, ldgp, Ga_dst, Ga_src, workspace,
+                                       workspace_bytes, stream);
 }
 
 }  // extern "C"

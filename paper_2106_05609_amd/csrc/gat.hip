@@ -2,7 +2,8 @@
 // entries of a row and the weighted sum of the gathered rows in ONE pass (running maximum and running sum,
 // rescaled block by block), so every neighbour row is gathered once.  The score of an entry needs the whole
 // gathered row, which a wavefront holds across its lanes: the dot product with the attention vector is a
-// reduction over the lanes.  HBM-bound like the other aggregations.
+// reduction over the lanes.  HBM-bound like the other aggregations.  Several heads side by side in a row are taken
+// together by teams of lanes: a row is gathered once, not once per head.
 #include "wave.h"
 
 namespace gas {
@@ -14,16 +15,16 @@ struct GatArgs {
     const char* P; int64_t ldp;
     const char* a_dst; const char* a_src;
     char* Z; int64_t ldz;
-    int F;
+    int F;                                        // width of a head; head h has columns h F .. of P and Z
     float slope;
     int relu;                                     // ReLU on the output row
 };
 
 // Rows of at most 64 pieces of 16 bytes, G = 16, 32 or 64 lanes per row (at least the number of pieces).  A
-// wavefront's S = 64 / G teams of G lanes each hold the whole row and take the entries in turn (team t the entries
-// t, t + S, ... of every block of 64), eight at a time per team: gathers, scores (one reduction over the team's
-// lanes for all eight), one rescale of the running sums to the new maximum, then the weighted adds.  Every team
-// keeps its own running maximum and sums, and the teams' states are merged pair by pair at the end.  A row of
+// wavefront's S = 64 / (G H) slots of H teams of G lanes each hold the whole row, a head per team, and take the entries
+// in turn (slot t the entries t, t + S, ... of every block of 64), eight at a time per slot: gathers, scores (one
+// reduction over the team's lanes for all eight), one rescale of the running sums to the new maximum, then the weighted
+// adds.  Every team keeps its own running maximum and sums, and the slots' states are merged pair by pair at the end.  A row of
 // more than kLongRow entries is shared by the kLongWaves wavefronts of a workgroup in the same way, block of 64
 // entries by block, and their states are merged in wavefront order.  Which lane takes which entry depends on the
 // row's length and the width alone, so the result is the same bits on every run.
@@ -42,21 +43,23 @@ __device__ __forceinline__ void merge_state(float& m, float& l, float (&acc)[E],
 
 // The entries of the blocks first, first + stride, ... of row v = [b, e), b < e: afterwards every team of the
 // wavefront holds the merged state of all of them.
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, int e, int first, int stride,
                                            float& m, float& l, float (&acc)[Elems<BF>::E]) {
-    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = 64 / G;
-    const int lane = threadIdx.x & 63, team = lane / G, tl = lane % G;
-    const bool on = tl * E < a.F;
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = HeadTeams<G, H>::kSlots;
+    const HeadTeams<G, H> ht;
+    const int lane = threadIdx.x & 63, team = ht.slot;
+    const bool on = ht.tl * E < a.F;
+    const int64_t own = (int64_t)ht.head * a.F + ht.tl * E;      // the lane's first column
     float ad[E], ar[E], x[E];
     u32x4 t = {0u, 0u, 0u, 0u};
-    if (on) t = *reinterpret_cast<const u32x4*>(a.a_dst + (int64_t)tl * E * EB);
+    if (on) t = *reinterpret_cast<const u32x4*>(a.a_dst + own * EB);
     unpack<BF>(t, ad);
     t = u32x4{0u, 0u, 0u, 0u};
-    if (on) t = *reinterpret_cast<const u32x4*>(a.a_src + (int64_t)tl * E * EB);
+    if (on) t = *reinterpret_cast<const u32x4*>(a.a_src + own * EB);
     unpack<BF>(t, ar);
     t = u32x4{0u, 0u, 0u, 0u};
-    if (on) t = *reinterpret_cast<const u32x4*>(a.P + (v * a.ldp + (int64_t)tl * E) * EB);
+    if (on) t = *reinterpret_cast<const u32x4*>(a.P + (v * a.ldp + own) * EB);
     unpack<BF>(t, x);
     float sv = 0.f;
 #pragma unroll
@@ -79,7 +82,7 @@ __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, i
                 else c = __shfl(mine, kk & 63);
                 r[j] = u32x4{0u, 0u, 0u, 0u};
                 if (on && kk < cnt)
-                    r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + (int64_t)tl * E) * EB);
+                    r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + own) * EB);
             }
             float sc[U], mb = m;
 #pragma unroll
@@ -99,24 +102,28 @@ __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, i
             }
             if (mb > -INFINITY) {                         // a team may have had no entry of its own yet
                 const float scale = expf(m - mb);         // m = -inf at the start: scale 0 on sums that are 0
-                l *= scale;
+                // the eight entries are summed by themselves first: a sum over a long row is then one of few large terms
+                float lb = 0.f, part[E];
 #pragma unroll
-                for (int i = 0; i < E; ++i) acc[i] *= scale;
+                for (int i = 0; i < E; ++i) part[i] = 0.f;
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
                     const float p = expf(sc[j] - mb);     // 0 for the padding entries
-                    l += p;
+                    lb += p;
                     unpack<BF>(r[j], x);
 #pragma unroll
-                    for (int i = 0; i < E; ++i) acc[i] += p * x[i];
+                    for (int i = 0; i < E; ++i) part[i] += p * x[i];
                 }
+                l = l * scale + lb;
+#pragma unroll
+                for (int i = 0; i < E; ++i) acc[i] = acc[i] * scale + part[i];
                 m = mb;
             }
         }
     }
     // both partners of an exchange compute the same merged state
 #pragma unroll
-    for (int o = G; o < 64; o <<= 1) {
+    for (int o = G * H; o < 64; o <<= 1) {
         const float mo = __shfl_xor(m, o), lo = __shfl_xor(l, o);
         float acco[E];
 #pragma unroll
@@ -125,41 +132,41 @@ __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, i
     }
 }
 
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __device__ __forceinline__ void gat_finish(const GatArgs& a, int64_t v, float l, float (&acc)[Elems<BF>::E]) {
     constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4;
-    const int lane = threadIdx.x & 63;
-    if (lane >= G || lane * E >= a.F) return;         // team 0 stores
+    const HeadTeams<G, H> ht;
+    if (ht.slot > 0 || ht.tl * E >= a.F) return;      // slot 0 stores
     const float inv = 1.f / l;
 #pragma unroll
     for (int i = 0; i < E; ++i) {
         acc[i] *= inv;
         if (a.relu) acc[i] = fmaxf(acc[i], 0.f);
     }
-    __builtin_nontemporal_store(pack<BF>(acc), reinterpret_cast<u32x4*>(a.Z + (v * a.ldz + (int64_t)lane * E) * EB));
+    __builtin_nontemporal_store(pack<BF>(acc), reinterpret_cast<u32x4*>(a.Z + (v * a.ldz + (int64_t)ht.head * a.F + ht.tl * E) * EB));
 }
 
 // one wavefront per row; long rows are left to gat_long_rows_kernel
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __global__ __launch_bounds__(64) void gat_rows_kernel(GatArgs a) {
     constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4;
     const int64_t v = blockIdx.x;
-    const int lane = threadIdx.x;
     const int b = a.rowptr[v], e = a.rowptr[v + 1];
     if (e == b) {
-        if (lane < G && lane * E < a.F)
-            *reinterpret_cast<u32x4*>(a.Z + (v * a.ldz + (int64_t)lane * E) * EB) = u32x4{0u, 0u, 0u, 0u};
+        const HeadTeams<G, H> ht;
+        if (ht.slot == 0 && ht.tl * E < a.F)
+            *reinterpret_cast<u32x4*>(a.Z + (v * a.ldz + (int64_t)ht.head * a.F + ht.tl * E) * EB) = u32x4{0u, 0u, 0u, 0u};
         return;
     }
     if (e - b > kLongRow) return;
     float m, l, acc[E];
-    gat_gather<BF, G>(a, v, b, e, 0, 1, m, l, acc);
-    gat_finish<BF, G>(a, v, l, acc);
+    gat_gather<BF, G, H>(a, v, b, e, 0, 1, m, l, acc);
+    gat_finish<BF, G, H>(a, v, l, acc);
 }
 
 // Workgroup w looks at the rows w, w + gridDim.x, ... (512 of them at a time), and every row of more than kLongRow
 // entries among them is gathered by all its wavefronts together.
-template <bool BF, int G>
+template <bool BF, int G, int H>
 __global__ __launch_bounds__(64 * kLongWaves) void gat_long_rows_kernel(GatArgs a) {
     constexpr int E = Elems<BF>::E, T = 64 * kLongWaves;
     __shared__ int queue[T];
@@ -172,7 +179,7 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_long_rows_kernel(GatArgs 
             const int64_t v = queue[q];
             const int b = a.rowptr[v], e = a.rowptr[v + 1];
             float m, l, acc[E];
-            gat_gather<BF, G>(a, v, b, e, w, kLongWaves, m, l, acc);
+            gat_gather<BF, G, H>(a, v, b, e, w, kLongWaves, m, l, acc);
             if (w > 0) {
                 red[w][E][lane] = m;
                 red[w][E + 1][lane] = l;
@@ -187,26 +194,28 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_long_rows_kernel(GatArgs 
                     for (int i = 0; i < E; ++i) acco[i] = red[o][i][lane];
                     merge_state<E>(m, l, acc, red[o][E][lane], red[o][E + 1][lane], acco);
                 }
-                gat_finish<BF, G>(a, v, l, acc);
+                gat_finish<BF, G, H>(a, v, l, acc);
             }
             __syncthreads();
         }
     }
 }
 
-template <bool BF, int G>
+template <bool BF, int G, int H>
 void launch_rows(const GatArgs& a, hipStream_t s) {
-    hipLaunchKernelGGL((gat_rows_kernel<BF, G>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
+    hipLaunchKernelGGL((gat_rows_kernel<BF, G, H>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
     const unsigned blocks = long_row_blocks(a.n_rows);
-    hipLaunchKernelGGL((gat_long_rows_kernel<BF, G>), dim3(blocks), dim3(64 * kLongWaves), 0, s, a);
+    hipLaunchKernelGGL((gat_long_rows_kernel<BF, G, H>), dim3(blocks), dim3(64 * kLongWaves), 0, s, a);
 }
 
+// H heads of at most 64 / H teams of lanes
 template <bool BF>
-void launch_vec(const GatArgs& a, hipStream_t s) {
-    const int pieces = a.F / Elems<BF>::E;            // at most 64
-    if (pieces <= 16) launch_rows<BF, 16>(a, s);
-    else if (pieces <= 32) launch_rows<BF, 32>(a, s);
-    else launch_rows<BF, 64>(a, s);
+void launch_vec(const GatArgs& a, int H, hipStream_t s) {
+    const int G = gat_team<BF>(a.F);
+    if (G == 64) launch_rows<BF, 64, 1>(a, s);
+    else if (G == 32) H == 2 ? launch_rows<BF, 32, 2>(a, s) : launch_rows<BF, 32, 1>(a, s);
+    else if (G == 16) H == 4 ? launch_rows<BF, 16, 4>(a, s) : H == 2 ? launch_rows<BF, 16, 2>(a, s) : launch_rows<BF, 16, 1>(a, s);
+    else if constexpr (BF) H == 4 ? launch_rows<BF, 8, 4>(a, s) : H == 2 ? launch_rows<BF, 8, 2>(a, s) : launch_rows<BF, 8, 1>(a, s);
 }
 
 // any alignment, widths up to 64 * NE: lane l owns elements l, l + 64, ...; one entry at a time
@@ -275,32 +284,45 @@ gas_status launch_generic(const GatArgs& a, hipStream_t s) {
 
 using namespace gas;
 
-extern "C" gas_status gas_gat_aggregate(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* P,
-                                        int64_t ldp, gas_dtype dt, int32_t F, const void* a_dst, const void* a_src,
-                                        float negative_slope, int relu, void* Z, int64_t ldz, void* stream) {
-    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_gat_aggregate: unknown dtype %d", (int)dt);
-    GAS_REQUIRE(n_rows >= 0 && F > 0, "gas_gat_aggregate: n_rows=%lld F=%d", (long long)n_rows, F);
-    GAS_REQUIRE(F <= 1024, "gas_gat_aggregate: F=%d exceeds 1024", F);
+extern "C" gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* P,
+                                              int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
+                                              const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz,
+                                              void* stream) {
+    const char* who = "gas_gat_aggregate";
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    GAS_REQUIRE(n_rows >= 0 && F > 0 && heads > 0, "%s: n_rows=%lld F=%d heads=%d", who, (long long)n_rows, F, heads);
+    GAS_REQUIRE(F <= 1024, "%s: F=%d exceeds 1024", who, F);
     if (n_rows == 0) return GAS_OK;
-    GAS_REQUIRE(rowptr && col && P && a_dst && a_src && Z, "gas_gat_aggregate: null pointer");
-    GAS_REQUIRE(ldp >= F && ldz >= F, "gas_gat_aggregate: row stride smaller than the row");
-    GAS_REQUIRE(Z != P, "gas_gat_aggregate: the output must not alias the input");
-    GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL, "gas_gat_aggregate: too many rows for one launch");
+    GAS_REQUIRE(rowptr && col && P && a_dst && a_src && Z, "%s: null pointer", who);
+    GAS_REQUIRE(ldp >= (int64_t)heads * F && ldz >= (int64_t)heads * F, "%s: row stride smaller than the row", who);
+    GAS_REQUIRE(Z != P, "%s: the output must not alias the input", who);
+    GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL, "%s: too many rows for one launch", who);
     GatArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;
     a.P = static_cast<const char*>(P); a.ldp = ldp;
     a.a_dst = static_cast<const char*>(a_dst); a.a_src = static_cast<const char*>(a_src);
     a.Z = static_cast<char*>(Z); a.ldz = ldz;
     a.F = F; a.slope = negative_slope; a.relu = relu;
-    const int e = dt == GAS_BF16 ? 8 : 4;
+    const int e = dt == GAS_BF16 ? 8 : 4, eb = elem_bytes(dt);
     hipStream_t s = (hipStream_t)stream;
     const bool vec = F % e == 0 && F <= 64 * e && ldp % e == 0 && ldz % e == 0 && aligned16(P) && aligned16(Z) &&
                      aligned16(a_dst) && aligned16(a_src);
-    if (vec) {
-        if (dt == GAS_BF16) launch_vec<true>(a, s);
-        else launch_vec<false>(a, s);
+    const int H = vec ? gat_heads_together(dt == GAS_BF16 ? gat_team<true>(F) : gat_team<false>(F), heads) : 1;
+    for (int32_t h = 0; h < heads; h += H) {
+        gas_status st = GAS_OK;
+        if (vec && dt == GAS_BF16) launch_vec<true>(a, H, s);
+        else if (vec) launch_vec<false>(a, H, s);
+        else st = dt == GAS_BF16 ? launch_generic<true>(a, s) : launch_generic<false>(a, s);
+        if (st != GAS_OK) return st;
         GAS_CHECK_HIP(hipGetLastError());
-        return GAS_OK;
+        a.P += (int64_t)H * F * eb; a.Z += (int64_t)H * F * eb;
+        a.a_dst += (int64_t)H * F * eb; a.a_src += (int64_t)H * F * eb;
     }
-    return dt == GAS_BF16 ? launch_generic<true>(a, s) : launch_generic<false>(a, s);
+    return GAS_OK;
+}
+
+extern "C" gas_status gas_gat_aggregate(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* P,
+                                        int64_t ldp, gas_dtype dt, int32_t F, const void* a_dst, const void* a_src,
+                                        float negative_slope, int relu, void* Z, int64_t ldz, void* stream) {
+    return gas_gat_aggregate_heads(rowptr, col, n_rows, P, ldp, dt, F, 1, a_dst, a_src, negative_slope, relu, Z, ldz, stream);
 }

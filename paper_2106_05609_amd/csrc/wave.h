@@ -48,11 +48,11 @@ __device__ __forceinline__ float team_sum(float v) {
     return v;
 }
 
-// wave_sum8 inside every team of G = 16 or 32 lanes (G = 64: wave_sum8 itself): the same halving exchanges on the team's three upper lane
+// wave_sum8 inside every team of G = 8, 16 or 32 lanes (G = 64: wave_sum8 itself): the same halving exchanges on the team's three upper lane
 // bits, the remaining steps on the lower ones, and every lane reads the eight totals back from its own team.
 template <int G>
 __device__ __forceinline__ void team_sum8(float (&s)[8]) {
-    static_assert(G == 16 || G == 32 || G == 64, "teams of 16, 32 or 64 lanes");
+    static_assert(G == 8 || G == 16 || G == 32 || G == 64, "teams of 8 to 64 lanes");
     if constexpr (G == 64) {
         wave_sum8(s);
         return;
@@ -77,6 +77,47 @@ __device__ __forceinline__ void team_sum8(float (&s)[8]) {
 #pragma unroll
     for (int j = 0; j < 8; ++j)
         s[j] = __shfl(t, base + (G / 2) * ((j >> 2) & 1) + (G / 4) * ((j >> 1) & 1) + (G / 8) * (j & 1));
+}
+
+// ---- several attention heads in one wavefront
+// The row of a node holds H heads side by side.  Team t = lane / G of a wavefront has head t % H of the entry that
+// slot t / H works on, so the teams of a slot load one contiguous row, and a head's sums never leave its teams.
+template <int G, int H>
+struct HeadTeams {
+    static_assert(G * H <= 64, "the heads of an entry fit a wavefront");
+    static constexpr int kSlots = 64 / (G * H);
+    int tl, head, slot;
+    __device__ __forceinline__ HeadTeams() {
+        const int lane = threadIdx.x & 63;
+        tl = lane % G;
+        head = lane / G % H;
+        slot = lane / (G * H);
+    }
+    // the same head's lanes of the other slots, added / compared pair by pair
+    static __device__ __forceinline__ float over_slots(float v) {
+#pragma unroll
+        for (int o = G * H; o < 64; o <<= 1) v += __shfl_xor(v, o);
+        return v;
+    }
+    static __device__ __forceinline__ float max_over_slots(float v) {
+#pragma unroll
+        for (int o = G * H; o < 64; o <<= 1) v = fmaxf(v, __shfl_xor(v, o));
+        return v;
+    }
+};
+
+// A value per head (the same in all lanes of the head) over the W wavefronts of a workgroup in wavefront order; every
+// thread calls it; red: W * 4 floats.
+template <int W, bool MAX>
+__device__ __forceinline__ float across_waves_by_head(float x, int head, bool writer, float (*red)[4]) {
+    if constexpr (W == 1) return x;
+    if (writer) red[threadIdx.x >> 6][head] = x;
+    __syncthreads();
+    float r = red[0][head];
+#pragma unroll
+    for (int o = 1; o < W; ++o) r = MAX ? fmaxf(r, red[o][head]) : r + red[o][head];
+    __syncthreads();
+    return r;
 }
 
 // ---- rows too long for one wavefront
@@ -132,6 +173,20 @@ template <bool BF>
 __device__ __forceinline__ u32x4 pack(const float (&x)[Elems<BF>::E]) {
     if constexpr (BF) return u32x4{pack_bf16(x[0], x[1]), pack_bf16(x[2], x[3]), pack_bf16(x[4], x[5]), pack_bf16(x[6], x[7])};
     else return u32x4{__float_as_uint(x[0]), __float_as_uint(x[1]), __float_as_uint(x[2]), __float_as_uint(x[3])};
+}
+
+// ---- how many lanes a head takes (the team), and how many heads a wavefront takes together
+template <bool BF>
+inline int gat_team(int32_t F) {
+    const int pieces = F / Elems<BF>::E;              // whole pieces, at most 64
+    return BF && pieces <= 8 ? 8 : (pieces <= 16 ? 16 : (pieces <= 32 ? 32 : 64));
+}
+// Powers of two: team numbers split by shifts.  95,000 nodes, 550,000 entries, four heads of 64 floats: 66 us, a
+// launch per head 4 x 37 us.
+inline int gat_heads_together(int team, int32_t heads) {
+    int H = 1;
+    while (H < 4 && heads % (2 * H) == 0 && team * 2 * H <= 64) H *= 2;
+    return H;
 }
 
 }  // namespace gas

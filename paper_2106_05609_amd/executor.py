@@ -735,8 +735,7 @@ def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope
     weights[l] = (W, a_dst, a_src); bg: the batch subgraph with self-loops.  Per layer: P = X W for every row of
     the mini-batch tensor (gas_linear), then scores, softmax and weighted sum in one pass (gas_gat_aggregate,
     ReLU in its epilogue on all layers but the last), push, pull.  heads > 1: the columns of W, a_dst and a_src are
-    `heads` equal blocks; one gas_gat_aggregate call per head on its block of columns of P (a strided view),
-    writing its block of the output."""
+    `heads` equal blocks, all taken by one gas_gat_aggregate call."""
     dev, dt = x_feat.device, x_feat.dtype
     nb, nv = bg.nb, bg.nv
     x = torch.empty((nv, x_feat.shape[1]), dtype=dt, device=dev)
@@ -750,13 +749,9 @@ def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope
         B.gas_linear(x, w, p)
         x_next = torch.empty((nb if last else nv, w.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
-        fh = w.shape[1] // heads
-        if fh * heads != w.shape[1]:
+        if w.shape[1] % heads:
             raise ValueError("gat_forward_batch: the layer width is not a multiple of the number of heads")
-        for h in range(heads):
-            cols = slice(h * fh, (h + 1) * fh)
-            B.gas_gat_aggregate(bg.rowptr, bg.col, p[:, cols], a_dst[cols], a_src[cols], y[:, cols], negative_slope,
-                                relu=not last)
+        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads)
         if last:
             break
         if do_push:
@@ -857,12 +852,6 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
     L = len(weights)
     kept = []
     y = None
-
-    def blocks(width):
-        fh = width // heads
-        if fh * heads != width:
-            raise ValueError("gat_train_batch: the layer width is not a multiple of the number of heads")
-        return [slice(h * fh, (h + 1) * fh) for h in range(heads)]
     for l in range(1, L + 1):
         w, a_dst, a_src = weights[l - 1]
         last = l == L
@@ -870,8 +859,9 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         B.gas_linear(x, w, p)
         x_next = torch.empty((nb if last else nv, w.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
-        for c in blocks(w.shape[1]):
-            B.gas_gat_aggregate(bg.rowptr, bg.col, p[:, c], a_dst[c], a_src[c], y[:, c], negative_slope, relu=not last)
+        if w.shape[1] % heads:
+            raise ValueError("gat_train_batch: the layer width is not a multiple of the number of heads")
+        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads)
         kept.append((x, p, y))
         if last:
             break
@@ -885,9 +875,8 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         gp = torch.empty_like(p)
         gd = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         gs = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
-        for c in blocks(w.shape[1]):
-            B.gas_gat_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p[:, c], a_dst[c], a_src[c],
-                                    g[:, c], gp[:, c], gd[c], gs[c], negative_slope, plan_t=bg.plan_t_all)
+        B.gas_gat_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, a_dst, a_src, g, gp, gd, gs,
+                                negative_slope, heads=heads)
         grads[l - 1] = (_weight_grad(x, gp), gd, gs)
         if l == 1:
             break

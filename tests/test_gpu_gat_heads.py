@@ -1,0 +1,56 @@
+"""Several attention heads in one call: forward and backward against the oracle head by head, for head widths on both sides
+of a team of lanes and head counts that are and are not taken together, with rows and columns that a workgroup shares."""
+import numpy as np
+import pytest
+import torch
+
+from gas_inputs import rng
+from oracle import ops as oops
+from tests.test_gpu_ops import TOL, _gat_bwd_row_scale, _pattern_with_long_rows
+from tests.util import node_rel_err, to_np
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("F,heads", [(64, 4), (48, 4), (64, 2), (32, 3), (32, 6), (128, 2), (128, 4), (136, 2), (100, 5), (8, 8)])
+def test_heads_in_one_call(dtype, F, heads):
+    import paper_2106_05609_amd as gas
+    nv = 400
+    ptr, col = _pattern_with_long_rows(43, nv, empty_rows=False)
+    col[::2] = 3                                               # a column of 17,000 entries
+    nb, width = ptr.size - 1, F * heads
+    rows = np.repeat(np.arange(nb), np.diff(ptr)).astype(np.int32)
+    pos = np.lexsort((rows, col)).astype(np.int32)
+    colptr = np.concatenate([[0], np.cumsum(np.bincount(col, minlength=nv))]).astype(np.int32)
+    p = rng.normal_matrix(14, 980, nv, width, dtype=dtype) * 0.5
+    a_dst, a_src = (rng.normal(14, s, 0, width, dtype=dtype) * 0.2 for s in (981, 982))
+    gz = rng.normal_matrix(14, 983, nb, width, dtype=dtype)
+    d_ptr, d_col, d_colptr, d_row, d_pos = (torch.from_numpy(a).cuda() for a in (ptr, col, colptr, rows[pos], pos))
+    d_p, d_ad, d_as, d_gz = (t.cuda() for t in (p, a_dst, a_src, gz))
+    z = torch.full((nb, width), float("nan"), dtype=dtype, device="cuda")
+    gas.gas_gat_aggregate(d_ptr, d_col, d_p, d_ad, d_as, z, heads=heads)
+    gp = torch.full((nv, width), float("nan"), dtype=dtype, device="cuda")
+    gd, gs = (torch.full((width,), float("nan"), device="cuda") for _ in range(2))
+    gas.gas_gat_aggregate_bwd(d_ptr, d_col, d_colptr, d_row, d_pos, d_p, d_ad, d_as, d_gz, gp, gd, gs, heads=heads)
+    torch.cuda.synchronize()
+    for h in range(heads):
+        c = slice(h * F, (h + 1) * F)
+        one = [np.ascontiguousarray(to_np(t[:, c].contiguous())) for t in (p, gz)]
+        ad, asr = to_np(a_dst[c].contiguous()), to_np(a_src[c].contiguous())
+        want = oops.gat_aggregate(ptr, col, one[0], ad, asr)
+        assert node_rel_err(to_np(z[:, c]), want) <= TOL[dtype], (h, node_rel_err(to_np(z[:, c]), want))
+        want_p, want_d, want_s = oops.gat_aggregate_bwd(ptr, col, one[0], ad, asr, one[1], nv, 0.2)
+        scale = _gat_bwd_row_scale(ptr, col, one[0], ad, asr, one[1], nb, nv)     # of the sums that cancel
+        assert node_rel_err(to_np(gp[:, c]), want_p, scale=scale) <= TOL[dtype], (h, node_rel_err(to_np(gp[:, c]), want_p, scale=scale))
+        both = max(np.abs(want_d).max(), np.abs(want_s).max())
+        assert np.abs(to_np(gd[c]) - want_d).max() <= TOL[dtype] * both and np.abs(to_np(gs[c]) - want_s).max() <= TOL[dtype] * both
+
+
+def test_head_counts_that_do_not_divide_are_refused():
+    import paper_2106_05609_amd as gas
+    t = torch.zeros(3, 10, device="cuda")
+    ptr, col = torch.zeros(4, dtype=torch.int32, device="cuda"), torch.zeros(0, dtype=torch.int32, device="cuda")
+    for heads in (0, 3):
+        with pytest.raises(ValueError):
+            gas.gas_gat_aggregate(ptr, col, t, t[0], t[0], torch.empty_like(t), heads=heads)
