@@ -113,6 +113,12 @@ def _mlp_in_two(z, w1, w2) -> bool:
     return z.dtype == torch.float32 or z.shape[1] % 8 != 0 or w1.shape[1] % 8 != 0 or w2.shape[1] % 8 != 0
 
 
+def _pushes(do_push, table) -> bool:
+    """Whether a layer's transform stores its rows to the history table as well: not to host memory, which the row copy
+    writes with whole lines and few workgroups."""
+    return do_push and not isinstance(table, B.HostTable)
+
+
 def gcnii_beta(layer: int) -> float:
     return math.log(0.5 / layer + 1.0)
 
@@ -485,7 +491,11 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
                 B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, bg.val, x, table, z)
             else:
                 B.gas_spmm(bg.plan, bg.rowptr, bg.col, bg.val, x, z)
-            B.gas_linear(z, model.weights[l - 1], y, relu=not last)
+            pushed = not last and _pushes(do_push, histories[l - 1])
+            if pushed:
+                B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], relu=True)
+            else:
+                B.gas_linear(z, model.weights[l - 1], y, relu=not last)
         elif model.op == "gin":
             if fused:
                 B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, None, x, table, z, diag=1.0 + model.gin_eps)
@@ -505,7 +515,12 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             else:
                 B.gas_spmm(bg.plan, bg.rowptr, bg.col, bg.val, x, z, s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha)
             beta = gcnii_beta(l)
-            B.gas_linear(z, model.weights[l - 1], y, c_identity=1.0 - beta, c_weight=beta, relu=not last)
+            pushed = not last and _pushes(do_push, histories[l - 1])
+            if pushed:
+                B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], c_identity=1.0 - beta,
+                                  c_weight=beta, relu=True)
+            else:
+                B.gas_linear(z, model.weights[l - 1], y, c_identity=1.0 - beta, c_weight=beta, relu=not last)
         saved.append((z, h, y))
         if last:
             break
@@ -805,11 +820,15 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q)
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
-        B.gas_linear(cat, w2, y, relu=not last)
+        pushed = not last and _pushes(do_push, histories[l - 1])
+        if pushed:
+            B.gas_linear_push(cat, w2, y, bg.n_id[:nb], histories[l - 1], relu=True)
+        else:
+            B.gas_linear(cat, w2, y, relu=not last)
         kept.append((x, p, cat, y))
         if last:
             break
-        _next_input(x_next, bg, histories[l - 1], do_push)
+        _next_input(x_next, bg, histories[l - 1], do_push and not pushed)
         x = x_next
     grads = {}
     g = grad_out(y) if callable(grad_out) else grad_out
