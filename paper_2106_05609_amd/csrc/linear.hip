@@ -4,14 +4,14 @@
 //
 // This is the only dense contraction of the step (the W of the paper's GCN,
 // GCNII and GIN operator equations), so it is the only place MFMA is used.
-// fp32 data uses the bf16 instruction on operands split in three (split.h), bf16 data v_mfma_f32_32x32x16_bf16
-// with fp32 accumulation.
+// fp32 data uses the bf16 instruction on operands split in three (split.h), the fused fp32 MLP
+// v_mfma_f32_32x32x2_f32, bf16 data v_mfma_f32_32x32x16_bf16, all with fp32 accumulation.
 //
 // Tiling: a workgroup of 4 wavefronts (2 x 2) owns a BM x BN tile of Y, each
 // wavefront a sub-tile made of 32x32 MFMA blocks.  K is walked in tiles: the
 // next A (rows of Z) and B (rows of W) tiles are fetched from global memory
 // into registers while the current ones are consumed from LDS.
-//   fp32: A is stored [m][k] so that one 128-bit LDS read gives a lane the four
+//   fused fp32 MLP: A is stored [m][k] so that one 128-bit LDS read gives a lane the four
 //         k values of four consecutive MFMAs; lanes 0-31 and 32-63 of an MFMA
 //         take different k, and A and B agree on which.
 //   bf16: both operands need eight consecutive k per lane.  Z is [m][k]
@@ -114,49 +114,29 @@ template <int BN, bool VEC>
 struct BTileF32 {
     static constexpr int NV = kBK * BN / 4 / 256;
     f32x4 r[NV];
-    // trans: W is [N][K] row-major; a vector then holds 4 consecutive k of one n
-    __device__ __forceinline__ void fetch(const float* W, int K, int N, int k0, int n0, int tid, bool trans = false) {
+    __device__ __forceinline__ void fetch(const float* W, int K, int N, int k0, int n0, int tid) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int idx = tid + 256 * i;
             f32x4 v = {0.f, 0.f, 0.f, 0.f};
-            if (!trans) {
-                const int k = k0 + idx / (BN / 4), n = n0 + 4 * (idx % (BN / 4));
-                if (k < K) {
-                    if constexpr (VEC) {
-                        if (n < N) v = *reinterpret_cast<const f32x4*>(W + (int64_t)k * N + n);
-                    } else {
+            const int k = k0 + idx / (BN / 4), n = n0 + 4 * (idx % (BN / 4));
+            if (k < K) {
+                if constexpr (VEC) {
+                    if (n < N) v = *reinterpret_cast<const f32x4*>(W + (int64_t)k * N + n);
+                } else {
 #pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (n + e < N) v[e] = W[(int64_t)k * N + n + e];
-                    }
-                }
-            } else {
-                const int n = n0 + idx / (kBK / 4), k = k0 + 4 * (idx % (kBK / 4));
-                if (n < N) {
-                    if constexpr (VEC) {
-                        if (k < K) v = *reinterpret_cast<const f32x4*>(W + (int64_t)n * K + k);
-                    } else {
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (k + e < K) v[e] = W[(int64_t)n * K + k + e];
-                    }
+                    for (int e = 0; e < 4; ++e)
+                        if (n + e < N) v[e] = W[(int64_t)k * N + n + e];
                 }
             }
             r[i] = v;
         }
     }
-    __device__ __forceinline__ void stage(float (*Bs)[BN + 4], int tid, bool trans = false) {
+    __device__ __forceinline__ void stage(float (*Bs)[BN + 4], int tid) {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             const int idx = tid + 256 * i;
-            if (!trans) {
-                *reinterpret_cast<f32x4*>(&Bs[idx / (BN / 4)][4 * (idx % (BN / 4))]) = r[i];
-            } else {
-                const int n = idx / (kBK / 4), k = 4 * (idx % (kBK / 4));
-#pragma unroll
-                for (int e = 0; e < 4; ++e) Bs[k + e][n] = r[i][e];
-            }
+            *reinterpret_cast<f32x4*>(&Bs[idx / (BN / 4)][4 * (idx % (BN / 4))]) = r[i];
         }
     }
 };
