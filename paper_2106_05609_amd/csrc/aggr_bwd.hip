@@ -885,22 +885,105 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_cols_kernel(GatB
 }
 
 template <bool BF, int G, int H>
-void launch_gat_bwd(const GatBwdArgs& a, hipStream_t s) {
+void launch_gat_bwd(const GatBwdArgs& a, bool columns, hipStream_t s) {
     if (a.n_rows > 0) {
         hipLaunchKernelGGL((gat_bwd_rows_vec_kernel<BF, G, H>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
         hipLaunchKernelGGL((gat_bwd_long_rows_kernel<BF, G, H>), dim3(long_row_blocks(a.n_rows)), dim3(64 * kLongWaves), 0, s, a);
     }
+    if (!columns) return;
     hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H>), dim3((unsigned)a.n_cols), dim3(64), 0, s, a);
     hipLaunchKernelGGL((gat_bwd_long_cols_kernel<BF, G, H>), dim3(long_row_blocks(a.n_cols)), dim3(64 * kLongWaves), 0, s, a);
 }
 
 template <bool BF>
-void launch_gat_bwd_heads(const GatBwdArgs& a, int H, hipStream_t s) {
+void launch_gat_bwd_heads(const GatBwdArgs& a, int H, bool columns, hipStream_t s) {
     const int G = gat_team<BF>(a.F);
-    if (G == 64) launch_gat_bwd<BF, 64, 1>(a, s);
-    else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, s) : launch_gat_bwd<BF, 32, 1>(a, s);
-    else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, s) : launch_gat_bwd<BF, 16, 1>(a, s);
-    else if constexpr (BF) H == 4 ? launch_gat_bwd<BF, 8, 4>(a, s) : H == 2 ? launch_gat_bwd<BF, 8, 2>(a, s) : launch_gat_bwd<BF, 8, 1>(a, s);
+    if (G == 64) launch_gat_bwd<BF, 64, 1>(a, columns, s);
+    else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, columns, s) : launch_gat_bwd<BF, 32, 1>(a, columns, s);
+    else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, columns, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, columns, s) : launch_gat_bwd<BF, 16, 1>(a, columns, s);
+    else if constexpr (BF) H == 4 ? launch_gat_bwd<BF, 8, 4>(a, columns, s) : H == 2 ? launch_gat_bwd<BF, 8, 2>(a, columns, s) : launch_gat_bwd<BF, 8, 1>(a, columns, s);
+}
+
+// ---- the column side of one head, with a plan of the CSC copy: on patterns of many short columns the grouped rows of the
+// backward aggregation beat a wavefront per column (50 M-node graph, 24.7 M columns of 2.8 entries, bf16: 24.4 ms for
+// the whole call against 31.2; at 22 entries a column, fp32, 14.3 against 13.9).
+// The attention weights and the score gradients in the order of the CSC copy: the coefficients of the backward
+// aggregation, and the terms of the column totals.
+__global__ __launch_bounds__(256) void permute_entries_kernel(const f32x2_t* __restrict__ pair,
+                                                              const int32_t* __restrict__ pos, int64_t n,
+                                                              float* __restrict__ val_t, float* __restrict__ dt_t) {
+    const int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (q >= n) return;
+    const f32x2_t p = pair[pos[q]];
+    val_t[q] = p[0];
+    dt_t[q] = p[1];
+}
+
+// tsum[u] = the column's total of dt.  A wavefront takes 64 consecutive columns, whose terms are contiguous: a lane
+// adds the terms of its own column in stored order when there are at most 64 of them.  Longer columns are left to
+// column_totals_long_kernel: hub columns sit next to each other, and sixty-four of them in one wavefront's share,
+// summed one after the other, were most of this step's time.
+constexpr int kLongColumn = 64;
+
+__global__ __launch_bounds__(256) void column_totals_kernel(const int32_t* __restrict__ colptr, const float* __restrict__ dt_t,
+                                                            int64_t n_cols, float* __restrict__ tsum) {
+    const int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (u >= n_cols) return;
+    const int b = colptr[u], e = colptr[u + 1];
+    if (e - b > kLongColumn) return;
+    float ts = 0.f;
+    for (int q = b; q < e; q += 8) {                  // eight loads in flight, added in stored order
+        float x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = q + j < e ? dt_t[q + j] : 0.f;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ts += x[j];
+    }
+    tsum[u] = ts;
+}
+
+// The columns of more than kLongColumn terms, found as the long rows are: one wavefront per column, lanes stride over
+// its terms, then a fixed reduction over the lanes.
+__global__ __launch_bounds__(64 * kLongWaves) void column_totals_long_kernel(const int32_t* __restrict__ colptr,
+                                                                             const float* __restrict__ dt_t, int64_t n_cols,
+                                                                             float* __restrict__ tsum) {
+    constexpr int T = 64 * kLongWaves;
+    __shared__ int queue[T];
+    __shared__ int n_queued;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    for (int64_t r0 = blockIdx.x; r0 < n_cols; r0 += (int64_t)T * gridDim.x) {
+        const int nq = queue_long_rows(colptr, n_cols, r0, queue, &n_queued, kLongColumn);
+        for (int q = w; q < nq; q += kLongWaves) {
+            const int64_t u = queue[q];
+            const int b = colptr[u], e = colptr[u + 1];
+            float p = 0.f;
+            for (int t = b + lane; t < e; t += 64) p += dt_t[t];
+            p = wave_sum(p);
+            if (lane == 0) tsum[u] = p;
+        }
+        __syncthreads();
+    }
+}
+
+// GP[u] += tsum[u] a_src + csum[u] a_dst after the backward aggregation has left sum_k alpha_k GZ[row k] in GP[u]:
+// one thread per 16-byte piece.
+template <bool BF>
+__global__ __launch_bounds__(256) void gat_bwd_rank_one_kernel(GatBwdArgs a) {
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4;
+    const int pieces = a.F / E;
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= a.n_out * pieces) return;
+    const int64_t u = idx / pieces;
+    const int p = (int)(idx - u * pieces);
+    const float ts = a.tsum[u], cs = u < a.n_rows ? a.csum[u] : 0.f;
+    float g[E], ar[E], ad[E];
+    char* gp = a.GP + (u * a.ldgp + (int64_t)p * E) * EB;
+    unpack<BF>(*reinterpret_cast<const u32x4*>(gp), g);
+    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_src + (int64_t)p * E * EB), ar);
+    unpack<BF>(*reinterpret_cast<const u32x4*>(a.a_dst + (int64_t)p * E * EB), ad);
+#pragma unroll
+    for (int i = 0; i < E; ++i) g[i] = g[i] + ts * ar[i] + cs * ad[i];
+    *reinterpret_cast<u32x4*>(gp) = pack<BF>(g);
 }
 
 // Two weighted column sums of one matrix in a pass over it (the gradients of the two attention vectors):
@@ -1161,7 +1244,7 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
 int64_t gas_gat_aggregate_bwd_heads_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F, int32_t heads) {
     if (n_rows < 0 || n_cols <= 0 || nnz < 0 || F <= 0 || heads <= 0) return 0;
     const int64_t H = heads < 4 ? heads : 4;               // heads taken together
-    return align_up(nnz * H * 8) + align_up(n_rows * H * 4) + align_up(n_cols * H * 4) +
+    return align_up(nnz * H * 8) + 2 * align_up(nnz * 4) + align_up(n_rows * H * 4) + align_up(n_cols * H * 4) +
            align_up(colsum_scratch_floats(n_cols, (int)(H * F)) * 4);
 }
 
@@ -1209,13 +1292,34 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
     char* w = static_cast<char*>(workspace);
     a.pair = reinterpret_cast<f32x2_t*>(w);
     a.alpha = reinterpret_cast<float*>(w); a.dt = a.alpha + nnz; w += align_up(nnz * H * 8);
+    float* val_t = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
+    float* dt_t = reinterpret_cast<float*>(w); w += align_up(nnz * 4);
     a.csum = reinterpret_cast<float*>(w); w += align_up(n_rows * H * 4);
     a.tsum = reinterpret_cast<float*>(w); w += align_up(n_cols * H * 4);
     float* colsum_scratch = reinterpret_cast<float*>(w);
     for (int32_t h = 0; h < heads; h += H) {
         if (vec) {
-            if (bf) launch_gat_bwd_heads<true>(a, H, s);
-            else launch_gat_bwd_heads<false>(a, H, s);
+            const bool planned = H == 1 && plan_t && n_out > 0;
+            if (bf) launch_gat_bwd_heads<true>(a, H, !planned, s);
+            else launch_gat_bwd_heads<false>(a, H, !planned, s);
+            if (planned) {
+                if (nnz > 0)
+                    hipLaunchKernelGGL(permute_entries_kernel, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, s, a.pair,
+                                       csc_pos, nnz, val_t, dt_t);
+                hipLaunchKernelGGL(column_totals_kernel, dim3((unsigned)((n_cols + 255) / 256)), dim3(256), 0, s, colptr, dt_t,
+                                   n_cols, a.tsum);
+                hipLaunchKernelGGL(column_totals_long_kernel, dim3(long_row_blocks(n_cols)), dim3(64 * kLongWaves), 0, s, colptr,
+                                   dt_t, n_cols, a.tsum);
+                GAS_CHECK_HIP(hipGetLastError());
+                // GP[u] = sum over the entries (v, u) of alpha GZ[v]: the backward aggregation with the attention weights
+                // as coefficients, in the order of the CSC copy; then the two rank-one terms
+                const gas_status st = gas_spmm_t(plan_t, colptr, row, val_t, 0.f, 1.f, 0, a.GZ, ldgz, dt, F, a.GP, ldgp, dt, stream);
+                if (st != GAS_OK) return st;
+                const int64_t pieces = n_out * (F / (bf ? 8 : 4));
+                GAS_REQUIRE((pieces + 255) / 256 <= 0x7FFFFFFFLL, "gas_gat_aggregate_bwd: output too large for one launch");
+                if (bf) hipLaunchKernelGGL(gat_bwd_rank_one_kernel<true>, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
+                else hipLaunchKernelGGL(gat_bwd_rank_one_kernel<false>, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, s, a);
+            }
         } else {
             if (n_rows > 0) {
                 if (bf) hipLaunchKernelGGL(gat_bwd_rows_kernel<true>, dim3((unsigned)n_rows), dim3(64), 0, s, a);

@@ -895,7 +895,7 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         gd = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         gs = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         B.gas_gat_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, a_dst, a_src, g, gp, gd, gs,
-                                negative_slope, heads=heads)
+                                negative_slope, plan_t=bg.plan_t_all, heads=heads)
         grads[l - 1] = (_weight_grad(x, gp), gd, gs)
         if l == 1:
             break
