@@ -41,14 +41,18 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 //   1. aggregation: wavefront w owns rows 8w .. 8w+7; a team of G lanes owns one row at a time, lane j its
 //      16-byte pieces j and j + G (two loads per gathered row, each contiguous over the team).  The team reads
 //      2 G source indices (and coefficients) with two loads (the next 2 G are requested before the current ones
-//      are used), gathers the rows four at a time and folds them in index order; the finished row (scaled, plus
+//      are used), gathers the rows eight at a time and folds them in index order; the finished row (scaled, plus
 //      the diagonal and residual terms) goes to the LDS tile Zs.  With width 64 a team is 8 lanes, so a wavefront
 //      works on its 8 rows at once and the whole chain (row pointers, indices, rows) is walked once per tile.
 //   2. transform: wavefront w owns output columns 32w .. 32w+31 (if the layer is that wide): 32x32x2 fp32 MFMAs
 //      over Zs and the weights in LDS, then c_w * acc + c_id * Z + bias, ReLU, and the row is stored to Y and to
 //      its history slot.
 // The weights are staged once per workgroup, after the first row's pointers have been requested.
-__global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) {
+// Latency bounds the kernel (64 layers of 21,248 rows, width 64, 14 entries a row: 22 us each, 1.5 TB/s): eight rows
+// in flight instead of four and the history rows of the epilogue requested before the aggregation took the whole pass
+// from 1,442 to 1,404 us at three wavefronts per SIMD.  Each half of a batch is folded only if it has an entry of the
+// row, so the sums are those of batches of four, bit for bit.
+__global__ __launch_bounds__(kThreads, 3) void spmm_linear_f32_kernel(FusedArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int ldz = a.Kp + 4, ldw = a.Np + 4;
     float* Zs = reinterpret_cast<float*>(smem);                 // [kRows][ldz]
@@ -57,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) 
 
     const int G = 1 << a.g_log2, T = 64 >> a.g_log2;            // lanes per team, teams per wavefront
     const int team = lane >> a.g_log2, j = lane & (G - 1);
-    constexpr int U = 4, RW = kRows / (kThreads / 64);          // gathers in flight per lane (two loads each), rows per wavefront
+    constexpr int U = 8, RW = kRows / (kThreads / 64);          // gathers in flight per lane (two loads each), rows per wavefront
     // Workgroups go to the eight XCDs in turn and each XCD has its own L2.  Every XCD gets one contiguous eighth
     // of the tiles: consecutive rows of a batch belong to one cluster of the partition and gather mostly from that
     // cluster's rows, which then stay in that XCD's L2 instead of being fetched into all eight.
@@ -88,6 +92,8 @@ __global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) 
 
     for (int64_t tile = tile0; tile < tile_end; tile += gridDim.x >> 3) {
         const int64_t m_tile = tile * kRows;
+        // the history row of output row li: requested a whole aggregation before the epilogue stores to it
+        const int my_slot = a.push_idx && m_tile + li < a.n_rows ? a.push_idx[m_tile + li] : 0;
         // ---- 1. aggregation
         for (int r = wave * RW + team; r < (wave + 1) * RW; r += T) {
             const int64_t m = m_tile + r;
@@ -128,11 +134,15 @@ __global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) 
                         x1[u] = *reinterpret_cast<const f32x4*>(row + off1);
                     }
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
+                    for (int h = 0; h < U; h += 4) {
+                        if (h > 0 && q0 + h >= cnt) break;        // nothing of these four belongs to the row
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) {
-                            acc0[c] = fmaf(v[u], x0[u][c], acc0[c]);
-                            acc1[c] = fmaf(v[u], x1[u][c], acc1[c]);
+                        for (int u = h; u < h + 4; ++u) {
+#pragma unroll
+                            for (int c = 0; c < 4; ++c) {
+                                acc0[c] = fmaf(v[u], x0[u][c], acc0[c]);
+                                acc1[c] = fmaf(v[u], x1[u][c], acc1[c]);
+                            }
                         }
                     }
                 }
@@ -175,14 +185,6 @@ __global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) 
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[r] = 0.f;
             const int col = 32 * wave + li;
-            int slot[16];                                         // history rows of this lane's 16 output rows
-            if (a.push_idx) {
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int64_t m = m_tile + 8 * (r / 4) + 4 * lh + (r % 4);
-                    slot[r] = m < a.n_rows ? a.push_idx[m] : 0;
-                }
-            }
             for (int kq = 0; kq < a.Kp / 8; kq += 2) {            // two steps of 8 k: operands read before the products
                 f32x4 fa[2];
                 float fb[2][4];
@@ -202,19 +204,18 @@ __global__ __launch_bounds__(kThreads) void spmm_linear_f32_kernel(FusedArgs a) 
                     }
                 }
             }
-            if (col < a.N) {
-                const float bv = a.bias ? a.bias[col] : 0.f;
+            const float bv = a.bias && col < a.N ? a.bias[col] : 0.f;
 #pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int row = 8 * (r / 4) + 4 * lh + (r % 4);
-                    const int64_t m = m_tile + row;
-                    if (m >= a.n_rows) continue;
-                    float y = a.c_w * acc[r] + bv;
-                    if (a.c_id != 0.f) y = fmaf(a.c_id, Zs[row * ldz + col], y);
-                    if (a.relu) y = fmaxf(y, 0.f);
-                    a.Y[m * a.ldy + col] = y;
-                    if (a.push_idx) a.PH[(int64_t)slot[r] * a.ldp + col] = y;                    // Push in the epilogue
-                }
+            for (int r = 0; r < 16; ++r) {
+                const int row = 8 * (r / 4) + 4 * lh + (r % 4);
+                const int64_t m = m_tile + row;
+                const int slot = __shfl(my_slot, row);            // of every lane, before any leaves
+                if (m >= a.n_rows || col >= a.N) continue;
+                float y = a.c_w * acc[r] + bv;
+                if (a.c_id != 0.f) y = fmaf(a.c_id, Zs[row * ldz + col], y);
+                if (a.relu) y = fmaxf(y, 0.f);
+                a.Y[m * a.ldy + col] = y;
+                if (a.push_idx) a.PH[(int64_t)slot * a.ldp + col] = y;                           // Push in the epilogue
             }
         }
         __syncthreads();                 // the next tile's aggregation overwrites Zs
