@@ -48,7 +48,7 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 //      over Zs and the weights in LDS, then c_w * acc + c_id * Z + bias, ReLU, and the row is stored to Y and to
 //      its history slot.
 // The weights are staged once per workgroup, after the first row's pointers have been requested.
-// Latency bounds the kernel (64 layers of 21,248 rows, width 64, 14 entries a row: 22 us each, 1.5 TB/s): eight rows
+// Latency bounds the kernel (64 layers of 21,248 rows, width 64, 14 entries a row: 22 us each, 1.3 TB/s): eight rows
 // in flight instead of four and the history rows of the epilogue requested before the aggregation took the whole pass
 // from 1,442 to 1,404 us at three wavefronts per SIMD.  Each half of a batch is folded only if it has an entry of the
 // row, so the sums are those of batches of four, bit for bit.
