@@ -354,21 +354,7 @@ __device__ __forceinline__ void transpose8x8_bf16(const u32x4 (&in)[8], u32x4 (&
         }
 }
 
-// Eight elements at p, zeros from the left-th on.  ANY: p is aligned to its elements only and the row may end inside
-// (one load where it does not).
-typedef u32x4 u32x4_at2 __attribute__((aligned(2)));
-template <bool ANY>
-__device__ __forceinline__ u32x4 load8_bf16(const uint16_t* p, int64_t left) {
-    if constexpr (!ANY) return *reinterpret_cast<const u32x4*>(p);
-    if (left >= 8) return *reinterpret_cast<const u32x4_at2*>(p);
-    u32x4 v = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int e = 0; e < 7; ++e)
-        if (e < left) v[e / 2] |= (uint32_t)p[e] << (16 * (e & 1));
-    return v;
-}
-
-template <int BM, bool ANY = false>
+template <int BM>
 struct ATileBF16 {
     static constexpr int NV = BM * kBKh / 8 / 256;
     u32x4 r[NV];
@@ -379,7 +365,7 @@ struct ATileBF16 {
             const int64_t m = m0 + (idx >> 3);
             const int k = k0 + 8 * (idx & 7);
             r[i] = u32x4{0u, 0u, 0u, 0u};
-            if (m < M && k < K) r[i] = load8_bf16<ANY>(Z + m * ld + k, K - k);
+            if (m < M && k < K) r[i] = *reinterpret_cast<const u32x4*>(Z + m * ld + k);
         }
     }
     __device__ __forceinline__ void stage(uint16_t (*As)[kLdh], int tid) {
@@ -393,7 +379,7 @@ struct ATileBF16 {
 
 // One kBKh x BN tile of a bf16 weight matrix into Bs[n][k].  Row-major [K][N]: transposed on the way (8 x 8
 // blocks).  trans (the matrix is [N][K] row-major): already in the layout the MFMA wants, plain 16-byte copies.
-template <int BN, bool ANY = false>
+template <int BN>
 struct BTileBF16 {
     u32x4 r[8];
     __device__ __forceinline__ void fetch(const uint16_t* W, int K, int N, int k0, int n0, int tid, bool trans = false) {
@@ -404,7 +390,7 @@ struct BTileBF16 {
             for (int i = 0; i < 8; ++i) {
                 const int k = k0 + 8 * kb + i;
                 r[i] = u32x4{0u, 0u, 0u, 0u};
-                if (k < K && n < N) r[i] = load8_bf16<ANY>(W + (int64_t)k * N + n, N - n);
+                if (k < K && n < N) r[i] = *reinterpret_cast<const u32x4*>(W + (int64_t)k * N + n);
             }
         } else {
 #pragma unroll
@@ -412,7 +398,7 @@ struct BTileBF16 {
                 const int idx = tid + 256 * i;
                 const int n = n0 + (idx >> 3), k = k0 + 8 * (idx & 7);
                 r[i] = u32x4{0u, 0u, 0u, 0u};
-                if (n < N && k < K) r[i] = load8_bf16<ANY>(W + (int64_t)n * K + k, K - k);
+                if (n < N && k < K) r[i] = *reinterpret_cast<const u32x4*>(W + (int64_t)n * K + k);
             }
         }
     }
@@ -457,7 +443,7 @@ __device__ __forceinline__ void mfma_tile_bf16(const uint16_t* A, int lda, int a
     }
 }
 
-template <int BN, bool ANY>
+template <int BN>
 __global__ __launch_bounds__(256) void linear_bf16_kernel(LinArgs a) {
     constexpr int BM = 128, TM = 2, TN = BN / 64;
     __shared__ __attribute__((aligned(16))) uint16_t As[BM][kLdh];
@@ -470,8 +456,8 @@ __global__ __launch_bounds__(256) void linear_bf16_kernel(LinArgs a) {
     const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (BN / 2);
     f32x16 acc[TM][TN];
     zero_acc(acc);
-    ATileBF16<BM, ANY> ta;
-    BTileBF16<BN, ANY> tb;
+    ATileBF16<BM> ta;
+    BTileBF16<BN> tb;
     const bool tr = a.trans_w != 0;
     ta.fetch(Z, a.ldz, a.M, a.K, m0, 0, tid);
     tb.fetch(W, a.K, a.N, 0, n0, tid, tr);
@@ -1077,7 +1063,27 @@ gas_status launch_ws(const WsArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
-// ====================================================================== element-wise path of the fused MLP
+// ====================================================================== element-wise paths
+// For bf16 operands that are not 16-byte aligned (odd widths, odd strides):
+// one thread per output element, fp32 accumulation.
+__global__ __launch_bounds__(256) void linear_bf16_generic_kernel(LinArgs a) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (idx >= a.M * a.N) return;
+    const int64_t m = idx / a.N;
+    const int n = (int)(idx % a.N);
+    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
+    const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
+    float s = 0.f;
+    for (int k = 0; k < a.K; ++k)
+        s = fmaf(bf16_val(Z, m * a.ldz + k), bf16_val(W, a.trans_w ? (int64_t)n * a.K + k : (int64_t)k * a.N + n), s);
+    float y = a.c_w * s;
+    if (a.bias) y += bf16_val(reinterpret_cast<const uint16_t*>(a.bias), n);
+    if (a.c_id != 0.f) y += a.c_id * bf16_val(Z, m * a.ldz + n);
+    if (a.relu) y = fmaxf(y, 0.f);
+    if (a.mask && !(bf16_val(reinterpret_cast<const uint16_t*>(a.mask), m * a.ldmask + n) > 0.f)) y = 0.f;
+    reinterpret_cast<uint16_t*>(a.Y)[m * a.ldy + n] = (uint16_t)f32_to_bf16(y);
+}
+
 // One workgroup per row; the hidden row goes through LDS (bf16-rounded for
 // bf16 data, as in the MFMA kernel).
 template <bool BF>
@@ -1202,7 +1208,6 @@ __global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
 
 // bf16: both operands need 8 consecutive rows per lane, so both tiles are transposed on the way into LDS
 // (the same 8 x 8 register transposition as for the weights of the forward kernel).
-template <bool ANY>
 __global__ __launch_bounds__(256) void dw_bf16_kernel(DwArgs a) {
     __shared__ __attribute__((aligned(16))) uint16_t Zt[kDwTile][kLdh];     // [feature][row]
     __shared__ __attribute__((aligned(16))) uint16_t Gt[kDwTile][kLdh];
@@ -1227,7 +1232,7 @@ __global__ __launch_bounds__(256) void dw_bf16_kernel(DwArgs a) {
         for (int i = 0; i < 8; ++i) {
             const int64_t m = m0 + 8 * rb + i;
             r[i] = u32x4{0u, 0u, 0u, 0u};
-            if (m < m_end && f < flim) r[i] = load8_bf16<ANY>(src + m * ld + f, flim - f);
+            if (m < m_end && f < flim) r[i] = *reinterpret_cast<const u32x4*>(src + m * ld + f);
         }
     };
     fetch(m_begin);
@@ -1321,6 +1326,22 @@ __global__ __launch_bounds__(512) void dw_bf16_wide_kernel(DwArgs a) {
         }
 }
 
+// element-wise path for bf16 operands that are not 16-byte aligned: one thread per (slab, k, j)
+__global__ __launch_bounds__(256) void dw_bf16_generic_kernel(DwArgs a) {
+    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const int64_t per = (int64_t)a.K * a.N;
+    if (idx >= per * a.n_slabs) return;
+    const int slab = (int)(idx / per);
+    const int k = (int)((idx % per) / a.N), n = (int)(idx % a.N);
+    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
+    const uint16_t* G = reinterpret_cast<const uint16_t*>(a.G);
+    const int64_t m_begin = (int64_t)slab * a.slab;
+    const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
+    float s = 0.f;
+    for (int64_t m = m_begin; m < m_end; ++m) s = fmaf(bf16_val(Z, m * a.ldz + k), bf16_val(G, m * a.ldg + n), s);
+    a.partial[idx] = s;
+}
+
 // dW = c_w * (sum of the slabs' partial tiles).  A workgroup owns 32 consecutive outputs; eight threads per output
 // each add every eighth slab in slab order, four loads in flight, and the eight sums are added in a fixed order.
 constexpr int kDwReduceOut = 32, kDwReduceWays = 8;
@@ -1404,13 +1425,11 @@ gas_status launch_split(const LinArgs& a, hipStream_t s) {
 }
 
 template <int BN>
-gas_status launch_bf16(const LinArgs& a, bool vec, hipStream_t s) {
+gas_status launch_bf16(const LinArgs& a, hipStream_t s) {
     const int64_t gm = (a.M + 127) / 128;
     const int gn = (a.N + BN - 1) / BN;
     if (gm > 0x7FFFFFFF || gn > 65535) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
-    const dim3 grid((unsigned)gm, (unsigned)gn), block(256);
-    if (vec) hipLaunchKernelGGL((linear_bf16_kernel<BN, false>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((linear_bf16_kernel<BN, true>), grid, block, 0, s, a);
+    hipLaunchKernelGGL((linear_bf16_kernel<BN>), dim3((unsigned)gm, (unsigned)gn), dim3(256), 0, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
@@ -1473,7 +1492,15 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         return launch_split<64, 64, 2, 4>(a, s);
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
-    if (vec && F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 && n_rows >= 4096 &&
+    if (!vec) {
+        const int64_t total = n_rows * (int64_t)F_out;
+        const int64_t blocks = (total + 255) / 256;
+        if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "%s: problem too large for the element-wise path", who);
+        hipLaunchKernelGGL(linear_bf16_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+        GAS_CHECK_HIP(hipGetLastError());
+        return push_after(push, Y, ldy, n_rows, F_out, dt, s);
+    }
+    if (F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 && n_rows >= 4096 &&
         (!mask || (aligned16(mask) && ldmask % 8 == 0)) && ldz < (1 << 24) && ldy < (1 << 24) && ldmask < (1 << 24)) {
         const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
@@ -1488,7 +1515,7 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         const gas_status st = F_in <= 64 ? launch_ws<4>(w, s) : (F_in <= 128 ? launch_ws<8>(w, s) : launch_ws<16>(w, s));
         return (st != GAS_OK || scatter) ? st : push_after(push, Y, ldy, n_rows, F_out, dt, s);
     }
-    const gas_status st = F_out <= 64 ? launch_bf16<64>(a, vec, s) : (F_out <= 128 ? launch_bf16<128>(a, vec, s) : launch_bf16<256>(a, vec, s));
+    const gas_status st = F_out <= 64 ? launch_bf16<64>(a, s) : (F_out <= 128 ? launch_bf16<128>(a, s) : launch_bf16<256>(a, s));
     return st != GAS_OK ? st : push_after(push, Y, ldy, n_rows, F_out, dt, s);
 }
 
@@ -1610,9 +1637,11 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
             GAS_CHECK_HIP(attr);
             hipLaunchKernelGGL(dw_bf16_wide_kernel, dim3((unsigned)n_slabs), dim3(512), smem, s, a);
         } else if (vec) {
-            hipLaunchKernelGGL(dw_bf16_kernel<false>, grid, dim3(256), 0, s, a);
-        } else {                 // 53,000 x 81 x 256: 31 us (a thread per element: 820 us)
-            hipLaunchKernelGGL(dw_bf16_kernel<true>, grid, dim3(256), 0, s, a);
+            hipLaunchKernelGGL(dw_bf16_kernel, grid, dim3(256), 0, s, a);
+        } else {
+            const int64_t blocks = (per * n_slabs + 255) / 256;
+            GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for the element-wise path");
+            hipLaunchKernelGGL(dw_bf16_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
         }
     }
     hipLaunchKernelGGL(dw_reduce_kernel, dim3(rblocks), dim3(256), 0, s, a);

@@ -51,3 +51,42 @@ def test_aggregation_of_odd_rows(F, dtype):
     xfull = (xfull.view(torch.bfloat16) if dtype == torch.bfloat16 else xfull).cuda()
     gas.gas_spmm_t(plan, d_ptr, d_col, d_val, xfull, z2)
     assert node_rel_err(to_np(z2), oops.spmm(ptr, col, val, xo)) <= TOL[dtype]
+
+
+# rows, input and output width: several k steps with a remainder, one and several column tiles with a tail
+PRODUCTS = [(1, 1, 1), (300, 81, 256), (129, 1433, 47), (257, 131, 129), (200, 70, 300), (5000, 250, 33)]
+
+
+@pytest.mark.parametrize("views", [False, True])
+@pytest.mark.parametrize("what", ["linear", "input", "weight"])
+@pytest.mark.parametrize("m,k,n", PRODUCTS)
+def test_bf16_products_of_odd_widths(what, m, k, n, views):
+    """views: rows start one element past a 16-byte boundary and have an odd stride, the output lies between guard columns."""
+    import paper_2106_05609_amd as gas
+
+    def operand(stream, rows, cols):
+        t = rng.normal_matrix(3, stream, rows, cols, dtype=torch.bfloat16).cuda()
+        return torch.nn.functional.pad(t, (1, 2 + cols % 2))[:, 1:cols + 1] if views else t
+
+    z, g, w = operand(820, m, k), operand(821, m, n), rng.normal_matrix(3, 822, k, n, dtype=torch.bfloat16).cuda()
+    z64, g64, w64 = z.double(), g.double(), w.double()
+    if what == "weight":
+        out = torch.full((k, n), float("nan"), device="cuda")
+        ws = torch.empty(max(1, gas.gas_linear_bwd_weight_workspace(m, k, n)), dtype=torch.uint8, device="cuda")
+        gas.gas_linear_bwd_weight(z, g, out, ws)
+        want, size, terms, stored = z64.t() @ g64, z64.t().abs() @ g64.abs(), m, 0.0
+    else:
+        cols = n if what == "linear" else k
+        pad = torch.full((m, cols + 3), 7.0, dtype=torch.bfloat16, device="cuda")
+        out = pad[:, 1:cols + 1] if views else torch.full((m, cols), float("nan"), dtype=torch.bfloat16, device="cuda")
+        if what == "linear":
+            gas.gas_linear(z, w, out)
+            want, size, terms = z64 @ w64, z64.abs() @ w64.abs(), k
+        else:
+            gas.gas_linear_bwd_input(g, w, out)
+            want, size, terms = g64 @ w64.t(), g64.abs() @ w64.t().abs(), n
+        stored = 2.0 ** -8                 # the output's rounding to bf16: eight significant bits, half a unit of the last
+        if views:
+            assert bool((pad[:, 0] == 7.0).all()) and bool((pad[:, cols + 1:] == 7.0).all())
+    # products of bf16 numbers are exact in fp32; every addition rounds a partial sum of at most `size`
+    assert bool(((out.double() - want).abs() <= stored * want.abs() + (terms + 2) * 2.0 ** -24 * size * (1 + stored)).all())
