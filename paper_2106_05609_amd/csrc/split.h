@@ -17,9 +17,15 @@
 // 534 us (748).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
 // compute unit: 55-63 us; products and split interleaved by hand in one wavefront, two LDS buffers: 49-56 us.
 //
-// What the split cannot represent is found in its result: an infinity, a NaN or a value that rounds to an infinite
-// bf16 makes the accumulator non-finite (0 * inf in the terms beside it, if not itself), and a wavefront that finds
-// one takes its block again with the fp32 instruction (plain_tile), so such inputs give what fp32 arithmetic gives.
+// What the split cannot represent: an infinity, a NaN or a value that rounds to an infinite bf16 makes the accumulator
+// non-finite (0 * inf in the terms beside it, if not itself), and a wavefront that finds one takes its block again with
+// the fp32 instruction (plain_tile), so such inputs give what fp32 arithmetic gives.  The other end is not seen in the
+// result: below 2^-110 the last bits of a value lie under bf16's smallest subnormal, 2^-133 (relative error 2.2e-6 for
+// an operand of 2^-116 N(0,1), 5.6e-4 at 2^-124).  So the least non-zero magnitude is kept while staging, and a workgroup
+// that met one below 2^-110 takes its tile again with both operands times 2^40: every fp32 number is then represented
+// whole, and what leaves the range at the upper end is non-finite, as above.  The search costs one and a half
+// instructions a value (4,000 x 256 x 256: 9.7 -> 10.0 us, 50,000 rows 53.7 -> 54.0 us); with such a value in every tile
+// 50,000 rows take 92 us (the fp32 instruction 86 us), with one beyond 2^88 as well 211 us.
 #pragma once
 #include "common.h"
 
@@ -29,6 +35,9 @@ namespace {
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef f32x4 f32x4_any __attribute__((aligned(4)));      // a 16-byte load at a float's alignment
+
+constexpr float kUp = 0x1p40f;
+constexpr uint32_t kLeast = 2 * ((127 - 110) << 23) - 1;      // 2 bits - 1 of 2^-110
 
 // x0, x1 -> their three bf16 parts, packed in pairs
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint32_t& m, uint32_t& l) {
@@ -115,15 +124,25 @@ struct SplitTile {
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[i][e] = 8 * piece_of(i) + e < left ? v[i][e] : 0.f;
     }
-    __device__ __forceinline__ void stage(uint16_t* planes) const {
+    // low: the least of 2 bits - 1 over the values staged, as an integer (zeros come out largest)
+    template <bool SCALED>
+    __device__ __forceinline__ void stage(uint16_t* planes, uint32_t& low) const {
 #pragma unroll
         for (int i = 0; i < NV; ++i) {
             if (!holds(i)) continue;
             u32x4 h, m, l;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
+                float x0 = v[i][2 * e], x1 = v[i][2 * e + 1];
+                if constexpr (SCALED) {
+                    x0 *= kUp;
+                    x1 *= kUp;
+                } else {
+                    const uint32_t t0 = 2 * __float_as_uint(x0) - 1, t1 = 2 * __float_as_uint(x1) - 1;
+                    low = min(low, min(t0, t1));
+                }
                 uint32_t a, b, c;
-                split_pair(v[i][2 * e], v[i][2 * e + 1], a, b, c);
+                split_pair(x0, x1, a, b, c);
                 h[e] = a; m[e] = b; l[e] = c;
             }
             uint16_t* to = planes + at(row_of(i), piece_of(i));
@@ -134,15 +153,15 @@ struct SplitTile {
     }
 };
 
-// A BM x BN tile of sum_q A(r, q) B(c, q), q_begin <= q < q_end (not empty), by WM x WN wavefronts; `lds` holds
-// 3 (BM + BN) 16 KS bf16 elements.  acc: the wavefront's TM x TN blocks of 32 x 32, at rows wm0.. and columns wn0..
+// A BM x BN tile of sum_q A(r, q) B(c, q), q_begin <= q < q_end (not empty), by WM x WN wavefronts; `lds` holds kLdsBytes.  acc: the wavefront's TM x TN blocks of 32 x 32, at rows wm0.. and columns wn0..
 // of the tile.
 template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC>
 struct SplitGemm {
     static constexpr int T = 64 * WM * WN, TM = BM / 32 / WM, TN = BN / 32 / WN;     // threads, 32 x 32 blocks of a wavefront
     using TA = SplitTile<BM, KS, AKC, T>;
     using TB = SplitTile<BN, KS, BKC, T>;
-    static constexpr int kLdsBytes = 3 * (TA::kPlane + TB::kPlane) * 2;
+    static constexpr int kFlag = 3 * (TA::kPlane + TB::kPlane);              // where the flag lies, in bf16 elements
+    static constexpr int kLdsBytes = kFlag * 2 + 16;
     TA ta;
     TB tb;
 
@@ -175,10 +194,11 @@ struct SplitGemm {
         }
     }
 
-    // acc = the products; whether all values of the wavefront's blocks are finite (else: plain_tile)
-    __device__ __forceinline__ bool run(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
-                                        int64_t b0, int64_t b_end, int64_t q_begin, int64_t q_end, uint16_t* lds, int wm0,
-                                        int wn0, f32x16 (&acc)[TM][TN]) {
+    // acc = the products of the operands as they are, or of both times kUp (the products divided by its square at the end)
+    template <bool SCALED>
+    __device__ __forceinline__ void pass(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
+                                         int64_t b0, int64_t b_end, int64_t q_begin, int64_t q_end, uint16_t* lds, int wm0,
+                                         int wn0, f32x16 (&acc)[TM][TN]) {
         ta.init(A, lda, a0, a_end);
         tb.init(B, ldb, b0, b_end);
         if (q_begin + TA::kQ <= q_end) {
@@ -195,10 +215,12 @@ struct SplitGemm {
             for (int j = 0; j < TN; ++j)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
-        auto stage = [&]() {
+        uint32_t low = 0xFFFFFFFFu;
+        auto stage = [&](bool last) {        // last: no whole step follows
             __syncthreads();                 // everyone is done reading the previous step
-            ta.stage(lds);
-            tb.stage(lds + 3 * TA::kPlane);
+            ta.template stage<SCALED>(lds, low);
+            tb.template stage<SCALED>(lds + 3 * TA::kPlane, low);
+            if (!SCALED && last && low < kLeast) *reinterpret_cast<uint32_t*>(lds + kFlag) = 1;
             __syncthreads();
         };
         auto multiply = [&]() {
@@ -208,13 +230,13 @@ struct SplitGemm {
         };
         int64_t q = q_begin;
         for (; q + 2 * TA::kQ <= q_end; q += TA::kQ) {
-            stage();
+            stage(false);
             ta.fetch(q + TA::kQ);
             tb.fetch(q + TA::kQ);
             multiply();
         }
         if (q + TA::kQ <= q_end) {           // the last whole step
-            stage();
+            stage(true);
             if (q + TA::kQ < q_end) {
                 ta.fetch_last(q + TA::kQ, q_end);
                 tb.fetch_last(q + TA::kQ, q_end);
@@ -225,10 +247,9 @@ struct SplitGemm {
         if (q < q_end) {                     // a step that is not whole
             ta.mask((int)(q_end - q));
             tb.mask((int)(q_end - q));
-            stage();
+            stage(true);
             multiply();
         }
-        float bad = 0.f;
 #pragma unroll
         for (int i = 0; i < TM; ++i)
 #pragma unroll
@@ -236,8 +257,26 @@ struct SplitGemm {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     acc[i][j][r] += small[i][j][r];
-                    bad = fmaf(acc[i][j][r], 0.f, bad);      // stays 0 for finite values, else NaN
+                    if constexpr (SCALED) acc[i][j][r] *= 1.f / (kUp * kUp);
                 }
+    }
+
+    // acc = the products; whether all values of the wavefront's blocks are finite (else: plain_tile)
+    __device__ __forceinline__ bool run(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
+                                        int64_t b0, int64_t b_end, int64_t q_begin, int64_t q_end, uint16_t* lds, int wm0,
+                                        int wn0, f32x16 (&acc)[TM][TN]) {
+        uint32_t* flag = reinterpret_cast<uint32_t*>(lds + kFlag);
+        if (threadIdx.x == 0) *flag = 0;     // before the first barrier of the pass, which sets it between its last two
+        pass<false>(A, lda, a0, a_end, B, ldb, b0, b_end, q_begin, q_end, lds, wm0, wn0, acc);
+        if (__builtin_amdgcn_readfirstlane(*flag))
+            pass<true>(A, lda, a0, a_end, B, ldb, b0, b_end, q_begin, q_end, lds, wm0, wn0, acc);
+        float bad = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) bad = fmaf(acc[i][j][r], 0.f, bad);      // stays 0 for finite values, else NaN
         return !__any(bad != 0.f);
     }
 };

@@ -69,3 +69,61 @@ def test_operands_that_bf16_parts_cannot_hold(what, bad, m, k, n):
     scale = _product(what, z.abs().double(), w.abs().double(), g.abs().double())[fine]
     t = {"linear": k, "input": n, "weight": m}[what]
     assert bool(((got.double()[fine] - want.double()[fine]).abs() <= 2 * t * 2.0 ** -24 * scale).all())
+
+
+def _operands(what, m, k, n):
+    """(z, w, g) with the two factors of the product first, and how many terms a sum has."""
+    z, w, g = (rng.normal_matrix(11, s, a, b) for s, a, b in ((720, m, k), (721, k, n), (722, m, n)))
+    return {"linear": (z, w, k), "input": (g, w, n), "weight": (z, g, m)}[what]
+
+
+def _check_every_element(what, a, b, terms, k, n):
+    m = a.shape[0]
+    if what == "linear":
+        got, (a64, b64) = _call(what, a, b, torch.zeros(m, n)), (a.double(), b.double())
+    elif what == "input":
+        got, (a64, b64) = _call(what, torch.zeros(m, k), b, a), (a.double(), b.double().t())
+    else:
+        got, (a64, b64) = _call(what, a, torch.zeros(k, n), b), (a.double().t(), b.double())
+    want, size = a64 @ b64, a64.abs() @ b64.abs()
+    # each product within 2^-24 of itself, each addition within 2^-24 of a partial sum of at most `size`; below the normal
+    # numbers a rounding is at most 2^-150
+    bound = (terms + 8) * (2.0 ** -24 * size + 2.0 ** -149)
+    assert bool(((got.double() - want).abs() <= bound).all()), float(((got.double() - want).abs() / bound).max())
+
+
+@pytest.mark.parametrize("what", ["linear", "input", "weight"])
+@pytest.mark.parametrize("up_a,up_b", [(-108, 0), (-112, 0), (-116, 0), (-124, 0), (-132, 0), (0, -120), (-116, -10), (-140, 60), (-126, 100), (-64, -64)])
+@pytest.mark.parametrize("m,k,n", [(70, 20, 72), (24577, 136, 256)])
+def test_operands_near_the_bottom_of_the_range(what, up_a, up_b, m, k, n):
+    a, b, terms = _operands(what, m, k, n)
+    _check_every_element(what, (a.double() * 2.0 ** up_a).float(), (b.double() * 2.0 ** up_b).float(), terms, k, n)
+
+
+@pytest.mark.parametrize("what", ["linear", "input", "weight"])
+@pytest.mark.parametrize("large", [1.0, 2.0 ** 60, 2.0 ** 100])
+def test_small_values_beside_others(what, large):
+    """A row and single elements below 2^-110 among ordinary ones, and beside values that leave the range when scaled up."""
+    m, k, n = 300, 96, 130
+    a, b, terms = _operands(what, m, k, n)
+    a[5] *= 2.0 ** -118
+    a[::7, 3] = 2.0 ** -130
+    b[3] = 0.0
+    b[3, ::2] = 2.0 ** 20 / 3.0
+    a[11, 2] = large
+    _check_every_element(what, a, b, terms, k, n)
+
+
+@pytest.mark.parametrize("what", ["linear", "weight"])
+@pytest.mark.parametrize("t", [100, 4096, 100000])
+def test_one_signed_sums(what, t):
+    """Sums that only grow, as products of ReLU activations: a rounding that leaned to one side would add up here.  Bound: a
+    quarter of what t roundings of one direction would come to at most, and for slabs the fp32 figure (sqrt) as above."""
+    m, k, n = (500, t, 64) if what == "linear" else (t, 64, 48)
+    if what == "linear" and t > 4096:
+        pytest.skip("no layer is that wide")
+    z, w, g = (rng.normal_matrix(11, s, a, b).abs() for s, a, b in ((730, m, k), (731, k, n), (732, m, n)))
+    got, want = _call(what, z, w, g).double(), _product(what, z.double(), w.double(), g.double())
+    err = (got - want) / want
+    assert float(err.norm() / np.sqrt(err.numel())) <= (1.0 + np.sqrt(min(t, 4096) / 3)) * 2.0 ** -24
+    assert abs(float(err.mean())) <= 0.25 * (1.0 + np.sqrt(min(t, 4096) / 3)) * 2.0 ** -24
