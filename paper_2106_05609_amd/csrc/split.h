@@ -3,9 +3,11 @@
 // A float is the sum of three bf16 numbers: x = h + m + l with h the nearest bf16 to x, m the nearest to x - h and l
 // to x - h - m (8 + 8 + 8 significant bits; both differences are exact).  A product is then taken as
 //     a b = ah bh + (ah bm + am bh) + (am bm + ah bl + al bh),
-// six v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the three dropped terms are below 2^-26 of |a b|, a quarter
-// of the fp32 rounding of one product.  Six instructions of 32 cycles do what eight v_mfma_f32_32x32x2_f32 of 64
-// cycles do: 16 k of a 32 x 32 block.
+// six v_mfma_f32_32x32x16_bf16 with fp32 accumulation; the three dropped terms are at most 2^-24 of |a b|, an fp32
+// rounding of the product (|m| <= 2^-8, |l| <= 2^-17 beside h = 1; 2^-27 of it root mean square for normally
+// distributed operands).  Six instructions of 32 cycles do what eight v_mfma_f32_32x32x2_f32 of 64 cycles do: 16 k of
+// a 32 x 32 block.  A product that is all there is of its sum (K = 1) is taken by the fp32 instruction, which rounds it
+// correctly; from two terms on the fewer roundings of the sum outweigh what is dropped (2.7e-8 against 3.2e-8).
 //
 // ah bh has an accumulator of its own and the five small terms share another, so the large one is rounded once per 16
 // k: the relative error against 64 bits (2-norm, N(0,1) operands) is 9.0e-8 at K = 256 and 1.7e-7 at K = 832, with the
@@ -261,10 +263,11 @@ struct SplitGemm {
                 }
     }
 
-    // acc = the products; whether all values of the wavefront's blocks are finite (else: plain_tile)
+    // acc = the products; whether they stand (not if a value of the wavefront's blocks is not finite): else plain_tile
     __device__ __forceinline__ bool run(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
                                         int64_t b0, int64_t b_end, int64_t q_begin, int64_t q_end, uint16_t* lds, int wm0,
                                         int wn0, f32x16 (&acc)[TM][TN]) {
+        if (q_end - q_begin == 1) return false;      // sums of one term: the dropped parts would be all of their error
         uint32_t* flag = reinterpret_cast<uint32_t*>(lds + kFlag);
         if (threadIdx.x == 0) *flag = 0;     // before the first barrier of the pass, which sets it between its last two
         pass<false>(A, lda, a0, a_end, B, ldb, b0, b_end, q_begin, q_end, lds, wm0, wn0, acc);

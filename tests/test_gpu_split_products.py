@@ -127,3 +127,19 @@ def test_one_signed_sums(what, t):
     err = (got - want) / want
     assert float(err.norm() / np.sqrt(err.numel())) <= (1.0 + np.sqrt(min(t, 4096) / 3)) * 2.0 ** -24
     assert abs(float(err.mean())) <= 0.25 * (1.0 + np.sqrt(min(t, 4096) / 3)) * 2.0 ** -24
+
+
+@pytest.mark.parametrize("what", ["linear", "input", "weight"])
+@pytest.mark.parametrize("rows,cols", [(1, 1), (70, 65), (25000, 130)])
+def test_sums_of_one_term_are_rounded_once(what, rows, cols):
+    """One input feature, one output feature, one row: the result is the fp32 product."""
+    a, b = rng.normal_matrix(11, 740, rows, 1), rng.normal_matrix(11, 741, 1, cols)
+    if what == "linear":
+        got = _call(what, a, b, torch.zeros(rows, cols))
+    elif what == "input":
+        got = _call(what, torch.zeros(rows, cols), b.t().contiguous(), a)
+    else:
+        rows = min(rows, 300)                              # the gradient is [rows, cols]
+        a = a[:rows]
+        got = _call(what, a.t().contiguous(), torch.zeros(rows, cols), b)
+    assert torch.equal(got, a * b)
