@@ -470,11 +470,15 @@ GAS_API gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32_t*
  * written (the in-batch nodes when histories are constants, or all of V_b).  workspace: device memory of at least
  * gas_*_bwd_workspace(...) bytes, caller-owned, contents undefined afterwards.
  * plan_t: a plan of the CSC copy for exactly the n_out output rows, gas_plan_create(colptr, colptr[n_out], max_F >= F,
- * n_out, row), or NULL.  With it, and rows of at most 64 pieces of 16 bytes that are 16-byte aligned, the row pass
- * gathers like the forward call and the sum of whole rows over a column's entries is taken by gas_spmm_t's kernels
- * (which rounds it to the storage type before the remaining terms are added: one more rounding for bf16).  Without
- * it, or for other shapes, plain kernels run: one wavefront per row and per column, one entry at a time; slow, and
- * the definition the fast path is tested against.  Fixed summation order either way (not the same order: the two
+ * n_out, row), or NULL.  Rows of at most 64 pieces of 16 bytes that are 16-byte aligned take fast paths:
+ *   gas_pna_aggregate_bwd with a plan: the row pass gathers like the forward call and the sum of whole rows over a
+ *     column's entries is taken by gas_spmm_t's kernels (which rounds it to the storage type before the remaining terms
+ *     are added: one more rounding for bf16);
+ *   gas_gat_aggregate_bwd with or without one: the row pass gathers like the forward call; the column side is taken by
+ *     gas_spmm_t's kernels as above where a plan is given and the heads are taken one by one, else by one gather over
+ *     the columns (all heads of a launch together; any plan is then unused).
+ * Everything else takes plain kernels: one wavefront per row and per column, one entry at a time (and one head); slow,
+ * and the definition the fast paths are tested against.  Fixed summation order either way (not the same order: the
  * paths agree to rounding).  The plan's partial-sum workspace is in use during the call, as in gas_spmm_t.
  *
  * gas_pna_aggregate_bwd: G [n_rows, 9 F] is the gradient of gas_pna_aggregate's output.  With s and d as there and

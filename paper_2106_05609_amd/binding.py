@@ -719,7 +719,8 @@ def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, ga
 def gas_gat_aggregate_bwd(rowptr, col, colptr, row, csc_pos, p, a_dst, a_src, gz, gp_out, ga_dst, ga_src,
                           negative_slope=0.2, plan_t=None, heads=1):
     """Backward of gas_gat_aggregate (gz: gradient before any activation): gp_out [n_out, F] rows of P's gradient,
-    ga_dst / ga_src float32 [F].  plan_t: a Plan of the CSC copy for those n_out columns, or None (used where the heads are taken one by one)."""
+    ga_dst / ga_src float32 [F].  plan_t: a Plan of the CSC copy for those n_out columns, or None; used where the heads are taken
+    one by one (see gas.h).  heads > 1: as in gas_gat_aggregate."""
     pp, ldp = _mat(p)
     zp, ldz = _mat(gz)
     op, ldo = _mat(gp_out)

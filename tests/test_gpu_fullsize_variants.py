@@ -121,12 +121,15 @@ def _check_gat(cfg_id, gas, dev, cfg, g, sg, F, dt, plan_t, delta):
     csc_pos = sg.csc_perm.to(torch.int32)
     res = {}
     for name, plan in (("fast", plan_t), ("plain", None)):
+        # the plain kernels: rows that start one element past a 16-byte boundary
+        rows_p, rows_gz = (torch.nn.functional.pad(t, (1, 2))[:, 1:F + 1] for t in (p, gz)) if name == "plain" else (p, gz)
         gp = torch.full((nv, F), float("nan"), dtype=dt, device=dev)
         gd = torch.full((F,), float("nan"), device=dev)
         gs = torch.full((F,), float("nan"), device=dev)
-        gas.gas_gat_aggregate_bwd(sg.rowptr, sg.col, sg.colptr, sg.row, csc_pos, p, a_dst, a_src, gz, gp, gd, gs, 0.2,
+        gas.gas_gat_aggregate_bwd(sg.rowptr, sg.col, sg.colptr, sg.row, csc_pos, rows_p, a_dst, a_src, rows_gz, gp, gd, gs, 0.2,
                                   plan_t=plan)
         res[name] = (gp, gd, gs)
+        del rows_p, rows_gz
     # The two vector gradients are sums over all entries, so no sample of the pattern gives them: the two paths are
     # compared with each other (each is compared with the oracle on small graphs).  They are sums of millions of
     # signed terms that cancel to a total far below the sum of their magnitudes, which is what a path's rounding

@@ -12,9 +12,10 @@ from tests.util import node_rel_err, to_np
 pytestmark = pytest.mark.gpu
 
 
+@pytest.mark.parametrize("planned", [False, True])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("F,heads", [(64, 4), (48, 4), (64, 2), (32, 3), (32, 6), (128, 2), (128, 4), (136, 2), (100, 5), (8, 8)])
-def test_heads_in_one_call(dtype, F, heads):
+def test_heads_in_one_call(dtype, F, heads, planned):
     import paper_2106_05609_amd as gas
     nv = 400
     ptr, col = _pattern_with_long_rows(43, nv, empty_rows=False)
@@ -32,7 +33,8 @@ def test_heads_in_one_call(dtype, F, heads):
     gas.gas_gat_aggregate(d_ptr, d_col, d_p, d_ad, d_as, z, heads=heads)
     gp = torch.full((nv, width), float("nan"), dtype=dtype, device="cuda")
     gd, gs = (torch.full((width,), float("nan"), device="cuda") for _ in range(2))
-    gas.gas_gat_aggregate_bwd(d_ptr, d_col, d_colptr, d_row, d_pos, d_p, d_ad, d_as, d_gz, gp, gd, gs, heads=heads)
+    plan_t = gas.gas_plan_create(d_colptr, col.size, F, n_rows=nv, ind=d_row) if planned else None
+    gas.gas_gat_aggregate_bwd(d_ptr, d_col, d_colptr, d_row, d_pos, d_p, d_ad, d_as, d_gz, gp, gd, gs, heads=heads, plan_t=plan_t)
     torch.cuda.synchronize()
     for h in range(heads):
         c = slice(h * F, (h + 1) * F)

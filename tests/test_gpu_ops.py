@@ -741,6 +741,8 @@ def test_gat_aggregate_backward_parity(gas, graphs_small, name, dtype, F):
     a_src = rng.normal(12, 972, 0, F, dtype=dtype) * 0.3
     gz = rng.normal_matrix(12, 973, nb, F, dtype=dtype)
     d = lambda t: t.to("cuda")
+    # rows one element past a 16-byte boundary: what the plain kernels take whatever the width (plan or no plan)
+    off = lambda t: torch.nn.functional.pad(t.to("cuda"), (1, 2))[:, 1:F + 1]
     want_p, want_d, want_s = oops.gat_aggregate_bwd(to_np(sg.rowptr), to_np(sg.col), to_np(p), to_np(a_dst), to_np(a_src),
                                                     to_np(gz), nv, 0.2)
     # Per-row scale of the rounding errors.  The softmax's backward subtracts the row's mean of dalpha from every
@@ -750,22 +752,23 @@ def test_gat_aggregate_backward_parity(gas, graphs_small, name, dtype, F):
     # An in-batch row v also receives (sum_k dt_k) a_dst, a sum over its own row's entries that cancels (it is
     # exactly zero for slope 1): its error is relative to sum_k alpha_k ||GZ[v]|| ||P[col k]|| max|a_dst|.
     terms = _gat_bwd_row_scale(to_np(sg.rowptr), to_np(sg.col), to_np(p), to_np(a_dst), to_np(a_src), to_np(gz), nb, nv)
-    for fast in (False, True):
+    for fast in (False, None, True):                       # plain kernels; no plan; a plan of the CSC copy
+        rows_p, rows_gz = (off(p), off(gz)) if fast is False else (d(p), d(gz))
         for n_out in (nv, nb):
             plan_t = gas.gas_plan_create(d(sg.colptr)[: n_out + 1], int(sg.colptr[n_out]), F, n_rows=n_out, ind=d(sg.row)) \
                 if fast else None
             gp = torch.full((n_out, F), float("nan"), dtype=dtype, device="cuda")
             gd = torch.full((F,), float("nan"), device="cuda")
             gs = torch.full((F,), float("nan"), device="cuda")
-            gas.gas_gat_aggregate_bwd(d(sg.rowptr), d(sg.col), d(sg.colptr), d(sg.row), d(sg.csc_perm).int(), d(p), d(a_dst),
-                                      d(a_src), d(gz), gp, gd, gs, 0.2, plan_t=plan_t)
+            gas.gas_gat_aggregate_bwd(d(sg.rowptr), d(sg.col), d(sg.colptr), d(sg.row), d(sg.csc_perm).int(), rows_p, d(a_dst),
+                                      d(a_src), rows_gz, gp, gd, gs, 0.2, plan_t=plan_t)
             assert node_rel_err(to_np(gp), want_p[:n_out], scale=terms[:n_out]) <= TOL[dtype], \
                 (fast, n_out, node_rel_err(to_np(gp), want_p[:n_out], scale=terms[:n_out]))
             # the two vector gradients are sums over all entries: against the size of the larger of the two
             scale = max(np.abs(want_d).max(), np.abs(want_s).max())
             assert np.abs(to_np(gd) - want_d).max() <= TOL[dtype] * scale and np.abs(to_np(gs) - want_s).max() <= TOL[dtype] * scale
             gp2 = torch.full((n_out, F), float("nan"), dtype=dtype, device="cuda")
-            gas.gas_gat_aggregate_bwd(d(sg.rowptr), d(sg.col), d(sg.colptr), d(sg.row), d(sg.csc_perm).int(), d(p), d(a_dst),
-                                      d(a_src), d(gz), gp2, gd, gs, 0.2, plan_t=plan_t)
+            gas.gas_gat_aggregate_bwd(d(sg.rowptr), d(sg.col), d(sg.colptr), d(sg.row), d(sg.csc_perm).int(), rows_p, d(a_dst),
+                                      d(a_src), rows_gz, gp2, gd, gs, 0.2, plan_t=plan_t)
             assert torch.equal(gp.view(torch.int16 if dtype == torch.bfloat16 else torch.int32),
                                gp2.view(torch.int16 if dtype == torch.bfloat16 else torch.int32))     # fixed order
