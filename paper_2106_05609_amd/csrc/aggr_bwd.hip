@@ -1274,12 +1274,14 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
                 (long long)need, (long long)workspace_bytes);
     GAS_REQUIRE(!plan_t || plan_t->n_rows == n_out, "gas_gat_aggregate_bwd: the plan is for %lld columns, n_out is %lld",
                 plan_t ? (long long)plan_t->n_rows : 0ll, (long long)n_out);
-    GAS_REQUIRE(!plan_t || plan_t->nnz <= nnz, "gas_gat_aggregate_bwd: the plan has %lld entries, the pattern %lld",
-                plan_t ? (long long)plan_t->nnz : 0ll, (long long)nnz);
     hipStream_t s = (hipStream_t)stream;
     const bool bf = dt == GAS_BF16;
     const int eb = elem_bytes(dt);
     const bool vec = vec_rows(dt, F, {P, GZ, GP, a_dst, a_src}, {ldp, ldgz, ldgp});
+    // a plan that the call has no use for (rows for the plain kernels, no output rows) may be any other pattern's
+    GAS_REQUIRE(!plan_t || !vec || n_out == 0 || plan_t->nnz <= nnz,
+                "gas_gat_aggregate_bwd: the plan has %lld entries, the pattern %lld", plan_t ? (long long)plan_t->nnz : 0ll,
+                (long long)nnz);
     const int H = vec ? gat_heads_together(bf ? gat_team<true>(F) : gat_team<false>(F), heads) : 1;
     GatBwdArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;

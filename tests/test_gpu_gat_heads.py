@@ -56,3 +56,20 @@ def test_head_counts_that_do_not_divide_are_refused():
     for heads in (0, 3):
         with pytest.raises(ValueError):
             gas.gas_gat_aggregate(ptr, col, t, t[0], t[0], torch.empty_like(t), heads=heads)
+
+
+def test_a_plan_that_is_not_used_may_have_more_entries():
+    """Rows that the plain kernels take: the plan is not looked at; rows for the fast path: it is refused."""
+    import paper_2106_05609_amd as gas
+    nv, F = 6, 16
+    ptr, col = torch.arange(nv + 1, dtype=torch.int32, device="cuda"), torch.arange(nv, dtype=torch.int32, device="cuda")
+    other_ptr, other = 2 * ptr, torch.cat([col, col])
+    plan = gas.gas_plan_create(other_ptr, 2 * nv, F, n_rows=nv, ind=other)
+    rows = rng.normal_matrix(14, 995, nv, F + 2).cuda()
+    a = rng.normal(14, 996, 0, F).cuda()
+    gd, gs, gp = torch.empty(F, device="cuda"), torch.empty(F, device="cuda"), torch.empty(nv, F, device="cuda")
+    call = lambda p, g: gas.gas_gat_aggregate_bwd(ptr, col, ptr, col, col, p, a, a, g, gp, gd, gs, plan_t=plan)
+    call(rows[:, 1:F + 1], rows[:, 1:F + 1])
+    assert torch.equal(gp, rows[:, 1:F + 1])               # one entry a row: its weight is 1, its score has no gradient
+    with pytest.raises(gas.GasError):
+        call(rows[:, :F].contiguous(), rows[:, :F].contiguous())
