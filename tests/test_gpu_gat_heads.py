@@ -73,3 +73,35 @@ def test_a_plan_that_is_not_used_may_have_more_entries():
     assert torch.equal(gp, rows[:, 1:F + 1])               # one entry a row: its weight is 1, its score has no gradient
     with pytest.raises(gas.GasError):
         call(rows[:, :F].contiguous(), rows[:, :F].contiguous())
+
+
+def test_more_columns_than_a_launch_has_wavefronts():
+    """2^26 + 5 columns, entries in the first and the last of them, against the same entries on a table of those columns."""
+    import paper_2106_05609_amd as gas
+    if torch.cuda.mem_get_info()[0] < 24 << 30:
+        pytest.skip("needs 24 GiB of device memory")
+    n_cols, nb, F, heads = (1 << 26) + 5, 10, 8, 2
+    width = F * heads
+    d = lambda a: torch.from_numpy(a.astype(np.int32)).cuda()
+    used = np.concatenate([np.arange(nb), n_cols - nb + np.arange(nb)])           # columns with an entry, in order
+    small_col = np.stack([np.arange(nb), nb + np.arange(nb)], 1).reshape(-1)      # row v: columns v and nb + v of those
+    pos = np.concatenate([2 * np.arange(nb), 2 * np.arange(nb) + 1])              # CSC order
+    ptr, row = d(2 * np.arange(nb + 1)), d(np.concatenate([np.arange(nb), np.arange(nb)]))
+    small_p = (rng.normal_matrix(14, 997, 2 * nb, width, dtype=torch.bfloat16) * 0.5).cuda()
+    ad, asr = ((rng.normal(14, s, 0, width, dtype=torch.bfloat16) * 0.2).cuda() for s in (998, 999))
+    gz = rng.normal_matrix(14, 1000, nb, width, dtype=torch.bfloat16).cuda()
+    big_p = torch.zeros(n_cols, width, dtype=torch.bfloat16, device="cuda")
+    big_p[torch.from_numpy(used).cuda()] = small_p
+    big_ptr = torch.full((n_cols + 1,), nb, dtype=torch.int32, device="cuda")
+    big_ptr[:nb + 1] = torch.arange(nb + 1, device="cuda")
+    big_ptr[-nb - 1:] += torch.arange(nb + 1, dtype=torch.int32, device="cuda")
+    got = []
+    for p, col, colptr in ((big_p, used[small_col], big_ptr), (small_p, small_col, d(np.arange(2 * nb + 1)))):
+        gp = torch.full_like(p, 7.0)
+        gd, gs = (torch.empty(width, device="cuda") for _ in range(2))
+        gas.gas_gat_aggregate_bwd(ptr, d(col), colptr, row, d(pos), p, ad, asr, gz, gp, gd, gs, heads=heads)
+        got.append((gp, gd, gs))
+    at = torch.from_numpy(used).cuda()
+    assert torch.equal(got[0][0][at], got[1][0])
+    assert bool((got[0][0][nb:n_cols - nb] == 0).all())
+    assert torch.allclose(got[0][1], got[1][1], rtol=1e-5, atol=1e-6) and torch.allclose(got[0][2], got[1][2], rtol=1e-5, atol=1e-6)
