@@ -107,10 +107,16 @@ ONE_LAUNCH_MAX_ROW = 512
 
 
 def _mlp_in_two(z, w1, w2) -> bool:
-    """Whether GIN's MLP is faster as two products with the hidden activation stored between them: in fp32 (4,000 rows,
-    256 -> 256 -> 256: 22 us against 33 us fused, whose 32-row tiles split every weight again), and in bf16 with widths
-    the fused kernels take an element at a time."""
-    return z.dtype == torch.float32 or z.shape[1] % 8 != 0 or w1.shape[1] % 8 != 0 or w2.shape[1] % 8 != 0
+    """Whether GIN's MLP is faster as two products with the hidden activation stored between them, which run on bf16 parts
+    (csrc/split.h) where the fused fp32 kernel uses the fp32 instruction on 32 rows a workgroup: 4,000 rows of
+    256 -> 256 -> 256 19 us against 33 fused, 64 -> 64 -> 64 11 against 13.  Narrow layers of few rows save a launch by the fused kernel: up to three
+    steps of 32 of the two reduced widths, 32 output columns and a workgroup for every compute unit (4,000 rows: 32 -> 32 -> 32 8 us
+    fused, 11 in two, 64 -> 32 -> 32 9.7 and 10.8; 128 -> 32 -> 32 12.7 and 10.9, 24,000 rows of 32 -> 32 -> 32 16.5 and 10.7).
+    bf16 has fused kernels of its own."""
+    if z.dtype != torch.float32:
+        return False
+    steps = -(-z.shape[1] // 32) + -(-w1.shape[1] // 32)
+    return not (z.shape[0] <= 8192 and steps <= 3 and w2.shape[1] <= 32)
 
 
 def _pushes(do_push, table) -> bool:

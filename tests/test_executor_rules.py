@@ -1,0 +1,16 @@
+"""Which form of a call the executor takes."""
+import pytest
+import torch
+
+from paper_2106_05609_amd import executor
+
+
+@pytest.mark.parametrize("dtype,rows,f_in,hidden,f_out,in_two", [
+    (torch.float32, 2000, 32, 32, 32, False), (torch.float32, 8192, 64, 32, 7, False), (torch.float32, 20, 8, 64, 32, False),
+    (torch.float32, 8193, 32, 32, 32, True), (torch.float32, 100, 33, 64, 32, True), (torch.float32, 100, 32, 32, 33, True),
+    (torch.float32, 4000, 256, 256, 256, True), (torch.float32, 500, 64, 64, 64, True), (torch.float32, 500, 1433, 32, 7, True),
+    # measured: the fused bf16 kernels were the faster ones at a hundred rows of odd widths
+    (torch.bfloat16, 100, 250, 250, 250, False), (torch.bfloat16, 5000, 256, 256, 47, False), (torch.bfloat16, 5000, 256, 256, 256, False)])
+def test_form_of_the_mlp(dtype, rows, f_in, hidden, f_out, in_two):
+    shape = lambda *s: torch.empty(*s, dtype=dtype, device="meta")
+    assert executor._mlp_in_two(shape(rows, f_in), shape(f_in, hidden), shape(hidden, f_out)) is in_two
