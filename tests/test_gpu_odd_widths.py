@@ -90,3 +90,23 @@ def test_bf16_products_of_odd_widths(what, m, k, n, views):
             assert bool((pad[:, 0] == 7.0).all()) and bool((pad[:, cols + 1:] == 7.0).all())
     # products of bf16 numbers are exact in fp32; every addition rounds a partial sum of at most `size`
     assert bool(((out.double() - want).abs() <= stored * want.abs() + (terms + 2) * 2.0 ** -24 * size * (1 + stored)).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("F", [7, 33, 250, 256])
+def test_push_of_odd_rows_to_host_memory(F, dtype):
+    """From the transform's call and by itself: the rows named, and no byte of their neighbours."""
+    import paper_2106_05609_amd as gas
+    m, n_table = 300, 1001
+    z, w = rng.normal_matrix(3, 830, m, 40, dtype=dtype).cuda(), rng.normal_matrix(3, 831, 40, F, dtype=dtype).cuda()
+    w2 = rng.normal_matrix(3, 832, F, F, dtype=dtype).cuda()
+    idx = rng.permutation(3, 833, n_table)[:m].to(torch.int32).cuda()
+    y, h = (torch.empty(m, F, dtype=dtype, device="cuda") for _ in range(2))
+    for call in (lambda t: gas.gas_linear_push(z, w, y, idx, t), lambda t: gas.gas_mlp2_push(z, w, w2, y, idx, t),
+                 lambda t: gas.gas_mlp2_keep(z, w, w2, y, h, idx=idx, hist=t), lambda t: gas.gas_push(y, idx, t)):
+        rows = torch.full((n_table, F), 7.0, dtype=dtype).pin_memory()
+        call(gas.HostTable(rows))
+        torch.cuda.synchronize()
+        want = torch.full((n_table, F), 7.0, dtype=dtype)
+        want[idx.cpu().long()] = y.cpu()
+        assert torch.equal(rows, want)
