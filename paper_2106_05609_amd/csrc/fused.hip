@@ -270,7 +270,9 @@ gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const floa
     a.diag = diag; a.s_agg = s_agg; a.s_res = s_res; a.c_id = c_identity; a.c_w = c_weight; a.relu = relu;
 
     const int smem = 4 * (kRows * (a.Kp + 4) + a.Kp * (a.Np + 4));      // at most 84,480 bytes
-    const int64_t per_cu = smem <= 32768 ? 4 : (smem <= 65536 ? 2 : 1);          // workgroups per CU
+    // Workgroups that a CU holds at once, by registers (three) and LDS: one more would wait for a slot and then walk its
+    // tiles alone.  100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us.
+    const int64_t per_cu = smem <= 32768 ? 3 : (smem <= 65536 ? 2 : 1);
     const int64_t per_xcd = (a.n_tiles + 7) / 8;                                   // a multiple of eight workgroups
     const unsigned blocks = (unsigned)(8 * (per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu));
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(spmm_linear_f32_kernel),

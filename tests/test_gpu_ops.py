@@ -419,6 +419,22 @@ def test_layer_in_one_launch_matches_the_oracle(gas, graphs_small, name, K, N, v
     assert torch.equal(y2, y3)
 
 
+@pytest.mark.parametrize("m,F", [(24576, 64), (24577, 64), (60001, 64), (50001, 32), (30011, 128)])
+def test_layer_in_one_launch_when_workgroups_take_several_tiles(gas, m, F):
+    """More tiles than workgroups that fit: the same bits as the rows in calls of their own."""
+    x, w = rng.normal_matrix(7, 360, 500, F).cuda(), rng.normal_matrix(7, 361, F, F).cuda()
+    lens = torch.arange(m) % 9
+    ptr = torch.cat([torch.zeros(1, dtype=torch.long), torch.cumsum(lens, 0)]).int()
+    src, val = ((torch.arange(int(ptr[-1])) * 31) % 500).int().cuda(), rng.normal(7, 362, 0, int(ptr[-1])).cuda()
+    y, parts = torch.full((m, F), float("nan"), device="cuda"), torch.full((m, F), float("nan"), device="cuda")
+    gas.gas_spmm_linear(ptr.cuda(), src, val, x, w, y, relu=True)
+    for a in range(0, m, 5000):
+        b = min(m, a + 5000)
+        e0, e1 = int(ptr[a]), int(ptr[b])
+        gas.gas_spmm_linear((ptr[a:b + 1] - e0).cuda(), src[e0:e1], val[e0:e1], x, w, parts[a:b], relu=True)
+    assert torch.equal(y, parts)
+
+
 def test_layer_in_one_launch_limits(gas):
     """Shapes the one-launch layer does not take are refused before anything is launched."""
     ptr = dev(torch.tensor([0, 1, 2], dtype=torch.int32))
