@@ -142,20 +142,6 @@ __device__ __forceinline__ int queue_long_rows(const int32_t* rowptr, int64_t n_
     return *n_queued;
 }
 
-// A value that is the same in all lanes of a wavefront, summed (or its maximum taken) over the W wavefronts of
-// the workgroup in wavefront order; every thread of the workgroup calls it.
-template <int W, bool MAX>
-__device__ __forceinline__ float across_waves(float x, float* red) {
-    if constexpr (W == 1) return x;
-    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
-    __syncthreads();
-    float r = red[0];
-#pragma unroll
-    for (int o = 1; o < W; ++o) r = MAX ? fmaxf(r, red[o]) : r + red[o];
-    __syncthreads();
-    return r;
-}
-
 // elements in a 16-byte piece
 template <bool BF> struct Elems { static constexpr int E = BF ? 8 : 4; };
 

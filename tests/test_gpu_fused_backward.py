@@ -68,3 +68,31 @@ def test_many_matrices_updated_in_shared_launches(dtype):
     for w, dw in zip(ws, dws):
         gas.gas_sgd_step(w, dw, 0.1, 0.01)
     assert all(torch.equal(a, b) for a, b in zip(got, ws))
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("n,F", [(70, 64), (5000, 64), (25000, 72), (30000, 256)])
+def test_input_gradient_with_identity_and_total(n, F, dtype):
+    """GCNII's call: the identity term, no addend, no mask, and the initial residual's running total."""
+    import paper_2106_05609_amd as gas
+    gp, w, t0 = (rng.normal_matrix(5, s, a, F, dtype=dtype).cuda() for s, a in ((920, n), (921, F), (922, n + 9)))
+    want, total = torch.empty_like(gp), t0.clone()
+    gas.gas_linear_bwd_input(gp, w, want, c_identity=0.6, c_weight=0.4)
+    gas.gas_axpy(total[:n], want, total[:n], 0.1)
+    got, total2 = torch.empty_like(want), t0.clone()
+    gas.gas_linear_bwd_input_add(gp, w, got, c_identity=0.6, c_weight=0.4, total=total2[:n], c_total=0.1)
+    assert torch.equal(got, want) and torch.equal(total2, total)
+
+
+@pytest.mark.parametrize("n,f_out,f_in", [(65, 64, 64), (5000, 64, 72), (30000, 40, 250)])
+def test_input_gradient_in_place_of_the_addend(n, f_out, f_in):
+    import paper_2106_05609_amd as gas
+    gp, w, add, y = (rng.normal_matrix(5, s, a, b).cuda() for s, a, b in ((923, n, f_out), (924, f_in, f_out), (925, n, f_in), (926, n, f_in)))
+    want = torch.empty_like(add)
+    gas.gas_linear_bwd_input_add(gp, w, want, c_weight=0.7, add=add, mask=y)
+    gas.gas_linear_bwd_input_add(gp, w, add, c_weight=0.7, add=add, mask=y)
+    assert torch.equal(add, want)
+    t = torch.zeros(4, 8, dtype=torch.bfloat16, device="cuda")
+    out = torch.zeros(4, 8, dtype=torch.bfloat16, device="cuda")
+    with pytest.raises(gas.GasError):                              # bf16 rounds in between: no addend in place
+        gas.gas_linear_bwd_input_add(t, torch.zeros(8, 8, dtype=torch.bfloat16, device="cuda"), out, add=out)
