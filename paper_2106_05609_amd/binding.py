@@ -135,9 +135,15 @@ def _ptr(t, dtype=None):
     return t.data_ptr()
 
 
+# the current stream's handle without a Stream object around it, where torch has these (they are not public)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    # the current stream's handle without a Stream object around it
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    if _raw_stream is None or _device is None:
+        return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def gas_version() -> int:

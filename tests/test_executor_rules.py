@@ -1,4 +1,4 @@
-"""Which form of a call the executor takes."""
+"""Which form of a call the executor and the binding take."""
 import pytest
 import torch
 
@@ -14,3 +14,15 @@ from paper_2106_05609_amd import executor
 def test_form_of_the_mlp(dtype, rows, f_in, hidden, f_out, in_two):
     shape = lambda *s: torch.empty(*s, dtype=dtype, device="meta")
     assert executor._mlp_in_two(shape(rows, f_in), shape(f_in, hidden), shape(hidden, f_out)) is in_two
+
+
+@pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
+def test_stream_without_torchs_private_functions(missing, monkeypatch):
+    from paper_2106_05609_amd import binding
+
+    class Stream:
+        cuda_stream = 1234
+
+    monkeypatch.setattr(binding, missing, None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: Stream)
+    assert binding._stream() == 1234
