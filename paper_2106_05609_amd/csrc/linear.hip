@@ -236,8 +236,10 @@ __device__ __forceinline__ void store_tile(const LinArgs& a, int64_t m0, int n0,
     const bool whole = m0 + 32 * TM <= a.M && n0 + 32 * TN <= a.N && a.ldy < kNear && a.ldz < kNear && a.ldmask < kNear &&
                        a.ld_push < kNear && a.ldadd < kNear && a.ldtotal < kNear;
     const bool extra = a.c_id != 0.f || a.mask || a.add || a.total;
-    if (whole && !extra && !a.push_idx) store_rows<TM, TN, true, false, false>(a, m0, n0, li, lh, acc);
-    else if (whole && !extra) store_rows<TM, TN, true, false, true>(a, m0, n0, li, lh, acc);
+    if (!extra && !a.push_idx) {
+        if (whole) store_rows<TM, TN, true, false, false>(a, m0, n0, li, lh, acc);
+        else store_rows<TM, TN, false, false, false>(a, m0, n0, li, lh, acc);
+    } else if (whole && !extra) store_rows<TM, TN, true, false, true>(a, m0, n0, li, lh, acc);
     else if (whole && !a.push_idx) store_rows<TM, TN, true, true, false>(a, m0, n0, li, lh, acc);
     else if (!a.push_idx) store_rows<TM, TN, false, true, false>(a, m0, n0, li, lh, acc);
     else store_rows<TM, TN, false, true, true>(a, m0, n0, li, lh, acc);
@@ -1484,11 +1486,18 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         a.add = static_cast<const char*>(add); a.ldadd = ldadd;
         a.total = static_cast<char*>(total); a.ldtotal = ldtotal; a.c_total = c_total;
         a.push_idx = push.idx; a.push_hist = static_cast<char*>(push.hist); a.ld_push = push.ld_hist;
-        // The largest tile that still gives most compute units a workgroup: a larger one splits each value for more
-        // products.  50,000 x 256 x 256: 54 us in 128 x 128 tiles; 4,000 x 256 x 256: 11 us in 64 x 64 tiles.
-        const int64_t tiles = (n_rows + 127) / 128;
-        if (F_out > 64 && tiles * ((F_out + 127) / 128) >= 192) return launch_split<128, 128, 2, 2>(a, s);
-        if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);
+        // Up to 16 input columns one step of 16 k takes them all.  Up to 64 a tile's loads and stores outweigh its products, and
+        // many small workgroups overlap best until their number hides that too (100,000 x 64 x 64: 13.5 us, in 128 x 64 tiles
+        // 15.6; 28,000 x 47 x 100: 11, 13 in 128 x 64, 17 in 128 x 128; but 300,000 x 64 x 256: 127, 103 in 128 x 128).  Beyond,
+        // a larger tile splits each value for more products, as long as most compute units have a workgroup: 128 x 128
+        // where two each are nearly reached (28,000 x 256 x 128, 219 tiles: 23 us, in 128 x 64 18; 50,000 x 256 x 128, 391
+        // tiles: 27, in 128 x 64 35), 4,000 x 256 x 256 10 us in 64 x 64 tiles.
+        const int64_t tiles = (n_rows + 127) / 128, large = tiles * ((F_out + 127) / 128);
+        if (F_in <= 16) return launch_split<64, 64, 1, 4>(a, s);
+        if (F_in > 64 || large >= 2048) {
+            if (F_out > 64 && large >= 352) return launch_split<128, 128, 2, 2>(a, s);
+            if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);
+        }
         return launch_split<64, 64, 2, 4>(a, s);
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;

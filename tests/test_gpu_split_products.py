@@ -143,3 +143,21 @@ def test_sums_of_one_term_are_rounded_once(what, rows, cols):
         a = a[:rows]
         got = _call(what, a.t().contiguous(), torch.zeros(rows, cols), b)
     assert torch.equal(got, a * b)
+
+
+# the borders of the rules that choose a tile: 16, 17, 64 and 65 input columns, 352 tiles of 128 x 128 (here 345 rows of tiles
+# and more), one and several columns of tiles, ragged last tiles
+@pytest.mark.parametrize("what", ["linear", "input"])
+@pytest.mark.parametrize("m,k,n", [(300, 16, 130), (300, 17, 130), (50000, 5, 7), (44929, 64, 65), (44929, 65, 65), (45057, 65, 65),
+                                   (24577, 65, 64), (24449, 65, 47), (262145, 64, 70)])
+def test_borders_of_the_tile_rules(what, m, k, n):
+    z, w = rng.normal_matrix(11, 750, m, k).cuda(), rng.normal_matrix(11, 751, k, n).cuda()
+    import paper_2106_05609_amd as gas
+    out = torch.full((m, n), float("nan"), device="cuda")
+    if what == "linear":
+        gas.gas_linear(z, w, out)
+    else:
+        gas.gas_linear_bwd_input(z, w.t().contiguous(), out)
+    z64, w64 = z.double(), w.double()
+    bound = (k + 8) * 2.0 ** -24 * (z64.abs() @ w64.abs())
+    assert bool(((out.double() - z64 @ w64).abs() <= bound).all())
