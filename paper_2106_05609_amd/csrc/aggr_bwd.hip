@@ -904,7 +904,7 @@ void launch_gat_bwd(const GatBwdArgs& a, bool columns, hipStream_t s) {
 
 template <bool BF>
 void launch_gat_bwd_heads(const GatBwdArgs& a, int H, bool columns, hipStream_t s) {
-    const int G = gat_team<BF>(a.F);
+    const int G = gat_team<BF>(a.F, true);
     if (G == 64) launch_gat_bwd<BF, 64, 1>(a, columns, s);
     else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, columns, s) : launch_gat_bwd<BF, 32, 1>(a, columns, s);
     else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, columns, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, columns, s) : launch_gat_bwd<BF, 16, 1>(a, columns, s);
@@ -1289,7 +1289,7 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
     GAS_REQUIRE(!plan_t || !vec || n_out == 0 || plan_t->nnz <= nnz,
                 "gas_gat_aggregate_bwd: the plan has %lld entries, the pattern %lld", plan_t ? (long long)plan_t->nnz : 0ll,
                 (long long)nnz);
-    const int H = vec ? gat_heads_together(bf ? gat_team<true>(F) : gat_team<false>(F), heads) : 1;
+    const int H = !vec ? 1 : (bf ? gat_heads_together<true>(F, heads) : gat_heads_together<false>(F, heads));
     GatBwdArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;
     a.colptr = colptr; a.row = row; a.csc_pos = csc_pos; a.n_cols = n_cols; a.n_out = n_out;

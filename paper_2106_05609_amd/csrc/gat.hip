@@ -211,11 +211,11 @@ void launch_rows(const GatArgs& a, hipStream_t s) {
 // H heads of at most 64 / H teams of lanes
 template <bool BF>
 void launch_vec(const GatArgs& a, int H, hipStream_t s) {
-    const int G = gat_team<BF>(a.F);
+    const int G = gat_team<BF>(a.F, H > 1);
     if (G == 64) launch_rows<BF, 64, 1>(a, s);
     else if (G == 32) H == 2 ? launch_rows<BF, 32, 2>(a, s) : launch_rows<BF, 32, 1>(a, s);
     else if (G == 16) H == 4 ? launch_rows<BF, 16, 4>(a, s) : H == 2 ? launch_rows<BF, 16, 2>(a, s) : launch_rows<BF, 16, 1>(a, s);
-    else if constexpr (BF) H == 4 ? launch_rows<BF, 8, 4>(a, s) : H == 2 ? launch_rows<BF, 8, 2>(a, s) : launch_rows<BF, 8, 1>(a, s);
+    else if constexpr (BF) H == 4 ? launch_rows<BF, 8, 4>(a, s) : launch_rows<BF, 8, 2>(a, s);
 }
 
 // any alignment, widths up to 64 * NE: lane l owns elements l, l + 64, ...; one entry at a time
@@ -307,7 +307,7 @@ extern "C" gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32
     hipStream_t s = (hipStream_t)stream;
     const bool vec = F % e == 0 && F <= 64 * e && ldp % e == 0 && ldz % e == 0 && aligned16(P) && aligned16(Z) &&
                      aligned16(a_dst) && aligned16(a_src);
-    const int H = vec ? gat_heads_together(dt == GAS_BF16 ? gat_team<true>(F) : gat_team<false>(F), heads) : 1;
+    const int H = !vec ? 1 : (dt == GAS_BF16 ? gat_heads_together<true>(F, heads) : gat_heads_together<false>(F, heads));
     for (int32_t h = 0; h < heads; h += H) {
         gas_status st = GAS_OK;
         if (vec && dt == GAS_BF16) launch_vec<true>(a, H, s);

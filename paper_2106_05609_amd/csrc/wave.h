@@ -162,16 +162,21 @@ __device__ __forceinline__ u32x4 pack(const float (&x)[Elems<BF>::E]) {
 }
 
 // ---- how many lanes a head takes (the team), and how many heads a wavefront takes together
+// eight: teams of 8 for heads of at most 8 pieces (64 bf16).  The backward pass and several heads together take them; the
+// forward pass of one head keeps 16 lanes: with 8 the entries of a short row are spread over eight slots whose eight loads
+// stay mostly empty (200,000 rows of 3 entries, 64 bf16: 193 us, with teams of 8 237; 100,000 of 12: 112 and 131; from 30
+// entries on teams of 8 are the faster ones, 1,000 rows of 60 13 and 11 us, but a call does not know its rows' lengths).
 template <bool BF>
-inline int gat_team(int32_t F) {
+inline int gat_team(int32_t F, bool eight) {
     const int pieces = F / Elems<BF>::E;              // whole pieces, at most 64
-    return BF && pieces <= 8 ? 8 : (pieces <= 16 ? 16 : (pieces <= 32 ? 32 : 64));
+    return BF && eight && pieces <= 8 ? 8 : (pieces <= 16 ? 16 : (pieces <= 32 ? 32 : 64));
 }
 // Powers of two: team numbers split by shifts.  95,000 nodes, 550,000 entries, four heads of 64 floats: 66 us, a
 // launch per head 4 x 37 us.
-inline int gat_heads_together(int team, int32_t heads) {
+template <bool BF>
+inline int gat_heads_together(int32_t F, int32_t heads) {
     int H = 1;
-    while (H < 4 && heads % (2 * H) == 0 && team * 2 * H <= 64) H *= 2;
+    while (H < 4 && heads % (2 * H) == 0 && gat_team<BF>(F, false) * 2 * H <= 64) H *= 2;
     return H;
 }
 
