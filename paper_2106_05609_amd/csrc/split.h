@@ -12,11 +12,12 @@
 // ah bh has an accumulator of its own and the five small terms share another, so the large one is rounded once per 16
 // k: the relative error against 64 bits (2-norm, N(0,1) operands) is 9.0e-8 at K = 256 and 1.7e-7 at K = 832, with the
 // fp32 instruction 2.9e-7 and 5.2e-7.  With one accumulator for all six it is 2.5e-7 and 4.5e-7, but the instruction's
-// rounding has a bias that adds up: 2.1e-6 against 8.8e-7 for a weight gradient over 600,000 rows.
+// rounding has a bias that adds up: a weight gradient over 600,000 rows is 2.1e-6 off (fp32 instruction 8.7e-7, two
+// accumulators 3.2e-7).  Sums that only grow, of absolute values, over the same rows: 5.9e-8 (fp32 instruction 7.3e-8).
 //
 // What bounds it: matrix pipe 52 %, vector instructions of the split 31 % of the cycles by the counters, the clock
-// falls to 1.8 GHz under this load; 50,000 x 256 x 256 take 54 us (91 us with the fp32 instruction), 600,000 rows
-// 534 us (748).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
+// falls to 1.8 GHz under this load; 50,000 x 256 x 256 take 54 us (87 us with the fp32 instruction), 600,000 rows
+// 545 us (738).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
 // compute unit: 55-63 us; products and split interleaved by hand in one wavefront, two LDS buffers: 49-56 us.
 //
 // What the split cannot represent: an infinity, a NaN or a value that rounds to an infinite bf16 makes the accumulator
@@ -26,7 +27,7 @@
 // an operand of 2^-116 N(0,1), 5.6e-4 at 2^-124).  So the least non-zero magnitude is kept while staging, and a workgroup
 // that met one below 2^-110 takes its tile again with both operands times 2^40: every fp32 number is then represented
 // whole, and what leaves the range at the upper end is non-finite, as above.  The search costs one and a half
-// instructions a value (4,000 x 256 x 256: 9.7 -> 10.0 us, 50,000 rows 53.7 -> 54.0 us); with such a value in every tile
+// instructions a value (4,000 x 256 x 256: 9.7 -> 10.3 us, 50,000 rows 53.7 -> 54.0 us); with such a value in every tile
 // 50,000 rows take 92 us (the fp32 instruction 86 us), with one beyond 2^88 as well 211 us.
 #pragma once
 #include "common.h"
