@@ -26,9 +26,9 @@
  *     host before anything is launched; a failed call launches nothing.
  *   - Index VALUES are not range-checked on the hot path (an out-of-range
  *     index is undefined behaviour); gas_validate_indices checks them.
- *   - Rows whose base address and byte stride are multiples of 16 take the
- *     128-bit path; anything else falls back to an element-wise path with
- *     identical results.
+ *   - Rows of any alignment and width are taken.  Those whose base address and
+ *     byte stride are multiples of 16 take the fastest kernels; others take
+ *     other ones or an element-wise path, whose results agree to rounding.
  *   - Reductions use no atomics and a fixed order: results are bit-identical
  *     from run to run for the same inputs and the same plan.
  */
@@ -398,7 +398,8 @@ GAS_API gas_status gas_softmax_xent(const void* A, int64_t lda, int64_t n_rows, 
                             void* G, int64_t ldg, void* stream);
 GAS_API gas_status gas_sgd_step(void* W, int64_t n, gas_dtype dt, const float* dW, float lr, float weight_decay,
                         void* stream);
-/* gas_sgd_step of `count` matrices, in order (W, n, dW: host arrays of `count`); the matrices share launches. */
+/* gas_sgd_step of `count` matrices, in order (W, n, dW: host arrays of `count`); the matrices share launches.  A gradient
+ * must not overlap a matrix of the call. */
 GAS_API gas_status gas_sgd_steps(int32_t count, void* const* W, const int64_t* n, gas_dtype dt, const float* const* dW,
                          float lr, float weight_decay, void* stream);
 

@@ -1559,7 +1559,8 @@ gas_status gas_linear_bwd_input_add(const void* GP, int64_t ldgp, int64_t n_rows
                                     int64_t ldadd, const void* mask, int64_t ldmask, float c_total, void* total,
                                     int64_t ldtotal, void* GZ, int64_t ldgz, void* stream) {
     const char* who = "gas_linear_bwd_input_add";
-    GAS_REQUIRE((!add || ldadd >= F_in) && (!total || ldtotal >= F_in), "%s: row stride smaller than the row", who);
+    GAS_REQUIRE((!add || ldadd >= F_in) && (!mask || ldmask >= F_in) && (!total || ldtotal >= F_in),
+                "%s: row stride smaller than the row", who);
     GAS_REQUIRE(!total || (total != GZ && total != GP && total != add && total != mask), "%s: the total aliases another matrix", who);
     GAS_REQUIRE(!add || add != GZ || ldadd == ldgz, "%s: an output in place of the addend needs its row stride", who);
     hipStream_t s = (hipStream_t)stream;

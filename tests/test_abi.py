@@ -124,3 +124,15 @@ def test_a_zero_count_is_a_no_op():
         st = fn(*_args(params, None, 0, 0))
         assert st == (-1 if name in ("gas_linear_bwd_weight", "gas_linear_bwd_weight_static", "gas_sq_norm",
                                   "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd") else 0), name
+
+
+def test_a_refused_input_gradient_has_launched_nothing():
+    """bf16 takes its steps in several launches: a mask whose rows are too narrow is refused before the first (without a GPU a
+    launch would be a HIP error)."""
+    L = binding.lib()
+    L.gas_linear_bwd_input_add.restype = ctypes.c_int
+    p, q, i, f = ctypes.c_void_p, ctypes.c_int64, ctypes.c_int32, ctypes.c_float
+    a = [p(4096 * k) for k in range(1, 7)]                   # never dereferenced on the host
+    st = L.gas_linear_bwd_input_add(a[0], q(8), q(4), i(8), a[1], i(8), ctypes.c_int(1), f(0.0), f(1.0), a[2], q(8), a[3], q(3),
+                                    f(0.0), a[4], q(8), a[5], q(8), p(0))
+    assert st == -1 and b"row stride" in L.gas_last_error()
