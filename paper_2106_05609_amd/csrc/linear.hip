@@ -270,6 +270,322 @@ __global__ __launch_bounds__(256, WPS) void linear_split_kernel(LinArgs a) {
     store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
+// fp32, weights stationary: a matrix of up to 32 KT x 256 stays, split, in the registers of one persistent workgroup of
+// eight wavefronts (32 output columns each), and row tiles stream past it: a row is split once, not once per column tile,
+// and a weight once per workgroup, not once per row tile.
+//
+// Products of 16 x 16 x 32, taken transposed (the weights are the first operand): a lane ends up with eight consecutive
+// columns of one row, stored as two 16-byte pieces.  LDS holds the three parts of two row tiles: while one is multiplied the
+// next is split and written, by wavefronts 0-3 before their products and by 4-7 after theirs, so that of the two wavefronts
+// of a SIMD one splits while the other multiplies; one barrier a tile.  The operands of a step are read from LDS one step
+// ahead (sched_barrier keeps them there: left to itself the compiler reads each fragment right before its use, 50,000 x 256 x
+// 256 then take 50 us).  With 256 columns the registers do not hold all of it: the third parts of the first LS steps lie in LDS (without:
+// spills, 54 us).
+//
+// Bound by the matrix pipe and the vector unit together, at the clock that the power allows (1.7-1.9 GHz; the instructions alone,
+// on random operands, reach 1,400-1,900 TFLOP/s): 50,000 x 256 x 256 46 us, by the 128 x 128 tiles above 59; 600,000 rows 454 (1,040 TFLOP/s
+// of bf16 products) and 567, with the push 520 and 601.  The same products in the same order: the same bits.
+//
+// A tile that holds a value below 2^-110 is staged again times 2^40 (split.h says why), and so are the weights if one of
+// them is; a wavefront whose sums are not finite takes its block again with the fp32 instruction.
+template <int KT, bool MASK>
+struct WsSplit {
+    static constexpr int RB = KT <= 4 ? 2 : 1, ROWS = 16 * RB;                  // rows of a tile
+    static constexpr int KP = 4 * KT, PITCH = (KP + 7) / 8 * 64;                // pieces of eight k, bf16 elements of a row in LDS
+    static constexpr int PLANE = ROWS * PITCH;
+    static constexpr int LS = KT == 8 ? (MASK ? 6 : 4) : (KT == 7 ? 2 : 0);     // steps of 32 k whose third parts lie in LDS
+    static constexpr int kLdsBytes = 2 * 3 * PLANE * 2 + LS * 2 * 512 * 16 + 32;
+};
+template <int KT, bool TRANS, bool MASK>
+__global__ __launch_bounds__(512) void linear_ws_split_kernel(LinArgs a, int64_t n_tiles) {
+    using L = WsSplit<KT, MASK>;
+    constexpr int RB = L::RB, ROWS = L::ROWS, KP = L::KP, PITCH = L::PITCH, PLANE = L::PLANE, LS = L::LS;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    uint16_t* planes = reinterpret_cast<uint16_t*>(smem);                              // [2][3][ROWS][PITCH]
+    bf16x8* wlds = reinterpret_cast<bf16x8*>(smem + 2 * 3 * PLANE * 2);                // [LS][2][512]
+    uint32_t* low_tile = reinterpret_cast<uint32_t*>(smem + 2 * 3 * PLANE * 2 + LS * 2 * 512 * 16);     // [4], of tile it & 3
+    uint32_t* low_w = low_tile + 4;
+    const float* Z = reinterpret_cast<const float*>(a.Z);
+    const float* W = reinterpret_cast<const float*>(a.W);
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int c0 = 32 * wave;                                         // the wavefront's first column
+    const int wcol = c0 + 8 * (li >> 2) + (li & 3);                   // column of the lane's weights in block 0 (+ 4 in block 1)
+    if (tid < 5) low_tile[tid] = 0;
+    __syncthreads();
+
+    auto split8 = [](const float (&x)[8], bf16x8 (&f)[3]) {
+        u32x4 h, m, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t u, v, w;
+            split_pair(x[2 * e], x[2 * e + 1], u, v, w);
+            h[e] = u; m[e] = v; l[e] = w;
+        }
+        f[0] = __builtin_bit_cast(bf16x8, h);
+        f[1] = __builtin_bit_cast(bf16x8, m);
+        f[2] = __builtin_bit_cast(bf16x8, l);
+    };
+    auto least = [](const float (&x)[8], uint32_t low) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) low = min(low, 2 * __float_as_uint(x[e]) - 1);
+        return low;
+    };
+
+    // ---- the thread's piece of a row tile: eight k of one row
+    const int prow = tid / KP, piece = tid % KP;
+    const int at = prow * PITCH + 8 * (piece ^ (prow & 7));
+    const bool stages = ROWS * KP == 512 || prow < ROWS;
+    float raw[8];
+    auto fetch = [&](int64_t tile) {
+        if (!stages) return;
+        int64_t m = tile * ROWS + prow;
+        m = m < a.M ? m : a.M - 1;
+        // no branch around the loads and no write to their registers until stage(): either would wait for what is in flight
+        const float* p = Z + m * a.ldz;
+        const f32x4 u = *reinterpret_cast<const f32x4_any*>(p + min(8 * piece, a.K - 4));
+        const f32x4 v = *reinterpret_cast<const f32x4_any*>(p + min(8 * piece + 4, a.K - 4));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) { raw[e] = u[e]; raw[4 + e] = v[e]; }
+    };
+    // columns beyond the last come out zero (a four that begins before the last column and ends beyond was loaded from K - 4)
+    auto trim = [&]() {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const int left = a.K - 8 * piece - 4 * q;                  // columns of this four
+            float w[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                w[e] = left > e ? raw[4 * q + e] : 0.f;
+                if (a.K & 3) {
+#pragma unroll
+                    for (int l = 1; l < 4; ++l)
+                        if (e < l) w[e] = left == l ? raw[4 * q + e + 4 - l] : w[e];
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e) raw[4 * q + e] = w[e];
+        }
+    };
+    auto write = [&](int it) {
+        bf16x8 f[3];
+        split8(raw, f);
+#pragma unroll
+        for (int part = 0; part < 3; ++part) *reinterpret_cast<bf16x8*>(planes + ((it & 1) * 3 + part) * PLANE + at) = f[part];
+    };
+    auto stage = [&](int it) {
+        if (!stages) return;
+        if (a.K != 32 * KT) trim();
+        if (least(raw, 0xFFFFFFFFu) < kLeast) low_tile[it & 3] = 1;
+        write(it);
+    };
+
+    int64_t tile = blockIdx.x;
+    const int64_t step = gridDim.x;
+    if (tile < n_tiles) fetch(tile);
+    bf16x8 wf[KT][2][2], wl[KT > LS ? KT - LS : 1][2];
+    auto weights = [&](auto times_up) {
+        constexpr bool UP = decltype(times_up)::value;
+        uint32_t low = 0xFFFFFFFFu;
+        int col = wcol, q = lq;
+        // the second, rare pass forms its addresses anew and takes one fragment after the other: nothing is kept for it
+        if constexpr (UP) asm volatile("" : "+v"(col), "+v"(q));
+#pragma unroll
+        for (int s = 0; s < KT; ++s)
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int c = min(col + 4 * b, a.N - 1), k0 = 32 * s + 8 * q;        // eight k of one column
+                float x[8];
+                if (TRANS && k0 + 8 <= a.K) {
+                    const f32x4_any* p = reinterpret_cast<const f32x4_any*>(W + (int64_t)c * a.K + k0);
+                    const f32x4 u = p[0], v = p[1];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { x[e] = u[e]; x[4 + e] = v[e]; }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        const int64_t k = min(k0 + e, a.K - 1);
+                        const float v = TRANS ? W[(int64_t)c * a.K + k] : W[k * a.N + c];
+                        x[e] = k0 + e < a.K ? v : 0.f;
+                    }
+                }
+                low = least(x, low);
+                if constexpr (UP) {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) x[e] *= kUp;
+                }
+                bf16x8 f[3];
+                split8(x, f);
+                wf[s][b][0] = f[0];
+                wf[s][b][1] = f[1];
+                if (s < LS) wlds[(2 * s + b) * 512 + tid] = f[2];
+                else wl[s - LS][b] = f[2];
+                if constexpr (UP) __builtin_amdgcn_sched_barrier(0);
+            }
+        if (low < kLeast) *low_w = 1;
+    };
+    weights(std::false_type());
+    if (tile < n_tiles) stage(0);
+    if (tile + step < n_tiles) fetch(tile + step);
+    __syncthreads();
+    const bool scaled_w = __builtin_amdgcn_readfirstlane(*low_w) != 0;
+    if (scaled_w) weights(std::true_type());           // (a lane's pieces in LDS are its own)
+
+    const int ocol = c0 + 8 * lq;                                     // the lane's eight output columns
+    const bool cols = c0 + 32 <= a.N;
+    float kv[MASK ? RB : 1][8];
+    auto mask_rows = [&](int64_t m, int rb) {
+        if constexpr (MASK) {
+            const float* x = reinterpret_cast<const float*>(a.mask) + (m < a.M ? m : a.M - 1) * a.ldmask + ocol;
+            if (cols) {
+                const f32x4 u = *reinterpret_cast<const f32x4_any*>(x), w = *reinterpret_cast<const f32x4_any*>(x + 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { kv[rb][e] = u[e]; kv[rb][4 + e] = w[e]; }
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) kv[rb][e] = ocol + e < a.N ? x[e] : 0.f;
+            }
+        }
+    };
+    // the lane's eight columns of row m
+    auto store = [&](int64_t m, int rb, const f32x4 (&acc)[2]) {
+        if (m >= a.M) return;
+        float y[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) y[e] = a.c_w * acc[e >> 2][e & 3];
+        if (a.bias) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] += cols || ocol + e < a.N ? reinterpret_cast<const float*>(a.bias)[ocol + e] : 0.f;
+        }
+        if (a.relu) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = fmaxf(y[e], 0.f);
+        }
+        if constexpr (MASK) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) y[e] = kv[rb][e] > 0.f ? y[e] : 0.f;
+        }
+        auto put = [&](float* to) {
+            if (cols) {
+                *reinterpret_cast<f32x4_any*>(to) = f32x4{y[0], y[1], y[2], y[3]};
+                *reinterpret_cast<f32x4_any*>(to + 4) = f32x4{y[4], y[5], y[6], y[7]};
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    if (ocol + e < a.N) to[e] = y[e];
+            }
+        };
+        put(reinterpret_cast<float*>(a.Y) + m * a.ldy + ocol);
+        if (a.push_idx) put(reinterpret_cast<float*>(a.push_hist) + (int64_t)a.push_idx[m] * a.ld_push + ocol);
+    };
+    // the wavefront's columns of 16 rows by the fp32 instruction: four k, one of them a lane's
+    auto plain = [&](int64_t m, f32x4 (&acc)[2]) {
+        const float* z = Z + (m < a.M ? m : a.M - 1) * a.ldz;
+#pragma unroll
+        for (int b = 0; b < 2; ++b) acc[b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+        for (int k0 = 0; k0 < a.K; k0 += 4) {
+            const int64_t k = min(k0 + lq, a.K - 1);
+            const bool in = k0 + lq < a.K;
+            const float x = in ? z[k] : 0.f;
+#pragma unroll
+            for (int b = 0; b < 2; ++b) {
+                const int64_t c = min(wcol + 4 * b, a.N - 1);
+                const float w = TRANS ? W[c * a.K + k] : W[k * a.N + c];
+                acc[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(in ? w : 0.f, x, acc[b], 0, 0, 0);
+            }
+        }
+    };
+
+    // the large product between two small ones: its sums do not wait for theirs
+    constexpr int PZ[6] = {1, 0, 0, 1, 2, 0}, PW[6] = {0, 0, 1, 1, 0, 2}, kLarge = 1;
+    const bool early = wave < 4;
+    int it = 0;
+#pragma unroll 1
+    for (; tile < n_tiles; tile += step, ++it) {
+        auto advance = [&]() {
+            if (tile + step < n_tiles) stage(it + 1);
+            if (tile + 2 * step < n_tiles) fetch(tile + 2 * step);
+        };
+        const bool scaled = __builtin_amdgcn_readfirstlane(low_tile[it & 3]) != 0;         // set before the last barrier
+        if (tid == 0) low_tile[(it + 3) & 3] = 0;                                           // the tile before: read by all
+        if (scaled) {                                      // staged again, then what was on its way is fetched again
+            fetch(tile);
+            if (stages) {
+                if (a.K != 32 * KT) trim();
+#pragma unroll
+                for (int e = 0; e < 8; ++e) raw[e] *= kUp;
+                write(it);
+            }
+            if (tile + step < n_tiles) fetch(tile + step);
+            __syncthreads();
+        }
+        if (early) advance();
+        if (c0 < a.N) {
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) mask_rows(tile * ROWS + 16 * rb + li, rb);
+            // piece 4 s + lq of row li (+ 16 rb) lies at piece ^ (row & 7): two addresses and constants
+            const uint16_t* zp[2];
+#pragma unroll
+            for (int h = 0; h < 2; ++h) zp[h] = planes + (it & 1) * 3 * PLANE + li * PITCH + 8 * ((4 * h + lq) ^ (li & 7));
+            f32x4 acc[RB][2], small[RB][2];
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) acc[rb][b] = small[rb][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // Step i = s RB + rb.  The first two parts of its rows are read from LDS one step ahead of its products, the
+            // operands of its last two products (third parts) before its first ones.
+            bf16x8 z[2][2], z2, third[2];
+            auto ahead = [&](int i) {
+                const int s = i / RB, rb = i % RB;
+#pragma unroll
+                for (int part = 0; part < 2; ++part)
+                    z[i & 1][part] = *reinterpret_cast<const bf16x8*>(zp[s & 1] + part * PLANE + 16 * rb * PITCH + 64 * (s >> 1));
+            };
+            ahead(0);
+#pragma unroll
+            for (int i = 0; i < KT * RB; ++i) {
+                const int s = i / RB, rb = i % RB;
+                z2 = *reinterpret_cast<const bf16x8*>(zp[s & 1] + 2 * PLANE + 16 * rb * PITCH + 64 * (s >> 1));
+#pragma unroll
+                for (int b = 0; b < 2; ++b) third[b] = s < LS ? wlds[(2 * s + b) * 512 + tid] : wl[s < LS ? 0 : s - LS][b];
+                if (i + 1 < KT * RB) ahead(i + 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int t = 0; t < 6; ++t)
+#pragma unroll
+                    for (int b = 0; b < 2; ++b) {
+                        f32x4& c = t == kLarge ? acc[rb][b] : small[rb][b];
+                        c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(PW[t] == 2 ? third[b] : wf[s][b][PW[t] & 1],
+                                                                    PZ[t] == 2 ? z2 : z[i & 1][PZ[t] & 1], c, 0, 0, 0);
+                    }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            float bad = 0.f;
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+                for (int b = 0; b < 2; ++b) {
+                    acc[rb][b] += small[rb][b];
+                    if (scaled || scaled_w) {
+                        if (scaled) acc[rb][b] *= 1.f / kUp;
+                        if (scaled_w) acc[rb][b] *= 1.f / kUp;
+                    }
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) bad = fmaf(acc[rb][b][r], 0.f, bad);      // stays 0 for finite values, else NaN
+                }
+            if (__any(bad != 0.f)) {
+#pragma unroll
+                for (int rb = 0; rb < RB; ++rb) plain(tile * ROWS + 16 * rb + li, acc[rb]);
+            }
+#pragma unroll
+            for (int rb = 0; rb < RB; ++rb) store(tile * ROWS + 16 * rb + li, rb, acc[rb]);
+        }
+        if (!early) advance();
+        __syncthreads();
+    }
+}
+
 // fp32 fused MLP: 32 rows per workgroup; wavefront w owns hidden / output
 // columns [64w, 64w+64).  Phase 1 leaves relu(Z W1 + b1) in LDS (fp32), phase 2
 // multiplies it by W2 with the hidden tile as the A operand.
@@ -1426,6 +1742,30 @@ gas_status launch_split(const LinArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
+template <int KT, bool TRANS, bool MASK>
+gas_status launch_ws_split(const LinArgs& a, hipStream_t s) {
+    constexpr int smem = WsSplit<KT, MASK>::kLdsBytes, rows = WsSplit<KT, MASK>::ROWS;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_ws_split_kernel<KT, TRANS, MASK>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    GAS_CHECK_HIP(attr);
+    const int64_t n_tiles = (a.M + rows - 1) / rows;
+    const unsigned blocks = (unsigned)(n_tiles < 256 ? n_tiles : 256);                     // one per compute unit
+    hipLaunchKernelGGL((linear_ws_split_kernel<KT, TRANS, MASK>), dim3(blocks), dim3(512), smem, s, a, n_tiles);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+template <bool TRANS, bool MASK>
+gas_status run_ws_split(const LinArgs& a, hipStream_t s) {
+    switch ((a.K + 31) / 32) {
+        case 3: return launch_ws_split<3, TRANS, MASK>(a, s);
+        case 4: return launch_ws_split<4, TRANS, MASK>(a, s);
+        case 5: return launch_ws_split<5, TRANS, MASK>(a, s);
+        case 6: return launch_ws_split<6, TRANS, MASK>(a, s);
+        case 7: return launch_ws_split<7, TRANS, MASK>(a, s);
+        default: return launch_ws_split<8, TRANS, MASK>(a, s);
+    }
+}
+
 template <int BN>
 gas_status launch_bf16(const LinArgs& a, hipStream_t s) {
     const int64_t gm = (a.M + 127) / 128;
@@ -1494,6 +1834,19 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         // tiles: 27, in 128 x 64 35), 4,000 x 256 x 256 10 us in 64 x 64 tiles.
         const int64_t tiles = (n_rows + 127) / 128, large = tiles * ((F_out + 127) / 128);
         if (F_in <= 16) return launch_split<64, 64, 1, 4>(a, s);
+        // One to two columns of 128 x 128 tiles, in more than one round of the 512 that run at once: the weights stay put instead
+        // (33,000 rows 256 -> 256: 32 us, in tiles 48; 50,000 rows 256 -> 136: 40 and 52, 144 -> 256: 36 and 40, 72 -> 256: 27 and 31;
+        // below, 26,000 rows 256 -> 256: 27 and 27, 16,000: 20 and 18).  The tiles stay where they do no work for padding:
+        // 96 whole columns in less than three rounds (50,000 rows 96 -> 256: 27 and 26; 100,000: 44 and 46), up to 160 in two
+        // full rounds (64,000 rows 160 -> 256: 45 and 41; 100,000: 62 and 67).
+        if (F_in > 64 && F_in <= 256 && F_out > 128 && F_out <= 256 && large > 512 &&
+            c_identity == 0.f && !add && !total && (!mask || trans_w)) {
+            const bool unpadded = F_in % 32 == 0 && F_in <= 160 && F_out > 192;
+            if (!unpadded || (F_in <= 96 ? large > 1536 : large <= 896 || large > 1024)) {
+                if (mask) return run_ws_split<true, true>(a, s);
+                return trans_w ? run_ws_split<true, false>(a, s) : run_ws_split<false, false>(a, s);
+            }
+        }
         if (F_in > 64 || large >= 2048) {
             if (F_out > 64 && large >= 352) return launch_split<128, 128, 2, 2>(a, s);
             if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);

@@ -158,3 +158,68 @@ def test_borders_of_the_tile_rules(what, m, k, n):
     z64, w64 = z.double(), w.double()
     bound = (k + 8) * 2.0 ** -24 * (z64.abs() @ w64.abs())
     assert bool(((out.double() - z64 @ w64).abs() <= bound).all())
+
+
+def _every_option(m, k, n, z, w):
+    """(name, result, oracle, bound) of the transform in each form that keeps its weights in place: bias and ReLU, push, rows with
+    a stride, the input gradient, the input gradient with a mask."""
+    import paper_2106_05609_amd as gas
+    d = "cuda"
+    bias, idx, mask = rng.normal_matrix(11, 762, 1, n)[0].to(d), torch.randperm(m, generator=torch.Generator().manual_seed(3)).int().to(d), rng.normal_matrix(11, 763, m, n).to(d)
+    want, bound = z.double() @ w.double(), (k + 8) * (2.0 ** -24 * (z.double().abs() @ w.double().abs()) + 2.0 ** -149)
+    new = lambda: torch.full((m, n), float("nan"), device=d)
+    y = new()
+    gas.gas_linear(z, w, y)
+    yield "linear", y, want, bound
+    y2, hist = new(), torch.full((m, n + 3), float("nan"), device=d)
+    gas.gas_linear_push(z, w, y2, idx, hist[:, :n], relu=True)
+    yield "push", y2, y.double().clamp(min=0), 0.0
+    yield "history", hist[idx.long(), :n], y2.double(), 0.0
+    assert bool(torch.isnan(hist[:, n:]).all())
+    wide = torch.full((m, n + 5), float("nan"), device=d)
+    strided = torch.zeros(m, k + 3, device=d)
+    strided[:, 1:1 + k] = z
+    gas.gas_linear(strided[:, 1:1 + k], w, wide[:, 2:2 + n], bias=bias, c_weight=0.5)
+    yield "strided", wide[:, 2:2 + n], 0.5 * want + bias.double(), 0.5 * bound + 2.0 ** -23 * (0.5 * want.abs() + bias.double().abs())
+    assert bool(torch.isnan(wide[:, :2]).all()) and bool(torch.isnan(wide[:, 2 + n:]).all())
+    g = new()
+    gas.gas_linear_bwd_input(z, w.t().contiguous(), g)
+    yield "input", g, want, bound
+    g2 = new()
+    gas.gas_linear_bwd_input(z, w.t().contiguous(), g2, mask=mask)
+    yield "masked", g2, torch.where(mask > 0, g, torch.zeros_like(g)).double(), 0.0
+
+
+# weights kept in registers: every count of 32-wide steps, widths that are no whole number of fours or of 32 columns, a last row
+# tile of one row and of all but one, rows on both sides of the rule (512 tiles of 128 x 128)
+@pytest.mark.parametrize("m,k,n", [(32768, 256, 256), (32769, 65, 129), (32800, 97, 131), (33000, 128, 256), (32783, 131, 200),
+                                   (32769, 190, 255), (40001, 223, 160), (33001, 254, 256), (33008, 256, 130), (98400, 96, 256),
+                                   (60000, 160, 256), (65700, 160, 250)])
+def test_weights_in_registers(m, k, n):
+    z, w = rng.normal_matrix(11, 760, m, k).cuda(), rng.normal_matrix(11, 761, k, n).cuda()
+    for name, got, want, bound in _every_option(m, k, n, z, w):
+        assert bool(((got.double() - want).abs() <= bound).all()), name
+
+
+@pytest.mark.parametrize("z_low,w_low,z_bad", [(True, False, None), (False, True, None), (True, True, None), (True, True, 3e38),
+                                               (False, False, float("inf")), (True, False, float("nan"))])
+def test_weights_in_registers_and_values_that_the_split_cannot_hold(z_low, w_low, z_bad):
+    import paper_2106_05609_amd as gas
+    m, k, n = 33001, 101, 140
+    z, w = rng.normal_matrix(11, 764, m, k), rng.normal_matrix(11, 765, k, n)
+    if z_low:
+        z[::40] *= 2.0 ** -118                       # some tiles, none and several of their rows
+        z[7, 3] = 2.0 ** -130
+    if w_low:
+        w[:, 5] *= 2.0 ** -116
+    if z_bad is not None:
+        z[m // 2, 3] = z_bad
+        z[m - 1, k - 1] = -z_bad
+    z, w = z.cuda(), w.cuda()
+    want, size = z.double() @ w.double(), z.double().abs() @ w.double().abs()
+    for trans in (False, True):
+        y = torch.full((m, n), float("nan"), device="cuda")
+        gas.gas_linear_bwd_input(z, w.t().contiguous(), y) if trans else gas.gas_linear(z, w, y)
+        fine = size < 3.4e38                         # the rest: what fp32 arithmetic gives, infinite or not a number
+        assert bool(((y.double() - want).abs() <= (k + 8) * (2.0 ** -24 * size + 2.0 ** -149))[fine].all())
+        assert not bool(torch.isfinite(y)[~torch.isfinite(want)].any())
