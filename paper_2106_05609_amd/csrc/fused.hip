@@ -2,17 +2,16 @@
 // its two sources (fresh in-batch rows, stored halo rows), the dense transform on the aggregated tile while it is
 // still in LDS, and the Push of the result.  A deep narrow model (the 64-layer GCNII of the paper's experiments,
 // width 64) spends its time on launches, not on bytes: its weight matrix is 16 KB and a whole tile of aggregated
-// rows is 8 KB, so both sit in LDS and the layer needs neither the Z round trip through HBM nor a second launch.
+// rows is 8 KB, so the layer needs neither the Z round trip through HBM nor a second launch.
 // Wide layers (256) keep their two kernels: there the weights fill the register file of the transform.
 #include "common.h"
 
 namespace gas {
 namespace {
 
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-constexpr int kRows = 32;            // rows of the batch subgraph per tile = one 32-row MFMA block
+constexpr int kRows = 32;            // rows of the batch subgraph per tile = two 16-row MFMA blocks
 constexpr int kMaxWidth = 128;
+typedef f32x4 f32x4_any __attribute__((aligned(4)));      // a 16-byte access at a float's alignment
 
 struct FusedArgs {
     const int32_t* rowptr; const int32_t* src; const float* val;
@@ -24,202 +23,242 @@ struct FusedArgs {
     float* Y; int64_t ldy;
     float* Zout; int64_t ldzo;       // optional copy of the aggregated rows (a training pass reads them again)
     const int32_t* push_idx; float* PH; int64_t ldp;
-    int K, N, Kp, Np;                // widths, and the widths padded to the MFMA's steps (8 and 32)
-    int g_log2;                      // lanes per row in the aggregation = 1 << g_log2 (>= K / 8)
+    int K, N;                        // widths
     float diag, s_agg, s_res, c_id, c_w;
     int relu;
 };
 
-__device__ __forceinline__ const float* source_row(const FusedArgs& a, int s) {
-    const bool fresh = s >= 0;
-    return (fresh ? a.X : a.H) + (int64_t)(fresh ? s : -1 - s) * (fresh ? a.ldx : a.ldh);
-}
-
 constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile each
+
+// Lane u of every team of G lanes to the whole team, by data-parallel moves (row_newbcast: one lane of each 16; for teams
+// of eight the two halves of a 16 take their own).  u is a constant wherever this is called.
+template <int G>
+__device__ __forceinline__ int team_lane(int v, int u) {
+#define GAS_CASE(n)                                                                                     \
+    case n:                                                                                             \
+        if constexpr (G == 16) return __builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0xf, false);  \
+        else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0x3, false), v, 0x150 + ((n) + 8) % 16, 0xf, 0xc, false);
+    switch (u) {
+        GAS_CASE(0) GAS_CASE(1) GAS_CASE(2) GAS_CASE(3) GAS_CASE(4) GAS_CASE(5) GAS_CASE(6) GAS_CASE(7)
+        GAS_CASE(8) GAS_CASE(9) GAS_CASE(10) GAS_CASE(11) GAS_CASE(12) GAS_CASE(13) GAS_CASE(14) GAS_CASE(15)
+    }
+#undef GAS_CASE
+    return v;
+}
 
 // Workgroups of four wavefronts, looping over tiles of 32 rows.  Per tile:
 //   1. aggregation: wavefront w owns rows 8w .. 8w+7; a team of G lanes owns one row at a time, lane j its
-//      16-byte pieces j and j + G (two loads per gathered row, each contiguous over the team).  The team reads
+//      16-byte pieces j and j + G (P loads per gathered row, each contiguous over the team).  The team reads
 //      2 G source indices (and coefficients) with two loads (the next 2 G are requested before the current ones
-//      are used), gathers the rows eight at a time and folds them in index order; the finished row (scaled, plus
-//      the diagonal and residual terms) goes to the LDS tile Zs.  With width 64 a team is 8 lanes, so a wavefront
-//      works on its 8 rows at once and the whole chain (row pointers, indices, rows) is walked once per tile.
-//   2. transform: wavefront w owns output columns 32w .. 32w+31 (if the layer is that wide): 32x32x2 fp32 MFMAs
-//      over Zs and the weights in LDS, then c_w * acc + c_id * Z + bias, ReLU, and the row is stored to Y and to
-//      its history slot.
-// The weights are staged once per workgroup, after the first row's pointers have been requested.
-// Latency bounds the kernel (64 layers of 21,248 rows, width 64, 14 entries a row: 22 us each, 1.3 TB/s): eight rows
-// in flight instead of four and the history rows of the epilogue requested before the aggregation took the whole pass
-// from 1,442 to 1,404 us at three wavefronts per SIMD.  Each half of a batch is folded only if it has an entry of the
-// row, so the sums are those of batches of four, bit for bit.
-__global__ __launch_bounds__(kThreads, 3) void spmm_linear_f32_kernel(FusedArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int ldz = a.Kp + 4, ldw = a.Np + 4;
-    float* Zs = reinterpret_cast<float*>(smem);                 // [kRows][ldz]
-    float* Ws = Zs + kRows * ldz;                               // [Kp][ldw]
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-
-    const int G = 1 << a.g_log2, T = 64 >> a.g_log2;            // lanes per team, teams per wavefront
-    const int team = lane >> a.g_log2, j = lane & (G - 1);
-    constexpr int U = 8, RW = kRows / (kThreads / 64);          // gathers in flight per lane (two loads each), rows per wavefront
+//      are used); the lane that read an index forms the row's address, the team takes it over by two moves instead of
+//      forming it G times.  The rows are gathered eight at a time and folded in index order; the finished row (scaled,
+//      plus the diagonal and residual terms, requested before the gathers) goes to the LDS tile Zs.  With width 64 a
+//      team is 8 lanes, so a wavefront works on its 8 rows at once and the whole chain (row pointers, indices,
+//      rows) is walked once per tile.
+//   2. transform: the weights are in registers from the start, wavefront w's 16 output columns (of 64; NB times that
+//      for 128) by all k, so the four wavefronts share the products.  16x16x4 fp32 MFMAs, taken transposed: a lane has four
+//      consecutive columns of a row, which get c_w * acc + c_id * Z + bias and ReLU and are stored to Y and to the
+//      row's history slot as 16 bytes.
+// 64 layers of 21,248 rows, width 64, 15 entries a row: 17.7 us each (with the addresses formed by every lane, 32x32x2
+// products by two of the four wavefronts and the weights in LDS 21.9).  Without the gathers 7.6 us, without the transform
+// 13.7: what is left is the gather's chain of two to three batches and the rows that every XCD fetches anew (4.6 TB/s).
+template <int G, int P, int NB>
+__global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kernel(FusedArgs a) {
+    constexpr int KQ = G * P / 4, LDZ = 16 * KQ + 4;                      // steps of 16 k, floats of a row of Zs
+    __shared__ __attribute__((aligned(16))) float Zs[kRows * LDZ];
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lq = lane >> 4;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    constexpr int T = 64 / G, U = 8, RW = kRows / (kThreads / 64);        // teams, gathers in flight per lane (P loads each), rows per wavefront
+    const int team = lane / G, j = lane % G;
     // Workgroups go to the eight XCDs in turn and each XCD has its own L2.  Every XCD gets one contiguous eighth
     // of the tiles: consecutive rows of a batch belong to one cluster of the partition and gather mostly from that
     // cluster's rows, which then stay in that XCD's L2 instead of being fetched into all eight.
     const int64_t per_xcd = (a.n_tiles + 7) / 8;
     const int xcd = blockIdx.x & 7;
     const int64_t tile_end = min(a.n_tiles, (xcd + 1) * per_xcd), tile0 = xcd * per_xcd + (blockIdx.x >> 3);
+    if (tile0 >= tile_end) return;
     // the first row's pointers are requested before the weights, so the two latencies overlap
-    int b_first = 0, e_first = 0;
+    int b_first, e_first;
     {
-        const int64_t m = tile0 * kRows + wave * RW + team;
-        if (tile0 < tile_end && team < RW && m < a.n_rows) { b_first = a.rowptr[m]; e_first = a.rowptr[m + 1]; }
+        const int64_t m = min(tile0 * kRows + wave * RW + team, a.n_rows - 1);
+        b_first = a.rowptr[m];
+        e_first = a.rowptr[m + 1];
     }
-
-    // weights, zero-padded to Kp x Np
-    const int nq = a.Np / 4, n_pieces = a.Kp * nq;
-    for (int idx = tid; idx < n_pieces; idx += kThreads) {
-        const int k = idx / nq, n = 4 * (idx % nq);
-        f32x4 v = {0.f, 0.f, 0.f, 0.f};
-        if (k < a.K && n < a.N) v = *reinterpret_cast<const f32x4*>(a.W + (int64_t)k * a.N + n);
-        *reinterpret_cast<f32x4*>(Ws + k * ldw + n) = v;
-    }
+    // weights of k = 16 g + 4 lq .. + 3 and column 16 (wave + 4 b) + li; zero outside the matrix
+    f32x4 w[NB][KQ];
+#pragma unroll
+    for (int b = 0; b < NB; ++b)
+#pragma unroll
+        for (int g = 0; g < KQ; ++g) {
+            const int n = 16 * (wave + 4 * b) + li, k = 16 * g + 4 * lq;
+            const float* p = a.W + (int64_t)min(k, a.K - 4) * a.N + min(n, a.N - 1);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[b][g][e] = p[(int64_t)e * a.N];
+        }
     // the padding columns of Zs are cleared once (the aggregation never writes them)
-    for (int idx = tid; idx < kRows * (a.Kp - a.K); idx += kThreads)
-        Zs[(idx / (a.Kp - a.K)) * ldz + a.K + idx % (a.Kp - a.K)] = 0.f;
+    const int pad = 16 * KQ - a.K;
+    for (int idx = tid; idx < kRows * pad; idx += kThreads) Zs[(idx / pad) * LDZ + a.K + idx % pad] = 0.f;
 
-    const bool piece0 = 4 * j < a.K, piece1 = 4 * (j + G) < a.K;
-    const int off0 = piece0 ? 4 * j : 0, off1 = piece1 ? 4 * (j + G) : 0;
+    const bool piece0 = 4 * j < a.K, piece1 = P == 2 && 4 * (j + G) < a.K;
+    const int off0 = piece0 ? 16 * j : 0, off1 = piece1 ? 16 * (j + G) : 0;                  // bytes
 
     for (int64_t tile = tile0; tile < tile_end; tile += gridDim.x >> 3) {
         const int64_t m_tile = tile * kRows;
-        // the history row of output row li: requested a whole aggregation before the epilogue stores to it
-        const int my_slot = a.push_idx && m_tile + li < a.n_rows ? a.push_idx[m_tile + li] : 0;
+        // the history rows of output rows li and 16 + li: requested a whole aggregation before the epilogue stores to them
+        int slot[2] = {0, 0};
+        if (a.push_idx) {
+#pragma unroll
+            for (int h = 0; h < 2; ++h) slot[h] = a.push_idx[min(m_tile + 16 * h + li, a.n_rows - 1)];
+        }
         // ---- 1. aggregation
+#pragma unroll 1
         for (int r = wave * RW + team; r < (wave + 1) * RW; r += T) {
-            const int64_t m = m_tile + r;
-            const bool row_on = m < a.n_rows;
+            const bool row_on = m_tile + r < a.n_rows;
+            const int64_t m = row_on ? m_tile + r : a.n_rows - 1;          // a row beyond the last repeats it; nothing stores it
             const bool have = tile == tile0 && r == wave * RW + team;      // requested before the weights
-            const int b = have ? b_first : (row_on ? a.rowptr[m] : 0), e = have ? e_first : (row_on ? a.rowptr[m + 1] : 0);
-            f32x4 acc0 = {0.f, 0.f, 0.f, 0.f}, acc1 = {0.f, 0.f, 0.f, 0.f};
-            auto fetch = [&](int k, int& s0, int& s1, float& v0, float& v1) {
-                const bool on0 = k + j < e, on1 = k + G + j < e;
-                s0 = on0 ? a.src[k + j] : 0;
-                s1 = on1 ? a.src[k + G + j] : 0;
-                v0 = (a.val && on0) ? a.val[k + j] : 1.f;
-                v1 = (a.val && on1) ? a.val[k + G + j] : 1.f;
+            const int b = have ? b_first : a.rowptr[m], e = have ? e_first : a.rowptr[m + 1];
+            f32x4 acc[P], res[P], own[P];
+            auto piece = [&](const float* base, int64_t ld, f32x4 (&v)[P]) {
+                const char* row = reinterpret_cast<const char*>(base + m * ld);
+                v[0] = *reinterpret_cast<const f32x4*>(row + off0);
+                if constexpr (P == 2) v[1] = *reinterpret_cast<const f32x4*>(row + off1);
             };
-            int s0, s1, k0 = b;
-            float v0, v1;
-            fetch(k0, s0, s1, v0, v1);
-            while (k0 < e) {
-                const int cnt = min(2 * G, e - k0);
-                int ns0, ns1;
-                float nv0, nv1;
-                fetch(k0 + 2 * G, ns0, ns1, nv0, nv1);           // the next indices, before these are used
-                for (int q0 = 0; q0 < cnt; q0 += U) {
-                    const bool lo = q0 < G;                       // a batch of U lies in one half (G is a multiple of U)
-                    const int sh = lo ? s0 : s1, qb = lo ? q0 : q0 - G;
-                    const float vh = lo ? v0 : v1;
-                    f32x4 x0[U], x1[U];
-                    float v[U];
-                    // every load is issued, from a valid address: entries past the end re-read the batch's first
-                    // row with coefficient zero, lanes past the width re-read piece 0 and drop the result
+            if (a.R) piece(a.R, a.ldr, res);
+            if (a.diag != 0.f) piece(a.X, a.ldx, own);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) {
-                        const bool on = q0 + u < cnt;
-                        const int s = __shfl(sh, on ? qb + u : qb, G);
-                        v[u] = on ? __shfl(vh, qb + u, G) : 0.f;
-                        const float* row = source_row(a, s);
-                        x0[u] = *reinterpret_cast<const f32x4*>(row + off0);
-                        x1[u] = *reinterpret_cast<const f32x4*>(row + off1);
-                    }
+            for (int p = 0; p < P; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
+            // entries k + j and k + G + j (the row's last one past its end: a valid address, never folded)
+            int s[2];
+            float v[2];
+            auto fetch = [&](int k) {
 #pragma unroll
-                    for (int h = 0; h < U; h += 4) {
-                        if (h > 0 && q0 + h >= cnt) break;        // nothing of these four belongs to the row
+                for (int h = 0; h < 2; ++h) {
+                    const int at = min(k + G * h + j, e - 1);
+                    s[h] = a.src[at];
+                    v[h] = a.val ? a.val[at] : 1.f;
+                }
+            };
+            if (b < e) fetch(b);
+            for (int k0 = b; k0 < e; k0 += 2 * G) {
+                const int cnt = e - k0;
+                int lo[2], hi[2], wt[2];
 #pragma unroll
-                        for (int u = h; u < h + 4; ++u) {
+                for (int h = 0; h < 2; ++h) {
+                    const bool fresh = s[h] >= 0;
+                    const uint64_t p = (uint64_t)(fresh ? a.X : a.H) + (uint64_t)((int64_t)(fresh ? s[h] : -1 - s[h]) * (fresh ? a.ldx : a.ldh)) * 4;
+                    lo[h] = (int)(uint32_t)p;
+                    hi[h] = (int)(uint32_t)(p >> 32);
+                    wt[h] = __float_as_int(v[h]);
+                }
+                fetch(min(k0 + 2 * G, e - 1));                            // the next indices, before these are used
 #pragma unroll
-                            for (int c = 0; c < 4; ++c) {
-                                acc0[c] = fmaf(v[u], x0[u][c], acc0[c]);
-                                acc1[c] = fmaf(v[u], x1[u][c], acc1[c]);
+                for (int h = 0; h < 2; ++h)
+#pragma unroll
+                    for (int q = 0; q < G; q += U) {
+                        if (G * h + q >= cnt) break;
+                        f32x4 x[U][P];
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const char* row = reinterpret_cast<const char*>((uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) |
+                                                                            ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32));
+                            x[u][0] = *reinterpret_cast<const f32x4*>(row + off0);
+                            if constexpr (P == 2) x[u][1] = *reinterpret_cast<const f32x4*>(row + off1);
+                        }
+#pragma unroll
+                        for (int u = 0; u < U; ++u) {
+                            const float f = __int_as_float(team_lane<G>(wt[h], q + u));
+                            if (G * h + q + u < cnt) {
+#pragma unroll
+                                for (int p = 0; p < P; ++p)
+#pragma unroll
+                                    for (int c = 0; c < 4; ++c) acc[p][c] = fmaf(f, x[u][p][c], acc[p][c]);
                             }
                         }
                     }
-                }
-                s0 = ns0; s1 = ns1; v0 = nv0; v1 = nv1; k0 += 2 * G;
             }
-            auto finish = [&](const f32x4& acc, int p) {
-                f32x4 z = {0.f, 0.f, 0.f, 0.f};
-                if (row_on) {
 #pragma unroll
-                    for (int c = 0; c < 4; ++c) z[c] = a.s_agg * acc[c];
-                    if (a.diag != 0.f) {
-                        const f32x4 d = *reinterpret_cast<const f32x4*>(a.X + m * a.ldx + 4 * p);
+            for (int p = 0; p < P; ++p) {
+                if (!(p == 0 ? piece0 : piece1)) continue;
+                f32x4 z;
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) z[c] = fmaf(a.diag, d[c], z[c]);
-                    }
-                    if (a.R) {
-                        const f32x4 d = *reinterpret_cast<const f32x4*>(a.R + m * a.ldr + 4 * p);
+                for (int c = 0; c < 4; ++c) z[c] = a.s_agg * acc[p][c];
+                if (a.diag != 0.f) {
 #pragma unroll
-                        for (int c = 0; c < 4; ++c) z[c] = fmaf(a.s_res, d[c], z[c]);
-                    }
+                    for (int c = 0; c < 4; ++c) z[c] = fmaf(a.diag, own[p][c], z[c]);
                 }
-                *reinterpret_cast<f32x4*>(Zs + r * ldz + 4 * p) = z;
-            };
-            if (piece0) finish(acc0, j);
-            if (piece1) finish(acc1, j + G);
-        }
-        __syncthreads();                 // Zs (and, the first time, Ws) complete
-        if (a.Zout) {                    // the aggregated rows as gas_spmm would have stored them
-            const int kq4 = a.K / 4;
-            for (int idx = tid; idx < kRows * kq4; idx += kThreads) {
-                const int row = idx / kq4, c = 4 * (idx % kq4);
-                if (m_tile + row < a.n_rows)
-                    *reinterpret_cast<f32x4*>(a.Zout + (m_tile + row) * a.ldzo + c) =
-                        *reinterpret_cast<const f32x4*>(Zs + row * ldz + c);
+                if (a.R) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) z[c] = fmaf(a.s_res, res[p][c], z[c]);
+                }
+                const int c0 = 4 * (j + G * p);
+                *reinterpret_cast<f32x4*>(Zs + r * LDZ + c0) = z;
+                if (a.Zout && row_on) *reinterpret_cast<f32x4*>(a.Zout + m * a.ldzo + c0) = z;      // as gas_spmm would have stored it
             }
         }
+        __syncthreads();                 // Zs complete
         // ---- 2. transform of the tile
-        if (32 * wave < a.Np) {
-            f32x16 acc;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-            const int col = 32 * wave + li;
-            for (int kq = 0; kq < a.Kp / 8; kq += 2) {            // two steps of 8 k: operands read before the products
-                f32x4 fa[2];
-                float fb[2][4];
+        for (int b = 0; b < NB; ++b) {
+            const int n = 16 * (wave + 4 * b) + 4 * lq;                    // the lane's four columns
+            if (16 * (wave + 4 * b) >= a.N) break;
+            f32x4 acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int kk = min(kq + h, a.Kp / 8 - 1) * 8 + lh * 4;
-                    fa[h] = *reinterpret_cast<const f32x4*>(Zs + li * ldz + kk);
+            for (int g = 0; g < KQ; ++g) {
+                if (16 * g >= a.K) break;
+                f32x4 z[2], f = w[b][g];
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) fb[h][q] = Ws[(kk + q) * ldw + col];
-                }
+                for (int h = 0; h < 2; ++h) z[h] = *reinterpret_cast<const f32x4*>(Zs + (16 * h + li) * LDZ + 16 * g + 4 * lq);
+                if (16 * g + 16 > a.K && 16 * g + 4 * lq >= a.K) f = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    if (kq + h < a.Kp / 8) {
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[h][q], fb[h][q], acc, 0, 0, 0);
-                    }
-                }
+                    for (int h = 0; h < 2; ++h) acc[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(f[e], z[h][e], acc[h], 0, 0, 0);
             }
-            const float bv = a.bias && col < a.N ? a.bias[col] : 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int row = 8 * (r / 4) + 4 * lh + (r % 4);
-                const int64_t m = m_tile + row;
-                const int slot = __shfl(my_slot, row);            // of every lane, before any leaves
-                if (m >= a.n_rows || col >= a.N) continue;
-                float y = a.c_w * acc[r] + bv;
-                if (a.c_id != 0.f) y = fmaf(a.c_id, Zs[row * ldz + col], y);
-                if (a.relu) y = fmaxf(y, 0.f);
-                a.Y[m * a.ldy + col] = y;
-                if (a.push_idx) a.PH[(int64_t)slot * a.ldp + col] = y;                           // Push in the epilogue
+            for (int h = 0; h < 2; ++h) {
+                const int64_t m = m_tile + 16 * h + li;
+                if (m >= a.n_rows || n >= a.N) continue;
+                f32x4 y;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) y[c] = a.c_w * acc[h][c];
+                if (a.bias) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y[c] += a.bias[n + c];
+                }
+                if (a.c_id != 0.f) {
+                    const f32x4 z = *reinterpret_cast<const f32x4*>(Zs + (16 * h + li) * LDZ + n);
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y[c] = fmaf(a.c_id, z[c], y[c]);
+                }
+                if (a.relu) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) y[c] = fmaxf(y[c], 0.f);
+                }
+                *reinterpret_cast<f32x4_any*>(a.Y + m * a.ldy + n) = y;
+                if (a.push_idx) *reinterpret_cast<f32x4_any*>(a.PH + (int64_t)slot[h] * a.ldp + n) = y;      // Push in the epilogue
             }
         }
         __syncthreads();                 // the next tile's aggregation overwrites Zs
     }
+}
+
+template <int G, int P, int NB>
+gas_status launch_layer(const FusedArgs& a, hipStream_t s) {
+    // Workgroups that a CU holds at once (by registers): one more would wait for a slot and then walk its tiles alone.
+    // 100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us.
+    constexpr int64_t per_cu = G == 8 ? 3 : 2;
+    const int64_t per_xcd = (a.n_tiles + 7) / 8;                                   // a multiple of eight workgroups
+    const unsigned blocks = (unsigned)(8 * (per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu));
+    hipLaunchKernelGGL((spmm_linear_f32_kernel<G, P, NB>), dim3(blocks), dim3(kThreads), 0, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+
+gas_status run_layer(const FusedArgs& a, hipStream_t s) {
+    // lanes per row and 16-byte pieces per lane by the input width, blocks of 16 output columns per wavefront by the output's
+    if (a.K <= 32) return a.N <= 64 ? launch_layer<8, 1, 1>(a, s) : launch_layer<8, 1, 2>(a, s);
+    if (a.K <= 64) return a.N <= 64 ? launch_layer<8, 2, 1>(a, s) : launch_layer<8, 2, 2>(a, s);
+    return a.N <= 64 ? launch_layer<16, 2, 1>(a, s) : launch_layer<16, 2, 2>(a, s);
 }
 
 }  // namespace
@@ -264,24 +303,9 @@ gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const floa
     a.Y = reinterpret_cast<float*>(Y); a.ldy = ldy;
     a.Zout = reinterpret_cast<float*>(Z_out); a.ldzo = ldz_out;
     a.push_idx = push_idx; a.PH = reinterpret_cast<float*>(push_hist); a.ldp = ld_push;
-    a.K = F_in; a.N = F_out; a.Kp = (F_in + 7) & ~7; a.Np = (F_out + 31) & ~31;
-    a.g_log2 = 3;
-    while ((8 << a.g_log2) < F_in) ++a.g_log2;          // 8 or 16 lanes per row, two 16-byte pieces each
+    a.K = F_in; a.N = F_out;
     a.diag = diag; a.s_agg = s_agg; a.s_res = s_res; a.c_id = c_identity; a.c_w = c_weight; a.relu = relu;
-
-    const int smem = 4 * (kRows * (a.Kp + 4) + a.Kp * (a.Np + 4));      // at most 84,480 bytes
-    // Workgroups that a CU holds at once, by registers (three) and LDS: one more would wait for a slot and then walk its
-    // tiles alone.  100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us.
-    const int64_t per_cu = smem <= 32768 ? 3 : (smem <= 65536 ? 2 : 1);
-    const int64_t per_xcd = (a.n_tiles + 7) / 8;                                   // a multiple of eight workgroups
-    const unsigned blocks = (unsigned)(8 * (per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu));
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(spmm_linear_f32_kernel),
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                       4 * (kRows * (kMaxWidth + 4) + kMaxWidth * (kMaxWidth + 4)));
-    GAS_CHECK_HIP(attr);
-    hipLaunchKernelGGL(spmm_linear_f32_kernel, dim3(blocks), dim3(kThreads), smem, (hipStream_t)stream, a);
-    GAS_CHECK_HIP(hipGetLastError());
-    return GAS_OK;
+    return run_layer(a, (hipStream_t)stream);
 }
 
 }  // extern "C"

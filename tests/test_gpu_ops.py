@@ -419,6 +419,44 @@ def test_layer_in_one_launch_matches_the_oracle(gas, graphs_small, name, K, N, v
     assert torch.equal(y2, y3)
 
 
+def _short_rows(m, n_x, n_h, seed):
+    """CSR with rows of 0 .. 40 entries, every count, whose sources are rows of x (n_x) and, below zero, of a table (n_h)."""
+    lens = torch.arange(m) % 41
+    ptr = torch.cat([torch.zeros(1, dtype=torch.long), torch.cumsum(lens, 0)]).int()
+    src = (torch.arange(int(ptr[-1])) * 7919) % (n_x + n_h)
+    src = torch.where(src < n_x, src, n_x - 1 - src).int()
+    return ptr, src, rng.normal(7, seed, 0, int(ptr[-1])).clone()
+
+
+def _aggregate64(ptr, src, val, x, h):
+    """(sum over a row's entries, sum of the terms' magnitudes) in 64 bits; an entry with an infinite source gives an infinity."""
+    rows = torch.repeat_interleave(torch.arange(ptr.numel() - 1), (ptr[1:] - ptr[:-1]).long())
+    terms = val.double()[:, None] * torch.where(src[:, None] >= 0, x.double()[src.clamp(min=0).long()],
+                                                h.double()[(-1 - src).clamp(min=0).long()])
+    zero = torch.zeros(ptr.numel() - 1, x.shape[1], dtype=torch.float64)
+    return zero.index_add(0, rows, terms), zero.index_add(0, rows, terms.abs())
+
+
+# lanes and pieces per row (up to 32, 64, 128 input columns), blocks of 16 output columns, widths that leave some of them idle
+@pytest.mark.parametrize("K,N", [(4, 4), (20, 16), (32, 68), (36, 128), (48, 48), (64, 20), (64, 64), (68, 64), (100, 128), (128, 4)])
+def test_layer_in_one_launch_widths_and_row_lengths(gas, K, N):
+    m, n_x, n_h = 333, 401, 150
+    ptr, src, val = _short_rows(m, n_x, n_h, 790)
+    x, h, w, bias = (rng.normal_matrix(7, 791 + i, *d) for i, d in enumerate([(n_x, K), (n_h, K), (K, N), (1, N)]))
+    x[5, K // 2] = float("inf")               # reaches the rows that list it and no other
+    z, size = _aggregate64(ptr, src, val, x, h)
+    y, zo = torch.full((m, N), float("nan"), device="cuda"), torch.full((m, K), float("nan"), device="cuda")
+    gas.gas_spmm_linear(dev(ptr), dev(src), dev(val), dev(x), dev(w), y, hist=dev(h), bias=dev(bias[0]), z_out=zo)
+    met = ~torch.isfinite(z)
+    assert torch.equal(zo.cpu()[met].double(), z[met])
+    # an entry's product and its addition within 2^-24 of a partial sum each, at most 41 of them; then K more
+    assert bool(((zo.cpu().double() - z).abs() <= 42 * 2.0 ** -24 * size)[~met].all())
+    fine = ~met.any(1)
+    want = z @ w.double() + bias.double()
+    bound = (K + 44) * 2.0 ** -24 * (size @ w.double().abs() + bias.double().abs())
+    assert bool(((y.cpu().double() - want).abs() <= bound)[fine].all())
+
+
 @pytest.mark.parametrize("m,F", [(24576, 64), (24577, 64), (60001, 64), (50001, 32), (30011, 128)])
 def test_layer_in_one_launch_when_workgroups_take_several_tiles(gas, m, F):
     """More tiles than workgroups that fit: the same bits as the rows in calls of their own."""
