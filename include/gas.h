@@ -320,6 +320,23 @@ GAS_API gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, co
                            void* stream);
 
 /*
+ * Its counterpart in the backward pass, one launch per narrow layer: the adjoint of the aggregation and of the layer
+ * below's ReLU (gas_spmm_t_relu), then the input gradient of that layer's transform (gas_linear_bwd_input_add):
+ *     GX[u, :] = (Y[u, :] > 0) * s_agg * sum_k val[k] * G[row[k], :]            u in [0, n_cols), k in column u
+ *     GZ[u, :] = c_identity * GX[u, :] + c_weight * (GX W^T)[u, :]
+ *     total[u, :] += c_total * GZ[u, :]                                          (if total != NULL)
+ * G [>= max(row)+1, F] is the gradient at the aggregated rows of the layer above, Y [n_cols, F] the layer below's output,
+ * W [F_below, F] that layer's weights.  GX is written (the weight gradient reads it).  Needs no plan; rows of any length are handled, long ones are not split.
+ * Restrictions as for gas_spmm_linear: GAS_F32 only; F and F_below multiples of 4, at most 128; G, Y, GX, W and total
+ * 16-byte aligned with row strides that are multiples of 4 elements; no output may alias another matrix.
+ */
+GAS_API gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* row, const float* val, int64_t n_cols,
+                           const void* G, int64_t ldg, gas_dtype dt, int32_t F, float s_agg,
+                           const void* Y, int64_t ldy, void* GX, int64_t ldgx,
+                           const void* W, int32_t F_below, float c_identity, float c_weight,
+                           float c_total, void* total, int64_t ldtotal, void* GZ, int64_t ldgz, void* stream);
+
+/*
  * Backward pass of the transform (chain rule on the operator equations; the
  * paper takes gradients through its layers, Section 2 advantage (1), without
  * spelling them out).  With P = c_identity * Z + c_weight * (Z W) and Y = relu(P):

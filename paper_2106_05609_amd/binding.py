@@ -16,7 +16,7 @@ EXPORTS = [
     "gas_last_error", "gas_version", "gas_validate_indices",
     "gas_pull", "gas_push", "gas_host_table_pointer", "gas_pull_host", "gas_push_host",
     "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
-    "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear",
+    "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear", "gas_spmm_t_relu_linear",
     "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace", "gas_linear_bwd_weight_static",
     "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
     "gas_pna_aggregate", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
@@ -67,6 +67,7 @@ _SIGNATURES = dict(
     gas_linear="pqqipipiffipqp", gas_mlp2="pqqipippipiipqp", gas_linear_push="pqqipipiffipqppqqp",
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
     gas_spmm_linear="pppqpqpqqiiffpqfpipffipqpqppqqp", gas_relu_bwd="pqpqqiipqp", gas_linear_bwd_input="pqqipiiffpqpqp",
+    gas_spmm_t_relu_linear="pppqpqiifpqpqpifffpqpqp",
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
     gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp",
@@ -455,6 +456,24 @@ def gas_spmm_linear(rowptr, src, val, x, w, y, hist=None, diag=0.0, s_agg=1.0, r
         s_agg, rp, ldr, s_res, _ptr(w), w.shape[1], _ptr(bias), c_identity,
         c_weight, int(relu), yp, ldy, zp, ldzo, _ptr(push_idx, torch.int32), pp,
         0 if push_hist is None else push_hist.shape[0], ldp, _stream()))
+
+
+def gas_spmm_t_relu_linear(colptr, row, val, g, y, gx, w, gz, s_agg=1.0, c_identity=0.0, c_weight=1.0, total=None, c_total=0.0):
+    """gx = (y > 0) * s_agg * (adjoint of the aggregation applied to g), gz = c_identity * gx + c_weight * gx @ w.T (w: the
+    weights of the layer below) and total += c_total * gz in one launch."""
+    (n, f), f_below = gx.shape, w.shape[0]
+    a, lda = _mat(g)
+    yp, ldy = _mat(y)
+    xp, ldx = _mat(gx)
+    zp, ldz = _mat(gz)
+    tp, ldt = (0, 0) if total is None else _mat(total)
+    if g.shape[1] != f or y.shape[1] != f or y.shape[0] < n or w.shape[1] != f or gz.shape != (n, f_below) or \
+            colptr.numel() < n + 1 or not (g.dtype == gx.dtype == y.dtype == w.dtype == gz.dtype) or \
+            (total is not None and (total.dtype != g.dtype or total.shape[1] != f_below or total.shape[0] < n)):
+        raise ValueError("gas_spmm_t_relu_linear: shapes or dtypes do not match")
+    _check(_calls().gas_spmm_t_relu_linear(
+        _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32), n, a, lda, _dt(g), f, s_agg, yp, ldy, xp,
+        ldx, _ptr(w), f_below, c_identity, c_weight, c_total, tp, ldt, zp, ldz, _stream()))
 
 
 def gas_mlp2_push(z, w1, w2, y, idx, hist, b1=None, b2=None, relu_out=False):

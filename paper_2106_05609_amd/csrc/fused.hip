@@ -26,6 +26,10 @@ struct FusedArgs {
     int K, N;                        // widths
     float diag, s_agg, s_res, c_id, c_w;
     int relu;
+    // backward pass: aggregated rows are zero where mask <= 0, total += c_total * Y
+    const float* mask; int64_t ldm;
+    float* total; int64_t ldt;
+    float c_total;
 };
 
 constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile each
@@ -62,7 +66,10 @@ __device__ __forceinline__ int team_lane(int v, int u) {
 // 64 layers of 21,248 rows, width 64, 15 entries a row: 17.7 us each (with the addresses formed by every lane, 32x32x2
 // products by two of the four wavefronts and the weights in LDS 21.9).  Without the gathers 7.6 us, without the transform
 // 13.7: what is left is the gather's chain of two to three batches and the rows that every XCD fetches anew (4.6 TB/s).
-template <int G, int P, int NB>
+// BWD: the same on the adjoint (gas_spmm_t_relu_linear): the pattern is the CSC copy, the activations of the layer below mask
+// the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 20 us where the
+// aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
+template <int G, int P, int NB, bool BWD>
 __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kernel(FusedArgs a) {
     constexpr int KQ = G * P / 4, LDZ = 16 * KQ + 4;                      // steps of 16 k, floats of a row of Zs
     __shared__ __attribute__((aligned(16))) float Zs[kRows * LDZ];
@@ -91,9 +98,13 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
 #pragma unroll
         for (int g = 0; g < KQ; ++g) {
             const int n = 16 * (wave + 4 * b) + li, k = 16 * g + 4 * lq;
-            const float* p = a.W + (int64_t)min(k, a.K - 4) * a.N + min(n, a.N - 1);
+            if constexpr (BWD) {
+                w[b][g] = *reinterpret_cast<const f32x4*>(a.W + (int64_t)min(n, a.N - 1) * a.K + min(k, a.K - 4));
+            } else {
+                const float* p = a.W + (int64_t)min(k, a.K - 4) * a.N + min(n, a.N - 1);
 #pragma unroll
-            for (int e = 0; e < 4; ++e) w[b][g][e] = p[(int64_t)e * a.N];
+                for (int e = 0; e < 4; ++e) w[b][g][e] = p[(int64_t)e * a.N];
+            }
         }
     // the padding columns of Zs are cleared once (the aggregation never writes them)
     const int pad = 16 * KQ - a.K;
@@ -106,7 +117,7 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
         const int64_t m_tile = tile * kRows;
         // the history rows of output rows li and 16 + li: requested a whole aggregation before the epilogue stores to them
         int slot[2] = {0, 0};
-        if (a.push_idx) {
+        if (!BWD && a.push_idx) {
 #pragma unroll
             for (int h = 0; h < 2; ++h) slot[h] = a.push_idx[min(m_tile + 16 * h + li, a.n_rows - 1)];
         }
@@ -117,14 +128,15 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
             const int64_t m = row_on ? m_tile + r : a.n_rows - 1;          // a row beyond the last repeats it; nothing stores it
             const bool have = tile == tile0 && r == wave * RW + team;      // requested before the weights
             const int b = have ? b_first : a.rowptr[m], e = have ? e_first : a.rowptr[m + 1];
-            f32x4 acc[P], res[P], own[P];
+            f32x4 acc[P], res[P], own[P], act[P];
             auto piece = [&](const float* base, int64_t ld, f32x4 (&v)[P]) {
                 const char* row = reinterpret_cast<const char*>(base + m * ld);
                 v[0] = *reinterpret_cast<const f32x4*>(row + off0);
                 if constexpr (P == 2) v[1] = *reinterpret_cast<const f32x4*>(row + off1);
             };
-            if (a.R) piece(a.R, a.ldr, res);
-            if (a.diag != 0.f) piece(a.X, a.ldx, own);
+            if (!BWD && a.R) piece(a.R, a.ldr, res);
+            if (!BWD && a.diag != 0.f) piece(a.X, a.ldx, own);
+            if constexpr (BWD) piece(a.mask, a.ldm, act);
 #pragma unroll
             for (int p = 0; p < P; ++p) acc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
             // entries k + j and k + G + j (the row's last one past its end: a valid address, never folded)
@@ -182,17 +194,32 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
                 f32x4 z;
 #pragma unroll
                 for (int c = 0; c < 4; ++c) z[c] = a.s_agg * acc[p][c];
-                if (a.diag != 0.f) {
+                if (!BWD && a.diag != 0.f) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) z[c] = fmaf(a.diag, own[p][c], z[c]);
                 }
-                if (a.R) {
+                if (!BWD && a.R) {
 #pragma unroll
                     for (int c = 0; c < 4; ++c) z[c] = fmaf(a.s_res, res[p][c], z[c]);
+                }
+                if constexpr (BWD) {
+#pragma unroll
+                    for (int c = 0; c < 4; ++c) z[c] = act[p][c] > 0.f ? z[c] : 0.f;
                 }
                 const int c0 = 4 * (j + G * p);
                 *reinterpret_cast<f32x4*>(Zs + r * LDZ + c0) = z;
                 if (a.Zout && row_on) *reinterpret_cast<f32x4*>(a.Zout + m * a.ldzo + c0) = z;      // as gas_spmm would have stored it
+            }
+        }
+        // the total's rows are requested before the wait for the tile
+        f32x4 sum[BWD ? NB : 1][2];
+        if constexpr (BWD) {
+            if (a.total) {
+#pragma unroll
+                for (int b = 0; b < NB; ++b)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        sum[b][h] = *reinterpret_cast<const f32x4*>(a.total + min(m_tile + 16 * h + li, a.n_rows - 1) * a.ldt + min(16 * (wave + 4 * b) + 4 * lq, a.N - 4));
             }
         }
         __syncthreads();                 // Zs complete
@@ -235,30 +262,38 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
                     for (int c = 0; c < 4; ++c) y[c] = fmaxf(y[c], 0.f);
                 }
                 *reinterpret_cast<f32x4_any*>(a.Y + m * a.ldy + n) = y;
-                if (a.push_idx) *reinterpret_cast<f32x4_any*>(a.PH + (int64_t)slot[h] * a.ldp + n) = y;      // Push in the epilogue
+                if constexpr (BWD) {
+                    if (a.total) {
+#pragma unroll
+                        for (int c = 0; c < 4; ++c) sum[b][h][c] += a.c_total * y[c];
+                        *reinterpret_cast<f32x4*>(a.total + m * a.ldt + n) = sum[b][h];
+                    }
+                }
+                if (!BWD && a.push_idx) *reinterpret_cast<f32x4_any*>(a.PH + (int64_t)slot[h] * a.ldp + n) = y;      // Push in the epilogue
             }
         }
         __syncthreads();                 // the next tile's aggregation overwrites Zs
     }
 }
 
-template <int G, int P, int NB>
+template <int G, int P, int NB, bool BWD>
 gas_status launch_layer(const FusedArgs& a, hipStream_t s) {
     // Workgroups that a CU holds at once (by registers): one more would wait for a slot and then walk its tiles alone.
     // 100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us.
     constexpr int64_t per_cu = G == 8 ? 3 : 2;
     const int64_t per_xcd = (a.n_tiles + 7) / 8;                                   // a multiple of eight workgroups
     const unsigned blocks = (unsigned)(8 * (per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu));
-    hipLaunchKernelGGL((spmm_linear_f32_kernel<G, P, NB>), dim3(blocks), dim3(kThreads), 0, s, a);
+    hipLaunchKernelGGL((spmm_linear_f32_kernel<G, P, NB, BWD>), dim3(blocks), dim3(kThreads), 0, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
 
+template <bool BWD>
 gas_status run_layer(const FusedArgs& a, hipStream_t s) {
     // lanes per row and 16-byte pieces per lane by the input width, blocks of 16 output columns per wavefront by the output's
-    if (a.K <= 32) return a.N <= 64 ? launch_layer<8, 1, 1>(a, s) : launch_layer<8, 1, 2>(a, s);
-    if (a.K <= 64) return a.N <= 64 ? launch_layer<8, 2, 1>(a, s) : launch_layer<8, 2, 2>(a, s);
-    return a.N <= 64 ? launch_layer<16, 2, 1>(a, s) : launch_layer<16, 2, 2>(a, s);
+    if (a.K <= 32) return a.N <= 64 ? launch_layer<8, 1, 1, BWD>(a, s) : launch_layer<8, 1, 2, BWD>(a, s);
+    if (a.K <= 64) return a.N <= 64 ? launch_layer<8, 2, 1, BWD>(a, s) : launch_layer<8, 2, 2, BWD>(a, s);
+    return a.N <= 64 ? launch_layer<16, 2, 1, BWD>(a, s) : launch_layer<16, 2, 2, BWD>(a, s);
 }
 
 }  // namespace
@@ -305,7 +340,43 @@ gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const floa
     a.push_idx = push_idx; a.PH = reinterpret_cast<float*>(push_hist); a.ldp = ld_push;
     a.K = F_in; a.N = F_out;
     a.diag = diag; a.s_agg = s_agg; a.s_res = s_res; a.c_id = c_identity; a.c_w = c_weight; a.relu = relu;
-    return run_layer(a, (hipStream_t)stream);
+    return run_layer<false>(a, (hipStream_t)stream);
+}
+
+gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* row, const float* val, int64_t n_cols,
+                                  const void* G, int64_t ldg, gas_dtype dt, int32_t F, float s_agg, const void* Y,
+                                  int64_t ldy, void* GX, int64_t ldgx, const void* W, int32_t F_below, float c_identity,
+                                  float c_weight, float c_total, void* total, int64_t ldtotal, void* GZ, int64_t ldgz,
+                                  void* stream) {
+    const char* who = "gas_spmm_t_relu_linear";
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "%s: fp32 only (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
+    GAS_REQUIRE(n_cols >= 0 && n_cols < 0x7FFFFFFFLL, "%s: n_cols=%lld", who, (long long)n_cols);
+    GAS_REQUIRE(F > 0 && F_below > 0 && F <= kMaxWidth && F_below <= kMaxWidth && F % 4 == 0 && F_below % 4 == 0,
+                "%s: widths %d, %d: multiples of 4 up to %d only", who, F, F_below, kMaxWidth);
+    if (n_cols == 0) return GAS_OK;
+    GAS_REQUIRE(colptr && row && G && Y && GX && W && GZ, "%s: null pointer", who);
+    GAS_REQUIRE(ldg >= F && ldy >= F && ldgx >= F && ldgz >= F_below && (!total || ldtotal >= F_below),
+                "%s: row stride smaller than the width", who);
+    GAS_REQUIRE(c_identity == 0.f || F == F_below, "%s: the identity term needs equal widths", who);
+    GAS_REQUIRE(G != GX && G != GZ && G != total && GX != GZ && GX != total && Y != GX && Y != GZ && Y != total &&
+                    (!total || total != GZ),
+                "%s: an output aliases another matrix", who);
+    GAS_REQUIRE(aligned16(G) && ldg % 4 == 0 && aligned16(Y) && ldy % 4 == 0 && aligned16(GX) && ldgx % 4 == 0 && aligned16(W) &&
+                    (!total || (aligned16(total) && ldtotal % 4 == 0)),
+                "%s: rows must be 16-byte aligned (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
+    FusedArgs a{};
+    a.rowptr = colptr; a.src = row; a.val = val;
+    a.n_rows = n_cols; a.n_tiles = (n_cols + kRows - 1) / kRows;
+    a.X = reinterpret_cast<const float*>(G); a.ldx = ldg;
+    a.mask = reinterpret_cast<const float*>(Y); a.ldm = ldy;
+    a.Zout = reinterpret_cast<float*>(GX); a.ldzo = ldgx;
+    a.W = reinterpret_cast<const float*>(W);
+    a.Y = reinterpret_cast<float*>(GZ); a.ldy = ldgz;
+    a.total = reinterpret_cast<float*>(total); a.ldt = ldtotal; a.c_total = c_total;
+    a.K = F; a.N = F_below;
+    a.s_agg = s_agg; a.c_id = c_identity; a.c_w = c_weight;
+    return run_layer<true>(a, (hipStream_t)stream);
 }
 
 }  // extern "C"

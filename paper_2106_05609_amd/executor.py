@@ -52,7 +52,9 @@ class BatchGraph:
         self._n_id_host = None
         self._plan_t_all, self._max_F = None, max_F
         self.colptr, self.row, self.val_t, self.plan_t = colptr, row, None, None
+        self.max_col = 0             # most in-batch rows that list one in-batch node
         if colptr is not None:
+            self.max_col = int((colptr[1:self.nb + 1] - colptr[:self.nb]).max().item()) if self.nb > 0 else 0
             # backward over the in-batch columns only: histories are constants
             nnz_t = int(colptr[self.nb].item())
             self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], nnz_t, max_F,
@@ -547,14 +549,17 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     grads = {}
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
+    ready = None                              # the gradient at the layer's aggregated rows, if the launch above formed it
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
-        gz = torch.empty_like(z) if l > 1 or model.op != "gcn" else None
+        gz, ready = ready, None
         if model.op == "gcn":
             grads[l - 1] = weight_grad(z, g)
-            if l > 1:                         # below the first layer there is nothing to train
+            if l > 1 and gz is None:          # below the first layer there is nothing to train
+                gz = torch.empty_like(z)
                 B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
         elif model.op == "gin":
+            gz = torch.empty_like(z)
             w1, w2 = model.weights[l - 1]
             dw2 = weight_grad(h, g)
             gh = torch.empty_like(h)
@@ -570,10 +575,12 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             beta = gcnii_beta(l)
             grads[l - 1] = weight_grad(z, g, beta)
             if g_h0 is None:
-                g_h0 = torch.zeros((nv, gz.shape[1]), dtype=dt, device=dev)
-            # the initial residual's share on the way: g_h0 += alpha * gz
-            B.gas_linear_bwd_input_add(g, model.weights[l - 1], gz, c_identity=1.0 - beta, c_weight=beta,
-                                       total=g_h0[:nb], c_total=model.alpha)
+                g_h0 = torch.zeros((nv, z.shape[1]), dtype=dt, device=dev)
+            if gz is None:
+                # the initial residual's share on the way: g_h0 += alpha * gz
+                gz = torch.empty_like(z)
+                B.gas_linear_bwd_input_add(g, model.weights[l - 1], gz, c_identity=1.0 - beta, c_weight=beta,
+                                           total=g_h0[:nb], c_total=model.alpha)
         if l == 1:
             if model.op == "gcnii":
                 gx = torch.empty((nv, gz.shape[1]), dtype=dt, device=dev)
@@ -583,12 +590,20 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         # the adjoint of the aggregation and of the layer below's ReLU in one pass
         gx = torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         y_below = saved[l - 2][2]
-        if model.op == "gin":
+        s_agg = 1.0 - model.alpha if model.op == "gcnii" else 1.0
+        w_below = model.weights[l - 2]
+        if (fused and (model.op == "gcnii" or (model.op == "gcn" and l > 2)) and bg.max_col <= ONE_LAUNCH_MAX_ROW
+                and B.spmm_linear_supported(gz, w_below.shape[0]) and w_below.data_ptr() % 16 == 0):
+            # narrow layers: the layer below's input gradient in the same launch (GCN's first layer has none)
+            beta = gcnii_beta(l - 1) if model.op == "gcnii" else 1.0
+            ready = torch.empty((nb, w_below.shape[0]), dtype=dt, device=dev)
+            B.gas_spmm_t_relu_linear(bg.colptr, bg.row, bg.val_t, gz, y_below, gx, w_below, ready, s_agg=s_agg,
+                                     c_identity=1.0 - beta, c_weight=beta,
+                                     total=None if g_h0 is None else g_h0[:nb], c_total=model.alpha)
+        elif model.op == "gin":
             B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, None, gz, y_below, gx, diag=1.0 + model.gin_eps)
-        elif model.op == "gcn":
-            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, y_below, gx)
         else:
-            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, y_below, gx, s_agg=1.0 - model.alpha)
+            B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, bg.val_t, gz, y_below, gx, s_agg=s_agg)
         g = gx
     if model.op == "gcnii":
         gp = torch.empty_like(g_h0)

@@ -457,6 +457,30 @@ def test_layer_in_one_launch_widths_and_row_lengths(gas, K, N):
     assert bool(((y.cpu().double() - want).abs() <= bound)[fine].all())
 
 
+# the same lanes, pieces and blocks on the adjoint; part of a tile, one short of a tile, several; with and without the identity term
+@pytest.mark.parametrize("m", [2, 31, 333])
+@pytest.mark.parametrize("F,F_below", [(4, 4), (20, 68), (36, 128), (48, 48), (64, 64), (64, 100), (68, 64), (100, 36), (128, 128)])
+def test_backward_layer_in_one_launch(gas, m, F, F_below):
+    ptr, src, val = _short_rows(m, 401, 0, 800)
+    ident = 0.4 if F == F_below else 0.0
+    g, y, w, tot = (rng.normal_matrix(7, 801 + i, *d) for i, d in enumerate([(401, F), (m, F), (F_below, F), (m, F_below)]))
+    g[5, F // 2] = float("inf")
+    z, size = _aggregate64(ptr, src, val, g, g)
+    on = (y > 0).double()
+    z, size = torch.where(on > 0, 0.9 * z, torch.zeros_like(z)), torch.where(on > 0, 0.9 * size, torch.zeros_like(z))
+    gx, gz, total = torch.full((m, F), float("nan"), device="cuda"), torch.full((m, F_below), float("nan"), device="cuda"), dev(tot).clone()
+    gas.gas_spmm_t_relu_linear(dev(ptr), dev(src), dev(val), dev(g), dev(y), gx, dev(w), gz, s_agg=0.9, c_identity=ident,
+                               c_weight=0.7, total=total, c_total=0.1)
+    met = ~torch.isfinite(z)
+    assert torch.equal(gx.cpu()[met].double(), z[met])
+    assert bool(((gx.cpu().double() - z).abs() <= 44 * 2.0 ** -24 * size)[~met].all())
+    fine = ~met.any(1)
+    want = 0.7 * (z @ w.double().t()) + (ident * z if ident else 0.0)
+    bound = (F + 48) * 2.0 ** -24 * (size @ w.double().abs().t() + (size if ident else 0.0))
+    assert bool(((gz.cpu().double() - want).abs() <= bound)[fine].all())
+    assert bool(((total.cpu().double() - (tot.double() + 0.1 * want)).abs() <= bound + 2.0 ** -23 * (tot.double().abs() + want.abs()))[fine].all())
+
+
 @pytest.mark.parametrize("m,F", [(24576, 64), (24577, 64), (60001, 64), (50001, 32), (30011, 128)])
 def test_layer_in_one_launch_when_workgroups_take_several_tiles(gas, m, F):
     """More tiles than workgroups that fit: the same bits as the rows in calls of their own."""
