@@ -17,7 +17,8 @@ EXPORTS = [
     "gas_pull", "gas_push", "gas_host_table_pointer", "gas_pull_host", "gas_push_host",
     "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
     "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear", "gas_spmm_t_relu_linear",
-    "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace", "gas_linear_bwd_weight_static",
+    "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace",
+    "gas_linear_bwd_weight_static", "gas_linear_bwd_weights", "gas_linear_bwd_weights_workspace",
     "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
     "gas_pna_aggregate", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
     "gas_gat_aggregate_bwd_heads", "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
@@ -47,6 +48,7 @@ def lib():
         L.gas_version.restype = C.c_int
         L.gas_plan_destroy.restype = None
         L.gas_linear_bwd_weight_workspace.restype = C.c_int64
+        L.gas_linear_bwd_weights_workspace.restype = C.c_int64
         L.gas_pna_aggregate_bwd_workspace.restype = C.c_int64
         L.gas_gat_aggregate_bwd_workspace.restype = C.c_int64
         L.gas_gat_aggregate_bwd_heads_workspace.restype = C.c_int64
@@ -68,6 +70,7 @@ _SIGNATURES = dict(
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
     gas_spmm_linear="pppqpqpqqiiffpqfpipffipqpqppqqp", gas_relu_bwd="pqpqqiipqp", gas_linear_bwd_input="pqqipiiffpqpqp",
     gas_spmm_t_relu_linear="pppqpqiifpqpqpifffpqpqp",
+    gas_linear_bwd_weights_workspace="ipppi", gas_linear_bwd_weights="ipppppppipppqp",
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
     gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp",
@@ -380,6 +383,29 @@ def gas_linear_bwd_weight(z, gp, dw, workspace, c_weight=1.0):
     _check(_calls().gas_linear_bwd_weight(a, lda, b, ldb, z.shape[0], z.shape[1],
                                        gp.shape[1], _dt(z), c_weight, _ptr(dw),
                                        _ptr(workspace), nbytes, _stream()))
+
+
+def gas_linear_bwd_weights(items):
+    """gas_linear_bwd_weight of every (z, gp, dw, c_weight) of a list, of one dtype; in float32 they share launches.  The
+    workspace is allocated here, once for all."""
+    n = len(items)
+    if n == 0:
+        return
+    dt, dev = items[0][0].dtype, items[0][0].device
+    zs, gs = [_mat(z) for z, _, _, _ in items], [_mat(g) for _, g, _, _ in items]
+    for z, g, dw, _ in items:
+        if z.dtype != dt or g.dtype != dt or dw.dtype != torch.float32 or not dw.is_contiguous() or \
+                z.shape[0] != g.shape[0] or dw.shape != (z.shape[1], g.shape[1]):
+            raise ValueError("gas_linear_bwd_weights: shapes or dtypes do not match")
+    pointers, longs, ints = C.c_void_p * n, C.c_int64 * n, C.c_int32 * n
+    rows = longs(*[z.shape[0] for z, _, _, _ in items])
+    f_in, f_out = ints(*[z.shape[1] for z, _, _, _ in items]), ints(*[g.shape[1] for _, g, _, _ in items])
+    need = _calls().gas_linear_bwd_weights_workspace(n, rows, f_in, f_out, _dt(items[0][0]))
+    ws = torch.empty(max(1, need), dtype=torch.uint8, device=dev)
+    _check(_calls().gas_linear_bwd_weights(
+        n, pointers(*[p for p, _ in zs]), longs(*[ld for _, ld in zs]), pointers(*[p for p, _ in gs]),
+        longs(*[ld for _, ld in gs]), rows, f_in, f_out, _dt(items[0][0]), (C.c_float * n)(*[c for _, _, _, c in items]),
+        pointers(*[dw.data_ptr() for _, _, dw, _ in items]), ws.data_ptr(), need, _stream()))
 
 
 def gas_linear_bwd_weight_static(z, gp, dw, c_weight=1.0):

@@ -20,6 +20,7 @@
 //         regroups it in registers and writes eight 16-byte [n][k] pieces.
 // The accumulator of a 32x32 block keeps, in register r of lane (li, lh),
 // row 8*(r/4) + 4*lh + r%4 and column li.
+#include <algorithm>
 #include <type_traits>
 
 #include "common.h"
@@ -1440,9 +1441,9 @@ constexpr int kDwTile = 128;
 // Rows per slab: a function of the shape alone (the workspace size and the order of the sum follow from it).
 // About four workgroups per compute unit, at most 4096 rows (long slabs amortise the partial tile they write),
 // at least 128: a small batch then still spreads over the chip instead of queueing in a handful of workgroups.
+static int64_t dw_tiles(int K, int N) { return (int64_t)((K + kDwTile - 1) / kDwTile) * ((N + kDwTile - 1) / kDwTile); }
 static int64_t dw_slab_rows(int64_t M, int K, int N) {
-    const int64_t tiles = (int64_t)((K + kDwTile - 1) / kDwTile) * ((N + kDwTile - 1) / kDwTile);
-    int64_t slab = (M * tiles + 1023) / 1024;
+    int64_t slab = (M * dw_tiles(K, N) + 1023) / 1024;
     slab = (slab + 63) / 64 * 64;
     return slab < 128 ? 128 : (slab > 4096 ? 4096 : slab);
 }
@@ -1489,15 +1490,14 @@ struct DwArgs {
 // fp32: both operands split into bf16 parts (split.h), eight consecutive rows of one feature per LDS piece.  The tiles
 // of one slab follow each other on one XCD: they read the same rows.
 constexpr int kDwSplitKS = 2;
-template <int BT, int WPS>
-__global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
+template <int BT>
+__device__ __forceinline__ void dw_split_block(const DwArgs& a, unsigned block, char* smem) {
     using S = SplitGemm<BT, BT, 2, 2, kDwSplitKS, false, false>;
-    extern __shared__ __attribute__((aligned(16))) char smem[];
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const unsigned tn = (a.N + BT - 1) / BT, tiles = (a.K + BT - 1) / BT * tn;
-    const unsigned of_xcd = blockIdx.x / 8, tile = of_xcd % tiles;
-    const int slab = (int)(of_xcd / tiles * 8 + blockIdx.x % 8);
+    const unsigned of_xcd = block / 8, tile = of_xcd % tiles;
+    const int slab = (int)(of_xcd / tiles * 8 + block % 8);
     if (slab >= a.n_slabs) return;                     // the grid is padded to a multiple of eight slabs
     const int k0 = (int)(tile / tn) * BT, n0 = (int)(tile % tn) * BT;
     const int64_t m_begin = (int64_t)slab * a.slab;
@@ -1522,6 +1522,33 @@ __global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
                 if (k < a.K) out[(int64_t)k * a.N + n] = acc[i][j][r];
             }
         }
+}
+template <int BT, int WPS>
+__global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    dw_split_block<BT>(a, blockIdx.x, smem);
+}
+
+// Several weight gradients in one launch: problem i has the workgroups from first[i] on.  A gradient of few rows fills the chip
+// for less time than its two launches take: 16 of 21,248 rows of 64 x 64 take 57 us together and 181 one by one, nine of
+// 4,000 x 256 x 256 67 and 174.
+constexpr int kDwBatch = 16;
+struct DwBatch {
+    DwArgs p[kDwBatch];
+    unsigned first[kDwBatch];
+    int count;
+};
+__device__ __forceinline__ int dw_problem(const DwBatch& b) {
+    int i = 0;
+    while (i + 1 < b.count && blockIdx.x >= b.first[i + 1]) ++i;
+    return i;
+}
+template <int BT, int WPS>
+__global__ __launch_bounds__(256, WPS) void dw_batch_split_kernel(DwBatch b) {
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const int i = dw_problem(b);
+    const DwArgs a = b.p[i];
+    dw_split_block<BT>(a, blockIdx.x - b.first[i], smem);
 }
 
 // bf16: both operands need 8 consecutive rows per lane, so both tiles are transposed on the way into LDS
@@ -1663,10 +1690,9 @@ __global__ __launch_bounds__(256) void dw_bf16_generic_kernel(DwArgs a) {
 // dW = c_w * (sum of the slabs' partial tiles).  A workgroup owns 32 consecutive outputs; eight threads per output
 // each add every eighth slab in slab order, four loads in flight, and the eight sums are added in a fixed order.
 constexpr int kDwReduceOut = 32, kDwReduceWays = 8;
-__global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
-    __shared__ float part[kDwReduceWays][kDwReduceOut];
+__device__ __forceinline__ void dw_reduce_block(const DwArgs& a, unsigned block, float (*part)[kDwReduceOut]) {
     const int o = threadIdx.x % kDwReduceOut, way = threadIdx.x / kDwReduceOut;
-    const int64_t idx = (int64_t)blockIdx.x * kDwReduceOut + o;
+    const int64_t idx = (int64_t)block * kDwReduceOut + o;
     const int64_t per = (int64_t)a.K * a.N;
     float s = 0.f;
     if (idx < per) {
@@ -1687,6 +1713,16 @@ __global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
         for (int w = 1; w < kDwReduceWays; ++w) t += part[w][o];
         a.dW[idx] = a.c_w * t;
     }
+}
+__global__ __launch_bounds__(256) void dw_reduce_kernel(DwArgs a) {
+    __shared__ float part[kDwReduceWays][kDwReduceOut];
+    dw_reduce_block(a, blockIdx.x, part);
+}
+__global__ __launch_bounds__(256) void dw_batch_reduce_kernel(DwBatch b) {
+    __shared__ float part[kDwReduceWays][kDwReduceOut];
+    const int i = dw_problem(b);
+    const DwArgs a = b.p[i];
+    dw_reduce_block(a, blockIdx.x - b.first[i], part);
 }
 
 // ReLU backward, element-wise: GP = GY where Y > 0, else 0
@@ -2016,6 +2052,84 @@ gas_status gas_linear_bwd_weight(const void* Z, int64_t ldz, const void* GP, int
                                  int32_t F_in, int32_t F_out, gas_dtype dt, float c_weight, float* dW,
                                  void* workspace, int64_t workspace_bytes, void* stream) {
     return run_dw(Z, ldz, GP, ldgp, n_rows, F_in, F_out, dt, c_weight, dW, workspace, workspace_bytes, false, stream);
+}
+
+int64_t gas_linear_bwd_weights_workspace(int32_t count, const int64_t* n_rows, const int32_t* F_in, const int32_t* F_out,
+                                         gas_dtype dt) {
+    if (count <= 0 || !n_rows || !F_in || !F_out) return 0;
+    int64_t most = 0, launch = 0;
+    for (int32_t i = 0; i < count; ++i) {              // bf16: a launch for each; fp32: kDwBatch at a time
+        if (dt != GAS_F32 || i % kDwBatch == 0) launch = 0;
+        launch += gas_linear_bwd_weight_workspace(n_rows[i], F_in[i], F_out[i]);
+        most = std::max(most, launch);
+    }
+    return most;
+}
+
+gas_status gas_linear_bwd_weights(int32_t count, const void* const* Z, const int64_t* ldz, const void* const* GP,
+                                  const int64_t* ldgp, const int64_t* n_rows, const int32_t* F_in, const int32_t* F_out,
+                                  gas_dtype dt, const float* c_weight, float* const* dW, void* workspace,
+                                  int64_t workspace_bytes, void* stream) {
+    const char* who = "gas_linear_bwd_weights";
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    GAS_REQUIRE(count >= 0 && (count == 0 || (Z && ldz && GP && ldgp && n_rows && F_in && F_out && c_weight && dW)),
+                "%s: count=%d or a null array", who, count);
+    for (int32_t i = 0; i < count; ++i) {
+        GAS_REQUIRE(n_rows[i] >= 0 && F_in[i] > 0 && F_out[i] > 0, "%s: %d: n_rows=%lld widths %d, %d", who, i, (long long)n_rows[i],
+                    F_in[i], F_out[i]);
+        GAS_REQUIRE(dW[i] && (n_rows[i] == 0 || (Z[i] && GP[i])), "%s: %d: null pointer", who, i);
+        GAS_REQUIRE(n_rows[i] == 0 || (ldz[i] >= F_in[i] && ldgp[i] >= F_out[i]), "%s: %d: row stride smaller than the row", who, i);
+    }
+    const int64_t need = gas_linear_bwd_weights_workspace(count, n_rows, F_in, F_out, dt);
+    GAS_REQUIRE(need == 0 || (workspace && workspace_bytes >= need), "%s: workspace of %lld bytes needed, %lld given", who,
+                (long long)need, (long long)workspace_bytes);
+    if (dt != GAS_F32) {
+        for (int32_t i = 0; i < count; ++i) {
+            const gas_status st = gas_linear_bwd_weight(Z[i], ldz[i], GP[i], ldgp[i], n_rows[i], F_in[i], F_out[i], dt, c_weight[i],
+                                                        dW[i], workspace, workspace_bytes, stream);
+            if (st != GAS_OK) return st;
+        }
+        return GAS_OK;
+    }
+    hipStream_t s = (hipStream_t)stream;
+    for (int32_t i0 = 0; i0 < count; i0 += kDwBatch) {
+        const int32_t n = std::min(count - i0, (int32_t)kDwBatch);
+        int64_t at = 0, reduce_blocks = 0, blocks[2] = {0, 0};
+        DwBatch tile[2], all;              // 128 x 128 tiles, 64 x 64 tiles, and all of them for the sums over the slabs
+        tile[0].count = tile[1].count = all.count = 0;
+        for (int32_t i = i0; i < i0 + n; ++i) {
+            DwArgs a;
+            a.Z = static_cast<const char*>(Z[i]); a.ldz = ldz[i];
+            a.G = static_cast<const char*>(GP[i]); a.ldg = ldgp[i];
+            a.M = n_rows[i]; a.K = F_in[i]; a.N = F_out[i]; a.c_w = c_weight[i];
+            a.partial = static_cast<float*>(workspace) + at; a.dW = dW[i];
+            a.slab = (int)dw_slab_rows(n_rows[i], F_in[i], F_out[i]);
+            const int64_t n_slabs = (n_rows[i] + a.slab - 1) / a.slab, per = (int64_t)F_in[i] * F_out[i];
+            GAS_REQUIRE(n_slabs <= 0x7FFFFFFFLL, "%s: too many rows", who);
+            a.n_slabs = (int)n_slabs;
+            at += n_slabs * per;
+            all.p[all.count] = a;
+            all.first[all.count++] = (unsigned)reduce_blocks;
+            reduce_blocks += (per + kDwReduceOut - 1) / kDwReduceOut;
+            if (n_slabs > 0) {
+                const int t = F_in[i] <= 64 && F_out[i] <= 64;
+                tile[t].p[tile[t].count] = a;
+                tile[t].first[tile[t].count++] = (unsigned)blocks[t];
+                blocks[t] += (n_slabs + 7) / 8 * 8 * (t ? 1 : dw_tiles(F_in[i], F_out[i]));
+            }
+            GAS_REQUIRE(blocks[0] <= 0x7FFFFFFFLL && blocks[1] <= 0x7FFFFFFFLL && reduce_blocks <= 0x7FFFFFFFLL,
+                        "%s: too large for one launch", who);
+        }
+        if (blocks[0] > 0)
+            hipLaunchKernelGGL((dw_batch_split_kernel<kDwTile, 2>), dim3((unsigned)blocks[0]), dim3(256),
+                               (SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes), s, tile[0]);
+        if (blocks[1] > 0)
+            hipLaunchKernelGGL((dw_batch_split_kernel<64, 4>), dim3((unsigned)blocks[1]), dim3(256),
+                               (SplitGemm<64, 64, 2, 2, kDwSplitKS, false, false>::kLdsBytes), s, tile[1]);
+        hipLaunchKernelGGL(dw_batch_reduce_kernel, dim3((unsigned)reduce_blocks), dim3(256), 0, s, all);
+        GAS_CHECK_HIP(hipGetLastError());
+    }
+    return GAS_OK;
 }
 
 gas_status gas_linear_bwd_weight_static(const void* Z, int64_t ldz, const void* GP, int64_t ldgp, int64_t n_rows,

@@ -121,6 +121,35 @@ def _mlp_in_two(z, w1, w2) -> bool:
     return not (z.shape[0] <= 8192 and steps <= 3 and w2.shape[1] <= 32)
 
 
+class _WeightGrads:
+    """The weight gradients of a backward pass.  Small ones wait for each other and share launches
+    (gas_linear_bwd_weights): 21,248 rows of 64 x 64, 64 layers, 12 us each alone and 4 together.  A gradient matrix of
+    more than 16 MB fills the chip by itself and is not kept waiting (it would only hold memory); bf16 has kernels
+    of its own."""
+    LARGEST, TOGETHER = 16 << 20, 16
+
+    def __init__(self):
+        self.waiting = []
+
+    def add(self, z, g, dw=None, c=1.0):
+        """dW = c * z^T g, complete after done()."""
+        if dw is None:
+            dw = torch.empty((z.shape[1], g.shape[1]), dtype=torch.float32, device=z.device)
+        if z.dtype == torch.float32 and 4 * g.numel() <= self.LARGEST:
+            self.waiting.append((z, g, dw, c))
+            if len(self.waiting) == self.TOGETHER:
+                self.done()
+            return dw
+        ws = torch.empty(max(1, B.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])),
+                         dtype=torch.uint8, device=z.device)
+        B.gas_linear_bwd_weight(z, g, dw, ws, c_weight=c)
+        return dw
+
+    def done(self):
+        B.gas_linear_bwd_weights(self.waiting)
+        self.waiting = []
+
+
 def _pushes(do_push, table) -> bool:
     """Whether a training pass of GCN, GCNII or PNA lets the transform store its rows to the history table as well: not to
     host memory, which gas_push_host writes with few workgroups.  (The forward passes and GIN push from the transform
@@ -539,13 +568,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             B.gas_pull(histories[l - 1], bg.n_id[nb:], x_next[nb:])
         x = x_next
     # ---- backward
-    def weight_grad(zz, gg, c=1.0):
-        dw = torch.empty((zz.shape[1], gg.shape[1]), dtype=torch.float32, device=dev)
-        ws = torch.empty(max(1, B.gas_linear_bwd_weight_workspace(zz.shape[0], zz.shape[1], gg.shape[1])),
-                         dtype=torch.uint8, device=dev)
-        B.gas_linear_bwd_weight(zz, gg, dw, ws, c_weight=c)
-        return dw
-
+    wg = _WeightGrads()
     grads = {}
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
@@ -554,17 +577,17 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
         if model.op == "gcn":
-            grads[l - 1] = weight_grad(z, g)
+            grads[l - 1] = wg.add(z, g)
             if l > 1 and gz is None:          # below the first layer there is nothing to train
                 gz = torch.empty_like(z)
                 B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
         elif model.op == "gin":
             gz = torch.empty_like(z)
             w1, w2 = model.weights[l - 1]
-            dw2 = weight_grad(h, g)
+            dw2 = wg.add(h, g)
             gh = torch.empty_like(h)
             B.gas_linear_bwd_input(g, w2, gh, mask=h)
-            grads[l - 1] = (weight_grad(z, gh), dw2)
+            grads[l - 1] = (wg.add(z, gh), dw2)
             B.gas_linear_bwd_input(gh, w1, gz)
             # gradient of this layer's eps: sum over the in-batch nodes of <dL/dZ_v, h_v> (h = the layer's input)
             if "eps" not in grads:
@@ -573,7 +596,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             B.gas_row_dot(gz, x_in[:nb], torch.empty(nb, dtype=torch.float32, device=dev), grads["eps"][l - 1:l])
         else:
             beta = gcnii_beta(l)
-            grads[l - 1] = weight_grad(z, g, beta)
+            grads[l - 1] = wg.add(z, g, c=beta)
             if g_h0 is None:
                 g_h0 = torch.zeros((nv, z.shape[1]), dtype=dt, device=dev)
             if gz is None:
@@ -608,7 +631,8 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     if model.op == "gcnii":
         gp = torch.empty_like(g_h0)
         B.gas_relu_bwd(g_h0, h0, gp)
-        grads["w_in"] = weight_grad(x0, gp)
+        grads["w_in"] = wg.add(x0, gp)
+    wg.done()
     return y, grads, {"x0": x0, "h0": h0, "layers": saved}
 
 
@@ -799,15 +823,6 @@ def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope
     return y
 
 
-def _weight_grad(zz, gg, dw=None):
-    if dw is None:
-        dw = torch.empty((zz.shape[1], gg.shape[1]), dtype=torch.float32, device=zz.device)
-    ws = torch.empty(max(1, B.gas_linear_bwd_weight_workspace(zz.shape[0], zz.shape[1], gg.shape[1])),
-                     dtype=torch.uint8, device=zz.device)
-    B.gas_linear_bwd_weight(zz, gg, dw, ws)
-    return dw
-
-
 def _next_input(y_rows, bg: BatchGraph, history, do_push):
     """Push the in-batch rows (already in rows 0..nb-1 of the next mini-batch tensor) and pull its halo rows."""
     if do_push:
@@ -852,13 +867,13 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
             break
         _next_input(x_next, bg, histories[l - 1], do_push and not pushed)
         x = x_next
-    grads = {}
+    grads, wg = {}, _WeightGrads()
     g = grad_out(y) if callable(grad_out) else grad_out
     for l in range(L, 0, -1):
         w1, w2 = weights[l - 1]
         x, p, cat, _ = kept[l - 1]            # g: the gradient before this layer's activation
         f, f1 = x.shape[1], w1.shape[1]
-        dw2 = _weight_grad(cat, g)
+        dw2 = wg.add(cat, g)
         gcat = torch.empty_like(cat)
         B.gas_linear_bwd_input(g, w2, gcat)
         gp = torch.empty((nv, f1), dtype=dt, device=dev)
@@ -866,8 +881,8 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         B.gas_pna_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, gcat[:, f:], gp, delta, gadd=gq,
                                 plan_t=bg.plan_t_all)
         dw1 = torch.empty((2 * f, f1), dtype=torch.float32, device=dev)
-        _weight_grad(x[:nb], gq, dw1[:f])
-        _weight_grad(x, gp, dw1[f:])
+        wg.add(x[:nb], gq, dw1[:f])
+        wg.add(x, gp, dw1[f:])
         grads[l - 1] = (dw1, dw2)
         if l == 1:
             break
@@ -877,6 +892,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         B.gas_linear_bwd_input_add(gp[:nb], w1[f:], part, add=gcat[:, :f])
         g = torch.empty((nb, f), dtype=dt, device=dev)
         B.gas_linear_bwd_input_add(gq, w1[:f], g, add=part, mask=kept[l - 2][3])
+    wg.done()
     return y, grads, kept
 
 
@@ -908,7 +924,7 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
             break
         _next_input(x_next, bg, histories[l - 1], do_push)
         x = x_next
-    grads = {}
+    grads, wg = {}, _WeightGrads()
     g = grad_out(y) if callable(grad_out) else grad_out
     for l in range(L, 0, -1):
         w, a_dst, a_src = weights[l - 1]
@@ -918,11 +934,12 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         gs = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         B.gas_gat_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, a_dst, a_src, g, gp, gd, gs,
                                 negative_slope, plan_t=bg.plan_t_all, heads=heads)
-        grads[l - 1] = (_weight_grad(x, gp), gd, gs)
+        grads[l - 1] = (wg.add(x, gp), gd, gs)
         if l == 1:
             break
         g = torch.empty((nb, w.shape[0]), dtype=dt, device=dev)
         B.gas_linear_bwd_input(gp[:nb], w, g, mask=kept[l - 2][2])
+    wg.done()
     return y, grads, kept
 
 

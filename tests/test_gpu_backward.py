@@ -161,3 +161,26 @@ def test_training_forward_in_place_gives_the_same_bits(cfg_id, scale):
             assert torch.equal(u, v)
     for u, v in zip(h0, h1):
         assert torch.equal(u, v)
+
+
+# both tiles (64 and 128 wide) and their edges, an empty sum, one row, rows on both sides of a slab, more problems than share a launch
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shapes", [[(0, 5, 7)], [(300, 64, 64)], [(127, 64, 64), (0, 8, 8), (1, 1, 1), (129, 65, 64), (5000, 143, 256)],
+                                    [(1 + 97 * i, 8 * (i % 9) + 8, 8 * (i % 17) + 8) for i in range(35)]])
+def test_weight_gradients_in_shared_launches(gas, dtype, shapes):
+    items, wants = [], []
+    for i, (m, k, n) in enumerate(shapes):
+        z, g = (rng.normal_matrix(12, 820 + 2 * i + j, m, w + 8).to(dtype) for j, w in enumerate((k, n)))
+        c = 0.5 + i % 3
+        items.append((dev(z)[:, :k], dev(g)[:, 8:8 + n], torch.full((k, n), float("nan"), device="cuda"), c))
+        z, g = z[:, :k].double(), g[:, 8:8 + n].double()
+        # fp32: an operand's parts are exact, a product within 2^-24, an addition within 2^-24 of a partial sum
+        wants.append((c * (z.t() @ g), (m + 8) * 2.0 ** -24 * c * (z.abs().t() @ g.abs())))
+    gas.gas_linear_bwd_weights(items)
+    first = [dw.clone() for _, _, dw, _ in items]
+    for (_, _, dw, _), (want, bound) in zip(items, wants):
+        assert bool(((dw.cpu().double() - want).abs() <= bound).all())
+    for (z, g, dw, c), one in zip(items, first):               # the same bits as a call of its own
+        ws = torch.empty(max(1, gas.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])), dtype=torch.uint8, device="cuda")
+        gas.gas_linear_bwd_weight(z, g, dw, ws, c_weight=c)
+        assert torch.equal(one, dw)
