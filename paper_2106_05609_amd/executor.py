@@ -11,6 +11,7 @@ gas_* call.  For layer l of a batch B with halo V_b \\ B:
 The first layer's X is a gas_pull of all of V_b from the feature table (exact
 inputs); GCNII first applies its graph-agnostic input projection to all rows.
 """
+import itertools
 import math
 
 import torch
@@ -119,6 +120,23 @@ def _mlp_in_two(z, w1, w2) -> bool:
         return False
     steps = -(-z.shape[1] // 32) + -(-w1.shape[1] // 32)
     return not (z.shape[0] <= 8192 and steps <= 3 and w2.shape[1] <= 32)
+
+
+def _matrices(rows, widths, dtype, device):
+    """A matrix of `rows` rows for every width.  Four or more of one width in a row share an allocation, each on a 512-byte boundary
+    as if it had its own: a deep narrow model's pass has hundreds of matrices, and its launches are shorter than what
+    allocating and slicing them one by one takes (2 us each)."""
+    if len(widths) < 4:
+        return [torch.empty((rows, width), dtype=dtype, device=device) for width in widths]
+    out, size = [], torch.finfo(dtype).bits // 8
+    for width, run in itertools.groupby(widths):
+        n = len(list(run))
+        if n < 4:
+            out += [torch.empty((rows, width), dtype=dtype, device=device) for _ in range(n)]
+            continue
+        stride = -(-rows * width * size // 512) * (512 // size)
+        out += torch.empty(n * stride, dtype=dtype, device=device).as_strided((n, rows, width), (stride, width, 1)).unbind(0)
+    return out
 
 
 class _WeightGrads:
@@ -498,26 +516,28 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     L = model.n_layers
     saved = []
     y = None
+    ids = bg.n_id[:nb]
+    widths = [model.out_width(l) for l in range(L)]
+    zs = _matrices(nb, [x.shape[1]] + widths[:-1], dt, dev)
+    # whole mini-batch tensors where the halo rows are pulled into them
+    ys = _matrices(nb, widths, dt, dev) if fused else _matrices(nv, widths[:-1], dt, dev) + _matrices(nb, widths[-1:], dt, dev)
+    short_rows = fused and model.op in ("gcn", "gcnii") and bg.max_row <= ONE_LAUNCH_MAX_ROW
     for l in range(1, L + 1):
         last = l == L
-        f_in, f_out = x.shape[1], model.out_width(l - 1)
-        z = torch.empty((nb, f_in), dtype=dt, device=dev)
-        x_next = torch.empty((nb if (last or fused) else nv, f_out), dtype=dt, device=dev)
-        y = x_next[:nb]
+        z, x_next = zs[l - 1], ys[l - 1]
+        y = x_next if fused or last else x_next[:nb]
         h, pushed = None, False
         table = (x_feat if l == 1 else histories[l - 2]) if fused else None
         if fused and model.op == "gcnii" and l == 1:
             table = None                                  # layer 1 gathers the projected features from h0 itself
-        one_launch = (fused and model.op in ("gcn", "gcnii") and B.spmm_linear_supported(x, f_out)
-                      and bg.max_row <= ONE_LAUNCH_MAX_ROW)
-        if one_launch:
+        if short_rows and B.spmm_linear_supported(x, widths[l - 1]):
             # narrow layers: aggregation, transform and Push in one launch; Z is kept for the weight gradient
             push = not last and do_push
             beta = gcnii_beta(l) if model.op == "gcnii" else 1.0
             kw = dict(s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha, c_identity=1.0 - beta,
                       c_weight=beta) if model.op == "gcnii" else {}
             B.gas_spmm_linear(bg.rowptr, bg.col if table is None else bg.src, bg.val, x, model.weights[l - 1], y,
-                              hist=table, relu=not last, z_out=z, push_idx=bg.n_id[:nb] if push else None,
+                              hist=table, relu=not last, z_out=z, push_idx=ids if push else None,
                               push_hist=histories[l - 1] if push else None, **kw)
             saved.append((z, h, y))
             if last:
@@ -531,7 +551,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
                 B.gas_spmm(bg.plan, bg.rowptr, bg.col, bg.val, x, z)
             pushed = not last and _pushes(do_push, histories[l - 1])
             if pushed:
-                B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], relu=True)
+                B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], relu=True)
             else:
                 B.gas_linear(z, model.weights[l - 1], y, relu=not last)
         elif model.op == "gin":
@@ -543,7 +563,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             h = torch.empty((nb, w1.shape[1]), dtype=dt, device=dev)
             # both products in one call, the hidden activation stored for the backward pass, the Push in its epilogue
             push = not last and do_push
-            B.gas_mlp2_keep(z, w1, w2, y, h, idx=bg.n_id[:nb] if push else None,
+            B.gas_mlp2_keep(z, w1, w2, y, h, idx=ids if push else None,
                             hist=histories[l - 1] if push else None, relu_out=not last)
             pushed = push
         else:
@@ -555,7 +575,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             beta = gcnii_beta(l)
             pushed = not last and _pushes(do_push, histories[l - 1])
             if pushed:
-                B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], c_identity=1.0 - beta,
+                B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], c_identity=1.0 - beta,
                                   c_weight=beta, relu=True)
             else:
                 B.gas_linear(z, model.weights[l - 1], y, c_identity=1.0 - beta, c_weight=beta, relu=not last)
@@ -563,7 +583,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         if last:
             break
         if do_push and not pushed:
-            B.gas_push(y, bg.n_id[:nb], histories[l - 1])
+            B.gas_push(y, ids, histories[l - 1])
         if nv > nb and not fused:
             B.gas_pull(histories[l - 1], bg.n_id[nb:], x_next[nb:])
         x = x_next
@@ -573,11 +593,14 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
     ready = None                              # the gradient at the layer's aggregated rows, if the launch above formed it
+    one_width = L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
+    dws = _matrices(widths[0], widths, torch.float32, dev) if one_width else [None] * L
+    gxs, spare, total = [], [], None
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
         if model.op == "gcn":
-            grads[l - 1] = wg.add(z, g)
+            grads[l - 1] = wg.add(z, g, dws[l - 1])
             if l > 1 and gz is None:          # below the first layer there is nothing to train
                 gz = torch.empty_like(z)
                 B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
@@ -596,14 +619,15 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             B.gas_row_dot(gz, x_in[:nb], torch.empty(nb, dtype=torch.float32, device=dev), grads["eps"][l - 1:l])
         else:
             beta = gcnii_beta(l)
-            grads[l - 1] = wg.add(z, g, c=beta)
+            grads[l - 1] = wg.add(z, g, dws[l - 1], beta)
             if g_h0 is None:
                 g_h0 = torch.zeros((nv, z.shape[1]), dtype=dt, device=dev)
+                total = g_h0[:nb]
             if gz is None:
                 # the initial residual's share on the way: g_h0 += alpha * gz
                 gz = torch.empty_like(z)
                 B.gas_linear_bwd_input_add(g, model.weights[l - 1], gz, c_identity=1.0 - beta, c_weight=beta,
-                                           total=g_h0[:nb], c_total=model.alpha)
+                                           total=total, c_total=model.alpha)
         if l == 1:
             if model.op == "gcnii":
                 gx = torch.empty((nv, gz.shape[1]), dtype=dt, device=dev)
@@ -611,18 +635,22 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
                 B.gas_axpy(g_h0, gx, g_h0, 1.0)
             break
         # the adjoint of the aggregation and of the layer below's ReLU in one pass
-        gx = torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         y_below = saved[l - 2][2]
+        if one_width and not gxs:             # as many as wait for their weight gradients together
+            gxs = _matrices(nb, widths[max(0, l - 1 - wg.TOGETHER):l - 1], dt, dev)
+        gx = gxs.pop() if gxs else torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         s_agg = 1.0 - model.alpha if model.op == "gcnii" else 1.0
         w_below = model.weights[l - 2]
         if (fused and (model.op == "gcnii" or (model.op == "gcn" and l > 2)) and bg.max_col <= ONE_LAUNCH_MAX_ROW
                 and B.spmm_linear_supported(gz, w_below.shape[0]) and w_below.data_ptr() % 16 == 0):
             # narrow layers: the layer below's input gradient in the same launch (GCN's first layer has none)
             beta = gcnii_beta(l - 1) if model.op == "gcnii" else 1.0
-            ready = torch.empty((nb, w_below.shape[0]), dtype=dt, device=dev)
+            ready = spare.pop() if spare and spare[-1].shape[1] == w_below.shape[0] else torch.empty(
+                (nb, w_below.shape[0]), dtype=dt, device=dev)
             B.gas_spmm_t_relu_linear(bg.colptr, bg.row, bg.val_t, gz, y_below, gx, w_below, ready, s_agg=s_agg,
                                      c_identity=1.0 - beta, c_weight=beta,
-                                     total=None if g_h0 is None else g_h0[:nb], c_total=model.alpha)
+                                     total=total, c_total=model.alpha)
+            spare.append(gz)                  # read by this launch; the next one may write it
         elif model.op == "gin":
             B.gas_spmm_t_relu(bg.plan_t, bg.colptr, bg.row, None, gz, y_below, gx, diag=1.0 + model.gin_eps)
         else:
