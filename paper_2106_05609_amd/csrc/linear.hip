@@ -271,6 +271,31 @@ __global__ __launch_bounds__(256, WPS) void linear_split_kernel(LinArgs a) {
     store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
+// The same tile by KG groups of four wavefronts that take the steps of 32 k in turn: where there is at most one tile for a
+// compute unit, one wavefront on a SIMD issues a vector instruction every eight cycles, two or more every four to five, and
+// its chains of dependent products and LDS reads leave the unit idle.  The sum over the groups goes through LDS.
+template <int BM, int BN, bool TRANS, int KG>
+__global__ __launch_bounds__(256 * KG) void linear_split_groups_kernel(LinArgs a) {
+    using G = SplitGemm<BM, BN, 2, 2, 2, true, TRANS>;
+    constexpr int TM = G::TM, TN = G::TN;
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    const float* Z = reinterpret_cast<const float*>(a.Z);
+    const float* W = reinterpret_cast<const float*>(a.W);
+    const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave >> 2;
+    const unsigned gn = (a.N + BN - 1) / BN, of_xcd = blockIdx.x / 8;
+    const int64_t m0 = ((int64_t)(of_xcd / gn) * 8 + blockIdx.x % 8) * BM;
+    if (m0 >= a.M) return;                             // the grid is padded to a multiple of eight row tiles
+    const int n0 = (int)(of_xcd % gn) * BN;
+    const int wm0 = ((wave >> 1) & 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    const int64_t ldw = TRANS ? a.K : a.N;
+    G g;
+    f32x16 acc[TM][TN];
+    if (!g.template run_groups<KG>(Z, a.ldz, m0, a.M, W, ldw, n0, a.N, a.K, reinterpret_cast<uint16_t*>(smem), group, wm0, wn0, acc))
+        plain_tile<TM, TN, true, TRANS>(Z, a.ldz, m0 + wm0, a.M, W, ldw, n0 + wn0, a.N, 0, a.K, acc);
+    if (group == 0) store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
+}
+
 // fp32, weights stationary: a matrix of up to 32 KT x 256 stays, split, in the registers of one persistent workgroup of
 // eight wavefronts (32 output columns each), and row tiles stream past it: a row is split once, not once per column tile,
 // and a weight once per workgroup, not once per row tile.
@@ -1778,6 +1803,18 @@ gas_status launch_split(const LinArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
+template <int BM, int BN, int KG, bool TRANS>
+gas_status launch_groups(const LinArgs& a, hipStream_t s) {
+    constexpr int smem = SplitGemm<BM, BN, 2, 2, 2, true, TRANS>::template kGroupsLdsBytes<KG>;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_split_groups_kernel<BM, BN, TRANS, KG>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    GAS_CHECK_HIP(attr);
+    const int64_t gm = ((a.M + BM - 1) / BM + 7) / 8 * 8, gn = (a.N + BN - 1) / BN;
+    hipLaunchKernelGGL((linear_split_groups_kernel<BM, BN, TRANS, KG>), dim3((unsigned)(gm * gn)), dim3(256 * KG), smem, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+
 template <int KT, bool TRANS, bool MASK>
 gas_status launch_ws_split(const LinArgs& a, hipStream_t s) {
     constexpr int smem = WsSplit<KT, MASK>::kLdsBytes, rows = WsSplit<KT, MASK>::ROWS;
@@ -1887,6 +1924,10 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
             if (F_out > 64 && large >= 352) return launch_split<128, 128, 2, 2>(a, s);
             if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);
         }
+        // No more than a tile for a compute unit: its steps go to four groups of wavefronts (500 x 1,024 x 1,024: 29.9 -> 24.5 us,
+        // 2,500 x 850 x 255 28.0 -> 22.5, 4,000 x 256 x 256 9.8 -> 9.0, 96 columns no difference; 316 tiles 11.9 -> 16.4)
+        if (F_in > 64 && (n_rows + 63) / 64 * ((F_out + 63) / 64) <= 256)
+            return trans_w ? launch_groups<64, 64, 4, true>(a, s) : launch_groups<64, 64, 4, false>(a, s);
         return launch_split<64, 64, 2, 4>(a, s);
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;

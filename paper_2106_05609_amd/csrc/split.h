@@ -67,15 +67,15 @@ struct SplitTile {
     int64_t ld;
 
     static __device__ __forceinline__ int row_of(int i) {
-        const int idx = threadIdx.x + T * i;
+        const int idx = threadIdx.x % T + T * i;
         return KC ? idx / kCh : idx % ROWS;
     }
     static __device__ __forceinline__ int piece_of(int i) {
         // q contiguous: neighbouring threads take one row's pieces; else a wavefront has one piece index
-        if constexpr (KC) return (threadIdx.x + T * i) % kCh;
-        else return (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6) * 64 + T * i) / ROWS;
+        if constexpr (KC) return (threadIdx.x % T + T * i) % kCh;
+        else return (__builtin_amdgcn_readfirstlane(threadIdx.x % T >> 6) * 64 + T * i) / ROWS;
     }
-    static __device__ __forceinline__ bool holds(int i) { return kPieces % T == 0 || (int)threadIdx.x + T * i < kPieces; }
+    static __device__ __forceinline__ bool holds(int i) { return kPieces % T == 0 || (int)(threadIdx.x % T) + T * i < kPieces; }
     // where piece `piece` of row `row` lies in a plane
     static __device__ __forceinline__ int at(int row, int piece) {
         return row * kQ + 8 * (KS == 2 ? (piece ^ ((row >> 1) & 3)) : (piece ^ ((row >> 2) & 1)));
@@ -262,6 +262,126 @@ struct SplitGemm {
                     acc[i][j][r] += small[i][j][r];
                     if constexpr (SCALED) acc[i][j][r] *= 1.f / (kUp * kUp);
                 }
+    }
+
+    // The same by KG groups of T threads, each with LDS of its own: group `group` takes every KG-th step, and group 0 ends up with
+    // the sum over the groups, added in their order (the other groups' acc is of no use afterwards).
+    template <bool SCALED, int KG>
+    __device__ __forceinline__ void pass_groups(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
+                                                int64_t b0, int64_t b_end, int64_t q_end, uint16_t* lds, uint32_t* flag, int group,
+                                                int wm0, int wn0, f32x16 (&acc)[TM][TN]) {
+        uint16_t* mine = lds + group * kFlag;
+        ta.init(A, lda, a0, a_end);
+        tb.init(B, ldb, b0, b_end);
+        auto fetch = [&](int64_t q) {
+            if (q + TA::kQ <= q_end) {
+                ta.fetch(q);
+                tb.fetch(q);
+            } else if (q < q_end) {
+                ta.fetch_last(q, q_end);
+                tb.fetch_last(q, q_end);
+            }
+        };
+        int64_t q = (int64_t)group * TA::kQ;
+        fetch(q);
+        f32x16 small[TM][TN];
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] = small[i][j][r] = 0.f;
+        uint32_t low = 0xFFFFFFFFu;
+        const int64_t rounds = (q_end + KG * TA::kQ - 1) / (KG * TA::kQ);       // the same for every group: they share the barriers
+#pragma unroll 1
+        for (int64_t r = 0; r < rounds; ++r, q += KG * TA::kQ) {
+            const bool on = q < q_end;
+            __syncthreads();                     // everyone is done reading the previous step
+            if (on) {
+                if (q + TA::kQ > q_end) {
+                    ta.mask((int)(q_end - q));
+                    tb.mask((int)(q_end - q));
+                }
+                ta.template stage<SCALED>(mine, low);
+                tb.template stage<SCALED>(mine + 3 * TA::kPlane, low);
+            }
+            if (!SCALED && r + 1 == rounds && low < kLeast) *flag = 1;
+            __syncthreads();
+            if (on) {
+                fetch(q + KG * TA::kQ);
+                products(mine, wm0, wn0, acc, small);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] += small[i][j][r];
+        // the groups' sums through LDS: [group - 1][block][thread][16], four floats an access
+        constexpr int kBlocks = TM * TN;
+        static_assert((KG - 1) * kBlocks * T * 16 * 4 <= KG * kFlag * 2, "the sums fit where the operands were");
+        float* sums = reinterpret_cast<float*>(lds);
+        const int t = threadIdx.x % T;
+        __syncthreads();
+        if (group > 0) {
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r)
+                        *reinterpret_cast<f32x4*>(sums + ((((group - 1) * kBlocks + i * TN + j) * 4 + r) * T + t) * 4) =
+                            f32x4{acc[i][j][4 * r], acc[i][j][4 * r + 1], acc[i][j][4 * r + 2], acc[i][j][4 * r + 3]};
+        }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+            for (int g = 1; g < KG; ++g)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) {
+                            const f32x4 v = *reinterpret_cast<const f32x4*>(sums + ((((g - 1) * kBlocks + i * TN + j) * 4 + r) * T + t) * 4);
+#pragma unroll
+                            for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] += v[e];
+                        }
+            if constexpr (SCALED) {
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j)
+#pragma unroll
+                        for (int r = 0; r < 16; ++r) acc[i][j][r] *= 1.f / (kUp * kUp);
+            }
+        }
+    }
+
+    // run() by KG groups; q from 0.  For group 0 as run(), the others take part and return true with nothing in acc.
+    template <int KG>
+    static constexpr int kGroupsLdsBytes = KG * kFlag * 2 + 16;
+    template <int KG>
+    __device__ __forceinline__ bool run_groups(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
+                                               int64_t b0, int64_t b_end, int64_t q_end, uint16_t* lds, int group, int wm0, int wn0,
+                                               f32x16 (&acc)[TM][TN]) {
+        uint32_t* flag = reinterpret_cast<uint32_t*>(lds + KG * kFlag);
+        if (threadIdx.x == 0) *flag = 0;         // before the first barrier of the pass, which sets it between its last two steps'
+        pass_groups<false, KG>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
+        if (__builtin_amdgcn_readfirstlane(*flag)) {
+            __syncthreads();                     // group 0 is done reading the sums
+            pass_groups<true, KG>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
+        }
+        if (group > 0) return true;
+        float bad = 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) bad = fmaf(acc[i][j][r], 0.f, bad);
+        return !__any(bad != 0.f);
     }
 
     // acc = the products; whether they stand (not if a value of the wavefront's blocks is not finite): else plain_tile

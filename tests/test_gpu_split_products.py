@@ -223,3 +223,13 @@ def test_weights_in_registers_and_values_that_the_split_cannot_hold(z_low, w_low
         fine = size < 3.4e38                         # the rest: what fp32 arithmetic gives, infinite or not a number
         assert bool(((y.double() - want).abs() <= (k + 8) * (2.0 ** -24 * size + 2.0 ** -149))[fine].all())
         assert not bool(torch.isfinite(y)[~torch.isfinite(want)].any())
+
+
+# few tiles, steps of 32 k dealt to four groups of wavefronts: fewer steps than groups, one group a step ahead, a last step that
+# is not whole, and both sides of the rule (256 tiles of 64 x 64)
+@pytest.mark.parametrize("what", ["linear", "input"])
+@pytest.mark.parametrize("m,k,n", [(1, 65, 3), (70, 96, 65), (64, 128, 64), (100, 129, 70), (130, 161, 300), (500, 1024, 130), (77, 1433, 63),
+                                   (4096, 70, 256), (4097, 70, 256)])
+def test_steps_in_groups(what, m, k, n):
+    a, b, terms = _operands(what, m, k, n) if what == "linear" else _operands(what, m, n, k)
+    _check_every_element(what, a, b, terms, *((k, n) if what == "linear" else (n, k)))
