@@ -1515,19 +1515,19 @@ struct DwArgs {
 // fp32: both operands split into bf16 parts (split.h), eight consecutive rows of one feature per LDS piece.  The tiles
 // of one slab follow each other on one XCD: they read the same rows.
 constexpr int kDwSplitKS = 2;
-template <int BT>
+template <int BK, int BN>
 __device__ __forceinline__ void dw_split_block(const DwArgs& a, unsigned block, char* smem) {
-    using S = SplitGemm<BT, BT, 2, 2, kDwSplitKS, false, false>;
+    using S = SplitGemm<BK, BN, 2, 2, kDwSplitKS, false, false>;
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const unsigned tn = (a.N + BT - 1) / BT, tiles = (a.K + BT - 1) / BT * tn;
+    const unsigned tn = (a.N + BN - 1) / BN, tiles = (a.K + BK - 1) / BK * tn;
     const unsigned of_xcd = block / 8, tile = of_xcd % tiles;
     const int slab = (int)(of_xcd / tiles * 8 + block % 8);
     if (slab >= a.n_slabs) return;                     // the grid is padded to a multiple of eight slabs
-    const int k0 = (int)(tile / tn) * BT, n0 = (int)(tile % tn) * BT;
+    const int k0 = (int)(tile / tn) * BK, n0 = (int)(tile % tn) * BN;
     const int64_t m_begin = (int64_t)slab * a.slab;
     const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
-    const int wk0 = (wave >> 1) * (BT / 2), wn0 = (wave & 1) * (BT / 2);
+    const int wk0 = (wave >> 1) * (BK / 2), wn0 = (wave & 1) * (BN / 2);
     const float* Z = reinterpret_cast<const float*>(a.Z);
     const float* G = reinterpret_cast<const float*>(a.G);
     S g;
@@ -1548,10 +1548,10 @@ __device__ __forceinline__ void dw_split_block(const DwArgs& a, unsigned block, 
             }
         }
 }
-template <int BT, int WPS>
+template <int BK, int BN, int WPS>
 __global__ __launch_bounds__(256, WPS) void dw_split_kernel(DwArgs a) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    dw_split_block<BT>(a, blockIdx.x, smem);
+    dw_split_block<BK, BN>(a, blockIdx.x, smem);
 }
 
 // Several weight gradients in one launch: problem i has the workgroups from first[i] on.  A gradient of few rows fills the chip
@@ -1568,12 +1568,12 @@ __device__ __forceinline__ int dw_problem(const DwBatch& b) {
     while (i + 1 < b.count && blockIdx.x >= b.first[i + 1]) ++i;
     return i;
 }
-template <int BT, int WPS>
+template <int BK, int BN, int WPS>
 __global__ __launch_bounds__(256, WPS) void dw_batch_split_kernel(DwBatch b) {
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const int i = dw_problem(b);
     const DwArgs a = b.p[i];
-    dw_split_block<BT>(a, blockIdx.x - b.first[i], smem);
+    dw_split_block<BK, BN>(a, blockIdx.x - b.first[i], smem);
 }
 
 // bf16: both operands need 8 consecutive rows per lane, so both tiles are transposed on the way into LDS
@@ -1813,6 +1813,33 @@ gas_status launch_groups(const LinArgs& a, hipStream_t s) {
     hipLaunchKernelGGL((linear_split_groups_kernel<BM, BN, TRANS, KG>), dim3((unsigned)(gm * gn)), dim3(256 * KG), smem, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
+}
+
+// The tile of the fp32 weight gradient: 64 wide where a width fits (21,000 x 64 x 64 in 64 x 64 tiles 8 us, in 128 x 128 15;
+// 98,000 x 256 x 64 in 128 x 64 tiles 44 us, in 128 x 128 61).  Shape 2 * (K <= 64) + (N <= 64).
+int dw_shape(int K, int N) { return 2 * (K <= 64) + (N <= 64); }
+int64_t dw_split_blocks(int shape, int64_t n_slabs, int K, int N) {
+    const int bk = shape & 2 ? 64 : 128, bn = shape & 1 ? 64 : 128;
+    return (n_slabs + 7) / 8 * 8 * ((K + bk - 1) / bk) * ((N + bn - 1) / bn);
+}
+template <int BK, int BN, int WPS>
+void launch_dw_tile(int64_t blocks, const DwArgs* one, const DwBatch* batch, hipStream_t s) {
+    constexpr int smem = SplitGemm<BK, BN, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
+    static_assert(smem <= 65536, "no attribute needed");
+    if (one) hipLaunchKernelGGL((dw_split_kernel<BK, BN, WPS>), dim3((unsigned)blocks), dim3(256), smem, s, *one);
+    else hipLaunchKernelGGL((dw_batch_split_kernel<BK, BN, WPS>), dim3((unsigned)blocks), dim3(256), smem, s, *batch);
+}
+gas_status launch_dw_blocks(int shape, int64_t blocks, const DwArgs* one, const DwBatch* batch, hipStream_t s) {
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_linear_bwd_weight: problem too large for one launch");
+    if (shape == 0) launch_dw_tile<128, 128, 2>(blocks, one, batch, s);
+    else if (shape == 1) launch_dw_tile<128, 64, 3>(blocks, one, batch, s);
+    else if (shape == 2) launch_dw_tile<64, 128, 3>(blocks, one, batch, s);
+    else launch_dw_tile<64, 64, 4>(blocks, one, batch, s);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+gas_status launch_dw_split(int shape, int64_t n_slabs, const DwArgs& a, hipStream_t s) {
+    return launch_dw_blocks(shape, dw_split_blocks(shape, n_slabs, a.K, a.N), &a, nullptr, s);
 }
 
 template <int KT, bool TRANS, bool MASK>
@@ -2058,16 +2085,8 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
     GAS_REQUIRE(tk <= 65535 && tn <= 65535, "gas_linear_bwd_weight: widths too large");
     dim3 grid((unsigned)n_slabs, tk, tn);
     if (dt == GAS_F32) {
-        const int64_t blocks = (n_slabs + 7) / 8 * 8 * tk * tn;
-        GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for one launch");
-        if (F_in <= 64 && F_out <= 64) {             // 21,000 x 64 x 64: 8 us, in a tile of 128 x 128 15 us
-            constexpr int smem = SplitGemm<64, 64, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
-            hipLaunchKernelGGL((dw_split_kernel<64, 4>), dim3((unsigned)blocks), dim3(256), smem, s, a);
-        } else {
-            constexpr int smem = SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes;
-            static_assert(smem <= 65536, "no attribute needed");
-            hipLaunchKernelGGL((dw_split_kernel<kDwTile, 2>), dim3((unsigned)blocks), dim3(256), smem, s, a);
-        }
+        const gas_status st = launch_dw_split(dw_shape(F_in, F_out), n_slabs, a, s);
+        if (st != GAS_OK) return st;
     } else {
         const bool vec = aligned16(Z) && aligned16(GP) && ldz % 8 == 0 && ldgp % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
         if (vec && F_in <= 256 && F_out <= 256 && F_in > 128 && F_out > 128) {
@@ -2135,9 +2154,11 @@ gas_status gas_linear_bwd_weights(int32_t count, const void* const* Z, const int
     hipStream_t s = (hipStream_t)stream;
     for (int32_t i0 = 0; i0 < count; i0 += kDwBatch) {
         const int32_t n = std::min(count - i0, (int32_t)kDwBatch);
-        int64_t at = 0, reduce_blocks = 0, blocks[2] = {0, 0};
-        DwBatch tile[2], all;              // 128 x 128 tiles, 64 x 64 tiles, and all of them for the sums over the slabs
-        tile[0].count = tile[1].count = all.count = 0;
+        int64_t at = 0, reduce_blocks = 0, blocks[4] = {0, 0, 0, 0};
+        DwBatch tile[4], all;              // by the shape of the tiles, and all of them for the sums over the slabs
+        tile[0].count = tile[1].count = tile[2].count = tile[3].count = all.count = 0;
+        bool wide = false;                 // where 128 x 128 tiles are launched anyway, half-filled ones cost less than a launch
+        for (int32_t i = i0; i < i0 + n; ++i) wide = wide || (n_rows[i] > 0 && F_in[i] > 64 && F_out[i] > 64);
         for (int32_t i = i0; i < i0 + n; ++i) {
             DwArgs a;
             a.Z = static_cast<const char*>(Z[i]); a.ldz = ldz[i];
@@ -2153,20 +2174,18 @@ gas_status gas_linear_bwd_weights(int32_t count, const void* const* Z, const int
             all.first[all.count++] = (unsigned)reduce_blocks;
             reduce_blocks += (per + kDwReduceOut - 1) / kDwReduceOut;
             if (n_slabs > 0) {
-                const int t = F_in[i] <= 64 && F_out[i] <= 64;
+                const int own = dw_shape(F_in[i], F_out[i]), t = wide && own != 3 ? 0 : own;
                 tile[t].p[tile[t].count] = a;
                 tile[t].first[tile[t].count++] = (unsigned)blocks[t];
-                blocks[t] += (n_slabs + 7) / 8 * 8 * (t ? 1 : dw_tiles(F_in[i], F_out[i]));
+                blocks[t] += dw_split_blocks(t, n_slabs, F_in[i], F_out[i]);
             }
-            GAS_REQUIRE(blocks[0] <= 0x7FFFFFFFLL && blocks[1] <= 0x7FFFFFFFLL && reduce_blocks <= 0x7FFFFFFFLL,
-                        "%s: too large for one launch", who);
+            GAS_REQUIRE(reduce_blocks <= 0x7FFFFFFFLL, "%s: too large for one launch", who);
         }
-        if (blocks[0] > 0)
-            hipLaunchKernelGGL((dw_batch_split_kernel<kDwTile, 2>), dim3((unsigned)blocks[0]), dim3(256),
-                               (SplitGemm<kDwTile, kDwTile, 2, 2, kDwSplitKS, false, false>::kLdsBytes), s, tile[0]);
-        if (blocks[1] > 0)
-            hipLaunchKernelGGL((dw_batch_split_kernel<64, 4>), dim3((unsigned)blocks[1]), dim3(256),
-                               (SplitGemm<64, 64, 2, 2, kDwSplitKS, false, false>::kLdsBytes), s, tile[1]);
+        for (int t = 0; t < 4; ++t) {
+            if (blocks[t] == 0) continue;
+            const gas_status st = launch_dw_blocks(t, blocks[t], nullptr, &tile[t], s);
+            if (st != GAS_OK) return st;
+        }
         hipLaunchKernelGGL(dw_batch_reduce_kernel, dim3((unsigned)reduce_blocks), dim3(256), 0, s, all);
         GAS_CHECK_HIP(hipGetLastError());
     }
