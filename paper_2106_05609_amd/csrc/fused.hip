@@ -5,6 +5,7 @@
 // rows is 8 KB, so the layer needs neither the Z round trip through HBM nor a second launch.
 // Wide layers (256) keep their two kernels: there the weights fill the register file of the transform.
 #include "common.h"
+#include "wave.h"
 
 namespace gas {
 namespace {
@@ -33,22 +34,6 @@ struct FusedArgs {
 };
 
 constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile each
-
-// Lane u of every team of G lanes to the whole team, by data-parallel moves (row_newbcast: one lane of each 16; for teams
-// of eight the two halves of a 16 take their own).  u is a constant wherever this is called.
-template <int G>
-__device__ __forceinline__ int team_lane(int v, int u) {
-#define GAS_CASE(n)                                                                                     \
-    case n:                                                                                             \
-        if constexpr (G == 16) return __builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0xf, false);  \
-        else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0x3, false), v, 0x150 + ((n) + 8) % 16, 0xf, 0xc, false);
-    switch (u) {
-        GAS_CASE(0) GAS_CASE(1) GAS_CASE(2) GAS_CASE(3) GAS_CASE(4) GAS_CASE(5) GAS_CASE(6) GAS_CASE(7)
-        GAS_CASE(8) GAS_CASE(9) GAS_CASE(10) GAS_CASE(11) GAS_CASE(12) GAS_CASE(13) GAS_CASE(14) GAS_CASE(15)
-    }
-#undef GAS_CASE
-    return v;
-}
 
 // Workgroups of four wavefronts, looping over tiles of 32 rows.  Per tile:
 //   1. aggregation: wavefront w owns rows 8w .. 8w+7; a team of G lanes owns one row at a time, lane j its

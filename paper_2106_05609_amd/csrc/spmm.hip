@@ -20,10 +20,12 @@
 // light rows follow in spmm_rows_kernel.  The chunks are cut and ordered by
 // L2-sized windows of the source rows (plan_host.h states the rules), so that
 // wavefronts running together gather from rows that fit the L2 of every XCD.
+// Batches without hubs whose rows are 512 or 1,024 bytes go by slices (spmm_slices_kernel).
 // The summation order is a
 // function of the plan alone, so results are bit-identical from run to run.
 #include "common.h"
 #include "plan.h"
+#include "wave.h"
 
 #include <algorithm>
 #include <string.h>
@@ -60,6 +62,7 @@ struct SpmmArgs {
     int64_t n_groups;
     int xcd_ranges;       // grouped light rows: one contiguous range of groups per XCD, [xcd_start[x], xcd_start[x+1])
     int64_t xcd_start[9];
+    int slices;           // rows of 512 or 1,024 bytes: 0 whole, 1 or 2 by slices of so many times 256 bytes
 };
 
 template <bool XBF>
@@ -481,6 +484,129 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
+// ---- rows of 512 or 1,024 bytes by slices of 256 or 512 bytes
+// A gathered row is fetched into the L2 of every XCD whose rows list it, and eight copies of a batch's rows do not fit.
+// Here an XCD takes one slice of a range of rows: 1,024-byte rows have four slices of 256 bytes, so a slice's two XCDs take
+// half of the rows each and an L2 holds a quarter of the bytes.  A team of 16 lanes owns one row's slice (P pieces of 16
+// bytes a lane); it reads 32 indices with two loads, the lane that read an index forms the row's address and the team
+// takes it by data-parallel moves.  Four rows of a wavefront walk their chain of dependent loads (row pointers, indices,
+// rows) together.  A row's entries are folded in the stored order: the sums are the wave-per-row kernel's, bit for bit.
+// Bounded by that chain and, with inputs that are not in the caches, by the misses.  us against the wave-per-row kernel on
+// rotating inputs, 256 floats: 50,000 clustered rows of 11 entries 56 (60 with a range of the rows per XCD, 83 without),
+// their adjoint with mask 52 (59, 83); 5,000 rows 9.4 (14); 4,000 rows of 119 27 (32); 160,000 clustered rows of 21 408
+// (473), adjoint 359 (436).  256 bf16: 50,000 rows 28 (37), 4,000 of 119 23 (31).
+// P = 2 (half the wavefronts, twice the bytes a step) is for short rows; with long, less even ones a wavefront waits for its
+// longest (7,500 power-law rows of 46: 45 us by P = 1, 66 by P = 2, wave-per-row 55).  Not kept: slices of 128 bytes (one for
+// each XCD; 49 us with inputs in the Infinity Cache, 77 without: HBM gives up single lines slowly), several rows a team with
+// the next row's indices requested ahead (its last workgroups end late), loads past a row's end not switched off.
+constexpr int kSliceRows = 16;      // rows of a workgroup (four wavefronts of four teams)
+
+template <int P, bool XBF, bool ZBF, bool MASK>
+__global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices) {
+    constexpr int G = 16, E = Unit<XBF>::E, U = P == 2 ? 4 : 8;
+    const int lane = threadIdx.x & 63, j = lane % G;
+    const int xcd = blockIdx.x & 7, parts = 8 / slices;                   // workgroups go to the eight XCDs in turn
+    const int unit = (xcd % slices) * (G * P) + j;                        // with P == 2 the lane's other one is unit + G
+    const int64_t tiles = (a.n_rows + kSliceRows - 1) / kSliceRows, per_part = (tiles + parts - 1) / parts;
+    const int64_t tile = (xcd / slices) * per_part + (blockIdx.x >> 3);
+    if ((int)(blockIdx.x >> 3) >= per_part || tile >= tiles) return;
+    const int64_t row = tile * kSliceRows + (threadIdx.x / G);
+    if (row >= a.n_rows) return;
+    const int b = a.ptr[row], e = a.ptr[row + 1];
+    const int64_t off = (int64_t)unit * 16;
+    // entries k + j and k + G + j (past the row's end its last one: a valid address, never folded)
+    int s[2];
+    float v[2];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int at = min(k + G * h + j, e - 1);
+            s[h] = a.ind[at];
+            v[h] = a.val ? a.val[at] : 1.f;
+        }
+    };
+    if (b < e) fetch(b);
+    auto piece = [&](const char* base, int64_t stride, u32x4 (&t)[P]) {
+#pragma unroll
+        for (int p = 0; p < P; ++p) t[p] = *reinterpret_cast<const u32x4*>(base + row * stride + off + 16 * G * p);
+    };
+    u32x4 own[P], res[P], act[P];
+    const bool use_own = a.diag != 0.f && row < a.n_diag;
+    if (use_own) piece(a.X, a.x_stride, own);
+    if (a.R) piece(a.R, a.r_stride, res);
+    if constexpr (MASK) piece(a.Y, a.y_stride, act);
+    float acc[P][E];
+#pragma unroll
+    for (int p = 0; p < P; ++p)
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[p][i] = 0.f;
+    for (int k0 = b; k0 < e; k0 += 2 * G) {
+        const int cnt = e - k0;
+        int lo[2], hi[2], wt[2];
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const bool fresh = s[h] >= 0;
+            const uint64_t p = (uint64_t)(fresh ? a.X : a.H) + (uint64_t)((int64_t)(fresh ? s[h] : -1 - s[h]) * (fresh ? a.x_stride : a.h_stride));
+            lo[h] = (int)(uint32_t)p;
+            hi[h] = (int)(uint32_t)(p >> 32);
+            wt[h] = __float_as_int(v[h]);
+        }
+        fetch(min(k0 + 2 * G, e - 1));                                    // the next indices, before these are used
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+            for (int q = 0; q < G; q += U) {
+                if (G * h + q >= cnt) break;
+                u32x4 x[U][P];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const char* r = reinterpret_cast<const char*>((uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) |
+                                                                  ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32));
+                    if (G * h + q + u < cnt) {
+#pragma unroll
+                        for (int p = 0; p < P; ++p) x[u][p] = *reinterpret_cast<const u32x4*>(r + off + 16 * G * p);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float f = __int_as_float(team_lane<G>(wt[h], q + u));
+                    if (G * h + q + u < cnt) {
+#pragma unroll
+                        for (int p = 0; p < P; ++p) Unit<XBF>::fma(acc[p], f, x[u][p]);
+                    }
+                }
+            }
+    }
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        float z[E];
+#pragma unroll
+        for (int i = 0; i < E; ++i) z[i] = a.s_agg * acc[p][i];
+        if (use_own) Unit<XBF>::fma(z, a.diag, own[p]);
+        if (a.R) Unit<XBF>::fma(z, a.s_res, res[p]);
+        if constexpr (MASK) {
+#pragma unroll
+            for (int i = 0; i < E; ++i) {
+                const float y = XBF ? (i & 1 ? bf16_hi(act[p][i / 2]) : bf16_lo(act[p][i / 2])) : __uint_as_float(act[p][i % 4]);
+                z[i] = y > 0.f ? z[i] : 0.f;
+            }
+        }
+        char* zp = a.Z + row * a.z_stride + (int64_t)(unit + G * p) * E * (ZBF ? 2 : 4);
+        if constexpr (ZBF) {
+            u32x4 o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = pack_bf16(z[2 * i], z[2 * i + 1]);
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(zp));
+        } else {
+#pragma unroll
+            for (int q = 0; q < E / 4; ++q) {
+                f32x4 o = {z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]};
+                __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(zp + 16 * q));
+            }
+        }
+    }
+}
+
 // Light rows, finished in one go (epilogue and store).  VB > 0: bundled into
 // groups, one wavefront per row (rows of exactly 64 vectors of VB bytes);
 // VB == 0: one wavefront per row, teams of G lanes per neighbour.
@@ -606,6 +732,17 @@ gas_status launch_rows(const SpmmArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
+template <int P, bool XBF, bool ZBF>
+gas_status launch_slices(const SpmmArgs& a, hipStream_t s) {
+    const int slices = a.units / (16 * P);                                // 1, 2 or 4
+    const int64_t tiles = (a.n_rows + kSliceRows - 1) / kSliceRows, parts = 8 / slices;
+    const int64_t blocks = 8 * ((tiles + parts - 1) / parts);
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
+    if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, true>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices);
+    else hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, false>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices);
+    return GAS_OK;
+}
+
 template <bool XBF, bool ZBF>
 gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
     const int u = a.units;
@@ -619,7 +756,9 @@ gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
     }
     gas_status st;
     // rows of exactly 1 KiB, 512 B or 256 B: grouped wave-per-row path
-    if (whole && a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
+    if (whole && a.slices && (u == 64 || u == 32))
+        st = a.slices == 2 ? launch_slices<2, XBF, ZBF>(a, s) : launch_slices<1, XBF, ZBF>(a, s);
+    else if (whole && a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
     else if (whole && a.group && u == 32) st = launch_rows<32, 1, 4, XBF, ZBF, 8>(a, s);
     else if (whole && a.group && u == 16) st = launch_rows<16, 1, 4, XBF, ZBF, 4>(a, s);
     else if (u <= 8) st = launch_rows<8, 1, 2, XBF, ZBF>(a, s);
@@ -682,6 +821,19 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.group = plan->d_group; a.n_groups = plan->n_groups;
     a.xcd_ranges = plan->xcd_ranges;
     for (int x = 0; x < 9; ++x) a.xcd_start[x] = plan->xcd_start[x];
+    // By slices: no row above the threshold, and (us on rotating inputs, whole rows -> slices)
+    // - a clustered pattern while the rows lie in the Infinity Cache: 51 MB 60 -> 56, 164 MB 473 -> 408; 512 MB 228 -> 270;
+    // - other patterns up to 16,384 rows: 5,000 power-law rows of 30 entries 31 -> 27, 7,500 of 46 55 -> 45, 4,000 equal ones of
+    //   119 32 -> 27; more of them are too uneven, a wavefront's teams wait for each other: 31,250 of 13 62 -> 72, 60,000 of 19
+    //   157 -> 188;
+    // - and with few entries a row up to 64 MB: adjoints over 31,250 and 60,000 power-law rows 47 -> 25 and 55 -> 45; over
+    //   312,500 (160 MB, bf16) a training step 3,534 -> 3,592.
+    // Two slices at a time where rows are short and, as a clustered pattern tells, of like lengths: 50,000 rows 62 -> 56 (an
+    // adjoint over 13,750 power-law rows: whole 65, one slice 52, two 75).
+    const int64_t row_bytes = plan->n_rows * a.units * 16;
+    const bool fits = plan->xcd_ranges ? row_bytes <= (int64_t)192 << 20
+                                       : plan->n_rows <= 16384 || (plan->nnz <= 8 * plan->n_rows && row_bytes <= (int64_t)64 << 20);
+    a.slices = plan->n_heavy > 0 || !fits ? 0 : plan->xcd_ranges && plan->nnz <= 16 * plan->n_rows ? 2 : 1;
     const bool whole = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
                        a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
                        (!H || (aligned16(H) && a.h_stride % 16 == 0)) && (!Y || (aligned16(Y) && a.y_stride % 16 == 0));

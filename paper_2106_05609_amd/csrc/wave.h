@@ -180,4 +180,20 @@ inline int gat_heads_together(int32_t F, int32_t heads) {
     return H;
 }
 
+// Lane u of every team of G lanes to the whole team, by data-parallel moves (row_newbcast: one lane of each 16; for teams
+// of eight the two halves of a 16 take their own).  u is a constant wherever this is called.
+template <int G>
+__device__ __forceinline__ int team_lane(int v, int u) {
+#define GAS_CASE(n)                                                                                     \
+    case n:                                                                                             \
+        if constexpr (G == 16) return __builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0xf, false);  \
+        else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0x3, false), v, 0x150 + ((n) + 8) % 16, 0xf, 0xc, false);
+    switch (u) {
+        GAS_CASE(0) GAS_CASE(1) GAS_CASE(2) GAS_CASE(3) GAS_CASE(4) GAS_CASE(5) GAS_CASE(6) GAS_CASE(7)
+        GAS_CASE(8) GAS_CASE(9) GAS_CASE(10) GAS_CASE(11) GAS_CASE(12) GAS_CASE(13) GAS_CASE(14) GAS_CASE(15)
+    }
+#undef GAS_CASE
+    return v;
+}
+
 }  // namespace gas

@@ -55,9 +55,11 @@ class BatchGraph:
         self.colptr, self.row, self.val_t, self.plan_t = colptr, row, None, None
         self.max_col = 0             # most in-batch rows that list one in-batch node
         if colptr is not None:
-            self.max_col = int((colptr[1:self.nb + 1] - colptr[:self.nb]).max().item()) if self.nb > 0 else 0
             # backward over the in-batch columns only: histories are constants
-            nnz_t = int(colptr[self.nb].item())
+            nnz_t = 0
+            if self.nb > 0:
+                longest = (colptr[1:self.nb + 1] - colptr[:self.nb]).max()
+                self.max_col, nnz_t = torch.stack((longest, colptr[self.nb])).tolist()         # one read-back
             self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], nnz_t, max_F,
                                                                      n_rows=self.nb, ind=row, options=plan_options))
             if normalise:

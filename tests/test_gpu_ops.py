@@ -349,6 +349,58 @@ def test_spmm_xcd_ranges_give_the_same_bits(gas, graphs_small, name):
     assert node_rel_err(out[1], want) <= 1e-5
 
 
+@pytest.mark.parametrize("dtype,F,out", [(torch.float32, 256, torch.float32), (torch.float32, 128, torch.float32),
+                                         (torch.bfloat16, 512, torch.bfloat16), (torch.bfloat16, 256, torch.float32)])
+@pytest.mark.parametrize("nb,mean,clustered", [(1, 9, 1), (15, 14, 1), (17, 14, 2), (31, 60, 1), (1000, 12, 1), (1000, 60, 2)])
+def test_spmm_by_slices(gas, nb, mean, clustered, dtype, F, out):
+    """Rows of 512 and 1,024 bytes without a row above the threshold go by slices of 256 bytes (of 512 up to 16
+    entries a row in a clustered pattern): lengths around the batches of 4, 8, 16 and 32 entries and the longest one, both sources, every term of the epilogue, the mask.  One more row, a heavy
+    one, sends the same rows through the wave-per-row kernel: the same bits of the sums."""
+    lengths = np.resize(np.array([9, 0, 1, 4, 8, 33, 15, 16, 17, 0, 32, 31, 5]), nb)
+    if mean > 16:
+        lengths[::10] = 512
+    assert (lengths.mean() > 16) == (mean > 16)
+    ptr = np.concatenate([[0], np.cumsum(lengths), [lengths.sum() + 513]]).astype(np.int32)
+    r = np.random.default_rng(nb)
+    nh = 50
+    col = r.integers(0, nb + 1 + nh, ptr[-1]).astype(np.int32)
+    val = r.normal(size=ptr[-1]).astype(np.float32)
+    x = rng.normal_matrix(11, 395, nb + 1, F, dtype=dtype)
+    hist = rng.normal_matrix(11, 396, nh, F, dtype=dtype)
+    res = rng.normal_matrix(11, 397, nb + 1, F, dtype=dtype)
+    y = rng.normal_matrix(11, 398, nb + 1, F, dtype=dtype)
+    dx, dh, dr, dy = dev(x), dev(hist), dev(res), dev(y)
+    dptr, dval = dev(torch.from_numpy(ptr)), dev(torch.from_numpy(val))
+    src = dev(torch.from_numpy(np.where(col <= nb, col, nb - col)))          # history row h is stored as -1 - h
+    own = dev(torch.from_numpy(np.minimum(col, nb)))                         # one source only
+    xo = np.concatenate([to_np(x), to_np(hist)])
+    got, plain = [], []
+    for n, heavy in ((nb, 0), (nb + 1, 1)):
+        plan = gas.gas_plan_create(dptr[: n + 1], int(ptr[n]), F, n_rows=n, ind=src, options=dict(xcd_ranges=clustered))
+        assert plan.describe()["n_heavy"] == heavy
+        z = torch.full((n, F), float("nan"), dtype=out, device="cuda")
+        gas.gas_spmm_hist(plan, dptr[: n + 1], src, dval, dx, dh, z, diag=1.1, s_agg=0.9, r=dr, s_res=0.1)
+        got.append(to_np(z)[:nb])
+        sums = [z]
+        gas.gas_spmm_hist(plan, dptr[: n + 1], src, dval, dx, dh, z)
+        if out == dtype:
+            z = torch.full((n, F), float("nan"), dtype=out, device="cuda")
+            gas.gas_spmm_t_relu(plan, dptr[: n + 1], own, None, dx, dy[:n], z, diag=1.1)
+            got.append(to_np(z)[:nb])
+            gas.gas_spmm_t_relu(plan, dptr[: n + 1], own, None, dx, dy[:n], z)
+            sums.append(z)
+        plain.append([to_np(t)[:nb] for t in sums])
+    for a, b in zip(*plain):
+        assert np.array_equal(a.view(np.uint8), b.view(np.uint8))
+    tol = 1e-5 if out == torch.float32 else TOL[out]
+    want = oops.spmm(ptr[: nb + 1], col[: ptr[nb]], val[: ptr[nb]], xo, diag=1.1, s_agg=0.9, r=to_np(res), s_res=0.1,
+                     out_dt=oops.F32 if out == torch.float32 else oops.BF16)
+    assert node_rel_err(got[0], want) <= tol
+    if out == dtype:
+        want = oops.spmm(ptr[: nb + 1], np.minimum(col, nb)[: ptr[nb]], None, to_np(x), diag=1.1)
+        assert node_rel_err(got[1], np.where(y[:nb].float().numpy() > 0, want, 0)) <= tol
+
+
 @pytest.mark.parametrize("name,K,N,variant", [("sbm", 64, 64, "gcnii"), ("sbm", 128, 64, "gcn"), ("powerlaw", 100, 36, "gcn"),
                                                ("powerlaw", 128, 128, "gcnii"), ("gin", 8, 4, "gin"), ("sbm", 64, 64, "plain"),
                                                ("gin", 64, 32, "all_terms")])
