@@ -499,8 +499,9 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     is computed in-graph for the halo rows too and its gradient includes them.  GIN's MLP stores its hidden
     activation here (gas_mlp2_keep: the backward pass reads it again).  Returns (Y_L, grads, kept) with
     grads[l] = dW_l (float32; a pair for GIN), grads["w_in"] for GCNII, and kept = the stored activations the
-    backward pass read (x0, h0, per layer (Z, hidden, Y)).  grad_out is dLoss/dY_L [nb, F_L], or a function
-    that returns it given Y_L.  fused: the forward aggregations read their halo rows from the feature table / the
+    backward pass read (x0, h0, per layer (Z, hidden, Y)).  Y_L and every gradient own their memory; kept activations
+    of one width share an allocation (_matrices), so keeping one of them keeps those.  grad_out is dLoss/dY_L
+    [nb, F_L], or a function that returns it given Y_L.  fused: the forward aggregations read their halo rows from the feature table / the
     history tables in place (gas_spmm_hist) and nothing is pulled; same bits.  GCNII's first layer gathers the
     projected features from the mini-batch tensor, its later layers from the histories.  Narrow fp32 layers of
     GCN and GCNII then take one launch each (gas_spmm_linear with Z kept; the row sums are taken in another order,
@@ -522,7 +523,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     widths = [model.out_width(l) for l in range(L)]
     zs = _matrices(nb, [x.shape[1]] + widths[:-1], dt, dev)
     # whole mini-batch tensors where the halo rows are pulled into them
-    ys = _matrices(nb, widths, dt, dev) if fused else _matrices(nv, widths[:-1], dt, dev) + _matrices(nb, widths[-1:], dt, dev)
+    ys = _matrices(nb if fused else nv, widths[:-1], dt, dev) + [torch.empty((nb, widths[-1]), dtype=dt, device=dev)]
     short_rows = fused and model.op in ("gcn", "gcnii") and bg.max_row <= ONE_LAUNCH_MAX_ROW
     for l in range(1, L + 1):
         last = l == L
@@ -596,13 +597,12 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     g_h0 = None
     ready = None                              # the gradient at the layer's aggregated rows, if the launch above formed it
     one_width = L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
-    dws = _matrices(widths[0], widths, torch.float32, dev) if one_width else [None] * L
     gxs, spare, total = [], [], None
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
         if model.op == "gcn":
-            grads[l - 1] = wg.add(z, g, dws[l - 1])
+            grads[l - 1] = wg.add(z, g)
             if l > 1 and gz is None:          # below the first layer there is nothing to train
                 gz = torch.empty_like(z)
                 B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
@@ -621,7 +621,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             B.gas_row_dot(gz, x_in[:nb], torch.empty(nb, dtype=torch.float32, device=dev), grads["eps"][l - 1:l])
         else:
             beta = gcnii_beta(l)
-            grads[l - 1] = wg.add(z, g, dws[l - 1], beta)
+            grads[l - 1] = wg.add(z, g, c=beta)
             if g_h0 is None:
                 g_h0 = torch.zeros((nv, z.shape[1]), dtype=dt, device=dev)
                 total = g_h0[:nb]

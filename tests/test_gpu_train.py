@@ -341,3 +341,18 @@ def test_training_step_with_the_regulariser_matches_oracle(gas, op):
         assert max_rel_err(to_np(a), b) <= 1e-4, max_rel_err(to_np(a), b)
     for a, b in zip(hs_gpu, hs_cpu):
         assert node_rel_err(to_np(a), b) <= 2e-5
+
+
+@pytest.mark.parametrize("fused", [True, False])
+def test_results_of_a_step_own_their_memory(fused):
+    """A caller who keeps the logits or one gradient of a deep model's step keeps that matrix, not the whole pass."""
+    from paper_2106_05609_amd import executor
+    wl = configs.build_workload(configs.config(3, 0.02))
+    gm = _gpu_model(wl)
+    sg = batches.batch_subgraph(wl.graph, wl.batches[0], wl.cfg.self_loops)
+    bg = _gpu_batch(wl, sg, wl.graph.deg.to("cuda"))
+    hs = [h.to("cuda") for h in configs.make_histories(wl.cfg)]
+    labels = torch.zeros(sg.nb, dtype=torch.int32, device="cuda")
+    _, _, y, grads = executor.train_step(gm, bg, wl.x.to("cuda"), hs, labels, 0.01, fused=fused)
+    for t in [y] + list(grads.values()):
+        assert t.untyped_storage().nbytes() == t.numel() * t.element_size(), tuple(t.shape)
