@@ -151,11 +151,14 @@ class _WeightGrads:
     def __init__(self):
         self.waiting = []
 
+    def waits(self, dtype, rows, width) -> bool:
+        return dtype == torch.float32 and 4 * rows * width <= self.LARGEST
+
     def add(self, z, g, dw=None, c=1.0):
         """dW = c * z^T g, complete after done()."""
         if dw is None:
             dw = torch.empty((z.shape[1], g.shape[1]), dtype=torch.float32, device=z.device)
-        if z.dtype == torch.float32 and 4 * g.numel() <= self.LARGEST:
+        if self.waits(z.dtype, *g.shape):
             self.waiting.append((z, g, dw, c))
             if len(self.waiting) == self.TOGETHER:
                 self.done()
@@ -596,7 +599,9 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
     ready = None                              # the gradient at the layer's aggregated rows, if the launch above formed it
-    one_width = L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
+    # gradient matrices of one width that wait for their weight gradients are allocated together
+    pooled = (L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
+              and wg.waits(dt, nb, widths[0]))
     gxs, spare, total = [], [], None
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
@@ -638,7 +643,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             break
         # the adjoint of the aggregation and of the layer below's ReLU in one pass
         y_below = saved[l - 2][2]
-        if one_width and not gxs:             # as many as wait for their weight gradients together
+        if pooled and not gxs:                # as many as wait together
             gxs = _matrices(nb, widths[max(0, l - 1 - wg.TOGETHER):l - 1], dt, dev)
         gx = gxs.pop() if gxs else torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         s_agg = 1.0 - model.alpha if model.op == "gcnii" else 1.0

@@ -356,3 +356,31 @@ def test_results_of_a_step_own_their_memory(fused):
     _, _, y, grads = executor.train_step(gm, bg, wl.x.to("cuda"), hs, labels, 0.01, fused=fused)
     for t in [y] + list(grads.values()):
         assert t.untyped_storage().nbytes() == t.numel() * t.element_size(), tuple(t.shape)
+
+
+# neither waits for its weight gradient: bf16, and fp32 matrices of more than 16 MB
+@pytest.mark.parametrize("dtype,nb", [(torch.bfloat16, 20000), (torch.float32, 66000)])
+def test_gradients_that_do_not_wait_are_not_allocated_together(dtype, nb):
+    """Backward pass of 20 layers of one width: a few gradient matrices at a time, not one for each layer."""
+    import paper_2106_05609_amd as gas
+    from paper_2106_05609_amd import executor
+    F, L = 64, 20
+    i = torch.arange(nb, device="cuda")
+    rowptr = torch.arange(0, 2 * nb + 1, 2, dtype=torch.int32, device="cuda")
+    col, row = ((torch.stack((i, (i + s) % nb), 1).reshape(-1)).int() for s in (1, -1))       # node i lists i and i + 1
+    bg = executor.BatchGraph(nb, i.int(), rowptr, col, torch.full((nb,), 2, dtype=torch.int32, device="cuda"), rowptr, row, max_F=F)
+    ws = [rng.glorot_uniform(13, 900 + l, F, F, dtype=dtype).to("cuda") for l in range(L + 1)]
+    model = executor.Model("gcnii", ws[1:], ws[0], alpha=0.1)
+    x = rng.normal_matrix(13, 930, nb, F, dtype=dtype).to("cuda")
+    hs = [torch.zeros((nb, F), dtype=dtype, device="cuda") for _ in range(L - 1)]
+    executor.train_batch(model, bg, x, hs, torch.zeros_like(x), fused=True)          # plans built on first use
+    before = []
+
+    def grad_out(y):
+        torch.cuda.reset_peak_memory_stats()
+        before.append(torch.cuda.memory_allocated())
+        return torch.ones_like(y)
+    _, grads, _ = executor.train_batch(model, bg, x, hs, grad_out, fused=True)
+    peak = torch.cuda.max_memory_allocated() - before[0]
+    small = gas.gas_linear_bwd_weight_workspace(nb, F, F) + sum(g.numel() * 4 for g in grads.values())
+    assert peak <= 8 * x.numel() * x.element_size() + small, peak / (x.numel() * x.element_size())
