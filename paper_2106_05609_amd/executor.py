@@ -201,8 +201,9 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
     nb = bg.nb
     if model.op == "gcnii":
         return _forward_gcnii_fused(model, bg, x_feat, histories, do_push)
+    ids = bg.n_id[:nb]
     x = torch.empty((nb, x_feat.shape[1]), dtype=dt, device=dev)
-    B.gas_pull(x_feat, bg.n_id[:nb], x)
+    B.gas_pull(x_feat, ids, x)
     L = model.n_layers
     y = None
     for l in range(1, L + 1):
@@ -213,14 +214,14 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
         if model.op == "gcn" and B.spmm_linear_supported(x, y.shape[1]) and bg.max_row <= ONE_LAUNCH_MAX_ROW:
             # narrow layers: aggregation, transform and Push in one launch
             B.gas_spmm_linear(bg.rowptr, bg.src, bg.val, x, model.weights[l - 1], y, hist=table, relu=not last,
-                              push_idx=bg.n_id[:nb] if push else None, push_hist=histories[l - 1] if push else None)
+                              push_idx=ids if push else None, push_hist=histories[l - 1] if push else None)
             x = y
             continue
         z = torch.empty((nb, x.shape[1]), dtype=dt, device=dev)
         if model.op == "gcn":
             B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, bg.val, x, table, z)
             if push:
-                B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], relu=True)
+                B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], relu=True)
             else:
                 B.gas_linear(z, model.weights[l - 1], y, relu=not last)
         else:
@@ -228,10 +229,10 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
             w1, w2 = model.weights[l - 1]
             if _mlp_in_two(z, w1, w2):
                 h = torch.empty((nb, w1.shape[1]), dtype=dt, device=dev)
-                B.gas_mlp2_keep(z, w1, w2, y, h, idx=bg.n_id[:nb] if push else None,
+                B.gas_mlp2_keep(z, w1, w2, y, h, idx=ids if push else None,
                                 hist=histories[l - 1] if push else None, relu_out=not last)
             elif push:
-                B.gas_mlp2_push(z, w1, w2, y, bg.n_id[:nb], histories[l - 1], relu_out=True)
+                B.gas_mlp2_push(z, w1, w2, y, ids, histories[l - 1], relu_out=True)
             else:
                 B.gas_mlp2(z, w1, w2, y, relu_out=not last)
         x = y
@@ -241,6 +242,7 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
 def _forward_gcnii_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push):
     dev, dt = x_feat.device, x_feat.dtype
     nb, nv = bg.nb, bg.nv
+    ids = bg.n_id[:nb]
     x0 = torch.empty((nv, x_feat.shape[1]), dtype=dt, device=dev)
     B.gas_pull(x_feat, bg.n_id, x0)
     h0 = torch.empty((nv, model.w_in.shape[1]), dtype=dt, device=dev)
@@ -257,7 +259,7 @@ def _forward_gcnii_fused(model: Model, bg: BatchGraph, x_feat, histories, do_pus
             B.gas_spmm_linear(bg.rowptr, bg.col if l == 1 else bg.src, bg.val, x, model.weights[l - 1], y,
                               hist=None if l == 1 else histories[l - 2], s_agg=1.0 - model.alpha, r=h0,
                               s_res=model.alpha, c_identity=1.0 - beta, c_weight=beta, relu=not last,
-                              push_idx=bg.n_id[:nb] if push else None, push_hist=histories[l - 1] if push else None)
+                              push_idx=ids if push else None, push_hist=histories[l - 1] if push else None)
             x = y
             continue
         z = torch.empty((nb, h0.shape[1]), dtype=dt, device=dev)
@@ -267,7 +269,7 @@ def _forward_gcnii_fused(model: Model, bg: BatchGraph, x_feat, histories, do_pus
             B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, bg.val, x, histories[l - 2], z, s_agg=1.0 - model.alpha, r=h0,
                             s_res=model.alpha)
         if push:
-            B.gas_linear_push(z, model.weights[l - 1], y, bg.n_id[:nb], histories[l - 1], c_identity=1.0 - beta,
+            B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], c_identity=1.0 - beta,
                               c_weight=beta, relu=True)
         else:
             B.gas_linear(z, model.weights[l - 1], y, c_identity=1.0 - beta, c_weight=beta, relu=not last)
