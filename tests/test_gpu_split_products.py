@@ -229,7 +229,10 @@ def test_weights_in_registers_and_values_that_the_split_cannot_hold(z_low, w_low
 # is not whole, and both sides of the rule (256 tiles of 64 x 64)
 @pytest.mark.parametrize("what", ["linear", "input"])
 @pytest.mark.parametrize("m,k,n", [(1, 65, 3), (70, 96, 65), (64, 128, 64), (100, 129, 70), (130, 161, 300), (500, 1024, 130), (77, 1433, 63),
-                                   (4096, 70, 256), (4097, 70, 256)])
+                                   (4096, 70, 256), (4097, 70, 256),
+                                   # six steps and more; 32 tiles on an XCD and 33 or 36
+                                   (1, 161, 3), (70, 161, 65), (64, 192, 64), (100, 193, 70), (4096, 165, 256), (4097, 165, 256),
+                                   (5376, 161, 66), (5632, 161, 130)])
 def test_steps_in_groups(what, m, k, n):
     a, b, terms = _operands(what, m, k, n) if what == "linear" else _operands(what, m, n, k)
     _check_every_element(what, a, b, terms, *((k, n) if what == "linear" else (n, k)))
