@@ -276,7 +276,7 @@ __global__ __launch_bounds__(256, WPS) void linear_split_kernel(LinArgs a) {
 // its chains of dependent products and LDS reads leave the unit idle.  The sum over the groups goes through LDS.
 template <int BM, int BN, bool TRANS, int KG>
 __global__ __launch_bounds__(256 * KG) void linear_split_groups_kernel(LinArgs a) {
-    using G = SplitGemm<BM, BN, 2, 2, 2, true, TRANS>;
+    using G = SplitGemm<BM, BN, 2, 2, 2, true, TRANS, KG>;
     constexpr int TM = G::TM, TN = G::TN;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const float* Z = reinterpret_cast<const float*>(a.Z);
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(256 * KG) void linear_split_groups_kernel(LinArgs a
     const int64_t ldw = TRANS ? a.K : a.N;
     G g;
     f32x16 acc[TM][TN];
-    if (!g.template run_groups<KG>(Z, a.ldz, m0, a.M, W, ldw, n0, a.N, a.K, reinterpret_cast<uint16_t*>(smem), group, wm0, wn0, acc))
+    if (!g.run_groups(Z, a.ldz, m0, a.M, W, ldw, n0, a.N, a.K, reinterpret_cast<uint16_t*>(smem), group, wm0, wn0, acc))
         plain_tile<TM, TN, true, TRANS>(Z, a.ldz, m0 + wm0, a.M, W, ldw, n0 + wn0, a.N, 0, a.K, acc);
     if (group == 0) store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
@@ -1805,7 +1805,7 @@ gas_status launch_split(const LinArgs& a, hipStream_t s) {
 
 template <int BM, int BN, int KG, bool TRANS>
 gas_status launch_groups(const LinArgs& a, hipStream_t s) {
-    constexpr int smem = SplitGemm<BM, BN, 2, 2, 2, true, TRANS>::template kGroupsLdsBytes<KG>;
+    constexpr int smem = SplitGemm<BM, BN, 2, 2, 2, true, TRANS, KG>::kGroupsLdsBytes;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_split_groups_kernel<BM, BN, TRANS, KG>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     GAS_CHECK_HIP(attr);

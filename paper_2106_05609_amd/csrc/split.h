@@ -54,7 +54,9 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint
 // index q.  KC: element (r, q) lies at X[r ld + q] (q contiguous), else at X[q ld + r].  A thread holds pieces of
 // eight consecutive q of one row and writes them to LDS as one 16-byte piece per part: [part][row][q], the pieces of a
 // row exchanged so that the 16-byte reads of consecutive rows fall on different banks.
-template <int ROWS, int KS, bool KC, int T>
+// KG groups of T threads each take a tile of their own; a thread's number in its group is `threadIdx.x` itself where there is one
+// group (a remainder there changed the order of the kernel's instructions: 6,000 x 498 x 192 in 64 x 64 tiles 22.5 -> 23.3 us).
+template <int ROWS, int KS, bool KC, int T, int KG>
 struct SplitTile {
     static constexpr int kQ = 16 * KS, kCh = 2 * KS, kPieces = ROWS * kCh;
     static constexpr int kPlane = ROWS * kQ;                              // bf16 elements
@@ -66,16 +68,17 @@ struct SplitTile {
     float v[NV][8];
     int64_t ld;
 
+    static __device__ __forceinline__ unsigned thread() { return KG == 1 ? threadIdx.x : threadIdx.x % T; }
     static __device__ __forceinline__ int row_of(int i) {
-        const int idx = threadIdx.x % T + T * i;
+        const int idx = thread() + T * i;
         return KC ? idx / kCh : idx % ROWS;
     }
     static __device__ __forceinline__ int piece_of(int i) {
         // q contiguous: neighbouring threads take one row's pieces; else a wavefront has one piece index
-        if constexpr (KC) return (threadIdx.x % T + T * i) % kCh;
-        else return (__builtin_amdgcn_readfirstlane(threadIdx.x % T >> 6) * 64 + T * i) / ROWS;
+        if constexpr (KC) return (thread() + T * i) % kCh;
+        else return (__builtin_amdgcn_readfirstlane(thread() >> 6) * 64 + T * i) / ROWS;
     }
-    static __device__ __forceinline__ bool holds(int i) { return kPieces % T == 0 || (int)(threadIdx.x % T) + T * i < kPieces; }
+    static __device__ __forceinline__ bool holds(int i) { return kPieces % T == 0 || (int)thread() + T * i < kPieces; }
     // where piece `piece` of row `row` lies in a plane
     static __device__ __forceinline__ int at(int row, int piece) {
         return row * kQ + 8 * (KS == 2 ? (piece ^ ((row >> 1) & 3)) : (piece ^ ((row >> 2) & 1)));
@@ -158,11 +161,11 @@ struct SplitTile {
 
 // A BM x BN tile of sum_q A(r, q) B(c, q), q_begin <= q < q_end (not empty), by WM x WN wavefronts; `lds` holds kLdsBytes.  acc: the wavefront's TM x TN blocks of 32 x 32, at rows wm0.. and columns wn0..
 // of the tile.
-template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC>
+template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC, int KG = 1>
 struct SplitGemm {
     static constexpr int T = 64 * WM * WN, TM = BM / 32 / WM, TN = BN / 32 / WN;     // threads, 32 x 32 blocks of a wavefront
-    using TA = SplitTile<BM, KS, AKC, T>;
-    using TB = SplitTile<BN, KS, BKC, T>;
+    using TA = SplitTile<BM, KS, AKC, T, KG>;
+    using TB = SplitTile<BN, KS, BKC, T, KG>;
     static constexpr int kFlag = 3 * (TA::kPlane + TB::kPlane);              // where the flag lies, in bf16 elements
     static constexpr int kLdsBytes = kFlag * 2 + 16;
     TA ta;
@@ -266,7 +269,7 @@ struct SplitGemm {
 
     // The same by KG groups of T threads, each with LDS of its own: group `group` takes every KG-th step, and group 0 ends up with
     // the sum over the groups, added in their order (the other groups' acc is of no use afterwards).
-    template <bool SCALED, int KG>
+    template <bool SCALED>
     __device__ __forceinline__ void pass_groups(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
                                                 int64_t b0, int64_t b_end, int64_t q_end, uint16_t* lds, uint32_t* flag, int group,
                                                 int wm0, int wn0, f32x16 (&acc)[TM][TN]) {
@@ -360,18 +363,16 @@ struct SplitGemm {
     }
 
     // run() by KG groups; q from 0.  For group 0 as run(), the others take part and return true with nothing in acc.
-    template <int KG>
     static constexpr int kGroupsLdsBytes = KG * kFlag * 2 + 16;
-    template <int KG>
     __device__ __forceinline__ bool run_groups(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
                                                int64_t b0, int64_t b_end, int64_t q_end, uint16_t* lds, int group, int wm0, int wn0,
                                                f32x16 (&acc)[TM][TN]) {
         uint32_t* flag = reinterpret_cast<uint32_t*>(lds + KG * kFlag);
         if (threadIdx.x == 0) *flag = 0;         // before the first barrier of the pass, which sets it between its last two steps'
-        pass_groups<false, KG>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
+        pass_groups<false>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
         if (__builtin_amdgcn_readfirstlane(*flag)) {
             __syncthreads();                     // group 0 is done reading the sums
-            pass_groups<true, KG>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
+            pass_groups<true>(A, lda, a0, a_end, B, ldb, b0, b_end, q_end, lds, flag, group, wm0, wn0, acc);
         }
         if (group > 0) return true;
         float bad = 0.f;
