@@ -822,18 +822,24 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.xcd_ranges = plan->xcd_ranges;
     for (int x = 0; x < 9; ++x) a.xcd_start[x] = plan->xcd_start[x];
     // By slices: no row above the threshold, and (us on rotating inputs, whole rows -> slices)
-    // - a clustered pattern while the rows lie in the Infinity Cache: 51 MB 60 -> 56, 164 MB 473 -> 408; 512 MB 228 -> 270;
-    // - other patterns up to 16,384 rows: 5,000 power-law rows of 30 entries 31 -> 27, 7,500 of 46 55 -> 45, 4,000 equal ones of
-    //   119 32 -> 27; more of them are too uneven, a wavefront's teams wait for each other: 31,250 of 13 62 -> 72, 60,000 of 19
-    //   157 -> 188;
-    // - and with few entries a row up to 64 MB: adjoints over 31,250 and 60,000 power-law rows 47 -> 25 and 55 -> 45; over
-    //   312,500 (160 MB, bf16) a training step 3,534 -> 3,592.
+    // - up to 6,144 rows of any pattern and length: 5,000 power-law rows of 30 entries 31 -> 27, 4,000 equal ones of 119
+    //   32 -> 27, 6,000 clustered of 26 16.6 -> 15.3; without clusters up to 16,384: 7,500 power-law rows of 46 55 -> 45;
+    // - a clustered pattern in rows of 512 bytes up to 96 MB: 100,000 rows of 22 entries 102 -> 90 (bf16 102 -> 97), 200,000 of
+    //   8 96 -> 86 (82 -> 72); 300,000 bf16 rows of 3 86 -> 93;
+    // - in rows of 1,024 bytes up to 56 MB and 16 entries: 50,000 rows of 11 60 -> 56, 64,000 of 14 84 -> 76 in clusters of
+    //   5,000 and 74 -> 77 in clusters of 1,250.  With more entries a whole row, fetched once into the XCD that has its
+    //   cluster, serves many: 12,000 rows of 30 29 -> 33, 64,000 of 22 98 -> 118;
+    // - other patterns of at most eight entries a row, fp32 up to 32 MB: adjoints over 31,250 power-law rows 47 -> 25.  A
+    //   wavefront's teams wait for each other where lengths are uneven, from there on for longer than the slices save:
+    //   65,000 rows of 1,024 bytes and 2.4 entries 43 -> 52, 100,000 of 512 37 -> 44, bf16 already 48,000 of 5.5 37 -> 41.
     // Two slices at a time where rows are short and, as a clustered pattern tells, of like lengths: 50,000 rows 62 -> 56 (an
     // adjoint over 13,750 power-law rows: whole 65, one slice 52, two 75).
     const int64_t row_bytes = plan->n_rows * a.units * 16;
-    const bool fits = plan->xcd_ranges ? row_bytes <= (int64_t)192 << 20
-                                       : plan->n_rows <= 16384 || (plan->nnz <= 8 * plan->n_rows && row_bytes <= (int64_t)64 << 20);
-    a.slices = plan->n_heavy > 0 || !fits ? 0 : plan->xcd_ranges && plan->nnz <= 16 * plan->n_rows ? 2 : 1;
+    const bool few = plan->nnz <= (plan->xcd_ranges ? 16 : 8) * plan->n_rows;
+    const bool fits = plan->n_rows <= (plan->xcd_ranges ? 6144 : 16384) ||
+                      (plan->xcd_ranges ? (a.units == 32 ? row_bytes <= (int64_t)96 << 20 : few && row_bytes <= (int64_t)56 << 20)
+                                        : few && dt_x == GAS_F32 && row_bytes <= (int64_t)32 << 20);
+    a.slices = plan->n_heavy > 0 || !fits ? 0 : plan->xcd_ranges && few ? 2 : 1;
     const bool whole = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
                        a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
                        (!H || (aligned16(H) && a.h_stride % 16 == 0)) && (!Y || (aligned16(Y) && a.y_stride % 16 == 0));

@@ -401,6 +401,34 @@ def test_spmm_by_slices(gas, nb, mean, clustered, dtype, F, out):
         assert node_rel_err(got[1], np.where(y[:nb].float().numpy() > 0, want, 0)) <= tol
 
 
+@pytest.mark.parametrize("dtype,F", [(torch.float32, 256), (torch.float32, 128), (torch.bfloat16, 256)])
+@pytest.mark.parametrize("nb,entries", [(6144, 20), (6145, 20), (16384, 17), (16385, 3), (16385, 9), (57345, 3)])
+def test_spmm_on_both_sides_of_the_slices_rule(gas, nb, entries, dtype, F):
+    """The same pattern taken as clustered and as not: by slices in one and by whole rows in the other, or the same in both,
+    on either side of the rule's lines.  The same bits, and those of 64 bits to rounding."""
+    r = np.random.default_rng(nb + entries)
+    ptr = np.concatenate([[0], np.cumsum(r.integers(0, 2 * entries + 1, nb))]).astype(np.int32)
+    col, val = r.integers(0, nb, ptr[-1]).astype(np.int32), r.normal(size=ptr[-1]).astype(np.float32)
+    x = dev(rng.normal_matrix(11, 399, nb, F, dtype=dtype))
+    dptr, dcol, dval = (dev(torch.from_numpy(t)) for t in (ptr, col, val))
+    out = []
+    for clustered in (1, 2):
+        plan = gas.gas_plan_create(dptr, int(ptr[-1]), F, n_rows=nb, ind=dcol, options=dict(xcd_ranges=clustered))
+        z = torch.full((nb, F), float("nan"), dtype=dtype, device="cuda")
+        gas.gas_spmm(plan, dptr, dcol, dval, x, z)
+        out.append(z)
+    assert torch.equal(*out)
+    rows = torch.repeat_interleave(torch.arange(nb, device="cuda"), (dptr[1:] - dptr[:-1]).long())
+    want, size = (torch.zeros(nb, F, dtype=torch.float64, device="cuda") for _ in range(2))
+    terms = dval.double()[:, None] * x.double()[dcol.long()]
+    want.index_add_(0, rows, terms)
+    size.index_add_(0, rows, terms.abs())
+    # a product and its addition within 2^-24 of a partial sum each, at most 2 * entries of them; one rounding to storage, half
+    # of bf16's spacing of 2^-7
+    bound = (2 * entries + 1) * 2.0 ** -24 * size + (2.0 ** -8 * want.abs() if dtype == torch.bfloat16 else 0.0)
+    assert bool(((out[0].double() - want).abs() <= 1.01 * bound).all())
+
+
 @pytest.mark.parametrize("name,K,N,variant", [("sbm", 64, 64, "gcnii"), ("sbm", 128, 64, "gcn"), ("powerlaw", 100, 36, "gcn"),
                                                ("powerlaw", 128, 128, "gcnii"), ("gin", 8, 4, "gin"), ("sbm", 64, 64, "plain"),
                                                ("gin", 64, 32, "all_terms")])
