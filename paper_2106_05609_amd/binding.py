@@ -385,9 +385,13 @@ def gas_linear_bwd_weight(z, gp, dw, workspace, c_weight=1.0):
                                        _ptr(workspace), nbytes, _stream()))
 
 
+SHARED_WORKSPACE = 128 << 20
+
+
 def gas_linear_bwd_weights(items):
     """gas_linear_bwd_weight of every (z, gp, dw, c_weight) of a list, of one dtype; in float32 they share launches.  The
-    workspace is allocated here, once for all."""
+    workspace is allocated here, once for all; a list that would share more than SHARED_WORKSPACE bytes goes in halves (16 of
+    21,248 rows of 64 x 64 take 44 MB together, 16,000 rows of 1,433 x 256 62 MB each)."""
     n = len(items)
     if n == 0:
         return
@@ -401,6 +405,10 @@ def gas_linear_bwd_weights(items):
     rows = longs(*[z.shape[0] for z, _, _, _ in items])
     f_in, f_out = ints(*[z.shape[1] for z, _, _, _ in items]), ints(*[g.shape[1] for _, g, _, _ in items])
     need = _calls().gas_linear_bwd_weights_workspace(n, rows, f_in, f_out, _dt(items[0][0]))
+    if need > SHARED_WORKSPACE and n > 1:
+        gas_linear_bwd_weights(items[:n // 2])
+        gas_linear_bwd_weights(items[n // 2:])
+        return
     ws = torch.empty(max(1, need), dtype=torch.uint8, device=dev)
     _check(_calls().gas_linear_bwd_weights(
         n, pointers(*[p for p, _ in zs]), longs(*[ld for _, ld in zs]), pointers(*[p for p, _ in gs]),

@@ -145,12 +145,11 @@ class _WeightGrads:
     """The weight gradients of a backward pass.  Small ones wait for each other and share launches
     (gas_linear_bwd_weights): 21,248 rows of 64 x 64, 64 layers, 12 us each alone and 4 together.  A gradient matrix of
     more than 16 MB fills the chip by itself and is not kept waiting (it would only hold memory); bf16 has kernels
-    of its own.  What waits shares at most 128 MB of workspace, or one gradient's own (16 of 21,248 rows of 64 x 64 take
-    44 MB together, 16,000 rows of 1,433 x 256 62 MB each)."""
-    LARGEST, TOGETHER, WORKSPACE = 16 << 20, 16, 128 << 20
+    of its own."""
+    LARGEST, TOGETHER = 16 << 20, 16
 
     def __init__(self):
-        self.waiting, self.need = [], 0
+        self.waiting = []
 
     def waits(self, dtype, rows, width) -> bool:
         return dtype == torch.float32 and 4 * rows * width <= self.LARGEST
@@ -158,23 +157,21 @@ class _WeightGrads:
     def add(self, z, g, dw=None, c=1.0):
         """dW = c * z^T g, complete after done()."""
         if dw is None:
-            dw = torch.empty((z.shape[1], g.shape[1]), dtype=torch.float32, device=z.device)
-        need = B.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])
+            k, n = z.shape[1], g.shape[1]
+            dw = torch.empty_strided((k, n), (n, 1), dtype=torch.float32, device=z.device)      # two thirds of torch.empty's host time
         if self.waits(z.dtype, *g.shape):
-            if self.need + need > self.WORKSPACE:
-                self.done()
             self.waiting.append((z, g, dw, c))
-            self.need += need
             if len(self.waiting) == self.TOGETHER:
                 self.done()
             return dw
-        ws = torch.empty(max(1, need), dtype=torch.uint8, device=z.device)
+        ws = torch.empty(max(1, B.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])),
+                         dtype=torch.uint8, device=z.device)
         B.gas_linear_bwd_weight(z, g, dw, ws, c_weight=c)
         return dw
 
     def done(self):
         B.gas_linear_bwd_weights(self.waiting)
-        self.waiting, self.need = [], 0
+        self.waiting = []
 
 
 def _pushes(do_push, table) -> bool:

@@ -28,22 +28,30 @@ def test_stream_without_torchs_private_functions(missing, monkeypatch):
     assert binding._stream() == 1234
 
 
-def test_shared_workspace_of_the_weight_gradients_is_bounded(monkeypatch):
-    """Gradients that wait are flushed before their common workspace would pass the bound, after TOGETHER of them, and
-    at the end; one that alone needs more goes alone."""
+@pytest.mark.parametrize("together", [True, False])
+def test_shared_workspace_of_the_weight_gradients_is_bounded(together, monkeypatch):
+    """A pass's gradients, and a list given at once, go in parts whose workspace stays below the bound, or one by one; each
+    of them once and in order."""
     from paper_2106_05609_amd import binding
-    calls = []
-    monkeypatch.setattr(binding, "gas_linear_bwd_weights", lambda items: calls.append(list(items)) if items else None)
-    wg = executor._WeightGrads()
+    real, calls = binding._calls(), []
+
+    class Recorded:
+        gas_linear_bwd_weights_workspace = real.gas_linear_bwd_weights_workspace
+
+        def gas_linear_bwd_weights(self, count, *args):
+            calls.append((count, args[-2], list(args[8])))
+            return 0
+    monkeypatch.setattr(binding, "_calls", lambda: Recorded())
+    monkeypatch.setattr(binding, "_stream", lambda: 0)
     shapes = [(16000, 1433, 256), (16000, 256, 256), (16000, 256, 47)] + [(21248, 64, 64)] * 40 + [(16000, 1433, 256)] * 4 + [(16000, 3000, 256)]
-    outs = []
-    for m, k, n in shapes:
-        outs.append(wg.add(torch.empty(m, k, device="meta"), torch.empty(m, n, device="meta")))
-    wg.done()
-    need = lambda z, g: binding.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])
-    for items in calls:
-        assert len(items) <= wg.TOGETHER
-        assert len(items) == 1 or sum(need(z, g) for z, g, _, _ in items) <= 128 << 20
-    done = [dw for items in calls for _, _, dw, _ in items]
-    assert len(done) == len(outs) and all(a is b for a, b in zip(done, outs))           # each once, in order
-    assert max(len(items) for items in calls) == wg.TOGETHER
+    items = [(torch.empty(m, k), torch.empty(m, n), torch.empty(k, n), 1.0) for m, k, n in shapes]
+    if together:
+        binding.gas_linear_bwd_weights(items)
+    else:
+        wg = executor._WeightGrads()
+        for z, g, dw, c in items:
+            assert wg.add(z, g, dw, c) is dw
+        wg.done()
+    assert all(need <= 128 << 20 or count == 1 for count, need, _ in calls)
+    assert [p for _, _, dws in calls for p in dws] == [dw.data_ptr() for _, _, dw, _ in items]
+    assert max(count for count, _, _ in calls) >= 6
