@@ -39,7 +39,7 @@ def test_shared_workspace_of_the_weight_gradients_is_bounded(together, monkeypat
         gas_linear_bwd_weights_workspace = real.gas_linear_bwd_weights_workspace
 
         def gas_linear_bwd_weights(self, count, *args):
-            calls.append((count, args[-2], list(args[8])))
+            calls.append((count, args[-2], list(args[9])))
             return 0
     monkeypatch.setattr(binding, "_calls", lambda: Recorded())
     monkeypatch.setattr(binding, "_stream", lambda: 0)
