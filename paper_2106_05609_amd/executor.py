@@ -53,14 +53,13 @@ class BatchGraph:
         self._n_id_host = None
         self._plan_t_all, self._max_F = None, max_F
         self.colptr, self.row, self.val_t, self.plan_t = colptr, row, None, None
-        self.max_col = 0             # most in-batch rows that list one in-batch node
+        self.nnz_t, self.max_col = 0, 0          # entries of the in-batch columns, and of the longest of them
         if colptr is not None:
             # backward over the in-batch columns only: histories are constants
-            nnz_t = 0
             if self.nb > 0:
                 longest = (colptr[1:self.nb + 1] - colptr[:self.nb]).max()
-                self.max_col, nnz_t = torch.stack((longest, colptr[self.nb])).tolist()         # one read-back
-            self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], nnz_t, max_F,
+                self.max_col, self.nnz_t = torch.stack((longest, colptr[self.nb])).tolist()    # one read-back
+            self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], self.nnz_t, max_F,
                                                                      n_rows=self.nb, ind=row, options=plan_options))
             if normalise:
                 self.val_t = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
@@ -107,8 +106,34 @@ class Model:
 
 
 # Rows longer than this keep the two-kernel form, whose plan splits them over wavefronts; the one-launch layer
-# gives a row to one team of lanes.
+# gives a row to one team of lanes (backward: _back_in_one_launch).
 ONE_LAUNCH_MAX_ROW = 512
+
+
+def _back_in_one_launch(width, rows, entries, longest) -> bool:
+    """Whether the adjoint of the aggregation and the input gradient below it, `width` columns wide, are one launch
+    (gas_spmm_t_relu_linear) and not two (gas_spmm_t_relu by its plan, gas_linear_bwd_input_add).  `rows` in-batch nodes,
+    `entries` of the pattern, `longest` of one of them.  One team of lanes walks a row's entries, 0.09 us each, and the
+    eight teams of a wavefront wait for the longest; the plan spreads a long row.  us, one launch and two:
+    - short rows: 512 rows of up to 30 entries, 32 -> 32 columns, 6.3 and 8.4, 21,248 8.8 and 18.0; 10,000 of up to 40
+      7.8 and 12.0;
+    - few rows, where the host bounds a pass and a launch more is 10 us of its time: 512 rows of up to 60 9.3 and 9.1;
+    - longer ones of like lengths where many rows hide them: 10,000 rows of up to 100 13.4 and 15.6, 21,248 of up to 200
+      34.8 and 41.5; but 512 rows of up to 100 13.3 and 10.2;
+    - power-law lengths up to 500 where rows have few entries (21,248 rows of 2.4 0.76-1.0 of the time, of 7.4 1.2-1.6);
+    - 64 columns, 256-byte rows, up to 8,192 rows of any lengths up to ONE_LAUNCH_MAX_ROW: 5,000 rows of up to 100 14.9
+      and 27.0, power law 0.8-1.0 of the time (21,248 rows 1.0-1.2);
+    - more than 64 columns double the lanes of a row and halve the rows in flight: 21,248 rows of up to 30, 80 -> 80, 30.5
+      and 33.9, of up to 60 46.8 and 43.1.  128 columns, 512-byte rows, have the better plan: 5,000 rows of up to 20 10.8
+      and 13.2, 10,000 15.9 and 15.5, 21,248 26.7 and 23.4."""
+    if longest > ONE_LAUNCH_MAX_ROW:
+        return False
+    if longest <= (64 if rows <= 4096 else 48 if width <= 64 else 32):
+        return width < 128 or rows <= 8192
+    if width > 64:
+        return False
+    alike = longest * rows <= 4 * entries
+    return (width == 64 and rows <= 8192) or (alike and 100 * longest <= rows) or (rows >= 16384 and entries <= 4 * rows)
 
 
 def _mlp_in_two(z, w1, w2) -> bool:
@@ -606,6 +631,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     pooled = (L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
               and wg.waits(dt, nb, widths[0]))
     gxs, spare, total = [], [], None
+    one_launch = {w: fused and _back_in_one_launch(w, nb, bg.nnz_t, bg.max_col) for w in set(widths)}
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
@@ -651,7 +677,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         gx = gxs.pop() if gxs else torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         s_agg = 1.0 - model.alpha if model.op == "gcnii" else 1.0
         w_below = model.weights[l - 2]
-        if (fused and (model.op == "gcnii" or (model.op == "gcn" and l > 2)) and bg.max_col <= ONE_LAUNCH_MAX_ROW
+        if (one_launch[widths[l - 2]] and (model.op == "gcnii" or (model.op == "gcn" and l > 2))
                 and B.spmm_linear_supported(gz, w_below.shape[0]) and w_below.data_ptr() % 16 == 0):
             # narrow layers: the layer below's input gradient in the same launch (GCN's first layer has none)
             beta = gcnii_beta(l - 1) if model.op == "gcnii" else 1.0

@@ -16,6 +16,17 @@ def test_form_of_the_mlp(dtype, rows, f_in, hidden, f_out, in_two):
     assert executor._mlp_in_two(shape(rows, f_in), shape(f_in, hidden), shape(hidden, f_out)) is in_two
 
 
+@pytest.mark.parametrize("width,rows,entries,longest,one", [
+    (64, 21248, 300_000, 40, True), (32, 512, 7_000, 48, True), (64, 5000, 500_000, 200, True), (64, 8192, 20_000, 512, True),
+    (60, 60_000, 140_000, 500, True), (32, 21_248, 2_000_000, 200, True), (128, 5000, 50_000, 20, True), (128, 4096, 90_000, 64, True),
+    (80, 21_248, 300_000, 30, True),
+    # measured: two launches were the faster form
+    (32, 512, 25_000, 100, False), (48, 8000, 60_000, 500, False), (64, 60_000, 450_000, 500, False), (16, 21_248, 157_000, 500, False),
+    (128, 10_000, 100_000, 20, False), (96, 5000, 150_000, 60, False), (68, 21_248, 500_000, 40, False), (128, 512, 20_000, 65, False), (64, 500, 10_000, 513, False)])
+def test_form_of_the_backward_layer(width, rows, entries, longest, one):
+    assert executor._back_in_one_launch(width, rows, entries, longest) is one
+
+
 @pytest.mark.parametrize("missing", ["_raw_stream", "_device"])
 def test_stream_without_torchs_private_functions(missing, monkeypatch):
     from paper_2106_05609_amd import binding
