@@ -1936,12 +1936,14 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         if (F_in <= 16) return launch_split<64, 64, 1, 4>(a, s);
         // One to two columns of 128 x 128 tiles, in more than one round of the 512 that run at once: the weights stay put instead
         // (33,000 rows 256 -> 256: 32 us, in tiles 48; 50,000 rows 256 -> 136: 40 and 52, 144 -> 256: 36 and 40, 72 -> 256: 27 and 31;
-        // below, 26,000 rows 256 -> 256: 27 and 27, 16,000: 20 and 18).  The tiles stay where they do no work for padding:
-        // 96 whole columns in less than three rounds (50,000 rows 96 -> 256: 27 and 26; 100,000: 44 and 46), up to 160 in two
-        // full rounds (64,000 rows 160 -> 256: 45 and 41; 100,000: 62 and 67).
+        // below, 26,000 rows 256 -> 256: 27 and 27, 16,000: 20 and 18).  The tiles stay where they do no work for padding, up to
+        // 160 whole columns to 256: 96 in less than three rounds (65,000 rows, the transform 27.7 us and with the weights in place
+        // 30.3, the input gradient 26.8 and 31.0), 128 and 160 in two full rounds, 897 to 1,024 tiles (65,000 rows of 160: 38.8 and
+        // 39.7, 37.1 and 41.3, of 128 33.3 and 32.8, 32.2 and 34.4; at 896 tiles of 160 39.5 and 36.4, 38.1 and 37.7, at 1,026
+        // 48.9 and 43.0, 46.6 and 44.5).  With any padding the weights stay (65,000 rows 160 -> 252: 49.1 and 38.7, 47.4 and 41.4).
         if (F_in > 64 && F_in <= 256 && F_out > 128 && F_out <= 256 && large > 512 &&
             c_identity == 0.f && !add && !total && (!mask || trans_w)) {
-            const bool unpadded = F_in % 32 == 0 && F_in <= 160 && F_out > 192;
+            const bool unpadded = F_in % 32 == 0 && F_in <= 160 && F_out == 256;
             if (!unpadded || (F_in <= 96 ? large > 1536 : large <= 896 || large > 1024)) {
                 if (mask) return run_ws_split<true, true>(a, s);
                 return trans_w ? run_ws_split<true, false>(a, s) : run_ws_split<false, false>(a, s);

@@ -194,7 +194,7 @@ def _every_option(m, k, n, z, w):
 # tile of one row and of all but one, rows on both sides of the rule (512 tiles of 128 x 128)
 @pytest.mark.parametrize("m,k,n", [(32768, 256, 256), (32769, 65, 129), (32800, 97, 131), (33000, 128, 256), (32783, 131, 200),
                                    (32769, 190, 255), (40001, 223, 160), (33001, 254, 256), (33008, 256, 130), (98400, 96, 256),
-                                   (60000, 160, 256), (65700, 160, 250)])
+                                   (60000, 160, 256), (65700, 160, 250), (57473, 128, 252), (49200, 96, 200)])
 def test_weights_in_registers(m, k, n):
     z, w = rng.normal_matrix(11, 760, m, k).cuda(), rng.normal_matrix(11, 761, k, n).cuda()
     for name, got, want, bound in _every_option(m, k, n, z, w):
