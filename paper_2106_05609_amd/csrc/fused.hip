@@ -54,6 +54,8 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 // BWD: the same on the adjoint (gas_spmm_t_relu_linear): the pattern is the CSC copy, the activations of the layer below mask
 // the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 20 us where the
 // aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
+// <8, 2, 2> spills 7 registers (BWD 11) to keep three wavefronts on a SIMD: 21,248 rows of 50, 64 -> 128, 33.5 us, with two
+// and none spilled 41.9 (rows of 5: 15.4 and 15.7).
 template <int G, int P, int NB, bool BWD>
 __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kernel(FusedArgs a) {
     constexpr int KQ = G * P / 4, LDZ = 16 * KQ + 4;                      // steps of 16 k, floats of a row of Zs
@@ -263,9 +265,14 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
 
 template <int G, int P, int NB, bool BWD>
 gas_status launch_layer(const FusedArgs& a, hipStream_t s) {
-    // Workgroups that a CU holds at once (by registers): one more would wait for a slot and then walk its tiles alone.
-    // 100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us.
-    constexpr int64_t per_cu = G == 8 ? 3 : 2;
+    // Workgroups that a CU holds at once, as the compiled kernel's registers and LDS allow: one more would wait for a slot and then
+    // walk its tiles alone (100,000 rows of 64, 14 entries each: 42 us, with a grid for four 54 us), one less leaves the others
+    // more tiles (60,000 rows of 15, 32 -> 32: 23.2 us by three, 19.5 by the four that fit).
+    static const int64_t per_cu = [] {
+        int n = 0;
+        const hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, spmm_linear_f32_kernel<G, P, NB, BWD>, kThreads, 0);
+        return e == hipSuccess && n > 0 ? n : 2;
+    }();
     const int64_t per_xcd = (a.n_tiles + 7) / 8;                                   // a multiple of eight workgroups
     const unsigned blocks = (unsigned)(8 * (per_xcd < 32 * per_cu ? per_xcd : 32 * per_cu));
     hipLaunchKernelGGL((spmm_linear_f32_kernel<G, P, NB, BWD>), dim3(blocks), dim3(kThreads), 0, s, a);
