@@ -1953,12 +1953,13 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
             if (F_out > 64 && large >= 352) return launch_split<128, 128, 2, 2>(a, s);
             if (tiles * ((F_out + 63) / 64) >= 384) return launch_split<128, 64, 2, 3>(a, s);
         }
-        // More than five steps of 32 k and no more than a tile for a compute unit: the steps go to four groups of wavefronts
-        // (500 x 1,024 x 1,024: 29.9 -> 24.5 us, 2,500 x 850 x 255 28.0 -> 22.5, 4,000 x 256 x 256 9.8 -> 9.0; up to 160 columns
-        // the sum over the groups costs what they save, 5,500 x 160 x 128: 8.5 -> 8.9).  A workgroup fills a unit, and the
-        // column tiles of a row tile share one of the eight XCDs of 32: at 33 tiles on an XCD one of them waits for a
-        // second round (5,120 x 192 x 192, 30 on an XCD: 9.4 and 9.1; 5,400 rows, 33: 11.2 and 16.5).
-        if (F_in > 160 && ((n_rows + 63) / 64 + 7) / 8 * ((F_out + 63) / 64) <= 32)
+        // No more than a tile for a compute unit: its steps go to four groups of wavefronts (500 x 1,024 x 1,024: 29.9 -> 24.5 us,
+        // 2,500 x 850 x 255 28.0 -> 22.5, 4,000 x 256 x 256 9.8 -> 9.0).  Up to five steps the sum over the groups costs a call
+        // that repeats itself more than they save (5,000 x 128 x 64: 5.8 -> 6.1), but right after the aggregation that wrote its
+        // input the same call ends 0.8 us earlier, 2,000 x 160 x 128 0.6, 512 x 80 x 64 0.1: that is how passes call it.  A
+        // workgroup fills a unit, and the column tiles of a row tile share one of the eight XCDs of 32: at 33 tiles on an
+        // XCD one of them waits for a second round (5,120 x 192 x 192, 30 on an XCD: 9.4 and 9.1; 5,400 rows, 33: 11.2 and 16.5).
+        if (F_in > 64 && ((n_rows + 63) / 64 + 7) / 8 * ((F_out + 63) / 64) <= 32)
             return trans_w ? launch_groups<64, 64, 4, true>(a, s) : launch_groups<64, 64, 4, false>(a, s);
         return launch_split<64, 64, 2, 4>(a, s);
     }
