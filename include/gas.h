@@ -374,7 +374,9 @@ GAS_API gas_status gas_linear_bwd_weight(const void* Z, int64_t ldz, const void*
                                  float* dW, void* workspace, int64_t workspace_bytes, void* stream);
 
 /* gas_linear_bwd_weight of `count` pairs (host arrays of `count`): in fp32 up to 16 of them share a launch, and another for
- * the sums over their slabs.  Same slabs, same bits as single calls.  No output may overlap another matrix of the call; the workspace is one for all. */
+ * the sums over their slabs.  Same slabs, and the same bits as single calls where no sum of a slab overflows or meets a value
+ * that is not finite: a block of a gradient with such a sum is formed by the fp32 instruction, and among wider problems the
+ * blocks of a narrow one are larger.  No output may overlap another matrix of the call; the workspace is one for all. */
 GAS_API int64_t gas_linear_bwd_weights_workspace(int32_t count, const int64_t* n_rows, const int32_t* F_in, const int32_t* F_out,
                            gas_dtype dt);
 GAS_API gas_status gas_linear_bwd_weights(int32_t count, const void* const* Z, const int64_t* ldz, const void* const* GP,

@@ -184,3 +184,28 @@ def test_weight_gradients_in_shared_launches(gas, dtype, shapes):
         ws = torch.empty(max(1, gas.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])), dtype=torch.uint8, device="cuda")
         gas.gas_linear_bwd_weight(z, g, dw, ws, c_weight=c)
         assert torch.equal(one, dw)
+
+
+def test_weight_gradients_in_shared_launches_with_values_that_are_not_finite(gas):
+    """Wide and narrow problems together, each with an infinity and a NaN in one row: they reach the row or the column of the
+    gradient that they enter and nothing else, whatever block that lies in.  Every other element within rounding of 64 bits,
+    and within rounding of a single call."""
+    items, wants = [], []
+    for i, (m, k, n) in enumerate([(700, 130, 140), (700, 200, 40), (700, 40, 200), (300, 64, 64), (129, 1, 300)]):
+        z, g = (rng.normal_matrix(12, 870 + 2 * i + j, m, w) for j, w in enumerate((k, n)))
+        z[m // 2, k // 2] = float("inf")
+        g[m // 3, n // 2] = float("nan")
+        items.append((dev(z), dev(g), torch.full((k, n), 7.0, device="cuda"), 1.0))
+        fine = torch.ones(k, n, dtype=torch.bool)
+        fine[k // 2], fine[:, n // 2] = False, False
+        z[m // 2, k // 2] = g[m // 3, n // 2] = 0.0
+        # fp32: an operand's parts are exact, a product within 2^-24, an addition within 2^-24 of a partial sum
+        wants.append((fine, z.double().t() @ g.double(), (m + 8) * 2.0 ** -24 * (z.double().abs().t() @ g.double().abs())))
+    gas.gas_linear_bwd_weights(items)
+    for (z, g, dw, _), (fine, want, bound) in zip(items, wants):
+        one = torch.full_like(dw, 7.0)
+        ws = torch.empty(max(1, gas.gas_linear_bwd_weight_workspace(z.shape[0], z.shape[1], g.shape[1])), dtype=torch.uint8, device="cuda")
+        gas.gas_linear_bwd_weight(z, g, one, ws)
+        for got in (dw.cpu(), one.cpu()):
+            assert torch.equal(torch.isfinite(got), fine)
+            assert bool(((got.double() - want).abs() <= bound)[fine].all())
