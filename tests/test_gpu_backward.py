@@ -209,3 +209,36 @@ def test_weight_gradients_in_shared_launches_with_values_that_are_not_finite(gas
         for got in (dw.cpu(), one.cpu()):
             assert torch.equal(torch.isfinite(got), fine)
             assert bool(((got.double() - want).abs() <= bound)[fine].all())
+
+
+# more layers than wait for their weight gradients together, three times over; narrow layers of GCN, of one width and of
+# several, whose backward layers take one launch each
+@pytest.mark.parametrize("fused", [True, False])
+@pytest.mark.parametrize("op,widths,max_col", [("gcnii", [128] + [64] * 36, None), ("gcnii", [40] + [32] * 19, None),
+                                                ("gcn", [64] * 6, None), ("gcn", [40, 64, 32, 64, 20, 8], None),
+                                                ("gcn", [64, 64, 64, 64, 64], 513), ("gcn", [24, 72, 72, 128, 128, 36], None)])
+def test_deep_and_narrow_backward_matches_oracle(op, widths, max_col, fused):
+    from paper_2106_05609_amd import executor
+    cfg = configs.config(3 if op == "gcnii" else 1, 0.02)
+    cfg.widths = widths
+    wl = configs.build_workload(cfg)
+    g = wl.graph
+    om, gm = oracle_model(wl), _gpu_model(wl)
+    hs = [h.to("cuda") for h in configs.make_histories(cfg, init="normal")]
+    sg = batches.batch_subgraph(g, wl.batches[0], cfg.self_loops)
+    bg = _gpu_batch(wl, sg, g.deg.to("cuda"))
+    assert executor._back_in_one_launch(64, bg.nb, bg.nnz_t, bg.max_col)
+    if max_col is not None:
+        bg.max_col = max_col                   # as if a node were listed by more rows than one launch takes
+    grad_out = rng.normal_matrix(cfg.seed, 630, sg.nb, widths[-1])
+    _, grads, kept = executor.train_batch(gm, bg, wl.x.to("cuda"), hs, grad_out.to("cuda"), fused=fused)
+    n_id, rp, cl = to_np(sg.n_id), to_np(sg.rowptr), to_np(sg.col)
+    # both sides read the masks off the same stored activations
+    saved = [(to_np(z), None, to_np(y)) for z, _, y in kept["layers"]]
+    want = omodel.gas_batch_backward(om, n_id, rp, cl, sg.nb, oops.gcn_norm(rp, cl, n_id, to_np(g.deg)), to_np(kept["x0"]),
+                                     None if kept["h0"] is None else to_np(kept["h0"]), saved, to_np(grad_out))
+    # a layer's aggregation and product each within 1e-6 of their largest element, through all layers above
+    tol = 1e-6 * max(20, 2 * om.n_layers)
+    assert set(grads) == set(want)
+    for l in want:
+        assert max_rel_err(to_np(grads[l]), want[l]) <= tol, (l, max_rel_err(to_np(grads[l]), want[l]))
