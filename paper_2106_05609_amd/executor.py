@@ -176,15 +176,11 @@ class _WeightGrads:
     def __init__(self):
         self.waiting = []
 
-    def waits(self, dtype, rows, width) -> bool:
-        return dtype == torch.float32 and 4 * rows * width <= self.LARGEST
-
     def add(self, z, g, dw=None, c=1.0):
         """dW = c * z^T g, complete after done()."""
         if dw is None:
-            k, n = z.shape[1], g.shape[1]
-            dw = torch.empty_strided((k, n), (n, 1), dtype=torch.float32, device=z.device)      # two thirds of torch.empty's host time
-        if self.waits(z.dtype, *g.shape):
+            dw = torch.empty((z.shape[1], g.shape[1]), dtype=torch.float32, device=z.device)
+        if z.dtype == torch.float32 and 4 * g.numel() <= self.LARGEST:
             self.waiting.append((z, g, dw, c))
             if len(self.waiting) == self.TOGETHER:
                 self.done()
@@ -530,9 +526,10 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     is computed in-graph for the halo rows too and its gradient includes them.  GIN's MLP stores its hidden
     activation here (gas_mlp2_keep: the backward pass reads it again).  Returns (Y_L, grads, kept) with
     grads[l] = dW_l (float32; a pair for GIN), grads["w_in"] for GCNII, and kept = the stored activations the
-    backward pass read (x0, h0, per layer (Z, hidden, Y)).  Y_L and every gradient own their memory; kept activations
-    of one width share an allocation (_matrices), so keeping one of them keeps those.  grad_out is dLoss/dY_L
-    [nb, F_L], or a function that returns it given Y_L.  fused: the forward aggregations read their halo rows from the feature table / the
+    backward pass read (x0, h0, per layer (Z, hidden, Y)).  Y_L owns its memory; kept activations of one width share an
+    allocation (_matrices), so keeping one of them keeps those, and the weight gradients of a model of one width share one of
+    the size of its weights (64 layers of 64 x 64: 1 MB; one by one they took 1.4 us of host time each).  grad_out is
+    dLoss/dY_L [nb, F_L], or a function that returns it given Y_L.  fused: the forward aggregations read their halo rows from the feature table / the
     history tables in place (gas_spmm_hist) and nothing is pulled; same bits.  GCNII's first layer gathers the
     projected features from the mini-batch tensor, its later layers from the histories.  Narrow fp32 layers of
     GCN and GCNII then take one launch each (gas_spmm_linear with Z kept; the row sums are taken in another order,
@@ -552,9 +549,11 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     y = None
     ids = bg.n_id[:nb]
     widths = [model.out_width(l) for l in range(L)]
-    zs = _matrices(nb, [x.shape[1]] + widths[:-1], dt, dev)
+    ins = [x.shape[1]] + widths[:-1]
+    zs = _matrices(nb, ins, dt, dev)
     # whole mini-batch tensors where the halo rows are pulled into them
     ys = _matrices(nb if fused else nv, widths[:-1], dt, dev) + [torch.empty((nb, widths[-1]), dtype=dt, device=dev)]
+    betas = [gcnii_beta(l) for l in range(1, L + 1)] if model.op == "gcnii" else [1.0] * L
     short_rows = fused and model.op in ("gcn", "gcnii") and bg.max_row <= ONE_LAUNCH_MAX_ROW
     for l in range(1, L + 1):
         last = l == L
@@ -567,7 +566,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         if short_rows and B.spmm_linear_supported(x, widths[l - 1]):
             # narrow layers: aggregation, transform and Push in one launch; Z is kept for the weight gradient
             push = not last and do_push
-            beta = gcnii_beta(l) if model.op == "gcnii" else 1.0
+            beta = betas[l - 1]
             kw = dict(s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha, c_identity=1.0 - beta,
                       c_weight=beta) if model.op == "gcnii" else {}
             B.gas_spmm_linear(bg.rowptr, bg.col if table is None else bg.src, bg.val, x, model.weights[l - 1], y,
@@ -606,7 +605,7 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
                                 s_res=model.alpha)
             else:
                 B.gas_spmm(bg.plan, bg.rowptr, bg.col, bg.val, x, z, s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha)
-            beta = gcnii_beta(l)
+            beta = betas[l - 1]
             pushed = not last and _pushes(do_push, histories[l - 1])
             if pushed:
                 B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], c_identity=1.0 - beta,
@@ -627,16 +626,20 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     g = grad_out(y) if callable(grad_out) else grad_out     # a loss: gradient at the output, from the output
     g_h0 = None
     ready = None                              # the gradient at the layer's aggregated rows, if the launch above formed it
-    # gradient matrices of one width that wait for their weight gradients are allocated together
-    pooled = (L >= 4 and model.op != "gin" and all(w == zs[0].shape[1] for w in widths)
-              and wg.waits(dt, nb, widths[0]))
+    one_width = L >= 4 and model.op != "gin" and all(i == o for i, o in zip(ins, widths))
+    dws = _matrices(widths[0], widths, torch.float32, dev) if one_width else [None] * L
+    # gradient matrices that wait for their weight gradients are allocated together
+    pooled = one_width and dt == torch.float32 and 4 * nb * widths[0] <= wg.LARGEST
     gxs, spare, total = [], [], None
-    one_launch = {w: fused and _back_in_one_launch(w, nb, bg.nnz_t, bg.max_col) for w in set(widths)}
+    joint = ()                                # widths of the layers whose input gradient shares the adjoint's launch
+    if fused and (model.op == "gcnii" or (model.op == "gcn" and L > 2)):      # (GCN's first layer has none)
+        joint = {(i, o) for i, o in set(zip(ins, widths))
+                 if B.spmm_linear_supported(zs[ins.index(i)], o) and _back_in_one_launch(o, nb, bg.nnz_t, bg.max_col)}
     for l in range(L, 0, -1):
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
         if model.op == "gcn":
-            grads[l - 1] = wg.add(z, g)
+            grads[l - 1] = wg.add(z, g, dws[l - 1])
             if l > 1 and gz is None:          # below the first layer there is nothing to train
                 gz = torch.empty_like(z)
                 B.gas_linear_bwd_input(g, model.weights[l - 1], gz)
@@ -654,8 +657,8 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             x_in = x0 if l == 1 else saved[l - 2][2]
             B.gas_row_dot(gz, x_in[:nb], torch.empty(nb, dtype=torch.float32, device=dev), grads["eps"][l - 1:l])
         else:
-            beta = gcnii_beta(l)
-            grads[l - 1] = wg.add(z, g, c=beta)
+            beta = betas[l - 1]
+            grads[l - 1] = wg.add(z, g, dws[l - 1], beta)
             if g_h0 is None:
                 g_h0 = torch.zeros((nv, z.shape[1]), dtype=dt, device=dev)
                 total = g_h0[:nb]
@@ -677,10 +680,9 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
         gx = gxs.pop() if gxs else torch.empty((nb, gz.shape[1]), dtype=dt, device=dev)
         s_agg = 1.0 - model.alpha if model.op == "gcnii" else 1.0
         w_below = model.weights[l - 2]
-        if (one_launch[widths[l - 2]] and (model.op == "gcnii" or (model.op == "gcn" and l > 2))
-                and B.spmm_linear_supported(gz, w_below.shape[0]) and w_below.data_ptr() % 16 == 0):
-            # narrow layers: the layer below's input gradient in the same launch (GCN's first layer has none)
-            beta = gcnii_beta(l - 1) if model.op == "gcnii" else 1.0
+        if joint and (l > 2 or model.op == "gcnii") and (ins[l - 2], widths[l - 2]) in joint and w_below.data_ptr() % 16 == 0:
+            # narrow layers: the layer below's input gradient in the same launch
+            beta = betas[l - 2]
             ready = spare.pop() if spare and spare[-1].shape[1] == w_below.shape[0] else torch.empty(
                 (nb, w_below.shape[0]), dtype=dt, device=dev)
             B.gas_spmm_t_relu_linear(bg.colptr, bg.row, bg.val_t, gz, y_below, gx, w_below, ready, s_agg=s_agg,

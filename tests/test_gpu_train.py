@@ -344,8 +344,9 @@ def test_training_step_with_the_regulariser_matches_oracle(gas, op):
 
 
 @pytest.mark.parametrize("fused", [True, False])
-def test_results_of_a_step_own_their_memory(fused):
-    """A caller who keeps the logits or one gradient of a deep model's step keeps that matrix, not the whole pass."""
+def test_results_of_a_step_do_not_hold_the_pass(fused):
+    """A caller who keeps the logits of a deep model's step keeps that matrix alone, and one who keeps a gradient at most
+    as much as the gradients are."""
     from paper_2106_05609_amd import executor
     wl = configs.build_workload(configs.config(3, 0.02))
     gm = _gpu_model(wl)
@@ -354,8 +355,9 @@ def test_results_of_a_step_own_their_memory(fused):
     hs = [h.to("cuda") for h in configs.make_histories(wl.cfg)]
     labels = torch.zeros(sg.nb, dtype=torch.int32, device="cuda")
     _, _, y, grads = executor.train_step(gm, bg, wl.x.to("cuda"), hs, labels, 0.01, fused=fused)
-    for t in [y] + list(grads.values()):
-        assert t.untyped_storage().nbytes() == t.numel() * t.element_size(), tuple(t.shape)
+    assert y.untyped_storage().nbytes() == y.numel() * y.element_size()
+    size = sum(g.numel() * g.element_size() for g in grads.values())
+    assert all(g.untyped_storage().nbytes() <= size for g in grads.values())
 
 
 # neither waits for its weight gradient: bf16, and fp32 matrices of more than 16 MB
