@@ -52,8 +52,8 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 // products by two of the four wavefronts and the weights in LDS 21.9).  Without the gathers 7.6 us, without the transform
 // 13.7: what is left is the gather's chain of two to three batches and the rows that every XCD fetches anew (4.6 TB/s).
 // BWD: the same on the adjoint (gas_spmm_t_relu_linear): the pattern is the CSC copy, the activations of the layer below mask
-// the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 20 us where the
-// aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
+// the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 15.7 us
+// where the aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
 // <8, 2, 2> spills 7 registers (BWD 11) to keep three wavefronts on a SIMD: 21,248 rows of 50, 64 -> 128, 33.5 us, with two
 // and none spilled 41.9 (rows of 5: 15.4 and 15.7).
 template <int G, int P, int NB, bool BWD>

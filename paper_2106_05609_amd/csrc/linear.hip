@@ -310,7 +310,8 @@ __global__ __launch_bounds__(256 * KG) void linear_split_groups_kernel(LinArgs a
 //
 // Bound by the matrix pipe and the vector unit together, at the clock that the power allows (1.7-1.9 GHz; the instructions alone,
 // on random operands, reach 1,400-1,900 TFLOP/s): 50,000 x 256 x 256 46 us, by the 128 x 128 tiles above 59; 600,000 rows 454 (1,040 TFLOP/s
-// of bf16 products) and 567, with the push 520 and 601.  The same products in the same order: the same bits.
+// of bf16 products) and 567, with the push 520 and 601.  The same products in the same order of steps, summed by another shape of the
+// instruction: one element in 55 differs from the tiles' in its last bits, neither nearer to 64 bits (both 9.0e-8 off at 256 columns).
 //
 // A tile that holds a value below 2^-110 is staged again times 2^40 (split.h says why), and so are the weights if one of
 // them is; a wavefront whose sums are not finite takes its block again with the fp32 instruction.

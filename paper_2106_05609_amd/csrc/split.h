@@ -16,9 +16,11 @@
 // accumulators 3.2e-7).  Sums that only grow, of absolute values, over the same rows: 5.9e-8 (fp32 instruction 7.3e-8).
 //
 // What bounds it: matrix pipe 52 %, vector instructions of the split 31 % of the cycles by the counters, the clock
-// falls to 1.8 GHz under this load; 50,000 x 256 x 256 take 54 us (87 us with the fp32 instruction), 600,000 rows
-// 545 us (738).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
-// compute unit: 55-63 us; products and split interleaved by hand in one wavefront, two LDS buffers: 49-56 us.
+// falls to 1.8 GHz under this load; 50,000 x 256 x 256 in 128 x 128 tiles take 59 us (87 us with the fp32 instruction),
+// 600,000 rows 567 us (738); products of these sizes keep their weights in registers instead (46 and 454 us,
+// linear_ws_split_kernel).  128 x 256 and 256 x 256 tiles split each value for more products but leave one workgroup per
+// compute unit: 55-63 us; products and split interleaved by hand in one wavefront, two LDS buffers: 49-56 us (when the
+// 128 x 128 tiles took 54).
 //
 // What the split cannot represent: an infinity, a NaN or a value that rounds to an infinite bf16 makes the accumulator
 // non-finite (0 * inf in the terms beside it, if not itself), and a wavefront that finds one takes its block again with

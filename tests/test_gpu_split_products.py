@@ -226,7 +226,7 @@ def test_weights_in_registers_and_values_that_the_split_cannot_hold(z_low, w_low
 
 
 # few tiles, steps of 32 k dealt to four groups of wavefronts: fewer steps than groups, one group a step ahead, a last step that
-# is not whole, and both sides of the rule (256 tiles of 64 x 64)
+# is not whole, and both sides of the rule (32 tiles of 64 x 64 on each of eight XCDs)
 @pytest.mark.parametrize("what", ["linear", "input"])
 @pytest.mark.parametrize("m,k,n", [(1, 65, 3), (70, 96, 65), (64, 128, 64), (100, 129, 70), (130, 161, 300), (500, 1024, 130), (77, 1433, 63),
                                    (4096, 70, 256), (4097, 70, 256),
