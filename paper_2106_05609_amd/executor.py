@@ -529,11 +529,11 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     backward pass read (x0, h0, per layer (Z, hidden, Y)).  Y_L owns its memory; kept activations of one width share an
     allocation (_matrices), so keeping one of them keeps those, and the weight gradients of a model of one width share one of
     the size of its weights (64 layers of 64 x 64: 1 MB; one by one they took 1.4 us of host time each).  grad_out is
-    dLoss/dY_L [nb, F_L], or a function that returns it given Y_L.  fused: the forward aggregations read their halo rows from the feature table / the
-    history tables in place (gas_spmm_hist) and nothing is pulled; same bits.  GCNII's first layer gathers the
-    projected features from the mini-batch tensor, its later layers from the histories.  Narrow fp32 layers of
-    GCN and GCNII then take one launch each (gas_spmm_linear with Z kept; the row sums are taken in another order,
-    so these agree with the other form to rounding, not bit for bit).  Every step is a gas_* call."""
+    dLoss/dY_L [nb, F_L], or a function that returns it given Y_L.  fused: the forward aggregations read their
+    halo rows from the feature table / the history tables in place (gas_spmm_hist) and nothing is pulled; same
+    bits.  GCNII's first layer gathers the projected features from the mini-batch tensor, its later layers from
+    the histories.  Narrow fp32 layers of GCN and GCNII then take one launch each (gas_spmm_linear with Z kept;
+    the row sums are taken in another order, so these agree with the other form to rounding, not bit for bit).  Every step is a gas_* call."""
     dev, dt = x_feat.device, x_feat.dtype
     nb, nv = bg.nb, bg.nv
     all_rows = not fused or model.op == "gcnii"      # GCNII projects the features of every node of V_b
