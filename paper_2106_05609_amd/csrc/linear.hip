@@ -1577,121 +1577,107 @@ __global__ __launch_bounds__(256, WPS) void dw_batch_split_kernel(DwBatch b) {
     dw_split_block<BK, BN>(a, blockIdx.x - b.first[i], smem);
 }
 
-// bf16: both operands need 8 consecutive rows per lane, so both tiles are transposed on the way into LDS
-// (the same 8 x 8 register transposition as for the weights of the forward kernel).
-__global__ __launch_bounds__(256) void dw_bf16_kernel(DwArgs a) {
-    __shared__ __attribute__((aligned(16))) uint16_t Zt[kDwTile][kLdh];     // [feature][row]
-    __shared__ __attribute__((aligned(16))) uint16_t Gt[kDwTile][kLdh];
+// bf16: both operands of an instruction need consecutive rows of one feature.  The rows lie in LDS as they come from memory and
+// are transposed on the way out (ds_read_b64_tr_b16: sixteen lanes read four rows of sixteen features, and a lane receives
+// one feature of the four rows), two buffers of 64 rows, the next rows in registers during the products: one barrier a step.
+// A workgroup of eight wavefronts owns a BK x BN tile of a slab's partial; with both widths at most 256 that is the whole
+// partial, and Z and G are read once.
+// Bounded by memory: 312,500 rows, 256 x 256: 384 MB with the slabs' partials in 79 us (4.9 TB/s; transposed on the way into
+// LDS, with one buffer, whose 16-byte stores met 16 to a bank, 110); 128 x 256, 304 MB, 69 us (in tiles of 128 x 128 81).
+// LDS: 16-byte unit u of row r lies at unit u ^ 4 (r & 3), so the 32 bytes that four lanes read of each of four rows, and the
+// neighbouring ones that the next sixteen lanes read, fall on banks of their own.
+constexpr int kDwRows = 64;
+template <int B> __device__ __forceinline__ int dw_lds_unit(int row, int unit) { return row * (B / 8) + (unit ^ (4 * (row & 3))); }
+
+template <int BK, int BN, int WK>
+__global__ __launch_bounds__(512) void dw_bf16_kernel(DwArgs a) {
+    constexpr int WN = 8 / WK, TK = BK / WK / 32, TN = BN / WN / 32;           // wavefronts, 32 x 32 blocks of one
+    constexpr int NZ = kDwRows * BK / 8 / 512, NG = kDwRows * BN / 8 / 512;    // 16-byte units a thread brings
+    typedef short s16x4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __attribute__((aligned(16))) char smem[];
+    uint16_t* lds = reinterpret_cast<uint16_t*>(smem);                         // [2][64 * BK, then 64 * BN]
     const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
     const uint16_t* G = reinterpret_cast<const uint16_t*>(a.G);
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-    const int slab = blockIdx.x, k0 = blockIdx.y * kDwTile, n0 = blockIdx.z * kDwTile;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int slab = blockIdx.x, k0 = blockIdx.y * BK, n0 = blockIdx.z * BN;
     const int64_t m_begin = (int64_t)slab * a.slab;
     const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
-    const int wk0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
-    f32x16 acc[2][2];
+    const int wk0 = (wave / WN) * (32 * TK), wn0 = (wave % WN) * (32 * TN);
+    f32x16 acc[TK][TN];
     zero_acc(acc);
-    // a 64(row) x 128(feature) tile is 8 x 16 blocks of 8 x 8: threads 0-127 take Z's, threads 128-255 G's
-    const bool mine_z = tid < 128;
-    const int t = tid & 127, rb = t / 16, fb = t % 16;
-    u32x4 r[8];
+    u32x4 rz[NZ], rg[NG];
+    // loads from clamped addresses, zeroed by a select: no branch around them
+    auto bring = [&](const uint16_t* src, int64_t ld, int64_t m0, int f0, int flim, int idx, int units) {
+        const int64_t m = m0 + idx / units;
+        const int f = f0 + 8 * (idx % units);
+        const bool ok = m < m_end && f < flim;
+        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ok ? src + m * ld + f : src));
+        return ok ? v : u32x4{0u, 0u, 0u, 0u};
+    };
     auto fetch = [&](int64_t m0) {
-        const uint16_t* src = mine_z ? Z : G;
-        const int64_t ld = mine_z ? a.ldz : a.ldg;
-        const int f = (mine_z ? k0 : n0) + 8 * fb, flim = mine_z ? a.K : a.N;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t m = m0 + 8 * rb + i;
-            r[i] = u32x4{0u, 0u, 0u, 0u};
-            if (m < m_end && f < flim) r[i] = *reinterpret_cast<const u32x4*>(src + m * ld + f);
+        for (int i = 0; i < NZ; ++i) rz[i] = bring(Z, a.ldz, m0, k0, a.K, tid + 512 * i, BK / 8);
+#pragma unroll
+        for (int i = 0; i < NG; ++i) rg[i] = bring(G, a.ldg, m0, n0, a.N, tid + 512 * i, BN / 8);
+    };
+    auto stage = [&](int buf) {
+        u32x4* zt = reinterpret_cast<u32x4*>(lds + buf * kDwRows * (BK + BN));
+        u32x4* gt = zt + kDwRows * BK / 8;
+#pragma unroll
+        for (int i = 0; i < NZ; ++i) zt[dw_lds_unit<BK>((tid + 512 * i) / (BK / 8), (tid + 512 * i) % (BK / 8))] = rz[i];
+#pragma unroll
+        for (int i = 0; i < NG; ++i) gt[dw_lds_unit<BN>((tid + 512 * i) / (BN / 8), (tid + 512 * i) % (BN / 8))] = rg[i];
+    };
+    // a lane's eight consecutive rows 16 kk + 8 lh .. + 7 of feature f0 + li, in two reads of four rows
+    const int i16 = lane & 15, feat = 16 * ((lane >> 4) & 1) + 4 * (i16 & 3);
+    auto fragment = [&](const uint16_t* tile, auto width, int f0, int kk) {
+        constexpr int B = decltype(width)::value;
+        s16x4 h[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const int row = 16 * kk + 8 * lh + 4 * t + (i16 >> 2), f = f0 + feat;
+            const uint16_t* p = tile + 8 * dw_lds_unit<B>(row, f >> 3) + (f & 7);
+            h[t] = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
         }
+        typedef short s16x8 __attribute__((ext_vector_type(8)));
+        return __builtin_bit_cast(bf16x8, s16x8{h[0][0], h[0][1], h[0][2], h[0][3], h[1][0], h[1][1], h[1][2], h[1][3]});
     };
     fetch(m_begin);
-    for (int64_t m0 = m_begin; m0 < m_end; m0 += kBKh) {
-        __syncthreads();
-        {
-            u32x4 tt[8];
-            transpose8x8_bf16(r, tt);
-            uint16_t (*dst)[kLdh] = mine_z ? Zt : Gt;
+    stage(0);
+    if (m_begin + kDwRows < m_end) fetch(m_begin + kDwRows);
+    int buf = 0;
+    for (int64_t m0 = m_begin; m0 < m_end; m0 += kDwRows, buf ^= 1) {
+        __syncthreads();                           // rows m0 .. staged; the other buffer's rows are done with
+        const uint16_t* zt = lds + buf * kDwRows * (BK + BN);
+        const uint16_t* gt = zt + kDwRows * BK;
 #pragma unroll
-            for (int c = 0; c < 8; ++c) *reinterpret_cast<u32x4*>(&dst[8 * fb + c][8 * rb]) = tt[c];
+        for (int kk = 0; kk < kDwRows / 16; ++kk) {
+            bf16x8 fa[TK], fb[TN];
+#pragma unroll
+            for (int i = 0; i < TK; ++i) fa[i] = fragment(zt, std::integral_constant<int, BK>{}, wk0 + 32 * i, kk);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[j] = fragment(gt, std::integral_constant<int, BN>{}, wn0 + 32 * j, kk);
+#pragma unroll
+            for (int i = 0; i < TK; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[i], fb[j], acc[i][j], 0, 0, 0);
         }
-        __syncthreads();
-        if (m0 + kBKh < m_end) fetch(m0 + kBKh);
-        mfma_tile_bf16<2, 2>(&Zt[0][0], kLdh, wk0, 0, Gt, wn0, li, lh, acc);
+        if (m0 + kDwRows < m_end) {
+            stage(buf ^ 1);
+            if (m0 + 2 * kDwRows < m_end) fetch(m0 + 2 * kDwRows);
+        }
     }
     float* out = a.partial + (int64_t)slab * a.K * a.N;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < TK; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < TN; ++j) {
             const int n = n0 + wn0 + 32 * j + li;
             if (n >= a.N) continue;
 #pragma unroll
             for (int rr = 0; rr < 16; ++rr) {
                 const int k = k0 + wk0 + 32 * i + 8 * (rr / 4) + 4 * lh + (rr % 4);
-                if (k < a.K) out[(int64_t)k * a.N + n] = acc[i][j][rr];
-            }
-        }
-}
-
-// bf16, both widths at most 256: one workgroup of eight wavefronts owns the whole [K][N] partial of its slab, so
-// Z and G are read once (the 128 x 128 kernel above reads each of them once per tile column / row).  Wavefront
-// (wk, wn) of a 4 x 2 arrangement accumulates rows 64 wk.. of dW and columns 128 wn..: eight 32 x 32 tiles.
-__global__ __launch_bounds__(512) void dw_bf16_wide_kernel(DwArgs a) {
-    extern __shared__ __attribute__((aligned(16))) char smem[];               // above the 64 KB static limit
-    uint16_t (*Zt)[kLdh] = reinterpret_cast<uint16_t (*)[kLdh]>(smem);        // [256 features][64 rows + pad]
-    uint16_t (*Gt)[kLdh] = Zt + 256;
-    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
-    const uint16_t* G = reinterpret_cast<const uint16_t*>(a.G);
-    const int tid = threadIdx.x, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int slab = blockIdx.x;
-    const int64_t m_begin = (int64_t)slab * a.slab;
-    const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
-    const int wk0 = (wave >> 1) * 64, wn0 = (wave & 1) * 128;
-    f32x16 acc[2][4];
-    zero_acc(acc);
-    // a 64(row) x 256(feature) tile is 8 x 32 blocks of 8 x 8: threads 0-255 take Z's, threads 256-511 G's
-    const bool mine_z = tid < 256;
-    const int t = tid & 255, rb = t / 32, fb = t % 32;
-    const uint16_t* src = mine_z ? Z : G;
-    const int64_t ld = mine_z ? a.ldz : a.ldg;
-    const int f = 8 * fb, flim = mine_z ? a.K : a.N;
-    u32x4 r[8];
-    auto fetch = [&](int64_t m0) {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const int64_t m = m0 + 8 * rb + i;
-            const bool ok = m < m_end && f < flim;
-            const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ok ? src + m * ld + f : src));
-            r[i] = ok ? v : u32x4{0u, 0u, 0u, 0u};
-        }
-    };
-    fetch(m_begin);
-    for (int64_t m0 = m_begin; m0 < m_end; m0 += kBKh) {
-        __syncthreads();
-        {
-            u32x4 tt[8];
-            transpose8x8_bf16(r, tt);
-            uint16_t (*dst)[kLdh] = mine_z ? Zt : Gt;
-#pragma unroll
-            for (int c = 0; c < 8; ++c) *reinterpret_cast<u32x4*>(&dst[8 * fb + c][8 * rb]) = tt[c];
-        }
-        __syncthreads();
-        if (m0 + kBKh < m_end) fetch(m0 + kBKh);
-        mfma_tile_bf16<2, 4>(&Zt[0][0], kLdh, wk0, 0, Gt, wn0, li, lh, acc);
-    }
-    float* out = a.partial + (int64_t)slab * a.K * a.N;
-#pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int n = wn0 + 32 * j + li;
-            if (n >= a.N) continue;
-#pragma unroll
-            for (int rr = 0; rr < 16; ++rr) {
-                const int k = wk0 + 32 * i + 8 * (rr / 4) + 4 * lh + (rr % 4);
                 if (k < a.K) out[(int64_t)k * a.N + n] = acc[i][j][rr];
             }
         }
@@ -1841,6 +1827,26 @@ gas_status launch_dw_blocks(int shape, int64_t blocks, const DwArgs* one, const 
 }
 gas_status launch_dw_split(int shape, int64_t n_slabs, const DwArgs& a, hipStream_t s) {
     return launch_dw_blocks(shape, dw_split_blocks(shape, n_slabs, a.K, a.N), &a, nullptr, s);
+}
+
+template <int BK, int BN, int WK>
+gas_status launch_dw_bf16_tile(const DwArgs& a, hipStream_t s) {
+    constexpr int smem = 2 * kDwRows * (BK + BN) * 2;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(dw_bf16_kernel<BK, BN, WK>),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    GAS_CHECK_HIP(attr);
+    const dim3 grid((unsigned)a.n_slabs, (unsigned)((a.K + BK - 1) / BK), (unsigned)((a.N + BN - 1) / BN));
+    hipLaunchKernelGGL((dw_bf16_kernel<BK, BN, WK>), grid, dim3(512), smem, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+
+// One tile for both widths up to 256; beyond, tiles of 128 x 128 (a 256-wide one would leave compute units without any).
+gas_status launch_dw_bf16(const DwArgs& a, hipStream_t s) {
+    if (a.K > 256 || a.N > 256 || (a.K <= 128 && a.N <= 128)) return launch_dw_bf16_tile<128, 128, 4>(a, s);
+    if (a.K <= 128) return launch_dw_bf16_tile<128, 256, 2>(a, s);
+    if (a.N <= 128) return launch_dw_bf16_tile<256, 128, 4>(a, s);
+    return launch_dw_bf16_tile<256, 256, 4>(a, s);
 }
 
 template <int KT, bool TRANS, bool MASK>
@@ -2090,20 +2096,14 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
                 (long long)gas_linear_bwd_weight_workspace(n_rows, F_in, F_out), (long long)workspace_bytes);
     const unsigned tk = (unsigned)((F_in + kDwTile - 1) / kDwTile), tn = (unsigned)((F_out + kDwTile - 1) / kDwTile);
     GAS_REQUIRE(tk <= 65535 && tn <= 65535, "gas_linear_bwd_weight: widths too large");
-    dim3 grid((unsigned)n_slabs, tk, tn);
     if (dt == GAS_F32) {
         const gas_status st = launch_dw_split(dw_shape(F_in, F_out), n_slabs, a, s);
         if (st != GAS_OK) return st;
     } else {
         const bool vec = aligned16(Z) && aligned16(GP) && ldz % 8 == 0 && ldgp % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
-        if (vec && F_in <= 256 && F_out <= 256 && F_in > 128 && F_out > 128) {
-            constexpr int smem = 2 * 256 * kLdh * 2;
-            static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(dw_bf16_wide_kernel),
-                                                               hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-            GAS_CHECK_HIP(attr);
-            hipLaunchKernelGGL(dw_bf16_wide_kernel, dim3((unsigned)n_slabs), dim3(512), smem, s, a);
-        } else if (vec) {
-            hipLaunchKernelGGL(dw_bf16_kernel, grid, dim3(256), 0, s, a);
+        if (vec) {
+            const gas_status st = launch_dw_bf16(a, s);
+            if (st != GAS_OK) return st;
         } else {
             const int64_t blocks = (per * n_slabs + 255) / 256;
             GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for the element-wise path");

@@ -242,3 +242,22 @@ def test_deep_and_narrow_backward_matches_oracle(op, widths, max_col, fused):
     assert set(grads) == set(want)
     for l in want:
         assert max_rel_err(to_np(grads[l]), want[l]) <= tol, (l, max_rel_err(to_np(grads[l]), want[l]))
+
+
+# one row, one 64-row step and its neighbours, more than one slab; widths of one tile, of each pair of tile widths, of neither's
+# whole, and beyond 256
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 129, 3000])
+@pytest.mark.parametrize("k,n", [(8, 8), (128, 136), (136, 128), (120, 128), (256, 256), (264, 40), (40, 520)])
+def test_bf16_weight_gradient_by_tiles(rows, k, n):
+    """Against 64 bits: the products of two bf16 values are exact in fp32, so every element is off by at most one rounding per
+    row and slab of its terms' magnitudes."""
+    import paper_2106_05609_amd as gas
+    gen = torch.Generator(device="cuda").manual_seed(rows + k)
+    z = torch.randn(rows, k + 8, generator=gen, device="cuda").bfloat16()[:, :k]
+    g = torch.randn(rows, n, generator=gen, device="cuda").bfloat16()
+    dw = torch.full((k, n), 9.0, device="cuda")
+    ws = torch.full((gas.gas_linear_bwd_weight_workspace(rows, k, n),), 255, dtype=torch.uint8, device="cuda")      # NaN
+    gas.gas_linear_bwd_weight(z, g, dw, ws, c_weight=0.5)
+    zd, gd = z.double().t().contiguous(), g.double()
+    bound = (rows + 64) * 2.0 ** -24 * 0.5 * (zd.abs() @ gd.abs())
+    assert ((dw.double() - 0.5 * (zd @ gd)).abs() <= bound).all()
