@@ -967,7 +967,7 @@ __device__ __forceinline__ void load_w_frags(const uint16_t* W, int K, int ncols
 // other way round).  Then a lane holds, for ONE row m of the tile, 4 groups of
 // 4 consecutive output columns, which go to the [m][n] LDS tiles as 8-byte
 // stores after a packed hardware fp32->bf16 conversion.
-template <int KT1>
+template <int KT1, bool MASK>
 __global__ __launch_bounds__(512) void ws_bf16_kernel(WsArgs a) {
     constexpr int LDA = 16 * KT1 + 8;                 // bf16 elements per LDS row of the Z tile
     constexpr int LDY = 256 + 8;                      // ... of the output staging tile
@@ -1052,6 +1052,18 @@ __global__ __launch_bounds__(512) void ws_bf16_kernel(WsArgs a) {
                 prow[i] = pi[row];
             }
         }
+        // the mask's rows are requested a product ahead of their use (312,500 rows, 256 x 256: 112 -> 98 us; asked for where
+        // they are used they wait for the next tile's rows as well)
+        u32x4 km[NPI];
+        if constexpr (MASK) {
+            const uint16_t* mbase = a.mask + tile * kWsRows * a.ldmask;
+#pragma unroll
+            for (int i = 0; i < NPI; ++i) {
+                const int row = (tid >> 5) + 16 * i, v = tid & 31;
+                const bool ok = v < (a.N >> 3) && (out_full || tile * kWsRows + row < a.M);
+                km[i] = *reinterpret_cast<const u32x4*>(mbase + (ok ? (uint32_t)row * (uint32_t)a.ldmask + 8u * v : 0u));
+            }
+        }
         const uint16_t* At = As + buf * kWsRows * LDA;
         f32x16 acc[MT];
 #pragma unroll
@@ -1088,10 +1100,14 @@ __global__ __launch_bounds__(512) void ws_bf16_kernel(WsArgs a) {
                 *reinterpret_cast<u32x2*>(Ys + (32 * t + li) * LDY + nbase + 8 * q) =
                     u32x2{pack_bf16(v[0], v[1]), pack_bf16(v[2], v[3])};
             }
-        // take delivery of the history slots before new loads are queued behind them: the stores below then
+        // take delivery of the history slots and of the mask before new loads are queued behind them: the stores below then
         // need no wait that the loads just issued would have to satisfy first
 #pragma unroll
         for (int i = 0; i < NPI; ++i) asm volatile("" : "+v"(prow[i]));
+        if constexpr (MASK) {
+#pragma unroll
+            for (int i = 0; i < NPI; ++i) asm volatile("" : "+v"(km[i]));
+        }
         if (next < a.n_tiles) {
             stage(buf ^ 1, next);                      // the other buffer: nobody reads it before the next (1)
             if (next + gridDim.x < a.n_tiles) fetch(next + gridDim.x);
@@ -1100,7 +1116,6 @@ __global__ __launch_bounds__(512) void ws_bf16_kernel(WsArgs a) {
         {
             const int vpr = a.N >> 3;                  // 16-byte vectors per output row
             uint16_t* ybase = a.Y + tile * kWsRows * a.ldy;
-            const uint16_t* mbase = a.mask ? a.mask + tile * kWsRows * a.ldmask : nullptr;
             const int v = tid & 31;
             if (v < vpr) {
 #pragma unroll
@@ -1108,12 +1123,11 @@ __global__ __launch_bounds__(512) void ws_bf16_kernel(WsArgs a) {
                     const int row = (tid >> 5) + 16 * i;
                     if (out_full || tile * kWsRows + row < a.M) {
                         u32x4 o = *reinterpret_cast<const u32x4*>(Ys + row * LDY + 8 * v);
-                        if (mbase) {
-                            const u32x4 km = *reinterpret_cast<const u32x4*>(mbase + ((uint32_t)row * (uint32_t)a.ldmask + 8u * v));
+                        if constexpr (MASK) {
 #pragma unroll
                             for (int q = 0; q < 4; ++q) {
-                                if (!(bf16_lo(km[q]) > 0.f)) o[q] &= 0xFFFF0000u;
-                                if (!(bf16_hi(km[q]) > 0.f)) o[q] &= 0x0000FFFFu;
+                                if (!(bf16_lo(km[i][q]) > 0.f)) o[q] &= 0xFFFF0000u;
+                                if (!(bf16_hi(km[i][q]) > 0.f)) o[q] &= 0x0000FFFFu;
                             }
                         }
                         __builtin_nontemporal_store(
@@ -1391,10 +1405,10 @@ gas_status launch_ws_mlp(const WsArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
-template <int KT1>
-gas_status launch_ws(const WsArgs& a, hipStream_t s) {
+template <int KT1, bool MASK>
+gas_status launch_ws_kernel(const WsArgs& a, hipStream_t s) {
     constexpr int smem = 2 * (2 * kWsRows * (16 * KT1 + 8) + kWsRows * (256 + 8)) + 256 * 4;   // + the bias in fp32
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(ws_bf16_kernel<KT1>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(ws_bf16_kernel<KT1, MASK>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     GAS_CHECK_HIP(attr);
     int dev = 0, cus = 256;
@@ -1403,10 +1417,12 @@ gas_status launch_ws(const WsArgs& a, hipStream_t s) {
         if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && v > 0) cus = v;
     }
     const int64_t blocks = a.n_tiles < cus ? a.n_tiles : cus;
-    hipLaunchKernelGGL((ws_bf16_kernel<KT1>), dim3((unsigned)blocks), dim3(512), smem, s, a);
+    hipLaunchKernelGGL((ws_bf16_kernel<KT1, MASK>), dim3((unsigned)blocks), dim3(512), smem, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
+template <int KT1>
+gas_status launch_ws(const WsArgs& a, hipStream_t s) { return a.mask ? launch_ws_kernel<KT1, true>(a, s) : launch_ws_kernel<KT1, false>(a, s); }
 
 // ====================================================================== element-wise paths
 // For bf16 operands that are not 16-byte aligned (odd widths, odd strides):
