@@ -195,6 +195,16 @@ GAS_API gas_status gas_spmm_hist(const gas_plan* plan, const int32_t* rowptr, co
                          void* Z, int64_t ldz, gas_dtype dt_z, void* stream);
 
 /*
+ * gas_spmm_hist for rows that all lie in ONE table (the first layer, whose inputs are rows of the feature table): src[k] < 0
+ * names row -1-src[k] of `table` (gas_fuse_sources with nb = 0), and the diagonal term of row v reads row own[v]
+ * (int32[n_rows]; may be NULL where diag == 0).  Same bits as gas_pull of the rows
+ * (to a matrix whose rows are aligned as the table's are) followed by gas_spmm, no copy.
+ */
+GAS_API gas_status gas_spmm_table(const gas_plan* plan, const int32_t* rowptr, const int32_t* src, const float* val, float diag,
+                          const int32_t* own, const void* table, int64_t n_table_rows, int64_t ld_table, gas_dtype dt_x,
+                          int32_t F, float s_agg, void* Z, int64_t ldz, gas_dtype dt_z, void* stream);
+
+/*
  * Source indices for gas_spmm_hist from the local column ids of a batch
  * subgraph: src[k] = col[k] if col[k] < nb (in-batch), else -1 - n_id[col[k]]
  * (global id of the halo node, i.e. its row in every history table).  Done

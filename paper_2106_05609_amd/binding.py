@@ -15,7 +15,7 @@ OK = 0
 EXPORTS = [
     "gas_last_error", "gas_version", "gas_validate_indices",
     "gas_pull", "gas_push", "gas_host_table_pointer", "gas_pull_host", "gas_push_host",
-    "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
+    "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_spmm_table", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
     "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear", "gas_spmm_t_relu_linear",
     "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace",
     "gas_linear_bwd_weight_static", "gas_linear_bwd_weights", "gas_linear_bwd_weights_workspace",
@@ -64,7 +64,7 @@ _SIGNATURES = dict(
     gas_validate_indices="pqqp", gas_pull="pqqpqqiipqp", gas_push="pqpqqiipqqp", gas_host_table_pointer="pp",
     gas_pull_host="pqqpqqiipqp", gas_push_host="pqpqqiipqqp", gas_gcn_norm="ppqpppp", gas_plan_create_opt="ppqqippp",
     gas_plan_describe="pp", gas_plan_copy_lists="ppppp", gas_spmm="ppppfpqiifpqfpqip",
-    gas_spmm_hist="ppppfpqpqqiifpqfpqip", gas_fuse_sources="pqqppp", gas_spmm_t="ppppffqpqiipqip",
+    gas_spmm_hist="ppppfpqpqqiifpqfpqip", gas_spmm_table="ppppfppqqiifpqip", gas_fuse_sources="pqqppp", gas_spmm_t="ppppffqpqiipqip",
     gas_spmm_t_relu="ppppffqpqiipqpqp", gas_linear_bwd_input_add="pqqipiiffpqpqfpqpqp", gas_sgd_steps="ippipffp",
     gas_linear="pqqipipiffipqp", gas_mlp2="pqqipippipiipqp", gas_linear_push="pqqipipiffipqppqqp",
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
@@ -276,6 +276,17 @@ def gas_spmm_hist(plan, rowptr, src, val, x, hist, z, diag=0.0, s_agg=1.0, r=Non
                                diag, xp, ldx, hp, hist.shape[0], ldh, _dt(x),
                                x.shape[1], s_agg, rp, ldr, s_res, zp, ldz,
                                _dt(z), _stream()))
+
+
+def gas_spmm_table(plan, rowptr, src, val, table, z, diag=0.0, s_agg=1.0, own=None):
+    """Every row is one of the table's: an entry's -1 - src, the diagonal term's own[v]."""
+    tp, ldt = _mat(table)
+    zp, ldz = _mat(z)
+    if z.shape[1] != table.shape[1] or z.shape[0] < plan.n_rows or (own is not None and own.numel() < plan.n_rows):
+        raise ValueError("gas_spmm_table: shapes do not match")
+    _check(_calls().gas_spmm_table(plan.handle, _ptr(rowptr, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32), diag,
+                                _ptr(own, torch.int32), tp, table.shape[0], ldt, _dt(table), table.shape[1], s_agg, zp, ldz,
+                                _dt(z), _stream()))
 
 
 def gas_spmm_t(plan, colptr, row, val, g, gx, diag=0.0, s_agg=1.0):

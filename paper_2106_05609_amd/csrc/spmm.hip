@@ -48,6 +48,7 @@ struct SpmmArgs {
     int64_t y_stride;
     char* Z;
     int64_t z_stride;
+    const int32_t* own;   // the diagonal term's rows: row own[v] of H, or (null) row v of X
     float diag, s_agg, s_res;
     int64_t n_rows, n_diag;
     int units;            // 16-byte units per row of X, the last one may overlap its neighbour
@@ -64,6 +65,10 @@ struct SpmmArgs {
     int64_t xcd_start[9];
     int slices;           // rows of 512 or 1,024 bytes: 0 whole, 1 or 2 by slices of so many times 256 bytes
 };
+
+__device__ __forceinline__ const char* own_row(const SpmmArgs& a, int64_t row) {
+    return a.own ? a.H + (int64_t)a.own[row] * a.h_stride : a.X + row * a.x_stride;
+}
 
 template <bool XBF>
 struct Unit {
@@ -181,7 +186,7 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
         float t[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) t[e] = 0.f;
-        Unit<XBF>::fma(t, a.diag, load_unit<XBF>(a.X + row * a.x_stride + start * EB));
+        Unit<XBF>::fma(t, a.diag, load_unit<XBF>(own_row(a, row) + start * EB));
 #pragma unroll
         for (int e = 0; e < E; ++e) z[e] += t[e];
     }
@@ -320,6 +325,7 @@ __device__ __forceinline__ void light_group(const SpmmArgs& a, int64_t g) {
     const int my_ptr = lane <= nrows ? a.ptr[r0 + lane] : 0;
     const int e0 = __builtin_amdgcn_readlane(my_ptr, 0);
     const int e1 = __builtin_amdgcn_readlane(my_ptr, nrows);
+    const int my_own = a.own && lane < nrows ? a.own[r0 + lane] : 0;
     const char* xb = a.X + (int64_t)lane * VB;
     const char* hb = a.H + (int64_t)lane * VB;
     LaneAcc<VB, XBF> acc;
@@ -335,7 +341,8 @@ __device__ __forceinline__ void light_group(const SpmmArgs& a, int64_t g) {
     auto load_own = [&](int rr) -> V {
         V v{};
         const int64_t row = (int64_t)r0 + rr;
-        if (use_diag && rr < nrows && row < a.n_diag) v = *reinterpret_cast<const V*>(xb + row * a.x_stride);
+        if (use_diag && rr < nrows && row < a.n_diag)
+            v = *reinterpret_cast<const V*>(a.own ? hb + (int64_t)__builtin_amdgcn_readlane(my_own, rr) * a.h_stride : xb + row * a.x_stride);
         return v;
     };
 #pragma unroll
@@ -526,15 +533,15 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
         }
     };
     if (b < e) fetch(b);
-    auto piece = [&](const char* base, int64_t stride, u32x4 (&t)[P]) {
+    auto piece = [&](const char* base, u32x4 (&t)[P]) {
 #pragma unroll
-        for (int p = 0; p < P; ++p) t[p] = *reinterpret_cast<const u32x4*>(base + row * stride + off + 16 * G * p);
+        for (int p = 0; p < P; ++p) t[p] = *reinterpret_cast<const u32x4*>(base + off + 16 * G * p);
     };
     u32x4 own[P], res[P], act[P];
     const bool use_own = a.diag != 0.f && row < a.n_diag;
-    if (use_own) piece(a.X, a.x_stride, own);
-    if (a.R) piece(a.R, a.r_stride, res);
-    if constexpr (MASK) piece(a.Y, a.y_stride, act);
+    if (use_own) piece(own_row(a, row), own);
+    if (a.R) piece(a.R + row * a.r_stride, res);
+    if constexpr (MASK) piece(a.Y + row * a.y_stride, act);
     float acc[P][E];
 #pragma unroll
     for (int p = 0; p < P; ++p)
@@ -683,7 +690,7 @@ __global__ __launch_bounds__(256) void spmm_generic_kernel(SpmmArgs a) {
             acc = fmaf(a.val ? a.val[k] : 1.f, x, acc);
         }
         float z = a.s_agg * acc;
-        if (a.diag != 0.f && row < a.n_diag) z += a.diag * ld(a.X, a.x_stride, row, f);
+        if (a.diag != 0.f && row < a.n_diag) z += a.diag * ld(own_row(a, row), 0, 0, f);
         if (a.R) z += a.s_res * ld(a.R, a.r_stride, row, f);
         if (a.Y && !(ld(a.Y, a.y_stride, row, f) > 0.f)) z = 0.f;
         if constexpr (ZBF) *reinterpret_cast<uint16_t*>(a.Z + row * a.z_stride + 2 * f) = (uint16_t)f32_to_bf16(z);
@@ -776,7 +783,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
                     float diag, int64_t n_diag, const void* X, int64_t ldx, const void* H, int64_t ldh,
                     gas_dtype dt_x, int32_t F, float s_agg,
                     const void* R, int64_t ldr, float s_res, void* Z, int64_t ldz, gas_dtype dt_z, hipStream_t s,
-                    const void* Y = nullptr, int64_t ldy = 0) {
+                    const void* Y = nullptr, int64_t ldy = 0, const int32_t* own = nullptr) {
     if (!valid_dtype(dt_x) || !valid_dtype(dt_z)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype", who);
     if (dt_x == GAS_F32 && dt_z == GAS_BF16)
         return fail(GAS_ERR_DTYPE, "%s: fp32 input with bf16 output is not supported", who);
@@ -799,7 +806,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
                                            ldx, H ? static_cast<const char*>(H) + f0 * xb : nullptr, ldh, dt_x, fw, s_agg,
                                            R ? static_cast<const char*>(R) + f0 * xb : nullptr, ldr, s_res,
                                            static_cast<char*>(Z) + f0 * zb, ldz, dt_z, s,
-                                           Y ? static_cast<const char*>(Y) + f0 * xb : nullptr, ldy);
+                                           Y ? static_cast<const char*>(Y) + f0 * xb : nullptr, ldy, own);
             if (st != GAS_OK) return st;
         }
         return GAS_OK;
@@ -811,7 +818,7 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.R = static_cast<const char*>(R); a.r_stride = ldr * xb;
     a.Y = static_cast<const char*>(Y); a.y_stride = ldy * xb;
     a.Z = static_cast<char*>(Z); a.z_stride = ldz * zb;
-    a.diag = diag; a.s_agg = s_agg; a.s_res = s_res;
+    a.own = own; a.diag = diag; a.s_agg = s_agg; a.s_res = s_res;
     a.n_rows = plan->n_rows; a.n_diag = n_diag;
     a.units = (F * xb + 15) / 16; a.F = F;
     a.threshold = plan->threshold;
@@ -906,6 +913,15 @@ gas_status gas_spmm_hist(const gas_plan* plan, const int32_t* rowptr, const int3
     GAS_REQUIRE(Z != hist, "gas_spmm_hist: output aliases the history table");
     return run_spmm("gas_spmm_hist", plan, rowptr, src, val, diag, plan ? plan->n_rows : 0, X, ldx, hist, ld_hist,
                     dt_x, F, s_agg, R, ldr, s_res, Z, ldz, dt_z, (hipStream_t)stream);
+}
+
+gas_status gas_spmm_table(const gas_plan* plan, const int32_t* rowptr, const int32_t* src, const float* val, float diag,
+                          const int32_t* own, const void* table, int64_t n_table_rows, int64_t ld_table, gas_dtype dt_x, int32_t F,
+                          float s_agg, void* Z, int64_t ldz, gas_dtype dt_z, void* stream) {
+    GAS_REQUIRE(table && n_table_rows > 0, "gas_spmm_table: null or empty table");
+    GAS_REQUIRE(diag == 0.f || own, "gas_spmm_table: the diagonal term needs the rows' ids");
+    return run_spmm("gas_spmm_table", plan, rowptr, src, val, diag, plan ? plan->n_rows : 0, table, ld_table, table, ld_table, dt_x, F,
+                    s_agg, nullptr, 0, 0.f, Z, ldz, dt_z, (hipStream_t)stream, nullptr, 0, own);
 }
 
 gas_status gas_fuse_sources(const int32_t* col, int64_t nnz, int64_t nb, const int32_t* n_id, int32_t* src,

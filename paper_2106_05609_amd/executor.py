@@ -48,7 +48,7 @@ class BatchGraph:
         if normalise:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
             part("gcn_norm_csr", lambda: B.gas_gcn_norm(rowptr, col, n_id, deg, self.val))
-        self._src = None
+        self._src = self._src_first = None
         self.csc_pos = csc_pos       # int32[nnz]: position of every CSC entry in the CSR arrays (PNA / GAT backward)
         self._n_id_host = None
         self._plan_t_all, self._max_F = None, max_F
@@ -85,11 +85,19 @@ class BatchGraph:
 
     @property
     def src(self):
-        """Source indices for gas_spmm_hist (built on first use, once per batch)."""
+        """Source indices for gas_spmm_hist (built on first use, once per batch, together with the first layer's)."""
         if self._src is None:
-            self._src = torch.empty_like(self.col)
-            B.gas_fuse_sources(self.col, self.nb, self.n_id, self._src)
+            src, first = torch.empty_like(self.col), torch.empty_like(self.col)
+            B.gas_fuse_sources(self.col, self.nb, self.n_id, src)
+            B.gas_fuse_sources(self.col, 0, self.n_id, first)
+            self._src, self._src_first = src, first
         return self._src
+
+    @property
+    def src_first(self):
+        """Source indices of a first layer that reads the feature table in place (gas_spmm_table)."""
+        self.src
+        return self._src_first
 
 
 class Model:
@@ -211,7 +219,8 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
     aggregation (gas_spmm_hist) instead of being pulled into the mini-batch
     tensor, and the Push taken in the transform's epilogue: per layer
     aggregate(X_batch, H[l-1]) -> transform, rows stored to H[l] as well.
-    Layer 1 reads its halo rows from the feature table the same way.  GCNII: its first layer aggregates the
+    Layer 1 reads all its rows from the feature table in place (gas_spmm_table: no copy of the in-batch rows; 5,000 rows of
+    1,433 floats 22 us, of 512 rows a launch of three).  GCNII: its first layer aggregates the
     projected features of all of V_b, which no table holds, so that layer gathers from the mini-batch tensor; from
     layer 2 on the halo rows come from the history tables in place.  Narrow fp32 layers of GCN and GCNII (widths
     up to 128, no row above ONE_LAUNCH_MAX_ROW entries) take one launch each (gas_spmm_linear)."""
@@ -220,8 +229,7 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
     if model.op == "gcnii":
         return _forward_gcnii_fused(model, bg, x_feat, histories, do_push)
     ids = bg.n_id[:nb]
-    x = torch.empty((nb, x_feat.shape[1]), dtype=dt, device=dev)
-    B.gas_pull(x_feat, ids, x)
+    x = x_feat
     L = model.n_layers
     y = None
     for l in range(1, L + 1):
@@ -231,19 +239,24 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
         push = not last and do_push          # the transform stores its rows to the next history table as well
         if model.op == "gcn" and B.spmm_linear_supported(x, y.shape[1]) and bg.max_row <= ONE_LAUNCH_MAX_ROW:
             # narrow layers: aggregation, transform and Push in one launch
-            B.gas_spmm_linear(bg.rowptr, bg.src, bg.val, x, model.weights[l - 1], y, hist=table, relu=not last,
-                              push_idx=ids if push else None, push_hist=histories[l - 1] if push else None)
+            B.gas_spmm_linear(bg.rowptr, bg.src_first if l == 1 else bg.src, bg.val, x, model.weights[l - 1], y, hist=table,
+                              relu=not last, push_idx=ids if push else None, push_hist=histories[l - 1] if push else None)
             x = y
             continue
         z = torch.empty((nb, x.shape[1]), dtype=dt, device=dev)
-        if model.op == "gcn":
+        if l == 1:
+            B.gas_spmm_table(bg.plan, bg.rowptr, bg.src_first, bg.val if model.op == "gcn" else None, table, z,
+                             diag=0.0 if model.op == "gcn" else 1.0 + model.gin_eps, own=bg.n_id)
+        elif model.op == "gcn":
             B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, bg.val, x, table, z)
+        else:
+            B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, None, x, table, z, diag=1.0 + model.gin_eps)
+        if model.op == "gcn":
             if push:
                 B.gas_linear_push(z, model.weights[l - 1], y, ids, histories[l - 1], relu=True)
             else:
                 B.gas_linear(z, model.weights[l - 1], y, relu=not last)
         else:
-            B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, None, x, table, z, diag=1.0 + model.gin_eps)
             w1, w2 = model.weights[l - 1]
             if _mlp_in_two(z, w1, w2):
                 h = torch.empty((nb, w1.shape[1]), dtype=dt, device=dev)
@@ -534,12 +547,21 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
     bits.  GCNII's first layer gathers the projected features from the mini-batch tensor, its later layers from
     the histories.  Narrow fp32 layers of GCN and GCNII then take one launch each (gas_spmm_linear with Z kept;
     the row sums are taken in another order, so these agree with the other form to rounding, not bit for bit).  Every step is a gas_* call."""
+    return _train_batch(model, bg, x_feat, histories, grad_out, do_push, fused, keep_input=True)
+
+
+def _train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_push, fused, keep_input):
+    """train_batch; keep_input False: a fused GCN, whose backward pass does not read its input, aggregates the feature
+    table in place and returns no x0."""
     dev, dt = x_feat.device, x_feat.dtype
     nb, nv = bg.nb, bg.nv
     all_rows = not fused or model.op == "gcnii"      # GCNII projects the features of every node of V_b
-    x0 = torch.empty((nv if all_rows else nb, x_feat.shape[1]), dtype=dt, device=dev)
-    B.gas_pull(x_feat, bg.n_id if all_rows else bg.n_id[:nb], x0)
-    x, h0 = x0, None
+    in_place = fused and model.op == "gcn" and not keep_input
+    x0 = None
+    if not in_place:
+        x0 = torch.empty((nv if all_rows else nb, x_feat.shape[1]), dtype=dt, device=dev)
+        B.gas_pull(x_feat, bg.n_id if all_rows else bg.n_id[:nb], x0)
+    x, h0 = x_feat if in_place else x0, None
     if model.op == "gcnii":
         h0 = torch.empty((nv, model.w_in.shape[1]), dtype=dt, device=dev)
         B.gas_linear(x0, model.w_in, h0, relu=True)
@@ -569,16 +591,18 @@ def train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_pu
             beta = betas[l - 1]
             kw = dict(s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha, c_identity=1.0 - beta,
                       c_weight=beta) if model.op == "gcnii" else {}
-            B.gas_spmm_linear(bg.rowptr, bg.col if table is None else bg.src, bg.val, x, model.weights[l - 1], y,
-                              hist=table, relu=not last, z_out=z, push_idx=ids if push else None,
-                              push_hist=histories[l - 1] if push else None, **kw)
+            src = bg.col if table is None else bg.src_first if in_place and l == 1 else bg.src
+            B.gas_spmm_linear(bg.rowptr, src, bg.val, x, model.weights[l - 1], y, hist=table, relu=not last, z_out=z,
+                              push_idx=ids if push else None, push_hist=histories[l - 1] if push else None, **kw)
             saved.append((z, h, y))
             if last:
                 break
             x = x_next
             continue
         if model.op == "gcn":
-            if fused:
+            if in_place and l == 1:
+                B.gas_spmm_table(bg.plan, bg.rowptr, bg.src_first, bg.val, table, z)
+            elif fused:
                 B.gas_spmm_hist(bg.plan, bg.rowptr, bg.src, bg.val, x, table, z)
             else:
                 B.gas_spmm(bg.plan, bg.rowptr, bg.col, bg.val, x, z)
@@ -765,7 +789,7 @@ def train_step(model: Model, bg: BatchGraph, x_feat, histories, labels_batch, lr
         g = torch.empty_like(y)
         B.gas_softmax_xent(y, labels_batch, g, loss_rows, loss_sum, scale=1.0 / max(1, n_labelled))
         return g
-    y, grads, kept = train_batch(model, bg, x_feat, histories, loss_grad, fused=fused)
+    y, grads, kept = _train_batch(model, bg, x_feat, histories, loss_grad, True, fused, keep_input=False)
     if reg_weight != 0.0:
         # loss + reg_weight * sum over the layers of Eq. (3), each differentiated with respect to its layer's
         # weights; reg_eps[l-1]: layer l's drawn perturbations [nv, F_in]
