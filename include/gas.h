@@ -347,6 +347,31 @@ GAS_API gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* 
                            float c_total, void* total, int64_t ldtotal, void* GZ, int64_t ldgz, void* stream);
 
 /*
+ * `count` consecutive layers of one width (gas_spmm_linear with F_in == F_out == F) and their counterparts in the backward pass
+ * (gas_spmm_t_relu_linear): layer l reads what layer l - 1 wrote (l = 0: X, backward G).  Same bits as one call per layer.
+ * The arrays hist, W, Y, ... are HOST arrays of `count` device pointers, c_identity and c_weight of `count` floats, ld_hist and
+ * ld_push of `count` row strides; they are read before the call returns.  hist[l] may be NULL where the layer's indices name no stored row; Z_out, push_idx with
+ * push_hist, and any element of Z_out or push_hist, may be NULL (nothing is kept, nothing is pushed).  The first layer may have
+ * indices of its own (src_first; else pass src).  Layers but the last apply ReLU, the last as relu_last says.
+ * Y[l] may be written again from layer l + 2 on (two matrices in turn serve a forward pass; the same for GZ), otherwise no
+ * output may alias another matrix of the call.
+ * One call for a deep narrow model, whose layers take the card less time than a call through a binding takes the host.
+ * Restrictions as for the single calls; every layer is checked before anything is launched.
+ */
+GAS_API gas_status gas_spmm_linear_layers(int32_t count, const int32_t* rowptr, const int32_t* src_first, const int32_t* src,
+                           const float* val, int64_t n_rows, const void* X, int64_t ldx, const void* const* hist,
+                           int64_t n_hist_rows, const int64_t* ld_hist, gas_dtype dt, int32_t F, float s_agg, const void* R,
+                           int64_t ldr, float s_res, const void* const* W, const float* c_identity, const float* c_weight,
+                           int relu_last, void* const* Y, int64_t ldy, void* const* Z_out, int64_t ldz_out,
+                           const int32_t* push_idx, void* const* push_hist, int64_t n_push_rows,
+                           const int64_t* ld_push, void* stream);
+GAS_API gas_status gas_spmm_t_relu_linear_layers(int32_t count, const int32_t* colptr, const int32_t* row, const float* val,
+                           int64_t n_cols, const void* G, int64_t ldg, gas_dtype dt, int32_t F, float s_agg,
+                           const void* const* Y, int64_t ldy, void* const* GX, int64_t ldgx, const void* const* W,
+                           const float* c_identity, const float* c_weight, float c_total, void* total, int64_t ldtotal,
+                           void* const* GZ, int64_t ldgz, void* stream);
+
+/*
  * Backward pass of the transform (chain rule on the operator equations; the
  * paper takes gradients through its layers, Section 2 advantage (1), without
  * spelling them out).  With P = c_identity * Z + c_weight * (Z W) and Y = relu(P):

@@ -17,6 +17,7 @@ EXPORTS = [
     "gas_pull", "gas_push", "gas_host_table_pointer", "gas_pull_host", "gas_push_host",
     "gas_gcn_norm", "gas_plan_create", "gas_plan_create_opt", "gas_plan_destroy", "gas_plan_describe", "gas_plan_copy_lists", "gas_spmm", "gas_spmm_hist", "gas_spmm_table", "gas_fuse_sources", "gas_spmm_t", "gas_spmm_t_relu",
     "gas_linear", "gas_mlp2", "gas_linear_push", "gas_mlp2_push", "gas_mlp2_keep", "gas_spmm_linear", "gas_spmm_t_relu_linear",
+    "gas_spmm_linear_layers", "gas_spmm_t_relu_linear_layers",
     "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace",
     "gas_linear_bwd_weight_static", "gas_linear_bwd_weights", "gas_linear_bwd_weights_workspace",
     "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
@@ -70,6 +71,7 @@ _SIGNATURES = dict(
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
     gas_spmm_linear="pppqpqpqqiiffpqfpipffipqpqppqqp", gas_relu_bwd="pqpqqiipqp", gas_linear_bwd_input="pqqipiiffpqpqp",
     gas_spmm_t_relu_linear="pppqpqiifpqpqpifffpqpqp",
+    gas_spmm_linear_layers="ippppqpqpqpiifpqfpppipqpqppqpp", gas_spmm_t_relu_linear_layers="ipppqpqiifpqpqpppfpqpqp",
     gas_linear_bwd_weights_workspace="ipppi", gas_linear_bwd_weights="ipppppppipppqp",
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
@@ -521,6 +523,79 @@ def gas_spmm_t_relu_linear(colptr, row, val, g, y, gx, w, gz, s_agg=1.0, c_ident
         ldx, _ptr(w), f_below, c_identity, c_weight, c_total, tp, ldt, zp, ldz, _stream()))
 
 
+def _pointers(mats, n, shape, like, what, null=False):
+    """(pointers, row strides) of `n` matrices of one shape and type (None: a null pointer, where allowed)."""
+    if len(mats) != n:
+        raise ValueError(f"{what}: {len(mats)} matrices for {n} layers")
+    ptrs, lds = [], []
+    for t in mats:
+        if t is None and null:
+            ptrs.append(None)
+            lds.append(0)
+            continue
+        size, step = t.shape, t.stride()                     # as _mat, with few calls: there are hundreds of matrices
+        if len(size) != 2 or size[1] != shape[1] or size[0] < shape[0] or t.dtype != like or (step[1] != 1 and size[1] > 1):
+            raise ValueError(f"{what}: shapes, dtypes or strides do not match")
+        ptrs.append(t.data_ptr())
+        lds.append(step[0] if size[0] > 1 else max(step[0], size[1]))
+    return (C.c_void_p * n)(*ptrs), lds
+
+
+def _one_stride(lds, what):
+    if any(ld != lds[0] for ld in lds):
+        raise ValueError(f"{what}: row strides do not match")
+    return lds[0]
+
+
+def gas_spmm_linear_layers(rowptr, src_first, src, val, x, ws, ys, hists, s_agg=1.0, r=None, s_res=0.0,
+                           c_identity=None, c_weight=None, relu_last=False, z_outs=None, push_idx=None, push_hists=None):
+    """gas_spmm_linear of len(ws) layers of one width, each reading the one before: lists of weights, outputs (of one row stride;
+    an output may come again from the layer after next on), history tables and, optionally, kept aggregated rows and tables to
+    push to (None: none)."""
+    n, (n_rows, f) = len(ws), ys[0].shape
+    xp, ldx = _mat(x)
+    rp, ldr = (0, 0) if r is None else _mat(r)
+    wp, _ = _pointers(ws, n, (f, f), x.dtype, "gas_spmm_linear_layers: weights")
+    yp, ldy = _pointers(ys, n, (n_rows, f), x.dtype, "gas_spmm_linear_layers: outputs")
+    hp, lds_h = _pointers(hists, n, (0, f), x.dtype, "gas_spmm_linear_layers: histories", null=True)
+    zp, ldz = (None, [0]) if z_outs is None else _pointers(z_outs, n, (n_rows, f), x.dtype, "gas_spmm_linear_layers: kept rows")
+    pp, lds_p = (None, []) if push_hists is None else _pointers(push_hists, n, (0, f), x.dtype, "gas_spmm_linear_layers: tables", null=True)
+    if x.shape[1] != f or rowptr.numel() != n_rows + 1 or not all(w.is_contiguous() for w in ws) or \
+            (r is not None and (r.dtype != x.dtype or r.shape[1] != f or r.shape[0] < n_rows)) or \
+            (push_idx is None) != (push_hists is None) or (push_idx is not None and push_idx.numel() != n_rows):
+        raise ValueError("gas_spmm_linear_layers: shapes or dtypes do not match")
+    floats, longs = C.c_float * n, C.c_int64 * n
+    n_hist_rows = min((t.shape[0] for t in hists if t is not None), default=0)
+    n_push_rows = min((t.shape[0] for t in push_hists or () if t is not None), default=0)
+    ldy, ldz = _one_stride(ldy, "gas_spmm_linear_layers: outputs"), _one_stride(ldz, "gas_spmm_linear_layers: kept rows")
+    _check(_calls().gas_spmm_linear_layers(
+        n, _ptr(rowptr, torch.int32), _ptr(src_first, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32), n_rows, xp, ldx,
+        hp, n_hist_rows, longs(*lds_h), _dt(x), f, s_agg, rp, ldr, s_res, wp, floats(*(c_identity or [0.0] * n)),
+        floats(*(c_weight or [1.0] * n)), int(relu_last), yp, ldy, zp, ldz, _ptr(push_idx, torch.int32), pp, n_push_rows,
+        longs(*lds_p), _stream()))
+
+
+def gas_spmm_t_relu_linear_layers(colptr, row, val, g, ys, gxs, ws, gzs, s_agg=1.0, c_identity=None, c_weight=None, total=None,
+                                  c_total=0.0):
+    """gas_spmm_t_relu_linear of len(ws) layers of one width, from the top one down, each reading the gz of the one before."""
+    n, (n_rows, f) = len(ws), gxs[0].shape
+    a, lda = _mat(g)
+    tp, ldt = (0, 0) if total is None else _mat(total)
+    what = "gas_spmm_t_relu_linear_layers"
+    yp, ldy = _pointers(ys, n, (n_rows, f), g.dtype, what)
+    xp, ldx = _pointers(gxs, n, (n_rows, f), g.dtype, what)
+    wp, _ = _pointers(ws, n, (f, f), g.dtype, what)
+    zp, ldz = _pointers(gzs, n, (n_rows, f), g.dtype, what)
+    if g.shape[1] != f or colptr.numel() < n_rows + 1 or not all(w.is_contiguous() for w in ws) or \
+            (total is not None and (total.dtype != g.dtype or total.shape[1] != f or total.shape[0] < n_rows)):
+        raise ValueError("gas_spmm_t_relu_linear_layers: shapes or dtypes do not match")
+    floats = C.c_float * n
+    ldy, ldx, ldz = (_one_stride(ld, what) for ld in (ldy, ldx, ldz))
+    _check(_calls().gas_spmm_t_relu_linear_layers(
+        n, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32), n_rows, a, lda, _dt(g), f, s_agg, yp, ldy, xp,
+        ldx, wp, floats(*(c_identity or [0.0] * n)), floats(*(c_weight or [1.0] * n)), c_total, tp, ldt, zp, ldz, _stream()))
+
+
 def gas_mlp2_push(z, w1, w2, y, idx, hist, b1=None, b2=None, relu_out=False):
     """gas_mlp2, and y[i] is also stored to hist[idx[i]]."""
     zp, ldz = _mat(z)
@@ -678,8 +753,8 @@ class HostTable:
     def dim(self):
         return 2
 
-    def stride(self, i):
-        return self.tensor.stride(i)
+    def stride(self, *i):
+        return self.tensor.stride(*i)
 
 
 class DiskTable:

@@ -288,19 +288,11 @@ gas_status run_layer(const FusedArgs& a, hipStream_t s) {
     return a.N <= 64 ? launch_layer<16, 2, 1, BWD>(a, s) : launch_layer<16, 2, 2, BWD>(a, s);
 }
 
-}  // namespace
-}  // namespace gas
-
-using namespace gas;
-
-extern "C" {
-
-gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const float* val, int64_t n_rows, const void* X,
-                           int64_t ldx, const void* hist, int64_t n_hist_rows, int64_t ld_hist, gas_dtype dt,
-                           int32_t F_in, float diag, float s_agg, const void* R, int64_t ldr, float s_res,
-                           const void* W, int32_t F_out, const void* bias, float c_identity, float c_weight, int relu,
-                           void* Y, int64_t ldy, void* Z_out, int64_t ldz_out, const int32_t* push_idx,
-                           void* push_hist, int64_t n_push_rows, int64_t ld_push, void* stream) {
+// the arguments of gas_spmm_linear and of gas_spmm_t_relu_linear (and of each of their layers), checked
+gas_status check_layer(const int32_t* rowptr, const int32_t* src, int64_t n_rows, const void* X, int64_t ldx, const void* hist,
+                       int64_t n_hist_rows, int64_t ld_hist, gas_dtype dt, int32_t F_in, const void* R, int64_t ldr, const void* W,
+                       int32_t F_out, float c_identity, const void* Y, int64_t ldy, const void* Z_out, int64_t ldz_out,
+                       const int32_t* push_idx, const void* push_hist, int64_t n_push_rows, int64_t ld_push) {
     if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_spmm_linear: unknown dtype %d", (int)dt);
     if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "gas_spmm_linear: fp32 only (use gas_spmm_hist + gas_linear_push)");
     GAS_REQUIRE(n_rows >= 0 && n_rows < 0x7FFFFFFFLL, "gas_spmm_linear: n_rows=%lld", (long long)n_rows);
@@ -319,7 +311,46 @@ gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const floa
     const bool al = aligned16(X) && ldx % 4 == 0 && aligned16(W) && (!hist || (aligned16(hist) && ld_hist % 4 == 0)) &&
                     (!R || (aligned16(R) && ldr % 4 == 0)) && (!Z_out || (aligned16(Z_out) && ldz_out % 4 == 0));
     GAS_REQUIRE(al, "gas_spmm_linear: rows must be 16-byte aligned (use gas_spmm_hist + gas_linear_push)");
+    return GAS_OK;
+}
+gas_status check_layer_bwd(const char* who, const int32_t* colptr, const int32_t* row, int64_t n_cols, const void* G, int64_t ldg,
+                           gas_dtype dt, int32_t F, const void* Y, int64_t ldy, const void* GX, int64_t ldgx, const void* W,
+                           int32_t F_below, float c_identity, const void* total, int64_t ldtotal, const void* GZ, int64_t ldgz) {
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "%s: fp32 only (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
+    GAS_REQUIRE(n_cols >= 0 && n_cols < 0x7FFFFFFFLL, "%s: n_cols=%lld", who, (long long)n_cols);
+    GAS_REQUIRE(F > 0 && F_below > 0 && F <= kMaxWidth && F_below <= kMaxWidth && F % 4 == 0 && F_below % 4 == 0,
+                "%s: widths %d, %d: multiples of 4 up to %d only", who, F, F_below, kMaxWidth);
+    if (n_cols == 0) return GAS_OK;
+    GAS_REQUIRE(colptr && row && G && Y && GX && W && GZ, "%s: null pointer", who);
+    GAS_REQUIRE(ldg >= F && ldy >= F && ldgx >= F && ldgz >= F_below && (!total || ldtotal >= F_below),
+                "%s: row stride smaller than the width", who);
+    GAS_REQUIRE(c_identity == 0.f || F == F_below, "%s: the identity term needs equal widths", who);
+    GAS_REQUIRE(G != GX && G != GZ && G != total && GX != GZ && GX != total && Y != GX && Y != GZ && Y != total &&
+                    (!total || total != GZ),
+                "%s: an output aliases another matrix", who);
+    GAS_REQUIRE(aligned16(G) && ldg % 4 == 0 && aligned16(Y) && ldy % 4 == 0 && aligned16(GX) && ldgx % 4 == 0 && aligned16(W) &&
+                    (!total || (aligned16(total) && ldtotal % 4 == 0)),
+                "%s: rows must be 16-byte aligned (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
+    return GAS_OK;
+}
 
+}  // namespace
+}  // namespace gas
+
+using namespace gas;
+
+extern "C" {
+
+gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const float* val, int64_t n_rows, const void* X,
+                           int64_t ldx, const void* hist, int64_t n_hist_rows, int64_t ld_hist, gas_dtype dt,
+                           int32_t F_in, float diag, float s_agg, const void* R, int64_t ldr, float s_res,
+                           const void* W, int32_t F_out, const void* bias, float c_identity, float c_weight, int relu,
+                           void* Y, int64_t ldy, void* Z_out, int64_t ldz_out, const int32_t* push_idx,
+                           void* push_hist, int64_t n_push_rows, int64_t ld_push, void* stream) {
+    const gas_status st = check_layer(rowptr, src, n_rows, X, ldx, hist, n_hist_rows, ld_hist, dt, F_in, R, ldr, W, F_out, c_identity,
+                                      Y, ldy, Z_out, ldz_out, push_idx, push_hist, n_push_rows, ld_push);
+    if (st != GAS_OK || n_rows == 0) return st;
     FusedArgs a{};
     a.rowptr = rowptr; a.src = src; a.val = val;
     a.n_rows = n_rows; a.n_tiles = (n_rows + kRows - 1) / kRows;
@@ -340,23 +371,9 @@ gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* row, con
                                   int64_t ldy, void* GX, int64_t ldgx, const void* W, int32_t F_below, float c_identity,
                                   float c_weight, float c_total, void* total, int64_t ldtotal, void* GZ, int64_t ldgz,
                                   void* stream) {
-    const char* who = "gas_spmm_t_relu_linear";
-    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
-    if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "%s: fp32 only (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
-    GAS_REQUIRE(n_cols >= 0 && n_cols < 0x7FFFFFFFLL, "%s: n_cols=%lld", who, (long long)n_cols);
-    GAS_REQUIRE(F > 0 && F_below > 0 && F <= kMaxWidth && F_below <= kMaxWidth && F % 4 == 0 && F_below % 4 == 0,
-                "%s: widths %d, %d: multiples of 4 up to %d only", who, F, F_below, kMaxWidth);
-    if (n_cols == 0) return GAS_OK;
-    GAS_REQUIRE(colptr && row && G && Y && GX && W && GZ, "%s: null pointer", who);
-    GAS_REQUIRE(ldg >= F && ldy >= F && ldgx >= F && ldgz >= F_below && (!total || ldtotal >= F_below),
-                "%s: row stride smaller than the width", who);
-    GAS_REQUIRE(c_identity == 0.f || F == F_below, "%s: the identity term needs equal widths", who);
-    GAS_REQUIRE(G != GX && G != GZ && G != total && GX != GZ && GX != total && Y != GX && Y != GZ && Y != total &&
-                    (!total || total != GZ),
-                "%s: an output aliases another matrix", who);
-    GAS_REQUIRE(aligned16(G) && ldg % 4 == 0 && aligned16(Y) && ldy % 4 == 0 && aligned16(GX) && ldgx % 4 == 0 && aligned16(W) &&
-                    (!total || (aligned16(total) && ldtotal % 4 == 0)),
-                "%s: rows must be 16-byte aligned (use gas_spmm_t_relu + gas_linear_bwd_input)", who);
+    const gas_status st = check_layer_bwd("gas_spmm_t_relu_linear", colptr, row, n_cols, G, ldg, dt, F, Y, ldy, GX, ldgx, W, F_below,
+                                          c_identity, total, ldtotal, GZ, ldgz);
+    if (st != GAS_OK || n_cols == 0) return st;
     FusedArgs a{};
     a.rowptr = colptr; a.src = row; a.val = val;
     a.n_rows = n_cols; a.n_tiles = (n_cols + kRows - 1) / kRows;
@@ -369,6 +386,67 @@ gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* row, con
     a.K = F; a.N = F_below;
     a.s_agg = s_agg; a.c_id = c_identity; a.c_w = c_weight;
     return run_layer<true>(a, (hipStream_t)stream);
+}
+
+gas_status gas_spmm_linear_layers(int32_t count, const int32_t* rowptr, const int32_t* src_first, const int32_t* src,
+                                  const float* val, int64_t n_rows, const void* X, int64_t ldx, const void* const* hist,
+                                  int64_t n_hist_rows, const int64_t* ld_hist, gas_dtype dt, int32_t F, float s_agg, const void* R,
+                                  int64_t ldr, float s_res, const void* const* W, const float* c_identity,
+                                  const float* c_weight, int relu_last, void* const* Y, int64_t ldy, void* const* Z_out,
+                                  int64_t ldz_out, const int32_t* push_idx, void* const* push_hist, int64_t n_push_rows,
+                                  const int64_t* ld_push, void* stream) {
+    const char* who = "gas_spmm_linear_layers";
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    GAS_REQUIRE(count >= 0 && n_rows >= 0, "%s: count=%d, n_rows=%lld", who, count, (long long)n_rows);
+    if (count == 0 || n_rows == 0) return GAS_OK;
+    GAS_REQUIRE(hist && ld_hist && W && c_identity && c_weight && Y && (!push_hist || ld_push), "%s: null pointer", who);
+    GAS_REQUIRE((push_idx == nullptr) == (push_hist == nullptr), "%s: push_idx and push_hist go together", who);
+    for (int pass = 0; pass < 2; ++pass)                       // every argument is checked before anything is launched
+        for (int l = 0; l < count; ++l) {
+            const int32_t* ind = l ? src : src_first;
+            const void* x = l ? Y[l - 1] : X;
+            const int64_t ld = l ? ldy : ldx;
+            void* z = Z_out ? Z_out[l] : nullptr;
+            void* table = push_hist ? push_hist[l] : nullptr;
+            const int32_t* ids = table ? push_idx : nullptr;
+            const int64_t ldp = table ? ld_push[l] : 0;
+            gas_status st;
+            if (pass == 0) {
+                st = check_layer(rowptr, ind, n_rows, x, ld, hist[l], n_hist_rows, ld_hist[l], dt, F, R, ldr, W[l], F, c_identity[l],
+                                 Y[l], ldy, z, ldz_out, ids, table, n_push_rows, ldp);
+                if (st == GAS_OK && Y[l] == x) st = fail(GAS_ERR_ARG, "%s: layer %d writes the rows that it reads", who, l);
+            } else {
+                st = gas_spmm_linear(rowptr, ind, val, n_rows, x, ld, hist[l], n_hist_rows, ld_hist[l], dt, F, 0.f, s_agg, R, ldr, s_res,
+                                     W[l], F, nullptr, c_identity[l], c_weight[l], l + 1 < count || relu_last, Y[l], ldy, z, ldz_out, ids,
+                                     table, n_push_rows, ldp, stream);
+            }
+            if (st != GAS_OK) return st;
+        }
+    return GAS_OK;
+}
+
+gas_status gas_spmm_t_relu_linear_layers(int32_t count, const int32_t* colptr, const int32_t* row, const float* val,
+                                         int64_t n_cols, const void* G, int64_t ldg, gas_dtype dt, int32_t F, float s_agg,
+                                         const void* const* Y, int64_t ldy, void* const* GX, int64_t ldgx, const void* const* W,
+                                         const float* c_identity, const float* c_weight, float c_total, void* total,
+                                         int64_t ldtotal, void* const* GZ, int64_t ldgz, void* stream) {
+    const char* who = "gas_spmm_t_relu_linear_layers";
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    GAS_REQUIRE(count >= 0 && n_cols >= 0, "%s: count=%d, n_cols=%lld", who, count, (long long)n_cols);
+    if (count == 0 || n_cols == 0) return GAS_OK;
+    GAS_REQUIRE(Y && GX && W && c_identity && c_weight && GZ, "%s: null pointer", who);
+    for (int pass = 0; pass < 2; ++pass)
+        for (int l = 0; l < count; ++l) {
+            const void* g = l ? GZ[l - 1] : G;
+            const int64_t ld = l ? ldgz : ldg;
+            const gas_status st =
+                pass == 0 ? check_layer_bwd(who, colptr, row, n_cols, g, ld, dt, F, Y[l], ldy, GX[l], ldgx, W[l], F, c_identity[l],
+                                            total, ldtotal, GZ[l], ldgz)
+                          : gas_spmm_t_relu_linear(colptr, row, val, n_cols, g, ld, dt, F, s_agg, Y[l], ldy, GX[l], ldgx, W[l], F,
+                                                   c_identity[l], c_weight[l], c_total, total, ldtotal, GZ[l], ldgz, stream);
+            if (st != GAS_OK) return st;
+        }
+    return GAS_OK;
 }
 
 }  // extern "C"

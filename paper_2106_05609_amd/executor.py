@@ -144,6 +144,37 @@ def _back_in_one_launch(width, rows, entries, longest) -> bool:
     return (width == 64 and rows <= 8192) or (alike and 100 * longest <= rows) or (rows >= 16384 and entries <= 4 * rows)
 
 
+def _layers_together(model: Model, bg, h0) -> bool:
+    """Whether GCNII's layers (all of one width) go in groups by one call (gas_spmm_linear_layers): narrow fp32 layers without long
+    rows, of few rows.  A layer takes the host 13 us by a call of its own and 5 in a group.  16 layers of 64, one by one and in
+    groups: 500 rows 214 and 125 us, 5,000 213 and 152, 12,500 221 and 155; 21,248 283 and 282, where the card takes longer
+    than either and a pass that starts on an idle one waits 30 us for its first groups."""
+    return B.spmm_linear_supported(h0, h0.shape[1]) and bg.max_row <= ONE_LAUNCH_MAX_ROW and model.n_layers >= 2 and 0 < bg.nb <= 16384
+
+
+def _layer_groups(count, most=8):
+    """Ranges of layers that go in one call: 2, 2, 4 and then `most`.  The pointers and the launch of a layer take the host 7 us:
+    the card has work in hand while the next, larger call is put together."""
+    first = 0
+    while first < count:
+        end = min(count, first + max(2, min(most, first)))
+        yield range(first, end)
+        first = end
+
+
+def _forward_layers(model: Model, bg, h0, histories, ids, betas, ys, zs):
+    """GCNII's layers by gas_spmm_linear_layers: layer l into ys[l], its aggregated rows into zs[l] (None: not kept); ids None:
+    no Push."""
+    L = model.n_layers
+    tables, pushed = [None] + list(histories[:L - 1]), list(histories[:L - 1]) + [None]
+    for g in _layer_groups(L):
+        a, b = g.start, g.stop
+        B.gas_spmm_linear_layers(bg.rowptr, bg.col if a == 0 else bg.src, bg.src, bg.val, h0 if a == 0 else ys[a - 1], model.weights[a:b],
+                                 ys[a:b], tables[a:b], s_agg=1.0 - model.alpha, r=h0, s_res=model.alpha,
+                                 c_identity=[1.0 - x for x in betas[a:b]], c_weight=betas[a:b], relu_last=b < L,
+                                 z_outs=None if zs is None else zs[a:b], push_idx=ids, push_hists=None if ids is None else pushed[a:b])
+
+
 def _mlp_in_two(z, w1, w2) -> bool:
     """Whether GIN's MLP is faster as two products with the hidden activation stored between them, which run on bf16 parts
     (csrc/split.h) where the fused fp32 kernel uses the fp32 instruction on 32 rows a workgroup: 4,000 rows of
@@ -280,6 +311,12 @@ def _forward_gcnii_fused(model: Model, bg: BatchGraph, x_feat, histories, do_pus
     B.gas_linear(x0, model.w_in, h0, relu=True)
     x, y = h0, None
     L = model.n_layers
+    if _layers_together(model, bg, h0):
+        y = torch.empty((nb, h0.shape[1]), dtype=dt, device=dev)
+        turns = [torch.empty_like(y) for _ in range(min(2, L - 1))]
+        _forward_layers(model, bg, h0, histories, ids if do_push else None, [gcnii_beta(l) for l in range(1, L + 1)],
+                        [turns[l % 2] for l in range(L - 1)] + [y], None)
+        return y
     for l in range(1, L + 1):
         last = l == L
         y = torch.empty((nb, model.out_width(l - 1)), dtype=dt, device=dev)
@@ -577,7 +614,11 @@ def _train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_p
     ys = _matrices(nb if fused else nv, widths[:-1], dt, dev) + [torch.empty((nb, widths[-1]), dtype=dt, device=dev)]
     betas = [gcnii_beta(l) for l in range(1, L + 1)] if model.op == "gcnii" else [1.0] * L
     short_rows = fused and model.op in ("gcn", "gcnii") and bg.max_row <= ONE_LAUNCH_MAX_ROW
-    for l in range(1, L + 1):
+    together = fused and model.op == "gcnii" and _layers_together(model, bg, h0)
+    if together:
+        _forward_layers(model, bg, h0, histories, ids if do_push else None, betas, ys, zs)
+        saved, y = [(z, None, out) for z, out in zip(zs, ys)], ys[-1]
+    for l in range(1, L + 1) if not together else ():
         last = l == L
         z, x_next = zs[l - 1], ys[l - 1]
         y = x_next if fused or last else x_next[:nb]
@@ -659,7 +700,32 @@ def _train_batch(model: Model, bg: BatchGraph, x_feat, histories, grad_out, do_p
     if fused and (model.op == "gcnii" or (model.op == "gcn" and L > 2)):      # (GCN's first layer has none)
         joint = {(i, o) for i, o in set(zip(ins, widths))
                  if B.spmm_linear_supported(zs[ins.index(i)], o) and _back_in_one_launch(o, nb, bg.nnz_t, bg.max_col)}
-    for l in range(L, 0, -1):
+    by_layers = together and pooled and joint == {(widths[0], widths[0])} and all(w.data_ptr() % 16 == 0 for w in model.weights)
+    if by_layers:
+        # the launches of as many layers in one call as wait for their weight gradients together
+        f = widths[0]
+        g_h0 = torch.zeros((nv, f), dtype=dt, device=dev)
+        gzs = [torch.empty((nb, f), dtype=dt, device=dev) for _ in range(2)]      # in turn, layer L's first
+        B.gas_linear_bwd_input_add(g, model.weights[L - 1], gzs[0], c_identity=1.0 - betas[L - 1], c_weight=betas[L - 1],
+                                   total=g_h0[:nb], c_total=model.alpha)
+        grads[L - 1] = wg.add(zs[L - 1], g, dws[L - 1], betas[L - 1])
+        top = L - 1
+        while top > 0:
+            down = range(top - 1, max(-1, top - 1 - wg.TOGETHER), -1)
+            gxs = _matrices(nb, [f] * len(down), dt, dev)
+            for some in _layer_groups(len(down)):
+                some, part = down[some.start:some.stop], gxs[some.start:some.stop]
+                B.gas_spmm_t_relu_linear_layers(bg.colptr, bg.row, bg.val_t, gzs[(L - 2 - some[0]) % 2], [ys[l] for l in some], part,
+                                                [model.weights[l] for l in some], [gzs[(L - 1 - l) % 2] for l in some],
+                                                s_agg=1.0 - model.alpha, c_identity=[1.0 - betas[l] for l in some],
+                                                c_weight=[betas[l] for l in some], total=g_h0[:nb], c_total=model.alpha)
+            for l, gx in zip(down, gxs):
+                grads[l] = wg.add(zs[l], gx, dws[l], betas[l])
+            top = down[-1]
+        gx = torch.empty((nv, f), dtype=dt, device=dev)
+        B.gas_spmm_t(bg.plan_t_all, bg.colptr, bg.row, bg.val_t, gzs[(L - 1) % 2], gx, s_agg=1.0 - model.alpha)
+        B.gas_axpy(g_h0, gx, g_h0, 1.0)
+    for l in range(L, 0, -1) if not by_layers else ():
         z, h, _ = saved[l - 1]                # g: the gradient before this layer's activation
         gz, ready = ready, None
         if model.op == "gcn":
