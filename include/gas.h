@@ -502,6 +502,40 @@ GAS_API gas_status gas_pna_aggregate(const int32_t* rowptr, const int32_t* col, 
                              const void* X, int64_t ldx, gas_dtype dt, int32_t F,
                              const void* add, int64_t ldadd, float delta,
                              void* out, int64_t ldout, void* stream);
+/* blocks: 9 as above, or 3: the aggregates alone, without the scaled blocks (gas_pna_linear takes them). */
+GAS_API gas_status gas_pna_aggregate_blocks(const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                             const void* X, int64_t ldx, gas_dtype dt, int32_t F,
+                             const void* add, int64_t ldadd, float delta, int32_t blocks,
+                             void* out, int64_t ldout, void* stream);
+
+/*
+ * The transform of a PNA layer by the rows' degrees (fp32).  With X = [h (F columns) | A (3 F1 columns: mean, min, max) | ...],
+ * d_v the number of entries of row v, s_v = log(d_v + 1) / delta and W [F + 9 F1, F_out] cut into Wh, Wa, Wb, Wc:
+ *     gas_pna_linear:            Y[v] = act( h Wh + A (Wa + s_v Wb + Wc / s_v) )       (what gas_linear gives for the nine blocks
+ *                                of gas_pna_aggregate, which are not read), also to push_hist[push_idx[v]] if given
+ *     gas_pna_linear_bwd_input:  GX[v] = [G Wh^T | G (Wa + s_v Wb + Wc / s_v)^T]: the gradient at h and at A, the nine blocks'
+ *                                folded with their scalers (gas_pna_aggregate_bwd_blocks with 3)
+ *     gas_pna_linear_bwd_weight: dW [F + 9 F1, F_out] of the nine blocks
+ * Rows of one degree share the matrix in brackets and are taken together: gas_pna_groups lists the rows of each degree (0 ..
+ * max_degree, at most 63; a row of more entries is undefined behaviour) in a buffer of gas_pna_groups_workspace bytes,
+ * 16-byte aligned, once for a pattern; the calls take it with the same n_rows and max_degree.  Nothing is read back.  Fixed orders of summation;
+ * results agree with the plain calls to rounding.  workspace: caller-owned, at least the bytes of the *_workspace call,
+ * contents undefined afterwards.  Outputs must not alias inputs.  n_rows == 0 is a no-op.
+ */
+GAS_API int64_t gas_pna_groups_workspace(int64_t n_rows, int32_t max_degree);
+GAS_API gas_status gas_pna_groups(const int32_t* rowptr, int64_t n_rows, int32_t max_degree, void* groups, void* stream);
+GAS_API int64_t gas_pna_linear_workspace(int32_t max_degree, int32_t F, int32_t F1, int32_t F_out);
+GAS_API gas_status gas_pna_linear(const void* groups, int64_t n_rows, int32_t max_degree, const void* X, int64_t ldx, int32_t F,
+                             int32_t F1, const void* W, int32_t F_out, float delta, int relu, void* Y, int64_t ldy,
+                             const int32_t* push_idx, void* push_hist, int64_t ld_push, void* workspace,
+                             int64_t workspace_bytes, void* stream);
+GAS_API gas_status gas_pna_linear_bwd_input(const void* groups, int64_t n_rows, int32_t max_degree, const void* G, int64_t ldg,
+                             int32_t F, int32_t F1, const void* W, int32_t F_out, float delta, void* GX, int64_t ldgx,
+                             void* workspace, int64_t workspace_bytes, void* stream);
+GAS_API int64_t gas_pna_linear_bwd_weight_workspace(int64_t n_rows, int32_t max_degree, int32_t F, int32_t F1, int32_t F_out);
+GAS_API gas_status gas_pna_linear_bwd_weight(const void* groups, int64_t n_rows, int32_t max_degree, const void* X, int64_t ldx,
+                             const void* G, int64_t ldg, int32_t F, int32_t F1, int32_t F_out, float delta, float* dW,
+                             void* workspace, int64_t workspace_bytes, void* stream);
 
 /*
  * GAT's anisotropic aggregation (operator appendix), one head: for every row
@@ -562,6 +596,12 @@ GAS_API int64_t gas_pna_aggregate_bwd_workspace(int64_t n_rows, int64_t nnz, int
 GAS_API gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
                                  int64_t nnz, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_out,
                                  const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta,
+                                 const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd, int64_t ldga,
+                                 void* workspace, int64_t workspace_bytes, void* stream);
+/* blocks: 9 as above, or 3: G [n_rows, 3 F] holds c_0, c_1, c_2 themselves. */
+GAS_API gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t rows,
+                                 int64_t entries, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_out,
+                                 const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta, int32_t blocks,
                                  const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd, int64_t ldga,
                                  void* workspace, int64_t workspace_bytes, void* stream);
 GAS_API int64_t gas_gat_aggregate_bwd_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F);

@@ -21,7 +21,9 @@ EXPORTS = [
     "gas_relu_bwd", "gas_linear_bwd_input", "gas_linear_bwd_input_add", "gas_linear_bwd_weight", "gas_linear_bwd_weight_workspace",
     "gas_linear_bwd_weight_static", "gas_linear_bwd_weights", "gas_linear_bwd_weights_workspace",
     "gas_softmax_xent", "gas_sgd_step", "gas_sgd_steps", "gas_sq_norm", "gas_sgd_step_clipped", "gas_axpy", "gas_row_distance", "gas_row_distance_bwd", "gas_row_dot",
-    "gas_pna_aggregate", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
+    "gas_pna_aggregate", "gas_pna_aggregate_blocks", "gas_pna_aggregate_bwd_blocks", "gas_pna_groups", "gas_pna_groups_workspace",
+    "gas_pna_linear", "gas_pna_linear_workspace", "gas_pna_linear_bwd_input", "gas_pna_linear_bwd_weight",
+    "gas_pna_linear_bwd_weight_workspace", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
     "gas_gat_aggregate_bwd_heads", "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
     "gas_gat_aggregate_bwd_heads_workspace",
     "gas_disk_open", "gas_disk_close", "gas_disk_pull", "gas_disk_push", "gas_disk_wait", "gas_disk_read_rows",
@@ -50,6 +52,8 @@ def lib():
         L.gas_plan_destroy.restype = None
         L.gas_linear_bwd_weight_workspace.restype = C.c_int64
         L.gas_linear_bwd_weights_workspace.restype = C.c_int64
+        for name in ("gas_pna_groups_workspace", "gas_pna_linear_workspace", "gas_pna_linear_bwd_weight_workspace"):
+            getattr(L, name).restype = C.c_int64
         L.gas_pna_aggregate_bwd_workspace.restype = C.c_int64
         L.gas_gat_aggregate_bwd_workspace.restype = C.c_int64
         L.gas_gat_aggregate_bwd_heads_workspace.restype = C.c_int64
@@ -75,7 +79,10 @@ _SIGNATURES = dict(
     gas_linear_bwd_weights_workspace="ipppi", gas_linear_bwd_weights="ipppppppipppqp",
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
-    gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp",
+    gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp", gas_pna_aggregate_blocks="ppqpqiipqfipqp",
+    gas_pna_aggregate_bwd_blocks="pppqqpppqpqiifipqpqpqpqp", gas_pna_groups="pqipp", gas_pna_groups_workspace="qi",
+    gas_pna_linear="pqipqiipifipqppqpqp", gas_pna_linear_workspace="iiii", gas_pna_linear_bwd_input="pqipqiipifpqpqp",
+    gas_pna_linear_bwd_weight="pqipqpqiiifppqp", gas_pna_linear_bwd_weight_workspace="qiiii",
     gas_gat_aggregate_heads="ppqpqiiippfipqp", gas_pna_aggregate_bwd_workspace="qqi",
     gas_pna_aggregate_bwd="pppqqpppqpqiifpqpqpqpqp", gas_gat_aggregate_bwd_heads_workspace="qqqii",
     gas_gat_aggregate_bwd_heads="pppqpppqqqpqiiippfpqpqpppqp", gas_axpy="pqpqqiifpqp", gas_row_distance="pqpqqiippp",
@@ -665,17 +672,72 @@ def gas_sgd_step_clipped(w, dw, lr, sq_norms, max_norm, weight_decay=0.0):
 
 
 def gas_pna_aggregate(rowptr, col, x, out, delta, add=None):
-    """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add)."""
+    """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add); out [n_rows, 3F]: the
+    aggregators alone."""
     xp, ldx = _mat(x)
     op, ldo = _mat(out)
     ap, lda = (0, 0) if add is None else _mat(add)
     n_rows = rowptr.numel() - 1
-    if out.dtype != x.dtype or out.shape[0] < n_rows or out.shape[1] != 9 * x.shape[1] or \
+    blocks = 3 if out.shape[1] == 3 * x.shape[1] else 9
+    if out.dtype != x.dtype or out.shape[0] < n_rows or out.shape[1] != blocks * x.shape[1] or \
             (add is not None and (add.dtype != x.dtype or add.shape[1] != x.shape[1] or add.shape[0] < n_rows)):
         raise ValueError("gas_pna_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_pna_aggregate(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, xp, ldx,
-                                   _dt(x), x.shape[1], ap, lda, delta, op, ldo,
-                                   _stream()))
+    _check(_calls().gas_pna_aggregate_blocks(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, xp, ldx,
+                                          _dt(x), x.shape[1], ap, lda, delta, blocks, op, ldo, _stream()))
+
+
+PNA_MAX_DEGREE = 63
+
+
+def gas_pna_groups(rowptr, max_degree):
+    """The rows of a pattern by their number of entries (at most max_degree, itself at most PNA_MAX_DEGREE), for gas_pna_linear
+    and its backward calls."""
+    n_rows = rowptr.numel() - 1
+    groups = torch.empty(max(1, _calls().gas_pna_groups_workspace(n_rows, max_degree)), dtype=torch.uint8, device=rowptr.device)
+    _check(_calls().gas_pna_groups(_ptr(rowptr, torch.int32), n_rows, max_degree, groups.data_ptr(), _stream()))
+    return groups
+
+
+def _pna_widths(x, w, f1, groups, max_degree):
+    """F of w [F + 9 F1, F_out], checked against a matrix of the rows' [h | A ..] and the groups."""
+    f = w.shape[0] - 9 * f1
+    if f <= 0 or x.shape[1] < f + 3 * f1 or groups.numel() != _calls().gas_pna_groups_workspace(x.shape[0], max_degree) or \
+            x.dtype != torch.float32:
+        raise ValueError("gas_pna_linear: shapes or dtypes do not match")
+    return f
+
+
+def gas_pna_linear(groups, max_degree, x, w, f1, delta, y, relu=False, idx=None, hist=None):
+    """y = act(h Wh + A (Wa + s Wb + Wc / s)) for x = [h | A ..], w = [Wh; Wa; Wb; Wc] with blocks of 3 f1 rows, and (idx, hist)
+    push y."""
+    f, (xp, ldx), (yp, ldy) = _pna_widths(x, w, f1, groups, max_degree), _mat(x), _mat(y)
+    hp, ldh = (0, 0) if hist is None else _mat(hist)
+    if w.dtype != x.dtype or y.dtype != x.dtype or y.shape != (x.shape[0], w.shape[1]) or (idx is None) != (hist is None) or \
+            (hist is not None and (hist.dtype != x.dtype or hist.shape[1] != w.shape[1] or idx.numel() != x.shape[0])):
+        raise ValueError("gas_pna_linear: shapes or dtypes do not match")
+    ws = torch.empty(_calls().gas_pna_linear_workspace(max_degree, f, f1, w.shape[1]), dtype=torch.uint8, device=x.device)
+    _check(_calls().gas_pna_linear(groups.data_ptr(), x.shape[0], max_degree, xp, ldx, f, f1, _ptr(w), w.shape[1], delta, int(relu), yp,
+                                ldy, _ptr(idx, torch.int32), hp, ldh, ws.data_ptr(), ws.numel(), _stream()))
+
+
+def gas_pna_linear_bwd_input(groups, max_degree, g, w, f1, delta, gx):
+    """gx = [g Wh^T | g (Wa + s Wb + Wc / s)^T]."""
+    f, (gp, ldg), (op, ldo) = _pna_widths(gx, w, f1, groups, max_degree), _mat(g), _mat(gx)
+    if g.shape != (gx.shape[0], w.shape[1]) or g.dtype != gx.dtype or w.dtype != gx.dtype:
+        raise ValueError("gas_pna_linear_bwd_input: shapes or dtypes do not match")
+    ws = torch.empty(_calls().gas_pna_linear_workspace(max_degree, f, f1, w.shape[1]), dtype=torch.uint8, device=g.device)
+    _check(_calls().gas_pna_linear_bwd_input(groups.data_ptr(), g.shape[0], max_degree, gp, ldg, f, f1, _ptr(w), w.shape[1], delta, op,
+                                          ldo, ws.data_ptr(), ws.numel(), _stream()))
+
+
+def gas_pna_linear_bwd_weight(groups, max_degree, x, g, f1, delta, dw):
+    """dw [F + 9 f1, F_out] for x = [h | A ..] and the gradient g at the output."""
+    f, (xp, ldx), (gp, ldg) = _pna_widths(x, dw, f1, groups, max_degree), _mat(x), _mat(g)
+    if g.shape != (x.shape[0], dw.shape[1]) or g.dtype != x.dtype or dw.dtype != torch.float32 or not dw.is_contiguous():
+        raise ValueError("gas_pna_linear_bwd_weight: shapes or dtypes do not match")
+    ws = torch.empty(_calls().gas_pna_linear_bwd_weight_workspace(x.shape[0], max_degree, f, f1, g.shape[1]), dtype=torch.uint8, device=x.device)
+    _check(_calls().gas_pna_linear_bwd_weight(groups.data_ptr(), x.shape[0], max_degree, xp, ldx, gp, ldg, f, f1, g.shape[1], delta,
+                                           dw.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
 
 
 def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False, heads=1):
@@ -842,23 +904,25 @@ class DiskTable:
 
 
 def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, gadd=None, plan_t=None):
-    """Backward of gas_pna_aggregate: gx [n_out, F] (n_out = gx.shape[0] columns of the pattern), gadd [n_rows, F].
+    """Backward of gas_pna_aggregate: gx [n_out, F] (n_out = gx.shape[0] columns of the pattern), gadd [n_rows, F]; g of nine
+    blocks or of three, folded with their scalers.
     plan_t: a Plan of the CSC copy for those n_out columns (fast path), or None (plain kernels)."""
     xp, ldx = _mat(x)
     gp, ldg = _mat(g)
     op, ldo = _mat(gx)
     ap, lda = (0, 0) if gadd is None else _mat(gadd)
     n_rows, F = rowptr.numel() - 1, x.shape[1]
-    if g.shape != (n_rows, 9 * F) or gx.shape[1] != F or g.dtype != x.dtype or gx.dtype != x.dtype:
+    blocks = 3 if g.shape[1] == 3 * F else 9
+    if g.shape != (n_rows, blocks * F) or gx.shape[1] != F or g.dtype != x.dtype or gx.dtype != x.dtype:
         raise ValueError("gas_pna_aggregate_bwd: shapes or dtypes do not match")
     nnz = col.numel()
     nbytes = int(_calls().gas_pna_aggregate_bwd_workspace(n_rows, nnz, F))
     ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x.device)
-    _check(_calls().gas_pna_aggregate_bwd(plan_t.handle if plan_t is not None else 0,
-                                       _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
-                                       nnz, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
-                                       gx.shape[0], xp, ldx, _dt(x), F, delta,
-                                       gp, ldg, op, ldo, ap, lda, _ptr(ws), nbytes, _stream()))
+    _check(_calls().gas_pna_aggregate_bwd_blocks(plan_t.handle if plan_t is not None else 0,
+                                              _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
+                                              nnz, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
+                                              gx.shape[0], xp, ldx, _dt(x), F, delta, blocks,
+                                              gp, ldg, op, ldo, ap, lda, _ptr(ws), nbytes, _stream()))
 
 
 def gas_gat_aggregate_bwd(rowptr, col, colptr, row, csc_pos, p, a_dst, a_src, gz, gp_out, ga_dst, ga_src,

@@ -42,6 +42,7 @@ struct PnaBwdArgs {
     int32_t* K;        // [n_rows][2][F]: entry position of the first minimum and of the first maximum
     int F;
     float inv_delta;
+    int folded;        // G has three blocks, the nine folded with their scalers
 };
 
 // Row v: the three block gradients folded with their scalers, and which entry holds each feature's extremes.
@@ -71,8 +72,9 @@ __global__ __launch_bounds__(64) void pna_bwd_rows_kernel(PnaBwdArgs a) {
         float cc[3];
 #pragma unroll
         for (int i = 0; i < 3; ++i)
-            cc[i] = ld<BF>(a.G, v * a.ldg + (int64_t)i * a.F + f) + s * ld<BF>(a.G, v * a.ldg + (int64_t)(3 + i) * a.F + f) +
-                    ld<BF>(a.G, v * a.ldg + (int64_t)(6 + i) * a.F + f) / s;
+            cc[i] = a.folded ? ld<BF>(a.G, v * a.ldg + (int64_t)i * a.F + f)
+                             : ld<BF>(a.G, v * a.ldg + (int64_t)i * a.F + f) + s * ld<BF>(a.G, v * a.ldg + (int64_t)(3 + i) * a.F + f) +
+                                   ld<BF>(a.G, v * a.ldg + (int64_t)(6 + i) * a.F + f) / s;
         c[0] = cc[0] / d; c[a.F] = cc[1]; c[2 * a.F] = cc[2];
         kk[0] = kmin; kk[a.F] = kmax;
         if (a.Gadd) st<BF>(a.Gadd, v * a.ldga + f, cc[0] + cc[1] + cc[2]);
@@ -125,6 +127,7 @@ struct PnaFastArgs {
     uint2* ent;            // [nnz]: x = start | count << 16 in the row's minima list, y = the same for the maxima
     int F;
     float inv_delta;
+    int folded;
 };
 
 // Row v = [b, e), b < e.  G: lanes that hold a row (at least its number of pieces).  With G < 64 the wavefront's
@@ -233,6 +236,11 @@ __device__ __forceinline__ void pna_bwd_row(const PnaFastArgs& a, int64_t v, int
         for (int j = 0; j < 3; ++j) {
             float g0[E], g1[E], g2[E];
             unpack<BF>(*reinterpret_cast<const u32x4*>(grow + (int64_t)j * a.F * EB), g0);
+            if (a.folded) {
+#pragma unroll
+                for (int i = 0; i < E; ++i) cc[j][i] = g0[i];
+                continue;
+            }
             unpack<BF>(*reinterpret_cast<const u32x4*>(grow + (int64_t)(3 + j) * a.F * EB), g1);
             unpack<BF>(*reinterpret_cast<const u32x4*>(grow + (int64_t)(6 + j) * a.F * EB), g2);
 #pragma unroll
@@ -1172,14 +1180,24 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
                                  int64_t n_out, const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta,
                                  const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd, int64_t ldga,
                                  void* workspace, int64_t workspace_bytes, void* stream) {
+    return gas_pna_aggregate_bwd_blocks(plan_t, rowptr, col, n_rows, nnz, colptr, row, csc_pos, n_out, X, ldx, dt, F, delta, 9, G, ldg,
+                                        GX, ldgx, Gadd, ldga, workspace, workspace_bytes, stream);
+}
+
+gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                        int64_t nnz, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos,
+                                        int64_t n_out, const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta,
+                                        int32_t blocks, const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd,
+                                        int64_t ldga, void* workspace, int64_t workspace_bytes, void* stream) {
     if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_pna_aggregate_bwd: unknown dtype %d", (int)dt);
     GAS_REQUIRE(n_rows >= 0 && n_out >= 0 && nnz >= 0 && F > 0, "gas_pna_aggregate_bwd: n_rows=%lld n_out=%lld nnz=%lld F=%d",
                 (long long)n_rows, (long long)n_out, (long long)nnz, F);
     GAS_REQUIRE(delta > 0.f, "gas_pna_aggregate_bwd: delta must be positive");
+    GAS_REQUIRE(blocks == 9 || blocks == 3, "gas_pna_aggregate_bwd: %d blocks (9, or 3 folded ones)", blocks);
     GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL && n_out <= 0x7FFFFFFFLL, "gas_pna_aggregate_bwd: too many rows for one launch");
     if (n_rows == 0 && n_out == 0) return GAS_OK;
     GAS_REQUIRE(n_out == 0 || (colptr && GX && ldgx >= F), "gas_pna_aggregate_bwd: null column pointers or output");
-    GAS_REQUIRE(n_rows == 0 || (rowptr && col && row && csc_pos && X && G && ldx >= F && ldg >= 9 * (int64_t)F),
+    GAS_REQUIRE(n_rows == 0 || (rowptr && col && row && csc_pos && X && G && ldx >= F && ldg >= blocks * (int64_t)F),
                 "gas_pna_aggregate_bwd: null pointer or row stride smaller than the row");
     GAS_REQUIRE(!Gadd || ldga >= F, "gas_pna_aggregate_bwd: row stride of Gadd smaller than F");
     GAS_REQUIRE(n_rows == 0 || (workspace && workspace_bytes >= gas_pna_aggregate_bwd_workspace(n_rows, nnz, F)),
@@ -1203,7 +1221,7 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
         a.items_f = reinterpret_cast<uint16_t*>(w); w += align_up(n_rows * 2 * (int64_t)F * 2);
         a.items_v = reinterpret_cast<float*>(w); w += align_up(n_rows * 2 * (int64_t)F * 4);
         a.ent = reinterpret_cast<uint2*>(w);
-        a.F = F; a.inv_delta = 1.f / delta;
+        a.F = F; a.inv_delta = 1.f / delta; a.folded = blocks == 3;
         const int pieces = F / (bf ? 8 : 4);
         if (bf) {
             if (pieces <= 16) launch_pna_bwd_rows<true, 16>(a, s);
@@ -1235,7 +1253,7 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
     a.Gadd = static_cast<char*>(Gadd); a.ldga = ldga;
     a.C = static_cast<float*>(workspace);
     a.K = reinterpret_cast<int32_t*>(static_cast<char*>(workspace) + align_up(n_rows * 3 * (int64_t)F * 4));
-    a.F = F; a.inv_delta = 1.f / delta;
+    a.F = F; a.inv_delta = 1.f / delta; a.folded = blocks == 3;
     if (n_rows > 0) {
         if (bf) hipLaunchKernelGGL(pna_bwd_rows_kernel<true>, dim3((unsigned)n_rows), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(pna_bwd_rows_kernel<false>, dim3((unsigned)n_rows), dim3(64), 0, s, a);

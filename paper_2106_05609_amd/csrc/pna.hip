@@ -14,6 +14,7 @@ struct PnaArgs {
     char* out; int64_t ldout;
     int F;
     float inv_delta;
+    int blocks;                                   // of the output: 9, or 3 (the aggregates alone)
 };
 
 // Rows of at most 64 pieces of 16 bytes, G = 16, 32 or 64 lanes per row (at least the number of pieces).  A
@@ -101,10 +102,11 @@ __device__ __forceinline__ void pna_finish(const PnaArgs& a, int64_t v, int n_en
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
         if (j % S != team) continue;
+        __builtin_nontemporal_store(pack<BF>(agg[j]), reinterpret_cast<u32x4*>(o + (int64_t)j * a.F * EB));
+        if (a.blocks == 3) continue;
         float t1[E], t2[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) { t1[i] = s * agg[j][i]; t2[i] = agg[j][i] * inv_s; }
-        __builtin_nontemporal_store(pack<BF>(agg[j]), reinterpret_cast<u32x4*>(o + (int64_t)j * a.F * EB));
         __builtin_nontemporal_store(pack<BF>(t1), reinterpret_cast<u32x4*>(o + (int64_t)(3 + j) * a.F * EB));
         __builtin_nontemporal_store(pack<BF>(t2), reinterpret_cast<u32x4*>(o + (int64_t)(6 + j) * a.F * EB));
     }
@@ -224,10 +226,11 @@ __global__ __launch_bounds__(64) void pna_wide_rows_kernel(PnaArgs a) {
         char* o = a.out + (v * a.ldout + (int64_t)piece * E) * EB;
 #pragma unroll
         for (int j = 0; j < 3; ++j) {
+            __builtin_nontemporal_store(pack<BF>(agg[j]), reinterpret_cast<u32x4*>(o + (int64_t)j * a.F * EB));
+            if (a.blocks == 3) continue;
             float t1[E], t2[E];
 #pragma unroll
             for (int i = 0; i < E; ++i) { t1[i] = s * agg[j][i]; t2[i] = agg[j][i] * inv_s; }
-            __builtin_nontemporal_store(pack<BF>(agg[j]), reinterpret_cast<u32x4*>(o + (int64_t)j * a.F * EB));
             __builtin_nontemporal_store(pack<BF>(t1), reinterpret_cast<u32x4*>(o + (int64_t)(3 + j) * a.F * EB));
             __builtin_nontemporal_store(pack<BF>(t2), reinterpret_cast<u32x4*>(o + (int64_t)(6 + j) * a.F * EB));
         }
@@ -277,6 +280,7 @@ __global__ __launch_bounds__(256) void pna_generic_kernel(PnaArgs a) {
     const float inv_s = e > b ? 1.f / s : 0.f;
     for (int j = 0; j < 3; ++j) {
         st(v * a.ldout + (int64_t)j * a.F + f, agg[j]);
+        if (a.blocks == 3) continue;
         st(v * a.ldout + (int64_t)(3 + j) * a.F + f, s * agg[j]);
         st(v * a.ldout + (int64_t)(6 + j) * a.F + f, agg[j] * inv_s);
     }
@@ -290,12 +294,19 @@ using namespace gas;
 extern "C" gas_status gas_pna_aggregate(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* X,
                                         int64_t ldx, gas_dtype dt, int32_t F, const void* add, int64_t ldadd,
                                         float delta, void* out, int64_t ldout, void* stream) {
+    return gas_pna_aggregate_blocks(rowptr, col, n_rows, X, ldx, dt, F, add, ldadd, delta, 9, out, ldout, stream);
+}
+
+extern "C" gas_status gas_pna_aggregate_blocks(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* X,
+                                               int64_t ldx, gas_dtype dt, int32_t F, const void* add, int64_t ldadd,
+                                               float delta, int32_t blocks, void* out, int64_t ldout, void* stream) {
     if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_pna_aggregate: unknown dtype %d", (int)dt);
     GAS_REQUIRE(n_rows >= 0 && F > 0, "gas_pna_aggregate: n_rows=%lld F=%d", (long long)n_rows, F);
     GAS_REQUIRE(delta > 0.f, "gas_pna_aggregate: delta must be positive");
     if (n_rows == 0) return GAS_OK;
+    GAS_REQUIRE(blocks == 9 || blocks == 3, "gas_pna_aggregate: %d blocks (9, or 3 without the scaled ones)", blocks);
     GAS_REQUIRE(rowptr && col && X && out, "gas_pna_aggregate: null pointer");
-    GAS_REQUIRE(ldx >= F && ldout >= 9 * (int64_t)F && (!add || ldadd >= F), "gas_pna_aggregate: row stride smaller than the row");
+    GAS_REQUIRE(ldx >= F && ldout >= blocks * (int64_t)F && (!add || ldadd >= F), "gas_pna_aggregate: row stride smaller than the row");
     GAS_REQUIRE(out != X && out != add, "gas_pna_aggregate: the output must not alias an input");
     GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL, "gas_pna_aggregate: too many rows for one launch");
     PnaArgs a;
@@ -303,7 +314,7 @@ extern "C" gas_status gas_pna_aggregate(const int32_t* rowptr, const int32_t* co
     a.X = static_cast<const char*>(X); a.ldx = ldx;
     a.add = static_cast<const char*>(add); a.ldadd = ldadd;
     a.out = static_cast<char*>(out); a.ldout = ldout;
-    a.F = F; a.inv_delta = 1.f / delta;
+    a.F = F; a.inv_delta = 1.f / delta; a.blocks = blocks;
     const int e = dt == GAS_BF16 ? 8 : 4;
     hipStream_t s = (hipStream_t)stream;
     const bool vec = F % e == 0 && ldx % e == 0 && ldout % e == 0 && (!add || ldadd % e == 0) && aligned16(X) &&

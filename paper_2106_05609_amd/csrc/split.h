@@ -58,7 +58,8 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& h, uint
 // row exchanged so that the 16-byte reads of consecutive rows fall on different banks.
 // KG groups of T threads each take a tile of their own; a thread's number in its group is `threadIdx.x` itself where there is one
 // group (a remainder there changed the order of the kernel's instructions: 6,000 x 498 x 192 in 64 x 64 tiles 22.5 -> 23.3 us).
-template <int ROWS, int KS, bool KC, int T, int KG>
+// IDX: the matrix's rows are those that idx names (KC: row r of the tile is row idx[r] of X; else q is row idx[q]).
+template <int ROWS, int KS, bool KC, int T, int KG, bool IDX = false>
 struct SplitTile {
     static constexpr int kQ = 16 * KS, kCh = 2 * KS, kPieces = ROWS * kCh;
     static constexpr int kPlane = ROWS * kQ;                              // bf16 elements
@@ -69,7 +70,13 @@ struct SplitTile {
     uint32_t off;              // ... and the thread's row from there, in bytes: a load is scalar base + 32-bit offset
     float v[NV][8];
     int64_t ld;
+    const int32_t* idx = nullptr;
 
+    __device__ __forceinline__ int64_t named(int64_t row) const {
+        if constexpr (!IDX) return row;
+        else if constexpr (KC) return idx[row];
+        else return __builtin_amdgcn_readfirstlane(idx[row]);      // a wavefront has one piece: one q
+    }
     static __device__ __forceinline__ unsigned thread() { return KG == 1 ? threadIdx.x : threadIdx.x % T; }
     static __device__ __forceinline__ int row_of(int i) {
         const int idx = thread() + T * i;
@@ -93,7 +100,7 @@ struct SplitTile {
         off = (uint32_t)(row_of(0) < last ? row_of(0) : last) * 4;             // not KC: T is a multiple of ROWS
 #pragma unroll
         for (int i = 0; i < NV; ++i)
-            p[i] = KC ? X + (r0 + (row_of(i) < last ? row_of(i) : last)) * ld + 8 * piece_of(i) : X + r0;
+            p[i] = KC ? X + named(r0 + (row_of(i) < last ? row_of(i) : last)) * ld + 8 * piece_of(i) : X + r0;
     }
     __device__ __forceinline__ void fetch(int64_t q0) {                       // q0 .. q0 + kQ - 1
 #pragma unroll
@@ -104,6 +111,10 @@ struct SplitTile {
                 const f32x4 b = *reinterpret_cast<const f32x4_any*>(p[i] + q0 + 4);
 #pragma unroll
                 for (int e = 0; e < 4; ++e) { v[i][e] = a[e]; v[i][4 + e] = b[e]; }
+            } else if constexpr (IDX) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e)
+                    v[i][e] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p[i] + named(q0 + 8 * piece_of(i) + e) * ld) + off);
             } else {
                 const char* u = reinterpret_cast<const char*>(p[i] + (q0 + 8 * piece_of(i)) * ld);
 #pragma unroll
@@ -122,7 +133,7 @@ struct SplitTile {
             for (int e = 0; e < 8; ++e) {
                 const int64_t k = q + e < q_end ? q + e : q_end - 1;
                 v[i][e] = KC ? p[i][k - 8 * piece_of(i)]
-                             : *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p[i] + k * ld) + off);
+                             : *reinterpret_cast<const float*>(reinterpret_cast<const char*>(p[i] + named(k) * ld) + off);
             }
         }
     }
@@ -163,11 +174,11 @@ struct SplitTile {
 
 // A BM x BN tile of sum_q A(r, q) B(c, q), q_begin <= q < q_end (not empty), by WM x WN wavefronts; `lds` holds kLdsBytes.  acc: the wavefront's TM x TN blocks of 32 x 32, at rows wm0.. and columns wn0..
 // of the tile.
-template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC, int KG = 1>
+template <int BM, int BN, int WM, int WN, int KS, bool AKC, bool BKC, int KG = 1, bool AIDX = false, bool BIDX = false>
 struct SplitGemm {
     static constexpr int T = 64 * WM * WN, TM = BM / 32 / WM, TN = BN / 32 / WN;     // threads, 32 x 32 blocks of a wavefront
-    using TA = SplitTile<BM, KS, AKC, T, KG>;
-    using TB = SplitTile<BN, KS, BKC, T, KG>;
+    using TA = SplitTile<BM, KS, AKC, T, KG, AIDX>;
+    using TB = SplitTile<BN, KS, BKC, T, KG, BIDX>;
     static constexpr int kFlag = 3 * (TA::kPlane + TB::kPlane);              // where the flag lies, in bf16 elements
     static constexpr int kLdsBytes = kFlag * 2 + 16;
     TA ta;
@@ -410,10 +421,12 @@ struct SplitGemm {
 
 // The wavefront's block by the fp32 instruction, straight from memory: rows a_r0.. of A and b_r0.. of B (clamped to
 // the last), q0 <= q < q_end.
-template <int TM, int TN, bool AKC, bool BKC>
+template <int TM, int TN, bool AKC, bool BKC, bool AIDX = false, bool BIDX = false>
 __device__ __forceinline__ void plain_tile(const float* A, int64_t lda, int64_t a_r0, int64_t a_end, const float* B,
                                         int64_t ldb, int64_t b_r0, int64_t b_end, int64_t q0, int64_t q_end,
-                                        f32x16 (&acc)[TM][TN]) {
+                                        f32x16 (&acc)[TM][TN], const int32_t* idx = nullptr) {
+    auto row_a = [&](int64_t r) { return AIDX ? (int64_t)idx[r] : r; };
+    auto row_b = [&](int64_t r) { return BIDX ? (int64_t)idx[r] : r; };
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
 #pragma unroll
     for (int i = 0; i < TM; ++i)
@@ -430,14 +443,14 @@ __device__ __forceinline__ void plain_tile(const float* A, int64_t lda, int64_t 
         for (int i = 0; i < TM; ++i) {
             int64_t r = a_r0 + 32 * i + li;
             r = r < a_end ? r : a_end - 1;
-            fa[i] = AKC ? A[r * lda + qq] : A[qq * lda + r];
+            fa[i] = AKC ? A[row_a(r) * lda + qq] : A[row_a(qq) * lda + r];
             fa[i] = in ? fa[i] : 0.f;
         }
 #pragma unroll
         for (int j = 0; j < TN; ++j) {
             int64_t r = b_r0 + 32 * j + li;
             r = r < b_end ? r : b_end - 1;
-            fb[j] = BKC ? B[r * ldb + qq] : B[qq * ldb + r];
+            fb[j] = BKC ? B[row_b(r) * ldb + qq] : B[row_b(qq) * ldb + r];
             fb[j] = in ? fb[j] : 0.f;
         }
 #pragma unroll

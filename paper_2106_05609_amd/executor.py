@@ -49,6 +49,7 @@ class BatchGraph:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
             part("gcn_norm_csr", lambda: B.gas_gcn_norm(rowptr, col, n_id, deg, self.val))
         self._src = self._src_first = None
+        self._groups = None
         self.csc_pos = csc_pos       # int32[nnz]: position of every CSC entry in the CSR arrays (PNA / GAT backward)
         self._n_id_host = None
         self._plan_t_all, self._max_F = None, max_F
@@ -75,6 +76,18 @@ class BatchGraph:
         if self._plan_t_all is None:
             self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row)
         return self._plan_t_all
+
+    @property
+    def groups(self):
+        """The in-batch rows by degree (gas_pna_groups; max_row is the largest), built on first use, once per batch, and complete
+        when this returns: any stream may read it.  None while a graph is captured that would record the building instead."""
+        if self._groups is None:
+            if torch.cuda.is_current_stream_capturing():
+                return None
+            groups = B.gas_pna_groups(self.rowptr, self.max_row)
+            torch.cuda.current_stream().synchronize()
+            self._groups = groups
+        return self._groups
 
     @property
     def n_id_host(self):
@@ -902,6 +915,22 @@ def appnp_forward_batch(w1, w2, alpha, n_steps, bg: BatchGraph, x_feat, historie
     return y
 
 
+# Rows from which on PNA's transforms go by degree, and their products' terms (rows x columns x outputs).
+PNA_GROUPED_ROWS, PNA_GROUPED_TERMS = 24_576, 2_000_000_000
+
+
+def _by_degree(bg: BatchGraph, x, w2):
+    """The batch's rows by degree if a PNA layer's transforms take them so (gas_pna_linear), else None: fp32, degrees up to
+    PNA_MAX_DEGREE, and enough work that fewer columns outweigh the tiles that a degree fills in part, the degrees' matrices
+    and two launches more.  Passes of three layers, us without -> with: 50,000 rows of 256 -> 256 forward 906 -> 758, training
+    2,790 -> 2,471, 128 -> 128 414 -> 398 and 1,536 -> 1,415; but 100 -> 64 313 -> 311 and 1,083 -> 1,177, 16,000 rows of
+    256 -> 256 359 -> 357 and 1,110 -> 1,090, 8,000 238 -> 264 and 722 -> 755."""
+    if x.dtype != torch.float32 or bg.max_row > B.PNA_MAX_DEGREE or bg.nb < PNA_GROUPED_ROWS or \
+            bg.nb * w2.shape[0] * w2.shape[1] < PNA_GROUPED_TERMS or bg.nb < 512 * (bg.max_row + 1):
+        return None
+    return bg.groups
+
+
 def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None):
     """One PNA layer (paper, operator appendix) for the in-batch rows: h'_v = W2 [h_v, (+)_w W1 [h_v, h_w]].
     x: mini-batch tensor [nv, F]; w1 [2F, F1] (rows 0..F-1 multiply the receiving node, rows F.. the neighbour),
@@ -924,6 +953,21 @@ def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None):
     return y
 
 
+def _pna_messages(bg: BatchGraph, x, w1, delta, blocks):
+    """The neighbour part of the messages of every row of x and [h | aggregates]: the aggregators' `blocks` (9, or 3 without the
+    scaled ones)."""
+    dev, dt, nb = x.device, x.dtype, bg.nb
+    f, f1 = x.shape[1], w1.shape[1]
+    p = torch.empty((x.shape[0], f1), dtype=dt, device=dev)
+    B.gas_linear(x, w1[f:], p)
+    q = torch.empty((nb, f1), dtype=dt, device=dev)
+    B.gas_linear(x[:nb], w1[:f], q)
+    cat = torch.empty((nb, f + blocks * f1), dtype=dt, device=dev)
+    B.gas_pull(x, None, cat[:, :f], base=0, n=nb)                 # h_v into the first F columns (a strided row copy)
+    B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q)
+    return p, cat
+
+
 def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push=True):
     """All layers of a PNA model for one mini-batch in the order of Algorithm 1; weights[l] = (W1, W2)."""
     dev, dt = x_feat.device, x_feat.dtype
@@ -936,7 +980,13 @@ def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push
         w1, w2 = weights[l - 1]
         last = l == L
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
-        y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb])
+        groups = _by_degree(bg, x, w2)
+        if groups is None:
+            y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb])
+        else:
+            y, f, f1 = x_next[:nb], x.shape[1], w1.shape[1]
+            cat = _pna_messages(bg, x, w1, delta, 3)[1]
+            B.gas_pna_linear(groups, bg.max_row, cat, w2, f1, delta, y, relu=not last)
         if last:
             break
         if do_push:
@@ -1003,18 +1053,15 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
     for l in range(1, L + 1):
         w1, w2 = weights[l - 1]
         last = l == L
-        f, f1 = x.shape[1], w1.shape[1]
-        p = torch.empty((nv, f1), dtype=dt, device=dev)
-        B.gas_linear(x, w1[f:], p)
-        q = torch.empty((nb, f1), dtype=dt, device=dev)
-        B.gas_linear(x[:nb], w1[:f], q)
-        cat = torch.empty((nb, f + 9 * f1), dtype=dt, device=dev)
-        B.gas_pull(x, None, cat[:, :f], base=0, n=nb)
-        B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q)
+        groups = _by_degree(bg, x, w2)
+        p, cat = _pna_messages(bg, x, w1, delta, 9)
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
         pushed = not last and _pushes(do_push, histories[l - 1])
-        if pushed:
+        if groups is not None:
+            B.gas_pna_linear(groups, bg.max_row, cat, w2, w1.shape[1], delta, y, relu=not last, idx=bg.n_id[:nb] if pushed else None,
+                             hist=histories[l - 1] if pushed else None)
+        elif pushed:
             B.gas_linear_push(cat, w2, y, bg.n_id[:nb], histories[l - 1], relu=True)
         else:
             B.gas_linear(cat, w2, y, relu=not last)
@@ -1029,9 +1076,16 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         w1, w2 = weights[l - 1]
         x, p, cat, _ = kept[l - 1]            # g: the gradient before this layer's activation
         f, f1 = x.shape[1], w1.shape[1]
-        dw2 = wg.add(cat, g)
-        gcat = torch.empty_like(cat)
-        B.gas_linear_bwd_input(g, w2, gcat)
+        groups = _by_degree(bg, x, w2)
+        if groups is not None:
+            dw2 = torch.empty(w2.shape, dtype=torch.float32, device=dev)
+            B.gas_pna_linear_bwd_weight(groups, bg.max_row, cat, g, f1, delta, dw2)
+            gcat = torch.empty((nb, f + 3 * f1), dtype=dt, device=dev)       # the nine blocks folded with their scalers
+            B.gas_pna_linear_bwd_input(groups, bg.max_row, g, w2, f1, delta, gcat)
+        else:
+            dw2 = wg.add(cat, g)
+            gcat = torch.empty_like(cat)
+            B.gas_linear_bwd_input(g, w2, gcat)
         gp = torch.empty((nv, f1), dtype=dt, device=dev)
         gq = torch.empty((nb, f1), dtype=dt, device=dev)
         B.gas_pna_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, gcat[:, f:], gp, delta, gadd=gq,

@@ -66,3 +66,14 @@ def test_shared_workspace_of_the_weight_gradients_is_bounded(together, monkeypat
     assert all(need <= 128 << 20 or count == 1 for count, need, _ in calls)
     assert [p for _, _, dws in calls for p in dws] == [dw.data_ptr() for _, _, dw, _ in items]
     assert max(count for count, _, _ in calls) >= 6
+
+
+@pytest.mark.parametrize("rows,longest,f,f1,out,dtype,grouped", [
+    (50_000, 26, 256, 64, 256, torch.float32, True), (50_000, 41, 128, 32, 128, torch.float32, True),
+    (50_000, 26, 100, 16, 64, torch.float32, False), (16_000, 24, 256, 64, 256, torch.float32, False),
+    (50_000, 64, 256, 64, 256, torch.float32, False), (50_000, 26, 256, 64, 256, torch.bfloat16, False)])
+def test_which_pna_layers_go_by_degree(rows, longest, f, f1, out, dtype, grouped):
+    class Batch:
+        nb, max_row, groups = rows, longest, "groups"
+    got = executor._by_degree(Batch, torch.empty(0, f, dtype=dtype), torch.empty(f + 9 * f1, out))
+    assert (got == "groups") == grouped

@@ -1,0 +1,108 @@
+"""PNA's transform by the rows' degrees (gas_pna_linear and its backward calls) against 64 bits, and the executor's passes by
+degree against its passes without."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(n, most, gen):
+    d = torch.randint(0, most + 1, (n,), generator=gen)
+    d[: min(n, 3)] = torch.tensor([most, 0, most])[: min(n, 3)]
+    return d, torch.cat([torch.zeros(1, dtype=torch.long), d.cumsum(0)]).int().cuda()
+
+
+# one row; a tile and a slab and their neighbours; degrees that no row has; widths of one tile and of several, that nothing divides
+@pytest.mark.parametrize("n,most", [(1, 0), (1, 5), (127, 0), (129, 0), (513, 1), (1025, 63), (5000, 12)])
+@pytest.mark.parametrize("f,f1,n_out", [(8, 8, 8), (64, 16, 64), (33, 11, 47), (256, 64, 256)])
+def test_products_by_degree(n, most, f, f1, n_out):
+    import paper_2106_05609_amd as gas
+    from paper_2106_05609_amd import binding as B
+    gen = torch.Generator().manual_seed(n + f)
+    d, ptr = _rows(n, most, gen)
+    delta = 1.7
+    x = torch.randn(n, f + 9 * f1, generator=gen)
+    x[d == 0, f:] = 0.0                                        # a row without entries has zero aggregates
+    w, g = torch.randn(f + 9 * f1, n_out, generator=gen), torch.randn(n, n_out, generator=gen)
+    s = torch.log(d.double() + 1.0)[:, None] / delta
+    inv = torch.where(d[:, None] > 0, 1.0 / s, torch.zeros_like(s))
+    a = x[:, f:f + 3 * f1].double()
+    full = torch.cat([x[:, :f].double(), a, s * a, inv * a], 1)
+    mag = full.abs() @ w.double().abs()
+    groups = B.gas_pna_groups(ptr, most)
+    X, W, G = x.cuda(), w.cuda(), g.cuda()
+    hist, ids = torch.zeros(2 * n, n_out, device="cuda"), torch.randperm(2 * n, generator=gen)[:n].int().cuda()
+    for relu in (False, True):
+        y = torch.full((n, n_out), 5.0, device="cuda")
+        B.gas_pna_linear(groups, most, X, W, f1, delta, y, relu=relu, idx=ids if relu else None, hist=hist if relu else None)
+        want = full @ w.double()
+        # a rounding per term of the sum, of the scaled blocks and of the scaler itself
+        err = (y.cpu().double() - (want.clamp(min=0) if relu else want)).abs()
+        assert (err <= 32 * 2.0 ** -24 * mag).all()
+    assert torch.equal(hist[ids.long()], y) and hist.count_nonzero() == y.count_nonzero()
+    gx = torch.full((n, f + 3 * f1), 5.0, device="cuda")
+    B.gas_pna_linear_bwd_input(groups, most, G, W, f1, delta, gx)
+    nine = g.double() @ w.double().t()
+    cut = [nine[:, f + 3 * f1 * k:f + 3 * f1 * (k + 1)] for k in range(3)]
+    nine_abs = g.double().abs() @ w.double().abs().t()
+    cut_abs = [nine_abs[:, f + 3 * f1 * k:f + 3 * f1 * (k + 1)] for k in range(3)]
+    want = torch.cat([nine[:, :f], cut[0] + s * cut[1] + inv * cut[2]], 1)
+    bound = torch.cat([nine_abs[:, :f], cut_abs[0] + s * cut_abs[1] + inv * cut_abs[2]], 1)
+    assert ((gx.cpu().double() - want).abs() <= 32 * 2.0 ** -24 * bound).all()
+    dw = torch.full((f + 9 * f1, n_out), 5.0, device="cuda")
+    B.gas_pna_linear_bwd_weight(groups, most, X, G, f1, delta, dw)
+    bound = full.abs().t() @ g.double().abs()
+    assert ((dw.cpu().double() - full.t() @ g.double()).abs() <= (32 + n ** 0.5) * 2.0 ** -24 * bound).all()
+
+
+def test_infinite_and_tiny_values_by_degree():
+    """A non-finite value takes its block by the fp32 instruction, a tiny one its tile scaled: what fp32 arithmetic gives."""
+    from paper_2106_05609_amd import binding as B
+    gen = torch.Generator().manual_seed(5)
+    n, f, f1, n_out = 700, 64, 16, 64
+    d, ptr = _rows(n, 4, gen)
+    d = d.clamp(min=0)
+    x, w = torch.randn(n, f + 9 * f1, generator=gen), torch.randn(f + 9 * f1, n_out, generator=gen)
+    x[d == 0, f:] = 0.0
+    x[11] *= 2.0 ** -120
+    x[500, 3] = float("inf")
+    groups, y = B.gas_pna_groups(ptr, 4), torch.empty(n, n_out, device="cuda")
+    B.gas_pna_linear(groups, 4, x.cuda(), w.cuda(), f1, 1.3, y)
+    s = torch.log(d.double() + 1.0)[:, None] / 1.3
+    a = x[:, f:f + 3 * f1].double()
+    full = torch.cat([x[:, :f].double(), a, s * a, torch.where(d[:, None] > 0, a / s, torch.zeros_like(a))], 1)
+    want, got = full @ w.double(), y.cpu().double()
+    fine = torch.isfinite(want).all(1)
+    assert not fine[500] and fine.sum() == n - 1 and torch.equal(got[500].sign(), want[500].sign()) and got[500].isinf().all()
+    err = ((got - want)[fine]).abs()
+    assert (err <= 32 * 2.0 ** -24 * (full.abs() @ w.double().abs())[fine]).all()
+
+
+@pytest.mark.parametrize("f,hidden", [(40, 64), (64, 96)])
+def test_passes_by_degree_agree_with_passes_without(f, hidden, monkeypatch):
+    from gas_inputs import batches, graphs
+    from paper_2106_05609_amd import binding as B, executor
+    dev = torch.device("cuda")
+    g = graphs.sbm_partners(40_000, 6, 6.0, 0.85, 3, dev)
+    sg = batches.batch_subgraph(g, batches.split(g, 2, 0)[0], self_loops=False)
+    gen = torch.Generator(device=dev).manual_seed(1)
+    normal = lambda *shape: torch.randn(*shape, generator=gen, device=dev)
+    widths = [f, hidden, hidden]
+    ws = [(normal(2 * i, max(8, o // 4)) / i ** 0.5, normal(i + 9 * max(8, o // 4), o) / (3 * i) ** 0.5) for i, o in zip(widths, widths[1:])]
+    x, table, grad = normal(40_000, f), normal(40_000, hidden).clamp_(min=0), normal(sg.nb, hidden)
+    out = []
+    monkeypatch.setattr(executor, "PNA_GROUPED_TERMS", 0)
+    for least in (10_000, 1 << 40):
+        monkeypatch.setattr(executor, "PNA_GROUPED_ROWS", least)
+        bg = executor.BatchGraph(sg.nb, sg.n_id, sg.rowptr, sg.col, g.deg, sg.colptr, sg.row, max_F=256, normalise=False, csc_pos=sg.csc_perm)
+        assert bg.max_row <= B.PNA_MAX_DEGREE
+        h = [table.clone()]
+        y = executor.pna_forward_batch(ws, 2.0, bg, x, h)
+        assert (bg._groups is not None) == (least < 1 << 40)
+        h2 = [table.clone()]
+        y2, grads, kept = executor.pna_train_batch(ws, 2.0, bg, x, h2, grad)
+        out.append([y, y2, h[0], h2[0]] + [t for pair in (grads[l] for l in range(2)) for t in pair] + [kept[0][2], kept[1][2]])
+    for a, b in zip(*out):
+        # gradients: a hidden unit within rounding of zero, or a tie for an extreme, may fall on either side
+        assert (a - b).norm() <= (1e-5 if a is out[0][0] or a is out[0][1] else 4e-3) * b.norm()
