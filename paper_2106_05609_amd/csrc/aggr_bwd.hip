@@ -501,7 +501,7 @@ constexpr int kMaxPerLane = 16;                      // features per lane: F <= 
 
 struct GatBwdArgs {
     const int32_t* rowptr; const int32_t* col; int64_t n_rows;
-    const int32_t* colptr; const int32_t* row; const int32_t* csc_pos; int64_t n_cols, n_out;
+    const int32_t* colptr; const int32_t* row; const int32_t* csc_pos; int64_t n_cols, n_out, nnz;
     const char* P; int64_t ldp;
     const char* a_dst; const char* a_src;
     const char* GZ; int64_t ldgz;
@@ -626,8 +626,9 @@ __global__ __launch_bounds__(64) void gat_bwd_cols_kernel(GatBwdArgs a) {
 // attention weight) reduced over the team's lanes eight entries at a time.  W = 1: one wavefront has the whole row.
 // W = kLongWaves: the wavefronts of a workgroup take the row's blocks of 64 entries in turn (wavefront w the blocks
 // w, w + W, ...) and meet for the row's maximum and its three sums, which are added in wavefront order; `red` is
-// their LDS.  Either way an entry's pair is stored and read again by one and the same lane (lane tl < 8 of a team has
-// the slot's tl-th entry of a block), so no lane ever reads another lane's store.
+// their LDS.  Either way an entry's pair is stored and read again by one and the same lane (the first of every G / 8 lanes of
+// a team: lane j G / 8 has the slot's j-th entry of a block, where the reductions leave its sums), so no lane ever
+// reads another lane's store.
 template <bool BF, int G, int H, int W>
 __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int b, int e, float (*red)[4]) {
     constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = HeadTeams<G, H>::kSlots;
@@ -635,6 +636,8 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
     const int lane = threadIdx.x & 63;
     const int first = W == 1 ? 0 : (int)(threadIdx.x >> 6);
     const bool on = ht.tl * E < a.F, writer = ht.tl == 0 && ht.slot == 0;
+    const int mine_j = ht.tl / (G / 8);                                // of eight entries, the one whose sums this lane has
+    const bool owner = ht.tl % (G / 8) == 0;
     const int64_t own = (int64_t)ht.head * a.F + ht.tl * E;            // the lane's first column
     auto piece = [&](const char* base, int64_t row_elems) {
         u32x4 t = {0u, 0u, 0u, 0u};
@@ -669,7 +672,7 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
                 r[j] = u32x4{0u, 0u, 0u, 0u};
                 if (on && kk < cnt) r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + own) * EB);
             }
-            float sw[U], da[U];
+            float sw[U], da[U];                // this lane's share, of eight entries
 #pragma unroll
             for (int j = 0; j < U; ++j) {
                 unpack<BF>(r[j], x);
@@ -681,17 +684,10 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
                     da[j] = fmaf(gz[i], x[i], da[j]);
                 }
             }
-            team_sum8<G>(sw);
-            team_sum8<G>(da);
-            f32x2_t kept = {0.f, 0.f};
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                const float t = sv + sw[j];
-                if (j0 + j * S + ht.slot < cnt) mx = fmaxf(mx, t > 0.f ? t : a.slope * t);
-                if (ht.tl == j) kept = f32x2_t{t, da[j]};
-            }
-            const int kk = j0 + ht.tl * S + ht.slot;
-            const bool mine_too = ht.tl < U && kk < cnt;
+            f32x2_t kept = {sv + team_sum8_own<G>(sw), team_sum8_own<G>(da)};
+            const int kk = j0 + mine_j * S + ht.slot;
+            if (kk < cnt) mx = fmaxf(mx, kept[0] > 0.f ? kept[0] : a.slope * kept[0]);
+            const bool mine_too = owner && kk < cnt;
             // The gradient is not continuous where a score is zero (LeakyReLU): a score within 2^-20 of zero beside its
             // terms of P[v] and its other half, about one in 10^5, is formed again in 64 bits from rows read again.  (An
             // other half whose own terms cancel is not noticed.  Scores all of whose terms are zero are zero: attention
@@ -711,7 +707,7 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
                     for (int i = 0; i < E; ++i) s += (double)xd[i] * xv[i] + (double)xs[i] * xw[i];
 #pragma unroll
                     for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o);
-                    if (near && ht.tl == j) kept[0] = (float)s;
+                    if (near && mine_j == j) kept[0] = (float)s;
                 }
             }
             if (mine_too) a.pair[(int64_t)(k0 + kk) * H + ht.head] = kept;
@@ -720,13 +716,13 @@ __device__ __forceinline__ void gat_bwd_row(const GatBwdArgs& a, int64_t v, int 
     // the lane's own entries once more
     auto each = [&](auto&& fn) {
         for (int k0 = b + 64 * first; k0 < e; k0 += 64 * W)
-            for (int kk = ht.tl * S + ht.slot; kk < min(64, e - k0); kk += U * S)
-                if (ht.tl < U) fn(a.pair[(int64_t)(k0 + kk) * H + ht.head]);
+            for (int kk = mine_j * S + ht.slot; kk < min(64, e - k0); kk += U * S)
+                if (owner) fn(a.pair[(int64_t)(k0 + kk) * H + ht.head]);
     };
     auto total = [&](float x) {
         return across_waves_by_head<W, false>(HeadTeams<G, H>::over_slots(team_sum<G>(x)), ht.head, writer, red);
     };
-    mx = across_waves_by_head<W, true>(HeadTeams<G, H>::max_over_slots(mx), ht.head, writer, red);
+    mx = across_waves_by_head<W, true>(HeadTeams<G, H>::max_over_slots(team_max8<G>(mx)), ht.head, writer, red);
     float den = 0.f;
     each([&](f32x2_t& p) { den += expf((p[0] > 0.f ? p[0] : a.slope * p[0]) - mx); });
     den = total(den);
@@ -777,10 +773,10 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_rows_kernel(GatB
 // rows of GZ in flight per lane with the entries' pairs beside them; afterwards every slot holds the sums
 // acc = sum alpha GZ[v] (for u < n_out) and ts = sum dt.  One gather does what a permutation of the pairs into column
 // order, column totals, an aggregation per head and a rank-one update did in six launches a head.
-template <bool BF, int G, int H>
+template <bool BF, int G, int H, int U>
 __device__ __forceinline__ void gat_bwd_col(const GatBwdArgs& a, int64_t u, int b, int e, int first, int stride, float& ts,
                                             float (&acc)[Elems<BF>::E]) {
-    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, U = 8, S = HeadTeams<G, H>::kSlots;
+    constexpr int E = Elems<BF>::E, EB = BF ? 2 : 4, S = HeadTeams<G, H>::kSlots;
     const HeadTeams<G, H> ht;
     const int lane = threadIdx.x & 63;
     const bool on = ht.tl * E < a.F && u < a.n_out;
@@ -812,7 +808,7 @@ __device__ __forceinline__ void gat_bwd_col(const GatBwdArgs& a, int64_t u, int 
                     if (on) r[j] = *reinterpret_cast<const u32x4*>(gz + (int64_t)v * a.ldgz * EB);
                 }
             }
-            float tb = 0.f, part[E];                       // eight entries by themselves first, as in the forward pass
+            float tb = 0.f, part[E];                       // U entries by themselves first, as in the forward pass
 #pragma unroll
             for (int i = 0; i < E; ++i) part[i] = 0.f;
 #pragma unroll
@@ -854,15 +850,19 @@ __device__ __forceinline__ void gat_bwd_col_finish(const GatBwdArgs& a, int64_t 
 // one wavefront per column, 2^25 columns per blockIdx.y (a launch's first dimension holds at most 2^32 - 1 threads: 67 M
 // columns); long columns are left to gat_bwd_long_cols_kernel.  (A loop over the columns instead of the second dimension
 // made one head of 256 floats without a plan 10 % slower.)
-constexpr int64_t kColBlocks = 1 << 25;
-template <bool BF, int G, int H>
+// U entries of a slot in flight: four where columns are short (most are a halo node's, of one or two entries), so that twice
+// the wavefronts find registers, else eight.  A training pass, us with eight and four: 115,000 columns of 4.8 entries, four heads
+// of 64 floats, 1,566 and 1,521, 57,000 of 4 of 32 bf16 529 and 495; but power-law columns of more than seven 3,807 and 4,065,
+// bf16 1,974 and 2,100.  By two entries 489-4,383.
+constexpr int64_t kColBlocks = 1 << 25, kShortColumn = 7;
+template <bool BF, int G, int H, int U>
 __global__ __launch_bounds__(64) void gat_bwd_cols_vec_kernel(GatBwdArgs a) {
     const int64_t u = blockIdx.x + blockIdx.y * kColBlocks;
     if (u >= a.n_cols) return;
     const int b = a.colptr[u], e = a.colptr[u + 1];
     if (e - b > kLongRow) return;
     float ts, acc[Elems<BF>::E];
-    gat_bwd_col<BF, G, H>(a, u, b, e, 0, 1, ts, acc);
+    gat_bwd_col<BF, G, H, U>(a, u, b, e, 0, 1, ts, acc);
     gat_bwd_col_finish<BF, G, H>(a, u, ts, acc);
 }
 
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_cols_kernel(GatB
         for (int q = 0; q < nq; ++q) {
             const int64_t u = queue[q];
             float ts, acc[E];
-            gat_bwd_col<BF, G, H>(a, u, a.colptr[u], a.colptr[u + 1], w, kLongWaves, ts, acc);
+            gat_bwd_col<BF, G, H, 8>(a, u, a.colptr[u], a.colptr[u + 1], w, kLongWaves, ts, acc);
             if (w > 0) {
                 red[w][E][lane] = ts;
 #pragma unroll
@@ -906,7 +906,8 @@ void launch_gat_bwd(const GatBwdArgs& a, bool columns, hipStream_t s) {
     }
     if (!columns) return;
     const dim3 cols((unsigned)(a.n_cols < kColBlocks ? a.n_cols : kColBlocks), (unsigned)((a.n_cols + kColBlocks - 1) / kColBlocks));
-    hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H>), cols, dim3(64), 0, s, a);
+    if (a.nnz <= kShortColumn * a.n_cols) hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H, 4>), cols, dim3(64), 0, s, a);
+    else hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H, 8>), cols, dim3(64), 0, s, a);
     hipLaunchKernelGGL((gat_bwd_long_cols_kernel<BF, G, H>), dim3(long_row_blocks(a.n_cols)), dim3(64 * kLongWaves), 0, s, a);
 }
 
@@ -1310,7 +1311,7 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
     const int H = !vec ? 1 : (bf ? gat_heads_together<true>(F, heads) : gat_heads_together<false>(F, heads));
     GatBwdArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;
-    a.colptr = colptr; a.row = row; a.csc_pos = csc_pos; a.n_cols = n_cols; a.n_out = n_out;
+    a.colptr = colptr; a.row = row; a.csc_pos = csc_pos; a.n_cols = n_cols; a.n_out = n_out; a.nnz = nnz;
     a.P = static_cast<const char*>(P); a.ldp = ldp;
     a.a_dst = static_cast<const char*>(a_dst); a.a_src = static_cast<const char*>(a_src);
     a.GZ = static_cast<const char*>(GZ); a.ldgz = ldgz;

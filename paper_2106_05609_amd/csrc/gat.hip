@@ -84,7 +84,7 @@ __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, i
                 if (on && kk < cnt)
                     r[j] = *reinterpret_cast<const u32x4*>(a.P + ((int64_t)c * a.ldp + own) * EB);
             }
-            float sc[U], mb = m;
+            float sc[U];
 #pragma unroll
             for (int j = 0; j < U; ++j) {
                 unpack<BF>(r[j], x);
@@ -92,23 +92,21 @@ __device__ __forceinline__ void gat_gather(const GatArgs& a, int64_t v, int b, i
 #pragma unroll
                 for (int i = 0; i < E; ++i) sc[j] += ar[i] * x[i];
             }
-            team_sum8<G>(sc);
-#pragma unroll
-            for (int j = 0; j < U; ++j) {
-                float s = sc[j] + sv;
-                s = s > 0.f ? s : a.slope * s;
-                sc[j] = j0 + j * S + team < cnt ? s : -INFINITY;
-                mb = fmaxf(mb, sc[j]);
-            }
+            // a lane has one of the eight scores, and its weight: formed by every lane they are most of the instructions
+            float s = team_sum8_own<G>(sc) + sv;
+            s = s > 0.f ? s : a.slope * s;
+            s = j0 + ht.tl / (G / 8) * S + team < cnt ? s : -INFINITY;
+            const float mb = fmaxf(m, team_max8<G>(s));
             if (mb > -INFINITY) {                         // a team may have had no entry of its own yet
                 const float scale = expf(m - mb);         // m = -inf at the start: scale 0 on sums that are 0
                 // the eight entries are summed by themselves first: a sum over a long row is then one of few large terms
+                const float own_p = expf(s - mb);         // 0 for the padding entries
                 float lb = 0.f, part[E];
 #pragma unroll
                 for (int i = 0; i < E; ++i) part[i] = 0.f;
 #pragma unroll
                 for (int j = 0; j < U; ++j) {
-                    const float p = expf(sc[j] - mb);     // 0 for the padding entries
+                    const float p = team_value8<G>(own_p, j);
                     lb += p;
                     unpack<BF>(r[j], x);
 #pragma unroll

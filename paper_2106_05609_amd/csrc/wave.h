@@ -11,35 +11,6 @@ __device__ __forceinline__ float wave_sum(float v) {
     return v;
 }
 
-// Eight lane reductions at once: at each of the first three steps a lane keeps one half of its values, adds
-// the partner's copy of that half and hands over the other half, so 4 + 2 + 1 exchanges leave one partial sum per
-// lane; three more steps finish it, and the eight totals are read back from the lanes that hold them.  Ten
-// exchanges instead of forty-eight.  Value j ends up in the lanes whose bits 5..3 spell j.
-__device__ __forceinline__ void wave_sum8(float (&s)[8]) {
-    const int lane = threadIdx.x & 63;
-    float t4[4], t2[2];
-    const bool h5 = lane & 32, h4 = lane & 16, h3 = lane & 8;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float keep = h5 ? s[j + 4] : s[j], send = h5 ? s[j] : s[j + 4];
-        t4[j] = keep + __shfl_xor(send, 32);
-    }
-#pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float keep = h4 ? t4[j + 2] : t4[j], send = h4 ? t4[j] : t4[j + 2];
-        t2[j] = keep + __shfl_xor(send, 16);
-    }
-    float t = (h3 ? t2[1] : t2[0]) + __shfl_xor(h3 ? t2[0] : t2[1], 8);
-    t += __shfl_xor(t, 4);
-    t += __shfl_xor(t, 2);
-    t += __shfl_xor(t, 1);
-    // lane bits (5, 4, 3) = (j >> 2 & 1, j >> 1 & 1, j & 1): value j sits in lanes 32 (j>>2&1) + 16 (j>>1&1) + 8 (j&1)
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        s[j] = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, t),
-                                                                  32 * ((j >> 2) & 1) + 16 * ((j >> 1) & 1) + 8 * (j & 1)));
-}
-
 // Sum over the G lanes of a team: the wavefront's aligned groups of G lanes, G a power of two.
 template <int G>
 __device__ __forceinline__ float team_sum(float v) {
@@ -48,35 +19,31 @@ __device__ __forceinline__ float team_sum(float v) {
     return v;
 }
 
-// wave_sum8 inside every team of G = 8, 16 or 32 lanes (G = 64: wave_sum8 itself): the same halving exchanges on the team's three upper lane
-// bits, the remaining steps on the lower ones, and every lane reads the eight totals back from its own team.
+// Eight sums over the lanes of every team of G at once: at each of the first three steps a lane keeps one half of its values,
+// adds the partner's copy of that half and hands over the other half, so 4 + 2 + 1 exchanges leave one partial sum per lane,
+// and the remaining steps finish it: seven exchanges and more instead of 8 log2 G.  The lane's return value is the total of
+// s[tl / (G / 8)], tl its number in the team.
 template <int G>
-__device__ __forceinline__ void team_sum8(float (&s)[8]) {
+__device__ __forceinline__ float team_sum8_own(const float (&s)[8]) {
     static_assert(G == 8 || G == 16 || G == 32 || G == 64, "teams of 8 to 64 lanes");
-    if constexpr (G == 64) {
-        wave_sum8(s);
-        return;
-    }
     const int lane = threadIdx.x & 63;
-    float t4[4], t2[2];
     const bool ha = lane & (G / 2), hb = lane & (G / 4), hc = lane & (G / 8);
+    float t4[4], t2[2];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        const float keep = ha ? s[j + 4] : s[j], send = ha ? s[j] : s[j + 4];
-        t4[j] = keep + __shfl_xor(send, G / 2);
-    }
+    for (int j = 0; j < 4; ++j) t4[j] = (ha ? s[j + 4] : s[j]) + __shfl_xor(ha ? s[j] : s[j + 4], G / 2);
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-        const float keep = hb ? t4[j + 2] : t4[j], send = hb ? t4[j] : t4[j + 2];
-        t2[j] = keep + __shfl_xor(send, G / 4);
-    }
+    for (int j = 0; j < 2; ++j) t2[j] = (hb ? t4[j + 2] : t4[j]) + __shfl_xor(hb ? t4[j] : t4[j + 2], G / 4);
     float t = (hc ? t2[1] : t2[0]) + __shfl_xor(hc ? t2[0] : t2[1], G / 8);
 #pragma unroll
     for (int o = G / 16; o > 0; o >>= 1) t += __shfl_xor(t, o);
-    const int base = lane & ~(G - 1);
+    return t;
+}
+// The largest of the eight values that the lanes of a team hold so.
+template <int G>
+__device__ __forceinline__ float team_max8(float v) {
 #pragma unroll
-    for (int j = 0; j < 8; ++j)
-        s[j] = __shfl(t, base + (G / 2) * ((j >> 2) & 1) + (G / 4) * ((j >> 1) & 1) + (G / 8) * (j & 1));
+    for (int o = G / 2; o >= G / 8; o >>= 1) v = fmaxf(v, __shfl_xor(v, o));
+    return v;
 }
 
 // ---- several attention heads in one wavefront
@@ -178,6 +145,14 @@ inline int gat_heads_together(int32_t F, int32_t heads) {
     int H = 1;
     while (H < 4 && heads % (2 * H) == 0 && gat_team<BF>(F, false) * 2 * H <= 64) H *= 2;
     return H;
+}
+
+template <int G> __device__ __forceinline__ int team_lane(int v, int u);
+// Value j of the eight that the lanes of a team hold as team_sum8_own leaves them; j a constant wherever this is called.
+template <int G>
+__device__ __forceinline__ float team_value8(float v, int j) {
+    if constexpr (G <= 16) return __int_as_float(team_lane<G>(__float_as_int(v), j * (G / 8)));
+    else return __shfl(v, (threadIdx.x & 63 & ~(G - 1)) + j * (G / 8));
 }
 
 // Lane u of every team of G lanes to the whole team, by data-parallel moves (row_newbcast: one lane of each 16; for teams
