@@ -36,6 +36,12 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kWave = 64;
 
+// A load from an address that was put together from integers: of global memory, not a flat one.
+template <class T>
+__device__ __forceinline__ T load_global(uint64_t address) {
+    return *reinterpret_cast<const __attribute__((address_space(1))) T*>(address);
+}
+
 __device__ __forceinline__ float bf16_lo(uint32_t u) { return __uint_as_float(u << 16); }
 __device__ __forceinline__ float bf16_hi(uint32_t u) { return __uint_as_float(u & 0xFFFF0000u); }
 

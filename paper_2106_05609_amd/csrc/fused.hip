@@ -48,11 +48,12 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 //      for 128) by all k, so the four wavefronts share the products.  16x16x4 fp32 MFMAs, taken transposed: a lane has four
 //      consecutive columns of a row, which get c_w * acc + c_id * Z + bias and ReLU and are stored to Y and to the
 //      row's history slot as 16 bytes.
-// 64 layers of 21,248 rows, width 64, 15 entries a row: 17.7 us each (with the addresses formed by every lane, 32x32x2
+// 64 layers of 21,248 rows, width 64, 15 entries a row: 16.4 us each (17.7 with the loads past a row's end not switched off: the
+// eight teams of a wavefront go by its longest row, two entries in five more; with the addresses formed by every lane, 32x32x2
 // products by two of the four wavefronts and the weights in LDS 21.9).  Without the gathers 7.6 us, without the transform
 // 13.7: what is left is the gather's chain of two to three batches and the rows that every XCD fetches anew (4.6 TB/s).
 // BWD: the same on the adjoint (gas_spmm_t_relu_linear): the pattern is the CSC copy, the activations of the layer below mask
-// the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 15.7 us
+// the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 14.7 us
 // where the aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
 // <8, 2, 2> spills 7 registers (BWD 11) to keep three wavefronts on a SIMD: 21,248 rows of 50, 64 -> 128, 33.5 us, with two
 // and none spilled 41.9 (rows of 5: 15.4 and 15.7).
@@ -158,10 +159,11 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
                         f32x4 x[U][P];
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
-                            const char* row = reinterpret_cast<const char*>((uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) |
-                                                                            ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32));
-                            x[u][0] = *reinterpret_cast<const f32x4*>(row + off0);
-                            if constexpr (P == 2) x[u][1] = *reinterpret_cast<const f32x4*>(row + off1);
+                            const uint64_t row = (uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) | ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32);
+                            if (G * h + q + u < cnt) {       // a team past its row's end fetches nothing
+                                x[u][0] = load_global<f32x4>(row + off0);
+                                if constexpr (P == 2) x[u][1] = load_global<f32x4>(row + off1);
+                            }
                         }
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
