@@ -347,12 +347,13 @@ GAS_API gas_status gas_spmm_t_relu_linear(const int32_t* colptr, const int32_t* 
                            float c_total, void* total, int64_t ldtotal, void* GZ, int64_t ldgz, void* stream);
 
 /*
- * `count` consecutive layers of one width (gas_spmm_linear with F_in == F_out == F) and their counterparts in the backward pass
- * (gas_spmm_t_relu_linear): layer l reads what layer l - 1 wrote (l = 0: X, backward G).  Same bits as one call per layer.
- * The arrays hist, W, Y, ... are HOST arrays of `count` device pointers, c_identity and c_weight of `count` floats, ld_hist and
- * ld_push of `count` row strides; they are read before the call returns.  hist[l] may be NULL where the layer's indices name no stored row; Z_out, push_idx with
- * push_hist, and any element of Z_out or push_hist, may be NULL (nothing is kept, nothing is pushed).  The first layer may have
- * indices of its own (src_first; else pass src).  Layers but the last apply ReLU, the last as relu_last says.
+ * `count` consecutive layers of one width (gas_spmm_linear with F_in == F_out == F) and their counterparts in the backward
+ * pass (gas_spmm_t_relu_linear): layer l reads what layer l - 1 wrote (l = 0: X, backward G).  Same bits as one call per
+ * layer.  The arrays hist, W, Y, ... are HOST arrays of `count` device pointers, c_identity and c_weight of `count` floats,
+ * ld_hist and ld_push of `count` row strides; they are read before the call returns.  hist[l] may be NULL where the layer's
+ * indices name no stored row; Z_out, push_idx with push_hist, and any element of Z_out or push_hist, may be NULL (nothing is
+ * kept, nothing is pushed).  The first layer may have indices of its own (src_first; else pass src).  Layers but the last
+ * apply ReLU, the last as relu_last says.
  * Y[l] may be written again from layer l + 2 on (two matrices in turn serve a forward pass; the same for GZ), otherwise no
  * output may alias another matrix of the call.
  * One call for a deep narrow model, whose layers take the card less time than a call through a binding takes the host.

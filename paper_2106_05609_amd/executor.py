@@ -160,8 +160,8 @@ def _back_in_one_launch(width, rows, entries, longest) -> bool:
 def _layers_together(model: Model, bg, h0) -> bool:
     """Whether GCNII's layers (all of one width) go in groups by one call (gas_spmm_linear_layers): narrow fp32 layers without long
     rows, of few rows.  A layer takes the host 13 us by a call of its own and 5 in a group.  16 layers of 64, one by one and in
-    groups: 500 rows 214 and 125 us, 5,000 213 and 152, 12,500 221 and 155; 21,248 283 and 282, where the card takes longer
-    than either and a pass that starts on an idle one waits 30 us for its first groups."""
+    groups: 500 rows 245 and 143 us, 5,000 244 and 151, 12,500 246 and 208, 16,000 246 and 224; 21,248 287 and 289, where the card
+    takes longer than either and a pass that starts on an idle one waits 14 us for its first groups."""
     return B.spmm_linear_supported(h0, h0.shape[1]) and bg.max_row <= ONE_LAUNCH_MAX_ROW and model.n_layers >= 2 and 0 < bg.nb <= 16384
 
 
