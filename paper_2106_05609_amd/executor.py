@@ -19,6 +19,14 @@ import torch
 from . import binding as B
 
 
+class _Kept:
+    """An array, the stream that built it and the event after which it is complete."""
+
+    def __init__(self, array, stream):
+        self.array, self.stream, self.event, self.complete = array, stream, torch.cuda.Event(), False
+        self.event.record(stream)
+
+
 class BatchGraph:
     """Device-side index structure of one batch subgraph plus its plans."""
 
@@ -77,17 +85,29 @@ class BatchGraph:
             self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row)
         return self._plan_t_all
 
+    def _once(self, name, build):
+        """self.<name>, an array of this batch that `build` makes on first use, without a wait of the host: streams other than the
+        one that built it wait for it there.  While a graph is captured an array that is not known to be complete is built
+        again, as a part of the graph, and not kept: it has no contents before the graph has run."""
+        cur = torch.cuda.current_stream()
+        kept = getattr(self, name)
+        if torch.cuda.is_current_stream_capturing():
+            return kept.array if kept is not None and kept.complete else build()
+        if kept is None:
+            kept = _Kept(build(), cur)
+            setattr(self, name, kept)          # another thread may have been here: the contents are the same
+        elif kept.stream != cur:
+            if not kept.complete:
+                cur.wait_event(kept.event)
+            kept.array.record_stream(cur)
+        if not kept.complete:
+            kept.complete = kept.event.query()
+        return kept.array
+
     @property
     def groups(self):
-        """The in-batch rows by degree (gas_pna_groups; max_row is the largest), built on first use, once per batch, and complete
-        when this returns: any stream may read it.  None while a graph is captured that would record the building instead."""
-        if self._groups is None:
-            if torch.cuda.is_current_stream_capturing():
-                return None
-            groups = B.gas_pna_groups(self.rowptr, self.max_row)
-            torch.cuda.current_stream().synchronize()
-            self._groups = groups
-        return self._groups
+        """The in-batch rows by degree (gas_pna_groups; max_row is the largest), built on first use, once per batch."""
+        return self._once("_groups", lambda: B.gas_pna_groups(self.rowptr, self.max_row))
 
     @property
     def n_id_host(self):
@@ -919,16 +939,26 @@ def appnp_forward_batch(w1, w2, alpha, n_steps, bg: BatchGraph, x_feat, historie
 PNA_GROUPED_ROWS, PNA_GROUPED_TERMS = 24_576, 2_000_000_000
 
 
-def _by_degree(bg: BatchGraph, x, w2):
+def _by_degree(bg: BatchGraph, x, w2, groups=None):
     """The batch's rows by degree if a PNA layer's transforms take them so (gas_pna_linear), else None: fp32, degrees up to
     PNA_MAX_DEGREE, and enough work that fewer columns outweigh the tiles that a degree fills in part, the degrees' matrices
     and two launches more.  Passes of three layers, us without -> with: 50,000 rows of 256 -> 256 forward 906 -> 758, training
     2,790 -> 2,471, 128 -> 128 414 -> 398 and 1,536 -> 1,415; but 100 -> 64 313 -> 311 and 1,083 -> 1,177, 16,000 rows of
-    256 -> 256 359 -> 357 and 1,110 -> 1,090, 8,000 238 -> 264 and 722 -> 755."""
+    256 -> 256 359 -> 357 and 1,110 -> 1,090, 8,000 238 -> 264 and 722 -> 755.  The first pass over a batch builds the groups too: 50,000
+    rows of 256 -> 256 951 -> 818 and 2,859 -> 2,544, 128 -> 128 454 -> 456 and 1,573 -> 1,459."""
     if x.dtype != torch.float32 or bg.max_row > B.PNA_MAX_DEGREE or bg.nb < PNA_GROUPED_ROWS or \
             bg.nb * w2.shape[0] * w2.shape[1] < PNA_GROUPED_TERMS or bg.nb < 512 * (bg.max_row + 1):
         return None
-    return bg.groups
+    return bg.groups if groups is None else groups
+
+
+def _groups_of_layers(bg: BatchGraph, x, weights):
+    """_by_degree of every layer of a pass; a pass under capture, which may have to record their building, records it once."""
+    out, groups = [], None
+    for _, w2 in weights:
+        out.append(_by_degree(bg, x, w2, groups))
+        groups = groups if out[-1] is None else out[-1]
+    return out
 
 
 def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None):
@@ -976,11 +1006,12 @@ def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push
     B.gas_pull(x_feat, bg.n_id, x)
     L = len(weights)
     y = None
+    by_degree = _groups_of_layers(bg, x, weights)
     for l in range(1, L + 1):
         w1, w2 = weights[l - 1]
         last = l == L
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
-        groups = _by_degree(bg, x, w2)
+        groups = by_degree[l - 1]
         if groups is None:
             y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb])
         else:
@@ -1050,10 +1081,11 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
     L = len(weights)
     kept = []
     y = None
+    by_degree = _groups_of_layers(bg, x, weights)
     for l in range(1, L + 1):
         w1, w2 = weights[l - 1]
         last = l == L
-        groups = _by_degree(bg, x, w2)
+        groups = by_degree[l - 1]
         p, cat = _pna_messages(bg, x, w1, delta, 9)
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
@@ -1076,7 +1108,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         w1, w2 = weights[l - 1]
         x, p, cat, _ = kept[l - 1]            # g: the gradient before this layer's activation
         f, f1 = x.shape[1], w1.shape[1]
-        groups = _by_degree(bg, x, w2)
+        groups = by_degree[l - 1]
         if groups is not None:
             dw2 = torch.empty(w2.shape, dtype=torch.float32, device=dev)
             B.gas_pna_linear_bwd_weight(groups, bg.max_row, cat, g, f1, delta, dw2)

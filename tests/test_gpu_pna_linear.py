@@ -106,3 +106,89 @@ def test_passes_by_degree_agree_with_passes_without(f, hidden, monkeypatch):
     for a, b in zip(*out):
         # gradients: a hidden unit within rounding of zero, or a tie for an extreme, may fall on either side
         assert (a - b).norm() <= (1e-5 if a is out[0][0] or a is out[0][1] else 4e-3) * b.norm()
+
+
+@pytest.mark.parametrize("n,most", [(1, 0), (1, 63), (1023, 0), (1024, 5), (1025, 63), (5000, 12), (200_000, 26)])
+def test_rows_by_degree(n, most):
+    """Counts, tiles of 128 rows, slabs and the row ids, ascending for every degree, where one row, a workgroup's share of rows and
+    many shares are listed."""
+    from paper_2106_05609_amd import binding as B
+    d, ptr = _rows(n, most, torch.Generator().manual_seed(n + most))
+    got = B.gas_pna_groups(ptr, most).cpu().view(torch.int32)
+    count = torch.bincount(d, minlength=most + 1)
+    assert torch.equal(got[2:3 + most].long(), count)
+    n_tiles, n_slabs, slabs_at = int(got[0]), int(got[1]), 68 + 4 * (n // 128 + most + 1)
+    n_slabs_most = n // 512 + most + 1
+    rows_at = slabs_at + 4 * n_slabs_most
+    assert torch.equal(got[rows_at:rows_at + n].long(), torch.argsort(d, stable=True)) and n_slabs <= n_slabs_most
+    for parts, step in ((got[68:68 + 4 * n_tiles].view(-1, 4), 128), (got[slabs_at:slabs_at + 4 * n_slabs].view(-1, 4), 512)):
+        want, at = [], 0
+        for k, c in enumerate(count.tolist()):
+            want += [(k, at + i, min(step, c - i)) for i in range(0, c, step)]
+            at += c
+        assert [tuple(p[:3]) for p in parts.tolist()] == want
+
+
+def _pna_batch(f, hidden, layers, monkeypatch):
+    from gas_inputs import batches, graphs
+    from paper_2106_05609_amd import executor
+    dev = torch.device("cuda")
+    monkeypatch.setattr(executor, "PNA_GROUPED_TERMS", 0)
+    monkeypatch.setattr(executor, "PNA_GROUPED_ROWS", 10_000)
+    g = graphs.sbm_partners(40_000, 6, 6.0, 0.85, 3, dev)
+    sg = batches.batch_subgraph(g, batches.split(g, 2, 0)[0], self_loops=False)
+    gen = torch.Generator(device=dev).manual_seed(1)
+    normal = lambda *shape: torch.randn(*shape, generator=gen, device=dev)
+    widths = [f] + [hidden] * layers
+    ws = [(normal(2 * i, max(8, o // 4)) / i ** 0.5, normal(i + 9 * max(8, o // 4), o) / (3 * i) ** 0.5) for i, o in zip(widths, widths[1:])]
+    batch = lambda: executor.BatchGraph(sg.nb, sg.n_id, sg.rowptr, sg.col, g.deg, sg.colptr, sg.row, max_F=256, normalise=False, csc_pos=sg.csc_perm)
+    tables = [normal(40_000, hidden).clamp_(min=0) for _ in range(layers - 1)]
+    return batch, ws, normal(40_000, f), tables, normal(sg.nb, hidden)
+
+
+@pytest.mark.parametrize("train", [False, True])
+def test_a_captured_first_pass_goes_by_degree_too(train, monkeypatch):
+    """A pass over a new batch that is captured before any eager one has the eager pass's bits, in every replay, and leaves the
+    batch to later eager passes as it was."""
+    from paper_2106_05609_amd import executor
+    batch, ws, x, tables, grad = _pna_batch(40, 64, 2, monkeypatch)
+
+    def run(bg):
+        if not train:
+            return [executor.pna_forward_batch(ws, 2.0, bg, x, tables)]
+        y, grads, _ = executor.pna_train_batch(ws, 2.0, bg, x, tables, grad)
+        return [y] + [t for l in range(2) for t in grads[l]]
+    eager, captured = batch(), batch()
+    want = [t.clone() for t in run(eager) + tables]
+    for bg in (eager, captured):
+        bg.plan_t_all
+    assert eager._groups is not None and captured._groups is None
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = run(captured) + tables
+    assert captured._groups is None
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(got, want))
+        assert all(torch.equal(a, b) for a, b in zip(run(captured), want))
+        torch.cuda.synchronize()
+
+
+def test_groups_are_built_without_a_wait_of_the_host(monkeypatch):
+    """The host runs ahead of a busy stream, and another stream that asks in the meantime finds the lists complete."""
+    batch, ws, x, tables, _ = _pna_batch(40, 64, 1, monkeypatch)
+    from paper_2106_05609_amd import executor
+    want = executor.pna_forward_batch(ws, 2.0, batch(), x, tables)
+    bg, other, busy = batch(), torch.cuda.Stream(), torch.cuda.Event()
+    torch.cuda.synchronize()
+    torch.cuda._sleep(100_000_000)
+    busy.record()
+    bg.groups
+    assert not busy.query()
+    with torch.cuda.stream(other):
+        got = executor.pna_forward_batch(ws, 2.0, bg, x, tables)
+    torch.cuda.synchronize()
+    assert torch.equal(got, want)
+    assert bg.groups is bg.groups
