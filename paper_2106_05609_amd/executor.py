@@ -952,12 +952,27 @@ def _by_degree(bg: BatchGraph, x, w2, groups=None):
     return bg.groups if groups is None else groups
 
 
-def _groups_of_layers(bg: BatchGraph, x, weights):
-    """_by_degree of every layer of a pass; a pass under capture, which may have to record their building, records it once."""
+def _second_round(bg: BatchGraph, w2) -> bool:
+    """Whether the tiles that degrees fill in part (half a tile for a degree) take the forward product by degree, 128 x 128 a
+    workgroup, two on a compute unit, into a second round that the plain product does not need.  Forward passes of three layers,
+    us without -> with: 30,500 rows of up to 25 entries, 256 -> 256 (502 tiles for 512 places), 536 -> 475, 31,500 (518)
+    542 -> 579, 32,500 (532) 566 -> 590, 33,000, where the plain product has its second round too, 726 -> 598; 128 -> 128 at
+    63,000 of up to 28 (506) 469 -> 449, 65,000 (521) 498 -> 517, 66,000 579 -> 534.  Outputs of 64 columns a tile, three
+    workgroups on a compute unit, 32,000 rows of 192 -> 192 472 -> 466."""
+    n = w2.shape[1]
+    tiles, columns = -(-bg.nb // 128), -(-n // 128)
+    return -(-n // 64) * 64 == columns * 128 and tiles * columns <= 512 < (bg.nb / 128 + (bg.max_row + 1) / 2) * columns
+
+
+def _groups_of_layers(bg: BatchGraph, x, weights, gradients=True):
+    """_by_degree of every layer of a pass, for its gradients and for its forward product; a pass under capture, which may have
+    to record their building, records it once."""
     out, groups = [], None
     for _, w2 in weights:
-        out.append(_by_degree(bg, x, w2, groups))
-        groups = groups if out[-1] is None else out[-1]
+        second = _second_round(bg, w2)
+        got = _by_degree(bg, x, w2, groups) if gradients or not second else None
+        groups = groups if got is None else got
+        out.append((got, None if second else got))
     return out
 
 
@@ -1006,12 +1021,12 @@ def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push
     B.gas_pull(x_feat, bg.n_id, x)
     L = len(weights)
     y = None
-    by_degree = _groups_of_layers(bg, x, weights)
+    by_degree = _groups_of_layers(bg, x, weights, gradients=False)
     for l in range(1, L + 1):
         w1, w2 = weights[l - 1]
         last = l == L
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
-        groups = by_degree[l - 1]
+        groups = by_degree[l - 1][1]
         if groups is None:
             y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb])
         else:
@@ -1085,7 +1100,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
     for l in range(1, L + 1):
         w1, w2 = weights[l - 1]
         last = l == L
-        groups = by_degree[l - 1]
+        groups = by_degree[l - 1][1]
         p, cat = _pna_messages(bg, x, w1, delta, 9)
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
@@ -1108,7 +1123,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         w1, w2 = weights[l - 1]
         x, p, cat, _ = kept[l - 1]            # g: the gradient before this layer's activation
         f, f1 = x.shape[1], w1.shape[1]
-        groups = by_degree[l - 1]
+        groups = by_degree[l - 1][0]
         if groups is not None:
             dw2 = torch.empty(w2.shape, dtype=torch.float32, device=dev)
             B.gas_pna_linear_bwd_weight(groups, bg.max_row, cat, g, f1, delta, dw2)

@@ -77,3 +77,16 @@ def test_which_pna_layers_go_by_degree(rows, longest, f, f1, out, dtype, grouped
         nb, max_row, groups = rows, longest, "groups"
     got = executor._by_degree(Batch, torch.empty(0, f, dtype=dtype), torch.empty(f + 9 * f1, out))
     assert (got == "groups") == grouped
+
+
+@pytest.mark.parametrize("rows,longest,out,second", [
+    (30_500, 25, 256, False), (31_500, 25, 256, True), (32_500, 39, 208, True), (33_000, 26, 256, False), (50_000, 26, 256, False),
+    (63_000, 28, 128, False), (65_000, 27, 96, True), (66_000, 28, 128, False), (32_000, 26, 192, False)])
+def test_pna_forward_products_by_degree_take_no_round_more(rows, longest, out, second):
+    """256 compute units hold 512 tiles of 128 x 128 at once: a product of at most that many goes by degree only if its degrees'
+    tiles are no more either.  Gradients go by degree all the same."""
+    class Batch:
+        nb, max_row, groups = rows, longest, "groups"
+    w2 = torch.empty(out + 9 * (out // 4), out)
+    wide = executor._by_degree(Batch, torch.empty(0, out), w2)
+    assert executor._groups_of_layers(Batch, torch.empty(0, out), [(None, w2)]) == [(wide, None if second else wide)]
