@@ -17,7 +17,15 @@ namespace gas {
 namespace {
 
 constexpr int kMaxDegree = 63;                // a degree for every lane
-constexpr int kTile = 128, kSlab = 512;       // rows of a product's tile and of a weight gradient's slab
+constexpr int kTile = 128;                    // rows of a product's tile
+// Rows of a weight gradient's slab, whose partial is of the weights' size: about 128 slabs and one more for a degree, up to the
+// 4,096 rows of the plain gradient's.  256 + 64 x 3 -> 256, degrees up to 26, in MB: 50,000 rows 57, 1,000,000 125 (by 512
+// rows throughout 908; the nine blocks' plain gradient 209).
+constexpr int kSlabStep = 512, kMostSlab = 4096;
+inline int slab_rows(int64_t n) {
+    const int64_t s = (n + 128 * kSlabStep - 1) / (128 * kSlabStep) * kSlabStep;
+    return (int)(s < kSlabStep ? kSlabStep : s > kMostSlab ? kMostSlab : s);
+}
 
 // The rows by degree, in a buffer of the caller's: counts, then tiles and slabs (degree, first position, rows), the row
 // ids, ascending for each degree, and what the building of the lists needs: of each degree, its rows in every workgroup's share.
@@ -25,13 +33,15 @@ struct GroupsHead { int32_t n_tiles, n_slabs, count[kMaxDegree + 1], pad[2]; };
 struct Part { int32_t degree, start, rows, pad; };
 constexpr int kShare = 1024;                  // rows of a workgroup that counts or lists them
 inline int64_t most_tiles(int64_t n, int d) { return n / kTile + d + 1; }
-inline int64_t most_slabs(int64_t n, int d) { return n / kSlab + d + 1; }
+inline int64_t most_slabs(int64_t n, int d) { return n / slab_rows(n) + d + 1; }
 inline int64_t shares(int64_t n) { return (n + kShare - 1) / kShare; }
 struct Groups {
     GroupsHead* head; Part* tile; Part* slab; int32_t* row; int32_t* share;
+    int in_slab;                              // rows of a slab
     Groups(void* p, int64_t n, int d)
         : head(static_cast<GroupsHead*>(p)), tile(reinterpret_cast<Part*>(head + 1)), slab(tile + most_tiles(n, d)),
-          row(reinterpret_cast<int32_t*>(slab + most_slabs(n, d))), share(row + n) {}
+          row(reinterpret_cast<int32_t*>(slab + most_slabs(n, d))), share(row + n),
+          in_slab(slab_rows(n)) {}
 };
 
 __device__ __forceinline__ int degree_of(const int32_t* rowptr, int64_t r, int most) {
@@ -84,7 +94,7 @@ __global__ __launch_bounds__(256) void groups_list_kernel(const int32_t* rowptr,
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     next[wave][lane] = 0;
     if (wave == 0) {                          // lane d: degree d
-        const int c = lane <= most ? g.head->count[lane] : 0, t = (c + kTile - 1) / kTile, s = (c + kSlab - 1) / kSlab;
+        const int c = lane <= most ? g.head->count[lane] : 0, t = (c + kTile - 1) / kTile, s = (c + g.in_slab - 1) / g.in_slab;
         const int at = wave_scan(c), tile = wave_scan(t), slab = wave_scan(s);
         rows[lane] = c;
         first[lane] = at - c;
@@ -96,7 +106,8 @@ __global__ __launch_bounds__(256) void groups_list_kernel(const int32_t* rowptr,
     for (int d = blockIdx.x; d <= most; d += gridDim.x) {
         const int c = rows[d], at = first[d];
         for (int i = tid; i * kTile < c; i += 256) g.tile[tile0[d] + i] = Part{d, at + i * kTile, min(kTile, c - i * kTile), 0};
-        for (int i = tid; i * kSlab < c; i += 256) g.slab[slab0[d] + i] = Part{d, at + i * kSlab, min(kSlab, c - i * kSlab), 0};
+        for (int i = tid; i < (c + g.in_slab - 1) / g.in_slab; i += 256)
+            g.slab[slab0[d] + i] = Part{d, at + i * g.in_slab, min(g.in_slab, c - i * g.in_slab), 0};
     }
     constexpr int kSteps = kShare / 256;
     const int64_t r0 = (int64_t)blockIdx.x * kShare + wave * (kShare / 4) + lane;
@@ -220,7 +231,7 @@ __global__ __launch_bounds__(256, 2) void pna_dw_kernel(PnaDwArgs a) {
     const Part part = a.g.slab[slab];
     const int k0 = (int)(tile / tn) * kTile, n0 = (int)(tile % tn) * kTile, wk0 = (wave >> 1) * 64, wn0 = (wave & 1) * 64;
     // the slab's row ids in LDS: asked of memory where the rows are, every step waits for them first (139 us, 119 by LDS)
-    __shared__ int32_t ids[kSlab];
+    int32_t* ids = reinterpret_cast<int32_t*>(smem + S::kLdsBytes);
     for (int i = threadIdx.x; i < part.rows; i += 256) ids[i] = a.g.row[part.start + i];
     __syncthreads();
     S g;
@@ -405,14 +416,14 @@ gas_status gas_pna_linear_bwd_weight(const void* groups, int64_t n_rows, int32_t
     const Groups g(const_cast<void*>(groups), n_rows, max_degree);
     const PnaDwArgs a{g, static_cast<const float*>(X), ldx, static_cast<const float*>(G), ldg, F + 3 * F1, F_out, F, F1, 1.f / delta,
                       static_cast<float*>(workspace), dW};
-    constexpr int smem = SplitGemm<kTile, kTile, 2, 2, 2, false, false, 1, true, true>::kLdsBytes;
-    static const hipError_t attr =
-        hipFuncSetAttribute(reinterpret_cast<const void*>(pna_dw_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+    constexpr int lds = SplitGemm<kTile, kTile, 2, 2, 2, false, false, 1, true, true>::kLdsBytes;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pna_dw_kernel),
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, lds + 4 * kMostSlab);
     GAS_CHECK_HIP(attr);
     const int64_t tiles = (int64_t)((a.K + kTile - 1) / kTile) * ((a.N + kTile - 1) / kTile);
     const int64_t blocks = (most_slabs(n_rows, max_degree) + 7) / 8 * 8 * tiles;
     GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "%s: too many rows for one launch", who);
-    hipLaunchKernelGGL(pna_dw_kernel, dim3((unsigned)blocks), dim3(256), smem, (hipStream_t)stream, a);
+    hipLaunchKernelGGL(pna_dw_kernel, dim3((unsigned)blocks), dim3(256), lds + 4 * g.in_slab, (hipStream_t)stream, a);
     hipLaunchKernelGGL(pna_dw_reduce_kernel, dim3((unsigned)(((int64_t)a.K * a.N + 31) / 32)), dim3(256), 0, (hipStream_t)stream, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;

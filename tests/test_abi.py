@@ -136,3 +136,15 @@ def test_a_refused_input_gradient_has_launched_nothing():
     st = L.gas_linear_bwd_input_add(a[0], q(8), q(4), i(8), a[1], i(8), ctypes.c_int(1), f(0.0), f(1.0), a[2], q(8), a[3], q(3),
                                     f(0.0), a[4], q(8), a[5], q(8), p(0))
     assert st == -1 and b"row stride" in L.gas_last_error()
+
+
+def test_workspace_of_weight_gradients_by_degree_is_bounded():
+    """Partials of about 128 slabs and one more for a degree, of slabs of up to 4,096 rows: no more than the plain gradient of the
+    nine blocks takes where there are many rows."""
+    L = binding.lib()
+    for f, f1, f_out in ((256, 64, 256), (1433, 64, 256)):
+        for n in (1, 50_000, 65_537, 200_000, 1_000_000, 10_000_000):
+            got = L.gas_pna_linear_bwd_weight_workspace(ctypes.c_int64(n), 63, f, f1, f_out)
+            assert 0 < got <= 4 * (f + 3 * f1) * f_out * (max(128, n // 4096) + 64)
+            if n >= 1_000_000:
+                assert got <= 1.4 * L.gas_linear_bwd_weight_workspace(ctypes.c_int64(n), f + 9 * f1, f_out)

@@ -111,17 +111,18 @@ def test_passes_by_degree_agree_with_passes_without(f, hidden, monkeypatch):
 @pytest.mark.parametrize("n,most", [(1, 0), (1, 63), (1023, 0), (1024, 5), (1025, 63), (5000, 12), (200_000, 26)])
 def test_rows_by_degree(n, most):
     """Counts, tiles of 128 rows, slabs and the row ids, ascending for every degree, where one row, a workgroup's share of rows and
-    many shares are listed."""
+    many shares are listed; slabs of 512 rows, and of more from 65,537 rows on."""
     from paper_2106_05609_amd import binding as B
     d, ptr = _rows(n, most, torch.Generator().manual_seed(n + most))
     got = B.gas_pna_groups(ptr, most).cpu().view(torch.int32)
     count = torch.bincount(d, minlength=most + 1)
     assert torch.equal(got[2:3 + most].long(), count)
     n_tiles, n_slabs, slabs_at = int(got[0]), int(got[1]), 68 + 4 * (n // 128 + most + 1)
-    n_slabs_most = n // 512 + most + 1
+    slab = 512 * max(1, -(-n // 65_536))
+    n_slabs_most = n // slab + most + 1
     rows_at = slabs_at + 4 * n_slabs_most
     assert torch.equal(got[rows_at:rows_at + n].long(), torch.argsort(d, stable=True)) and n_slabs <= n_slabs_most
-    for parts, step in ((got[68:68 + 4 * n_tiles].view(-1, 4), 128), (got[slabs_at:slabs_at + 4 * n_slabs].view(-1, 4), 512)):
+    for parts, step in ((got[68:68 + 4 * n_tiles].view(-1, 4), 128), (got[slabs_at:slabs_at + 4 * n_slabs].view(-1, 4), slab)):
         want, at = [], 0
         for k, c in enumerate(count.tolist()):
             want += [(k, at + i, min(step, c - i)) for i in range(0, c, step)]
@@ -192,3 +193,22 @@ def test_groups_are_built_without_a_wait_of_the_host(monkeypatch):
     torch.cuda.synchronize()
     assert torch.equal(got, want)
     assert bg.groups is bg.groups
+
+
+def test_weight_gradient_by_long_slabs():
+    """300,000 rows: slabs of 2,560, of which the longest degree has many and the rare ones less than one."""
+    from paper_2106_05609_amd import binding as B
+    gen = torch.Generator().manual_seed(9)
+    n, most, f, f1, n_out, delta = 300_000, 20, 24, 8, 40, 1.7
+    d = torch.where(torch.rand(n, generator=gen) < 0.7, torch.tensor(7), torch.randint(0, 4, (n,), generator=gen))
+    d[100:400] = torch.arange(300) % (most + 1)
+    ptr = torch.cat([torch.zeros(1, dtype=torch.long), d.cumsum(0)]).int().cuda()
+    x, g = torch.randn(n, f + 9 * f1, generator=gen), torch.randn(n, n_out, generator=gen)
+    x[d == 0, f:] = 0.0
+    s = torch.log(d.double() + 1.0)[:, None] / delta
+    a = x[:, f:f + 3 * f1].double()
+    full = torch.cat([x[:, :f].double(), a, s * a, torch.where(d[:, None] > 0, a / s, torch.zeros_like(a))], 1)
+    dw = torch.empty(f + 9 * f1, n_out, device="cuda")
+    B.gas_pna_linear_bwd_weight(B.gas_pna_groups(ptr, most), most, x.cuda(), g.cuda(), f1, delta, dw)
+    bound = full.abs().t() @ g.double().abs()
+    assert ((dw.cpu().double() - full.t() @ g.double()).abs() <= (32 + n ** 0.5) * 2.0 ** -24 * bound).all()
