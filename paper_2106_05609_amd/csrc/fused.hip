@@ -48,15 +48,27 @@ constexpr int kThreads = 256;        // four wavefronts: eight rows of the tile 
 //      for 128) by all k, so the four wavefronts share the products.  16x16x4 fp32 MFMAs, taken transposed: a lane has four
 //      consecutive columns of a row, which get c_w * acc + c_id * Z + bias and ReLU and are stored to Y and to the
 //      row's history slot as 16 bytes.
-// 64 layers of 21,248 rows, width 64, 15 entries a row: 16.4 us each (17.7 with the loads past a row's end not switched off: the
-// eight teams of a wavefront go by its longest row, two entries in five more; with the addresses formed by every lane, 32x32x2
+// 64 layers of 21,248 rows, width 64, 15 entries a row: 16.4 us each (17.7 with the loads past a row's end not switched off,
+// kMaskedGathers; with the addresses formed by every lane, 32x32x2
 // products by two of the four wavefronts and the weights in LDS 21.9).  Without the gathers 7.6 us, without the transform
 // 13.7: what is left is the gather's chain of two to three batches and the rows that every XCD fetches anew (4.6 TB/s).
 // BWD: the same on the adjoint (gas_spmm_t_relu_linear): the pattern is the CSC copy, the activations of the layer below mask
 // the aggregated rows, the weights are taken transposed and a running total is kept.  21,248 rows of 64: 14.7 us
 // where the aggregation by plan (19) and the input gradient (9) were two launches; the whole pass of 64 layers 3,780 -> 3,426 us.
-// <8, 2, 2> spills 7 registers (BWD 11) to keep three wavefronts on a SIMD: 21,248 rows of 50, 64 -> 128, 33.5 us, with two
+// <8, 2, 2> spills 6 registers (BWD 11) to keep three wavefronts on a SIMD: 21,248 rows of 50, 64 -> 128, 33.5 us, with two
 // and none spilled 41.9 (rows of 5: 15.4 and 15.7).
+// Whether a team past its row's end fetches nothing; otherwise it fetches the row's last entry again, which it has just had.  The
+// eight teams of a wavefront go by its longest row, two entries in five more than their own.  The mask takes 5 to 8 registers:
+// it is on where the compiled kernel keeps its wavefronts on a SIMD and spills nothing for it.  Time without over with the mask, 30
+// patterns (500 to 50,000 rows of 5 to 40 entries, even and power law), geometric mean: up to 32 columns to at most 64 1.01
+// (BWD 1.02), 33 to 64 1.05 (1.02), 65 to 128 1.08, to more columns from up to 32 1.01, from 65 to 128 1.07 (1.06).  Off:
+// 65 to 128 to at most 64 BWD, three wavefronts to two, 21,248 rows of 40 entries 40 -> 48 us; up to 32 to more than 64 BWD, four
+// to three, 0.98; 33 to 64 to more than 64, twice the spills, 0.97 to 1.00.  A wavefront with one row of hundreds of entries among
+// short ones is the slower with it (500 rows of 8, one of 500, 32 -> 32, 41 -> 45 us); passes over power-law batches of
+// 50,000 rows, 32 -> 32, are not (221 -> 205).
+template <int G, int P, int NB, bool BWD>
+constexpr bool kMaskedGathers = G == 8 ? NB == 1 || (P == 1 && !BWD) : NB == 2 || !BWD;
+
 template <int G, int P, int NB, bool BWD>
 __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kernel(FusedArgs a) {
     constexpr int KQ = G * P / 4, LDZ = 16 * KQ + 4;                      // steps of 16 k, floats of a row of Zs
@@ -160,9 +172,15 @@ __global__ __launch_bounds__(kThreads, G == 8 ? 3 : 2) void spmm_linear_f32_kern
 #pragma unroll
                         for (int u = 0; u < U; ++u) {
                             const uint64_t row = (uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) | ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32);
-                            if (G * h + q + u < cnt) {       // a team past its row's end fetches nothing
-                                x[u][0] = load_global<f32x4>(row + off0);
-                                if constexpr (P == 2) x[u][1] = load_global<f32x4>(row + off1);
+                            if constexpr (kMaskedGathers<G, P, NB, BWD>) {
+                                if (G * h + q + u < cnt) {
+                                    x[u][0] = load_global<f32x4>(row + off0);
+                                    if constexpr (P == 2) x[u][1] = load_global<f32x4>(row + off1);
+                                }
+                            } else {
+                                const char* at = reinterpret_cast<const char*>(row);
+                                x[u][0] = *reinterpret_cast<const f32x4*>(at + off0);
+                                if constexpr (P == 2) x[u][1] = *reinterpret_cast<const f32x4*>(at + off1);
                             }
                         }
 #pragma unroll
