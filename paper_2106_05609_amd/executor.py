@@ -56,8 +56,7 @@ class BatchGraph:
         if normalise:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
             part("gcn_norm_csr", lambda: B.gas_gcn_norm(rowptr, col, n_id, deg, self.val))
-        self._src = self._src_first = None
-        self._groups = None
+        self._src = self._src_first = self._groups = None
         self.csc_pos = csc_pos       # int32[nnz]: position of every CSC entry in the CSR arrays (PNA / GAT backward)
         self._n_id_host = None
         self._plan_t_all, self._max_F = None, max_F
@@ -89,19 +88,19 @@ class BatchGraph:
         """self.<name>, an array of this batch that `build` makes on first use, without a wait of the host: streams other than the
         one that built it wait for it there.  While a graph is captured an array that is not known to be complete is built
         again, as a part of the graph, and not kept: it has no contents before the graph has run."""
-        cur = torch.cuda.current_stream()
         kept = getattr(self, name)
+        if kept is not None and kept.complete:
+            return kept.array
         if torch.cuda.is_current_stream_capturing():
-            return kept.array if kept is not None and kept.complete else build()
+            return build()
+        cur = torch.cuda.current_stream()
         if kept is None:
             kept = _Kept(build(), cur)
             setattr(self, name, kept)          # another thread may have been here: the contents are the same
-        elif kept.stream != cur:
-            if not kept.complete:
-                cur.wait_event(kept.event)
-            kept.array.record_stream(cur)
-        if not kept.complete:
+        else:
             kept.complete = kept.event.query()
+            if not kept.complete and kept.stream != cur:
+                cur.wait_event(kept.event)
         return kept.array
 
     @property
@@ -116,21 +115,29 @@ class BatchGraph:
             self._n_id_host = self.n_id.cpu()
         return self._n_id_host
 
+    def _sources(self, nb):
+        src = torch.empty_like(self.col)
+        B.gas_fuse_sources(self.col, nb, self.n_id, src)
+        return src
+
     @property
     def src(self):
-        """Source indices for gas_spmm_hist (built on first use, once per batch, together with the first layer's)."""
+        """Source indices for gas_spmm_hist (built on first use, once per batch)."""
         if self._src is None:
-            src, first = torch.empty_like(self.col), torch.empty_like(self.col)
-            B.gas_fuse_sources(self.col, self.nb, self.n_id, src)
-            B.gas_fuse_sources(self.col, 0, self.n_id, first)
-            self._src, self._src_first = src, first
+            self._src = self._sources(self.nb)
         return self._src
 
     @property
     def src_first(self):
-        """Source indices of a first layer that reads the feature table in place (gas_spmm_table)."""
-        self.src
-        return self._src_first
+        """Source indices of a first layer that reads the feature table in place (gas_spmm_table: GCN, and GIN without
+        gradients), built on first use, once per batch; under capture as a part of the graph, and not kept: they have no
+        contents before the graph has run."""
+        first = self._src_first
+        if first is None:
+            first = self._sources(0)
+            if not torch.cuda.is_current_stream_capturing():
+                self._src_first = first
+        return first
 
 
 class Model:
@@ -284,7 +291,9 @@ def forward_batch_fused(model: Model, bg: BatchGraph, x_feat, histories, do_push
     tensor, and the Push taken in the transform's epilogue: per layer
     aggregate(X_batch, H[l-1]) -> transform, rows stored to H[l] as well.
     Layer 1 reads all its rows from the feature table in place (gas_spmm_table: no copy of the in-batch rows; 5,000 rows of
-    1,433 floats 22 us, of 512 rows a launch of three).  GCNII: its first layer aggregates the
+    1,433 floats 22 us, of 512 rows a launch of three).  Copy and aggregation took 1.07 to 1.5 times as long in all of 520 cases
+    (GCN and GIN, 500 to 75,000 rows of 6 to 45 entries, clustered and power law, 40 to 1,433 columns of both types, with and without
+    the rows in the caches), the least with 75,000 power-law rows out of the caches: 212 and 194 us for 100 floats.  GCNII: its first layer aggregates the
     projected features of all of V_b, which no table holds, so that layer gathers from the mini-batch tensor; from
     layer 2 on the halo rows come from the history tables in place.  Narrow fp32 layers of GCN and GCNII (widths
     up to 128, no row above ONE_LAUNCH_MAX_ROW entries) take one launch each (gas_spmm_linear)."""

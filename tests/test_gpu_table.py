@@ -33,3 +33,45 @@ def test_spmm_table_has_the_bits_of_pull_and_spmm(rows, longest, f, ld, dtype, d
     if diag:
         with pytest.raises(gas.GasError):
             gas.gas_spmm_table(plan, ptr, src, val, table, z, diag=diag)
+
+
+@pytest.mark.parametrize("op,train", [("gcn", False), ("gcn", True), ("gin", False), ("gin", True), ("gcnii", False), ("gcnii", True)])
+def test_first_layer_indices_are_built_for_passes_that_read_them(op, train):
+    """By GCN and by GIN's inference, in their first pass and not with the other indices; a captured first pass records the
+    building and leaves the batch without them."""
+    from gas_inputs import batches, graphs
+    from paper_2106_05609_amd import executor
+    dev = torch.device("cuda")
+    g = graphs.sbm_partners(2_000, 8, 6.0, 0.85, 3, dev)
+    sg = batches.batch_subgraph(g, batches.split(g, 2, 0)[0], self_loops=op != "gin")
+    gen = torch.Generator(device=dev).manual_seed(1)
+    normal = lambda *shape: torch.randn(*shape, generator=gen, device=dev) / shape[0] ** 0.5
+    ws = [(normal(200, 200), normal(200, 200)) if op == "gin" else normal(200, 200) for _ in range(2)]
+    model = executor.Model(op, ws, normal(200, 200) if op == "gcnii" else None, 0.1 if op == "gcnii" else 0.0)
+    x, tables = normal(2_000, 200), [normal(2_000, 200)]
+    labels = torch.zeros(sg.nb, dtype=torch.int32, device=dev)
+
+    def batch():
+        bg = executor.BatchGraph(sg.nb, sg.n_id, sg.rowptr, sg.col, g.deg, sg.colptr, sg.row, max_F=256, normalise=op != "gin")
+        bg.src
+        bg.plan_t_all
+        return bg
+
+    def run(bg):
+        if train:
+            return executor.train_step(model, bg, x, tables, labels, 0.0, n_labelled=sg.nb, fused=True)[2]
+        return executor.forward_batch_fused(model, bg, x, tables)
+    eager, captured = batch(), batch()
+    assert eager._src_first is None
+    want = run(eager).clone()
+    reads = op == "gcn" or (op == "gin" and not train)
+    assert (eager._src_first is not None) == reads
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        got = run(captured)
+    assert captured._src_first is None and torch.equal(run(captured), want)
+    for _ in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got, want)
