@@ -671,14 +671,13 @@ def gas_sgd_step_clipped(w, dw, lr, sq_norms, max_norm, weight_decay=0.0):
                                       sq_norms.numel(), max_norm, _stream()))
 
 
-def gas_pna_aggregate(rowptr, col, x, out, delta, add=None):
-    """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add); out [n_rows, 3F]: the
-    aggregators alone."""
+def gas_pna_aggregate(rowptr, col, x, out, delta, add=None, blocks=9):
+    """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add); blocks = 3: out
+    [n_rows, 3F], the aggregators alone."""
     xp, ldx = _mat(x)
     op, ldo = _mat(out)
     ap, lda = (0, 0) if add is None else _mat(add)
     n_rows = rowptr.numel() - 1
-    blocks = 3 if out.shape[1] == 3 * x.shape[1] else 9
     if out.dtype != x.dtype or out.shape[0] < n_rows or out.shape[1] != blocks * x.shape[1] or \
             (add is not None and (add.dtype != x.dtype or add.shape[1] != x.shape[1] or add.shape[0] < n_rows)):
         raise ValueError("gas_pna_aggregate: shapes or dtypes do not match")
@@ -903,16 +902,15 @@ class DiskTable:
             pass
 
 
-def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, gadd=None, plan_t=None):
+def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, gadd=None, plan_t=None, blocks=9):
     """Backward of gas_pna_aggregate: gx [n_out, F] (n_out = gx.shape[0] columns of the pattern), gadd [n_rows, F]; g of nine
-    blocks or of three, folded with their scalers.
+    blocks, or of blocks = 3, folded with their scalers.
     plan_t: a Plan of the CSC copy for those n_out columns (fast path), or None (plain kernels)."""
     xp, ldx = _mat(x)
     gp, ldg = _mat(g)
     op, ldo = _mat(gx)
     ap, lda = (0, 0) if gadd is None else _mat(gadd)
     n_rows, F = rowptr.numel() - 1, x.shape[1]
-    blocks = 3 if g.shape[1] == 3 * F else 9
     if g.shape != (n_rows, blocks * F) or gx.shape[1] != F or g.dtype != x.dtype or gx.dtype != x.dtype:
         raise ValueError("gas_pna_aggregate_bwd: shapes or dtypes do not match")
     nnz = col.numel()

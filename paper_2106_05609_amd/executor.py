@@ -1018,7 +1018,7 @@ def _pna_messages(bg: BatchGraph, x, w1, delta, blocks):
     B.gas_linear(x[:nb], w1[:f], q)
     cat = torch.empty((nb, f + blocks * f1), dtype=dt, device=dev)
     B.gas_pull(x, None, cat[:, :f], base=0, n=nb)                 # h_v into the first F columns (a strided row copy)
-    B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q)
+    B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q, blocks=blocks)
     return p, cat
 
 
@@ -1145,7 +1145,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         gp = torch.empty((nv, f1), dtype=dt, device=dev)
         gq = torch.empty((nb, f1), dtype=dt, device=dev)
         B.gas_pna_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, gcat[:, f:], gp, delta, gadd=gq,
-                                plan_t=bg.plan_t_all)
+                                plan_t=bg.plan_t_all, blocks=9 if groups is None else 3)
         dw1 = torch.empty((2 * f, f1), dtype=torch.float32, device=dev)
         wg.add(x[:nb], gq, dw1[:f])
         wg.add(x, gp, dw1[f:])

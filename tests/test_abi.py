@@ -4,6 +4,9 @@ import ctypes
 import os
 import re
 
+import pytest
+import torch
+
 from paper_2106_05609_amd import binding
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
@@ -148,3 +151,14 @@ def test_workspace_of_weight_gradients_by_degree_is_bounded():
             assert 0 < got <= 4 * (f + 3 * f1) * f_out * (max(128, n // 4096) + 64)
             if n >= 1_000_000:
                 assert got <= 1.4 * L.gas_linear_bwd_weight_workspace(ctypes.c_int64(n), f + 9 * f1, f_out)
+
+
+def test_pna_blocks_are_nine_unless_three_are_asked_for():
+    """A matrix of three blocks does not pass for one of nine."""
+    ptr, col, x, three = torch.tensor([0, 1], dtype=torch.int32), torch.zeros(1, dtype=torch.int32), torch.zeros(1, 8), torch.zeros(1, 24)
+    with pytest.raises(ValueError, match="do not match"):
+        binding.gas_pna_aggregate(ptr, col, x, three, 1.0)
+    with pytest.raises(ValueError, match="do not match"):
+        binding.gas_pna_aggregate_bwd(ptr, col, ptr, col, col, x, three, torch.zeros(1, 8), 1.0)
+    with pytest.raises(ValueError, match="do not match"):
+        binding.gas_pna_aggregate(ptr, col, x, torch.zeros(1, 72), 1.0, blocks=3)
