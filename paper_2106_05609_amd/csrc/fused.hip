@@ -309,28 +309,28 @@ gas_status run_layer(const FusedArgs& a, hipStream_t s) {
 }
 
 // the arguments of gas_spmm_linear and of gas_spmm_t_relu_linear (and of each of their layers), checked
-gas_status check_layer(const int32_t* rowptr, const int32_t* src, int64_t n_rows, const void* X, int64_t ldx, const void* hist,
+gas_status check_layer(const char* who, const int32_t* rowptr, const int32_t* src, int64_t n_rows, const void* X, int64_t ldx, const void* hist,
                        int64_t n_hist_rows, int64_t ld_hist, gas_dtype dt, int32_t F_in, const void* R, int64_t ldr, const void* W,
                        int32_t F_out, float c_identity, const void* Y, int64_t ldy, const void* Z_out, int64_t ldz_out,
                        const int32_t* push_idx, const void* push_hist, int64_t n_push_rows, int64_t ld_push) {
-    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_spmm_linear: unknown dtype %d", (int)dt);
-    if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "gas_spmm_linear: fp32 only (use gas_spmm_hist + gas_linear_push)");
-    GAS_REQUIRE(n_rows >= 0 && n_rows < 0x7FFFFFFFLL, "gas_spmm_linear: n_rows=%lld", (long long)n_rows);
+    if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "%s: unknown dtype %d", who, (int)dt);
+    if (dt != GAS_F32) return fail(GAS_ERR_DTYPE, "%s: fp32 only (use gas_spmm_hist + gas_linear_push)", who);
+    GAS_REQUIRE(n_rows >= 0 && n_rows < 0x7FFFFFFFLL, "%s: n_rows=%lld", who, (long long)n_rows);
     GAS_REQUIRE(F_in > 0 && F_out > 0 && F_in <= kMaxWidth && F_out <= kMaxWidth && F_in % 4 == 0 && F_out % 4 == 0,
-                "gas_spmm_linear: widths %d -> %d: multiples of 4 up to %d only (use gas_spmm_hist + gas_linear_push)",
+                "%s: widths %d -> %d: multiples of 4 up to %d only (use gas_spmm_hist + gas_linear_push)", who,
                 F_in, F_out, kMaxWidth);
     if (n_rows == 0) return GAS_OK;
-    GAS_REQUIRE(rowptr && src && X && W && Y, "gas_spmm_linear: null pointer");
+    GAS_REQUIRE(rowptr && src && X && W && Y, "%s: null pointer", who);
     GAS_REQUIRE(ldx >= F_in && ldy >= F_out && (!hist || ld_hist >= F_in) && (!R || ldr >= F_in),
-                "gas_spmm_linear: row stride smaller than the width");
-    GAS_REQUIRE(n_hist_rows >= 0 && n_push_rows >= 0, "gas_spmm_linear: negative table size");
-    GAS_REQUIRE(c_identity == 0.f || F_in == F_out, "gas_spmm_linear: the identity term needs F_in == F_out");
-    GAS_REQUIRE((push_idx == nullptr) == (push_hist == nullptr), "gas_spmm_linear: push_idx and push_hist go together");
-    GAS_REQUIRE(!push_hist || ld_push >= F_out, "gas_spmm_linear: row stride of the push table smaller than F_out");
-    GAS_REQUIRE(!Z_out || ldz_out >= F_in, "gas_spmm_linear: row stride of Z_out smaller than F_in");
+                "%s: row stride smaller than the width", who);
+    GAS_REQUIRE(n_hist_rows >= 0 && n_push_rows >= 0, "%s: negative table size", who);
+    GAS_REQUIRE(c_identity == 0.f || F_in == F_out, "%s: the identity term needs F_in == F_out", who);
+    GAS_REQUIRE((push_idx == nullptr) == (push_hist == nullptr), "%s: push_idx and push_hist go together", who);
+    GAS_REQUIRE(!push_hist || ld_push >= F_out, "%s: row stride of the push table smaller than F_out", who);
+    GAS_REQUIRE(!Z_out || ldz_out >= F_in, "%s: row stride of Z_out smaller than F_in", who);
     const bool al = aligned16(X) && ldx % 4 == 0 && aligned16(W) && (!hist || (aligned16(hist) && ld_hist % 4 == 0)) &&
                     (!R || (aligned16(R) && ldr % 4 == 0)) && (!Z_out || (aligned16(Z_out) && ldz_out % 4 == 0));
-    GAS_REQUIRE(al, "gas_spmm_linear: rows must be 16-byte aligned (use gas_spmm_hist + gas_linear_push)");
+    GAS_REQUIRE(al, "%s: rows must be 16-byte aligned (use gas_spmm_hist + gas_linear_push)", who);
     return GAS_OK;
 }
 gas_status check_layer_bwd(const char* who, const int32_t* colptr, const int32_t* row, int64_t n_cols, const void* G, int64_t ldg,
@@ -368,7 +368,7 @@ gas_status gas_spmm_linear(const int32_t* rowptr, const int32_t* src, const floa
                            const void* W, int32_t F_out, const void* bias, float c_identity, float c_weight, int relu,
                            void* Y, int64_t ldy, void* Z_out, int64_t ldz_out, const int32_t* push_idx,
                            void* push_hist, int64_t n_push_rows, int64_t ld_push, void* stream) {
-    const gas_status st = check_layer(rowptr, src, n_rows, X, ldx, hist, n_hist_rows, ld_hist, dt, F_in, R, ldr, W, F_out, c_identity,
+    const gas_status st = check_layer("gas_spmm_linear", rowptr, src, n_rows, X, ldx, hist, n_hist_rows, ld_hist, dt, F_in, R, ldr, W, F_out, c_identity,
                                       Y, ldy, Z_out, ldz_out, push_idx, push_hist, n_push_rows, ld_push);
     if (st != GAS_OK || n_rows == 0) return st;
     FusedArgs a{};
@@ -432,7 +432,7 @@ gas_status gas_spmm_linear_layers(int32_t count, const int32_t* rowptr, const in
             const int64_t ldp = table ? ld_push[l] : 0;
             gas_status st;
             if (pass == 0) {
-                st = check_layer(rowptr, ind, n_rows, x, ld, hist[l], n_hist_rows, ld_hist[l], dt, F, R, ldr, W[l], F, c_identity[l],
+                st = check_layer(who, rowptr, ind, n_rows, x, ld, hist[l], n_hist_rows, ld_hist[l], dt, F, R, ldr, W[l], F, c_identity[l],
                                  Y[l], ldy, z, ldz_out, ids, table, n_push_rows, ldp);
                 if (st == GAS_OK && Y[l] == x) st = fail(GAS_ERR_ARG, "%s: layer %d writes the rows that it reads", who, l);
             } else {

@@ -162,3 +162,17 @@ def test_pna_blocks_are_nine_unless_three_are_asked_for():
         binding.gas_pna_aggregate_bwd(ptr, col, ptr, col, col, x, three, torch.zeros(1, 8), 1.0)
     with pytest.raises(ValueError, match="do not match"):
         binding.gas_pna_aggregate(ptr, col, x, torch.zeros(1, 72), 1.0, blocks=3)
+
+
+def test_refused_layers_name_the_call():
+    L = binding.lib()
+    i64, f32, p = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
+    at = p(1 << 20)                            # never read: the calls are refused
+    one, ld, half = (p * 1)(1 << 20), (i64 * 1)(64), (f32 * 1)(0.5)
+    for dt, said in ((1, b"fp32 only"), (7, b"unknown dtype")):
+        st = L.gas_spmm_linear_layers(1, at, at, at, at, i64(4), at, i64(64), one, i64(4), ld, dt, 64, f32(1), None, i64(0), f32(0), one, half,
+                                      half, 1, one, i64(64), None, i64(0), None, None, i64(0), None, None)
+        assert st == -2 and L.gas_last_error().startswith(b"gas_spmm_linear_layers: " + said)
+    st = L.gas_spmm_linear_layers(1, at, at, at, at, i64(4), at, i64(64), one, i64(4), ld, 0, 66, f32(1), None, i64(0), f32(0), one, half,
+                                  half, 1, one, i64(66), None, i64(0), None, None, i64(0), None, None)
+    assert st == -1 and L.gas_last_error().startswith(b"gas_spmm_linear_layers: widths")
