@@ -316,10 +316,15 @@ gas_status run_linear(const PnaLinArgs& a, int64_t n, int most, hipStream_t s) {
 gas_status check(const char* who, int64_t n_rows, int32_t max_degree, int32_t F, int32_t F1, int32_t N, float delta) {
     GAS_REQUIRE(n_rows >= 0 && n_rows < (1ll << 30) && max_degree >= 0 && max_degree <= kMaxDegree,
                 "%s: n_rows=%lld, degrees up to %d (at most %d)", who, (long long)n_rows, max_degree, kMaxDegree);
-    GAS_REQUIRE(F > 0 && F1 > 0 && N > 0 && F <= 65536 && F1 <= 65536 && N <= 65536, "%s: widths %d, %d, %d", who, F, F1, N);
+    GAS_REQUIRE(F > 0 && F1 > 0 && N > 0 && F <= 65536 && F1 <= 65536 && N <= 65536 && (F + 3ll * F1) * N < (1ll << 29),
+                "%s: widths %d, %d, %d", who, F, F1, N);      // 32 weights a workgroup of the last sum: as one_launch
     GAS_REQUIRE(delta > 0.f, "%s: delta must be positive", who);
     return GAS_OK;
 }
+
+// Whether workgroups of 256, a multiple of eight parts by `columns`, fit one launch (fewer than 2^32 threads); asked before
+// anything is launched.
+bool one_launch(int64_t parts, int64_t columns) { return (parts + 7) / 8 * 8 * columns < (1ll << 24); }
 
 gas_status degree_weights(const Groups& g, const void* W, int32_t F, int32_t F1, int32_t N, float delta, int max_degree, void* out,
                           hipStream_t s) {
@@ -372,6 +377,7 @@ gas_status gas_pna_linear(const void* groups, int64_t n_rows, int32_t max_degree
     GAS_REQUIRE(ldx >= F + 3 * (int64_t)F1 && ldy >= F_out && (!push_hist || ld_push >= F_out), "%s: row stride smaller than the row", who);
     GAS_REQUIRE((push_idx == nullptr) == (push_hist == nullptr), "%s: push_idx and push_hist go together", who);
     GAS_REQUIRE(Y != X, "%s: the output must not alias the input", who);
+    GAS_REQUIRE(one_launch(most_tiles(n_rows, max_degree), (F_out + 63) / 64), "%s: too many rows for one launch", who);
     GAS_REQUIRE(workspace_bytes >= gas_pna_linear_workspace(max_degree, F, F1, F_out), "%s: workspace too small", who);
     const Groups g(const_cast<void*>(groups), n_rows, max_degree);
     st = degree_weights(g, W, F, F1, F_out, delta, max_degree, workspace, (hipStream_t)stream);
@@ -390,6 +396,7 @@ gas_status gas_pna_linear_bwd_input(const void* groups, int64_t n_rows, int32_t 
     GAS_REQUIRE(groups && G && W && GX && workspace, "%s: null pointer", who);
     GAS_REQUIRE(ldg >= F_out && ldgx >= F + 3 * (int64_t)F1, "%s: row stride smaller than the row", who);
     GAS_REQUIRE(G != GX, "%s: the output must not alias the input", who);
+    GAS_REQUIRE(one_launch(most_tiles(n_rows, max_degree), (F + 3 * F1 + 63) / 64), "%s: too many rows for one launch", who);
     GAS_REQUIRE(workspace_bytes >= gas_pna_linear_workspace(max_degree, F, F1, F_out), "%s: workspace too small", who);
     const Groups g(const_cast<void*>(groups), n_rows, max_degree);
     st = degree_weights(g, W, F, F1, F_out, delta, max_degree, workspace, (hipStream_t)stream);
@@ -416,13 +423,13 @@ gas_status gas_pna_linear_bwd_weight(const void* groups, int64_t n_rows, int32_t
     const Groups g(const_cast<void*>(groups), n_rows, max_degree);
     const PnaDwArgs a{g, static_cast<const float*>(X), ldx, static_cast<const float*>(G), ldg, F + 3 * F1, F_out, F, F1, 1.f / delta,
                       static_cast<float*>(workspace), dW};
+    const int64_t tiles = (int64_t)((a.K + kTile - 1) / kTile) * ((a.N + kTile - 1) / kTile);
+    GAS_REQUIRE(one_launch(most_slabs(n_rows, max_degree), tiles), "%s: too many rows for one launch", who);
     constexpr int lds = SplitGemm<kTile, kTile, 2, 2, 2, false, false, 1, true, true>::kLdsBytes;
     static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(pna_dw_kernel),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, lds + 4 * kMostSlab);
     GAS_CHECK_HIP(attr);
-    const int64_t tiles = (int64_t)((a.K + kTile - 1) / kTile) * ((a.N + kTile - 1) / kTile);
     const int64_t blocks = (most_slabs(n_rows, max_degree) + 7) / 8 * 8 * tiles;
-    GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "%s: too many rows for one launch", who);
     hipLaunchKernelGGL(pna_dw_kernel, dim3((unsigned)blocks), dim3(256), lds + 4 * g.in_slab, (hipStream_t)stream, a);
     hipLaunchKernelGGL(pna_dw_reduce_kernel, dim3((unsigned)(((int64_t)a.K * a.N + 31) / 32)), dim3(256), 0, (hipStream_t)stream, a);
     GAS_CHECK_HIP(hipGetLastError());

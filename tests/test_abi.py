@@ -176,3 +176,19 @@ def test_refused_layers_name_the_call():
     st = L.gas_spmm_linear_layers(1, at, at, at, at, i64(4), at, i64(64), one, i64(4), ld, 0, 66, f32(1), None, i64(0), f32(0), one, half,
                                   half, 1, one, i64(66), None, i64(0), None, None, i64(0), None, None)
     assert st == -1 and L.gas_last_error().startswith(b"gas_spmm_linear_layers: widths")
+
+
+def test_products_by_degree_of_more_tiles_than_a_launch_holds():
+    """Refused before anything is launched."""
+    L = binding.lib()
+    i64, f32, p = ctypes.c_int64, ctypes.c_float, ctypes.c_void_p
+    at, other = p(1 << 20), p(1 << 21)
+    n, big = i64((1 << 30) - 1), i64(1 << 50)
+    other = p(1 << 21)
+    calls = {
+        "gas_pna_linear": (at, n, 3, at, i64(1024), 256, 64, at, 1024, f32(1), 0, other, i64(1024), None, None, i64(0), at, big, None),
+        "gas_pna_linear_bwd_input": (at, n, 3, at, i64(256), 1024, 256, at, 256, f32(1), other, i64(2048), at, big, None),
+        "gas_pna_linear_bwd_weight": (at, n, 3, at, i64(9000), at, i64(4096), 4096, 1024, 4096, f32(1), other, at, big, None)}
+    for name, args in calls.items():
+        assert getattr(L, name)(*args) == -1
+        assert L.gas_last_error() == name.encode() + b": too many rows for one launch", name
