@@ -1605,7 +1605,7 @@ __global__ __launch_bounds__(256, WPS) void dw_batch_split_kernel(DwBatch b) {
 constexpr int kDwRows = 64;
 template <int B> __device__ __forceinline__ int dw_lds_unit(int row, int unit) { return row * (B / 8) + (unit ^ (4 * (row & 3))); }
 
-template <int BK, int BN, int WK>
+template <int BK, int BN, int WK, bool PASS>
 __global__ __launch_bounds__(512) void dw_bf16_kernel(DwArgs a) {
     constexpr int WN = 8 / WK, TK = BK / WK / 32, TN = BN / WN / 32;           // wavefronts, 32 x 32 blocks of one
     constexpr int NZ = kDwRows * BK / 8 / 512, NG = kDwRows * BN / 8 / 512;    // 16-byte units a thread brings
@@ -1628,7 +1628,8 @@ __global__ __launch_bounds__(512) void dw_bf16_kernel(DwArgs a) {
         const int64_t m = m0 + idx / units;
         const int f = f0 + 8 * (idx % units);
         const bool ok = m < m_end && f < flim;
-        const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(ok ? src + m * ld + f : src));
+        const u32x4* p = reinterpret_cast<const u32x4*>(ok ? src + m * ld + f : src);
+        const u32x4 v = PASS ? __builtin_nontemporal_load(p) : *p;
         return ok ? v : u32x4{0u, 0u, 0u, 0u};
     };
     auto fetch = [&](int64_t m0) {
@@ -1845,24 +1846,33 @@ gas_status launch_dw_split(int shape, int64_t n_slabs, const DwArgs& a, hipStrea
     return launch_dw_blocks(shape, dw_split_blocks(shape, n_slabs, a.K, a.N), &a, nullptr, s);
 }
 
-template <int BK, int BN, int WK>
+template <int BK, int BN, int WK, bool PASS>
 gas_status launch_dw_bf16_tile(const DwArgs& a, hipStream_t s) {
     constexpr int smem = 2 * kDwRows * (BK + BN) * 2;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(dw_bf16_kernel<BK, BN, WK>),
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(dw_bf16_kernel<BK, BN, WK, PASS>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     GAS_CHECK_HIP(attr);
     const dim3 grid((unsigned)a.n_slabs, (unsigned)((a.K + BK - 1) / BK), (unsigned)((a.N + BN - 1) / BN));
-    hipLaunchKernelGGL((dw_bf16_kernel<BK, BN, WK>), grid, dim3(512), smem, s, a);
+    hipLaunchKernelGGL((dw_bf16_kernel<BK, BN, WK, PASS>), grid, dim3(512), smem, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
+template <bool PASS>
+gas_status launch_dw_bf16_whole(const DwArgs& a, hipStream_t s) {
+    if (a.K <= 128 && a.N <= 128) return launch_dw_bf16_tile<128, 128, 4, PASS>(a, s);
+    if (a.K <= 128) return launch_dw_bf16_tile<128, 256, 2, PASS>(a, s);
+    if (a.N <= 128) return launch_dw_bf16_tile<256, 128, 4, PASS>(a, s);
+    return launch_dw_bf16_tile<256, 256, 4, PASS>(a, s);
+}
 
 // One tile for both widths up to 256; beyond, tiles of 128 x 128 (a 256-wide one would leave compute units without any).
+// Loads pass the caches by (non-temporal) where one tile has both widths, so that every row is read once, and the rows are of
+// 96 MB or more, which the passes between their writing and this call mostly push out of the 256 MB behind the L2s.  us in
+// training passes, all weight gradients of one, by and through the caches: GIN of 312,500 rows of 128 254 and 268, of 150,000 of
+// 128 and 256 256 and 268; but of 150,000 of 128 160 and 156, GCN of 50,000 of 128 41.5 and 35.7, of 1,432 -> 256 163 and 135.
 gas_status launch_dw_bf16(const DwArgs& a, hipStream_t s) {
-    if (a.K > 256 || a.N > 256 || (a.K <= 128 && a.N <= 128)) return launch_dw_bf16_tile<128, 128, 4>(a, s);
-    if (a.K <= 128) return launch_dw_bf16_tile<128, 256, 2>(a, s);
-    if (a.N <= 128) return launch_dw_bf16_tile<256, 128, 4>(a, s);
-    return launch_dw_bf16_tile<256, 256, 4>(a, s);
+    if (a.K > 256 || a.N > 256) return launch_dw_bf16_tile<128, 128, 4, false>(a, s);
+    return a.M * 2 * (a.K + a.N) >= (96 << 20) ? launch_dw_bf16_whole<true>(a, s) : launch_dw_bf16_whole<false>(a, s);
 }
 
 template <int KT, bool TRANS, bool MASK>

@@ -261,3 +261,9 @@ def test_bf16_weight_gradient_by_tiles(rows, k, n):
     zd, gd = z.double().t().contiguous(), g.double()
     bound = (rows + 64) * 2.0 ** -24 * 0.5 * (zd.abs() @ gd.abs())
     assert ((dw.double() - 0.5 * (zd @ gd)).abs() <= bound).all()
+
+
+# rows of 96 MB, from which on the loads pass the caches by, in each pair of tile widths
+@pytest.mark.parametrize("rows,k,n", [(196_608, 128, 128), (131_072, 128, 256), (131_072, 256, 128), (98_304, 256, 256), (98_303, 256, 256)])
+def test_bf16_weight_gradient_of_many_rows(rows, k, n):
+    test_bf16_weight_gradient_by_tiles(rows, k, n)
