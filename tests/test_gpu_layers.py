@@ -101,3 +101,40 @@ def test_refused_layers():
         gas.gas_spmm_linear_layers(ptr, col, col, val, b(x), [b(w) for w in ws[:2]], [b(y) for y in ys], [None] * 2)
     torch.cuda.synchronize()
     assert all((y == 2.0).all() for y in ys)                 # nothing was launched
+
+
+# layers that fill several flushes of waiting weight gradients, and fewer than one; a batch without halo rows
+@pytest.mark.parametrize("layers,width,blocks", [(36, 64, 2), (19, 32, 2), (3, 128, 2), (2, 48, 1), (17, 64, 6)])
+def test_passes_by_groups_have_the_bits_of_passes_by_single_layers(layers, width, blocks, monkeypatch):
+    """Outputs, pushed tables and every gradient of a GCNII, in groups and with the groups switched off, which is what a larger
+    batch takes."""
+    from gas_inputs import batches, graphs
+    from paper_2106_05609_amd import binding as B, executor
+    dev = torch.device("cuda")
+    g = graphs.sbm_partners(3_000, 6, 7.0, 0.85, 3, dev)
+    sg = batches.batch_subgraph(g, batches.split(g, 6 // blocks if blocks < 6 else 6, 0)[0], self_loops=True)
+    gen = torch.Generator(device=dev).manual_seed(layers)
+    normal = lambda *shape: torch.randn(*shape, generator=gen, device=dev)
+    model = executor.Model("gcnii", [normal(width, width) / width ** 0.5 for _ in range(layers)], normal(20, width) / 20 ** 0.5, 0.1)
+    x, stored, grad = normal(3_000, 20), normal(layers - 1, 3_000, width).clamp_(min=0), normal(sg.nb, width)
+    calls = []
+    for name in ("gas_spmm_linear_layers", "gas_spmm_t_relu_linear_layers", "gas_spmm_linear", "gas_spmm_t_relu_linear"):
+        monkeypatch.setattr(B, name, lambda *a, _f=getattr(B, name), _n=name, **kw: (calls.append(_n), _f(*a, **kw))[1])
+    together, results = executor._layers_together, []
+    for on in (True, False):
+        monkeypatch.setattr(executor, "_layers_together", together if on else lambda *a: False)
+        bg = executor.BatchGraph(sg.nb, sg.n_id, sg.rowptr, sg.col, g.deg, sg.colptr, sg.row, max_F=128)
+        tables, tables2 = stored.clone(), stored.clone()
+        calls.clear()
+        y = executor.forward_batch_fused(model, bg, x, tables)
+        assert set(calls) == {"gas_spmm_linear_layers" if on else "gas_spmm_linear"}
+        calls.clear()
+        y2, grads, kept = executor.train_batch(model, bg, x, tables2, grad, fused=True)
+        assert ("gas_spmm_linear_layers" in calls) == on and ("gas_spmm_linear" in calls) != on
+        if layers >= 4:                        # fewer do not share their weight gradients' launches
+            assert ("gas_spmm_t_relu_linear_layers" in calls) == on and ("gas_spmm_t_relu_linear" in calls) != on
+        results.append([y, tables, y2, tables2] + [grads[l] for l in range(layers)] + [grads["w_in"]] +
+                       [t for z, _, out in kept["layers"] for t in (z, out)])
+    assert torch.isfinite(results[0][0]).all()
+    for a, b in zip(*results):
+        assert torch.equal(a, b)
