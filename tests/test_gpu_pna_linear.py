@@ -212,3 +212,44 @@ def test_weight_gradient_by_long_slabs():
     B.gas_pna_linear_bwd_weight(B.gas_pna_groups(ptr, most), most, x.cuda(), g.cuda(), f1, delta, dw)
     bound = full.abs().t() @ g.double().abs()
     assert ((dw.cpu().double() - full.t() @ g.double()).abs() <= (32 + n ** 0.5) * 2.0 ** -24 * bound).all()
+
+
+@pytest.mark.parametrize("by_degree", [True, False])
+def test_gradients_in_64_bits_from_the_pass_own_decisions(by_degree, monkeypatch):
+    """A hidden unit within rounding of zero, or a neighbour within rounding of an extreme, may fall on either side, and takes its
+    whole share of a gradient with it.  With the pass's own decisions (its activations' signs, the first extreme of its
+    messages) differentiation in 64 bits gives its gradients to rounding: six products and sums in a chain, each within
+    3e-7 of 64 bits in norm."""
+    from paper_2106_05609_amd import executor
+    batch, ws, x, tables, grad = _pna_batch(40, 64, 2, monkeypatch)
+    if not by_degree:
+        monkeypatch.setattr(executor, "PNA_GROUPED_ROWS", 1 << 40)
+    bg, delta = batch(), 2.0
+    stored = [t.double() for t in tables]
+    y, grads, kept = executor.pna_train_batch(ws, delta, bg, x, tables, grad)
+    assert (bg._groups is not None) == by_degree
+    nb, d, col, ids = bg.nb, (bg.rowptr[1:] - bg.rowptr[:-1]).long(), bg.col.long(), bg.n_id.long()
+    row, nnz = torch.repeat_interleave(torch.arange(nb, device="cuda"), d), col.numel()
+    s = torch.log(d.double() + 1.0)[:, None] / delta
+    some = (d > 0)[:, None]
+    params, h = [[w.double().requires_grad_() for w in pair] for pair in ws], x[ids].double()
+    for l, (w1, w2) in enumerate(params):
+        f, f1 = h.shape[1], w1.shape[1]
+        messages, index = (h @ w1[f:])[col], row[:, None].expand(-1, f1)
+        mine = kept[l][1][col]                                          # the pass's own messages
+
+        def first(how):
+            best = torch.zeros(nb, f1, device="cuda").scatter_reduce_(0, index, mine, how, include_self=False)
+            at = torch.where(mine == best[row], torch.arange(nnz, device="cuda")[:, None].expand(-1, f1), nnz)
+            return messages.gather(0, torch.full((nb, f1), nnz, device="cuda").scatter_reduce_(0, index, at, "amin").clamp(max=nnz - 1))
+        mean = torch.zeros(nb, f1, dtype=torch.float64, device="cuda").index_add(0, row, messages) / d.clamp(min=1)[:, None]
+        blocks = [torch.where(some, t + h[:nb] @ w1[:f], 0.0) for t in (mean, first("amin"), first("amax"))]
+        scaled = [s * t for t in blocks] + [t / torch.where(some, s, 1.0) for t in blocks]
+        out = torch.cat([h[:nb]] + blocks + scaled, 1) @ w2
+        if l == 0:
+            out = out * (kept[l][3] > 0)
+            h = torch.cat([out, stored[0][ids[nb:]]])
+    want = torch.autograd.grad(out, [w for pair in params for w in pair], grad.double())
+    assert (y - out).norm() <= 1.8e-6 * out.norm()
+    for got, exact in zip([t for l in range(2) for t in grads[l]], want):
+        assert (got - exact).norm() <= 1.8e-6 * exact.norm()
