@@ -163,17 +163,18 @@ def _back_in_one_launch(width, rows, entries, longest) -> bool:
     (gas_spmm_t_relu_linear) and not two (gas_spmm_t_relu by its plan, gas_linear_bwd_input_add).  `rows` in-batch nodes,
     `entries` of the pattern, `longest` of one of them.  One team of lanes walks a row's entries, 0.09 us each, and the
     eight teams of a wavefront wait for the longest; the plan spreads a long row.  us, one launch and two:
-    - short rows: 512 rows of up to 30 entries, 32 -> 32 columns, 6.3 and 8.4, 21,248 8.8 and 18.0; 10,000 of up to 40
-      7.8 and 12.0;
-    - few rows, where the host bounds a pass and a launch more is 10 us of its time: 512 rows of up to 60 9.3 and 9.1;
-    - longer ones of like lengths where many rows hide them: 10,000 rows of up to 100 13.4 and 15.6, 21,248 of up to 200
-      34.8 and 41.5; but 512 rows of up to 100 13.3 and 10.2;
+    - short rows: 512 rows of up to 30 entries, 32 -> 32 columns, 5.5 and 7.1, 21,248 8.1 and 15.2; 10,000 of up to 40
+      7.3 and 10.4;
+    - few rows, where the host bounds a pass and a launch more is 10 us of its time: 512 rows of up to 60 8.4 and 7.8;
+    - longer ones of like lengths where many rows hide them: 10,000 rows of up to 100 13.2 and 14.1, 21,248 of up to 200
+      31.8 and 38.8; but 512 rows of up to 100 11.4 and 8.9;
     - power-law lengths up to 500 where rows have few entries (21,248 rows of 2.4 0.76-1.0 of the time, of 7.4 1.2-1.6);
     - 64 columns, 256-byte rows, up to 8,192 rows of any lengths up to ONE_LAUNCH_MAX_ROW: 5,000 rows of up to 100 14.9
-      and 27.0, power law 0.8-1.0 of the time (21,248 rows 1.0-1.2);
-    - more than 64 columns double the lanes of a row and halve the rows in flight: 21,248 rows of up to 30, 80 -> 80, 30.5
-      and 33.9, of up to 60 46.8 and 43.1.  128 columns, 512-byte rows, have the better plan: 5,000 rows of up to 20 10.8
-      and 13.2, 10,000 15.9 and 15.5, 21,248 26.7 and 23.4."""
+      and 25.2, power law 0.8-1.0 of the time (21,248 rows 1.0-1.2);
+    - more than 64 columns double the lanes of a row and halve the rows in flight: 21,248 rows of up to 30, 80 -> 80, 26.1
+      and 30.8, 96 -> 96 28.6 and 28.8, of up to 60 39.3 and 40.4, 41.9 and 38.6, of up to 100 56.9 and 54.8.  128 columns,
+      512-byte rows, have the better plan: 5,000 rows of up to 20 11.7 and 12.0, 8,192 12.6 and 12.8, 10,000 17.5 and 15.1,
+      21,248 27.4 and 23.0."""
     if longest > ONE_LAUNCH_MAX_ROW:
         return False
     if longest <= (64 if rows <= 4096 else 48 if width <= 64 else 32):
@@ -186,15 +187,15 @@ def _back_in_one_launch(width, rows, entries, longest) -> bool:
 
 def _layers_together(model: Model, bg, h0) -> bool:
     """Whether GCNII's layers (all of one width) go in groups by one call (gas_spmm_linear_layers): narrow fp32 layers without long
-    rows, of few rows.  A layer takes the host 13 us by a call of its own and 5 in a group.  16 layers of 64, one by one and in
+    rows, of few rows.  A layer takes the host 14 us by a call of its own and 7 in a group of four or eight.  16 layers of 64, one by one and in
     groups: 500 rows 245 and 143 us, 5,000 244 and 151, 12,500 246 and 208, 16,000 246 and 224; 21,248 287 and 289, where the card
     takes longer than either and a pass that starts on an idle one waits 14 us for its first groups."""
     return B.spmm_linear_supported(h0, h0.shape[1]) and bg.max_row <= ONE_LAUNCH_MAX_ROW and model.n_layers >= 2 and 0 < bg.nb <= 16384
 
 
 def _layer_groups(count, most=8):
-    """Ranges of layers that go in one call: 2, 2, 4 and then `most`.  The pointers and the launch of a layer take the host 7 us:
-    the card has work in hand while the next, larger call is put together."""
+    """Ranges of layers that go in one call: 2, 2, 4 and then `most`: the card has work in hand while the host puts the next, larger
+    call together."""
     first = 0
     while first < count:
         end = min(count, first + max(2, min(most, first)))
