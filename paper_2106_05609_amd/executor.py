@@ -27,6 +27,26 @@ class _Kept:
         self.event.record(stream)
 
 
+def plan_limits(rows, entries, longest):
+    """Which rows of a pattern are cut into chunks, and how long a chunk is (gas_plan_options).  A wavefront, or a team of its lanes,
+    walks a light row's entries, 0.1 us each, and a launch waits for the longest; a chunk's partial sum is written and read
+    again, and any heavy row adds two launches.  So the line follows the batch: 256 entries where the whole takes some 200 us
+    and more, 64 where it takes 20, but no less than twice the mean (rows of like lengths hide each other's walks), and none
+    where the longest row is hardly longer than that.  us, rows above 512 by 256 entries and so, aggregations of power-law batches (and
+    their adjoints), 256 floats, 64 floats, 256 bf16:
+    - 250,000 rows of 40: 1,223 -> 1,192 (565 -> 553), 459 -> 417 (259 -> 245), 704 -> 659 (329 -> 321);
+    - 50,000 rows of 37: 260 -> 223 (121 -> 99), 140 -> 99 (99 -> 65), 180 -> 137 (117 -> 79);
+    - 15,000 rows of 43: 143 -> 83 (53 -> 41), 105 -> 43 (60 -> 33), 125 -> 53 (59 -> 38);
+    - 3,750 rows of 24, the longest 269: 34 -> 29, 33 -> 22, 33 -> 25; by chunks of 128 50, 43, 49;
+    - 25,000 rows of 18, the longest 141: whole 64, with 64 the line 75."""
+    if rows == 0:
+        return None
+    line = min(512, max(256 if entries >= 3_000_000 else 128 if entries >= 1_000_000 else 64, -(-2 * entries // rows)))
+    if longest <= min(512, line + 144):
+        return None
+    return dict(heavy_threshold=line, chunk=128 if entries >= 1_000_000 else 64 if entries >= 200_000 else 32)
+
+
 class BatchGraph:
     """Device-side index structure of one batch subgraph plus its plans."""
 
@@ -51,7 +71,8 @@ class BatchGraph:
         self.n_id, self.rowptr, self.col = n_id, rowptr, col
         self.nnz = int(col.numel())
         self.max_row = int((rowptr[1:] - rowptr[:-1]).max().item()) if self.nb > 0 else 0
-        self.plan = part("plan_csr", lambda: B.gas_plan_create(rowptr, self.nnz, max_F, ind=col, options=plan_options))
+        self.plan = part("plan_csr", lambda: B.gas_plan_create(rowptr, self.nnz, max_F, ind=col,
+                                                               options=plan_options or plan_limits(self.nb, self.nnz, self.max_row)))
         self.val = None
         if normalise:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
@@ -67,8 +88,8 @@ class BatchGraph:
             if self.nb > 0:
                 longest = (colptr[1:self.nb + 1] - colptr[:self.nb]).max()
                 self.max_col, self.nnz_t = torch.stack((longest, colptr[self.nb])).tolist()    # one read-back
-            self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], self.nnz_t, max_F,
-                                                                     n_rows=self.nb, ind=row, options=plan_options))
+            self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], self.nnz_t, max_F, n_rows=self.nb, ind=row,
+                                                                     options=plan_options or plan_limits(self.nb, self.nnz_t, self.max_col)))
             if normalise:
                 self.val_t = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
                 part("gcn_norm_csc", lambda: B.gas_gcn_norm(colptr, row, n_id, deg, self.val_t))
@@ -81,7 +102,9 @@ class BatchGraph:
         """Plan of the backward aggregation over ALL columns, halo included (GCNII's first layer: the gradient of
         the projected features of every node of V_b); built on first use, once per batch."""
         if self._plan_t_all is None:
-            self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row)
+            longest = int((self.colptr[1:] - self.colptr[:-1]).max().item()) if self.nv > 0 else 0
+            self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row,
+                                                 options=plan_limits(self.nv, self.nnz, longest))
         return self._plan_t_all
 
     def _once(self, name, build):

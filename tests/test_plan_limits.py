@@ -1,0 +1,27 @@
+"""The lines between light and heavy rows that a batch's plans are made with (executor.plan_limits)."""
+import pytest
+
+from paper_2106_05609_amd.executor import plan_limits
+
+
+@pytest.mark.parametrize("rows,entries,longest,want", [
+    (0, 0, 0, None),
+    (3_750, 89_108, 269, (64, 32)),                      # few entries: a launch waits for its longest row
+    (25_000, 462_196, 141, None),                        # hardly longer than the line
+    (15_000, 642_765, 563, (86, 64)),                    # twice the mean
+    (50_000, 1_826_185, 1_705, (128, 128)),
+    (600_000, 50_318_351, 17_482, (256, 128)),
+    (4_000, 480_381, 152, None),                         # long rows of like lengths
+    (1_000, 600_000, 5_000, (512, 64)),                  # no line above 512
+    (1, 513, 513, (512, 32)),
+])
+def test_lines_follow_the_batch(rows, entries, longest, want):
+    got = plan_limits(rows, entries, longest)
+    assert got == (None if want is None else dict(heavy_threshold=want[0], chunk=want[1]))
+
+
+def test_rows_above_512_are_always_cut():
+    for rows in (1, 100, 10_000, 1_000_000):
+        for mean in (1, 30, 400, 2_000):
+            got = plan_limits(rows, rows * mean, max(513, mean))
+            assert got is not None and got["heavy_threshold"] <= 512 and got["chunk"] <= 128
