@@ -20,7 +20,7 @@
 // light rows follow in spmm_rows_kernel.  The chunks are cut and ordered by
 // L2-sized windows of the source rows (plan_host.h states the rules), so that
 // wavefronts running together gather from rows that fit the L2 of every XCD.
-// Batches without hubs whose rows are 512 or 1,024 bytes go by slices (spmm_slices_kernel).
+// Light rows go by slices of a row instead (spmm_slices_kernel) where rows_form() says so.
 // The summation order is a
 // function of the plan alone, so results are bit-identical from run to run.
 #include "common.h"
@@ -29,6 +29,7 @@
 
 #include <algorithm>
 #include <string.h>
+#include <type_traits>
 #include <vector>
 
 namespace gas {
@@ -63,7 +64,7 @@ struct SpmmArgs {
     int64_t n_groups;
     int xcd_ranges;       // grouped light rows: one contiguous range of groups per XCD, [xcd_start[x], xcd_start[x+1])
     int64_t xcd_start[9];
-    int slices;           // rows of 512 or 1,024 bytes: 0 whole, 1 or 2 by slices of so many times 256 bytes
+    int pieces, in_turn;  // rows_form()
 };
 
 __device__ __forceinline__ const char* own_row(const SpmmArgs& a, int64_t row) {
@@ -222,7 +223,7 @@ __device__ __forceinline__ void epilogue(const SpmmArgs& a, int64_t row, int uni
     }
 }
 
-// ---- wave-per-row path for rows of exactly 64 vectors of VB bytes (1 KiB, 512 B or 256 B)
+// ---- wave-per-row path for rows of exactly 64 vectors of VB bytes (1 KiB or 512 B; chunks of heavy rows 256 B too)
 // Short rows are the common case on power-law graphs, and one wavefront per row
 // pays three dependent memory latencies (row pointers, indices, feature rows)
 // for a handful of gathers.  Here consecutive light rows are bundled at plan
@@ -491,36 +492,55 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
     }
 }
 
-// ---- rows of 512 or 1,024 bytes by slices of 256 or 512 bytes
-// A gathered row is fetched into the L2 of every XCD whose rows list it, and eight copies of a batch's rows do not fit.
-// Here an XCD takes one slice of a range of rows: 1,024-byte rows have four slices of 256 bytes, so a slice's two XCDs take
-// half of the rows each and an L2 holds a quarter of the bytes.  A team of 16 lanes owns one row's slice (P pieces of 16
-// bytes a lane); it reads 32 indices with two loads, the lane that read an index forms the row's address and the team
-// takes it by data-parallel moves.  Four rows of a wavefront walk their chain of dependent loads (row pointers, indices,
-// rows) together.  A row's entries are folded in the stored order: the sums are the wave-per-row kernel's, bit for bit.
-// Bounded by that chain and, with inputs that are not in the caches, by the misses.  us against the wave-per-row kernel on
-// rotating inputs, 256 floats: 50,000 clustered rows of 11 entries 56 (60 with a range of the rows per XCD, 83 without),
-// their adjoint with mask 52 (59, 83); 5,000 rows 9.4 (14); 4,000 rows of 119 27 (32); 160,000 clustered rows of 21 408
-// (473), adjoint 359 (436).  256 bf16: 50,000 rows 28 (37), 4,000 of 119 23 (31).
-// P = 2 (half the wavefronts, twice the bytes a step) is for short rows; with long, less even ones a wavefront waits for its
-// longest (7,500 power-law rows of 46: 45 us by P = 1, 66 by P = 2, wave-per-row 55).  Not kept: slices of 128 bytes (one for
-// each XCD; 49 us with inputs in the Infinity Cache, 77 without: HBM gives up single lines slowly), several rows a team with
-// the next row's indices requested ahead (its last workgroups end late), loads past a row's end not switched off.
+// ---- rows by slices
+// A team of 16 lanes owns one row's slice of up to 16 P pieces of 16 bytes (P pieces a lane); it reads 32 indices with two
+// loads, the lane that read an index forms the row's address and the team takes it by data-parallel moves.  Four rows of a
+// wavefront walk their chain of dependent loads (row pointers, indices, rows) together, where the kernels of a wavefront a row
+// walk one.  A row's entries are folded in the stored order: the sums are the wave-per-row kernel's, bit for bit.
+// Bounded by that chain and, with inputs that are not in the caches, by the misses.  us, a wavefront a row -> slices, inputs
+// that rotate through more than the Infinity Cache holds, 50,000 clustered rows of 11 entries: 47 floats 24 -> 16, 64 28 -> 16,
+// 136 50 -> 33, 184 53 -> 39, 248 61 -> 45, 1,433 429 -> 370, 128 bf16 30 -> 15, 136 36 -> 26; 150,000 power-law rows of 69, 64
+// floats 421 -> 385; 64,000 clustered rows of 23 entries, 256 floats 184 -> 108.
+// Contiguous (in_turn 0): the slices' rows, slice after slice, are cut into eight ranges, one for each XCD, so that a cluster is
+// gathered into one L2, of which an XCD then holds a slice of its rows.  In turn: a slice's rows are dealt to the XCDs one after the
+// other, for lengths that differ along the batch (a power law's first rows are its longest).
+// rows_form() has the line between the forms.  Not kept: slices of 128 bytes, one for each XCD (their rows' lines lie in an
+// eighth of an L2's channels: all gathers out of 2,048 rows of 1,024 bytes 2.1 ms whole, 2.7 by 256, 3.7 by 128 bytes), several
+// rows a team with the next row's indices requested ahead (its last workgroups end late), rows put in order of length within
+// a workgroup, loads past a row's end not switched off, steps without masks where every team has them in full (they cost
+// registers: a wavefront less on a SIMD).
 constexpr int kSliceRows = 16;      // rows of a workgroup (four wavefronts of four teams)
 
 template <int P, bool XBF, bool ZBF, bool MASK>
-__global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices) {
-    constexpr int G = 16, E = Unit<XBF>::E, U = P == 2 ? 4 : 8;
+__global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices, int width) {
+    constexpr int G = 16, E = Unit<XBF>::E, EB = XBF ? 2 : 4, U = P == 1 ? 8 : 4;
+    typedef std::conditional_t<XBF, u32x4_at2, u32x4_at4> Piece;
     const int lane = threadIdx.x & 63, j = lane % G;
-    const int xcd = blockIdx.x & 7, parts = 8 / slices;                   // workgroups go to the eight XCDs in turn
-    const int unit = (xcd % slices) * (G * P) + j;                        // with P == 2 the lane's other one is unit + G
-    const int64_t tiles = (a.n_rows + kSliceRows - 1) / kSliceRows, per_part = (tiles + parts - 1) / parts;
-    const int64_t tile = (xcd / slices) * per_part + (blockIdx.x >> 3);
-    if ((int)(blockIdx.x >> 3) >= per_part || tile >= tiles) return;
-    const int64_t row = tile * kSliceRows + (threadIdx.x / G);
+    const uint32_t tiles = (uint32_t)((a.n_rows + kSliceRows - 1) / kSliceRows);
+    const uint32_t xcd = blockIdx.x & 7, i = blockIdx.x >> 3;             // workgroups go to the eight XCDs in turn
+    uint32_t slice, tile;
+    if (a.in_turn) {
+        slice = blockIdx.x / tiles;
+        tile = blockIdx.x - slice * tiles;
+    } else {
+        const uint32_t jobs = tiles * slices, per = (jobs + 7) / 8, job = xcd * per + i;
+        if (i >= per || job >= jobs) return;
+        slice = job / tiles;
+        tile = job - slice * tiles;
+    }
+    const int64_t row = (int64_t)tile * kSliceRows + (threadIdx.x / G);
     if (row >= a.n_rows) return;
     const int b = a.ptr[row], e = a.ptr[row + 1];
-    const int64_t off = (int64_t)unit * 16;
+    if (e - b > a.threshold) return;                                      // heavy row: done by the chunk kernel
+    // the lane's units of the slice: j, j + G, ...; a lane past the slice's width loads nothing
+    uint32_t off[P];
+    bool mine[P];          // (P == 1 loads the slice's last unit there: one condition less for every load)
+#pragma unroll
+    for (int p = 0; p < P; ++p) {
+        const int w = j + G * p, unit = slice * width + w;
+        mine[p] = w < width && unit < a.units;
+        off[p] = unit_start<XBF>(a, min(unit, a.units - 1)) * EB;
+    }
     // entries k + j and k + G + j (past the row's end its last one: a valid address, never folded)
     int s[2];
     float v[2];
@@ -535,7 +555,7 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
     if (b < e) fetch(b);
     auto piece = [&](const char* base, u32x4 (&t)[P]) {
 #pragma unroll
-        for (int p = 0; p < P; ++p) t[p] = *reinterpret_cast<const u32x4*>(base + off + 16 * G * p);
+        for (int p = 0; p < P; ++p) t[p] = *reinterpret_cast<const Piece*>(base + off[p]);
     };
     u32x4 own[P], res[P], act[P];
     const bool use_own = a.diag != 0.f && row < a.n_diag;
@@ -567,11 +587,11 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
                 u32x4 x[U][P];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const char* r = reinterpret_cast<const char*>((uint64_t)(uint32_t)team_lane<G>(lo[h], q + u) |
-                                                                  ((uint64_t)(uint32_t)team_lane<G>(hi[h], q + u) << 32));
+                    const u32x2 r = {(uint32_t)team_lane<G>(lo[h], q + u), (uint32_t)team_lane<G>(hi[h], q + u)};
                     if (G * h + q + u < cnt) {
 #pragma unroll
-                        for (int p = 0; p < P; ++p) x[u][p] = *reinterpret_cast<const u32x4*>(r + off + 16 * G * p);
+                        for (int p = 0; p < P; ++p)
+                            if (P == 1 || mine[p]) x[u][p] = load_global<Piece>(__builtin_bit_cast(uint64_t, r) + off[p]);
                     }
                 }
 #pragma unroll
@@ -586,6 +606,7 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
     }
 #pragma unroll
     for (int p = 0; p < P; ++p) {
+        if (!mine[p]) continue;
         float z[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) z[i] = a.s_agg * acc[p][i];
@@ -598,17 +619,17 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
                 z[i] = y > 0.f ? z[i] : 0.f;
             }
         }
-        char* zp = a.Z + row * a.z_stride + (int64_t)(unit + G * p) * E * (ZBF ? 2 : 4);
+        char* zp = a.Z + row * a.z_stride + (int64_t)(off[p] / EB) * (ZBF ? 2 : 4);
         if constexpr (ZBF) {
             u32x4 o;
 #pragma unroll
             for (int i = 0; i < 4; ++i) o[i] = pack_bf16(z[2 * i], z[2 * i + 1]);
-            __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(zp));
+            __builtin_nontemporal_store(o, reinterpret_cast<u32x4_at2*>(zp));
         } else {
 #pragma unroll
             for (int q = 0; q < E / 4; ++q) {
                 f32x4 o = {z[4 * q], z[4 * q + 1], z[4 * q + 2], z[4 * q + 3]};
-                __builtin_nontemporal_store(o, reinterpret_cast<f32x4*>(zp + 16 * q));
+                __builtin_nontemporal_store(o, reinterpret_cast<f32x4_at4*>(zp + 16 * q));
             }
         }
     }
@@ -647,7 +668,8 @@ __global__ __launch_bounds__(256) void spmm_rows_kernel(SpmmArgs a) {
     }
 }
 
-// One wavefront per heavy row: add the chunk partials in chunk order.
+// One wavefront per heavy row: add the chunk partials in chunk order.  A hub has hundreds, each a load that the sum would wait
+// for: eight are requested together (600,000 rows, 10,600 heavy ones with 634,000 chunks of 256 floats 200 -> 135 us).
 template <bool XBF, bool ZBF>
 __global__ __launch_bounds__(256) void spmm_heavy_reduce_kernel(SpmmArgs a) {
     const int64_t h = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -659,8 +681,22 @@ __global__ __launch_bounds__(256) void spmm_heavy_reduce_kernel(SpmmArgs a) {
         float acc[E];
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[e] = 0.f;
-        for (int c = first; c < last; ++c) {
-            const float* src = a.partial + (int64_t)c * a.F + unit_start<XBF>(a, unit);
+        const float* src = a.partial + (int64_t)first * a.F + unit_start<XBF>(a, unit);
+        int c = first;
+        for (; c + 8 <= last; c += 8, src += 8 * (int64_t)a.F) {          // eight loads in flight, added in chunk order
+            f32x4 v[8][E / 4];
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int q = 0; q < E / 4; ++q) v[k][q] = *reinterpret_cast<const f32x4_at4*>(src + k * (int64_t)a.F + 4 * q);
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+#pragma unroll
+                for (int q = 0; q < E / 4; ++q)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) acc[4 * q + i] += v[k][q][i];
+        }
+        for (; c < last; ++c, src += a.F) {
 #pragma unroll
             for (int q = 0; q < E / 4; ++q) {
                 const f32x4 v = *reinterpret_cast<const f32x4_at4*>(src + 4 * q);
@@ -741,12 +777,12 @@ gas_status launch_rows(const SpmmArgs& a, hipStream_t s) {
 
 template <int P, bool XBF, bool ZBF>
 gas_status launch_slices(const SpmmArgs& a, hipStream_t s) {
-    const int slices = a.units / (16 * P);                                // 1, 2 or 4
-    const int64_t tiles = (a.n_rows + kSliceRows - 1) / kSliceRows, parts = 8 / slices;
-    const int64_t blocks = 8 * ((tiles + parts - 1) / parts);
+    const int slices = (a.units + 16 * P - 1) / (16 * P), width = (a.units + slices - 1) / slices;
+    const int64_t jobs = (a.n_rows + kSliceRows - 1) / kSliceRows * slices;
+    const int64_t blocks = a.in_turn ? jobs : 8 * ((jobs + 7) / 8);
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
-    if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, true>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices);
-    else hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, false>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices);
+    if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, true>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices, width);
+    else hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, false>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices, width);
     return GAS_OK;
 }
 
@@ -762,14 +798,13 @@ gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
                            0, s, a);
     }
     gas_status st;
-    // rows of exactly 1 KiB, 512 B or 256 B: grouped wave-per-row path
-    if (whole && a.slices && (u == 64 || u == 32))
-        st = a.slices == 2 ? launch_slices<2, XBF, ZBF>(a, s) : launch_slices<1, XBF, ZBF>(a, s);
+    if (a.pieces == 1) st = launch_slices<1, XBF, ZBF>(a, s);
+    else if (a.pieces == 2) st = launch_slices<2, XBF, ZBF>(a, s);
+    else if (a.pieces == 3) st = launch_slices<3, XBF, ZBF>(a, s);
+    // rows of exactly 1 KiB or 512 B: grouped wave-per-row path
     else if (whole && a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
     else if (whole && a.group && u == 32) st = launch_rows<32, 1, 4, XBF, ZBF, 8>(a, s);
-    else if (whole && a.group && u == 16) st = launch_rows<16, 1, 4, XBF, ZBF, 4>(a, s);
     else if (u <= 8) st = launch_rows<8, 1, 2, XBF, ZBF>(a, s);
-    else if (u <= 16) st = launch_rows<16, 1, 4, XBF, ZBF>(a, s);
     else if (u <= 32) st = launch_rows<32, 1, 4, XBF, ZBF>(a, s);
     else if (u <= 64) st = launch_rows<64, 1, 8, XBF, ZBF>(a, s);
     else if (u <= 128) st = launch_rows<64, 2, 4, XBF, ZBF>(a, s);
@@ -777,6 +812,48 @@ gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
     if (st != GAS_OK) return st;
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
+}
+
+// How the light rows are taken: by slices of 16 `pieces` units (0: a wavefront a row), contiguous or in turn.  us on rotating
+// inputs, a wavefront a row and slices, over clustered patterns of 2,000 to 200,000 rows of 7 to 31 entries and power laws of
+// 1,250 to 600,000 rows (mean 2 to 86) with their adjoints:
+// - up to 16 units a row fits one slice and always wins (64 floats: 50,000 clustered rows 28 and 16, their adjoint 29 and 15,
+//   250,000 power-law rows 326 and 316 forward, 187 and 140 adjoint), but for at most 8 units and few, long rows, where the
+//   other form has eight entries in flight beside each other (15,000 rows of 43, 32 floats 23 and 26);
+// - 17 to 31 units are one slice of two pieces a lane (136 bf16: 50,000 clustered rows 36 and 26, 600,000 power-law rows 2,337 and
+//   2,256); few long rows of a power law keep a wavefront each (50,000 rows of 36, 100 floats 114 and 119);
+// - 32 and 64 whole units, 512 and 1,024 bytes, go by 256 bytes (600,000 power-law rows of 84, 256 floats 5.06 and 4.94 ms,
+//   adjoint 1.86 and 1.79; 100,000 clustered rows of 10 147 and 101); 64 clustered with two pieces where few entries share a row and
+//   the batch is not much more than the L2s hold (50,000 of 11: 43 by one, 39 by two pieces; 75,000 of 7 48 and 43; 64,000 of 23
+//   108 and 145); a wavefront a row with more than 28 entries, which fetches a cluster's rows once into its XCD (25,000 of 31:
+//   56 and 62), and with fewer than four, grouped (312,500 rows of 0.9, 256 bf16 100 and 132);
+// - 33 to 48 units are one slice of three pieces (184 floats: 50,000 clustered rows 53 and 39, adjoint of 250,000 power-law rows 491
+//   and 456);
+// - 49 to 63 units are two slices that share a cache line: clustered and near the size of the L2s (248 floats: 50,000 rows 61
+//   and 45, 100,000 143 and 155; power law 600,000 5.32 and 5.55 ms);
+// - wider ones two pieces at a time where they are clustered or few (1,433 floats: 50,000 rows 429 and 370, 5,000 49 and 37; 150,000
+//   power-law rows 7.2 and 7.4 ms);
+// - few rows are a matter of the chain of loads alone: one piece a lane has eight entries in flight (5,000 rows of 11, 248
+//   floats 9.7 and 8.7; 1,250 power-law rows of 19, 184 floats 28 and 17, by three pieces 32).
+struct RowsForm { int pieces, in_turn; };
+RowsForm rows_form(const gas_plan* plan, int units, bool whole) {
+    const int64_t n = plan->n_rows, nnz = plan->nnz, bytes = n * units * 16;
+    const bool even = whole && (units == 32 || units == 64);
+    if (plan->xcd_ranges) {
+        if (units > 64) return {2, 0};
+        if (units <= 16 || n <= 8192 || (even && units == 32)) return {1, 0};
+        if (units <= 32) return {2, 0};
+        if (units <= 48) return {units <= 40 || bytes <= (int64_t)112 << 20 ? 3 : 0, 0};
+        if (nnz > 28 * n) return {0, 0};
+        if (!even) return {bytes <= (int64_t)80 << 20 ? 2 : 0, 0};
+        return {nnz <= 16 * n && bytes <= (int64_t)80 << 20 ? 2 : 1, 0};
+    }
+    if (units <= 8 && n < 65536) return {0, 0};
+    if (n <= 16384) return {units > 64 ? 2 : 1, 0};
+    if (units <= 16) return {1, 1};
+    if (even) return {nnz < 4 * n ? 0 : 1, 1};
+    if (units <= 32) return {n < 65536 && nnz > 24 * n ? 0 : 2, 1};
+    return {units <= 48 ? 3 : 0, 1};
 }
 
 gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, const int32_t* ind, const float* val,
@@ -828,28 +905,11 @@ gas_status run_spmm(const char* who, const gas_plan* plan, const int32_t* ptr, c
     a.group = plan->d_group; a.n_groups = plan->n_groups;
     a.xcd_ranges = plan->xcd_ranges;
     for (int x = 0; x < 9; ++x) a.xcd_start[x] = plan->xcd_start[x];
-    // By slices: no row above the threshold, and (us on rotating inputs, whole rows -> slices)
-    // - up to 6,144 rows of any pattern and length: 5,000 power-law rows of 30 entries 31 -> 27, 4,000 equal ones of 119
-    //   32 -> 27, 6,000 clustered of 26 16.6 -> 15.3; without clusters up to 16,384: 7,500 power-law rows of 46 55 -> 45;
-    // - a clustered pattern in rows of 512 bytes up to 96 MB: 100,000 rows of 22 entries 102 -> 90 (bf16 102 -> 97), 200,000 of
-    //   8 96 -> 86 (82 -> 72); 300,000 bf16 rows of 3 86 -> 93;
-    // - in rows of 1,024 bytes up to 56 MB and 16 entries: 50,000 rows of 11 60 -> 56, 64,000 of 14 84 -> 76 in clusters of
-    //   5,000 and 74 -> 77 in clusters of 1,250.  With more entries a whole row, fetched once into the XCD that has its
-    //   cluster, serves many: 12,000 rows of 30 29 -> 33, 64,000 of 22 98 -> 118;
-    // - other patterns of at most eight entries a row, fp32 up to 32 MB: adjoints over 31,250 power-law rows 47 -> 25.  A
-    //   wavefront's teams wait for each other where lengths are uneven, from there on for longer than the slices save:
-    //   65,000 rows of 1,024 bytes and 2.4 entries 43 -> 52, 100,000 of 512 37 -> 44, bf16 already 48,000 of 5.5 37 -> 41.
-    // Two slices at a time where rows are short and, as a clustered pattern tells, of like lengths: 50,000 rows 62 -> 56 (an
-    // adjoint over 13,750 power-law rows: whole 65, one slice 52, two 75).
-    const int64_t row_bytes = plan->n_rows * a.units * 16;
-    const bool few = plan->nnz <= (plan->xcd_ranges ? 16 : 8) * plan->n_rows;
-    const bool fits = plan->n_rows <= (plan->xcd_ranges ? 6144 : 16384) ||
-                      (plan->xcd_ranges ? (a.units == 32 ? row_bytes <= (int64_t)96 << 20 : few && row_bytes <= (int64_t)56 << 20)
-                                        : few && dt_x == GAS_F32 && row_bytes <= (int64_t)32 << 20);
-    a.slices = plan->n_heavy > 0 || !fits ? 0 : plan->xcd_ranges && few ? 2 : 1;
     const bool whole = (F * xb) % 16 == 0 && aligned16(X) && a.x_stride % 16 == 0 && aligned16(Z) &&
                        a.z_stride % 16 == 0 && (!R || (aligned16(R) && a.r_stride % 16 == 0)) &&
                        (!H || (aligned16(H) && a.h_stride % 16 == 0)) && (!Y || (aligned16(Y) && a.y_stride % 16 == 0));
+    const RowsForm form = rows_form(plan, a.units, whole);
+    a.pieces = form.pieces; a.in_turn = form.in_turn;
     const bool xbf = dt_x == GAS_BF16, zbf = dt_z == GAS_BF16;
     // From one 16-byte unit on, rows go by units whatever their width and alignment: a row of 1,433 floats 5,000 times,
     // 11 entries each, 49 us (element-wise 254 us).

@@ -161,8 +161,8 @@ template <int G>
 __device__ __forceinline__ int team_lane(int v, int u) {
 #define GAS_CASE(n)                                                                                     \
     case n:                                                                                             \
-        if constexpr (G == 16) return __builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0xf, false);  \
-        else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_update_dpp(0, v, 0x150 + (n), 0xf, 0x3, false), v, 0x150 + ((n) + 8) % 16, 0xf, 0xc, false);
+        if constexpr (G == 16) return __builtin_amdgcn_mov_dpp(v, 0x150 + (n), 0xf, 0xf, true);          \
+        else return __builtin_amdgcn_update_dpp(__builtin_amdgcn_mov_dpp(v, 0x150 + (n), 0xf, 0x3, true), v, 0x150 + ((n) + 8) % 16, 0xf, 0xc, false);
     switch (u) {
         GAS_CASE(0) GAS_CASE(1) GAS_CASE(2) GAS_CASE(3) GAS_CASE(4) GAS_CASE(5) GAS_CASE(6) GAS_CASE(7)
         GAS_CASE(8) GAS_CASE(9) GAS_CASE(10) GAS_CASE(11) GAS_CASE(12) GAS_CASE(13) GAS_CASE(14) GAS_CASE(15)
