@@ -1,6 +1,7 @@
-"""Thin ctypes binding of libgas.so: same names as the C ABI (include/gas.h),
+"""Thin binding of libgas.so: same names as the C ABI (include/gas.h),
 argument marshalling only.  Tensors are torch tensors on the GPU; every step
-runs in the library's kernels on torch's current stream."""
+runs in the library's kernels on torch's current stream.  The calls of a pass go
+through csrc/marshal.cpp, the others through ctypes."""
 import ctypes as C
 import os
 
@@ -93,19 +94,23 @@ _SIGNATURES = dict(
 
 
 class _Calls:
-    """The library's functions with their argument types declared: plain Python numbers are converted by ctypes itself,
-    where a ctypes object around every argument cost 3 us of a call's 8.  A handle of its own: what lib() returns takes
+    """The library's functions with their argument types declared: plain Python numbers are converted by ctypes itself, and those
+    of a pass by the marshalling module (30 arguments: 0.4 us, ctypes 3).  A handle of its own: what lib() returns takes
     any ctypes objects, as before."""
 
     def __init__(self):
+        global _mat, _size, _ptr
         lib()
+        from . import _marshal
+        _marshal.set_slow(_mat_any, _size_any, _ptr_any)
+        _mat, _size, _ptr = _marshal.mat, _marshal.size, _marshal.ptr
         raw = C.CDLL(LIB_PATH)
         types = dict(p=C.c_void_p, q=C.c_int64, i=C.c_int32, f=C.c_float)
         for name, sig in _SIGNATURES.items():
             fn = getattr(raw, name)
             fn.argtypes = [types[c] for c in sig]
             fn.restype = C.c_int64 if name.endswith("_workspace") else C.c_int
-            setattr(self, name, fn)
+            setattr(self, name, getattr(_marshal, name, fn))
 
 
 _typed = None
@@ -131,14 +136,23 @@ def _dt(t: torch.Tensor) -> int:
     raise TypeError(f"feature tensors are float32 or bfloat16, got {t.dtype}")
 
 
-def _mat(t: torch.Tensor):
+def _mat_any(t):
     """(pointer, leading dimension in elements) of a 2-D row-major tensor or view."""
     if t.dim() != 2 or (t.shape[1] > 1 and t.stride(1) != 1):
         raise ValueError("need a 2-D tensor with contiguous rows")
     return t.data_ptr(), t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
 
 
-def _ptr(t, dtype=None):
+_CODES = {torch.float32: F32, torch.bfloat16: BF16}
+
+
+def _size_any(t):
+    """_mat(t), rows, columns and the dtype's code (of any other type the dtype itself: equal only to itself, and no call takes
+    it)."""
+    return _mat_any(t) + (t.shape[0], t.shape[1], _CODES.get(t.dtype, t.dtype))
+
+
+def _ptr_any(t, dtype=None):
     if t is None:
         return 0
     if dtype is not None and t.dtype != dtype:
@@ -146,6 +160,16 @@ def _ptr(t, dtype=None):
     if not t.is_contiguous():
         raise ValueError("need a contiguous tensor")
     return t.data_ptr()
+
+
+_mat, _size, _ptr = _mat_any, _size_any, _ptr_any        # until the library is loaded (_Calls)
+_NONE = (0, 0, 0, 0, None)                               # _size of an argument that is not given
+
+
+def _weights(w):
+    """(pointer, rows, columns, dtype code) of a contiguous matrix."""
+    p, ld, rows, cols, dt = _size(w)
+    return _ptr(w) if ld != cols else p, rows, cols, dt
 
 
 # the current stream's handle without a Stream object around it, where torch has these (they are not public)
@@ -165,26 +189,26 @@ def gas_version() -> int:
 
 def gas_pull(hist, idx, dst, base=0, n=None):
     """dst[i] = hist[idx[i]] (idx int32 tensor) or hist[base+i] (idx None)."""
-    n = (idx.numel() if idx is not None else dst.shape[0]) if n is None else n
-    hp, ldh = _mat(hist)
-    dp, ldd = _mat(dst)
-    if dst.dtype != hist.dtype or dst.shape[1] != hist.shape[1] or dst.shape[0] < n:
+    hp, ldh, rows, F, dt = _size(hist)
+    dp, ldd, room, Fd, dtd = _size(dst)
+    if n is None:
+        n = idx.numel() if idx is not None else room
+    if dtd != dt or Fd != F or room < n:
         raise ValueError("gas_pull: dst does not match")
     fn = _calls().gas_pull_host if isinstance(hist, HostTable) else _calls().gas_pull
-    _check(fn(hp, hist.shape[0], ldh, _ptr(idx, torch.int32), base, n,
-              hist.shape[1], _dt(hist), dp, ldd, _stream()))
+    _check(fn(hp, rows, ldh, _ptr(idx, torch.int32), base, n, F, dt, dp, ldd, _stream()))
 
 
 def gas_push(src, idx, hist, base=0, n=None):
     """hist[idx[i]] = src[i] (idx int32 tensor, distinct) or hist[base+i] = src[i] (idx None)."""
-    n = (idx.numel() if idx is not None else src.shape[0]) if n is None else n
-    hp, ldh = _mat(hist)
-    sp, lds = _mat(src)
-    if src.dtype != hist.dtype or src.shape[1] != hist.shape[1] or src.shape[0] < n:
+    hp, ldh, rows, F, dt = _size(hist)
+    sp, lds, there, Fs, dts = _size(src)
+    if n is None:
+        n = idx.numel() if idx is not None else there
+    if dts != dt or Fs != F or there < n:
         raise ValueError("gas_push: src does not match")
     fn = _calls().gas_push_host if isinstance(hist, HostTable) else _calls().gas_push
-    _check(fn(sp, lds, _ptr(idx, torch.int32), base, n, hist.shape[1],
-              _dt(hist), hp, hist.shape[0], ldh, _stream()))
+    _check(fn(sp, lds, _ptr(idx, torch.int32), base, n, F, dt, hp, rows, ldh, _stream()))
 
 
 def gas_gcn_norm(ptr, ind, n_id, deg, val):
@@ -254,16 +278,15 @@ def gas_plan_destroy(plan: Plan):
 
 
 def gas_spmm(plan, rowptr, col, val, x, z, diag=0.0, s_agg=1.0, r=None, s_res=0.0):
-    xp, ldx = _mat(x)
-    zp, ldz = _mat(z)
-    rp, ldr = (0, 0) if r is None else _mat(r)
-    if r is not None and r.dtype != x.dtype:
+    xp, ldx, _, F, dt = _size(x)
+    zp, ldz, rows, Fz, dtz = _size(z)
+    rp, ldr, _, _, dtr = _NONE if r is None else _size(r)
+    if r is not None and dtr != dt:
         raise TypeError("gas_spmm: R must have X's dtype")
-    if z.shape[1] != x.shape[1] or z.shape[0] < plan.n_rows:
+    if Fz != F or rows < plan.n_rows:
         raise ValueError("gas_spmm: Z does not match")
     _check(_calls().gas_spmm(plan.handle, _ptr(rowptr, torch.int32), _ptr(col, torch.int32), _ptr(val, torch.float32),
-                          diag, xp, ldx, _dt(x), x.shape[1], s_agg, rp, ldr,
-                          s_res, zp, ldz, _dt(z), _stream()))
+                             diag, xp, ldx, dt, F, s_agg, rp, ldr, s_res, zp, ldz, dtz, _stream()))
 
 
 def gas_fuse_sources(col, nb, n_id, src):
@@ -273,72 +296,65 @@ def gas_fuse_sources(col, nb, n_id, src):
 
 def gas_spmm_hist(plan, rowptr, src, val, x, hist, z, diag=0.0, s_agg=1.0, r=None, s_res=0.0):
     """x: the in-batch rows [n_rows, F]; hist: the history table the halo rows are read from."""
-    xp, ldx = _mat(x)
-    hp, ldh = _mat(hist)
-    zp, ldz = _mat(z)
-    rp, ldr = (0, 0) if r is None else _mat(r)
-    if hist.dtype != x.dtype or hist.shape[1] != x.shape[1] or (r is not None and r.dtype != x.dtype):
+    xp, ldx, there, F, dt = _size(x)
+    hp, ldh, n_hist, Fh, dth = _size(hist)
+    zp, ldz, rows, Fz, dtz = _size(z)
+    rp, ldr, _, _, dtr = _NONE if r is None else _size(r)
+    if dth != dt or Fh != F or (r is not None and dtr != dt):
         raise TypeError("gas_spmm_hist: hist and R must match X")
-    if z.shape[1] != x.shape[1] or z.shape[0] < plan.n_rows or x.shape[0] < plan.n_rows:
+    if Fz != F or rows < plan.n_rows or there < plan.n_rows:
         raise ValueError("gas_spmm_hist: shapes do not match")
     _check(_calls().gas_spmm_hist(plan.handle, _ptr(rowptr, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32),
-                               diag, xp, ldx, hp, hist.shape[0], ldh, _dt(x),
-                               x.shape[1], s_agg, rp, ldr, s_res, zp, ldz,
-                               _dt(z), _stream()))
+                                  diag, xp, ldx, hp, n_hist, ldh, dt, F, s_agg, rp, ldr, s_res, zp, ldz, dtz, _stream()))
 
 
 def gas_spmm_table(plan, rowptr, src, val, table, z, diag=0.0, s_agg=1.0, own=None):
     """Every row is one of the table's: an entry's -1 - src, the diagonal term's own[v]."""
-    tp, ldt = _mat(table)
-    zp, ldz = _mat(z)
-    if z.shape[1] != table.shape[1] or z.shape[0] < plan.n_rows or (own is not None and own.numel() < plan.n_rows):
+    tp, ldt, n_table, F, dt = _size(table)
+    zp, ldz, rows, Fz, dtz = _size(z)
+    if Fz != F or rows < plan.n_rows or (own is not None and own.numel() < plan.n_rows):
         raise ValueError("gas_spmm_table: shapes do not match")
     _check(_calls().gas_spmm_table(plan.handle, _ptr(rowptr, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32), diag,
-                                _ptr(own, torch.int32), tp, table.shape[0], ldt, _dt(table), table.shape[1], s_agg, zp, ldz,
-                                _dt(z), _stream()))
+                                   _ptr(own, torch.int32), tp, n_table, ldt, dt, F, s_agg, zp, ldz, dtz, _stream()))
 
 
 def gas_spmm_t(plan, colptr, row, val, g, gx, diag=0.0, s_agg=1.0):
-    gp, ldg = _mat(g)
-    op, ldo = _mat(gx)
-    if gx.shape[1] != g.shape[1] or gx.shape[0] < plan.n_rows:
+    gp, ldg, there, F, dt = _size(g)
+    op, ldo, rows, Fo, dto = _size(gx)
+    if Fo != F or rows < plan.n_rows:
         raise ValueError("gas_spmm_t: GX does not match")
     _check(_calls().gas_spmm_t(plan.handle, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32),
-                            diag, s_agg, g.shape[0], gp, ldg, _dt(g), g.shape[1],
-                            op, ldo, _dt(gx), _stream()))
+                               diag, s_agg, there, gp, ldg, dt, F, op, ldo, dto, _stream()))
 
 
 def gas_spmm_t_relu(plan, colptr, row, val, g, y, gx, diag=0.0, s_agg=1.0):
     """gas_spmm_t, then zero where the activations y [n_rows, F] are not positive."""
-    gp, ldg = _mat(g)
-    yp, ldy = _mat(y)
-    op, ldo = _mat(gx)
-    if gx.shape[1] != g.shape[1] or gx.shape[0] < plan.n_rows or y.shape[1] != g.shape[1] or y.shape[0] < plan.n_rows or \
-            not (g.dtype == y.dtype == gx.dtype):
+    gp, ldg, there, F, dt = _size(g)
+    yp, ldy, ny, Fy, dty = _size(y)
+    op, ldo, rows, Fo, dto = _size(gx)
+    if Fo != F or rows < plan.n_rows or Fy != F or ny < plan.n_rows or not (dt == dty == dto):
         raise ValueError("gas_spmm_t_relu: shapes or dtypes do not match")
     _check(_calls().gas_spmm_t_relu(plan.handle, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32),
-                                    diag, s_agg, g.shape[0], gp, ldg, _dt(g), g.shape[1], yp, ldy, op, ldo, _stream()))
+                                    diag, s_agg, there, gp, ldg, dt, F, yp, ldy, op, ldo, _stream()))
 
 
 def gas_linear(z, w, y, bias=None, c_identity=0.0, c_weight=1.0, relu=False):
-    zp, ldz = _mat(z)
-    yp, ldy = _mat(y)
-    if w.dtype != z.dtype or y.dtype != z.dtype or w.shape[0] != z.shape[1] or y.shape != (z.shape[0], w.shape[1]):
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    wp, w_in, w_out, dtw = _weights(w)
+    if dtw != dt or dty != dt or w_in != f_in or ny != n or f_out != w_out:
         raise ValueError("gas_linear: shapes or dtypes do not match")
-    _check(_calls().gas_linear(zp, ldz, z.shape[0], z.shape[1], _ptr(w), w.shape[1],
-                            _ptr(bias), _dt(z), c_identity, c_weight,
-                            int(relu), yp, ldy, _stream()))
+    _check(_calls().gas_linear(zp, ldz, n, f_in, wp, f_out, _ptr(bias), dt, c_identity, c_weight, int(relu), yp, ldy, _stream()))
 
 
 def gas_mlp2(z, w1, w2, y, b1=None, b2=None, relu_out=False):
-    zp, ldz = _mat(z)
-    yp, ldy = _mat(y)
-    if not (w1.dtype == w2.dtype == z.dtype == y.dtype) or w1.shape[0] != z.shape[1] or w2.shape[0] != w1.shape[1] \
-            or y.shape != (z.shape[0], w2.shape[1]):
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    p1, w1_in, hidden, dt1 = _weights(w1)
+    p2, w2_in, w2_out, dt2 = _weights(w2)
+    if not (dt1 == dt2 == dt == dty) or w1_in != f_in or w2_in != hidden or ny != n or f_out != w2_out:
         raise ValueError("gas_mlp2: shapes or dtypes do not match")
-    _check(_calls().gas_mlp2(zp, ldz, z.shape[0], z.shape[1], _ptr(w1), w1.shape[1],
-                          _ptr(b1), _ptr(w2), w2.shape[1], _ptr(b2), _dt(z),
-                          int(relu_out), yp, ldy, _stream()))
+    _check(_calls().gas_mlp2(zp, ldz, n, f_in, p1, hidden, _ptr(b1), p2, f_out, _ptr(b2), dt, int(relu_out), yp, ldy, _stream()))
 
 
 def gas_validate_indices(idx, limit) -> bool:
@@ -362,29 +378,28 @@ def gas_relu_bwd(gy, y, gp):
 
 def gas_linear_bwd_input(gp, w, gz, c_identity=0.0, c_weight=1.0, mask=None):
     """gz [n, F_in] = c_identity * gp + c_weight * gp @ w.T, zeroed where mask <= 0; w is [F_in, F_out]."""
-    a, lda = _mat(gp)
-    c, ldc = _mat(gz)
-    mp, ldm = (0, 0) if mask is None else _mat(mask)
-    if w.dtype != gp.dtype or gz.dtype != gp.dtype or w.shape[1] != gp.shape[1] or gz.shape != (gp.shape[0], w.shape[0]) \
-            or (mask is not None and (mask.shape != gz.shape or mask.dtype != gp.dtype)):
+    a, lda, n, f_out, dt = _size(gp)
+    c, ldc, nz, f_in, dtz = _size(gz)
+    wp, w_in, w_out, dtw = _weights(w)
+    mp, ldm, nm, fm, dtm = (0, 0, nz, f_in, dt) if mask is None else _size(mask)
+    if dtw != dt or dtz != dt or w_out != f_out or nz != n or f_in != w_in or nm != nz or fm != f_in or dtm != dt:
         raise ValueError("gas_linear_bwd_input: shapes or dtypes do not match")
-    _check(_calls().gas_linear_bwd_input(a, lda, gp.shape[0], gp.shape[1], _ptr(w),
-                                      w.shape[0], _dt(gp), c_identity,
-                                      c_weight, mp, ldm, c, ldc, _stream()))
+    _check(_calls().gas_linear_bwd_input(a, lda, n, f_out, wp, f_in, dt, c_identity, c_weight, mp, ldm, c, ldc, _stream()))
 
 
 def gas_linear_bwd_input_add(gp, w, gz, c_identity=0.0, c_weight=1.0, add=None, mask=None, total=None, c_total=0.0):
     """gas_linear_bwd_input with `add` added before the mask; total += c_total * gz where given."""
-    a, lda = _mat(gp)
-    c, ldc = _mat(gz)
-    ap, ldadd = (0, 0) if add is None else _mat(add)
-    mp, ldm = (0, 0) if mask is None else _mat(mask)
-    tp, ldt = (0, 0) if total is None else _mat(total)
-    if w.dtype != gp.dtype or gz.dtype != gp.dtype or w.shape[1] != gp.shape[1] or gz.shape != (gp.shape[0], w.shape[0]) \
-            or any(t is not None and (t.shape != gz.shape or t.dtype != gp.dtype) for t in (add, mask, total)):
+    a, lda, n, f_out, dt = _size(gp)
+    c, ldc, nz, f_in, dtz = _size(gz)
+    wp, w_in, w_out, dtw = _weights(w)
+    same = (nz, f_in, dt)
+    ap, ldadd, *like_a = (0, 0, *same) if add is None else _size(add)
+    mp, ldm, *like_m = (0, 0, *same) if mask is None else _size(mask)
+    tp, ldt, *like_t = (0, 0, *same) if total is None else _size(total)
+    if dtw != dt or dtz != dt or w_out != f_out or nz != n or f_in != w_in or not (tuple(like_a) == tuple(like_m) == tuple(like_t) == same):
         raise ValueError("gas_linear_bwd_input_add: shapes or dtypes do not match")
-    _check(_calls().gas_linear_bwd_input_add(a, lda, gp.shape[0], gp.shape[1], _ptr(w), w.shape[0], _dt(gp), c_identity,
-                                             c_weight, ap, ldadd, mp, ldm, c_total, tp, ldt, c, ldc, _stream()))
+    _check(_calls().gas_linear_bwd_input_add(a, lda, n, f_out, wp, f_in, dt, c_identity, c_weight, ap, ldadd, mp, ldm, c_total, tp,
+                                             ldt, c, ldc, _stream()))
 
 
 def gas_linear_bwd_weight_workspace(n_rows, f_in, f_out) -> int:
@@ -415,25 +430,24 @@ def gas_linear_bwd_weights(items):
     n = len(items)
     if n == 0:
         return
-    dt, dev = items[0][0].dtype, items[0][0].device
-    zs, gs = [_mat(z) for z, _, _, _ in items], [_mat(g) for _, g, _, _ in items]
-    for z, g, dw, _ in items:
-        if z.dtype != dt or g.dtype != dt or dw.dtype != torch.float32 or not dw.is_contiguous() or \
-                z.shape[0] != g.shape[0] or dw.shape != (z.shape[1], g.shape[1]):
+    dev = items[0][0].device
+    zs, gs = [_size(z) for z, _, _, _ in items], [_size(g) for _, g, _, _ in items]
+    dt, dws = zs[0][4], []
+    for (_, _, rows, f_in, dtz), (_, _, rows_g, f_out, dtg), (_, _, dw, _) in zip(zs, gs, items):
+        if dtz != dt or dtg != dt or dw.dtype != torch.float32 or not dw.is_contiguous() or rows != rows_g or dw.shape != (f_in, f_out):
             raise ValueError("gas_linear_bwd_weights: shapes or dtypes do not match")
+        dws.append(dw.data_ptr())
     pointers, longs, ints = C.c_void_p * n, C.c_int64 * n, C.c_int32 * n
-    rows = longs(*[z.shape[0] for z, _, _, _ in items])
-    f_in, f_out = ints(*[z.shape[1] for z, _, _, _ in items]), ints(*[g.shape[1] for _, g, _, _ in items])
-    need = _calls().gas_linear_bwd_weights_workspace(n, rows, f_in, f_out, _dt(items[0][0]))
+    rows, f_in, f_out = longs(*[t[2] for t in zs]), ints(*[t[3] for t in zs]), ints(*[t[3] for t in gs])
+    need = _calls().gas_linear_bwd_weights_workspace(n, rows, f_in, f_out, dt)
     if need > SHARED_WORKSPACE and n > 1:
         gas_linear_bwd_weights(items[:n // 2])
         gas_linear_bwd_weights(items[n // 2:])
         return
     ws = torch.empty(max(1, need), dtype=torch.uint8, device=dev)
     _check(_calls().gas_linear_bwd_weights(
-        n, pointers(*[p for p, _ in zs]), longs(*[ld for _, ld in zs]), pointers(*[p for p, _ in gs]),
-        longs(*[ld for _, ld in gs]), rows, f_in, f_out, _dt(items[0][0]), (C.c_float * n)(*[c for _, _, _, c in items]),
-        pointers(*[dw.data_ptr() for _, _, dw, _ in items]), ws.data_ptr(), need, _stream()))
+        n, pointers(*[t[0] for t in zs]), longs(*[t[1] for t in zs]), pointers(*[t[0] for t in gs]), longs(*[t[1] for t in gs]),
+        rows, f_in, f_out, dt, (C.c_float * n)(*[c for _, _, _, c in items]), pointers(*dws), ws.data_ptr(), need, _stream()))
 
 
 def gas_linear_bwd_weight_static(z, gp, dw, c_weight=1.0):
@@ -450,84 +464,75 @@ def gas_linear_bwd_weight_static(z, gp, dw, c_weight=1.0):
 
 def gas_linear_push(z, w, y, idx, hist, bias=None, c_identity=0.0, c_weight=1.0, relu=False):
     """gas_linear, and y[i] is also stored to hist[idx[i]] (Push fused into the epilogue)."""
-    zp, ldz = _mat(z)
-    yp, ldy = _mat(y)
-    hp, ldh = _mat(hist)
-    if w.dtype != z.dtype or y.dtype != z.dtype or hist.dtype != z.dtype or w.shape[0] != z.shape[1] or \
-            y.shape != (z.shape[0], w.shape[1]) or hist.shape[1] != w.shape[1] or idx.numel() != z.shape[0]:
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    hp, ldh, n_hist, fh, dth = _size(hist)
+    wp, w_in, w_out, dtw = _weights(w)
+    if dtw != dt or dty != dt or dth != dt or w_in != f_in or ny != n or f_out != w_out or fh != w_out or idx.numel() != n:
         raise ValueError("gas_linear_push: shapes or dtypes do not match")
-    _check(_calls().gas_linear_push(zp, ldz, z.shape[0], z.shape[1], _ptr(w), w.shape[1],
-                                 _ptr(bias), _dt(z), c_identity, c_weight,
-                                 int(relu), yp, ldy, _ptr(idx, torch.int32), hp, hist.shape[0], ldh,
-                                 _stream()))
+    _check(_calls().gas_linear_push(zp, ldz, n, f_in, wp, f_out, _ptr(bias), dt, c_identity, c_weight, int(relu), yp, ldy,
+                                    _ptr(idx, torch.int32), hp, n_hist, ldh, _stream()))
 
 
 def gas_mlp2_keep(z, w1, w2, y, h_out, idx=None, hist=None, b1=None, b2=None, relu_out=False):
     """gas_mlp2 that also stores the hidden activation relu(z w1 + b1) to h_out, and (idx, hist given) pushes y."""
-    zp, ldz = _mat(z)
-    yp, ldy = _mat(y)
-    hp, ldh = _mat(h_out)
-    tp, ldt = (0, 0) if hist is None else _mat(hist)
-    if not (w1.dtype == w2.dtype == z.dtype == y.dtype == h_out.dtype) or w1.shape[0] != z.shape[1] or \
-            w2.shape[0] != w1.shape[1] or y.shape != (z.shape[0], w2.shape[1]) or \
-            h_out.shape != (z.shape[0], w1.shape[1]) or (hist is None) != (idx is None) or \
-            (hist is not None and (hist.dtype != z.dtype or hist.shape[1] != w2.shape[1] or idx.numel() != z.shape[0])):
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    hp, ldh, nh, fh, dth = _size(h_out)
+    p1, w1_in, hidden, dt1 = _weights(w1)
+    p2, w2_in, w2_out, dt2 = _weights(w2)
+    tp, ldt, n_hist, ft, dtt = (0, 0, 0, w2_out, dt) if hist is None else _size(hist)
+    if not (dt1 == dt2 == dt == dty == dth == dtt) or w1_in != f_in or w2_in != hidden or ny != n or f_out != w2_out or nh != n or \
+            fh != hidden or (hist is None) != (idx is None) or ft != w2_out or (hist is not None and idx.numel() != n):
         raise ValueError("gas_mlp2_keep: shapes or dtypes do not match")
-    _check(_calls().gas_mlp2_keep(zp, ldz, z.shape[0], z.shape[1], _ptr(w1), w1.shape[1],
-                               _ptr(b1), _ptr(w2), w2.shape[1], _ptr(b2), _dt(z),
-                               int(relu_out), yp, ldy, hp, ldh, _ptr(idx, torch.int32), tp,
-                               0 if hist is None else hist.shape[0], ldt, _stream()))
+    _check(_calls().gas_mlp2_keep(zp, ldz, n, f_in, p1, hidden, _ptr(b1), p2, f_out, _ptr(b2), dt, int(relu_out), yp, ldy, hp, ldh,
+                                  _ptr(idx, torch.int32), tp, n_hist, ldt, _stream()))
 
 
 def spmm_linear_supported(x, f_out) -> bool:
     """Whether gas_spmm_linear takes this layer (fp32, widths multiples of 4 up to 128)."""
     f_in = x.shape[1]
-    return x.dtype == torch.float32 and f_in % 4 == 0 and f_out % 4 == 0 and max(f_in, f_out) <= 128
+    return f_out <= 128 and f_in <= 128 and f_in % 4 == 0 and f_out % 4 == 0 and x.dtype == torch.float32
 
 
 def gas_spmm_linear(rowptr, src, val, x, w, y, hist=None, diag=0.0, s_agg=1.0, r=None, s_res=0.0, bias=None,
                     c_identity=0.0, c_weight=1.0, relu=False, push_idx=None, push_hist=None, z_out=None):
     """One layer in one launch: aggregation of the rows of y (sources: rows of x, or rows of hist for negative
     indices), transform by w, optional store of every output row to push_hist[push_idx[i]]."""
-    n_rows = y.shape[0]
-    xp, ldx = _mat(x)
-    yp, ldy = _mat(y)
-    hp, ldh = (0, 0) if hist is None else _mat(hist)
-    rp, ldr = (0, 0) if r is None else _mat(r)
-    pp, ldp = (0, 0) if push_hist is None else _mat(push_hist)
-    zp, ldzo = (0, 0) if z_out is None else _mat(z_out)
-    if z_out is not None and (z_out.dtype != x.dtype or z_out.shape[1] != x.shape[1] or z_out.shape[0] < n_rows):
+    xp, ldx, _, f_in, dt = _size(x)
+    yp, ldy, n_rows, f_out, dty = _size(y)
+    wp, w_in, w_out, dtw = _weights(w)
+    hp, ldh, n_hist, fh, dth = (0, 0, 0, f_in, dt) if hist is None else _size(hist)
+    rp, ldr, nr, fr, dtr = (0, 0, n_rows, f_in, dt) if r is None else _size(r)
+    pp, ldp, n_push, fp, dtp = (0, 0, 0, w_out, dt) if push_hist is None else _size(push_hist)
+    zp, ldzo, nz, fz, dtz = (0, 0, n_rows, f_in, dt) if z_out is None else _size(z_out)
+    if dtz != dt or fz != f_in or nz < n_rows:
         raise ValueError("gas_spmm_linear: z_out does not match")
-    if w.dtype != x.dtype or y.dtype != x.dtype or w.shape[0] != x.shape[1] or y.shape[1] != w.shape[1] or \
-            rowptr.numel() != n_rows + 1 or (hist is not None and (hist.dtype != x.dtype or hist.shape[1] != x.shape[1])) or \
-            (r is not None and (r.dtype != x.dtype or r.shape[1] != x.shape[1] or r.shape[0] < n_rows)) or \
-            (push_hist is not None and (push_hist.dtype != x.dtype or push_hist.shape[1] != w.shape[1] or
-                                        push_idx is None or push_idx.numel() != n_rows)):
+    if dtw != dt or dty != dt or w_in != f_in or f_out != w_out or rowptr.numel() != n_rows + 1 or dth != dt or fh != f_in or \
+            dtr != dt or fr != f_in or nr < n_rows or dtp != dt or fp != w_out or \
+            (push_hist is not None and (push_idx is None or push_idx.numel() != n_rows)):
         raise ValueError("gas_spmm_linear: shapes or dtypes do not match")
     _check(_calls().gas_spmm_linear(
-        _ptr(rowptr, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32), n_rows, xp, ldx, hp,
-        0 if hist is None else hist.shape[0], ldh, _dt(x), x.shape[1], diag,
-        s_agg, rp, ldr, s_res, _ptr(w), w.shape[1], _ptr(bias), c_identity,
-        c_weight, int(relu), yp, ldy, zp, ldzo, _ptr(push_idx, torch.int32), pp,
-        0 if push_hist is None else push_hist.shape[0], ldp, _stream()))
+        _ptr(rowptr, torch.int32), _ptr(src, torch.int32), _ptr(val, torch.float32), n_rows, xp, ldx, hp, n_hist, ldh, dt, f_in, diag,
+        s_agg, rp, ldr, s_res, wp, f_out, _ptr(bias), c_identity, c_weight, int(relu), yp, ldy, zp, ldzo,
+        _ptr(push_idx, torch.int32), pp, n_push, ldp, _stream()))
 
 
 def gas_spmm_t_relu_linear(colptr, row, val, g, y, gx, w, gz, s_agg=1.0, c_identity=0.0, c_weight=1.0, total=None, c_total=0.0):
     """gx = (y > 0) * s_agg * (adjoint of the aggregation applied to g), gz = c_identity * gx + c_weight * gx @ w.T (w: the
     weights of the layer below) and total += c_total * gz in one launch."""
-    (n, f), f_below = gx.shape, w.shape[0]
-    a, lda = _mat(g)
-    yp, ldy = _mat(y)
-    xp, ldx = _mat(gx)
-    zp, ldz = _mat(gz)
-    tp, ldt = (0, 0) if total is None else _mat(total)
-    if g.shape[1] != f or y.shape[1] != f or y.shape[0] < n or w.shape[1] != f or gz.shape != (n, f_below) or \
-            colptr.numel() < n + 1 or not (g.dtype == gx.dtype == y.dtype == w.dtype == gz.dtype) or \
-            (total is not None and (total.dtype != g.dtype or total.shape[1] != f_below or total.shape[0] < n)):
+    a, lda, _, fg, dt = _size(g)
+    yp, ldy, ny, fy, dty = _size(y)
+    xp, ldx, n, f, dtx = _size(gx)
+    zp, ldz, nz, f_below, dtz = _size(gz)
+    wp, w_in, w_out, dtw = _weights(w)
+    tp, ldt, nt, ft, dtt = (0, 0, n, w_in, dt) if total is None else _size(total)
+    if fg != f or fy != f or ny < n or w_out != f or nz != n or f_below != w_in or colptr.numel() < n + 1 or \
+            not (dt == dtx == dty == dtw == dtz == dtt) or ft != f_below or nt < n:
         raise ValueError("gas_spmm_t_relu_linear: shapes or dtypes do not match")
     _check(_calls().gas_spmm_t_relu_linear(
-        _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32), n, a, lda, _dt(g), f, s_agg, yp, ldy, xp,
-        ldx, _ptr(w), f_below, c_identity, c_weight, c_total, tp, ldt, zp, ldz, _stream()))
+        _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(val, torch.float32), n, a, lda, dt, f, s_agg, yp, ldy, xp,
+        ldx, wp, f_below, c_identity, c_weight, c_total, tp, ldt, zp, ldz, _stream()))
 
 
 def _pointers(mats, n, shape, like, what, null=False):
@@ -605,29 +610,27 @@ def gas_spmm_t_relu_linear_layers(colptr, row, val, g, ys, gxs, ws, gzs, s_agg=1
 
 def gas_mlp2_push(z, w1, w2, y, idx, hist, b1=None, b2=None, relu_out=False):
     """gas_mlp2, and y[i] is also stored to hist[idx[i]]."""
-    zp, ldz = _mat(z)
-    yp, ldy = _mat(y)
-    hp, ldh = _mat(hist)
-    if not (w1.dtype == w2.dtype == z.dtype == y.dtype == hist.dtype) or w1.shape[0] != z.shape[1] or \
-            w2.shape[0] != w1.shape[1] or y.shape != (z.shape[0], w2.shape[1]) or hist.shape[1] != w2.shape[1] or \
-            idx.numel() != z.shape[0]:
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    hp, ldh, n_hist, fh, dth = _size(hist)
+    p1, w1_in, hidden, dt1 = _weights(w1)
+    p2, w2_in, w2_out, dt2 = _weights(w2)
+    if not (dt1 == dt2 == dt == dty == dth) or w1_in != f_in or w2_in != hidden or ny != n or f_out != w2_out or fh != w2_out or \
+            idx.numel() != n:
         raise ValueError("gas_mlp2_push: shapes or dtypes do not match")
-    _check(_calls().gas_mlp2_push(zp, ldz, z.shape[0], z.shape[1], _ptr(w1), w1.shape[1],
-                               _ptr(b1), _ptr(w2), w2.shape[1], _ptr(b2), _dt(z),
-                               int(relu_out), yp, ldy, _ptr(idx, torch.int32), hp, hist.shape[0],
-                               ldh, _stream()))
+    _check(_calls().gas_mlp2_push(zp, ldz, n, f_in, p1, hidden, _ptr(b1), p2, f_out, _ptr(b2), dt, int(relu_out), yp, ldy,
+                                  _ptr(idx, torch.int32), hp, n_hist, ldh, _stream()))
 
 
 def gas_softmax_xent(a, labels, grad, loss_rows, loss_sum=None, scale=1.0):
     """Softmax cross-entropy per row and its gradient (scaled); rows with a label outside [0, C) are skipped."""
-    ap, lda = _mat(a)
-    gp, ldg = _mat(grad)
-    if grad.dtype != a.dtype or grad.shape != a.shape or labels.numel() != a.shape[0] or \
-            loss_rows.dtype != torch.float32 or loss_rows.numel() != a.shape[0] or not loss_rows.is_contiguous():
+    ap, lda, n, classes, dt = _size(a)
+    gp, ldg, ng, fg, dtg = _size(grad)
+    if dtg != dt or ng != n or fg != classes or labels.numel() != n or \
+            loss_rows.dtype != torch.float32 or loss_rows.numel() != n or not loss_rows.is_contiguous():
         raise ValueError("gas_softmax_xent: shapes or dtypes do not match")
-    _check(_calls().gas_softmax_xent(ap, lda, a.shape[0], a.shape[1], _dt(a),
-                                  _ptr(labels, torch.int32), scale, _ptr(loss_rows, torch.float32),
-                                  _ptr(loss_sum, torch.float32), gp, ldg, _stream()))
+    _check(_calls().gas_softmax_xent(ap, lda, n, classes, dt, _ptr(labels, torch.int32), scale, _ptr(loss_rows, torch.float32),
+                                     _ptr(loss_sum, torch.float32), gp, ldg, _stream()))
 
 
 def gas_sgd_step(w, dw, lr, weight_decay=0.0):
@@ -643,14 +646,17 @@ def gas_sgd_steps(pairs, lr, weight_decay=0.0):
     n = len(pairs)
     if n == 0:
         return
-    dt = pairs[0][0].dtype
+    dt, ws, dws, sizes = pairs[0][0].dtype, [], [], []
     for w, dw in pairs:
-        if not w.is_contiguous() or not dw.is_contiguous() or dw.dtype != torch.float32 or dw.numel() != w.numel() or \
-                w.dtype != dt:
+        size = w.numel()
+        if not w.is_contiguous() or not dw.is_contiguous() or dw.dtype != torch.float32 or dw.numel() != size or w.dtype != dt:
             raise ValueError("gas_sgd_steps: w and dw must be contiguous and of equal size, dw float32, w of one dtype")
-    _check(_calls().gas_sgd_steps(n, (C.c_void_p * n)(*[w.data_ptr() for w, _ in pairs]),
-                                  (C.c_int64 * n)(*[w.numel() for w, _ in pairs]), _dt(pairs[0][0]),
-                                  (C.c_void_p * n)(*[dw.data_ptr() for _, dw in pairs]), lr, weight_decay, _stream()))
+        ws.append(w.data_ptr())
+        dws.append(dw.data_ptr())
+        sizes.append(size)
+    pointers = C.c_void_p * n
+    _check(_calls().gas_sgd_steps(n, pointers(*ws), (C.c_int64 * n)(*sizes), _dt(pairs[0][0]), pointers(*dws), lr, weight_decay,
+                                  _stream()))
 
 
 def gas_sq_norm(x, out):
@@ -674,15 +680,14 @@ def gas_sgd_step_clipped(w, dw, lr, sq_norms, max_norm, weight_decay=0.0):
 def gas_pna_aggregate(rowptr, col, x, out, delta, add=None, blocks=9):
     """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add); blocks = 3: out
     [n_rows, 3F], the aggregators alone."""
-    xp, ldx = _mat(x)
-    op, ldo = _mat(out)
-    ap, lda = (0, 0) if add is None else _mat(add)
     n_rows = rowptr.numel() - 1
-    if out.dtype != x.dtype or out.shape[0] < n_rows or out.shape[1] != blocks * x.shape[1] or \
-            (add is not None and (add.dtype != x.dtype or add.shape[1] != x.shape[1] or add.shape[0] < n_rows)):
+    xp, ldx, _, F, dt = _size(x)
+    op, ldo, no, Fo, dto = _size(out)
+    ap, lda, na, Fa, dta = (0, 0, n_rows, F, dt) if add is None else _size(add)
+    if dto != dt or no < n_rows or Fo != blocks * F or dta != dt or Fa != F or na < n_rows:
         raise ValueError("gas_pna_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_pna_aggregate_blocks(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, xp, ldx,
-                                          _dt(x), x.shape[1], ap, lda, delta, blocks, op, ldo, _stream()))
+    _check(_calls().gas_pna_aggregate_blocks(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, xp, ldx, dt, F, ap, lda, delta,
+                                             blocks, op, ldo, _stream()))
 
 
 PNA_MAX_DEGREE = 63
@@ -742,13 +747,13 @@ def gas_pna_linear_bwd_weight(groups, max_degree, x, g, f1, delta, dw):
 def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False, heads=1):
     """z[v] = sum_k softmax_k(LeakyReLU(a_dst.p[v] + a_src.p[col k])) p[col k] over the entries of row v.  heads > 1: the
     columns of p and z and the elements of a_dst and a_src are that many equal blocks, a head each."""
-    pp, ldp = _mat(p)
-    zp, ldz = _mat(z)
-    n_rows, width = rowptr.numel() - 1, p.shape[1]
-    if z.dtype != p.dtype or a_dst.dtype != p.dtype or a_src.dtype != p.dtype or z.shape[1] != width or \
-            z.shape[0] < n_rows or a_dst.numel() != width or a_src.numel() != width or heads < 1 or width % heads:
+    pp, ldp, _, width, dt = _size(p)
+    zp, ldz, nz, fz, dtz = _size(z)
+    n_rows = rowptr.numel() - 1
+    if dtz != dt or a_dst.dtype != p.dtype or a_src.dtype != p.dtype or fz != width or \
+            nz < n_rows or a_dst.numel() != width or a_src.numel() != width or heads < 1 or width % heads:
         raise ValueError("gas_gat_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_gat_aggregate_heads(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, pp, ldp, _dt(p),
+    _check(_calls().gas_gat_aggregate_heads(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, pp, ldp, dt,
                                             width // heads, heads, _ptr(a_dst), _ptr(a_src), negative_slope, int(relu), zp,
                                             ldz, _stream()))
 
@@ -766,12 +771,11 @@ def gas_axpy(x, e, y, alpha=1.0):
 
 def gas_row_dot(a, b, dot, dot_sum=None):
     """dot[i] = <a[i], b[i]> (float32 [n]); dot_sum (float32 [1]) receives their sum in a fixed order."""
-    ap, lda = _mat(a)
-    bp, ldb = _mat(b)
-    if a.shape != b.shape or a.dtype != b.dtype or dot.dtype != torch.float32 or dot.numel() < a.shape[0]:
+    ap, lda, n, F, dt = _size(a)
+    bp, ldb, nb, Fb, dtb = _size(b)
+    if nb != n or Fb != F or dtb != dt or dot.dtype != torch.float32 or dot.numel() < n:
         raise ValueError("gas_row_dot: shapes or dtypes do not match")
-    _check(_calls().gas_row_dot(ap, lda, bp, ldb, a.shape[0], a.shape[1], _dt(a),
-                             _ptr(dot), _ptr(dot_sum), _stream()))
+    _check(_calls().gas_row_dot(ap, lda, bp, ldb, n, F, dt, _ptr(dot), _ptr(dot_sum), _stream()))
 
 
 def gas_row_distance(a, b, dist, dist_sum=None):
