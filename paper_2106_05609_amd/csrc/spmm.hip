@@ -511,7 +511,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // registers: a wavefront less on a SIMD).
 constexpr int kSliceRows = 16;      // rows of a workgroup (four wavefronts of four teams)
 
-template <int P, bool XBF, bool ZBF, bool MASK>
+template <int P, bool EVEN, bool XBF, bool ZBF, bool MASK>
 __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices, int width) {
     constexpr int G = 16, E = Unit<XBF>::E, EB = XBF ? 2 : 4, U = P == 1 ? 8 : 4;
     typedef std::conditional_t<XBF, u32x4_at2, u32x4_at4> Piece;
@@ -532,14 +532,15 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
     if (row >= a.n_rows) return;
     const int b = a.ptr[row], e = a.ptr[row + 1];
     if (e - b > a.threshold) return;                                      // heavy row: done by the chunk kernel
-    // the lane's units of the slice: j, j + G, ...; a lane past the slice's width loads nothing
+    // the lane's units of the slice: j, j + G, ...; a lane past the slice's width loads nothing there if it is the last piece of
+    // several, and else the row's last unit or one of the next slice, which it does not store: one condition less for every load
     uint32_t off[P];
-    bool mine[P];          // (P == 1 loads the slice's last unit there: one condition less for every load)
+    bool mine[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
         const int w = j + G * p, unit = slice * width + w;
-        mine[p] = w < width && unit < a.units;
-        off[p] = unit_start<XBF>(a, min(unit, a.units - 1)) * EB;
+        mine[p] = EVEN || (w < width && unit < a.units);
+        off[p] = EVEN ? unit * 16 : unit_start<XBF>(a, min(unit, a.units - 1)) * EB;
     }
     // entries k + j and k + G + j (past the row's end its last one: a valid address, never folded)
     int s[2];
@@ -591,7 +592,7 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
                     if (G * h + q + u < cnt) {
 #pragma unroll
                         for (int p = 0; p < P; ++p)
-                            if (P == 1 || mine[p]) x[u][p] = load_global<Piece>(__builtin_bit_cast(uint64_t, r) + off[p]);
+                            if (P == 1 || p + 1 < P || mine[p]) x[u][p] = load_global<Piece>(__builtin_bit_cast(uint64_t, r) + off[p]);
                     }
                 }
 #pragma unroll
@@ -781,8 +782,13 @@ gas_status launch_slices(const SpmmArgs& a, hipStream_t s) {
     const int64_t jobs = (a.n_rows + kSliceRows - 1) / kSliceRows * slices;
     const int64_t blocks = a.in_turn ? jobs : 8 * ((jobs + 7) / 8);
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
-    if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, true>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices, width);
-    else hipLaunchKernelGGL((spmm_slices_kernel<P, XBF, ZBF, false>), dim3((unsigned)blocks), dim3(256), 0, s, a, slices, width);
+    const dim3 grid((unsigned)blocks), block(256);
+    // whole slices need no masks: two pieces a lane 40 -> 39 us (adjoint 38 -> 37); one piece a lane has none, and three gain nothing
+    if (P == 2 && a.units == slices * 16 * P && a.units * 16 == a.F * (XBF ? 2 : 4)) {
+        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<2, true, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+        else hipLaunchKernelGGL((spmm_slices_kernel<2, true, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+    } else if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, false, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+    else hipLaunchKernelGGL((spmm_slices_kernel<P, false, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
     return GAS_OK;
 }
 
