@@ -788,6 +788,148 @@ __device__ __forceinline__ void mfma_tile_bf16(const uint16_t* A, int lda, int a
     }
 }
 
+// y = act(c_w acc + bias + c_id Z), masked, of a wavefront's blocks, two bytes a lane
+template <int TM, int TN>
+__device__ __forceinline__ void store_tile_bf16(const LinArgs& a, int64_t m0, int n0, int li, int lh, const f32x16 (&acc)[TM][TN]) {
+    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
+    uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
+    const uint16_t* bias = reinterpret_cast<const uint16_t*>(a.bias);
+    const uint16_t* mask = reinterpret_cast<const uint16_t*>(a.mask);
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + 32 * j + li;
+            if (n >= a.N) continue;
+            const float bv = bias ? bf16_val(bias, n) : 0.f;
+            float id[16], keep[16];          // asked for together
+            const int64_t mj = m0 + 32 * i + 4 * lh;
+            if (a.c_id != 0.f)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) id[r] = bf16_val(Z, min(mj + 8 * (r / 4) + r % 4, a.M - 1) * a.ldz + n);
+            if (mask)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) keep[r] = bf16_val(mask, min(mj + 8 * (r / 4) + r % 4, a.M - 1) * a.ldmask + n);
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int64_t m = mj + 8 * (r / 4) + r % 4;
+                if (m >= a.M) continue;
+                float y = a.c_w * acc[i][j][r] + bv;
+                if (a.c_id != 0.f) y += a.c_id * id[r];
+                if (a.relu) y = fmaxf(y, 0.f);
+                if (mask && !(keep[r] > 0.f)) y = 0.f;
+                Y[m * a.ldy + n] = (uint16_t)f32_to_bf16(y);
+            }
+        }
+}
+
+// One ROWS x kBKh tile of a bf16 operand whose rows need no alignment beyond their elements', into LDS as [row][q], q the reduced
+// index; KC: element (r, q) lies at X[r ld + q], else at X[q ld + r].  Loads are of single elements, a wavefront's side by side
+// from an address that it shares (an address a lane takes 100 registers more).  Turned, a lane keeps eight q of its row and writes
+// them as 16 bytes.  Rows beyond the last repeat it (nothing stores their products), q beyond the end come out zero.
+template <int ROWS, bool KC, int WAVES = 4>
+struct AnyTileBF16 {
+    static constexpr int NV = ROWS * kBKh / 2 / (64 * WAVES);
+    uint16_t lo[NV], hi[NV];      // packed on the way into LDS: before, each pair would be waited for before the next is asked for
+    typedef const __attribute__((address_space(1))) char* Row;
+    // the next row's address, if there is one: in scalar registers, and not before the row at hand is asked for
+    static __device__ __forceinline__ void step(Row& x, int64_t ld, bool more) {
+        x += more ? 2 * ld : 0;
+        asm volatile("" : "+s"(x) : : "memory");
+    }
+    static __device__ __forceinline__ uint16_t at(Row x, uint32_t byte) {
+        return *reinterpret_cast<const __attribute__((address_space(1))) uint16_t*>(x + byte);
+    }
+    __device__ __forceinline__ void fetch(const uint16_t* X, int64_t ld, int64_t r0, int64_t r_end, int64_t q0, int64_t q_end, int tid) {
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        const int last = (int)min(r_end - 1 - r0, (int64_t)ROWS), q_last = (int)min(q_end - 1 - q0, (int64_t)kBKh);
+        if constexpr (KC) {
+            const uint32_t q = 2u * (uint32_t)min(lane, q_last);
+            const int row = wave * (ROWS / WAVES);
+            Row x = (Row)(X + (r0 + min(row, last)) * ld + q0);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                lo[i] = at(x, q);
+                step(x, ld, row + 2 * i < last);
+                hi[i] = at(x, q);
+                step(x, ld, row + 2 * i + 1 < last);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < NV / 4; ++u) {
+                const int unit = wave * (NV / 4) + u, q = unit / (ROWS / 64) * 8;
+                const uint32_t row = 2u * (uint32_t)min(unit % (ROWS / 64) * 64 + lane, last);
+                Row x = (Row)(X + (q0 + min(q, q_last)) * ld + r0);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    lo[4 * u + c] = at(x, row);
+                    step(x, ld, q + 2 * c < q_last);
+                    hi[4 * u + c] = at(x, row);
+                    step(x, ld, q + 2 * c + 1 < q_last);
+                }
+            }
+        }
+    }
+    // left: q of the step inside
+    __device__ __forceinline__ void stage(uint16_t (*to)[kLdh], int64_t left, int tid) {
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+        if constexpr (KC) {
+            const bool in = lane < left;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                to[wave * (ROWS / WAVES) + 2 * i][lane] = in ? lo[i] : (uint16_t)0;
+                to[wave * (ROWS / WAVES) + 2 * i + 1][lane] = in ? hi[i] : (uint16_t)0;
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < NV / 4; ++u) {
+                const int unit = wave * (NV / 4) + u, q = unit / (ROWS / 64) * 8;
+                u32x4 v;
+#pragma unroll
+                for (int c = 0; c < 4; ++c) v[c] = ((uint32_t)lo[4 * u + c] | (uint32_t)hi[4 * u + c] << 16) & (q + 2 * c + 1 < left ? 0xFFFFFFFFu : (q + 2 * c < left ? 0xFFFFu : 0u));
+                *reinterpret_cast<u32x4*>(&to[unit % (ROWS / 64) * 64 + lane][q]) = v;
+            }
+        }
+    }
+};
+
+// Y tile of BM x BN by operands of any alignment and width (odd feature and class counts).  Bound by its loads, of two bytes a lane:
+// 16 of every row and column of a step's 64 k a wavefront, so 64 and 32 matrix instructions at 128 x 128.  A thread an output
+// before: 50,000 x 256 x 47 312 us and now 14, its input gradient 609 and 18, 256 x 250 1,059 and 31, 11,287 and 30; 500 x 256 x 47 32 and 7.
+template <int BM, int BN, bool TRANS>
+__global__ __launch_bounds__(256, 2) void linear_bf16_any_kernel(LinArgs a) {
+    constexpr int TM = BM / 64, TN = BN / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t As[BM][kLdh];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[BN][kLdh];
+    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
+    const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    const unsigned tn = (unsigned)((a.N + BN - 1) / BN), of_xcd = blockIdx.x / 8;   // a row tile's column tiles follow each other on one XCD
+    const int64_t m0 = ((int64_t)(of_xcd / tn) * 8 + blockIdx.x % 8) * BM;
+    const int n0 = (int)(of_xcd % tn) * BN;
+    if (m0 >= a.M) return;
+    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    f32x16 acc[TM][TN];
+    zero_acc(acc);
+    AnyTileBF16<BM, true> ta;
+    AnyTileBF16<BN, TRANS> tb;
+    const int64_t ldw = TRANS ? a.K : a.N;
+    ta.fetch(Z, a.ldz, m0, a.M, 0, a.K, tid);
+    tb.fetch(W, ldw, n0, a.N, 0, a.K, tid);
+    for (int k0 = 0; k0 < a.K; k0 += kBKh) {
+        __syncthreads();
+        ta.stage(As, a.K - k0, tid);
+        tb.stage(Bs, a.K - k0, tid);
+        __syncthreads();
+        if (k0 + kBKh < a.K) {
+            ta.fetch(Z, a.ldz, m0, a.M, k0 + kBKh, a.K, tid);
+            tb.fetch(W, ldw, n0, a.N, k0 + kBKh, a.K, tid);
+        }
+        mfma_tile_bf16<TM, TN>(&As[0][0], kLdh, wm0, 0, Bs, wn0, li, lh, acc);
+    }
+    store_tile_bf16<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
+}
+
 template <int BN>
 __global__ __launch_bounds__(256) void linear_bf16_kernel(LinArgs a) {
     constexpr int BM = 128, TM = 2, TN = BN / 64;
@@ -817,34 +959,17 @@ __global__ __launch_bounds__(256) void linear_bf16_kernel(LinArgs a) {
         }
         mfma_tile_bf16<TM, TN>(&As[0][0], kLdh, wm0, 0, Bs, wn0, li, lh, acc);
     }
-    uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
-    const uint16_t* bias = reinterpret_cast<const uint16_t*>(a.bias);
-    const uint16_t* mask = reinterpret_cast<const uint16_t*>(a.mask);
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j) {
-            const int n = n0 + wn0 + 32 * j + li;
-            if (n >= a.N) continue;
-            const float bv = bias ? bf16_val(bias, n) : 0.f;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int64_t m = m0 + wm0 + 32 * i + 8 * (r / 4) + 4 * lh + (r % 4);
-                if (m >= a.M) continue;
-                float y = a.c_w * acc[i][j][r] + bv;
-                if (a.c_id != 0.f) y += a.c_id * bf16_val(Z, m * a.ldz + n);
-                if (a.relu) y = fmaxf(y, 0.f);
-                if (mask && !(bf16_val(mask, m * a.ldmask + n) > 0.f)) y = 0.f;
-                Y[m * a.ldy + n] = (uint16_t)f32_to_bf16(y);
-            }
-        }
+    store_tile_bf16<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
 // bf16 fused MLP: 64 rows per workgroup, wavefronts 2 x 2 over (rows, columns).
 // Phase 1: hidden = relu(Z W1 + b1) for all F_hid columns, rounded to bf16 into
 // LDS.  Phase 2: Y = act(hidden W2 + b2), the hidden tile being the A operand.
-__global__ __launch_bounds__(256) void mlp2_bf16_kernel(MlpArgs a) {
-    constexpr int BM = kMlpRowsBF16, BN = 256, TN = 4;
+// ANY: operands of any alignment and width (AnyTileBF16), by eight wavefronts, whose loads bound it.  A workgroup a row before:
+// 50,000 x 81 -> 184 -> 184 429 us and now 44, 500 rows 16.6 and 14.7 (by four wavefronts 19.8).
+template <bool ANY>
+__global__ __launch_bounds__(ANY ? 512 : 256) void mlp2_bf16_kernel(MlpArgs a) {
+    constexpr int BM = kMlpRowsBF16, BN = 256, TN = ANY ? 2 : 4;
     constexpr int kLdHid = kHidMax + 8;
     extern __shared__ __attribute__((aligned(16))) char smem[];   // above the 64 KB static limit
     uint16_t (*Hs)[kLdHid] = reinterpret_cast<uint16_t (*)[kLdHid]>(smem);
@@ -856,21 +981,34 @@ __global__ __launch_bounds__(256) void mlp2_bf16_kernel(MlpArgs a) {
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
     const int64_t m0 = (int64_t)blockIdx.x * BM;
     const int n0 = blockIdx.y * BN;
-    const int wm0 = (wave >> 1) * 32, wn0 = (wave & 1) * (BN / 2);
+    const int wm0 = (wave / (8 / TN)) * 32, wn0 = wave % (8 / TN) * (32 * TN);
     f32x16 acc[1][TN];
     zero_acc(acc);
-    ATileBF16<BM> ta;
-    BTileBF16<BN> tb;
-    ta.fetch(Z, a.ldz, a.M, a.K, m0, 0, tid);
-    tb.fetch(W1, a.K, a.H, 0, 0, tid);
+    std::conditional_t<ANY, AnyTileBF16<BM, true, 8>, ATileBF16<BM>> ta;
+    std::conditional_t<ANY, AnyTileBF16<BN, false, 8>, BTileBF16<BN>> tb;
+    auto rows = [&](int k0) {
+        if constexpr (ANY) ta.fetch(Z, a.ldz, m0, a.M, k0, a.K, tid);
+        else ta.fetch(Z, a.ldz, a.M, a.K, m0, k0, tid);
+    };
+    auto weights = [&](const uint16_t* W, int K, int N, int k0, int c0) {
+        if constexpr (ANY) tb.fetch(W, N, c0, N, k0, K, tid);
+        else tb.fetch(W, K, N, k0, c0, tid);
+    };
+    auto stage_weights = [&](int left) {
+        if constexpr (ANY) tb.stage(Bs, left, tid);
+        else tb.stage(Bs, tid);
+    };
+    rows(0);
+    weights(W1, a.K, a.H, 0, 0);
     for (int k0 = 0; k0 < a.K; k0 += kBKh) {
         __syncthreads();
-        ta.stage(As, tid);
-        tb.stage(Bs, tid);
+        if constexpr (ANY) ta.stage(As, a.K - k0, tid);
+        else ta.stage(As, tid);
+        stage_weights(a.K - k0);
         __syncthreads();
         if (k0 + kBKh < a.K) {
-            ta.fetch(Z, a.ldz, a.M, a.K, m0, k0 + kBKh, tid);
-            tb.fetch(W1, a.K, a.H, k0 + kBKh, 0, tid);
+            rows(k0 + kBKh);
+            weights(W1, a.K, a.H, k0 + kBKh, 0);
         }
         mfma_tile_bf16<1, TN>(&As[0][0], kLdh, wm0, 0, Bs, wn0, li, lh, acc);
     }
@@ -886,12 +1024,12 @@ __global__ __launch_bounds__(256) void mlp2_bf16_kernel(MlpArgs a) {
         }
     }
     zero_acc(acc);
-    tb.fetch(W2, a.H, a.N, 0, n0, tid);
+    weights(W2, a.H, a.N, 0, n0);
     for (int k0 = 0; k0 < a.H; k0 += kBKh) {
         __syncthreads();                 // Hs written / previous Bs consumed
-        tb.stage(Bs, tid);
+        stage_weights(a.H - k0);
         __syncthreads();
-        if (k0 + kBKh < a.H) tb.fetch(W2, a.H, a.N, k0 + kBKh, n0, tid);
+        if (k0 + kBKh < a.H) weights(W2, a.H, a.N, k0 + kBKh, n0);
         mfma_tile_bf16<1, TN>(&Hs[0][0], kLdHid, wm0, k0, Bs, wn0, li, lh, acc);
     }
     uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
@@ -1424,56 +1562,6 @@ gas_status launch_ws_kernel(const WsArgs& a, hipStream_t s) {
 template <int KT1>
 gas_status launch_ws(const WsArgs& a, hipStream_t s) { return a.mask ? launch_ws_kernel<KT1, true>(a, s) : launch_ws_kernel<KT1, false>(a, s); }
 
-// ====================================================================== element-wise paths
-// For bf16 operands that are not 16-byte aligned (odd widths, odd strides):
-// one thread per output element, fp32 accumulation.
-__global__ __launch_bounds__(256) void linear_bf16_generic_kernel(LinArgs a) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= a.M * a.N) return;
-    const int64_t m = idx / a.N;
-    const int n = (int)(idx % a.N);
-    const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
-    const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
-    float s = 0.f;
-    for (int k = 0; k < a.K; ++k)
-        s = fmaf(bf16_val(Z, m * a.ldz + k), bf16_val(W, a.trans_w ? (int64_t)n * a.K + k : (int64_t)k * a.N + n), s);
-    float y = a.c_w * s;
-    if (a.bias) y += bf16_val(reinterpret_cast<const uint16_t*>(a.bias), n);
-    if (a.c_id != 0.f) y += a.c_id * bf16_val(Z, m * a.ldz + n);
-    if (a.relu) y = fmaxf(y, 0.f);
-    if (a.mask && !(bf16_val(reinterpret_cast<const uint16_t*>(a.mask), m * a.ldmask + n) > 0.f)) y = 0.f;
-    reinterpret_cast<uint16_t*>(a.Y)[m * a.ldy + n] = (uint16_t)f32_to_bf16(y);
-}
-
-// One workgroup per row; the hidden row goes through LDS (bf16-rounded for
-// bf16 data, as in the MFMA kernel).
-template <bool BF>
-__global__ __launch_bounds__(256) void mlp2_generic_kernel(MlpArgs a) {
-    __shared__ float h[kHidMax];
-    const int64_t m = blockIdx.x;
-    auto ld = [](const char* p, int64_t i) -> float {
-        if constexpr (BF) return bf16_val(reinterpret_cast<const uint16_t*>(p), i);
-        else return reinterpret_cast<const float*>(p)[i];
-    };
-    for (int j = threadIdx.x; j < a.H; j += 256) {
-        float s = 0.f;
-        for (int k = 0; k < a.K; ++k) s = fmaf(ld(a.Z, m * a.ldz + k), ld(a.W1, (int64_t)k * a.H + j), s);
-        if (a.b1) s += ld(a.b1, j);
-        s = fmaxf(s, 0.f);
-        if constexpr (BF) s = __uint_as_float(f32_to_bf16(s) << 16);
-        h[j] = s;
-    }
-    __syncthreads();
-    for (int n = threadIdx.x; n < a.N; n += 256) {
-        float s = 0.f;
-        for (int k = 0; k < a.H; ++k) s = fmaf(h[k], ld(a.W2, (int64_t)k * a.N + n), s);
-        if (a.b2) s += ld(a.b2, n);
-        if (a.relu_out) s = fmaxf(s, 0.f);
-        if constexpr (BF) reinterpret_cast<uint16_t*>(a.Y)[m * a.ldy + n] = (uint16_t)f32_to_bf16(s);
-        else reinterpret_cast<float*>(a.Y)[m * a.ldy + n] = s;
-    }
-}
-
 // ====================================================================== backward kernels
 // Weight gradient dW[k, j] = c_w * sum_m Z[m, k] * G[m, j]: the reduction runs over the rows.  The rows are cut
 // into slabs; a workgroup forms the 128 x 128 tile (tk, tj) of the partial product of one slab in fp32 and
@@ -1700,20 +1788,60 @@ __global__ __launch_bounds__(512) void dw_bf16_kernel(DwArgs a) {
         }
 }
 
-// element-wise path for bf16 operands that are not 16-byte aligned: one thread per (slab, k, j)
-__global__ __launch_bounds__(256) void dw_bf16_generic_kernel(DwArgs a) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    const int64_t per = (int64_t)a.K * a.N;
-    if (idx >= per * a.n_slabs) return;
-    const int slab = (int)(idx / per);
-    const int k = (int)((idx % per) / a.N), n = (int)(idx % a.N);
+// Operands of any alignment and width: tiles of BK x BN, steps of 64 rows, both turned on their way into LDS (AnyTileBF16).  A
+// thread an element of a slab's partial before: 50,000 x 256 x 47 358 us and now 19, 250 columns 1,746 and 39, 500 x 256 x 47 17.8 and 8.4.
+template <int BK, int BN>
+__global__ __launch_bounds__(256, 2) void dw_bf16_any_kernel(DwArgs a) {
+    constexpr int TK = BK / 64, TN = BN / 64;
+    __shared__ __attribute__((aligned(16))) uint16_t As[BK][kLdh];
+    __shared__ __attribute__((aligned(16))) uint16_t Bs[BN][kLdh];
     const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
     const uint16_t* G = reinterpret_cast<const uint16_t*>(a.G);
-    const int64_t m_begin = (int64_t)slab * a.slab;
-    const int64_t m_end = m_begin + a.slab < a.M ? m_begin + a.slab : a.M;
-    float s = 0.f;
-    for (int64_t m = m_begin; m < m_end; ++m) s = fmaf(bf16_val(Z, m * a.ldz + k), bf16_val(G, m * a.ldg + n), s);
-    a.partial[idx] = s;
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
+    const unsigned tn = (a.N + BN - 1) / BN, tiles = (a.K + BK - 1) / BK * tn, of_xcd = blockIdx.x / 8, tile = of_xcd % tiles;
+    const int slab = (int)(of_xcd / tiles * 8 + blockIdx.x % 8);      // the tiles of a slab follow each other on one XCD
+    if (slab >= a.n_slabs) return;
+    const int k0 = (int)(tile / tn) * BK, n0 = (int)(tile % tn) * BN;
+    const int wk0 = (wave >> 1) * (BK / 2), wn0 = (wave & 1) * (BN / 2);
+    const int64_t m_begin = (int64_t)slab * a.slab, m_end = min(a.M, m_begin + a.slab);
+    f32x16 acc[TK][TN];
+    zero_acc(acc);
+    AnyTileBF16<BK, false> ta;
+    AnyTileBF16<BN, false> tb;
+    ta.fetch(Z, a.ldz, k0, a.K, m_begin, m_end, tid);
+    tb.fetch(G, a.ldg, n0, a.N, m_begin, m_end, tid);
+    for (int64_t m = m_begin; m < m_end; m += kBKh) {
+        __syncthreads();
+        ta.stage(As, m_end - m, tid);
+        tb.stage(Bs, m_end - m, tid);
+        __syncthreads();
+        if (m + kBKh < m_end) {
+            ta.fetch(Z, a.ldz, k0, a.K, m + kBKh, m_end, tid);
+            tb.fetch(G, a.ldg, n0, a.N, m + kBKh, m_end, tid);
+        }
+        mfma_tile_bf16<TK, TN>(&As[0][0], kLdh, wk0, 0, Bs, wn0, li, lh, acc);
+    }
+    float* out = a.partial + (int64_t)slab * a.K * a.N;
+#pragma unroll
+    for (int i = 0; i < TK; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) {
+            const int n = n0 + wn0 + 32 * j + li;
+            if (n >= a.N) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int k = k0 + wk0 + 32 * i + 8 * (r / 4) + 4 * lh + (r % 4);
+                if (k < a.K) out[(int64_t)k * a.N + n] = acc[i][j][r];
+            }
+        }
+}
+template <int BK, int BN>
+gas_status launch_dw_any(const DwArgs& a, hipStream_t s) {
+    const int64_t tiles = (int64_t)((a.K + BK - 1) / BK) * ((a.N + BN - 1) / BN), blocks = ((int64_t)a.n_slabs + 7) / 8 * 8 * tiles;
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_linear_bwd_weight: too many workgroups for one launch");
+    hipLaunchKernelGGL((dw_bf16_any_kernel<BK, BN>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
 }
 
 // dW = c_w * (sum of the slabs' partial tiles).  A workgroup owns 32 consecutive outputs; eight threads per output
@@ -1909,6 +2037,16 @@ gas_status launch_bf16(const LinArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
+template <int BM, int BN>
+gas_status launch_bf16_any(const LinArgs& a, hipStream_t s) {
+    const int64_t blocks = ((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN);
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
+    if (a.trans_w) hipLaunchKernelGGL((linear_bf16_any_kernel<BM, BN, true>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    else hipLaunchKernelGGL((linear_bf16_any_kernel<BM, BN, false>), dim3((unsigned)blocks), dim3(256), 0, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
+}
+
 }  // namespace
 }  // namespace gas
 
@@ -1998,11 +2136,12 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
     if (!vec) {
-        const int64_t total = n_rows * (int64_t)F_out;
-        const int64_t blocks = (total + 255) / 256;
-        if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "%s: problem too large for the element-wise path", who);
-        hipLaunchKernelGGL(linear_bf16_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
-        GAS_CHECK_HIP(hipGetLastError());
+        // Small tiles until their number fills the units several times (256 -> 250 in 64 x 64 and in larger ones: 5,000 rows
+        // 9.5 and 14.1 us, 20,000 17.0 and 17.9, 50,000 34.5 and 30.3; the masked input gradient, whose larger tiles wait longer for
+        // the mask, 15.3 and 20.3, 31.5 and 36.0, at 150,000 81 and 76).
+        const gas_status st = (n_rows + 63) / 64 * ((F_out + 63) / 64) <= (trans_w ? 4096 : 2048) ? launch_bf16_any<64, 64>(a, s)
+                              : F_out <= 64 ? launch_bf16_any<128, 64>(a, s) : launch_bf16_any<128, 128>(a, s);
+        if (st != GAS_OK) return st;
         return push_after(push, Y, ldy, n_rows, F_out, dt, s);
     }
     if (F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 && n_rows >= 4096 &&
@@ -2131,9 +2270,9 @@ static gas_status run_dw(const void* Z, int64_t ldz, const void* GP, int64_t ldg
             const gas_status st = launch_dw_bf16(a, s);
             if (st != GAS_OK) return st;
         } else {
-            const int64_t blocks = (per * n_slabs + 255) / 256;
-            GAS_REQUIRE(blocks <= 0x7FFFFFFFLL, "gas_linear_bwd_weight: problem too large for the element-wise path");
-            hipLaunchKernelGGL(dw_bf16_generic_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
+            const gas_status st = F_in <= 64 ? (F_out <= 64 ? launch_dw_any<64, 64>(a, s) : launch_dw_any<64, 128>(a, s))
+                                             : (F_out <= 64 ? launch_dw_any<128, 64>(a, s) : launch_dw_any<128, 128>(a, s));
+            if (st != GAS_OK) return st;
         }
     }
     hipLaunchKernelGGL(dw_reduce_kernel, dim3(rblocks), dim3(256), 0, s, a);
@@ -2328,15 +2467,17 @@ static gas_status run_mlp2(const void* Z, int64_t ldz, int64_t n_rows, int32_t F
         w.H_out = static_cast<uint16_t*>(H_out); w.ldh_out = ldh_out;
         const gas_status st = F_in <= 128 ? launch_ws_mlp<8, 16>(w, s) : launch_ws_mlp<16, 16>(w, s);
         return (st != GAS_OK || scatter) ? st : push_after(push, Y, ldy, n_rows, F_out, dt, s);
-    } else if (vec) {
+    } else {
         constexpr int smem = 2 * (kMlpRowsBF16 * (kHidMax + 8 + kBKh + 8) + 256 * (kBKh + 8));
-        static const hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp2_bf16_kernel),
+        static const hipError_t e1 = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp2_bf16_kernel<false>),
+                                                         hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        static const hipError_t e2 = hipFuncSetAttribute(reinterpret_cast<const void*>(mlp2_bf16_kernel<true>),
                                                          hipFuncAttributeMaxDynamicSharedMemorySize, smem);
         GAS_CHECK_HIP(e1);
-        hipLaunchKernelGGL(mlp2_bf16_kernel, dim3((unsigned)((n_rows + kMlpRowsBF16 - 1) / kMlpRowsBF16), (unsigned)gn),
-                           dim3(256), smem, s, a);
-    } else {
-        hipLaunchKernelGGL(mlp2_generic_kernel<true>, dim3((unsigned)n_rows), dim3(256), 0, s, a);
+        GAS_CHECK_HIP(e2);
+        const dim3 grid((unsigned)((n_rows + kMlpRowsBF16 - 1) / kMlpRowsBF16), (unsigned)gn);
+        if (vec) hipLaunchKernelGGL(mlp2_bf16_kernel<false>, grid, dim3(256), smem, s, a);
+        else hipLaunchKernelGGL(mlp2_bf16_kernel<true>, grid, dim3(512), smem, s, a);
     }
     GAS_CHECK_HIP(hipGetLastError());
     return push_after(push, Y, ldy, n_rows, F_out, dt, s);

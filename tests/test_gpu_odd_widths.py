@@ -110,3 +110,32 @@ def test_push_of_odd_rows_to_host_memory(F, dtype):
         want = torch.full((n_table, F), 7.0, dtype=dtype)
         want[idx.cpu().long()] = y.cpu()
         assert torch.equal(rows, want)
+
+
+# around a tile of 64 and 128 rows and columns, a step of 64 and a word of two
+@pytest.mark.parametrize("m,k,h,n", [(1, 1, 1, 1), (63, 65, 63, 64), (64, 63, 65, 127), (65, 129, 255, 257), (129, 64, 256, 3), (16600, 9, 33, 129)])
+def test_bf16_mlp_and_masks_of_odd_widths(m, k, h, n):
+    """The fused MLP and the masked input gradient with an infinite row among finite ones, which no other row may see."""
+    import paper_2106_05609_amd as gas
+    z, w1, w2, g = (rng.normal_matrix(3, 840 + i, *s, dtype=torch.bfloat16).cuda() for i, s in
+                    enumerate(((m, k), (k, h), (h, n), (m, h))))
+    if m > 1:
+        z[m // 2] = float("inf")
+    b1, b2 = (rng.normal_matrix(3, 850 + i, 1, s, dtype=torch.bfloat16).cuda()[0] for i, s in enumerate((h, n)))
+    y = torch.full((m, n + 1), 7.0, dtype=torch.bfloat16, device="cuda")
+    gas.gas_mlp2(z, w1, w2, y[:, :n], b1=b1, b2=b2)
+    rows = torch.arange(m, device="cuda") != m // 2 if m > 1 else torch.ones(1, dtype=torch.bool, device="cuda")
+    z64 = z[rows].double()
+    hid, hid_size = (z64 @ w1.double() + b1.double()).clamp_min(0), z64.abs() @ w1.double().abs() + b1.double().abs()
+    # the hidden row is rounded to bf16 (2^-8 of it) after k + 1 fp32 sums; the output after h + 1 more
+    hid_err = 2.0 ** -8 * hid + (k + 2) * 2.0 ** -24 * hid_size * (1 + 2.0 ** -8)
+    want, size = hid @ w2.double() + b2.double(), hid @ w2.double().abs() + b2.double().abs()
+    bound = 2.0 ** -8 * want.abs() + (hid_err @ w2.double().abs() + (h + 2) * 2.0 ** -24 * (size + hid_err @ w2.double().abs())) * (1 + 2.0 ** -8)
+    assert bool(((y[rows, :n].double() - want).abs() <= bound).all()) and bool((y[:, n] == 7.0).all())
+    gz = torch.full((m, k + 1), 7.0, dtype=torch.bfloat16, device="cuda")
+    mask = rng.normal_matrix(3, 860, m, k, dtype=torch.bfloat16).cuda()
+    gas.gas_linear_bwd_input(g, w1, gz[:, :k], mask=mask)
+    want, size = g.double() @ w1.double().t(), g.double().abs() @ w1.double().t().abs()
+    want, size = want * (mask > 0), size * (mask > 0)
+    bound = 2.0 ** -8 * want.abs() + (h + 2) * 2.0 ** -24 * size * (1 + 2.0 ** -8)
+    assert bool(((gz[:, :k].double() - want).abs() <= bound).all()) and bool((gz[:, k] == 7.0).all())
