@@ -930,17 +930,21 @@ __global__ __launch_bounds__(256, 2) void linear_bf16_any_kernel(LinArgs a) {
     store_tile_bf16<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
-template <int BN>
+// Y tile of BM x BN, 16-byte loads.  A step's loads are under way while the one before is multiplied; where the units hold few
+// tiles, their latency and the turning of W bound it, so tiles are small (64 x 64 at 500 x 256 x 256 7.2 us, 128 x 256 20.1).
+template <int BM, int BN>
 __global__ __launch_bounds__(256) void linear_bf16_kernel(LinArgs a) {
-    constexpr int BM = 128, TM = 2, TN = BN / 64;
+    constexpr int TM = BM / 64, TN = BN / 64;
     __shared__ __attribute__((aligned(16))) uint16_t As[BM][kLdh];
     __shared__ __attribute__((aligned(16))) uint16_t Bs[BN][kLdh];
     const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
     const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63, li = lane & 31, lh = lane >> 5;
-    const int64_t m0 = (int64_t)blockIdx.x * BM;
-    const int n0 = blockIdx.y * BN;
-    const int wm0 = (wave >> 1) * 64, wn0 = (wave & 1) * (BN / 2);
+    const unsigned tn = (unsigned)((a.N + BN - 1) / BN), of_xcd = blockIdx.x / 8;   // a row tile's column tiles follow each other on one XCD
+    const int64_t m0 = ((int64_t)(of_xcd / tn) * 8 + blockIdx.x % 8) * BM;
+    const int n0 = (int)(of_xcd % tn) * BN;
+    if (m0 >= a.M) return;
+    const int wm0 = (wave >> 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
     f32x16 acc[TM][TN];
     zero_acc(acc);
     ATileBF16<BM> ta;
@@ -2027,12 +2031,11 @@ gas_status run_ws_split(const LinArgs& a, hipStream_t s) {
     }
 }
 
-template <int BN>
+template <int BM, int BN>
 gas_status launch_bf16(const LinArgs& a, hipStream_t s) {
-    const int64_t gm = (a.M + 127) / 128;
-    const int gn = (a.N + BN - 1) / BN;
-    if (gm > 0x7FFFFFFF || gn > 65535) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
-    hipLaunchKernelGGL((linear_bf16_kernel<BN>), dim3((unsigned)gm, (unsigned)gn), dim3(256), 0, s, a);
+    const int64_t blocks = ((a.M + BM - 1) / BM + 7) / 8 * 8 * ((a.N + BN - 1) / BN);
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_linear: problem too large for one launch");
+    hipLaunchKernelGGL((linear_bf16_kernel<BM, BN>), dim3((unsigned)blocks), dim3(256), 0, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
@@ -2144,8 +2147,16 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         if (st != GAS_OK) return st;
         return push_after(push, Y, ldy, n_rows, F_out, dt, s);
     }
-    if (F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 && n_rows >= 4096 &&
-        (!mask || (aligned16(mask) && ldmask % 8 == 0)) && ldz < (1 << 24) && ldy < (1 << 24) && ldmask < (1 << 24)) {
+    // A workgroup that keeps all weights needs several row tiles to be worth its start, and a tile of 64 x 64 a quarter of that:
+    // 500 rows 256 -> 256 in 64 x 64 7.2 us (128 x 256, one wavefront a unit, 20.1), 1,024 inputs 19.8 and 31.5, 16,000 rows 11.2
+    // and with the weights in place 16.9, 50,000 33.0 and 27.3; the masked input gradient, which starts sooner because its weights
+    // take no turning, 6,000 rows 6.6 and 8.8, 16,000 9.7 and 9.6.  Up to 64 columns six wavefronts of eight would hold no
+    // weights: 50,000 rows 256 -> 64 11.2 and 21.6, 300,000 49 and 56.  Wider than the weights-stationary kernel takes: 128 x
+    // 128 once small tiles fill the chip (100,000 rows 512 -> 256 98 and 89), but not transposed (90 and 98).
+    const bool ws = F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
+        (!mask || (aligned16(mask) && ldmask % 8 == 0)) && ldz < (1 << 24) && ldy < (1 << 24) && ldmask < (1 << 24);
+    const bool small = F_out <= 64 || (!ws && trans_w) || (n_rows + 63) / 64 * ((F_out + 63) / 64) <= (trans_w ? 512 : 1024);
+    if (ws && !small) {
         const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
         w.Z = static_cast<const uint16_t*>(Z); w.ldz = ldz;
@@ -2159,7 +2170,7 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         const gas_status st = F_in <= 64 ? launch_ws<4>(w, s) : (F_in <= 128 ? launch_ws<8>(w, s) : launch_ws<16>(w, s));
         return (st != GAS_OK || scatter) ? st : push_after(push, Y, ldy, n_rows, F_out, dt, s);
     }
-    const gas_status st = F_out <= 64 ? launch_bf16<64>(a, s) : (F_out <= 128 ? launch_bf16<128>(a, s) : launch_bf16<256>(a, s));
+    const gas_status st = small ? launch_bf16<64, 64>(a, s) : launch_bf16<128, 128>(a, s);
     return st != GAS_OK ? st : push_after(push, Y, ldy, n_rows, F_out, dt, s);
 }
 
@@ -2426,9 +2437,14 @@ static gas_status run_mlp2(const void* Z, int64_t ldz, int64_t n_rows, int32_t F
     const int q = dt == GAS_F32 ? 4 : 8;    // elements per 16 bytes
     const bool vec = aligned16(Z) && aligned16(W1) && aligned16(W2) && ldz % q == 0 && F_in % q == 0 &&
                      F_hid % q == 0 && F_out % q == 0;
-    const bool ws_path = dt == GAS_BF16 && vec && F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
-                         n_rows >= 4096 && ldz < (1 << 24) && ldy < (1 << 24) && H_out && aligned16(H_out) &&
-                         ldh_out % 8 == 0 && ldh_out < (1 << 24);
+    // The fused kernel holds both weight matrices in registers: for a narrow hidden layer most wavefronts hold nothing.  Hidden 64
+    // wide: two products 8.1 us, fused 10.1 (2,000 rows), 300,000 48 and 72; without a place for the hidden rows the tiled kernel 8.5
+    // and 9.7, at 60,000 20.7 and 19.2.  128 wide: 10,000 rows 10.9 and 11.1, 60,000 27.3 and 21.7.  256 wide: 500 rows 14.5 and 14.2
+    // (tiled 20.8), 30,000 39.7 and 20.7.
+    const bool fused = H_out ? F_hid > 64 && (F_hid > 128 || n_rows > 16000) : F_hid > 64 || n_rows > 30000;
+    const bool ws_path = dt == GAS_BF16 && vec && fused && F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
+                         ldz < (1 << 24) && ldy < (1 << 24) &&             // offsets inside a 64-row tile are 32-bit
+                         (!H_out || (aligned16(H_out) && ldh_out % 8 == 0 && ldh_out < (1 << 24)));
     if (H_out && !ws_path) {
         // only the weights-stationary kernel stores the hidden activation on its way: elsewhere two stored linears
         gas_status st = run_linear("gas_mlp2_keep", Z, ldz, n_rows, F_in, W1, 0, F_hid, b1, dt, 0.f, 1.f, 1, nullptr, 0,
@@ -2450,9 +2466,7 @@ static gas_status run_mlp2(const void* Z, int64_t ldz, int64_t n_rows, int32_t F
         dim3 grid((unsigned)((n_rows + kMlpRowsF32 - 1) / kMlpRowsF32), (unsigned)gn);
         if (vec) hipLaunchKernelGGL(mlp2_f32_kernel<true>, grid, dim3(256), smem, s, a);
         else hipLaunchKernelGGL(mlp2_f32_kernel<false>, grid, dim3(256), smem, s, a);
-    } else if (vec && F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 && n_rows >= 4096 &&
-               ldz < (1 << 24) && ldy < (1 << 24) &&      // offsets inside a 64-row tile are 32-bit
-               (!H_out || (aligned16(H_out) && ldh_out % 8 == 0 && ldh_out < (1 << 24)))) {
+    } else if (ws_path) {
         // the kernel scatters the rows itself if the history rows take 16-byte stores; else the row copy follows
         const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
