@@ -30,21 +30,23 @@ class _Kept:
 def plan_limits(rows, entries, longest):
     """Which rows of a pattern are cut into chunks, and how long a chunk is (gas_plan_options).  A wavefront, or a team of its lanes,
     walks a light row's entries, 0.1 us each, and a launch waits for the longest; a chunk's partial sum is written and read
-    again, and any heavy row adds two launches.  So the line follows the batch: 256 entries where the whole takes some 200 us
-    and more, 64 where it takes 20, but no less than twice the mean (rows of like lengths hide each other's walks), and none
-    where the longest row is hardly longer than that.  us, rows above 512 by 256 entries and so, aggregations of power-law batches (and
-    their adjoints), 256 floats, 64 floats, 256 bf16:
+    again, and any heavy row adds two launches.  So the line follows the batch: 256 entries where the whole takes half a
+    millisecond and more, 64 where it takes 20 to 200 us, but no less than twice the mean (rows of like lengths hide each other's
+    walks), and none where the longest row is hardly longer than that or its walk is short beside the launch.  us, rows above
+    512 by 256 entries and so, aggregations of power-law batches (and their adjoints), 256 floats, 64 floats, 256 bf16:
     - 250,000 rows of 40: 1,223 -> 1,192 (565 -> 553), 459 -> 417 (259 -> 245), 704 -> 659 (329 -> 321);
-    - 50,000 rows of 37: 260 -> 223 (121 -> 99), 140 -> 99 (99 -> 65), 180 -> 137 (117 -> 79);
     - 15,000 rows of 43: 143 -> 83 (53 -> 41), 105 -> 43 (60 -> 33), 125 -> 53 (59 -> 38);
     - 3,750 rows of 24, the longest 269: 34 -> 29, 33 -> 22, 33 -> 25; by chunks of 128 50, 43, 49;
-    - 25,000 rows of 18, the longest 141: whole 64, with 64 the line 75."""
+    - 25,000 rows of 18, the longest 141: whole 64, with 64 the line 75.
+    Forward passes of two layers, 240 bf16, line and chunk: 37,000 rows of 47, whole rows 378, 256 and 128 304, 128 and 128 290, 64
+    and 64 284; 100,000 rows of 43 756, 674, 654, 657; 350,000 rows of 68 2,915, 2,914, 2,917, 2,984; 117,000 rows of 17, the longest
+    290, 414, 448, 446, 431."""
     if rows == 0:
         return None
-    line = min(512, max(256 if entries >= 3_000_000 else 128 if entries >= 1_000_000 else 64, -(-2 * entries // rows)))
-    if longest <= min(512, line + 144):
+    line = min(512, max(256 if entries >= 10_000_000 else 128 if entries >= 3_000_000 else 64, -(-2 * entries // rows)))
+    if longest <= min(512, line + 144 + entries // 6000):
         return None
-    return dict(heavy_threshold=line, chunk=128 if entries >= 1_000_000 else 64 if entries >= 200_000 else 32)
+    return dict(heavy_threshold=line, chunk=128 if entries >= 10_000_000 else 64 if entries >= 200_000 else 32)
 
 
 class BatchGraph:

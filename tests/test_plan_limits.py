@@ -9,7 +9,9 @@ from paper_2106_05609_amd.executor import plan_limits
     (3_750, 89_108, 269, (64, 32)),                      # few entries: a launch waits for its longest row
     (25_000, 462_196, 141, None),                        # hardly longer than the line
     (15_000, 642_765, 563, (86, 64)),                    # twice the mean
-    (50_000, 1_826_185, 1_705, (128, 128)),
+    (50_000, 1_826_185, 1_705, (74, 64)),
+    (100_000, 4_311_623, 3_302, (128, 64)),
+    (116_664, 1_979_499, 290, None),                     # a short walk beside the launch
     (600_000, 50_318_351, 17_482, (256, 128)),
     (4_000, 480_381, 152, None),                         # long rows of like lengths
     (1_000, 600_000, 5_000, (512, 64)),                  # no line above 512
