@@ -508,6 +508,13 @@ GAS_API gas_status gas_pna_aggregate_blocks(const int32_t* rowptr, const int32_t
                              const void* X, int64_t ldx, gas_dtype dt, int32_t F,
                              const void* add, int64_t ldadd, float delta, int32_t blocks,
                              void* out, int64_t ldout, void* stream);
+/* The same for a pattern none of whose rows has more than `longest` entries (the output of a longer one is undefined), with
+ * own_to[v, 0:F_own] = own[v, 0:F_own] if own is given (the receiving nodes' own rows, to the columns before out). */
+GAS_API gas_status gas_pna_aggregate_own(const int32_t* rowptr, const int32_t* col, int64_t n_rows, int32_t longest,
+                             const void* X, int64_t ldx, gas_dtype dt, int32_t F,
+                             const void* add, int64_t ldadd, float delta, int32_t blocks,
+                             void* out, int64_t ldout, const void* own, int64_t ld_own, int32_t F_own,
+                             void* own_to, int64_t ld_own_to, void* stream);
 
 /*
  * The transform of a PNA layer by the rows' degrees (fp32).  With X = [h (F columns) | A (3 F1 columns: mean, min, max) | ...],
@@ -560,6 +567,12 @@ GAS_API gas_status gas_gat_aggregate(const int32_t* rowptr, const int32_t* col, 
 GAS_API gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32_t* col, int64_t n_rows, const void* P,
                                    int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
                                    const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz, void* stream);
+/* The same for a pattern none of whose rows has more than `longest` entries (the output of a longer one is undefined); row v of Z
+ * is also stored to push_hist[push_idx[v]] if push_idx is given (distinct, in range; heads * F columns). */
+GAS_API gas_status gas_gat_aggregate_push(const int32_t* rowptr, const int32_t* col, int64_t n_rows, int32_t longest, const void* P,
+                                  int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
+                                  const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz,
+                                  const int32_t* push_idx, void* push_hist, int64_t n_hist_rows, int64_t ld_push, void* stream);
 
 /*
  * Backward passes of the two aggregations above (chain rule on the equations of the operator appendix), without
@@ -605,6 +618,12 @@ GAS_API gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const in
                                  const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta, int32_t blocks,
                                  const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd, int64_t ldga,
                                  void* workspace, int64_t workspace_bytes, void* stream);
+/* The same for a pattern none of whose rows has more than `longest` entries (results of others are undefined). */
+GAS_API gas_status gas_pna_aggregate_bwd_bounded(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t rows,
+                                 int32_t longest, int64_t entries, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_out,
+                                 const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta, int32_t blocks,
+                                 const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd, int64_t ldga,
+                                 void* workspace, int64_t workspace_bytes, void* stream);
 GAS_API int64_t gas_gat_aggregate_bwd_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F);
 GAS_API gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
                                  const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
@@ -615,6 +634,14 @@ GAS_API gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* 
 /* The same for `heads` heads side by side (as gas_gat_aggregate_heads; Ga_dst, Ga_src [heads * F]). */
 GAS_API int64_t gas_gat_aggregate_bwd_heads_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F, int32_t heads);
 GAS_API gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                       const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
+                                       int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
+                                       int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
+                                       const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
+                                       void* workspace, int64_t workspace_bytes, void* stream);
+/* The same for a pattern none of whose rows, and columns, has more than `longest` and `longest_col` entries. */
+GAS_API gas_status gas_gat_aggregate_bwd_bounded(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                       int32_t longest, int32_t longest_col,
                                        const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
                                        int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
                                        int32_t heads, const void* a_dst, const void* a_src, float negative_slope,

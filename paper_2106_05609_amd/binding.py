@@ -26,7 +26,8 @@ EXPORTS = [
     "gas_pna_linear", "gas_pna_linear_workspace", "gas_pna_linear_bwd_input", "gas_pna_linear_bwd_weight",
     "gas_pna_linear_bwd_weight_workspace", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
     "gas_gat_aggregate_bwd_heads", "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
-    "gas_gat_aggregate_bwd_heads_workspace",
+    "gas_gat_aggregate_bwd_heads_workspace", "gas_gat_aggregate_push", "gas_pna_aggregate_own", "gas_pna_aggregate_bwd_bounded",
+    "gas_gat_aggregate_bwd_bounded",
     "gas_disk_open", "gas_disk_close", "gas_disk_pull", "gas_disk_push", "gas_disk_wait", "gas_disk_read_rows",
     "gas_disk_write_rows", "gas_disk_sync",
 ]
@@ -81,7 +82,9 @@ _SIGNATURES = dict(
     gas_linear_bwd_weight_workspace="qii", gas_linear_bwd_weight="pqpqqiiifppqp",
     gas_linear_bwd_weight_static="pqpqqiiifpp", gas_softmax_xent="pqqiipfpppqp", gas_sgd_step="pqipffp",
     gas_sq_norm="pqpp", gas_sgd_step_clipped="pqipffpifp", gas_pna_aggregate="ppqpqiipqfpqp", gas_pna_aggregate_blocks="ppqpqiipqfipqp",
-    gas_pna_aggregate_bwd_blocks="pppqqpppqpqiifipqpqpqpqp", gas_pna_groups="pqipp", gas_pna_groups_workspace="qi",
+    gas_pna_aggregate_bwd_blocks="pppqqpppqpqiifipqpqpqpqp", gas_pna_aggregate_bwd_bounded="pppqiqpppqpqiifipqpqpqpqp",
+    gas_pna_aggregate_own="ppqipqiipqfipqpqipqp", gas_gat_aggregate_push="ppqipqiiippfipqppqqp",
+    gas_gat_aggregate_bwd_bounded="pppqiipppqqqpqiiippfpqpqpppqp", gas_pna_groups="pqipp", gas_pna_groups_workspace="qi",
     gas_pna_linear="pqipqiipifipqppqpqp", gas_pna_linear_workspace="iiii", gas_pna_linear_bwd_input="pqipqiipifpqpqp",
     gas_pna_linear_bwd_weight="pqipqpqiiifppqp", gas_pna_linear_bwd_weight_workspace="qiiii",
     gas_gat_aggregate_heads="ppqpqiiippfipqp", gas_pna_aggregate_bwd_workspace="qqi",
@@ -677,17 +680,24 @@ def gas_sgd_step_clipped(w, dw, lr, sq_norms, max_norm, weight_decay=0.0):
                                       sq_norms.numel(), max_norm, _stream()))
 
 
-def gas_pna_aggregate(rowptr, col, x, out, delta, add=None, blocks=9):
+ANY_LENGTH = 0x7FFFFFFF          # of rows and columns: nothing is known
+
+
+def gas_pna_aggregate(rowptr, col, x, out, delta, add=None, blocks=9, longest=ANY_LENGTH, own=None, own_to=None):
     """out [n_rows, 9F] = scalers [1, s, 1/s] (x) aggregators [mean, min, max] over the neighbours (+ add); blocks = 3: out
-    [n_rows, 3F], the aggregators alone."""
+    [n_rows, 3F], the aggregators alone.  longest: no row has more entries; own_to[v] = own[v] if given."""
     n_rows = rowptr.numel() - 1
     xp, ldx, _, F, dt = _size(x)
     op, ldo, no, Fo, dto = _size(out)
     ap, lda, na, Fa, dta = (0, 0, n_rows, F, dt) if add is None else _size(add)
     if dto != dt or no < n_rows or Fo != blocks * F or dta != dt or Fa != F or na < n_rows:
         raise ValueError("gas_pna_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_pna_aggregate_blocks(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, xp, ldx, dt, F, ap, lda, delta,
-                                             blocks, op, ldo, _stream()))
+    wp, ldw, nw, Fw, dtw = (0, 0, n_rows, 0, dt) if own is None else _size(own)
+    tp, ldt, nt, Ft, dtt = (0, 0, n_rows, 0, dt) if own_to is None else _size(own_to)
+    if Fw != Ft or nw < n_rows or nt < n_rows or dtw != dt or dtt != dt:
+        raise ValueError("gas_pna_aggregate: the own rows and their target do not match")
+    _check(_calls().gas_pna_aggregate_own(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, longest, xp, ldx, dt, F, ap, lda,
+                                          delta, blocks, op, ldo, wp, ldw, Fw, tp, ldt, _stream()))
 
 
 PNA_MAX_DEGREE = 63
@@ -744,18 +754,23 @@ def gas_pna_linear_bwd_weight(groups, max_degree, x, g, f1, delta, dw):
                                            dw.data_ptr(), ws.data_ptr(), ws.numel(), _stream()))
 
 
-def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False, heads=1):
+def gas_gat_aggregate(rowptr, col, p, a_dst, a_src, z, negative_slope=0.2, relu=False, heads=1, longest=ANY_LENGTH, idx=None,
+                      hist=None):
     """z[v] = sum_k softmax_k(LeakyReLU(a_dst.p[v] + a_src.p[col k])) p[col k] over the entries of row v.  heads > 1: the
-    columns of p and z and the elements of a_dst and a_src are that many equal blocks, a head each."""
+    columns of p and z and the elements of a_dst and a_src are that many equal blocks, a head each.  longest: no row has more
+    entries; z[v] also goes to hist[idx[v]] if given (distinct)."""
     pp, ldp, _, width, dt = _size(p)
     zp, ldz, nz, fz, dtz = _size(z)
     n_rows = rowptr.numel() - 1
     if dtz != dt or a_dst.dtype != p.dtype or a_src.dtype != p.dtype or fz != width or \
             nz < n_rows or a_dst.numel() != width or a_src.numel() != width or heads < 1 or width % heads:
         raise ValueError("gas_gat_aggregate: shapes or dtypes do not match")
-    _check(_calls().gas_gat_aggregate_heads(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, pp, ldp, dt,
-                                            width // heads, heads, _ptr(a_dst), _ptr(a_src), negative_slope, int(relu), zp,
-                                            ldz, _stream()))
+    hp, ldh, n_hist, fh, dth = (0, 0, 0, width, dt) if hist is None else _size(hist)
+    if (idx is None) != (hist is None) or fh != width or dth != dt or (idx is not None and idx.numel() != n_rows):
+        raise ValueError("gas_gat_aggregate: the history table or its indices do not match")
+    _check(_calls().gas_gat_aggregate_push(_ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, longest, pp, ldp, dt,
+                                           width // heads, heads, _ptr(a_dst), _ptr(a_src), negative_slope, int(relu), zp,
+                                           ldz, _ptr(idx, torch.int32), hp, n_hist, ldh, _stream()))
 
 
 def gas_axpy(x, e, y, alpha=1.0):
@@ -906,10 +921,11 @@ class DiskTable:
             pass
 
 
-def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, gadd=None, plan_t=None, blocks=9):
+def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, gadd=None, plan_t=None, blocks=9,
+                          longest=ANY_LENGTH):
     """Backward of gas_pna_aggregate: gx [n_out, F] (n_out = gx.shape[0] columns of the pattern), gadd [n_rows, F]; g of nine
     blocks, or of blocks = 3, folded with their scalers.
-    plan_t: a Plan of the CSC copy for those n_out columns (fast path), or None (plain kernels)."""
+    plan_t: a Plan of the CSC copy for those n_out columns (fast path), or None (plain kernels).  longest: no row has more entries."""
     xp, ldx = _mat(x)
     gp, ldg = _mat(g)
     op, ldo = _mat(gx)
@@ -920,18 +936,18 @@ def gas_pna_aggregate_bwd(rowptr, col, colptr, row, csc_pos, x, g, gx, delta, ga
     nnz = col.numel()
     nbytes = int(_calls().gas_pna_aggregate_bwd_workspace(n_rows, nnz, F))
     ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=x.device)
-    _check(_calls().gas_pna_aggregate_bwd_blocks(plan_t.handle if plan_t is not None else 0,
-                                              _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
+    _check(_calls().gas_pna_aggregate_bwd_bounded(plan_t.handle if plan_t is not None else 0,
+                                              _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, longest,
                                               nnz, _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
                                               gx.shape[0], xp, ldx, _dt(x), F, delta, blocks,
                                               gp, ldg, op, ldo, ap, lda, _ptr(ws), nbytes, _stream()))
 
 
 def gas_gat_aggregate_bwd(rowptr, col, colptr, row, csc_pos, p, a_dst, a_src, gz, gp_out, ga_dst, ga_src,
-                          negative_slope=0.2, plan_t=None, heads=1):
+                          negative_slope=0.2, plan_t=None, heads=1, longest=ANY_LENGTH, longest_col=ANY_LENGTH):
     """Backward of gas_gat_aggregate (gz: gradient before any activation): gp_out [n_out, F] rows of P's gradient,
     ga_dst / ga_src float32 [F].  plan_t: a Plan of the CSC copy for those n_out columns, or None; used where the heads are taken
-    one by one (see gas.h).  heads > 1: as in gas_gat_aggregate."""
+    one by one (see gas.h).  heads > 1: as in gas_gat_aggregate.  No row has more than longest entries, no column longest_col."""
     pp, ldp = _mat(p)
     zp, ldz = _mat(gz)
     op, ldo = _mat(gp_out)
@@ -941,8 +957,8 @@ def gas_gat_aggregate_bwd(rowptr, col, colptr, row, csc_pos, p, a_dst, a_src, gz
         raise ValueError("gas_gat_aggregate_bwd: shapes or dtypes do not match")
     nbytes = int(_calls().gas_gat_aggregate_bwd_heads_workspace(n_rows, n_cols, nnz, F // heads, heads))
     ws = torch.empty(max(nbytes, 1), dtype=torch.uint8, device=p.device)
-    _check(_calls().gas_gat_aggregate_bwd_heads(plan_t.handle if plan_t is not None else 0,
-                                                _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows,
+    _check(_calls().gas_gat_aggregate_bwd_bounded(plan_t.handle if plan_t is not None else 0,
+                                                _ptr(rowptr, torch.int32), _ptr(col, torch.int32), n_rows, longest, longest_col,
                                                 _ptr(colptr, torch.int32), _ptr(row, torch.int32), _ptr(csc_pos, torch.int32),
                                                 n_cols, gp_out.shape[0], nnz, pp, ldp, _dt(p), F // heads, heads, _ptr(a_dst),
                                                 _ptr(a_src), negative_slope, zp, ldz, op, ldo, _ptr(ga_dst), _ptr(ga_src),

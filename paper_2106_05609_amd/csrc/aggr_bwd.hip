@@ -360,9 +360,11 @@ __global__ __launch_bounds__(64 * kLongWaves) void pna_bwd_long_rows_kernel(PnaF
     }
 }
 
+// No launch for the long rows, or columns, where there are none: it takes 4 to 6 us to find that out.
 template <bool BF, int G>
-void launch_pna_bwd_rows(const PnaFastArgs& a, hipStream_t s) {
+void launch_pna_bwd_rows(const PnaFastArgs& a, int longest, hipStream_t s) {
     hipLaunchKernelGGL((pna_bwd_rows_vec_kernel<BF, G>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
+    if (longest <= kLongRow) return;
     const unsigned blocks = long_row_blocks(a.n_rows);
     hipLaunchKernelGGL((pna_bwd_long_rows_kernel<BF, G>), dim3(blocks), dim3(64 * kLongWaves), 0, s, a);
 }
@@ -908,25 +910,25 @@ __global__ __launch_bounds__(64 * kLongWaves) void gat_bwd_long_cols_kernel(GatB
 }
 
 template <bool BF, int G, int H>
-void launch_gat_bwd(const GatBwdArgs& a, bool columns, hipStream_t s) {
+void launch_gat_bwd(const GatBwdArgs& a, bool columns, bool long_rows, bool long_cols, hipStream_t s) {
     if (a.n_rows > 0) {
         hipLaunchKernelGGL((gat_bwd_rows_vec_kernel<BF, G, H>), dim3((unsigned)a.n_rows), dim3(64), 0, s, a);
-        hipLaunchKernelGGL((gat_bwd_long_rows_kernel<BF, G, H>), dim3(long_row_blocks(a.n_rows)), dim3(64 * kLongWaves), 0, s, a);
+        if (long_rows) hipLaunchKernelGGL((gat_bwd_long_rows_kernel<BF, G, H>), dim3(long_row_blocks(a.n_rows)), dim3(64 * kLongWaves), 0, s, a);
     }
     if (!columns) return;
     const dim3 cols((unsigned)(a.n_cols < kColBlocks ? a.n_cols : kColBlocks), (unsigned)((a.n_cols + kColBlocks - 1) / kColBlocks));
     if (a.nnz <= kShortColumn * a.n_cols) hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H, 4>), cols, dim3(64), 0, s, a);
     else hipLaunchKernelGGL((gat_bwd_cols_vec_kernel<BF, G, H, 8>), cols, dim3(64), 0, s, a);
-    hipLaunchKernelGGL((gat_bwd_long_cols_kernel<BF, G, H>), dim3(long_row_blocks(a.n_cols)), dim3(64 * kLongWaves), 0, s, a);
+    if (long_cols) hipLaunchKernelGGL((gat_bwd_long_cols_kernel<BF, G, H>), dim3(long_row_blocks(a.n_cols)), dim3(64 * kLongWaves), 0, s, a);
 }
 
 template <bool BF>
-void launch_gat_bwd_heads(const GatBwdArgs& a, int H, bool columns, hipStream_t s) {
+void launch_gat_bwd_heads(const GatBwdArgs& a, int H, bool columns, bool long_rows, bool long_cols, hipStream_t s) {
     const int G = gat_team<BF>(a.F, true);
-    if (G == 64) launch_gat_bwd<BF, 64, 1>(a, columns, s);
-    else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, columns, s) : launch_gat_bwd<BF, 32, 1>(a, columns, s);
-    else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, columns, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, columns, s) : launch_gat_bwd<BF, 16, 1>(a, columns, s);
-    else if constexpr (BF) H == 4 ? launch_gat_bwd<BF, 8, 4>(a, columns, s) : H == 2 ? launch_gat_bwd<BF, 8, 2>(a, columns, s) : launch_gat_bwd<BF, 8, 1>(a, columns, s);
+    if (G == 64) launch_gat_bwd<BF, 64, 1>(a, columns, long_rows, long_cols, s);
+    else if (G == 32) H == 2 ? launch_gat_bwd<BF, 32, 2>(a, columns, long_rows, long_cols, s) : launch_gat_bwd<BF, 32, 1>(a, columns, long_rows, long_cols, s);
+    else if (G == 16) H == 4 ? launch_gat_bwd<BF, 16, 4>(a, columns, long_rows, long_cols, s) : H == 2 ? launch_gat_bwd<BF, 16, 2>(a, columns, long_rows, long_cols, s) : launch_gat_bwd<BF, 16, 1>(a, columns, long_rows, long_cols, s);
+    else if constexpr (BF) H == 4 ? launch_gat_bwd<BF, 8, 4>(a, columns, long_rows, long_cols, s) : H == 2 ? launch_gat_bwd<BF, 8, 2>(a, columns, long_rows, long_cols, s) : launch_gat_bwd<BF, 8, 1>(a, columns, long_rows, long_cols, s);
 }
 
 // ---- the column side of one head, with a plan of the CSC copy: on patterns of many short columns the grouped rows of the
@@ -1194,8 +1196,8 @@ gas_status gas_pna_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, 
                                         GX, ldgx, Gadd, ldga, workspace, workspace_bytes, stream);
 }
 
-gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
-                                        int64_t nnz, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos,
+gas_status gas_pna_aggregate_bwd_bounded(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                        int32_t longest, int64_t nnz, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos,
                                         int64_t n_out, const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta,
                                         int32_t blocks, const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd,
                                         int64_t ldga, void* workspace, int64_t workspace_bytes, void* stream) {
@@ -1234,13 +1236,13 @@ gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* r
         a.F = F; a.inv_delta = 1.f / delta; a.folded = blocks == 3;
         const int pieces = F / (bf ? 8 : 4);
         if (bf) {
-            if (pieces <= 16) launch_pna_bwd_rows<true, 16>(a, s);
-            else if (pieces <= 32) launch_pna_bwd_rows<true, 32>(a, s);
-            else launch_pna_bwd_rows<true, 64>(a, s);
+            if (pieces <= 16) launch_pna_bwd_rows<true, 16>(a, longest, s);
+            else if (pieces <= 32) launch_pna_bwd_rows<true, 32>(a, longest, s);
+            else launch_pna_bwd_rows<true, 64>(a, longest, s);
         } else {
-            if (pieces <= 16) launch_pna_bwd_rows<false, 16>(a, s);
-            else if (pieces <= 32) launch_pna_bwd_rows<false, 32>(a, s);
-            else launch_pna_bwd_rows<false, 64>(a, s);
+            if (pieces <= 16) launch_pna_bwd_rows<false, 16>(a, longest, s);
+            else if (pieces <= 32) launch_pna_bwd_rows<false, 32>(a, longest, s);
+            else launch_pna_bwd_rows<false, 64>(a, longest, s);
         }
         GAS_CHECK_HIP(hipGetLastError());
         // the mean's share: GX[u] = sum over the entries (v, u) of C0[v]
@@ -1248,6 +1250,8 @@ gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* r
         if (st != GAS_OK) return st;
         if (bf) hipLaunchKernelGGL(pna_bwd_winners_kernel<true>, dim3((unsigned)n_out), dim3(64), 0, s, a);
         else hipLaunchKernelGGL(pna_bwd_winners_kernel<false>, dim3((unsigned)n_out), dim3(64), 0, s, a);
+        GAS_CHECK_HIP(hipGetLastError());
+        if (plan_t->n_heavy == 0 && plan_t->threshold <= kLongWinners) return GAS_OK;     // no column is longer
         const size_t sums_bytes = (size_t)kLongWaves * F * 4;
         if (bf) hipLaunchKernelGGL(pna_bwd_winners_long_kernel<true>, dim3(long_row_blocks(n_out)), dim3(64 * kLongWaves), sums_bytes, s, a);
         else hipLaunchKernelGGL(pna_bwd_winners_long_kernel<false>, dim3(long_row_blocks(n_out)), dim3(64 * kLongWaves), sums_bytes, s, a);
@@ -1276,6 +1280,15 @@ gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* r
     return GAS_OK;
 }
 
+gas_status gas_pna_aggregate_bwd_blocks(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                        int64_t nnz, const int32_t* colptr, const int32_t* row, const int32_t* csc_pos,
+                                        int64_t n_out, const void* X, int64_t ldx, gas_dtype dt, int32_t F, float delta,
+                                        int32_t blocks, const void* G, int64_t ldg, void* GX, int64_t ldgx, void* Gadd,
+                                        int64_t ldga, void* workspace, int64_t workspace_bytes, void* stream) {
+    return gas_pna_aggregate_bwd_bounded(plan_t, rowptr, col, n_rows, 0x7FFFFFFF, nnz, colptr, row, csc_pos, n_out, X, ldx, dt, F, delta,
+                                         blocks, G, ldg, GX, ldgx, Gadd, ldga, workspace, workspace_bytes, stream);
+}
+
 int64_t gas_gat_aggregate_bwd_heads_workspace(int64_t n_rows, int64_t n_cols, int64_t nnz, int32_t F, int32_t heads) {
     if (n_rows < 0 || n_cols <= 0 || nnz < 0 || F <= 0 || heads <= 0) return 0;
     const int64_t H = heads < 4 ? heads : 4;               // heads taken together
@@ -1287,12 +1300,13 @@ int64_t gas_gat_aggregate_bwd_workspace(int64_t n_rows, int64_t n_cols, int64_t 
     return gas_gat_aggregate_bwd_heads_workspace(n_rows, n_cols, nnz, F, 1);
 }
 
-gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
-                                       const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
-                                       int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
-                                       int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
-                                       const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
-                                       void* workspace, int64_t workspace_bytes, void* stream) {
+gas_status gas_gat_aggregate_bwd_bounded(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                         int32_t longest, int32_t longest_col, const int32_t* colptr, const int32_t* row,
+                                         const int32_t* csc_pos, int64_t n_cols,
+                                         int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
+                                         int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
+                                         const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
+                                         void* workspace, int64_t workspace_bytes, void* stream) {
     if (!valid_dtype(dt)) return fail(GAS_ERR_DTYPE, "gas_gat_aggregate_bwd: unknown dtype %d", (int)dt);
     GAS_REQUIRE(n_rows >= 0 && n_cols >= n_rows && n_out >= 0 && n_out <= n_cols && nnz >= 0 && F > 0 && heads > 0 &&
                 F <= 64 * kMaxPerLane, "gas_gat_aggregate_bwd: n_rows=%lld n_cols=%lld n_out=%lld nnz=%lld F=%d (F <= %d) heads=%d",
@@ -1337,15 +1351,16 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
     for (int32_t h = 0; h < heads; h += H) {
         if (vec) {
             const bool planned = H == 1 && plan_t && n_out > 0;
-            if (bf) launch_gat_bwd_heads<true>(a, H, !planned, s);
-            else launch_gat_bwd_heads<false>(a, H, !planned, s);
+            if (bf) launch_gat_bwd_heads<true>(a, H, !planned, longest > kLongRow, longest_col > kLongRow, s);
+            else launch_gat_bwd_heads<false>(a, H, !planned, longest > kLongRow, longest_col > kLongRow, s);
             if (planned) {
                 if (nnz > 0)
                     hipLaunchKernelGGL(permute_entries_kernel, dim3((unsigned)((nnz + 255) / 256)), dim3(256), 0, s, a.pair,
                                        csc_pos, nnz, val_t, dt_t);
                 hipLaunchKernelGGL(column_totals_kernel, dim3((unsigned)((n_cols + 255) / 256)), dim3(256), 0, s, colptr, dt_t,
                                    n_cols, a.tsum);
-                hipLaunchKernelGGL(column_totals_long_kernel, dim3(long_row_blocks(n_cols)), dim3(64 * kLongWaves), 0, s, colptr,
+                if (longest_col > kLongColumn)
+                    hipLaunchKernelGGL(column_totals_long_kernel, dim3(long_row_blocks(n_cols)), dim3(64 * kLongWaves), 0, s, colptr,
                                    dt_t, n_cols, a.tsum);
                 GAS_CHECK_HIP(hipGetLastError());
                 // GP[u] = sum over the entries (v, u) of alpha GZ[v]: the backward aggregation with the attention weights
@@ -1377,6 +1392,17 @@ gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* ro
         if (a.GP) a.GP += step;
     }
     return GAS_OK;
+}
+
+gas_status gas_gat_aggregate_bwd_heads(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,
+                                       const int32_t* colptr, const int32_t* row, const int32_t* csc_pos, int64_t n_cols,
+                                       int64_t n_out, int64_t nnz, const void* P, int64_t ldp, gas_dtype dt, int32_t F,
+                                       int32_t heads, const void* a_dst, const void* a_src, float negative_slope,
+                                       const void* GZ, int64_t ldgz, void* GP, int64_t ldgp, float* Ga_dst, float* Ga_src,
+                                       void* workspace, int64_t workspace_bytes, void* stream) {
+    return gas_gat_aggregate_bwd_bounded(plan_t, rowptr, col, n_rows, 0x7FFFFFFF, 0x7FFFFFFF, colptr, row, csc_pos, n_cols, n_out, nnz,
+                                         P, ldp, dt, F, heads, a_dst, a_src, negative_slope, GZ, ldgz, GP, ldgp, Ga_dst, Ga_src,
+                                         workspace, workspace_bytes, stream);
 }
 
 gas_status gas_gat_aggregate_bwd(const gas_plan* plan_t, const int32_t* rowptr, const int32_t* col, int64_t n_rows,

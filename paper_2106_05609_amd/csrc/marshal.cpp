@@ -178,10 +178,10 @@ PyMethodDef methods[] = {
     GAS_CALL(gas_linear_bwd_input_add), GAS_CALL(gas_linear_bwd_weight), GAS_CALL(gas_linear_bwd_weight_workspace),
     GAS_CALL(gas_linear_bwd_weights), GAS_CALL(gas_linear_bwd_weights_workspace), GAS_CALL(gas_softmax_xent),
     GAS_CALL(gas_sgd_step), GAS_CALL(gas_sgd_steps), GAS_CALL(gas_axpy), GAS_CALL(gas_row_dot),
-    GAS_CALL(gas_pna_aggregate_blocks), GAS_CALL(gas_pna_aggregate_bwd_blocks), GAS_CALL(gas_pna_aggregate_bwd_workspace),
+    GAS_CALL(gas_pna_aggregate_own), GAS_CALL(gas_pna_aggregate_bwd_bounded), GAS_CALL(gas_pna_aggregate_bwd_workspace),
     GAS_CALL(gas_pna_groups), GAS_CALL(gas_pna_groups_workspace), GAS_CALL(gas_pna_linear), GAS_CALL(gas_pna_linear_workspace),
     GAS_CALL(gas_pna_linear_bwd_input), GAS_CALL(gas_pna_linear_bwd_weight), GAS_CALL(gas_pna_linear_bwd_weight_workspace),
-    GAS_CALL(gas_gat_aggregate_heads), GAS_CALL(gas_gat_aggregate_bwd_heads), GAS_CALL(gas_gat_aggregate_bwd_heads_workspace),
+    GAS_CALL(gas_gat_aggregate_push), GAS_CALL(gas_gat_aggregate_bwd_bounded), GAS_CALL(gas_gat_aggregate_bwd_heads_workspace),
     {nullptr, nullptr, 0, nullptr}};
 
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_marshal", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

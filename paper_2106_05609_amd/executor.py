@@ -104,10 +104,16 @@ class BatchGraph:
         """Plan of the backward aggregation over ALL columns, halo included (GCNII's first layer: the gradient of
         the projected features of every node of V_b); built on first use, once per batch."""
         if self._plan_t_all is None:
-            longest = int((self.colptr[1:] - self.colptr[:-1]).max().item()) if self.nv > 0 else 0
+            self._max_col_all = int((self.colptr[1:] - self.colptr[:-1]).max().item()) if self.nv > 0 else 0
             self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row,
-                                                 options=plan_limits(self.nv, self.nnz, longest))
+                                                 options=plan_limits(self.nv, self.nnz, self._max_col_all))
         return self._plan_t_all
+
+    @property
+    def max_col_all(self):
+        """Entries of the longest of all columns, halo included."""
+        self.plan_t_all
+        return self._max_col_all
 
     def _once(self, name, build):
         """self.<name>, an array of this batch that `build` makes on first use, without a wait of the host: streams other than the
@@ -301,8 +307,8 @@ class _WeightGrads:
 
 
 def _pushes(do_push, table) -> bool:
-    """Whether a training pass of GCN, GCNII or PNA lets the transform store its rows to the history table as well: not to
-    host memory, which gas_push_host writes with few workgroups.  (The forward passes and GIN push from the transform
+    """Whether a training pass of GCN or GCNII, or a pass of PNA, lets the transform store its rows to the history table as well, and of
+    GAT the aggregation: not to host memory, which gas_push_host writes with few workgroups.  (The other forward passes and GIN push from the transform
     there too: the link bounds both, 20,000 rows of 128 floats 199 us in one and 205 us in two, 50,000 of 256 981 and 982.)"""
     return do_push and not isinstance(table, B.HostTable)
 
@@ -1011,7 +1017,7 @@ def _groups_of_layers(bg: BatchGraph, x, weights, gradients=True):
     return out
 
 
-def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None):
+def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None, longest=B.ANY_LENGTH, idx=None, hist=None):
     """One PNA layer (paper, operator appendix) for the in-batch rows: h'_v = W2 [h_v, (+)_w W1 [h_v, h_w]].
     x: mini-batch tensor [nv, F]; w1 [2F, F1] (rows 0..F-1 multiply the receiving node, rows F.. the neighbour),
     w2 [F + 9 F1, F_out].  The neighbour part of a message is computed once per node (gas_linear over all of
@@ -1025,11 +1031,13 @@ def pna_layer(x, nb, rowptr, col, w1, w2, delta, relu, y=None):
     q = torch.empty((nb, f1), dtype=dt, device=dev)
     B.gas_linear(x[:nb], w1[:f], q)
     cat = torch.empty((nb, f + 9 * f1), dtype=dt, device=dev)
-    B.gas_pull(x, None, cat[:, :f], base=0, n=nb)                 # h_v into the first F columns (a strided row copy)
-    B.gas_pna_aggregate(rowptr, col, p, cat[:, f:], delta, add=q)
+    B.gas_pna_aggregate(rowptr, col, p, cat[:, f:], delta, add=q, longest=longest, own=x, own_to=cat[:, :f])   # h_v into the first F columns
     if y is None:
         y = torch.empty((nb, w2.shape[1]), dtype=dt, device=dev)
-    B.gas_linear(cat, w2, y, relu=relu)
+    if idx is not None:
+        B.gas_linear_push(cat, w2, y, idx, hist, relu=relu)
+    else:
+        B.gas_linear(cat, w2, y, relu=relu)
     return y
 
 
@@ -1043,8 +1051,8 @@ def _pna_messages(bg: BatchGraph, x, w1, delta, blocks):
     q = torch.empty((nb, f1), dtype=dt, device=dev)
     B.gas_linear(x[:nb], w1[:f], q)
     cat = torch.empty((nb, f + blocks * f1), dtype=dt, device=dev)
-    B.gas_pull(x, None, cat[:, :f], base=0, n=nb)                 # h_v into the first F columns (a strided row copy)
-    B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q, blocks=blocks)
+    # h_v goes into the first F columns
+    B.gas_pna_aggregate(bg.rowptr, bg.col, p, cat[:, f:], delta, add=q, blocks=blocks, longest=bg.max_row, own=x, own_to=cat[:, :f])
     return p, cat
 
 
@@ -1062,18 +1070,16 @@ def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push
         last = l == L
         x_next = torch.empty((nb if last else nv, w2.shape[1]), dtype=dt, device=dev)
         groups = by_degree[l - 1][1]
+        ids, hist = (bg.n_id[:nb], histories[l - 1]) if not last and _pushes(do_push, histories[l - 1]) else (None, None)
         if groups is None:
-            y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb])
+            y = pna_layer(x, nb, bg.rowptr, bg.col, w1, w2, delta, relu=not last, y=x_next[:nb], longest=bg.max_row, idx=ids, hist=hist)
         else:
             y, f, f1 = x_next[:nb], x.shape[1], w1.shape[1]
             cat = _pna_messages(bg, x, w1, delta, 3)[1]
-            B.gas_pna_linear(groups, bg.max_row, cat, w2, f1, delta, y, relu=not last)
+            B.gas_pna_linear(groups, bg.max_row, cat, w2, f1, delta, y, relu=not last, idx=ids, hist=hist)
         if last:
             break
-        if do_push:
-            B.gas_push(y, bg.n_id[:nb], histories[l - 1])
-        if nv > nb:
-            B.gas_pull(histories[l - 1], bg.n_id[nb:], x_next[nb:])
+        _next_input(x_next, bg, histories[l - 1], do_push and hist is None)
         x = x_next
     return y
 
@@ -1099,13 +1105,12 @@ def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope
         y = x_next[:nb]
         if w.shape[1] % heads:
             raise ValueError("gat_forward_batch: the layer width is not a multiple of the number of heads")
-        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads)
+        ids, hist = (bg.n_id[:nb], histories[l - 1]) if not last and _pushes(do_push, histories[l - 1]) else (None, None)
+        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads, longest=bg.max_row,
+                            idx=ids, hist=hist)
         if last:
             break
-        if do_push:
-            B.gas_push(y, bg.n_id[:nb], histories[l - 1])
-        if nv > nb:
-            B.gas_pull(histories[l - 1], bg.n_id[nb:], x_next[nb:])
+        _next_input(x_next, bg, histories[l - 1], do_push and hist is None)
         x = x_next
     return y
 
@@ -1171,7 +1176,7 @@ def pna_train_batch(weights, delta, bg: BatchGraph, x_feat, histories, grad_out,
         gp = torch.empty((nv, f1), dtype=dt, device=dev)
         gq = torch.empty((nb, f1), dtype=dt, device=dev)
         B.gas_pna_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, gcat[:, f:], gp, delta, gadd=gq,
-                                plan_t=bg.plan_t_all, blocks=9 if groups is None else 3)
+                                plan_t=bg.plan_t_all, blocks=9 if groups is None else 3, longest=bg.max_row)
         dw1 = torch.empty((2 * f, f1), dtype=torch.float32, device=dev)
         wg.add(x[:nb], gq, dw1[:f])
         wg.add(x, gp, dw1[f:])
@@ -1210,11 +1215,13 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         y = x_next[:nb]
         if w.shape[1] % heads:
             raise ValueError("gat_train_batch: the layer width is not a multiple of the number of heads")
-        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads)
+        ids, hist = (bg.n_id[:nb], histories[l - 1]) if not last and _pushes(do_push, histories[l - 1]) else (None, None)
+        B.gas_gat_aggregate(bg.rowptr, bg.col, p, a_dst, a_src, y, negative_slope, relu=not last, heads=heads, longest=bg.max_row,
+                            idx=ids, hist=hist)
         kept.append((x, p, y))
         if last:
             break
-        _next_input(x_next, bg, histories[l - 1], do_push)
+        _next_input(x_next, bg, histories[l - 1], do_push and hist is None)
         x = x_next
     grads, wg = {}, _WeightGrads()
     g = grad_out(y) if callable(grad_out) else grad_out
@@ -1225,7 +1232,7 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         gd = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         gs = torch.empty(w.shape[1], dtype=torch.float32, device=dev)
         B.gas_gat_aggregate_bwd(bg.rowptr, bg.col, bg.colptr, bg.row, bg.csc_pos, p, a_dst, a_src, g, gp, gd, gs,
-                                negative_slope, plan_t=bg.plan_t_all, heads=heads)
+                                negative_slope, plan_t=bg.plan_t_all, heads=heads, longest=bg.max_row, longest_col=bg.max_col_all)
         grads[l - 1] = (wg.add(x, gp), gd, gs)
         if l == 1:
             break
