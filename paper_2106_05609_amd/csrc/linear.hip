@@ -271,23 +271,23 @@ __global__ __launch_bounds__(256, WPS) void linear_split_kernel(LinArgs a) {
     store_tile<TM, TN>(a, m0 + wm0, n0 + wn0, li, lh, acc);
 }
 
-// The same tile by KG groups of four wavefronts that take the steps of 32 k in turn: where there is at most one tile for a
+// The same tile by KG groups of WM x WN wavefronts that take the steps of 32 k in turn: where there is at most one tile for a
 // compute unit, one wavefront on a SIMD issues a vector instruction every eight cycles, two or more every four to five, and
 // its chains of dependent products and LDS reads leave the unit idle.  The sum over the groups goes through LDS.
-template <int BM, int BN, bool TRANS, int KG>
-__global__ __launch_bounds__(256 * KG) void linear_split_groups_kernel(LinArgs a) {
-    using G = SplitGemm<BM, BN, 2, 2, 2, true, TRANS, KG>;
+template <int BM, int BN, int WM, int WN, bool TRANS, int KG>
+__global__ __launch_bounds__(64 * WM * WN * KG) void linear_split_groups_kernel(LinArgs a) {
+    using G = SplitGemm<BM, BN, WM, WN, 2, true, TRANS, KG>;
     constexpr int TM = G::TM, TN = G::TN;
     extern __shared__ __attribute__((aligned(16))) char smem[];
     const float* Z = reinterpret_cast<const float*>(a.Z);
     const float* W = reinterpret_cast<const float*>(a.W);
     const int lane = threadIdx.x & 63, li = lane & 31, lh = lane >> 5;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave >> 2;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), group = wave / (WM * WN);
     const unsigned gn = (a.N + BN - 1) / BN, of_xcd = blockIdx.x / 8;
     const int64_t m0 = ((int64_t)(of_xcd / gn) * 8 + blockIdx.x % 8) * BM;
     if (m0 >= a.M) return;                             // the grid is padded to a multiple of eight row tiles
     const int n0 = (int)(of_xcd % gn) * BN;
-    const int wm0 = ((wave >> 1) & 1) * (BM / 2), wn0 = (wave & 1) * (BN / 2);
+    const int wm0 = wave / WN % WM * (BM / WM), wn0 = wave % WN * (BN / WN);
     const int64_t ldw = TRANS ? a.K : a.N;
     G g;
     f32x16 acc[TM][TN];
@@ -1939,14 +1939,14 @@ gas_status launch_split(const LinArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
-template <int BM, int BN, int KG, bool TRANS>
+template <int BM, int BN, int WM, int WN, int KG, bool TRANS>
 gas_status launch_groups(const LinArgs& a, hipStream_t s) {
-    constexpr int smem = SplitGemm<BM, BN, 2, 2, 2, true, TRANS, KG>::kGroupsLdsBytes;
-    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_split_groups_kernel<BM, BN, TRANS, KG>),
+    constexpr int smem = SplitGemm<BM, BN, WM, WN, 2, true, TRANS, KG>::kGroupsLdsBytes;
+    static const hipError_t attr = hipFuncSetAttribute(reinterpret_cast<const void*>(linear_split_groups_kernel<BM, BN, WM, WN, TRANS, KG>),
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, smem);
     GAS_CHECK_HIP(attr);
     const int64_t gm = ((a.M + BM - 1) / BM + 7) / 8 * 8, gn = (a.N + BN - 1) / BN;
-    hipLaunchKernelGGL((linear_split_groups_kernel<BM, BN, TRANS, KG>), dim3((unsigned)(gm * gn)), dim3(256 * KG), smem, s, a);
+    hipLaunchKernelGGL((linear_split_groups_kernel<BM, BN, WM, WN, TRANS, KG>), dim3((unsigned)(gm * gn)), dim3(64 * WM * WN * KG), smem, s, a);
     GAS_CHECK_HIP(hipGetLastError());
     return GAS_OK;
 }
@@ -2133,8 +2133,14 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
         // input the same call ends 0.8 us earlier, 2,000 x 160 x 128 0.6, 512 x 80 x 64 0.1: that is how passes call it.  A
         // workgroup fills a unit, and the column tiles of a row tile share one of the eight XCDs of 32: at 33 tiles on an
         // XCD one of them waits for a second round (5,120 x 192 x 192, 30 on an XCD: 9.4 and 9.1; 5,400 rows, 33: 11.2 and 16.5).
-        if (F_in > 64 && ((n_rows + 63) / 64 + 7) / 8 * ((F_out + 63) / 64) <= 32)
-            return trans_w ? launch_groups<64, 64, 4, true>(a, s) : launch_groups<64, 64, 4, false>(a, s);
+        // Half as many rows a tile and twice the groups as long as that is one round too: most units are idle then, and each group has
+        // half the steps to split (500 x 256 x 256: 9.1 -> 7.5 us, 229 x 2,240 x 224 46.9 -> 31.3, 2,000 x 832 x 128 19.9 -> 14.6;
+        // steps of 16 k 38.4, two steps' loads in flight 34; at 64 tiles of 32 x 64 on an XCD, 4,000 x 256 x 256, 12.8 for 9.1).
+        auto on_xcd = [&](int rows) { return ((n_rows + rows - 1) / rows + 7) / 8 * ((F_out + 63) / 64); };
+        if (F_in > 96 && on_xcd(32) <= 32)
+            return trans_w ? launch_groups<32, 64, 1, 2, 8, true>(a, s) : launch_groups<32, 64, 1, 2, 8, false>(a, s);
+        if (F_in > 64 && on_xcd(64) <= 32)
+            return trans_w ? launch_groups<64, 64, 2, 2, 4, true>(a, s) : launch_groups<64, 64, 2, 2, 4, false>(a, s);
         return launch_split<64, 64, 2, 4>(a, s);
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;

@@ -281,7 +281,7 @@ struct SplitGemm {
     }
 
     // The same by KG groups of T threads, each with LDS of its own: group `group` takes every KG-th step, and group 0 ends up with
-    // the sum over the groups, added in their order (the other groups' acc is of no use afterwards).
+    // the sum over the groups, added pair by pair (the other groups' acc is of no use afterwards).
     template <bool SCALED>
     __device__ __forceinline__ void pass_groups(const float* A, int64_t lda, int64_t a0, int64_t a_end, const float* B, int64_t ldb,
                                                 int64_t b0, int64_t b_end, int64_t q_end, uint16_t* lds, uint32_t* flag, int group,
@@ -353,17 +353,23 @@ struct SplitGemm {
         __syncthreads();
         if (group == 0) {
 #pragma unroll
-            for (int g = 1; g < KG; ++g)
+            for (int i = 0; i < TM; ++i)
 #pragma unroll
-                for (int i = 0; i < TM; ++i)
+                for (int j = 0; j < TN; ++j)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j)
+                    for (int r = 0; r < 4; ++r) {
+                        f32x4 part[KG];
+                        part[0] = f32x4{acc[i][j][4 * r], acc[i][j][4 * r + 1], acc[i][j][4 * r + 2], acc[i][j][4 * r + 3]};
 #pragma unroll
-                        for (int r = 0; r < 4; ++r) {
-                            const f32x4 v = *reinterpret_cast<const f32x4*>(sums + ((((g - 1) * kBlocks + i * TN + j) * 4 + r) * T + t) * 4);
+                        for (int g = 1; g < KG; ++g)
+                            part[g] = *reinterpret_cast<const f32x4*>(sums + ((((g - 1) * kBlocks + i * TN + j) * 4 + r) * T + t) * 4);
 #pragma unroll
-                            for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] += v[e];
-                        }
+                        for (int d = 1; d < KG; d *= 2)           // pair by pair: in a row they lost what shorter sums gain
+#pragma unroll
+                            for (int g = 0; g + d < KG; g += 2 * d) part[g] += part[g + d];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[i][j][4 * r + e] = part[0][e];
+                    }
             if constexpr (SCALED) {
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
