@@ -496,7 +496,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // A team of 16 lanes owns one row's slice of up to 16 P pieces of 16 bytes (P pieces a lane); it reads 32 indices with two
 // loads, the lane that read an index forms the row's address and the team takes it by data-parallel moves.  Four rows of a
 // wavefront walk their chain of dependent loads (row pointers, indices, rows) together, where the kernels of a wavefront a row
-// walk one.  A row's entries are folded in the stored order: the sums are the wave-per-row kernel's, bit for bit.
+// walk one.  A row's entries are folded in the stored order (S: entry k into sum k % S): from 32 units on the sums are the
+// wave-per-row kernel's, bit for bit.
 // Bounded by that chain and, with inputs that are not in the caches, by the misses.  us, a wavefront a row -> slices, inputs
 // that rotate through more than the Infinity Cache holds, 50,000 clustered rows of 11 entries: 47 floats 24 -> 16, 64 28 -> 16,
 // 136 50 -> 33, 184 53 -> 39, 248 61 -> 45, 1,433 429 -> 370, 128 bf16 30 -> 15, 136 36 -> 26; 150,000 power-law rows of 69, 64
@@ -511,7 +512,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // registers: a wavefront less on a SIMD).
 constexpr int kSliceRows = 16;      // rows of a workgroup (four wavefronts of four teams)
 
-template <int P, bool EVEN, bool XBF, bool ZBF, bool MASK>
+template <int P, bool EVEN, int S, bool XBF, bool ZBF, bool MASK>
 __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices, int width) {
     constexpr int G = 16, E = Unit<XBF>::E, EB = XBF ? 2 : 4, U = P == 1 ? 8 : 4;
     typedef std::conditional_t<XBF, u32x4_at2, u32x4_at4> Piece;
@@ -563,11 +564,13 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
     if (use_own) piece(own_row(a, row), own);
     if (a.R) piece(a.R + row * a.r_stride, res);
     if constexpr (MASK) piece(a.Y + row * a.y_stride, act);
-    float acc[P][E];
+    float acc[S][P][E];
 #pragma unroll
-    for (int p = 0; p < P; ++p)
+    for (int t = 0; t < S; ++t)
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[p][i] = 0.f;
+        for (int p = 0; p < P; ++p)
+#pragma unroll
+            for (int i = 0; i < E; ++i) acc[t][p][i] = 0.f;
     for (int k0 = b; k0 < e; k0 += 2 * G) {
         const int cnt = e - k0;
         int lo[2], hi[2], wt[2];
@@ -600,17 +603,25 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
                     const float f = __int_as_float(team_lane<G>(wt[h], q + u));
                     if (G * h + q + u < cnt) {
 #pragma unroll
-                        for (int p = 0; p < P; ++p) Unit<XBF>::fma(acc[p], f, x[u][p]);
+                        for (int p = 0; p < P; ++p) Unit<XBF>::fma(acc[u % S][p], f, x[u][p]);
                     }
                 }
             }
     }
 #pragma unroll
+    for (int d = 1; d < S; d *= 2)
+#pragma unroll
+        for (int t = 0; t + d < S; t += 2 * d)
+#pragma unroll
+            for (int p = 0; p < P; ++p)
+#pragma unroll
+                for (int i = 0; i < E; ++i) acc[t][p][i] += acc[t + d][p][i];
+#pragma unroll
     for (int p = 0; p < P; ++p) {
         if (!mine[p]) continue;
         float z[E];
 #pragma unroll
-        for (int i = 0; i < E; ++i) z[i] = a.s_agg * acc[p][i];
+        for (int i = 0; i < E; ++i) z[i] = a.s_agg * acc[0][p][i];
         if (use_own) Unit<XBF>::fma(z, a.diag, own[p]);
         if (a.R) Unit<XBF>::fma(z, a.s_res, res[p]);
         if constexpr (MASK) {
@@ -783,12 +794,20 @@ gas_status launch_slices(const SpmmArgs& a, hipStream_t s) {
     const int64_t blocks = a.in_turn ? jobs : 8 * ((jobs + 7) / 8);
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
     const dim3 grid((unsigned)blocks), block(256);
+    // Rows narrower than 32 units: four, or two, partial sums a row, as many as where a wavefront's teams share such a row (error
+    // against 64 bits, 21 entries of 104 floats: 6.7e-8, in one sum 8.4e-8).
+    auto launch = [&](auto split) {
+        constexpr int S = decltype(split)::value;
+        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+        else hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+    };
     // whole slices need no masks: two pieces a lane 40 -> 39 us (adjoint 38 -> 37); one piece a lane has none, and three gain nothing
     if (P == 2 && a.units == slices * 16 * P && a.units * 16 == a.F * (XBF ? 2 : 4)) {
-        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<2, true, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
-        else hipLaunchKernelGGL((spmm_slices_kernel<2, true, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
-    } else if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, false, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
-    else hipLaunchKernelGGL((spmm_slices_kernel<P, false, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+        else hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+    } else if (P == 1 && a.units <= 16) launch(std::integral_constant<int, P == 1 ? 4 : 1>());
+    else if (P <= 2 && a.units < 32) launch(std::integral_constant<int, P <= 2 ? 2 : 1>());
+    else launch(std::integral_constant<int, 1>());
     return GAS_OK;
 }
 
