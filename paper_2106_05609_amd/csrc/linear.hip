@@ -2157,11 +2157,11 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     // 500 rows 256 -> 256 in 64 x 64 7.2 us (128 x 256, one wavefront a unit, 20.1), 1,024 inputs 19.8 and 31.5, 16,000 rows 11.2
     // and with the weights in place 16.9, 50,000 33.0 and 27.3; the masked input gradient, which starts sooner because its weights
     // take no turning, 6,000 rows 6.6 and 8.8, 16,000 9.7 and 9.6.  Up to 64 columns six wavefronts of eight would hold no
-    // weights: 50,000 rows 256 -> 64 11.2 and 21.6, 300,000 49 and 56.  Wider than the weights-stationary kernel takes: 128 x
+    // weights: 50,000 rows 256 -> 64 11.2 and 21.6, 300,000 49 and 56 (with a Push, a copy of 19 us after tiles, not).  Wider than the weights-stationary kernel takes: 128 x
     // 128 once small tiles fill the chip (100,000 rows 512 -> 256 98 and 89), but not transposed (90 and 98).
     const bool ws = F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
         (!mask || (aligned16(mask) && ldmask % 8 == 0)) && ldz < (1 << 24) && ldy < (1 << 24) && ldmask < (1 << 24);
-    const bool small = F_out <= 64 || (!ws && trans_w) || (n_rows + 63) / 64 * ((F_out + 63) / 64) <= (trans_w ? 512 : 1024);
+    const bool small = (F_out <= 64 && !(ws && push.idx)) || (!ws && trans_w) || (n_rows + 63) / 64 * ((F_out + 63) / 64) <= (trans_w ? 512 : 1024);
     if (ws && !small) {
         const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
