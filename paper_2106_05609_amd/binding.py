@@ -26,7 +26,7 @@ EXPORTS = [
     "gas_pna_linear", "gas_pna_linear_workspace", "gas_pna_linear_bwd_input", "gas_pna_linear_bwd_weight",
     "gas_pna_linear_bwd_weight_workspace", "gas_gat_aggregate", "gas_gat_aggregate_heads", "gas_pna_aggregate_bwd", "gas_gat_aggregate_bwd",
     "gas_gat_aggregate_bwd_heads", "gas_pna_aggregate_bwd_workspace", "gas_gat_aggregate_bwd_workspace",
-    "gas_gat_aggregate_bwd_heads_workspace", "gas_gat_aggregate_push", "gas_pna_aggregate_own", "gas_pna_aggregate_bwd_bounded",
+    "gas_gat_aggregate_bwd_heads_workspace", "gas_linear_in_order", "gas_gat_aggregate_push", "gas_pna_aggregate_own", "gas_pna_aggregate_bwd_bounded",
     "gas_gat_aggregate_bwd_bounded",
     "gas_disk_open", "gas_disk_close", "gas_disk_pull", "gas_disk_push", "gas_disk_wait", "gas_disk_read_rows",
     "gas_disk_write_rows", "gas_disk_sync",
@@ -73,7 +73,7 @@ _SIGNATURES = dict(
     gas_plan_describe="pp", gas_plan_copy_lists="ppppp", gas_spmm="ppppfpqiifpqfpqip",
     gas_spmm_hist="ppppfpqpqqiifpqfpqip", gas_spmm_table="ppppfppqqiifpqip", gas_fuse_sources="pqqppp", gas_spmm_t="ppppffqpqiipqip",
     gas_spmm_t_relu="ppppffqpqiipqpqp", gas_linear_bwd_input_add="pqqipiiffpqpqfpqpqp", gas_sgd_steps="ippipffp",
-    gas_linear="pqqipipiffipqp", gas_mlp2="pqqipippipiipqp", gas_linear_push="pqqipipiffipqppqqp",
+    gas_linear="pqqipipiffipqp", gas_linear_in_order="pqqipiipqp", gas_mlp2="pqqipippipiipqp", gas_linear_push="pqqipipiffipqppqqp",
     gas_mlp2_push="pqqipippipiipqppqqp", gas_mlp2_keep="pqqipippipiipqpqppqqp",
     gas_spmm_linear="pppqpqpqqiiffpqfpipffipqpqppqqp", gas_relu_bwd="pqpqqiipqp", gas_linear_bwd_input="pqqipiiffpqpqp",
     gas_spmm_t_relu_linear="pppqpqiifpqpqpifffpqpqp",
@@ -348,6 +348,15 @@ def gas_linear(z, w, y, bias=None, c_identity=0.0, c_weight=1.0, relu=False):
     if dtw != dt or dty != dt or w_in != f_in or ny != n or f_out != w_out:
         raise ValueError("gas_linear: shapes or dtypes do not match")
     _check(_calls().gas_linear(zp, ldz, n, f_in, wp, f_out, _ptr(bias), dt, c_identity, c_weight, int(relu), yp, ldy, _stream()))
+
+
+def gas_linear_in_order(z, w, y):
+    """y = z @ w, every sum in the order of k where the rows and widths take no 16-byte pieces (bf16)."""
+    zp, ldz, n, f_in, dt = _size(z)
+    yp, ldy, ny, f_out, dty = _size(y)
+    if ny != n or dty != dt or w.dtype != z.dtype or w.shape != (f_in, f_out):
+        raise ValueError("gas_linear_in_order: shapes or dtypes do not match")
+    _check(_calls().gas_linear_in_order(zp, ldz, n, f_in, _ptr(w), f_out, dt, yp, ldy, _stream()))
 
 
 def gas_mlp2(z, w1, w2, y, b1=None, b2=None, relu_out=False):

@@ -172,7 +172,7 @@ PyMethodDef methods[] = {
     {"set_slow", set_slow, METH_VARARGS, nullptr},
     GAS_CALL(gas_pull), GAS_CALL(gas_push), GAS_CALL(gas_pull_host), GAS_CALL(gas_push_host), GAS_CALL(gas_gcn_norm),
     GAS_CALL(gas_spmm), GAS_CALL(gas_spmm_hist), GAS_CALL(gas_spmm_table), GAS_CALL(gas_fuse_sources), GAS_CALL(gas_spmm_t),
-    GAS_CALL(gas_spmm_t_relu), GAS_CALL(gas_linear), GAS_CALL(gas_linear_push), GAS_CALL(gas_mlp2), GAS_CALL(gas_mlp2_push),
+    GAS_CALL(gas_spmm_t_relu), GAS_CALL(gas_linear), GAS_CALL(gas_linear_in_order), GAS_CALL(gas_linear_push), GAS_CALL(gas_mlp2), GAS_CALL(gas_mlp2_push),
     GAS_CALL(gas_mlp2_keep), GAS_CALL(gas_spmm_linear), GAS_CALL(gas_spmm_t_relu_linear), GAS_CALL(gas_spmm_linear_layers),
     GAS_CALL(gas_spmm_t_relu_linear_layers), GAS_CALL(gas_relu_bwd), GAS_CALL(gas_linear_bwd_input),
     GAS_CALL(gas_linear_bwd_input_add), GAS_CALL(gas_linear_bwd_weight), GAS_CALL(gas_linear_bwd_weight_workspace),

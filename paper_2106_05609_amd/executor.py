@@ -1210,7 +1210,9 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         w, a_dst, a_src = weights[l - 1]
         last = l == L
         p = torch.empty((nv, w.shape[1]), dtype=dt, device=dev)
-        B.gas_linear(x, w, p)
+        # The gradients of the attention vectors are sums that cancel: another order of the sums in p moves them by 1e-2 of
+        # their norm in bf16.  Odd widths keep the order that they have had.
+        B.gas_linear_in_order(x, w, p)
         x_next = torch.empty((nb if last else nv, w.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
         if w.shape[1] % heads:

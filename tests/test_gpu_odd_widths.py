@@ -139,3 +139,22 @@ def test_bf16_mlp_and_masks_of_odd_widths(m, k, h, n):
     want, size = want * (mask > 0), size * (mask > 0)
     bound = 2.0 ** -8 * want.abs() + (h + 2) * 2.0 ** -24 * size * (1 + 2.0 ** -8)
     assert bool(((gz[:, :k].double() - want).abs() <= bound).all()) and bool((gz[:, k] == 7.0).all())
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("m,k,n", [(300, 81, 256), (129, 745, 47), (70, 64, 64), (1, 1, 1)])
+def test_products_in_order(m, k, n, dtype):
+    """Odd bf16 widths: the bits of fp32 fused multiply-adds in the order of k (exact products, so one rounding a step: formed here in
+    64 bits, rounded to fp32 each time); elsewhere gas_linear's."""
+    import paper_2106_05609_amd as gas
+    z, w = rng.normal_matrix(3, 870, m, k, dtype=dtype).cuda(), rng.normal_matrix(3, 871, k, n, dtype=dtype).cuda()
+    y, want = (torch.full((m, n), float("nan"), dtype=dtype, device="cuda") for _ in range(2))
+    gas.gas_linear_in_order(z, w, y)
+    if dtype == torch.float32 or (k % 8 == 0 and n % 8 == 0):
+        gas.gas_linear(z, w, want)
+        assert torch.equal(y, want)
+        return
+    s = torch.zeros(m, n, device="cuda")
+    for i in range(k):
+        s = (s.double() + z[:, i:i + 1].double() * w[i:i + 1].double()).float()
+    assert torch.equal(y, s.to(dtype))
