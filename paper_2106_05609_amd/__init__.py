@@ -1,5 +1,5 @@
 """MI355X-native GAS layer step: hand-written HIP kernels behind a C ABI
-(include/gas.h), with a ctypes binding of the same names."""
+(include/gas.h), with a binding of the same names."""
 from .binding import (  # noqa: F401
     F32, BF16, GasError, Plan, HostTable, DiskTable, lib, gas_version,
     gas_pull, gas_push, gas_gcn_norm, gas_plan_create, gas_plan_destroy, gas_validate_indices,
