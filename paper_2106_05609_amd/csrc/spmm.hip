@@ -496,8 +496,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // A team of 16 lanes owns one row's slice of up to 16 P pieces of 16 bytes (P pieces a lane); it reads 32 indices with two
 // loads, the lane that read an index forms the row's address and the team takes it by data-parallel moves.  Four rows of a
 // wavefront walk their chain of dependent loads (row pointers, indices, rows) together, where the kernels of a wavefront a row
-// walk one.  A row's entries are folded in the stored order (S: entry k into sum k % S): from 32 units on the sums are the
-// wave-per-row kernel's, bit for bit.
+// walk one.  A row's entries are folded in the stored order (S: entry k into sum k % S): above 32 units, and for 32 whole
+// ones, the sums are the wave-per-row kernel's, bit for bit; below they have as many parts (launch_slices).
 // Bounded by that chain and, with inputs that are not in the caches, by the misses.  us, a wavefront a row -> slices, inputs
 // that rotate through more than the Infinity Cache holds, 50,000 clustered rows of 11 entries: 47 floats 24 -> 16, 64 28 -> 16,
 // 136 50 -> 33, 184 53 -> 39, 248 61 -> 45, 1,433 429 -> 370, 128 bf16 30 -> 15, 136 36 -> 26; 150,000 power-law rows of 69, 64
@@ -512,11 +512,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4, 4))) voi
 // registers: a wavefront less on a SIMD).
 constexpr int kSliceRows = 16;      // rows of a workgroup (four wavefronts of four teams)
 
-template <int P, bool EVEN, int S, bool XBF, bool ZBF, bool MASK>
-__global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices, int width) {
+// H == 2 states its wavefronts because the compiler otherwise keeps all of a row's addresses in registers (fp32 242 instead of 83).
+template <int P, bool EVEN, int S, int H, bool XBF, bool ZBF, bool MASK>
+__global__ __launch_bounds__(256, H == 1 ? 1 : XBF ? 4 : 5) void spmm_slices_kernel(SpmmArgs a, int slices, int width) {
     constexpr int G = 16, E = Unit<XBF>::E, EB = XBF ? 2 : 4, U = P == 1 ? 8 : 4;
     typedef std::conditional_t<XBF, u32x4_at2, u32x4_at4> Piece;
-    const int lane = threadIdx.x & 63, j = lane % G;
+    const int j = threadIdx.x % G, half = H == 2 ? j / 8 : 0;             // H == 2: a row's entries in turn to the team's halves
     const uint32_t tiles = (uint32_t)((a.n_rows + kSliceRows - 1) / kSliceRows);
     const uint32_t xcd = blockIdx.x & 7, i = blockIdx.x >> 3;             // workgroups go to the eight XCDs in turn
     uint32_t slice, tile;
@@ -539,10 +540,11 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
     bool mine[P];
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        const int w = j + G * p, unit = slice * width + w;
+        const int w = (H == 2 ? j % 8 : j) + G * p, unit = slice * width + w;
         mine[p] = EVEN || (w < width && unit < a.units);
         off[p] = EVEN ? unit * 16 : unit_start<XBF>(a, min(unit, a.units - 1)) * EB;
     }
+    static_assert(H == 1 || (P == 1 && !EVEN), "halves are for rows of up to eight units");
     // entries k + j and k + G + j (past the row's end its last one: a valid address, never folded)
     int s[2];
     float v[2];
@@ -571,8 +573,12 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
         for (int p = 0; p < P; ++p)
 #pragma unroll
             for (int i = 0; i < E; ++i) acc[t][p][i] = 0.f;
+    auto entry = [](int v, int u) {
+        if constexpr (H == 2) return pair_lane(v, u);
+        else return team_lane<G>(v, u);
+    };
     for (int k0 = b; k0 < e; k0 += 2 * G) {
-        const int cnt = e - k0;
+        const int cnt = e - k0, left = cnt - half;
         int lo[2], hi[2], wt[2];
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -586,13 +592,13 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
 #pragma unroll
         for (int h = 0; h < 2; ++h)
 #pragma unroll
-            for (int q = 0; q < G; q += U) {
+            for (int q = 0; q < G; q += H * U) {
                 if (G * h + q >= cnt) break;
                 u32x4 x[U][P];
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const u32x2 r = {(uint32_t)team_lane<G>(lo[h], q + u), (uint32_t)team_lane<G>(hi[h], q + u)};
-                    if (G * h + q + u < cnt) {
+                    const u32x2 r = {(uint32_t)entry(lo[h], q + H * u), (uint32_t)entry(hi[h], q + H * u)};
+                    if (G * h + q + H * u < left) {
 #pragma unroll
                         for (int p = 0; p < P; ++p)
                             if (P == 1 || p + 1 < P || mine[p]) x[u][p] = load_global<Piece>(__builtin_bit_cast(uint64_t, r) + off[p]);
@@ -600,8 +606,8 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
                 }
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
-                    const float f = __int_as_float(team_lane<G>(wt[h], q + u));
-                    if (G * h + q + u < cnt) {
+                    const float f = __int_as_float(entry(wt[h], q + H * u));
+                    if (G * h + q + H * u < left) {
 #pragma unroll
                         for (int p = 0; p < P; ++p) Unit<XBF>::fma(acc[u % S][p], f, x[u][p]);
                     }
@@ -616,9 +622,12 @@ __global__ __launch_bounds__(256) void spmm_slices_kernel(SpmmArgs a, int slices
             for (int p = 0; p < P; ++p)
 #pragma unroll
                 for (int i = 0; i < E; ++i) acc[t][p][i] += acc[t + d][p][i];
+    if constexpr (H == 2)
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[0][0][i] += other_half(acc[0][0][i]);
 #pragma unroll
     for (int p = 0; p < P; ++p) {
-        if (!mine[p]) continue;
+        if (!mine[p] || half) continue;
         float z[E];
 #pragma unroll
         for (int i = 0; i < E; ++i) z[i] = a.s_agg * acc[0][p][i];
@@ -788,26 +797,36 @@ gas_status launch_rows(const SpmmArgs& a, hipStream_t s) {
 }
 
 template <int P, bool XBF, bool ZBF>
-gas_status launch_slices(const SpmmArgs& a, hipStream_t s) {
+gas_status launch_slices(const SpmmArgs& a, bool whole, hipStream_t s) {
     const int slices = (a.units + 16 * P - 1) / (16 * P), width = (a.units + slices - 1) / slices;
     const int64_t jobs = (a.n_rows + kSliceRows - 1) / kSliceRows * slices;
     const int64_t blocks = a.in_turn ? jobs : 8 * ((jobs + 7) / 8);
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
     const dim3 grid((unsigned)blocks), block(256);
-    // Rows narrower than 32 units: four, or two, partial sums a row, as many as where a wavefront's teams share such a row (error
-    // against 64 bits, 21 entries of 104 floats: 6.7e-8, in one sum 8.4e-8).
+    // As many partial sums a row as a wavefront's teams make of it in the other form: eight up to 8 units, four up to 16, two up to 32, one
+    // beyond and for 32 whole units, which a wavefront takes at once there.  Root mean square error against 64 bits, 21 entries: in one
+    // sum 8.5e-8, in two 6.7e-8; 60: in one 1.4e-7, in two 1.0e-7, in four 8.1e-8, in eight 7.0e-8.  Eight are four in each half of a team,
+    // which takes every other entry: no lane is idle at 8 units (us, eight in each lane and so: 200,000 clustered rows of 9 entries, 32 floats
+    // 44.5 -> 30.1, 64 bf16 62.6 -> 37.9; 257,000 power-law rows of 19 103.6 -> 86.0, 139.0 -> 103.1; four in each lane 37.1 to 111.5).
     auto launch = [&](auto split) {
-        constexpr int S = decltype(split)::value;
-        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
-        else hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+        constexpr int H = decltype(split)::value == 8 ? 2 : 1, S = decltype(split)::value / H;
+        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, H, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+        else hipLaunchKernelGGL((spmm_slices_kernel<P, false, S, H, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
     };
-    // whole slices need no masks: two pieces a lane 40 -> 39 us (adjoint 38 -> 37); one piece a lane has none, and three gain nothing
-    if (P == 2 && a.units == slices * 16 * P && a.units * 16 == a.F * (XBF ? 2 : 4)) {
-        if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
-        else hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
-    } else if (P == 1 && a.units <= 16) launch(std::integral_constant<int, P == 1 ? 4 : 1>());
-    else if (P <= 2 && a.units < 32) launch(std::integral_constant<int, P <= 2 ? 2 : 1>());
-    else launch(std::integral_constant<int, 1>());
+    const bool two = a.units < 32 || (a.units == 32 && !whole);
+    if constexpr (P == 1) {
+        if (a.units <= 8) launch(std::integral_constant<int, 8>());
+        else if (a.units <= 16) launch(std::integral_constant<int, 4>());
+        else if (two) launch(std::integral_constant<int, 2>());
+        else launch(std::integral_constant<int, 1>());
+    } else if constexpr (P == 2) {                        // from 17 units on
+        // whole slices need no masks: two pieces a lane 40 -> 39 us (adjoint 38 -> 37); one piece a lane has none, and three gain nothing
+        if (two) launch(std::integral_constant<int, 2>());
+        else if (a.units == slices * 32 && a.units * 16 == a.F * (XBF ? 2 : 4)) {
+            if (a.Y) hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, 1, XBF, ZBF, true>), grid, block, 0, s, a, slices, width);
+            else hipLaunchKernelGGL((spmm_slices_kernel<2, true, 1, 1, XBF, ZBF, false>), grid, block, 0, s, a, slices, width);
+        } else launch(std::integral_constant<int, 1>());
+    } else launch(std::integral_constant<int, 1>());
     return GAS_OK;
 }
 
@@ -823,9 +842,9 @@ gas_status dispatch_units(const SpmmArgs& a, bool whole, hipStream_t s) {
                            0, s, a);
     }
     gas_status st;
-    if (a.pieces == 1) st = launch_slices<1, XBF, ZBF>(a, s);
-    else if (a.pieces == 2) st = launch_slices<2, XBF, ZBF>(a, s);
-    else if (a.pieces == 3) st = launch_slices<3, XBF, ZBF>(a, s);
+    if (a.pieces == 1) st = launch_slices<1, XBF, ZBF>(a, whole, s);
+    else if (a.pieces == 2) st = launch_slices<2, XBF, ZBF>(a, whole, s);
+    else if (a.pieces == 3) st = launch_slices<3, XBF, ZBF>(a, whole, s);
     // rows of exactly 1 KiB or 512 B: grouped wave-per-row path
     else if (whole && a.group && u == 64) st = launch_rows<64, 1, 8, XBF, ZBF, 16>(a, s);
     else if (whole && a.group && u == 32) st = launch_rows<32, 1, 4, XBF, ZBF, 8>(a, s);

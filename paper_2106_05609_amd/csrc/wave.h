@@ -171,4 +171,19 @@ __device__ __forceinline__ int team_lane(int v, int u) {
     return v;
 }
 
+// Lane u of every 16 to the lower eight of them and lane u + 1 to the upper eight.  u is even and a constant wherever this is called.
+__device__ __forceinline__ int pair_lane(int v, int u) {
+#define GAS_CASE(n) \
+    case n: return __builtin_amdgcn_update_dpp(__builtin_amdgcn_mov_dpp(v, 0x150 + (n), 0xf, 0x3, true), v, 0x151 + (n), 0xf, 0xc, false);
+    switch (u) {
+        GAS_CASE(0) GAS_CASE(2) GAS_CASE(4) GAS_CASE(6) GAS_CASE(8) GAS_CASE(10) GAS_CASE(12) GAS_CASE(14)
+    }
+#undef GAS_CASE
+    return v;
+}
+// The value of the lane eight further in every 16, around its end (row_ror:8).
+__device__ __forceinline__ float other_half(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x128, 0xf, 0xf, true));
+}
+
 }  // namespace gas

@@ -117,3 +117,46 @@ def test_chunks_of_heavy_rows_are_added_in_batches(gas, dtype, F):
         z = torch.full((n, F), float("nan"), dtype=dtype, device="cuda")
         gas.gas_spmm(plan, ptr, col, val, x, z, diag=0.5)
         _check(z, ptr, val.double()[:, None] * x.double()[col.long()], 0.5 * x[:n].double(), 0.5 * x[:n].double().abs())
+
+
+def _in_parts(x, ptr, col, parts):
+    """The rows' sums in fp32, entry k of a row into sum k % parts, the sums added pair by pair; of eight, the even ones and the odd
+    ones each pair by pair first, which two halves of a team hold."""
+    ptr, col = ptr.cpu().numpy(), col.cpu().numpy()
+    lengths, n = np.diff(ptr), len(ptr) - 1
+    acc = np.zeros((parts, n, x.shape[1]), np.float32)
+    for k in range(int(lengths.max())):
+        rows = np.flatnonzero(lengths > k)
+        acc[k % parts, rows] += x[col[ptr[rows] + k]]
+    for d in (2, 4, 1) if parts == 8 else [d for d in (1, 2) if d < parts]:
+        for t in range(parts):
+            if not t & d and not t & (6 if d == 1 and parts == 8 else 0) and t + d < parts:
+                acc[t] += acc[t + d]
+    return acc[0]
+
+
+# widths, where their rows start (elements past 16 bytes) and the partial sums of a row: a narrow row has as many as a wavefront's
+# teams would make of it, and one of 32 units two unless it is whole and aligned, when a wavefront takes it at once
+@pytest.mark.parametrize("dtype,F,offset,parts", [
+    (torch.float32, 5, 0, 8), (torch.float32, 31, 1, 8), (torch.float32, 32, 0, 8), (torch.float32, 33, 0, 4), (torch.float32, 64, 0, 4),
+    (torch.float32, 65, 0, 2), (torch.float32, 104, 0, 2), (torch.float32, 125, 0, 2), (torch.float32, 126, 3, 2), (torch.float32, 127, 0, 2),
+    (torch.float32, 128, 1, 2), (torch.float32, 128, 0, 1), (torch.float32, 129, 0, 1), (torch.float32, 256, 0, 1),
+    (torch.bfloat16, 64, 0, 8), (torch.bfloat16, 128, 0, 4), (torch.bfloat16, 200, 0, 2), (torch.bfloat16, 249, 0, 2),
+    (torch.bfloat16, 255, 1, 2), (torch.bfloat16, 256, 1, 2), (torch.bfloat16, 256, 0, 1)])
+@pytest.mark.parametrize("n", [500, 8200])           # by one piece a lane; above 8,192 rows by two where that form exists
+def test_partial_sums_of_a_row(gas, n, dtype, F, offset, parts):
+    """Bit for bit the sums in that many parts: rows long enough that one part fewer, or one more, gives other bits."""
+    ptr, r = _pattern(n, 12, 5 * n + F, longest=200)
+    nnz = int(ptr[-1])
+    gen = torch.Generator(device="cuda").manual_seed(F + offset)
+    stride = F + offset if offset else (F + 7) // 8 * 8
+    x = torch.randn(n, stride, generator=gen, device="cuda").to(dtype)[:, offset:offset + F]
+    col = torch.from_numpy(r.integers(0, n, nnz).astype(np.int32)).cuda()
+    plan = gas.gas_plan_create(ptr, nnz, F, ind=col, options=dict(xcd_ranges=1))
+    assert plan.describe()["n_heavy"] == 0
+    z = torch.full((n, F), float("nan"), device="cuda")
+    gas.gas_spmm(plan, ptr, col, None, x, z)
+    host = x.float().cpu().numpy()
+    assert np.array_equal(z.cpu().numpy(), _in_parts(host, ptr, col, parts))
+    if parts > 1:
+        assert not np.array_equal(z.cpu().numpy(), _in_parts(host, ptr, col, parts // 2))
