@@ -252,9 +252,9 @@ GAS_API gas_status gas_linear(const void* Z, int64_t ldz, int64_t n_rows, int32_
                       const void* W, int32_t F_out, const void* bias, gas_dtype dt,
                       float c_identity, float c_weight, int relu,
                       void* Y, int64_t ldy, void* stream);
-/* Y = Z W; in bf16 with widths that are no multiple of eight, or rows that are not 16-byte aligned, every output is summed in the
- * order of k by one thread (slow), elsewhere as gas_linear does it.  For results that depend on the last bits of Y by cancellation
- * and have to repeat those of such a sum. */
+/* Y = Z W; in bf16 with widths that are no multiple of eight, or rows that are not 16-byte aligned, every output is one chain of fp32
+ * multiply-adds in the order of k (by the vector units: up to three times as long as gas_linear), and only there: elsewhere the call is
+ * gas_linear and sums in its order.  For results that depend on the last bits of Y by cancellation and have to repeat those of such a sum. */
 GAS_API gas_status gas_linear_in_order(const void* Z, int64_t ldz, int64_t n_rows, int32_t F_in, const void* W, int32_t F_out,
                                gas_dtype dt, void* Y, int64_t ldy, void* stream);
 

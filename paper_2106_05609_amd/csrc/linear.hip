@@ -2040,18 +2040,74 @@ gas_status launch_bf16(const LinArgs& a, hipStream_t s) {
     return GAS_OK;
 }
 
-// The same products, a thread an output, its sum in the order of k (gas_linear_in_order): 16 to 20 times as long where tiles fill the
-// chip (50,000 x 256 x 250 1,059 us, in tiles 31).
+// Y = Z W, every output a chain of fp32 multiply-adds in the order of k (gas_linear_in_order), for operands of any alignment and width.
+// Bound by the multiply-adds of the vector units, with few rows by the chain of a tile's steps.  Tiles of 16 R x 64, R x 4 outputs a
+// lane, steps of 32 k through LDS; the last step ends with k, so no term is added that is not there.  us, a thread an output with every
+// operand out of the caches and so: 50,000 x 256 x 250 880 and 99, 20,000 x 1,433 x 128 1,033 and 152, 2,340 x 745 x 256 158 and 46 (by
+// matrix instructions, in another order, 30, 50 and 16).
+template <int R>
 __global__ __launch_bounds__(256) void linear_bf16_in_order_kernel(LinArgs a) {
-    const int64_t idx = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= a.M * a.N) return;
-    const int64_t m = idx / a.N;
-    const int n = (int)(idx % a.N);
+    constexpr int TM = 16 * R, TN = 64, BK = 32, NA = TM * BK / 256, NB = TN * BK / 256;
+    typedef float f32xR __attribute__((ext_vector_type(R)));
+    __shared__ __attribute__((aligned(16))) float As[BK][TM + (R == 1 ? 1 : 4)];      // [k][row]
+    __shared__ __attribute__((aligned(16))) float Bs[BK][TN + 4];                     // [k][column]
     const uint16_t* Z = reinterpret_cast<const uint16_t*>(a.Z);
     const uint16_t* W = reinterpret_cast<const uint16_t*>(a.W);
-    float s = 0.f;
-    for (int k = 0; k < a.K; ++k) s = fmaf(bf16_val(Z, m * a.ldz + k), bf16_val(W, (int64_t)k * a.N + n), s);
-    reinterpret_cast<uint16_t*>(a.Y)[m * a.ldy + n] = (uint16_t)f32_to_bf16(s);
+    const int tid = threadIdx.x, tx = tid % 16, ty = tid / 16;
+    const unsigned tn = (unsigned)((a.N + TN - 1) / TN), of_xcd = blockIdx.x / 8;     // a row tile's column tiles follow each other on one XCD
+    const int64_t m0 = ((int64_t)(of_xcd / tn) * 8 + blockIdx.x % 8) * TM;
+    const int n0 = (int)(of_xcd % tn) * TN;
+    if (m0 >= a.M) return;
+    uint16_t za[NA], wb[NB];
+    auto fetch = [&](int k0) {                                      // rows, columns and k beyond the last repeat it
+#pragma unroll
+        for (int i = 0; i < NA; ++i) za[i] = Z[min(m0 + tid / BK + 256 / BK * i, a.M - 1) * a.ldz + min(k0 + tid % BK, a.K - 1)];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) wb[i] = W[(int64_t)min(k0 + tid / TN + 256 / TN * i, a.K - 1) * a.N + min(n0 + tid % TN, a.N - 1)];
+    };
+    float acc[R][4] = {};
+    auto step = [&](int k) {
+        const f32xR z = *reinterpret_cast<const f32xR*>(&As[k][R * ty]);
+        const f32x4 w = *reinterpret_cast<const f32x4*>(&Bs[k][4 * tx]);
+#pragma unroll
+        for (int i = 0; i < R; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(z[i], w[j], acc[i][j]);
+    };
+    fetch(0);
+    for (int k0 = 0; k0 < a.K; k0 += BK) {
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < NA; ++i) As[tid % BK][tid / BK + 256 / BK * i] = __uint_as_float((uint32_t)za[i] << 16);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) Bs[tid / TN + 256 / TN * i][tid % TN] = __uint_as_float((uint32_t)wb[i] << 16);
+        __syncthreads();
+        if (k0 + BK < a.K) {
+            fetch(k0 + BK);
+#pragma unroll 8
+            for (int k = 0; k < BK; ++k) step(k);
+        } else {
+            for (int k = 0; k < a.K - k0; ++k) step(k);
+        }
+    }
+    uint16_t* Y = reinterpret_cast<uint16_t*>(a.Y);
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int64_t m = m0 + R * ty + i;
+            const int n = n0 + 4 * tx + j;
+            if (m < a.M && n < a.N) Y[m * a.ldy + n] = (uint16_t)f32_to_bf16(acc[i][j]);
+        }
+}
+
+template <int R>
+gas_status launch_in_order(const LinArgs& a, hipStream_t s) {
+    const int64_t blocks = ((a.M + 16 * R - 1) / (16 * R) + 7) / 8 * 8 * ((a.N + 63) / 64);
+    if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_linear_in_order: problem too large for one launch");
+    hipLaunchKernelGGL(linear_bf16_in_order_kernel<R>, dim3((unsigned)blocks), dim3(256), 0, s, a);
+    GAS_CHECK_HIP(hipGetLastError());
+    return GAS_OK;
 }
 
 template <int BM, int BN>
@@ -2160,11 +2216,10 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     }
     const bool vec = aligned16(Z) && aligned16(W) && ldz % 8 == 0 && F_in % 8 == 0 && F_out % 8 == 0;
     if (!vec && in_order) {
-        const int64_t blocks = (n_rows * (int64_t)F_out + 255) / 256;
-        if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "%s: problem too large for one launch", who);
-        hipLaunchKernelGGL(linear_bf16_in_order_kernel, dim3((unsigned)blocks), dim3(256), 0, s, a);
-        GAS_CHECK_HIP(hipGetLastError());
-        return GAS_OK;
+        // Tiles of 64 rows once they fill the units twice, of 16 while one of 64 a unit would be too many: us by 16, 32 and 64 rows,
+        // 2,340 x 745 x 64 39, 48, 70; 2,340 x 745 x 256 46, 52, 71; 5,000 x 745 x 250 66, 62, 72; 20,000 x 1,433 x 128 209, 153, 152.
+        const int64_t tiles = (n_rows + 63) / 64 * ((F_out + 63) / 64);
+        return tiles <= 256 ? launch_in_order<1>(a, s) : tiles <= 512 ? launch_in_order<2>(a, s) : launch_in_order<4>(a, s);
     }
     if (!vec) {
         // Small tiles until their number fills the units several times (256 -> 250 in 64 x 64 and in larger ones: 5,000 rows

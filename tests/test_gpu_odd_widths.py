@@ -142,7 +142,8 @@ def test_bf16_mlp_and_masks_of_odd_widths(m, k, h, n):
 
 
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("m,k,n", [(300, 81, 256), (129, 745, 47), (70, 64, 64), (1, 1, 1)])
+@pytest.mark.parametrize("m,k,n", [(300, 81, 256), (129, 745, 47), (70, 64, 64), (1, 1, 1), (15, 31, 63), (17, 33, 64), (513, 32, 65),
+                                   (16385, 33, 15), (8200, 65, 130), (33000, 31, 1)])
 def test_products_in_order(m, k, n, dtype):
     """Odd bf16 widths: the bits of fp32 fused multiply-adds in the order of k (exact products, so one rounding a step: formed here in
     64 bits, rounded to fp32 each time); elsewhere gas_linear's."""
