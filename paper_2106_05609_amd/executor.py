@@ -1087,7 +1087,7 @@ def pna_forward_batch(weights, delta, bg: BatchGraph, x_feat, histories, do_push
 def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope=0.2, do_push=True, heads=1):
     """All layers of a GAT (paper, operator appendix) for one mini-batch in the order of Algorithm 1;
     weights[l] = (W, a_dst, a_src); bg: the batch subgraph with self-loops.  Per layer: P = X W for every row of
-    the mini-batch tensor (gas_linear), then scores, softmax and weighted sum in one pass (gas_gat_aggregate,
+    the mini-batch tensor (gas_linear_in_order), then scores, softmax and weighted sum in one pass (gas_gat_aggregate,
     ReLU in its epilogue on all layers but the last), push, pull.  heads > 1: the columns of W, a_dst and a_src are
     `heads` equal blocks, all taken by one gas_gat_aggregate call."""
     dev, dt = x_feat.device, x_feat.dtype
@@ -1100,7 +1100,7 @@ def gat_forward_batch(weights, bg: BatchGraph, x_feat, histories, negative_slope
         w, a_dst, a_src = weights[l - 1]
         last = l == L
         p = torch.empty((nv, w.shape[1]), dtype=dt, device=dev)
-        B.gas_linear(x, w, p)
+        B.gas_linear_in_order(x, w, p)                                # as in training: the same weights push the same rows
         x_next = torch.empty((nb if last else nv, w.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]
         if w.shape[1] % heads:
@@ -1211,7 +1211,7 @@ def gat_train_batch(weights, bg: BatchGraph, x_feat, histories, grad_out, negati
         last = l == L
         p = torch.empty((nv, w.shape[1]), dtype=dt, device=dev)
         # The gradients of the attention vectors are sums that cancel: another order of the sums in p moves them by 1e-2 of
-        # their norm in bf16.  Odd widths keep the order that they have had.
+        # their norm in bf16.  Odd widths keep the order of k, here and in inference.
         B.gas_linear_in_order(x, w, p)
         x_next = torch.empty((nb if last else nv, w.shape[1]), dtype=dt, device=dev)
         y = x_next[:nb]

@@ -159,3 +159,26 @@ def test_products_in_order(m, k, n, dtype):
     for i in range(k):
         s = (s.double() + z[:, i:i + 1].double() * w[i:i + 1].double()).float()
     assert torch.equal(y, s.to(dtype))
+
+
+@pytest.mark.parametrize("f_in,f,heads,stride", [(75, 64, 2, 75), (64, 36, 4, 64), (64, 64, 1, 67), (64, 64, 1, 64)])
+def test_gat_passes_agree_in_bf16(f_in, f, heads, stride):
+    """Inference and training of the same weights give the same rows and push the same rows, also where widths or rows take no
+    16-byte pieces."""
+    from gas_inputs import configs, batches
+    from paper_2106_05609_amd import executor
+    cfg = configs.config(1, 0.05)
+    g = configs.build_graph(cfg)
+    sg = batches.batch_subgraph(g, batches.split(g, cfg.blocks_per_batch, cfg.seed)[0], True)
+    d = lambda t: t.cuda()
+    bg = executor.BatchGraph(sg.nb, d(sg.n_id), d(sg.rowptr), d(sg.col), None, d(sg.colptr), d(sg.row), max_F=max(f_in, f),
+                             normalise=False, csc_pos=d(sg.csc_perm).int())
+    bf = torch.bfloat16
+    x = rng.normal_matrix(3, 880, g.n, stride, dtype=bf).cuda()[:, :f_in]
+    ws = [(rng.glorot_uniform(3, 881 + l, (f_in, f)[l], f, dtype=bf).cuda(), rng.normal(3, 884 + l, 0, f, dtype=bf).cuda() * 0.3,
+           rng.normal(3, 887 + l, 0, f, dtype=bf).cuda() * 0.3) for l in range(2)]
+    hist = rng.normal_matrix(3, 890, g.n, f, dtype=bf).cuda()
+    tables = [hist.clone(), hist.clone()]
+    y = executor.gat_forward_batch(ws, bg, x, [tables[0]], heads=heads)
+    trained, _, _ = executor.gat_train_batch(ws, bg, x, [tables[1]], torch.zeros_like(y), heads=heads)
+    assert torch.equal(y, trained) and torch.equal(tables[0], tables[1])
