@@ -514,7 +514,8 @@ GAS_API gas_status gas_pna_aggregate_blocks(const int32_t* rowptr, const int32_t
                              const void* add, int64_t ldadd, float delta, int32_t blocks,
                              void* out, int64_t ldout, void* stream);
 /* The same for a pattern none of whose rows has more than `longest` entries (the output of a longer one is undefined), with
- * own_to[v, 0:F_own] = own[v, 0:F_own] if own is given (the receiving nodes' own rows, to the columns before out). */
+ * own_to[v, 0:F_own] = own[v, 0:F_own] if own is given (the receiving nodes' own rows, to the columns before out).  own_to's rows
+ * must not share memory with X, add, own or out: they are stored while other rows are still being aggregated. */
 GAS_API gas_status gas_pna_aggregate_own(const int32_t* rowptr, const int32_t* col, int64_t n_rows, int32_t longest,
                              const void* X, int64_t ldx, gas_dtype dt, int32_t F,
                              const void* add, int64_t ldadd, float delta, int32_t blocks,
@@ -573,7 +574,8 @@ GAS_API gas_status gas_gat_aggregate_heads(const int32_t* rowptr, const int32_t*
                                    int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
                                    const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz, void* stream);
 /* The same for a pattern none of whose rows has more than `longest` entries (the output of a longer one is undefined); row v of Z
- * is also stored to push_hist[push_idx[v]] if push_idx is given (distinct, in range; heads * F columns). */
+ * is also stored to push_hist[push_idx[v]] if push_idx is given (distinct, in range; heads * F columns).  The history table must not
+ * share memory with P, Z or the attention vectors: its rows are stored while other rows are still being aggregated. */
 GAS_API gas_status gas_gat_aggregate_push(const int32_t* rowptr, const int32_t* col, int64_t n_rows, int32_t longest, const void* P,
                                   int64_t ldp, gas_dtype dt, int32_t F, int32_t heads, const void* a_dst,
                                   const void* a_src, float negative_slope, int relu, void* Z, int64_t ldz,

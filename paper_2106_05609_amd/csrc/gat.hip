@@ -308,7 +308,7 @@ extern "C" gas_status gas_gat_aggregate_push(const int32_t* rowptr, const int32_
     GAS_REQUIRE(ldp >= (int64_t)heads * F && ldz >= (int64_t)heads * F, "%s: row stride smaller than the row", who);
     GAS_REQUIRE(Z != P, "%s: the output must not alias the input", who);
     GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL, "%s: too many rows for one launch", who);
-    GAS_REQUIRE(!push_idx || (push_hist && push_hist != Z && ld_push >= (int64_t)heads * F && n_hist_rows > 0),
+    GAS_REQUIRE(!push_idx || (push_hist && push_hist != Z && push_hist != P && ld_push >= (int64_t)heads * F && n_hist_rows > 0),
                 "%s: bad history table for the push", who);
     GatArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;

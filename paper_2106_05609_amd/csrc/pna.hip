@@ -318,7 +318,7 @@ extern "C" gas_status gas_pna_aggregate_own(const int32_t* rowptr, const int32_t
     GAS_REQUIRE(ldx >= F && ldout >= blocks * (int64_t)F && (!add || ldadd >= F), "gas_pna_aggregate: row stride smaller than the row");
     GAS_REQUIRE(out != X && out != add, "gas_pna_aggregate: the output must not alias an input");
     GAS_REQUIRE(n_rows <= 0x7FFFFFFFLL, "gas_pna_aggregate: too many rows for one launch");
-    GAS_REQUIRE(!own || (own_to && own_to != own && F_own > 0 && ld_own >= F_own && ld_own_to >= F_own),
+    GAS_REQUIRE(!own || (own_to && own_to != own && own_to != X && own_to != add && own_to != out && F_own > 0 && ld_own >= F_own && ld_own_to >= F_own),
                 "gas_pna_aggregate: bad target for the own rows");
     PnaArgs a;
     a.rowptr = rowptr; a.col = col; a.n_rows = n_rows;

@@ -106,4 +106,12 @@ def test_targets_that_do_not_fit_are_refused():
     for own, to in ((x, None), (None, z), (x, z[:, :8]), (x[:5], z), (x.bfloat16(), z)):
         with pytest.raises(ValueError):
             gas.gas_pna_aggregate(ptr, col, x, out, 1.0, own=own, own_to=to)
+    # rows that are stored while others still read them, or over what the same call writes
+    for table in (x, z):
+        with pytest.raises(gas.GasError):
+            gas.gas_gat_aggregate(ptr, col, x, x[0], x[0], z, idx=idx, hist=table)
+    add, own = torch.zeros(70, 16, device="cuda"), torch.ones(70, 16, device="cuda")
+    for to in (x, add, own, out[:, :16]):
+        with pytest.raises(gas.GasError):
+            gas.gas_pna_aggregate(ptr, col, x, out, 1.0, add=add, own=own, own_to=to)
     assert to_np(out).max() == 0
