@@ -2234,13 +2234,20 @@ static gas_status run_linear(const char* who, const void* Z, int64_t ldz, int64_
     // 500 rows 256 -> 256 in 64 x 64 7.2 us (128 x 256, one wavefront a unit, 20.1), 1,024 inputs 19.8 and 31.5, 16,000 rows 11.2
     // and with the weights in place 16.9, 50,000 33.0 and 27.3; the masked input gradient, which starts sooner because its weights
     // take no turning, 6,000 rows 6.6 and 8.8, 16,000 9.7 and 9.6.  Up to 64 columns six wavefronts of eight would hold no
-    // weights: 50,000 rows 256 -> 64 11.2 and 21.6, 300,000 49 and 56 (with a Push, a copy of 19 us after tiles, not).  Wider than the weights-stationary kernel takes: 128 x
-    // 128 once small tiles fill the chip (100,000 rows 512 -> 256 98 and 89), but not transposed (90 and 98).
+    // weights: 50,000 rows 256 -> 64 11.2 and 21.6, 300,000 49 and 56.  Wider than the weights-stationary kernel takes: 128 x 128 once small tiles
+    // fill the chip (100,000 rows 512 -> 256 98 and 89), but not transposed (90 and 98).
+    // With a Push, which that kernel stores itself and a copy of the rows, 3 to 19 us, follows tiles for: up to 128 inputs it starts soon and
+    // takes all but the few rows whose tiles are fewest (4,096 rows 128 -> 128 9.9 and 9.6, 9,000 10.4 and 11.3, 16,000 10.6 and 11.7, 128 ->
+    // 256 3,000 10.2 both, 9,000 11.1 and 12.5, 16,000 11.8 and 13.7); up to 64 columns tiles only between (128 -> 48 16,000 10.1 and 11.2,
+    // 40,000 15.0 and 13.7, 64 -> 64 3,000 7.0 and 9.1, 40,000 11.5 and 12.0).  With more inputs the line stays (256 -> 256 16,000 18.1
+    // and 17.1, 24,000 20.9 and 25.4; 256 -> 64 64,000 24.4 and 21.6, 300,000 62 and 77).
     const bool ws = F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
         (!mask || (aligned16(mask) && ldmask % 8 == 0)) && ldz < (1 << 24) && ldy < (1 << 24) && ldmask < (1 << 24);
-    const bool small = (F_out <= 64 && !(ws && push.idx)) || (!ws && trans_w) || (n_rows + 63) / 64 * ((F_out + 63) / 64) <= (trans_w ? 512 : 1024);
+    const bool scatter = ws && push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
+    const int64_t tiles = (n_rows + 63) / 64 * ((F_out + 63) / 64);
+    const bool small = !scatter || F_in > 128 ? (F_out <= 64 && !scatter) || (!ws && trans_w) || tiles <= (trans_w ? 512 : 1024)
+                                              : F_in > 64 && (F_out <= 64 ? tiles > 320 && tiles <= 1024 : tiles <= 192);
     if (ws && !small) {
-        const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
         w.Z = static_cast<const uint16_t*>(Z); w.ldz = ldz;
         w.W1 = static_cast<const uint16_t*>(W); w.b1 = static_cast<const uint16_t*>(bias);
