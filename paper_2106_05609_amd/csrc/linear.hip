@@ -2533,11 +2533,19 @@ static gas_status run_mlp2(const void* Z, int64_t ldz, int64_t n_rows, int32_t F
     const int q = dt == GAS_F32 ? 4 : 8;    // elements per 16 bytes
     const bool vec = aligned16(Z) && aligned16(W1) && aligned16(W2) && ldz % q == 0 && F_in % q == 0 &&
                      F_hid % q == 0 && F_out % q == 0;
-    // The fused kernel holds both weight matrices in registers: for a narrow hidden layer most wavefronts hold nothing.  Hidden 64
-    // wide: two products 8.1 us, fused 10.1 (2,000 rows), 300,000 48 and 72; without a place for the hidden rows the tiled kernel 8.5
-    // and 9.7, at 60,000 20.7 and 19.2.  128 wide: 10,000 rows 10.9 and 11.1, 60,000 27.3 and 21.7.  256 wide: 500 rows 14.5 and 14.2
-    // (tiled 20.8), 30,000 39.7 and 20.7.
-    const bool fused = H_out ? F_hid > 64 && (F_hid > 128 || n_rows > 16000) : F_hid > 64 || n_rows > 30000;
+    // The fused kernel holds both weight matrices in registers: for a narrow hidden layer most wavefronts hold nothing.  us, two products
+    // (without a place for the hidden rows the tiled kernel) and fused:
+    // - with that place, hidden 64 wide: 2,000 rows 8.1 and 10.1, 300,000 48 and 72, from 256 inputs 50,000 21.6 and 26.0, 150,000 52.2 and 49.9;
+    //   128 wide: 4,096 rows 10.7 and 11.0, 6,000 11.7 and 11.3, 12,000 13.3 and 11.7; 256 wide: 500 rows 14.5 and 14.2, 30,000 39.7 and 20.7;
+    // - without it, hidden 64 wide: 4,096 rows 8.7 and 10.1, 24,000 11.4 and 13.6, 60,000 20.7 and 19.2, from 256 inputs 1,000 14.0 and 12.6, 24,000
+    //   19.5 and 17.9; 256 wide: 500 rows 20.8 and 14.2.
+    // A Push, which the fused kernel stores itself, has a copy of the rows after the others: with the place, hidden 64 wide, 500 rows 12.2 and
+    // 10.7, 24,000 15.4 and 15.1, 40,000 17.8 and 18.8, from 256 inputs 500 15.1 and 13.5, 64,000 30.4 and 27.9; 128 wide 4,096 14.7 and 11.7; without it,
+    // hidden 64 wide, 500 rows 12.1 and 10.1, 64,000 26.9 and 21.4.
+    const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
+    const bool fused = F_hid > 128 || (scatter ? !H_out || F_hid > 64 || F_in > 64 || n_rows <= 30000
+                                       : H_out ? F_hid > 64 ? n_rows > 5000 : F_in > 128 && n_rows > 100000
+                                               : F_hid > 64 || F_in > 128 || n_rows > 30000);
     const bool ws_path = dt == GAS_BF16 && vec && fused && F_in <= 256 && F_out <= 256 && aligned16(Y) && ldy % 8 == 0 &&
                          ldz < (1 << 24) && ldy < (1 << 24) &&             // offsets inside a 64-row tile are 32-bit
                          (!H_out || (aligned16(H_out) && ldh_out % 8 == 0 && ldh_out < (1 << 24)));
@@ -2564,7 +2572,6 @@ static gas_status run_mlp2(const void* Z, int64_t ldz, int64_t n_rows, int32_t F
         else hipLaunchKernelGGL(mlp2_f32_kernel<false>, grid, dim3(256), smem, s, a);
     } else if (ws_path) {
         // the kernel scatters the rows itself if the history rows take 16-byte stores; else the row copy follows
-        const bool scatter = push.idx && aligned16(push.hist) && push.ld_hist % 8 == 0;
         WsArgs w{};
         w.Z = static_cast<const uint16_t*>(Z); w.ldz = ldz;
         w.W1 = static_cast<const uint16_t*>(W1); w.b1 = static_cast<const uint16_t*>(b1);
