@@ -32,7 +32,8 @@ def plan_limits(rows, entries, longest):
     walks a light row's entries, 0.1 us each, and a launch waits for the longest; a chunk's partial sum is written and read
     again, and any heavy row adds two launches.  So the line follows the batch: 256 entries where the whole takes half a
     millisecond and more, 64 where it takes 20 to 200 us, but no less than twice the mean (rows of like lengths hide each other's
-    walks), and none where the longest row is hardly longer than that or its walk is short beside the launch.  us, rows above
+    walks), and none where the longest row is hardly longer than that or its walk is short beside the launch.  Many rows hide a
+    walk: from 131,072 rows of a middling batch 256, and from 262,144 the plan's own 512 and 256.  us, rows above
     512 by 256 entries and so, aggregations of power-law batches (and their adjoints), 256 floats, 64 floats, 256 bf16:
     - 250,000 rows of 40: 1,223 -> 1,192 (565 -> 553), 459 -> 417 (259 -> 245), 704 -> 659 (329 -> 321);
     - 15,000 rows of 43: 143 -> 83 (53 -> 41), 105 -> 43 (60 -> 33), 125 -> 53 (59 -> 38);
@@ -40,13 +41,19 @@ def plan_limits(rows, entries, longest):
     - 25,000 rows of 18, the longest 141: whole 64, with 64 the line 75.
     Forward passes of two layers, 240 bf16, line and chunk: 37,000 rows of 47, whole rows 378, 256 and 128 304, 128 and 128 290, 64
     and 64 284; 100,000 rows of 43 756, 674, 654, 657; 350,000 rows of 68 2,915, 2,914, 2,917, 2,984; 117,000 rows of 17, the longest
-    290, 414, 448, 446, 431."""
+    290, 414, 448, 446, 431.  Of three layers, 256 bf16 (256 floats), 128 and 64, 256 and 128, 512 and 256: 293,000 rows of 15 1,185, 1,160, 1,185
+    (2,325, 2,299, 2,320), of 23 1,604, 1,555, 1,529 (3,092, 3,090, 3,083), of 31 1,980, 1,904, 1,852 (3,706, 3,696, 3,710), 391,000 rows of 20
+    1,901, 1,853, 1,824; 195,000 rows of 26 1,276, 1,224, 1,239 (2,373, 2,369, 2,382), of 36 1,570, 1,500, 1,506 (2,837, 2,822, 2,891); 146,000
+    of 28 1,018, 978, 1,039 (1,852, 1,851, 1,910); 98,000 of 45 1,055, 1,017, 1,038 (1,831, 1,840, 1,886)."""
     if rows == 0:
         return None
-    line = min(512, max(256 if entries >= 10_000_000 else 128 if entries >= 3_000_000 else 64, -(-2 * entries // rows)))
+    size, chunk = (256, 128) if entries >= 10_000_000 else (128, 64) if entries >= 3_000_000 else (64, 64 if entries >= 200_000 else 32)
+    if 3_000_000 <= entries < 10_000_000 and rows >= 131_072:
+        size, chunk = (512, 256) if rows >= 262_144 else (256, 128)
+    line = min(512, max(size, -(-2 * entries // rows)))
     if longest <= min(512, line + 144 + entries // 6000):
         return None
-    return dict(heavy_threshold=line, chunk=128 if entries >= 10_000_000 else 64 if entries >= 200_000 else 32)
+    return dict(heavy_threshold=line, chunk=chunk)
 
 
 class BatchGraph:

@@ -13,6 +13,13 @@ from paper_2106_05609_amd.executor import plan_limits
     (100_000, 4_311_623, 3_302, (128, 64)),
     (116_664, 1_979_499, 290, None),                     # a short walk beside the launch
     (600_000, 50_318_351, 17_482, (256, 128)),
+    (312_500, 6_869_018, 3_825, (512, 256)),             # many rows hide a long one's walk: the plan's own limits
+    (262_144, 3_000_000, 2_000, (512, 256)),
+    (262_143, 3_000_000, 2_000, (256, 128)),
+    (131_072, 9_999_999, 2_000, (256, 128)),
+    (131_071, 3_000_000, 2_000, (128, 64)),
+    (300_000, 2_999_999, 2_000, (64, 64)),
+    (300_000, 10_000_000, 2_000, (256, 128)),
     (4_000, 480_381, 152, None),                         # long rows of like lengths
     (1_000, 600_000, 5_000, (512, 64)),                  # no line above 512
     (1, 513, 513, (512, 32)),
