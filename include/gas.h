@@ -121,8 +121,8 @@ GAS_API gas_status gas_gcn_norm(const int32_t* ptr, const int32_t* ind, int64_t 
  * zero field = the default): rows with more than heavy_threshold entries
  * (512) are cut into chunks of at most `chunk` entries (256) that end at a
  * window boundary once they hold min_chunk entries (32); window_rows = rows of
- * the gathered table per window (default: 16 MiB worth of rows of max_F, at
- * most 256, floats, rounded down to a power of two; -1 = no windows); xcd_ranges: 0 = decide
+ * the gathered table per window (default: 2 MiB worth of rows of max_F floats,
+ * rounded down to a power of two; -1 = no windows); xcd_ranges: 0 = decide
  * from the pattern, 1 = always, 2 = never.  The parameters change which
  * wavefront sums what, never the set of terms: results agree to rounding
  * between parameter sets and are bit-identical for one set.

@@ -18,7 +18,7 @@
 //     reuse saves).  wshift < 0 turns windows off (chunks of `chunk` entries).
 //   * The chunks are processed in the order of their first entry's window (stable: chunks of one window keep their
 //     row-major order).  Workgroups take them four at a time and go to the XCDs in turn, so all eight XCDs walk
-//     the window sequence together and gather from the same part of it.  (Giving each XCD a range of windows
+//     the window sequence together, and one of the default size fits every L2.  (Giving each XCD a range of windows
 //     of its own fetches each source row into one L2 only, but the XCDs that get the sparse tail then wait on
 //     their own eighth of the fabric while the others sit idle: measured slower.)  The partial sums keep their
 //     row-major slots, so the order in which a row's partials are added does not depend on the processing order.
@@ -37,7 +37,7 @@ struct PlanParams {
     int32_t threshold = 512;
     int32_t chunk = 256;
     int32_t min_chunk = 32;
-    int32_t wshift = 14;        // 16384 rows per window; < 0: no windows
+    int32_t wshift = 11;        // 2048 rows per window; < 0: no windows
     int32_t xcd_mode = 0;       // 0 decide from the pattern, 1 always, 2 never
     int32_t group_block = 1024;
 };
@@ -56,13 +56,10 @@ static inline int64_t plan_window(int32_t v, int wshift) {
     return wshift < 0 ? 0 : ((plan_mag(v) >> wshift) << 1) | (v < 0 ? 1 : 0);
 }
 
-// Default window: 16 MiB of rows of max_F floats, as a power of two; of 256 floats where max_F is more (a wide input layer's
-// plan serves the layers behind it too).  Four L2s' worth: the gathers of the running chunks stay within a part of a window as
-// they go through it together, and a smaller one cuts more chunks, whose partial sums cost more than the reuse saves.
-// us with 2 MiB and with 16: 600,000 rows of 84 entries, 10,600 of them heavy, 256 floats 5,041 and 5,060, 184 floats 4,314 and 4,235,
-// 256 bf16 3,132 and 2,992, 136 bf16 2,477 and 2,337; 150,000 rows of 69 1,035 and 1,058, 890 and 871, 661 and 616, 515 and 479.
+// Default window: 2 MiB of rows of max_F floats (half of one XCD's L2), as a power of two.  What it costs and gains beside a larger one
+// depends on the rows' type, which a plan doesn't know; who makes plans for a batch may set window_rows.
 static inline int32_t plan_default_wshift(int32_t max_F) {
-    int64_t rows = (16ll << 20) / (std::min<int64_t>(max_F, 256) * 4);
+    int64_t rows = (2ll << 20) / ((int64_t)max_F * 4);
     int32_t s = 0;
     while ((2ll << s) <= rows) ++s;
     return s < 6 ? 6 : (s > 20 ? 20 : s);

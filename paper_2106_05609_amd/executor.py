@@ -56,6 +56,17 @@ def plan_limits(rows, entries, longest):
     return dict(heavy_threshold=line, chunk=chunk)
 
 
+def _windowed(limits, max_F):
+    """plan_limits with windows of 16 MiB of rows of max_F, at most 256 (a wide input layer's plan serves the layers behind it too), floats
+    where chunks are short: a window of the plan's own 2 MiB cuts more of them, whose partial sums cost more than the reuse
+    saves.  us of three layers forward with 2 and with 16 MiB, 256 bf16 (256 floats): 600,000 rows of 83 8,800 and 8,471 (13,793 and
+    13,846), 200,000 of 86 3,222 and 3,114 (5,173 and 5,153), 117,000 of 109 2,483 and 2,392 (3,920 and 3,890), 37,500 of 190 1,320
+    and 1,264 (1,815 and 1,854)."""
+    if limits is None or limits["chunk"] > 128:
+        return limits
+    return dict(limits, window_rows=min(1 << 20, (16 << 20) // (4 * min(max_F, 256))))
+
+
 class BatchGraph:
     """Device-side index structure of one batch subgraph plus its plans."""
 
@@ -81,7 +92,7 @@ class BatchGraph:
         self.nnz = int(col.numel())
         self.max_row = int((rowptr[1:] - rowptr[:-1]).max().item()) if self.nb > 0 else 0
         self.plan = part("plan_csr", lambda: B.gas_plan_create(rowptr, self.nnz, max_F, ind=col,
-                                                               options=plan_options or plan_limits(self.nb, self.nnz, self.max_row)))
+                                                               options=plan_options or _windowed(plan_limits(self.nb, self.nnz, self.max_row), max_F)))
         self.val = None
         if normalise:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
@@ -98,7 +109,7 @@ class BatchGraph:
                 longest = (colptr[1:self.nb + 1] - colptr[:self.nb]).max()
                 self.max_col, self.nnz_t = torch.stack((longest, colptr[self.nb])).tolist()    # one read-back
             self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], self.nnz_t, max_F, n_rows=self.nb, ind=row,
-                                                                     options=plan_options or plan_limits(self.nb, self.nnz_t, self.max_col)))
+                                                                     options=plan_options or _windowed(plan_limits(self.nb, self.nnz_t, self.max_col), max_F)))
             if normalise:
                 self.val_t = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
                 part("gcn_norm_csc", lambda: B.gas_gcn_norm(colptr, row, n_id, deg, self.val_t))
@@ -113,7 +124,7 @@ class BatchGraph:
         if self._plan_t_all is None:
             self._max_col_all = int((self.colptr[1:] - self.colptr[:-1]).max().item()) if self.nv > 0 else 0
             self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row,
-                                                 options=plan_limits(self.nv, self.nnz, self._max_col_all))
+                                                 options=_windowed(plan_limits(self.nv, self.nnz, self._max_col_all), self._max_F))
         return self._plan_t_all
 
     @property

@@ -99,3 +99,15 @@ def test_both_builders_give_the_same_aggregation_bits(gas):
         gas.gas_spmm(plan, d(sg.rowptr), d(sg.col), None, x, zt)
         out.append(to_np(zt))
     assert np.array_equal(out[0].view(np.uint8), out[1].view(np.uint8))
+
+
+@pytest.mark.parametrize("max_F,rows", [(256, 2048), (64, 8192), (100, 4096), (1433, 256), (1, 1 << 19)])
+def test_default_window_is_two_mebibytes_of_rows(gas, max_F, rows):
+    """Without options a plan's chunks end where windows of 2 MiB of rows of max_F floats do (a power of two of them)."""
+    step = max(1, rows // 70)                                 # some 70 entries a window: 32 make a chunk, 256 are the most
+    ind = (torch.arange(6000, dtype=torch.int32) * step).cuda()
+    ptr = torch.tensor([0, 6000], dtype=torch.int32, device="cuda")
+    chunks = [gas.gas_plan_create(ptr, 6000, max_F, ind=ind, options=o).lists()[2]
+              for o in (None, dict(window_rows=rows), dict(window_rows=2 * rows), dict(window_rows=rows // 2))]
+    assert np.array_equal(chunks[0], chunks[1])
+    assert not np.array_equal(chunks[0], chunks[2]) and not np.array_equal(chunks[0], chunks[3])

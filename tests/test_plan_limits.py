@@ -1,7 +1,7 @@
 """The lines between light and heavy rows that a batch's plans are made with (executor.plan_limits)."""
 import pytest
 
-from paper_2106_05609_amd.executor import plan_limits
+from paper_2106_05609_amd.executor import _windowed, plan_limits
 
 
 @pytest.mark.parametrize("rows,entries,longest,want", [
@@ -34,3 +34,10 @@ def test_rows_above_512_are_always_cut():
         for mean in (1, 30, 400, 2_000):
             got = plan_limits(rows, rows * mean, max(513, mean))
             assert got is not None and got["heavy_threshold"] <= 512 and got["chunk"] <= 128
+
+
+@pytest.mark.parametrize("max_F,rows", [(256, 16384), (1433, 16384), (184, 22795), (64, 65536), (1, 1 << 20)])
+def test_windows_of_short_chunks(max_F, rows):
+    assert _windowed(None, max_F) is None
+    assert _windowed(dict(heavy_threshold=512, chunk=256), max_F) == dict(heavy_threshold=512, chunk=256)
+    assert _windowed(dict(heavy_threshold=256, chunk=128), max_F) == dict(heavy_threshold=256, chunk=128, window_rows=rows)
