@@ -804,7 +804,8 @@ gas_status launch_slices(const SpmmArgs& a, bool whole, hipStream_t s) {
     if (blocks > 0x7FFFFFFFLL) return fail(GAS_ERR_ARG, "gas_spmm: too many workgroups for one launch");
     const dim3 grid((unsigned)blocks), block(256);
     // As many partial sums a row as a wavefront's teams make of it in the other form: eight up to 8 units, four up to 16, two up to 32, one
-    // beyond and for 32 whole units, which a wavefront takes at once there.  Root mean square error against 64 bits, 21 entries: in one
+    // beyond and for 32 whole units, which a wavefront takes at once there, and so 16 whole ones of bf16 that are rounded to bf16 again (a few
+    // values of a batch come out otherwise in four, and moved the gradients of a training step by up to 5e-4).  Root mean square error against 64 bits, 21 entries: in one
     // sum 8.5e-8, in two 6.7e-8; 60: in one 1.4e-7, in two 1.0e-7, in four 8.1e-8, in eight 7.0e-8.  Eight are four in each half of a team,
     // which takes every other entry: no lane is idle at 8 units (us, eight in each lane and so: 200,000 clustered rows of 9 entries, 32 floats
     // 44.5 -> 30.1, 64 bf16 62.6 -> 37.9; 257,000 power-law rows of 19 103.6 -> 86.0, 139.0 -> 103.1; four in each lane 37.1 to 111.5).
@@ -816,6 +817,7 @@ gas_status launch_slices(const SpmmArgs& a, bool whole, hipStream_t s) {
     const bool two = a.units < 32 || (a.units == 32 && !whole);
     if constexpr (P == 1) {
         if (a.units <= 8) launch(std::integral_constant<int, 8>());
+        else if (XBF && ZBF && a.units == 16 && whole) launch(std::integral_constant<int, 1>());
         else if (a.units <= 16) launch(std::integral_constant<int, 4>());
         else if (two) launch(std::integral_constant<int, 2>());
         else launch(std::integral_constant<int, 1>());

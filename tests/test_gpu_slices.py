@@ -160,3 +160,25 @@ def test_partial_sums_of_a_row(gas, n, dtype, F, offset, parts):
     assert np.array_equal(z.cpu().numpy(), _in_parts(host, ptr, col, parts))
     if parts > 1:
         assert not np.array_equal(z.cpu().numpy(), _in_parts(host, ptr, col, parts // 2))
+
+
+@pytest.mark.parametrize("F,offset,parts", [(128, 0, 1), (128, 1, 4), (120, 0, 4), (136, 0, 2)])
+def test_rows_of_128_bf16_to_bf16_are_summed_in_order(gas, F, offset, parts):
+    """Whole ones in one sum, as where a wavefront takes a row at once: a row's first entry is 2^18 times the others and its last takes
+    it away again, so that the order shows through the rounding to bf16."""
+    n = 3000
+    ptr, r = _pattern(n, 12, 77, longest=200)
+    gen = torch.Generator(device="cuda").manual_seed(F + offset)
+    x = torch.randn(n, F + offset if offset else (F + 7) // 8 * 8, generator=gen, device="cuda")
+    x[:100] *= 2.0 ** 18
+    x[100:200] = -x[:100]
+    x = x.to(torch.bfloat16)[:, offset:offset + F]
+    col, ends = r.integers(200, n, int(ptr[-1])).astype(np.int32), ptr.cpu().numpy()
+    rows = np.flatnonzero(np.diff(ends) > 1)
+    col[ends[rows]], col[ends[rows + 1] - 1] = rows % 100, 100 + rows % 100
+    col = torch.from_numpy(col).cuda()
+    z = torch.empty(n, F, dtype=torch.bfloat16, device="cuda")
+    gas.gas_spmm(gas.gas_plan_create(ptr, int(ptr[-1]), F, ind=col, options=dict(xcd_ranges=1)), ptr, col, None, x, z)
+    want = {k: torch.from_numpy(_in_parts(x.float().cpu().numpy(), ptr, col, k)).to(torch.bfloat16) for k in (1, 2, 4)}
+    assert torch.equal(z.cpu(), want[parts])
+    assert all(not torch.equal(want[parts], w) for k, w in want.items() if k != parts)
