@@ -73,7 +73,9 @@ class BatchGraph:
     def __init__(self, nb, n_id, rowptr, col, deg=None, colptr=None, row=None, max_F=256, normalise=True, timed=False,
                  plan_options=None, csc_pos=None):
         """timed: wait for the device after each part of the per-batch set-up and keep its wall time in
-        self.setup_ms (plans, coefficients, fused source indices); the benchmark reports it."""
+        self.setup_ms (plans, coefficients, fused source indices); the benchmark reports it.
+        plan_options: of all of the batch's plans (gas_plan_options).  A dict is taken as it is: a field that it doesn't
+        name, and all of them in an empty one, has the library's default.  None: what suits the batch (plan_limits)."""
         import time
         self.setup_ms = {}
 
@@ -87,12 +89,13 @@ class BatchGraph:
             self.setup_ms[name] = round((time.perf_counter() - t0) * 1e3, 3)
             return out
 
+        self._max_F, self._plan_options = max_F, plan_options
         self.nb, self.nv = int(nb), int(n_id.numel())
         self.n_id, self.rowptr, self.col = n_id, rowptr, col
         self.nnz = int(col.numel())
         self.max_row = int((rowptr[1:] - rowptr[:-1]).max().item()) if self.nb > 0 else 0
         self.plan = part("plan_csr", lambda: B.gas_plan_create(rowptr, self.nnz, max_F, ind=col,
-                                                               options=plan_options or _windowed(plan_limits(self.nb, self.nnz, self.max_row), max_F)))
+                                                               options=self._options(self.nb, self.nnz, self.max_row)))
         self.val = None
         if normalise:
             self.val = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
@@ -100,7 +103,7 @@ class BatchGraph:
         self._src = self._src_first = self._groups = None
         self.csc_pos = csc_pos       # int32[nnz]: position of every CSC entry in the CSR arrays (PNA / GAT backward)
         self._n_id_host = None
-        self._plan_t_all, self._max_F = None, max_F
+        self._plan_t_all = None
         self.colptr, self.row, self.val_t, self.plan_t = colptr, row, None, None
         self.nnz_t, self.max_col = 0, 0          # entries of the in-batch columns, and of the longest of them
         if colptr is not None:
@@ -109,13 +112,18 @@ class BatchGraph:
                 longest = (colptr[1:self.nb + 1] - colptr[:self.nb]).max()
                 self.max_col, self.nnz_t = torch.stack((longest, colptr[self.nb])).tolist()    # one read-back
             self.plan_t = part("plan_csc", lambda: B.gas_plan_create(colptr[: self.nb + 1], self.nnz_t, max_F, n_rows=self.nb, ind=row,
-                                                                     options=plan_options or _windowed(plan_limits(self.nb, self.nnz_t, self.max_col), max_F)))
+                                                                     options=self._options(self.nb, self.nnz_t, self.max_col)))
             if normalise:
                 self.val_t = torch.empty(self.nnz, dtype=torch.float32, device=col.device)
                 part("gcn_norm_csc", lambda: B.gas_gcn_norm(colptr, row, n_id, deg, self.val_t))
         if timed:
             part("fuse_sources", lambda: self.src)
             self.setup_ms["total"] = round(sum(self.setup_ms.values()), 3)
+
+    def _options(self, rows, entries, longest):
+        if self._plan_options is not None:
+            return self._plan_options
+        return _windowed(plan_limits(rows, entries, longest), self._max_F)
 
     @property
     def plan_t_all(self):
@@ -124,7 +132,7 @@ class BatchGraph:
         if self._plan_t_all is None:
             self._max_col_all = int((self.colptr[1:] - self.colptr[:-1]).max().item()) if self.nv > 0 else 0
             self._plan_t_all = B.gas_plan_create(self.colptr, self.nnz, self._max_F, ind=self.row,
-                                                 options=_windowed(plan_limits(self.nv, self.nnz, self._max_col_all), self._max_F))
+                                                 options=self._options(self.nv, self.nnz, self._max_col_all))
         return self._plan_t_all
 
     @property

@@ -1,5 +1,6 @@
 """The lines between light and heavy rows that a batch's plans are made with (executor.plan_limits)."""
 import pytest
+import torch
 
 from paper_2106_05609_amd.executor import _windowed, plan_limits
 
@@ -41,3 +42,20 @@ def test_windows_of_short_chunks(max_F, rows):
     assert _windowed(None, max_F) is None
     assert _windowed(dict(heavy_threshold=512, chunk=256), max_F) == dict(heavy_threshold=512, chunk=256)
     assert _windowed(dict(heavy_threshold=256, chunk=128), max_F) == dict(heavy_threshold=256, chunk=128, window_rows=rows)
+
+
+@pytest.mark.parametrize("given", [None, {}, dict(xcd_ranges=2)])
+def test_options_of_a_batch_are_all_or_none(given, monkeypatch):
+    """A caller's options reach each of the batch's plans as they are, an empty dict too; without any the limits do."""
+    from paper_2106_05609_amd import executor
+    nb, nv = 3, 5
+    rowptr = torch.tensor([0, 600, 601, 602], dtype=torch.int32)             # columns 0 and 4 of 300 and 301 entries
+    col = torch.cat([torch.zeros(300), torch.full((300,), 4), torch.tensor([1, 4])]).int()
+    colptr, row = torch.tensor([0, 300, 301, 301, 301, 602], dtype=torch.int32), torch.zeros(602, dtype=torch.int32)
+    seen = []
+    monkeypatch.setattr(executor.B, "gas_plan_create", lambda *a, options=None, **k: seen.append(options))
+    bg = executor.BatchGraph(nb, torch.arange(nv).int(), rowptr, col, None, colptr, row, max_F=256, normalise=False, plan_options=given)
+    bg.plan_t_all
+    limits = [_windowed(plan_limits(*p), 256) for p in ((3, 602, 600), (3, 301, 300), (5, 602, 301))]
+    assert limits[0] is not None
+    assert seen == (limits if given is None else [given] * 3)
