@@ -23,9 +23,18 @@ def stale() -> bool:
     return any(os.path.getmtime(f) > t for f in SOURCES + HEADERS) or _marshal_stale()
 
 
+def built_for() -> str:
+    """What _marshal.so is compiled against, beside its sources: it reads torch's tensors by their layout in memory."""
+    import torch
+    return f"torch {torch.__version__}, C++ ABI {int(torch._C._GLIBCXX_USE_CXX11_ABI)}, {sysconfig.get_config_var('SOABI')}"
+
+
 def _marshal_stale() -> bool:
-    return not os.path.exists(MARSHAL) or any(os.path.getmtime(f) > os.path.getmtime(MARSHAL)
-                                              for f in (MARSHAL_SOURCE, os.path.join(ROOT, "include", "gas.h")))
+    if not os.path.exists(MARSHAL) or any(os.path.getmtime(f) > os.path.getmtime(MARSHAL)
+                                          for f in (MARSHAL_SOURCE, os.path.join(ROOT, "include", "gas.h"))):
+        return True
+    with open(MARSHAL, "rb") as f:
+        return built_for().encode() + b"\0" not in f.read()          # the module's own string, without importing it
 
 
 def _marshal_commands(obj):
@@ -33,6 +42,7 @@ def _marshal_commands(obj):
     import torch
     from torch.utils import cpp_extension
     compile_ = ["g++", "-O2", "-std=c++17", "-fPIC", "-fvisibility=hidden", f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+                f'-DGAS_BUILT_FOR="{built_for()}"',
                 "-I" + os.path.join(ROOT, "include"), "-I" + sysconfig.get_paths()["include"]]
     for d in cpp_extension.include_paths():
         compile_ += ["-isystem", d]

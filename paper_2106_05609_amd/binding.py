@@ -4,6 +4,7 @@ runs in the library's kernels on torch's current stream.  The calls of a pass go
 through csrc/marshal.cpp, the others through ctypes."""
 import ctypes as C
 import os
+import warnings
 
 import torch
 
@@ -96,6 +97,29 @@ _SIGNATURES = dict(
 )
 
 
+def _marshalling():
+    """The marshalling module; None, with a warning, if it can't be loaded or was built for another torch or interpreter."""
+    from . import _build
+    try:
+        from . import _marshal
+        if getattr(_marshal, "built_for", None) != _build.built_for():
+            raise ImportError(f"_marshal.so was built for {getattr(_marshal, 'built_for', None)}, this is {_build.built_for()}")
+        return _marshal
+    except ImportError as e:
+        warnings.warn("every call goes through ctypes, which takes 3 to 11 us longer: build again with "
+                      f"`python -m paper_2106_05609_amd._build` ({e})", RuntimeWarning, stacklevel=2)
+        return None
+
+
+def _by_ctypes(fn):
+    def call(*args):
+        try:
+            return fn(*args)
+        except C.ArgumentError as e:                     # a type that no call takes
+            raise TypeError(str(e)) from None
+    return call
+
+
 class _Calls:
     """The library's functions with their argument types declared: plain Python numbers are converted by ctypes itself, and those
     of a pass by the marshalling module (30 arguments: 0.4 us, ctypes 3).  A handle of its own: what lib() returns takes
@@ -104,16 +128,19 @@ class _Calls:
     def __init__(self):
         global _mat, _size, _ptr
         lib()
-        from . import _marshal
-        _marshal.set_slow(_mat_any, _size_any, _ptr_any)
-        _mat, _size, _ptr = _marshal.mat, _marshal.size, _marshal.ptr
+        native = _marshalling()
+        if native is None:
+            _mat, _size, _ptr = _mat_any, _size_any, _ptr_any
+        else:
+            native.set_slow(_mat_any, _size_any, _ptr_any)
+            _mat, _size, _ptr = native.mat, native.size, native.ptr
         raw = C.CDLL(LIB_PATH)
         types = dict(p=C.c_void_p, q=C.c_int64, i=C.c_int32, f=C.c_float)
         for name, sig in _SIGNATURES.items():
             fn = getattr(raw, name)
             fn.argtypes = [types[c] for c in sig]
             fn.restype = C.c_int64 if name.endswith("_workspace") else C.c_int
-            setattr(self, name, getattr(_marshal, name, fn))
+            setattr(self, name, _by_ctypes(fn) if native is None else getattr(native, name, fn))
 
 
 _typed = None
