@@ -308,7 +308,7 @@ def main():
         "hbm_pull_spmm_push": hbm,
         "kernels": hm["kernels"],
         "roofline": {"kernel": ("gas_spmm_hist" if fused_head else "gas_spmm")
-                               + " = spmm_chunk_kernel + spmm_heavy_reduce_kernel + spmm_rows_kernel", "bound": "hbm",
+                               + " = spmm_chunk_kernel + spmm_heavy_reduce_kernel + spmm_slices_kernel", "bound": "hbm",
                      "achieved": round(spmm_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(spmm_gbs / HBM_PEAK_GBS, 4),
                      # what this machine reaches for a plain device copy, timed in this run, and the same call against it

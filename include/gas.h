@@ -105,7 +105,7 @@ GAS_API gas_status gas_gcn_norm(const int32_t* ptr, const int32_t* ind, int64_t 
  * and every epoch; one plan for the CSR, one for the CSC copy.  ptr is a device
  * pointer (int32[n_rows+1]); ind (device, int32[nnz], each row ascending) may
  * be NULL; when given it is used to cut and order the chunks of heavy rows by
- * L2-sized windows of the rows they gather, and to see whether the pattern is clustered (most entries of a row
+ * windows of the rows they gather (half of an L2 by default), and to see whether the pattern is clustered (most entries of a row
  * name rows near it, as in a batch of partition clusters): then each of the
  * eight XCDs is given one contiguous range of light rows, so a cluster is
  * gathered into one L2 instead of eight.  Either the local column ids or the

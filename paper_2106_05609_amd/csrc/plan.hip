@@ -1,6 +1,6 @@
 // gas_plan_create: the schedule of one compressed sparse pattern, built on the device.
 //
-// plan_host.h defines the plan (groups of light rows, chunks of heavy rows cut and ordered by L2-sized windows, the
+// plan_host.h defines the plan (groups of light rows, chunks of heavy rows cut and ordered by windows of the rows they gather, the
 // ranges of groups per XCD and the locality vote).  Here the same arrays are produced by kernels from the row
 // pointers and indices where they lie, in device memory: only a handful of counters cross to the host (two waits),
 // so building a plan costs a few passes over the indices of the heavy rows instead of a copy of all indices to the

@@ -18,8 +18,9 @@
 // one wavefront per chunk (spmm_chunk_kernel), whose fp32 partial sums go to a
 // workspace and are added in a fixed order by spmm_heavy_reduce_kernel; the
 // light rows follow in spmm_rows_kernel.  The chunks are cut and ordered by
-// L2-sized windows of the source rows (plan_host.h states the rules), so that
-// wavefronts running together gather from rows that fit the L2 of every XCD.
+// windows of the source rows (plan_host.h states the rules; half an L2 unless
+// the plan's maker asks for others), so that wavefronts running together gather
+// from the same rows.
 // Light rows go by slices of a row instead (spmm_slices_kernel) where rows_form() says so.
 // The summation order is a
 // function of the plan alone, so results are bit-identical from run to run.
