@@ -291,7 +291,7 @@ GAS_API gas_status gas_mlp2_push(const void* Z, int64_t ldz, int64_t n_rows, int
  * The GIN update for a training pass: gas_mlp2_push (idx == NULL and hist == NULL: no Push) which also stores the
  * hidden activation relu(Z W1 + b1) to H_out [n_rows, F_hid] (type dt, row stride ldh_out): the backward pass reads
  * it (weight gradient of W2, ReLU mask).  Where the fused kernel is the faster one (bf16, widths up to 256, 16-byte
- * aligned rows, a hidden layer that is not narrow) the hidden tile is stored from LDS on its way; elsewhere the call
+ * aligned rows; a narrow hidden layer with a Push or many inputs) the hidden tile is stored from LDS on its way; elsewhere the call
  * runs as two stored linears.  H_out must not alias Z or Y.
  */
 GAS_API gas_status gas_mlp2_keep(const void* Z, int64_t ldz, int64_t n_rows, int32_t F_in,
